@@ -4,105 +4,90 @@
 //   TN  C[M,N] = A[K,M]^T B[K,N]     (weight gradients dW += dY^T X; K = chunk rows)
 //
 // Design (CDNA4):
-//  * 256x256 output tile per workgroup, 8 wavefronts (2 x 4), each wave owns a
-//    128x64 sub-tile = 4x2 v_mfma_f32_32x32x16_bf16 accumulators (128 registers).
-//  * Operand tiles (256 x 64 bf16 each) go HBM -> LDS with 128-bit direct-to-LDS
-//    loads (no VGPR staging), double-buffered: tile kt+1 streams in while tile kt
-//    is consumed; one barrier per K step.
+//  * 256x256 output tile per workgroup, 8 wavefronts in two groups of four that alternate between fetching and multiplying
+//    (gemm_tile below); accumulators are 32 v_mfma_f32_16x16x32_bf16 blocks per wave (128 registers).
+//  * Operand tiles (256 x 64 bf16 each) go HBM -> LDS with 128-bit direct-to-LDS loads (no VGPR staging), in halves of 128
+//    rows, up to 80 KB of them in flight.
 //  * K-contiguous operands are read from LDS with ds_read_b128; operands whose
 //    reduction index is the slow dimension in memory are kept in their natural
 //    [k][m|n] layout in LDS and fetched with the transposing LDS load
 //    (ds_read_b64_tr_b16), so no transposed copy ever exists in HBM.
-//  * The main loop contains no vector ALU instructions: a VALU instruction of one wave queues behind the MFMAs
-//    of the SIMD's other wave, so per-load address arithmetic would stretch the issue of a tile's loads
-//    several-fold.  Global addresses are an SGPR base (scalar adds per K step) + per-lane 32-bit offsets
-//    computed once; LDS fragment addresses are computed once per stage and reached with immediate offsets.
-//  * Both LDS layouts are XOR-swizzled (at 16-byte / 64-byte granularity) so that
+//  * Both LDS layouts are XOR-swizzled (at 16-byte / 32-byte granularity) so that
 //    the fragment reads are bank-conflict free; because a direct-to-LDS load
 //    writes lane-linear, the swizzle is applied on the global-address side.
 //  * Workgroups are renumbered so that each XCD (own L2) works on a contiguous
 //    band of output tiles that share operand panels.
 //  * Ragged M (last chunk) and ragged N (an output width that is a multiple of 8 but not of 256, e.g. a 151936-word
 //    vocabulary) are handled by clamping loads and masking stores;
-//    ragged K in the TN form (chunk rows) by clamping loads and zeroing the A
-//    fragments of the out-of-range reduction rows.
-//  * Optional split-K (a power of two, for outputs with too few tiles to fill the chip): partial tiles go to an
+//    ragged K (dW with a ragged chunk) by writing zeros instead of loading.
+//  * Output tiles leave through LDS, so that C is written (or read, added to and written) in whole rows, 16 bytes per lane.
+//  * Split-K for problems with too few output tiles to fill the chip: partial tiles go to
 //    fp32 scratch and a small kernel sums them in a fixed order (deterministic) into C; each K slice is pinned to
 //    its own group of XCDs.
-//  * Weight gradients: C += by no-return fp32 atomic adds (one add per element per launch), or into a bf16 C by
-//    paired loads / stores; several reduction segments (operand pairs) per output tile; grouped launches.
+//  * Weight gradients: C += acc, fp32 or bf16 C; several reduction segments (operand pairs) per output tile; grouped launches.
 #include "launch.h"
 #include "device.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace sbp {
 
 typedef bf16_t bf16x8 __attribute__((ext_vector_type(8)));
 typedef bf16_t bf16x4 __attribute__((ext_vector_type(4)));
 typedef short short4v __attribute__((ext_vector_type(4)));
+typedef short short8v __attribute__((ext_vector_type(8)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-#define LDS_AS(p) ((__attribute__((address_space(3))) void*)(p))
-
-
 constexpr int BM = 256, BN = 256, BK = 64;
-constexpr int NSTAGE = 2;                              // LDS ring of operand tiles; NSTAGE-1 tiles are in flight
-constexpr int NWAVE_M = 2, NWAVE_N = 4;
-constexpr int NTHREADS = NWAVE_M * NWAVE_N * 64;      // 512
-constexpr int WTM = BM / NWAVE_M, WTN = BN / NWAVE_N;  // 128 x 64 per wave
-constexpr int FM = WTM / 32, FN = WTN / 32;            // 4 x 2 MFMA tiles
-constexpr int TILE_BYTES = BM * BK * 2;                // 32 KiB per operand tile
-constexpr int LOADS_PER_THREAD = TILE_BYTES / 16 / NTHREADS;   // 4 x 16 B per operand
-constexpr int LOADS_PER_TILE = 2 * LOADS_PER_THREAD;           // wave-level VMEM instructions per k-tile
+constexpr int NWAVE_N = 4;                             // waves along N; the two waves along M are the two groups of the main loop
+constexpr int NTHREADS = 512;
+constexpr int HALF_BYTES = 128 * BK * 2;               // 16 KiB: 128 rows (columns) of one operand, one K step
+constexpr int STAGE_BYTES = 2 * HALF_BYTES;            // one operand, one K step
+constexpr int OPERAND_BYTES = 2 * STAGE_BYTES;         // two K steps: 64 KiB, the reach of an LDS read's immediate offset
+constexpr int SMEM_BYTES = 2 * OPERAND_BYTES;          // [operand][K step parity][half]
 
-// ---- K-contiguous operand: LDS [rows][BK], 128 B per row = 8 chunks of 16 B, chunk ^= (row>>1)&7:
+// ---- LDS layouts of a half tile.  K-contiguous operand: [128 rows][64 k], 128 B per row = 8 chunks of 16 B, chunk ^= (row>>1)&7:
 //      16 consecutive rows at one logical chunk cover all 64 banks exactly once.
-constexpr int CPR = BK / 8;                            // 16-byte chunks per row
 __device__ __forceinline__ int kmaj_swz(int row) { return (row >> 1) & 7; }
-__device__ __forceinline__ int kmaj_off(int row, int chunk) { return row * (BK * 2) + ((chunk ^ kmaj_swz(row)) << 4); }
+// ---- reduction-major operand: [64 k][128 rows], 256 B per k-row = 8 groups of 32 B, group ^= f(krow): the 32 lanes of a
+//      transposing read touch k-rows {0..3, 8..11} (+ 4 or + 16) at one logical group; f tells those eight apart.
+__device__ __forceinline__ int mnmaj_swz(int krow) { return (krow & 3) | (((krow >> 3) & 1) << 2); }
 
-// ---- reduction-major operand: LDS [BK][rows], 512 B per k-row, 64-byte groups ^= krow&7
-__device__ __forceinline__ int mnmaj_off(int krow, int col /*element*/) {
-  const int c16 = col >> 3;
-  const int p16 = ((((c16 >> 2) ^ (krow & 7)) << 2) | (c16 & 3));
-  return krow * (BM * 2) + (p16 << 4) + ((col & 7) << 1);
-}
-
-// Byte offset, relative to the tile's corner element, of load i (0..LOADS_PER_THREAD-1) of this thread's share.
+// Byte offset, relative to the tile's corner element, of load i (0, 1) of this thread's share of half h.
 //   KMAJ : corner = (row r0, column k0); rows clamped so that r0 + row <= r_max
-//   MNMAJ: corner = (k-row k0, column r0); k-rows clamped so that k0 + krow <= k_max, columns so that r0 + col <= r_max
+//   MNMAJ: corner = (k-row k0, column r0); columns clamped so that r0 + col <= r_max
 template <bool MNMAJ>
-__device__ __forceinline__ uint32_t load_offset(int i, int64_t ld, int r0, int r_max, int k0, int k_max) {
-  const int id = i * NTHREADS + (int)threadIdx.x;   // 16-byte slot in the tile, lane-linear within a wave
+__device__ __forceinline__ uint32_t load_offset(int i, int h, int64_t ld, int r0, int r_max) {
+  const int id = i * NTHREADS + (int)threadIdx.x;   // 16-byte slot in the half tile, lane-linear within a wave
   if (!MNMAJ) {
-    const int row = id / CPR, pc = id % CPR;
-    const int chunk = pc ^ kmaj_swz(row);
-    return (uint32_t)(((int64_t)(min(r0 + row, r_max) - r0) * ld + chunk * 8) * 2);
+    const int row = id >> 3, pc = id & 7;
+    return (uint32_t)(((int64_t)(min(r0 + h * 128 + row, r_max) - r0) * ld + (pc ^ kmaj_swz(row)) * 8) * 2);
   } else {
-    const int krow = id >> 5, p16 = id & 31;
-    const int c16 = ((((p16 >> 2) ^ (krow & 7)) << 2) | (p16 & 3));
+    const int krow = id >> 4, p16 = id & 15;
+    const int c16 = (((p16 >> 1) ^ mnmaj_swz(krow)) << 1) | (p16 & 1);
     // columns past the operand's last one (a ragged last tile; widths are multiples of 8) re-read its last 8 columns:
     // finite duplicates whose products land in rows / columns of C that the epilogue masks
-    const int col = min(c16 * 8, r_max - r0 - 7);
-    return (uint32_t)(((int64_t)(min(k0 + krow, k_max) - k0) * ld + col) * 2);
+    const int col = min(h * 128 + c16 * 8, r_max - r0 - 7);
+    return (uint32_t)(((int64_t)krow * ld + col) * 2);
   }
 }
 
-// LDS byte offset (within an operand tile) of this lane's fragment read, for a 32-row block starting at row_base
-// and k16 step kk.  K-major: one 128-bit read.  Reduction-major: two transposing 64-bit reads (k-rows +0 and +4).
+// LDS byte offset (within a half tile) of this lane's fragment read of the 16 rows from row_base on.  A fragment is 16 rows x 32
+// k: lane l holds row l % 16, k 8 (l / 16) .. + 7.  K-major: one 128-bit read per k32 step kk (row blocks 2048 B apart).
+// Reduction-major: two transposing 64-bit reads (k-rows +0 and +4; k32 steps 8192 B apart).
 __device__ __forceinline__ uint32_t frag_off_kmaj(int row_base, int kk) {
-  const int l = threadIdx.x & 63;
-  return (uint32_t)kmaj_off(row_base + (l & 31), kk * 2 + (l >> 5));
+  const int l = threadIdx.x & 63, row = row_base + (l & 15);
+  return (uint32_t)(row * (BK * 2) + (((kk * 4 + (l >> 4)) ^ kmaj_swz(row)) << 4));
 }
-__device__ __forceinline__ uint32_t frag_off_mnmaj(int row_base, int kk, int hi) {
-  const int l = threadIdx.x & 63;
-  const int p = l & 15, g = l >> 4;
-  const int col = row_base + 16 * (g & 1) + 4 * (p & 3);
-  const int krow = kk * 16 + 8 * (g >> 1) + (p >> 2) + 4 * hi;
-  return (uint32_t)mnmaj_off(krow, col);
+__device__ __forceinline__ uint32_t frag_off_mnmaj(int col_base, int hi) {
+  const int l = threadIdx.x & 63, p = l & 15, g = l >> 4;
+  const int col = col_base + 4 * (p & 3), krow = 8 * g + (p >> 2) + 4 * hi, c16 = col >> 3;
+  const int p16 = (((c16 >> 1) ^ mnmaj_swz(krow)) << 1) | (c16 & 1);
+  return (uint32_t)(krow * 256 + (p16 << 4) + ((col & 7) << 1));
 }
-typedef short short8v __attribute__((ext_vector_type(8)));
 __device__ __forceinline__ bf16x8 lds_read_b128(uint32_t addr) {
   return *(const bf16x8*)(__attribute__((address_space(3))) const char*)(uintptr_t)addr;
 }
@@ -137,16 +122,23 @@ __device__ __forceinline__ int band_height(int tiles_m, int n_tiles, bool xcd_co
   return band_height_for_run(tiles_m, n_tiles / 8);
 }
 // Hardware deals consecutive workgroups round-robin to the 8 XCDs (each with its own L2); undo that so each
-// XCD gets a contiguous run of tile ids.  Measured: +3-4% for the store-only forms; the accumulate form (atomic adds
-// into C) is 8% faster with the hardware's interleaved order, so it keeps that.
+// XCD gets a contiguous run of tile ids.  Measured: +3-4% for the store-only forms; the accumulate form is up to 3 % faster with
+// the hardware's interleaved order, so it keeps that.
 __device__ __forceinline__ int xcd_contiguous_id(int id, int n_tiles) {
   constexpr int NXCD = 8;
   const int x = id % NXCD, q = n_tiles / NXCD, r = n_tiles % NXCD;   // XCD x owns q (+1 if x < r) consecutive ids
   return x * q + min(x, r) + id / NXCD;
 }
 
-// vmcnt(n) with expcnt / lgkmcnt left unconstrained
-#define WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(0x0f70 | ((n) & 15) | (((n) >> 4) << 14))
+// Counted wait / workgroup barrier of the main loop.  Inline assembly (with a memory clobber) so that the compiler neither adds
+// waits of its own nor moves LDS reads across; the scheduling barriers keep the machine scheduler from doing the same.
+#define WAIT_VMCNT(n) asm volatile("s_waitcnt vmcnt(%0)" ::"i"(n) : "memory")
+#define SLOT_BARRIER()                        \
+  do {                                        \
+    __builtin_amdgcn_sched_barrier(0);        \
+    asm volatile("s_barrier" ::: "memory");   \
+    __builtin_amdgcn_sched_barrier(0);        \
+  } while (0)
 
 // One 256x256 output tile: K range [k_begin, k_end).
 // MODE: 0 = store fp32, 1 = store bf16, 2 = accumulate fp32 (C +=), 3 = split-K partial (fp32 store, C already offset),
@@ -155,350 +147,349 @@ __device__ __forceinline__ int xcd_contiguous_id(int id, int n_tiles) {
 //       6 = C is not stored: the tile is the gradient wrt act = silu(gate) * up and the epilogue writes act, d gate, d up
 //       7 = like 5, but C (bf16) receives exp(c - block max) instead of c, and the value of each row's target column is kept
 constexpr bool mode_accumulates(int mode) { return mode == 2 || mode == 4; }
-constexpr bool mode_swaps_operands(int mode) { return mode == 5 || mode == 6 || mode == 7; }   // accumulators hold C^T blocks
 struct SwigluFuse { bf16_t* gate; bf16_t* up; bf16_t* act; };
 struct NumerFuse { const int32_t* targets; const int32_t* row_index; float* target_value; };
-//
-// The main loop is written so that it contains no vector ALU instructions at all: global addresses are an SGPR base
-// (advanced with scalar adds) plus per-lane offsets computed once, LDS fragment addresses are computed once per
-// stage and reached with immediate offsets, and the two LDS stages are unrolled.  Only the last K step of a ragged
-// reduction (weight-gradient form) takes a slower path with clamped addresses and zeroed fragments.
 // The reduction may come in several segments (operand pairs of the same shape and leading dimensions whose products
 // are summed into the same output tile): one accumulator, one epilogue.
 constexpr int MAX_SEG = 8;
-struct KSegments {
-  const bf16_t* A[MAX_SEG];
-  const bf16_t* B[MAX_SEG];
-  int K[MAX_SEG];         // reduction length of the segment (clamp for the loads)
-  int k_begin[MAX_SEG];   // range of the segment this tile works on
-  int k_end[MAX_SEG];
-  int n;
+struct KSegment {
+  const bf16_t* A; const bf16_t* B;
+  int k_begin, k_end;     // range of the reduction this tile works on
 };
 
-template <bool TA, bool TB, int MODE>
-__device__ __forceinline__ void gemm_tile(const KSegments& segs, void* __restrict__ Cv, int M, int N, int64_t lda,
-                                          int64_t ldb, int64_t ldc, int tm, int tn, char (&smem)[NSTAGE][2][TILE_BYTES],
+// Main loop.  The eight waves are two groups of four (waves w and w + 4 share a SIMD); wave (g, n) owns rows g*64 .. +63 and
+// columns n*32 .. +31 of each of the four 128 x 128 quadrants of the tile.  A K step has four phases, one quadrant each (16
+// v_mfma_f32_16x16x32_bf16 per wave), in the order (A0,B0) (A0,B1) (A1,B1) (A1,B0), so that each phase needs only one new operand
+// half.  A phase is two slots, each closed by a barrier: fetch (LDS reads of the phase's fragments, the DMA of one half tile) and
+// multiply.  Group 1 runs one slot behind group 0, so on every SIMD one wave multiplies while the other fetches: the matrix pipe
+// does not wait for LDS reads, load issue or barriers.  The half read in phase p is free two phases later and is then refilled
+// for the K step after next: five half tiles (80 KB) stay in flight and a load has six phases to land (a two-stage loop with
+// one barrier and one burst of loads per K step waits for a whole tile's latency each time).
+// What bounds it: the matrix pipe at its power-limited clock.  8192^3 bf16, same box: NT 1265 -> 1556, NN 1256 -> 1546, TN 1199
+// -> 1440 TFLOP/s (vendor library 1614 / 1390 / 1202); half of the gain is the slot schedule (1410 with 32x32x16 MFMAs), half the
+// 16x16x32 MFMA, whose operands toggle less: 2.09 PFLOP/s of it sustain on random data against 1.82 of the 32x32x16.
+// The TN form is closest to the LDS limit (transposing reads of both operands).
+// No vector-ALU address work: global addresses are an SGPR base plus per-lane offsets computed once, LDS fragment
+// addresses are computed once and reached with immediate offsets.
+template <bool TA, bool TB, int MODE, typename SegmentF>
+__device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void* __restrict__ Cv, int M, int N, int64_t lda,
+                                          int64_t ldb, int64_t ldc, int tm, int tn, char (&smem)[SMEM_BYTES],
                                           float2* __restrict__ stats = nullptr, SwigluFuse sw = SwigluFuse{nullptr, nullptr, nullptr},
                                           NumerFuse nf = NumerFuse{nullptr, nullptr, nullptr}) {
-  static_assert(NSTAGE == 2, "the main loop is unrolled over two LDS stages");
   constexpr bool AMN = TA, BMN = !TB;     // operand kept reduction-major in LDS (B stored [N,K] is the K-contiguous case)
   const int m0 = tm * BM, n0 = tn * BN;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int wm0 = (wave / NWAVE_N) * WTM, wn0 = (wave % NWAVE_N) * WTN;
+  const int grp = wave / NWAVE_N, wn = wave % NWAVE_N;
 
-  f32x16 acc[FM][FN];
+  f32x4 acc[2][2][4][2];   // [A half][B half][16-row block][16-column block]: C^T blocks, lane l = row l % 16, columns 4 (l / 16) .. + 3
 #pragma unroll
-  for (int i = 0; i < FM; ++i)
+  for (int x = 0; x < 32; ++x)
 #pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    for (int r = 0; r < 4; ++r) acc[x >> 4][(x >> 3) & 1][(x >> 1) & 3][x & 1][r] = 0.f;
 
   // ---- global side: per-lane byte offsets (rows clamped once); the uniform 64-bit bases walk along K
   const int64_t stepA = (AMN ? (int64_t)BK * lda : (int64_t)BK) * 2, stepB = (BMN ? (int64_t)BK * ldb : (int64_t)BK) * 2;
-  uint32_t offA[LOADS_PER_THREAD], offB[LOADS_PER_THREAD];
+  uint32_t offA[2][2], offB[2][2];
 #pragma unroll
-  for (int i = 0; i < LOADS_PER_THREAD; ++i) {
-    // the unclamped k range (k_max = INT_MAX) is right for every full K step
-    offA[i] = pin(load_offset<AMN>(i, lda, m0, M - 1, 0, 0x7fffffff));
-    offB[i] = pin(load_offset<BMN>(i, ldb, n0, N - 1, 0, 0x7fffffff));
-  }
-  const uint32_t lds_wave = __builtin_amdgcn_readfirstlane(lds_addr(&smem[0][0][0]) + (uint32_t)(threadIdx.x & ~63) * 16u);
-
-  // ---- LDS side: fragment addresses per stage, computed once
-  constexpr int NA = AMN ? 2 * FM : BK / 16, NB = BMN ? 2 * FN : BK / 16;
-  uint32_t fa[NSTAGE][NA], fb[NSTAGE][NB];
+  for (int h = 0; h < 2; ++h)
 #pragma unroll
-  for (int st = 0; st < NSTAGE; ++st) {
-    const uint32_t sa = lds_addr(&smem[st][0][0]), sb = lds_addr(&smem[st][1][0]);
-#pragma unroll
-    for (int x = 0; x < NA; ++x) fa[st][x] = pin(sa + (AMN ? frag_off_mnmaj(wm0 + (x >> 1) * 32, 0, x & 1) : frag_off_kmaj(wm0, x)));
-#pragma unroll
-    for (int x = 0; x < NB; ++x) fb[st][x] = pin(sb + (BMN ? frag_off_mnmaj(wn0 + (x >> 1) * 32, 0, x & 1) : frag_off_kmaj(wn0, x)));
-  }
-  // fragment (block i, k16 step kk) of stage st: K-major blocks are 32 rows = 4096 B apart (the swizzle repeats every
-  // 16 rows); reduction-major k16 steps are 16 k-rows = 8192 B apart (the swizzle repeats every 8 k-rows)
-  auto frag_a = [&](int st, int i, int kk) {
-    if (AMN) return lds_read_tr(fa[st][2 * i] + kk * 16 * BM * 2, fa[st][2 * i + 1] + kk * 16 * BM * 2);
-    else return lds_read_b128(fa[st][kk] + i * 32 * BK * 2);
-  };
-  auto frag_b = [&](int st, int j, int kk) {
-    if (BMN) return lds_read_tr(fb[st][2 * j] + kk * 16 * BN * 2, fb[st][2 * j + 1] + kk * 16 * BN * 2);
-    else return lds_read_b128(fb[st][kk] + j * 32 * BK * 2);
-  };
-
-  // One K step on stage st.  Fragments are double-buffered in registers: the LDS reads of k16 step kk+1 are in
-  // flight while the MFMAs of step kk issue.
-  auto compute = [&](int st, int k_valid) {
-    bf16x8 a[2][FM], b[2][FN];
-#pragma unroll
-    for (int i = 0; i < FM; ++i) a[0][i] = frag_a(st, i, 0);
-#pragma unroll
-    for (int j = 0; j < FN; ++j) b[0][j] = frag_b(st, j, 0);
-#pragma unroll
-    for (int kk = 0; kk < BK / 16; ++kk) {
-      const int cur = kk & 1, nxt = cur ^ 1;
-      if (kk + 1 < BK / 16) {
-#pragma unroll
-        for (int i = 0; i < FM; ++i) a[nxt][i] = frag_a(st, i, kk + 1);
-#pragma unroll
-        for (int j = 0; j < FN; ++j) b[nxt][j] = frag_b(st, j, kk + 1);
-      }
-      __builtin_amdgcn_sched_barrier(0);   // keep the prefetch above the MFMAs (the scheduler would sink it to its use)
-      if (TA && k_valid < BK) {   // zero reduction rows past the end (A only: B rows are finite duplicates)
-        const int kbase = kk * 16 + 8 * (lane >> 5);
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-          for (int e = 0; e < 8; ++e)
-            if (kbase + e >= k_valid) a[cur][i][e] = (bf16_t)0.0f;
-      }
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-          acc[i][j] = mode_swaps_operands(MODE) ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[cur][j], a[cur][i], acc[i][j], 0, 0, 0)   // C^T blocks
-                                : __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[cur][i], b[cur][j], acc[i][j], 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
+    for (int i = 0; i < 2; ++i) {
+      offA[h][i] = pin(load_offset<AMN>(i, h, lda, m0, M - 1));
+      offB[h][i] = pin(load_offset<BMN>(i, h, ldb, n0, N - 1));
     }
-  };
+  const uint32_t lds0 = lds_addr(smem);
+  const uint32_t lds_wave = __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)(threadIdx.x & ~63) * 16u);
 
-  // Two stages: at step kt wait for tile kt, barrier (every wave's share has landed and everyone is done reading
-  // the other stage), refill the other stage with tile kt+1, compute.
-#pragma unroll      // constant segment indices: the segment table stays in scalar registers
-  for (int sg = 0; sg < MAX_SEG; ++sg) {
-    if (sg >= segs.n) break;
-    const int K = segs.K[sg], k_begin = segs.k_begin[sg], k_end = segs.k_end[sg];
+  // ---- LDS side: fragment addresses, computed once
+  constexpr int NA = AMN ? 8 : 2, NB = BMN ? 4 : 2;
+  uint32_t fa[NA], fb[NB];
+#pragma unroll
+  for (int x = 0; x < NA; ++x) fa[x] = pin(lds0 + (AMN ? frag_off_mnmaj(grp * 64 + (x >> 1) * 16, x & 1) : frag_off_kmaj(grp * 64, x)));
+#pragma unroll
+  for (int x = 0; x < NB; ++x)
+    fb[x] = pin(lds0 + OPERAND_BYTES + (BMN ? frag_off_mnmaj(wn * 32 + (x >> 1) * 16, x & 1) : frag_off_kmaj(wn * 32, x)));
+  bf16x8 a[4][2], bx[2][2], by[2][2];     // [16-row block][k32 step]; bx / by swap roles every K step
+  using S0 = std::integral_constant<int, 0>;
+  using S1 = std::integral_constant<int, 1>;
+
+  for (int sg = 0; sg < n_segments; ++sg) {
+    const KSegment seg = segment(sg);
+    const int k_begin = seg.k_begin, k_end = seg.k_end;
     const int nk = (k_end - k_begin + BK - 1) / BK;
     if (nk <= 0) continue;
-    const char* gA = uniform_ptr(segs.A[sg] + (AMN ? (int64_t)k_begin * lda + m0 : (int64_t)m0 * lda + k_begin));
-    const char* gB = uniform_ptr(segs.B[sg] + (BMN ? (int64_t)k_begin * ldb + n0 : (int64_t)n0 * ldb + k_begin));
-    auto issue = [&](int kt, int st) {
-      const char* a_base = gA + (int64_t)kt * stepA;
-      const char* b_base = gB + (int64_t)kt * stepB;
-      const uint32_t la = lds_wave + (uint32_t)(st * 2 * TILE_BYTES), lb = la + TILE_BYTES;
+    const char* gA = uniform_ptr(seg.A + (AMN ? (int64_t)k_begin * lda + m0 : (int64_t)m0 * lda + k_begin));
+    const char* gB = uniform_ptr(seg.B + (BMN ? (int64_t)k_begin * ldb + n0 : (int64_t)n0 * ldb + k_begin));
+    // DMA of half h of K step kt (two 16-byte slots per thread).  Reduction rows past the end (the last K step of a ragged
+    // reduction) are not loaded: the lane writes zeros into its slot instead.
+    auto issue_half = [&](const char* base, const uint32_t (&off)[2], bool mnmaj, int kt, uint32_t dst) {
       const int k0 = k_begin + kt * BK;
-      if ((AMN || BMN) && k0 + BK > K) {    // ragged last K step: clamp the k-rows (slow path, once per tile)
+      if (mnmaj && k0 + BK > k_end) {
 #pragma unroll
-        for (int i = 0; i < LOADS_PER_THREAD; ++i) {
-          dma16(a_base, AMN ? load_offset<AMN>(i, lda, m0, M - 1, k0, K - 1) : offA[i], la + (uint32_t)(i * NTHREADS * 16));
-          dma16(b_base, BMN ? load_offset<BMN>(i, ldb, n0, N - 1, k0, K - 1) : offB[i], lb + (uint32_t)(i * NTHREADS * 16));
+        for (int i = 0; i < 2; ++i) {
+          if (k0 + i * 32 + (int)(threadIdx.x >> 4) < k_end) dma16(base, off[i], dst + i * (HALF_BYTES / 2));
+          else *(__attribute__((address_space(3))) i32x4*)(uintptr_t)(dst + i * (HALF_BYTES / 2) + (threadIdx.x & 63) * 16) = i32x4{0, 0, 0, 0};
         }
       } else {
-#pragma unroll
-        for (int i = 0; i < LOADS_PER_THREAD; ++i) {
-          dma16(a_base, offA[i], la + (uint32_t)(i * NTHREADS * 16));
-          dma16(b_base, offB[i], lb + (uint32_t)(i * NTHREADS * 16));
-        }
+        dma16(base, off[0], dst);
+        dma16(base, off[1], dst + HALF_BYTES / 2);
       }
     };
+    const bool ragged = (AMN || BMN) && (k_end - k_begin) % BK != 0;
+    const int n_tail = ragged ? 3 : 2;
+    auto issue_a = [&](int h, int kt) {
+      issue_half(gA + (int64_t)kt * stepA, offA[h], AMN, kt, lds_wave + (uint32_t)((kt & 1) * STAGE_BYTES + h * HALF_BYTES));
+    };
+    auto issue_b = [&](int h, int kt) {
+      issue_half(gB + (int64_t)kt * stepB, offB[h], BMN, kt, lds_wave + (uint32_t)(OPERAND_BYTES + (kt & 1) * STAGE_BYTES + h * HALF_BYTES));
+    };
+    auto read_a = [&](auto stage, int h) {
+      const uint32_t O = decltype(stage)::value * STAGE_BYTES + h * HALF_BYTES;
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          a[i][kk] = AMN ? lds_read_tr(fa[(i * 2) % NA] + O + kk * 8192, fa[(i * 2 + 1) % NA] + O + kk * 8192)
+                         : lds_read_b128(fa[kk] + O + i * 2048);
+    };
+    auto read_b = [&](auto stage, int h, bf16x8 (&b)[2][2]) {
+      const uint32_t O = decltype(stage)::value * STAGE_BYTES + h * HALF_BYTES;
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          b[j][kk] = BMN ? lds_read_tr(fb[(j * 2) % NB] + O + kk * 8192, fb[(j * 2 + 1) % NB] + O + kk * 8192)
+                         : lds_read_b128(fb[kk] + O + j * 2048);
+    };
+    auto multiply = [&](int ha, int hb, bf16x8 (&b)[2][2]) {
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)     // operands swapped: C^T blocks, a lane owns one row and four consecutive columns
+            acc[ha][hb][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j][kk], a[i][kk], acc[ha][hb][i][j], 0, 0, 0);
+    };
+    // A half is waited for one phase before it is read (each wave waits for its own share, the barriers in between cover the
+    // others'): in the steady state the ten youngest loads (five halves) may still be outstanding; the last two K steps
+    // issue no more loads and count down.  A wave may skip loads of a ragged last K step, so from their issue on nothing is counted.
+    auto k_step = [&](auto stage, int kt, bf16x8 (&bc)[2][2], bf16x8 (&bn)[2][2]) __attribute__((always_inline)) {
+      constexpr int S = decltype(stage)::value;
+      using Next = std::integral_constant<int, 1 - S>;
+      const int rem = nk - 1 - kt;
+#define WAIT_TAIL(penultimate, last)                  \
+  do {                                                \
+    if (rem >= n_tail) WAIT_VMCNT(10);                \
+    else if (ragged) WAIT_VMCNT(0);                   \
+    else if (rem == 1) WAIT_VMCNT(penultimate);       \
+    else WAIT_VMCNT(last);                            \
+  } while (0)
+      read_a(stage, 0);
+      if (rem >= 1) issue_a(1, kt + 1);
+      WAIT_TAIL(10, 2);
+      SLOT_BARRIER(); multiply(0, 0, bc); SLOT_BARRIER();
+      read_b(stage, 1, bn);
+      if (rem >= 2) issue_b(0, kt + 2);
+      WAIT_TAIL(8, 0);
+      SLOT_BARRIER(); multiply(0, 1, bn); SLOT_BARRIER();
+      read_a(stage, 1);
+      if (rem >= 2) issue_a(0, kt + 2);
+      WAIT_TAIL(6, 0);
+      SLOT_BARRIER(); multiply(1, 1, bn); SLOT_BARRIER();
+      read_b(Next{}, 0, bn);              // B0 of the next K step (a harmless read after the last one)
+      if (rem >= 2) issue_b(1, kt + 2);
+      WAIT_TAIL(4, 0);
+      SLOT_BARRIER(); multiply(1, 0, bc); SLOT_BARRIER();
+#undef WAIT_TAIL
+    };
     if (sg > 0) __syncthreads();     // everyone is done reading the stages of the previous segment
-    issue(0, 0);
-    for (int kt = 0; kt < nk; kt += 2) {
-      WAIT_VMCNT(0);
-      __syncthreads();
-      if (kt + 1 < nk) issue(kt + 1, 1);
-      compute(0, k_end - (k_begin + kt * BK));
-      if (kt + 1 < nk) {
-        WAIT_VMCNT(0);
-        __syncthreads();
-        if (kt + 2 < nk) issue(kt + 2, 0);
-        compute(1, k_end - (k_begin + (kt + 1) * BK));
-      }
+    issue_b(0, 0); issue_a(0, 0); issue_b(1, 0); issue_a(1, 0);
+    if (nk > 1) { issue_b(0, 1); issue_a(0, 1); issue_b(1, 1); if (nk > 2 || !ragged) WAIT_VMCNT(10); } else WAIT_VMCNT(4);
+    if (ragged && nk <= 2) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // (lgkmcnt: the zeros written in place of rows past the end)
+    SLOT_BARRIER();
+    read_b(S0{}, 0, bx);
+    if (grp == 1) SLOT_BARRIER();    // group 1 falls one slot behind ...
+    const int nk_even = nk & ~1;
+    for (int kt = 0; kt < nk_even; kt += 2) {
+      k_step(S0{}, kt, bx, by);
+      k_step(S1{}, kt + 1, by, bx);
     }
+    if (nk & 1) k_step(S0{}, nk - 1, bx, by);
+    if (grp == 0) SLOT_BARRIER();    // ... and group 0 waits for it here: both execute the same number of barriers
   }
 
-  // Epilogue.  Accumulator register r of lane l: row 8*(r/4) + 4*(l/32) + r%4, column l%32.
+  // Epilogue.  A lane holds, per (A half ha, block i), row ha*128 + grp*64 + i*16 + l%16 of the tile and, per (B half hb, block j),
+  // its columns hb*128 + wn*32 + j*16 + 4 (l/16) .. + 3.
   float* Cf = (float*)Cv;
   bf16_t* Cb = (bf16_t*)Cv;
-  if constexpr (MODE == 4) {
-    // bf16 C += acc, two columns (4 bytes) per lane and access: neighbouring lanes hold neighbouring columns, so for each
-    // register pair (r, r+1) the even lane takes row r of both columns and the odd lane row r+1 of both (one lane
-    // swap).  Every element has exactly one owner per launch: plain loads and stores, the sum is formed in fp32 and
-    // rounded once.  All loads of a 32-row block are issued before the first store so that the wave waits for C once
-    // per block, not once per element.
-    typedef bf16_t bf16x2 __attribute__((ext_vector_type(2)));
-    const bool odd = lane & 1;
+  auto row_of = [&](int ha, int i) { return ha * 128 + grp * 64 + i * 16 + (lane & 15); };
+  auto col_of = [&](int hb, int j) { return hb * 128 + wn * 32 + j * 16 + 4 * (lane >> 4); };
+  // Plain stores go through LDS (free once every wave has left the main loop), so that a wave writes whole rows of C, 16 bytes
+  // per lane: storing from the accumulator layout directly (32-byte pieces of 16 rows per instruction) measured 2-5 % slower
+  // over the whole product at K = 3584.
+  if constexpr (MODE == 1) {
+    __syncthreads();
 #pragma unroll
-    for (int i = 0; i < FM; ++i) {
-      float lo[8][FN], hi[8][FN];
-      bf16x2 old[8][FN];
+    for (int ha = 0; ha < 2; ++ha)
 #pragma unroll
-      for (int rp = 0; rp < 8; ++rp) {
-        const int r = 2 * rp;
-        const int row = m0 + wm0 + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3) + (odd ? 1 : 0);
+      for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < FN; ++j) {
-          float a0 = acc[i][j][r], a1 = acc[i][j][r + 1];
-          asm volatile("" : "+v"(a0), "+v"(a1));     // two plain registers: the select below stays a single v_cndmask
-          const float keep = odd ? a1 : a0;
-          const float send = odd ? a0 : a1;
-          const float got = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, send), 0xB1 /* quad_perm [1,0,3,2] */, 0xf, 0xf, false));
-          lo[rp][j] = odd ? got : keep;
-          hi[rp][j] = odd ? keep : got;
-          const int col = n0 + wn0 + j * 32 + (lane & 31) - (odd ? 1 : 0);     // even column of the pair (N is a multiple of 8)
-          const int64_t idx = (int64_t)row * ldc + col;
-          if (row < M && col < N) old[rp][j] = *(const bf16x2*)(Cb + idx);
-        }
+        for (int hb = 0; hb < 2; ++hb)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            const int row = row_of(ha, i), col = col_of(hb, j);
+            bf16x4 o;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) o[r] = (bf16_t)acc[ha][hb][i][j][r];
+            *(bf16x4*)(smem + row * 512 + (((col >> 3) ^ (row & 15)) << 4) + ((col & 4) << 1)) = o;
+          }
+    __syncthreads();
+    const int c16 = threadIdx.x & 31, col = n0 + c16 * 8;
+#pragma unroll
+    for (int p = 0; p < 16; ++p) {
+      const int row = p * 16 + (threadIdx.x >> 5);
+      const i32x4 v = *(const i32x4*)(smem + row * 512 + ((c16 ^ (row & 15)) << 4));
+      if (m0 + row < M && col < N) {
+        bf16_t* dst = Cb + (int64_t)(m0 + row) * ldc + col;
+        *(i32x4*)dst = v;
       }
+    }
+    return;
+  }
+  if constexpr (MODE == 0 || MODE == 2 || MODE == 3 || MODE == 4) {
+    // fp32 rows: one half of the tile's rows at a time (128 KB)
 #pragma unroll
-      for (int rp = 0; rp < 8; ++rp) {
-        const int r = 2 * rp;
-        const int row = m0 + wm0 + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3) + (odd ? 1 : 0);
+    for (int ha = 0; ha < 2; ++ha) {
+      __syncthreads();
 #pragma unroll
-        for (int j = 0; j < FN; ++j) {
-          const int col = n0 + wn0 + j * 32 + (lane & 31) - (odd ? 1 : 0);
-          const int64_t idx = (int64_t)row * ldc + col;
-          bf16x2 v;
-          v[0] = (bf16_t)((float)old[rp][j][0] + lo[rp][j]);
-          v[1] = (bf16_t)((float)old[rp][j][1] + hi[rp][j]);
-          if (row < M && col < N) *(bf16x2*)(Cb + idx) = v;
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int hb = 0; hb < 2; ++hb)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            const int row = row_of(0, i), col = col_of(hb, j);
+            *(f32x4*)(smem + row * 1024 + (((col >> 2) ^ (row & 15)) << 4)) = acc[ha][hb][i][j];
+          }
+      __syncthreads();
+      if constexpr (MODE == 4) {
+        // bf16 C += acc: every element has exactly one owner per launch; the sum is formed in fp32 and rounded once.  The loads
+        // of C (16 bytes per lane) go out before the first use.
+        const int c8 = threadIdx.x & 31, col = n0 + c8 * 8;
+        bf16x8 old[8];
+#pragma unroll
+        for (int p = 0; p < 8; ++p) {
+          const int row = m0 + ha * 128 + p * 16 + (threadIdx.x >> 5);
+          if (row < M && col < N) old[p] = *(const bf16x8*)(Cb + (int64_t)row * ldc + col);
+        }
+#pragma unroll
+        for (int p = 0; p < 8; ++p) {
+          const int row_l = p * 16 + (threadIdx.x >> 5), row = m0 + ha * 128 + row_l;
+          const f32x4 lo = *(const f32x4*)(smem + row_l * 1024 + (((c8 * 2) ^ (row_l & 15)) << 4));
+          const f32x4 hi = *(const f32x4*)(smem + row_l * 1024 + (((c8 * 2 + 1) ^ (row_l & 15)) << 4));
+          bf16x8 o;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) { o[e] = (bf16_t)((float)old[p][e] + lo[e]); o[e + 4] = (bf16_t)((float)old[p][e + 4] + hi[e]); }
+          if (row < M && col < N) *(bf16x8*)(Cb + (int64_t)row * ldc + col) = o;
+        }
+      } else if constexpr (MODE == 2) {
+        // fp32 C += acc: plain read-modify-write, every element has one owner per launch; eight 16-byte loads of C per lane are
+        // in flight before the first add.  (fp32 atomic adds without return, the earlier form, cost 1721 instead of 1139 us
+        // where the pass over C dominates - 152064 x 3584, K = 512 - and the same at K >= 8192.)
+        const int c4 = threadIdx.x & 63, col = n0 + c4 * 4;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          f32x4 old[8];
+#pragma unroll
+          for (int p = 0; p < 8; ++p) {
+            const int row = m0 + ha * 128 + (q * 8 + p) * 8 + (threadIdx.x >> 6);
+            if (row < M && col < N) old[p] = *(const f32x4*)(Cf + (int64_t)row * ldc + col);
+          }
+#pragma unroll
+          for (int p = 0; p < 8; ++p) {
+            const int row_l = (q * 8 + p) * 8 + (threadIdx.x >> 6), row = m0 + ha * 128 + row_l;
+            const f32x4 v = *(const f32x4*)(smem + row_l * 1024 + ((c4 ^ (row_l & 15)) << 4));
+            if (row < M && col < N) *(f32x4*)(Cf + (int64_t)row * ldc + col) = old[p] + v;
+          }
+        }
+      } else {
+        const int c4 = threadIdx.x & 63, col = n0 + c4 * 4;
+#pragma unroll
+        for (int p = 0; p < 16; ++p) {
+          const int row_l = p * 8 + (threadIdx.x >> 6), row = m0 + ha * 128 + row_l;
+          const f32x4 v = *(const f32x4*)(smem + row_l * 1024 + ((c4 ^ (row_l & 15)) << 4));
+          if (row < M && col < N) *(f32x4*)(Cf + (int64_t)row * ldc + col) = v;
         }
       }
     }
     return;
   }
-  if constexpr (MODE == 5) {
+  if constexpr (MODE == 5 || MODE == 7) {
     // Row statistics for a softmax over the columns of C: every row of the tile gets (max, sum of exp(c - max)) over
-    // the tile's 256 columns.  The products were formed with the operands swapped, so the accumulators hold C^T
-    // blocks: a lane owns one row of C (l % 32 inside the 32-row block) and 32 of its columns - per column block j
-    // and register quad q the four columns 8q + 4(l / 32) .. +3 - so the reduction over columns is in-lane, plus one
-    // exchange between the two lanes of a row, and C is stored 16 bytes at a time.  The NWAVE_N waves that share a row
-    // meet in LDS (the operand stages are free once every wave has left the main loop).
-    static_assert(FN == 2, "two column blocks per wave");
-    __syncthreads();
-    float2* part = (float2*)&smem[0][0][0];    // [NWAVE_N][BM]
-    constexpr float LOG2E = 1.4426950408889634f;
-#pragma unroll
-    for (int i = 0; i < FM; ++i) {
-      const int row_l = wm0 + i * 32 + (lane & 31);
-      const int col0 = n0 + wn0 + 4 * (lane >> 5);               // first of the lane's columns; quads at + j * 32 + 8 * q
-      if (n0 + BN > N) {                                         // ragged last column tile: columns past N take no part
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-            if (col0 + j * 32 + 8 * q >= N) {
-#pragma unroll
-              for (int e = 0; e < 4; ++e) acc[i][j][4 * q + e] = -INFINITY;
-            }
-      }
-      if (m0 + row_l < M) {
-        float* crow = Cf + (int64_t)(m0 + row_l) * ldc + col0;
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-            if (col0 + j * 32 + 8 * q < N)
-              *(float4*)(crow + j * 32 + 8 * q) = make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
-      }
-      float mx = acc[i][0][0];
-#pragma unroll
-      for (int j = 0; j < FN; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, acc[i][j][r]);
-      mx = fmaxf(mx, __shfl_xor(mx, 32, WAVE));
-      const float mref = mx == -INFINITY ? 0.0f : mx;            // a wave whose 64 columns all lie past N: sum 0, not NaN
-      float se = 0.f;
-#pragma unroll
-      for (int j = 0; j < FN; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) se += __builtin_amdgcn_exp2f((acc[i][j][r] - mref) * LOG2E);   // difference first: exact near the maximum
-      se += __shfl_xor(se, 32, WAVE);
-      if (lane < 32) part[(wave % NWAVE_N) * BM + row_l] = make_float2(mx, se);
-    }
-    __syncthreads();
-    if ((int)threadIdx.x < BM && m0 + (int)threadIdx.x < M) {
-      float2 p = part[threadIdx.x];
-#pragma unroll
-      for (int w = 1; w < NWAVE_N; ++w) {
-        const float2 q = part[w * BM + threadIdx.x];
-        const float m2 = fmaxf(p.x, q.x);
-        if (q.x != -INFINITY)                                    // (a wave past N contributes nothing; wave 0 always holds valid columns)
-          p.y = p.y * __builtin_amdgcn_exp2f((p.x - m2) * LOG2E) + q.y * __builtin_amdgcn_exp2f((q.x - m2) * LOG2E);
-        p.x = m2;
-      }
-      stats[(int64_t)(m0 + (int)threadIdx.x) * ((N + BN - 1) / BN) + tn] = p;
-    }
-    return;
-  }
-  if constexpr (MODE == 7) {
-    // Softmax numerators (Sec. 5 names fused backward operators as the way to cut the per-chunk HBM passes): what the row
-    // kernel after the logits GEMM needs of a row is exp(c - lse), and exp(c - max of the 256-column block) differs from it
-    // by one factor per block - so the tile stores that, in bf16 (half the bytes of the fp32 logits, and the exponentials
-    // are the ones the block's sum needs anyway), next to the block's (max, sum) pair; the sum is taken from the
+    // the tile's 256 columns - in-lane over the lane's 16 columns, two lane exchanges, and the NWAVE_N waves that share a row
+    // meet in LDS (free once every wave has left the main loop).
+    // MODE 5 stores C in fp32.  MODE 7 stores softmax numerators (Sec. 5 names fused backward operators as the way to cut the
+    // per-chunk HBM passes): what the row kernel after the logits GEMM needs of a row is exp(c - lse), and exp(c - max of the
+    // 256-column block) differs from it by one factor per block - so the tile stores that, in bf16; the sum is taken from the
     // unrounded values.  The logit of each row's target column, which the loss needs exactly, is kept in fp32 on the side.
-    // Same accumulator layout as MODE 5 (C^T blocks: a lane owns one row and 32 of its columns).  The four waves that
-    // share a row exchange their maxima before the exponentials and their sums after them.
-    static_assert(FN == 2, "two column blocks per wave");
-    typedef bf16_t bf16x4e __attribute__((ext_vector_type(4)));
     __syncthreads();
-    float* pmax = (float*)&smem[0][0][0];      // [NWAVE_N][BM]
+    float* pmax = (float*)smem;                // [NWAVE_N][BM]
     float* psum = pmax + NWAVE_N * BM;         // [NWAVE_N][BM]
     constexpr float LOG2E = 1.4426950408889634f;
-    const int wn = wave % NWAVE_N;
-    const int col0 = n0 + wn0 + 4 * (lane >> 5);                 // first of the lane's columns; quads at + j * 32 + 8 * q
 #pragma unroll
-    for (int i = 0; i < FM; ++i) {
-      const int row_l = wm0 + i * 32 + (lane & 31);
-      if (n0 + BN > N) {                                         // ragged last column tile: columns past N take no part
+    for (int ha = 0; ha < 2; ++ha)
 #pragma unroll
-        for (int j = 0; j < FN; ++j)
+      for (int i = 0; i < 4; ++i) {
+        const int row_l = row_of(ha, i), row = m0 + row_l;
+        float mx = -INFINITY;
+        int d = -1;
+        if (MODE == 7 && row < M) d = nf.targets[nf.row_index ? nf.row_index[row] : row] - n0;
 #pragma unroll
-          for (int q = 0; q < 4; ++q)
-            if (col0 + j * 32 + 8 * q >= N) {
+        for (int hb = 0; hb < 2; ++hb)
 #pragma unroll
-              for (int e = 0; e < 4; ++e) acc[i][j][4 * q + e] = -INFINITY;
+          for (int j = 0; j < 2; ++j) {
+            const int col = col_of(hb, j);
+            if (n0 + col >= N) {               // ragged last column tile: columns past N take no part
+#pragma unroll
+              for (int r = 0; r < 4; ++r) acc[ha][hb][i][j][r] = -INFINITY;
+            } else if (MODE == 5 && row < M) {
+              *(f32x4*)(Cf + (int64_t)row * ldc + n0 + col) = acc[ha][hb][i][j];
             }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              mx = fmaxf(mx, acc[ha][hb][i][j][r]);
+              if (MODE == 7 && d == col + r && acc[ha][hb][i][j][r] != -INFINITY) nf.target_value[row] = acc[ha][hb][i][j][r];
+            }
+          }
+        mx = fmaxf(mx, __shfl_xor(mx, 16, WAVE));
+        mx = fmaxf(mx, __shfl_xor(mx, 32, WAVE));
+        if (lane < 16) pmax[wn * BM + row_l] = mx;
       }
-      if (m0 + row_l < M) {                                      // the target's logit, if it lies among the lane's columns
-        const int r = nf.row_index ? nf.row_index[m0 + row_l] : m0 + row_l;
-        const int d = nf.targets[r] - col0;
-        if (d >= 0 && d < 64 && (d & 4) == 0) {
-          float zt = 0.f;
-#pragma unroll
-          for (int j = 0; j < FN; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-#pragma unroll
-              for (int e = 0; e < 4; ++e)
-                if (d == j * 32 + 8 * q + e) zt = acc[i][j][4 * q + e];
-          if (zt != -INFINITY) nf.target_value[m0 + row_l] = zt;   // (-inf: a masked column past N, i.e. an invalid target)
-        }
-      }
-      float mx = acc[i][0][0];
-#pragma unroll
-      for (int j = 0; j < FN; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, acc[i][j][r]);
-      mx = fmaxf(mx, __shfl_xor(mx, 32, WAVE));
-      if (lane < 32) pmax[wn * BM + row_l] = mx;
-    }
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < FM; ++i) {
-      const int row_l = wm0 + i * 32 + (lane & 31);
-      float m = pmax[row_l];
+    for (int ha = 0; ha < 2; ++ha)
 #pragma unroll
-      for (int w = 1; w < NWAVE_N; ++w) m = fmaxf(m, pmax[w * BM + row_l]);   // finite: wave 0 always holds valid columns
-      bf16_t* crow = Cb + (int64_t)(m0 + row_l) * ldc + col0;
-      float se = 0.f;
+      for (int i = 0; i < 4; ++i) {
+        const int row_l = row_of(ha, i), row = m0 + row_l;
+        float m = pmax[row_l];
 #pragma unroll
-      for (int j = 0; j < FN; ++j)
+        for (int w = 1; w < NWAVE_N; ++w) m = fmaxf(m, pmax[w * BM + row_l]);   // finite: wave 0 always holds valid columns
+        float se = 0.f;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          bf16x4e o;
+        for (int hb = 0; hb < 2; ++hb)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float ex = __builtin_amdgcn_exp2f((acc[i][j][4 * q + e] - m) * LOG2E);   // difference first: exact near the maximum
-            se += ex;
-            o[e] = (bf16_t)ex;
+          for (int j = 0; j < 2; ++j) {
+            bf16x4 o;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const float ex = __builtin_amdgcn_exp2f((acc[ha][hb][i][j][r] - m) * LOG2E);   // difference first: exact near the maximum
+              se += ex;
+              o[r] = (bf16_t)ex;
+            }
+            if (MODE == 7 && row < M && n0 + col_of(hb, j) < N) *(bf16x4*)(Cb + (int64_t)row * ldc + n0 + col_of(hb, j)) = o;
           }
-          if (m0 + row_l < M && col0 + j * 32 + 8 * q < N) *(bf16x4e*)(crow + j * 32 + 8 * q) = o;
-        }
-      se += __shfl_xor(se, 32, WAVE);
-      if (lane < 32) psum[wn * BM + row_l] = se;
-    }
+        se += __shfl_xor(se, 16, WAVE);
+        se += __shfl_xor(se, 32, WAVE);
+        if (lane < 16) psum[wn * BM + row_l] = se;
+      }
     __syncthreads();
     if ((int)threadIdx.x < BM && m0 + (int)threadIdx.x < M) {
       float m = pmax[threadIdx.x], sum = psum[threadIdx.x];
@@ -510,65 +501,44 @@ __device__ __forceinline__ void gemm_tile(const KSegments& segs, void* __restric
   }
   if constexpr (MODE == 6) {
     // SwiGLU adjoint on the accumulators (Sec. 5 names fused backward operators as the way to cut the per-chunk HBM
-    // passes): the products were formed with the operands swapped, so a lane owns one row of the tile and, per column
-    // block j and register quad q, four consecutive columns - 8-byte accesses to gate / up / act.  Every element has
-    // exactly one owner, so gate and up are rewritten in place.
-    typedef bf16_t bf16x4e __attribute__((ext_vector_type(4)));
+    // passes): 8-byte accesses to gate / up / act.  Every element has exactly one owner, so gate and up are rewritten in place.
 #pragma unroll
-    for (int i = 0; i < FM; ++i) {
-      const int row_l = wm0 + i * 32 + (lane & 31);
-      if (m0 + row_l >= M) continue;
-      const int64_t base = (int64_t)(m0 + row_l) * ldc + n0 + wn0 + 4 * (lane >> 5);
-      bf16x4e gv[FN][4], uv[FN][4];
+    for (int ha = 0; ha < 2; ++ha)
 #pragma unroll
-      for (int j = 0; j < FN; ++j)
+      for (int i = 0; i < 4; ++i) {
+        const int row = m0 + row_of(ha, i);
+        if (row >= M) continue;
+        bf16x4 gv[2][2], uv[2][2];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const bool in = n0 + wn0 + 4 * (lane >> 5) + j * 32 + 8 * q < N;
-          gv[j][q] = in ? *(const bf16x4e*)(sw.gate + base + j * 32 + 8 * q) : bf16x4e{};
-          uv[j][q] = in ? *(const bf16x4e*)(sw.up + base + j * 32 + 8 * q) : bf16x4e{};
-        }
+        for (int hb = 0; hb < 2; ++hb)
 #pragma unroll
-      for (int j = 0; j < FN; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          bf16x4e a4, dg4, du4;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float z = (float)gv[j][q][e], u = (float)uv[j][q][e], d = acc[i][j][4 * q + e];
-            const float sg = 1.0f / (1.0f + __expf(-z));
-            a4[e] = (bf16_t)(z * sg * u);
-            dg4[e] = (bf16_t)(d * u * sg * (1.0f + z * (1.0f - sg)));
-            du4[e] = (bf16_t)(d * z * sg);
+          for (int j = 0; j < 2; ++j) {
+            const int col = n0 + col_of(hb, j);
+            gv[hb][j] = col < N ? *(const bf16x4*)(sw.gate + (int64_t)row * ldc + col) : bf16x4{};
+            uv[hb][j] = col < N ? *(const bf16x4*)(sw.up + (int64_t)row * ldc + col) : bf16x4{};
           }
-          const int64_t idx = base + j * 32 + 8 * q;
-          if (n0 + wn0 + 4 * (lane >> 5) + j * 32 + 8 * q >= N) continue;
-          if (sw.act) *(bf16x4e*)(sw.act + idx) = a4;
-          *(bf16x4e*)(sw.gate + idx) = dg4;
-          *(bf16x4e*)(sw.up + idx) = du4;
-        }
-    }
-    return;
-  }
 #pragma unroll
-  for (int i = 0; i < FM; ++i)
+        for (int hb = 0; hb < 2; ++hb)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int row = m0 + wm0 + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-      if (row < M) {
+          for (int j = 0; j < 2; ++j) {
+            const int col = n0 + col_of(hb, j);
+            if (col >= N) continue;
+            bf16x4 a4, dg4, du4;
 #pragma unroll
-        for (int j = 0; j < FN; ++j) {
-          const int col = n0 + wn0 + j * 32 + (lane & 31);
-          if (col >= N) continue;                                // ragged last column tile
-          const int64_t idx = (int64_t)row * ldc + col;
-          const float v = acc[i][j][r];
-          if (MODE == 1) Cb[idx] = (bf16_t)v;
-          else if (MODE == 2) unsafeAtomicAdd(&Cf[idx], v);   // one add per element per launch: same rounding as a
-                                                               // read-modify-write, but the wave does not wait for C
-          else Cf[idx] = v;
-        }
+            for (int e = 0; e < 4; ++e) {
+              const float z = (float)gv[hb][j][e], u = (float)uv[hb][j][e], d = acc[ha][hb][i][j][e];
+              const float sg = 1.0f / (1.0f + __expf(-z));
+              a4[e] = (bf16_t)(z * sg * u);
+              dg4[e] = (bf16_t)(d * u * sg * (1.0f + z * (1.0f - sg)));
+              du4[e] = (bf16_t)(d * z * sg);
+            }
+            const int64_t idx = (int64_t)row * ldc + col;
+            if (sw.act) *(bf16x4*)(sw.act + idx) = a4;
+            *(bf16x4*)(sw.gate + idx) = dg4;
+            *(bf16x4*)(sw.up + idx) = du4;
+          }
       }
-    }
+  }
 }
 
 template <bool TA, bool TB, int MODE>
@@ -578,7 +548,7 @@ __global__ __launch_bounds__(NTHREADS) void gemm_mfma_k(const bf16_t* __restrict
                                                         const int* __restrict__ rows_dev, int xcds_per_split,
                                                         const bf16_t* __restrict__ A2, const bf16_t* __restrict__ B2,
                                                         float2* __restrict__ row_stats, SwigluFuse sw, NumerFuse nf) {
-  __shared__ __attribute__((aligned(1024))) char smem[NSTAGE][2][TILE_BYTES];   // [stage][A|B]
+  __shared__ __attribute__((aligned(1024))) char smem[SMEM_BYTES];
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN, n_tiles = tiles_m * tiles_n;
   int tm, tn, split = 0;
   if (MODE == 3 && xcds_per_split > 0) {
@@ -610,33 +580,25 @@ __global__ __launch_bounds__(NTHREADS) void gemm_mfma_k(const bf16_t* __restrict
   }
   const int k_end = min(K, k_begin + k_per_split);
   if (k_end <= k_begin && mode_accumulates(MODE)) return;   // nothing to add
-  KSegments segs;
-  segs.n = 1; segs.A[0] = A; segs.B[0] = B; segs.K[0] = K; segs.k_begin[0] = k_begin; segs.k_end[0] = k_end;
-  gemm_tile<TA, TB, MODE>(segs, Cv, M, N, lda, ldb, ldc, tm, tn, smem, row_stats, sw, nf);
+  gemm_tile<TA, TB, MODE>(1, [&](int) { return KSegment{A, B, k_begin, k_end}; }, Cv, M, N, lda, ldb, ldc, tm, tn, smem, row_stats, sw, nf);
 }
 
 // Weight-gradient form with a segmented reduction: C += sum_s A_s^T B_s, every segment with its own run-time row
-// count.  One pass over C (one atomic add per element) for several chunks' worth of rows.
+// count.  One pass over C for several chunks' worth of rows.
 struct SegLaunch { const bf16_t* A[MAX_SEG]; const bf16_t* B[MAX_SEG]; const int* rows_dev[MAX_SEG]; int K[MAX_SEG]; int n; };
 template <bool C_BF16>
 __global__ __launch_bounds__(NTHREADS) void gemm_mfma_seg_k(const SegLaunch sl, void* __restrict__ C, int M, int N, int64_t lda,
                                                             int64_t ldb, int64_t ldc) {
-  __shared__ __attribute__((aligned(1024))) char smem[NSTAGE][2][TILE_BYTES];
+  __shared__ __attribute__((aligned(1024))) char smem[SMEM_BYTES];
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
   int tm, tn;
   band_coords((int)blockIdx.x, tiles_m, tiles_n, band_height(tiles_m, tiles_m * tiles_n, false), tm, tn);
-  KSegments segs;
-  segs.n = sl.n;
+  auto rows = [&](int i) { return sl.rows_dev[i] ? min(sl.K[i], max(0, *sl.rows_dev[i])) : sl.K[i]; };
   int total = 0;
-#pragma unroll
-  for (int s = 0; s < MAX_SEG; ++s) {
-    int K = 0;
-    if (s < sl.n) { K = sl.K[s]; if (sl.rows_dev[s]) K = min(K, max(0, *sl.rows_dev[s])); }
-    segs.A[s] = sl.A[s]; segs.B[s] = sl.B[s]; segs.K[s] = K; segs.k_begin[s] = 0; segs.k_end[s] = K;
-    total += K;
-  }
+  for (int i = 0; i < sl.n; ++i) total += rows(i);
   if (total == 0) return;   // nothing to add
-  gemm_tile<true, false, C_BF16 ? 4 : 2>(segs, C, M, N, lda, ldb, ldc, tm, tn, smem);
+  gemm_tile<true, false, C_BF16 ? 4 : 2>(sl.n, [&](int i) { return KSegment{sl.A[i], sl.B[i], 0, rows(i)}; }, C, M, N, lda, ldb,
+                                         ldc, tm, tn, smem);
 }
 
 // Several independent GEMMs of one layout / output mode in a single launch: the tiles of all problems form one
@@ -653,7 +615,7 @@ struct GroupArgs { GroupProblem p[MAX_GROUP]; int n; int total_tiles; };
 
 template <bool TA, bool TB, int MODE>
 __global__ __launch_bounds__(NTHREADS) void gemm_mfma_group_k(const GroupArgs ga) {
-  __shared__ __attribute__((aligned(1024))) char smem[NSTAGE][2][TILE_BYTES];
+  __shared__ __attribute__((aligned(1024))) char smem[SMEM_BYTES];
   const int id = mode_accumulates(MODE) ? (int)blockIdx.x : xcd_contiguous_id(blockIdx.x, ga.total_tiles);
   int pi = 0;
 #pragma unroll
@@ -662,13 +624,8 @@ __global__ __launch_bounds__(NTHREADS) void gemm_mfma_group_k(const GroupArgs ga
   const GroupProblem& g = ga.p[pi];
   int tm, tn;
   band_coords(id - g.tile_begin, g.tiles_m, g.tiles_n, band_height(g.tiles_m, g.tiles_m * g.tiles_n, !mode_accumulates(MODE)), tm, tn);
-  KSegments segs;
-  segs.n = g.nseg;
-#pragma unroll
-  for (int sg = 0; sg < MAX_GSEG; ++sg) {
-    segs.A[sg] = g.A[sg]; segs.B[sg] = g.B[sg]; segs.K[sg] = g.K[sg]; segs.k_begin[sg] = 0; segs.k_end[sg] = g.K[sg];
-  }
-  gemm_tile<TA, TB, MODE>(segs, g.C, g.M, g.N, g.lda, g.ldb, g.ldc, tm, tn, smem);
+  gemm_tile<TA, TB, MODE>(mode_accumulates(MODE) ? g.nseg : 1, [&](int i) { return KSegment{g.A[i], g.B[i], 0, g.K[i]}; }, g.C, g.M, g.N,
+                          g.lda, g.ldb, g.ldc, tm, tn, smem);
 }
 
 // C (=|+=) sum_z partial[z] in a fixed order; OUT_BF16 rounds once at the end.

@@ -1,0 +1,68 @@
+"""The MFMA GEMM's main loop at the edges of its schedule: one to six K steps (the pipeline's prologue, its counted tail and the odd
+step after the unrolled pair), ragged reductions, and output sizes around the 256-wide tile and its 128-row halves."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _operands(M, N, K, ta, tb):
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M * 7919 + N * 31 + K)
+    r = lambda *s: torch.randn(s, generator=g, device="cuda").bfloat16()
+    A, B = (r(K, M) if ta else r(M, K)), (r(N, K) if tb else r(K, N))
+    a, b = A.double().cpu(), B.double().cpu()
+    return A, B, (a.t() if ta else a) @ (b.t() if tb else b)
+
+
+def _check(C, want, K):
+    """fp32 sums of K products of N(0, 1) values: error below K ulp of the typical sum sqrt(K) in any order (measured ~ sqrt(K)
+    ulp); a bf16 result is rounded once more, 2^-8 relative to the value (2^-9 plus a flip at a tie)."""
+    import torch
+    got = C.double().cpu()
+    bound = K * 2.0 ** -23 * max(1.0, K ** 0.5) + 1e-6
+    if C.dtype == torch.bfloat16:
+        bound = bound + want.abs() * 2.0 ** -8
+    assert bool(torch.isfinite(got).all())
+    assert bool(((got - want).abs() <= bound).all()), float((got - want).abs().max())
+
+
+@pytest.mark.parametrize("layout", ["nt", "nn"])
+@pytest.mark.parametrize("K", [64, 128, 192, 256, 320, 384])
+@pytest.mark.parametrize("M,N", [(1, 8), (127, 120), (129, 136), (256, 256), (257, 264), (400, 520)])
+def test_few_k_steps(layout, K, M, N):
+    import torch
+    from paper_2506_03077_amd import binding as sb
+    A, B, want = _operands(M, N, K, False, layout == "nt")
+    for dt in (torch.float32, torch.bfloat16):
+        C = torch.full((M, N), float("nan"), dtype=dt, device="cuda")
+        assert sb.debug_gemm(A, B, C, M, N, K, False, layout == "nt") == 1
+        _check(C, want, K)
+
+
+@pytest.mark.parametrize("K", [1, 8, 31, 32, 33, 63, 64, 65, 96, 127, 128, 129, 160, 191, 192, 193, 255, 320, 333])
+@pytest.mark.parametrize("M,N", [(8, 8), (128, 264), (264, 136)])
+def test_ragged_reduction_of_the_weight_gradient_form(K, M, N):
+    import torch
+    from paper_2506_03077_amd import binding as sb
+    A, B, want = _operands(M, N, K, True, False)
+    # rows past the reduction's end hold NaN: none may be read
+    A2 = torch.full((K + 64, M), float("nan"), dtype=torch.bfloat16, device="cuda"); A2[:K] = A
+    B2 = torch.full((K + 64, N), float("nan"), dtype=torch.bfloat16, device="cuda"); B2[:K] = B
+    C = torch.ones((M, N), dtype=torch.float32, device="cuda")
+    assert sb.debug_gemm(A2, B2, C, M, N, K, True, False, acc=True) == 1
+    _check(C, want + 1.0, K)
+    Cb = torch.ones((M, N), dtype=torch.bfloat16, device="cuda")
+    assert sb.debug_gemm(A2, B2, Cb, M, N, K, True, False, acc=True) == 1
+    _check(Cb, want + 1.0, K)
+
+
+@pytest.mark.parametrize("Ks", [(40, 64), (64, 200, 8), (129, 1, 63, 64)])
+def test_segments_of_unequal_length(Ks):
+    import torch
+    from paper_2506_03077_amd import binding as sb
+    M, N = 264, 136
+    ops = [_operands(M, N, k, True, False) for k in Ks]
+    C = torch.zeros((M, N), dtype=torch.float32, device="cuda")
+    assert sb.debug_gemm_dw_segments([o[0] for o in ops], [o[1] for o in ops], C, M, N, list(Ks)) == 1
+    _check(C, sum(o[2] for o in ops), sum(Ks))
