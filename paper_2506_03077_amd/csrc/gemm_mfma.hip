@@ -141,14 +141,21 @@ __device__ __forceinline__ int xcd_contiguous_id(int id, int n_tiles) {
   } while (0)
 
 // One 256x256 output tile: K range [k_begin, k_end).
-// MODE: 0 = store fp32, 1 = store bf16, 2 = accumulate fp32 (C +=), 3 = split-K partial (fp32 store, C already offset),
+// MODE: 0 = store fp32, 1 = store bf16, 2 = accumulate fp32 (C +=),
 //       4 = accumulate into a bf16 C (read, add in fp32, round once; weight-gradient form only),
 //       5 = store fp32 and emit per-row (max, sum of exp) pairs over the tile's columns (`stats`)
 //       6 = C is not stored: the tile is the gradient wrt act = silu(gate) * up and the epilogue writes act, d gate, d up
 //       7 = like 5, but C (bf16) receives exp(c - block max) instead of c, and the value of each row's target column is kept
+//       8 = store bf16 rows scaled by a per-row factor, row m to row index[m] of C
+//       9 = C (bf16) receives exp(c), columns N .. ldc zeros; the tile's row sums and the value of each row's target column are kept
 constexpr bool mode_accumulates(int mode) { return mode == 2 || mode == 4; }
+constexpr bool mode_splits(int mode) { return mode <= 2 || mode == 8; }      // forms whose reduction may be split over workgroups
+constexpr int PARTIAL_FLOATS = BM * BN;
+constexpr int EPI_OFFSET = SMEM_BYTES;                                         // mode 9 keeps 4 KB of row sums behind the staged tile
+constexpr int smem_bytes(int mode) { return SMEM_BYTES + (mode == 9 ? NWAVE_N * BM * 4 : 0); }
 struct SwigluFuse { bf16_t* gate; bf16_t* up; bf16_t* act; };
-struct NumerFuse { const int32_t* targets; const int32_t* row_index; float* target_value; };
+struct NumerFuse { const int32_t* targets; const int32_t* row_index; float* target_value; const int32_t* row_mask; };
+struct RowFuse { const float* scale; const int32_t* index; };
 // The reduction may come in several segments (operand pairs of the same shape and leading dimensions whose products
 // are summed into the same output tile): one accumulator, one epilogue.
 constexpr int MAX_SEG = 8;
@@ -173,9 +180,9 @@ struct KSegment {
 // addresses are computed once and reached with immediate offsets.
 template <bool TA, bool TB, int MODE, typename SegmentF>
 __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void* __restrict__ Cv, int M, int N, int64_t lda,
-                                          int64_t ldb, int64_t ldc, int tm, int tn, char (&smem)[SMEM_BYTES],
-                                          float2* __restrict__ stats = nullptr, SwigluFuse sw = SwigluFuse{nullptr, nullptr, nullptr},
-                                          NumerFuse nf = NumerFuse{nullptr, nullptr, nullptr}) {
+                                          int64_t ldb, int64_t ldc, int tm, int tn, char* smem,
+                                          float* __restrict__ partial = nullptr, void* __restrict__ stats_out = nullptr,
+                                          SwigluFuse sw = SwigluFuse{}, NumerFuse nf = NumerFuse{}, RowFuse rf = RowFuse{}) {
   constexpr bool AMN = TA, BMN = !TB;     // operand kept reduction-major in LDS (B stored [N,K] is the K-contiguous case)
   const int m0 = tm * BM, n0 = tn * BN;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -194,7 +201,7 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
   for (int h = 0; h < 2; ++h)
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      offA[h][i] = pin(load_offset<AMN>(i, h, lda, m0, M - 1));
+      offA[h][i] = pin(load_offset<AMN>(i, h, lda, m0, (AMN ? (M + 7) & ~7 : M) - 1));   // (padded A: whole 8-column granules)
       offB[h][i] = pin(load_offset<BMN>(i, h, ldb, n0, N - 1));
     }
   const uint32_t lds0 = lds_addr(smem);
@@ -326,12 +333,38 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
   // Plain stores go through LDS (free once every wave has left the main loop), so that a wave writes whole rows of C, 16 bytes
   // per lane: storing from the accumulator layout directly (32-byte pieces of 16 rows per instruction) measured 2-5 % slower
   // over the whole product at K = 3584.
-  if constexpr (MODE == 1) {
+  if constexpr (mode_splits(MODE)) {
+    if (partial) {     // a slice of the reduction: the whole fp32 tile, masked and combined by splitk_tail_k
+#pragma unroll
+      for (int ha = 0; ha < 2; ++ha) {
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int hb = 0; hb < 2; ++hb)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+              const int row = row_of(0, i), col = col_of(hb, j);
+              *(f32x4*)(smem + row * 1024 + (((col >> 2) ^ (row & 15)) << 4)) = acc[ha][hb][i][j];
+            }
+        __syncthreads();
+        const int c4 = threadIdx.x & 63;
+#pragma unroll
+        for (int p = 0; p < 16; ++p) {
+          const int row_l = p * 8 + (threadIdx.x >> 6);
+          *(f32x4*)(partial + (ha * 128 + row_l) * BN + c4 * 4) = *(const f32x4*)(smem + row_l * 1024 + ((c4 ^ (row_l & 15)) << 4));
+        }
+      }
+      return;
+    }
+  }
+  if constexpr (MODE == 1 || MODE == 8) {
     __syncthreads();
 #pragma unroll
     for (int ha = 0; ha < 2; ++ha)
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < 4; ++i) {
+        const float scale = MODE == 8 ? rf.scale[min(m0 + row_of(ha, i), M - 1)] : 1.0f;
 #pragma unroll
         for (int hb = 0; hb < 2; ++hb)
 #pragma unroll
@@ -339,9 +372,10 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
             const int row = row_of(ha, i), col = col_of(hb, j);
             bf16x4 o;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) o[r] = (bf16_t)acc[ha][hb][i][j][r];
+            for (int r = 0; r < 4; ++r) o[r] = (bf16_t)(MODE == 8 ? acc[ha][hb][i][j][r] * scale : acc[ha][hb][i][j][r]);
             *(bf16x4*)(smem + row * 512 + (((col >> 3) ^ (row & 15)) << 4) + ((col & 4) << 1)) = o;
           }
+      }
     __syncthreads();
     const int c16 = threadIdx.x & 31, col = n0 + c16 * 8;
 #pragma unroll
@@ -349,13 +383,13 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
       const int row = p * 16 + (threadIdx.x >> 5);
       const i32x4 v = *(const i32x4*)(smem + row * 512 + ((c16 ^ (row & 15)) << 4));
       if (m0 + row < M && col < N) {
-        bf16_t* dst = Cb + (int64_t)(m0 + row) * ldc + col;
-        *(i32x4*)dst = v;
+        const int64_t r_out = MODE == 8 ? (int64_t)rf.index[m0 + row] : (int64_t)(m0 + row);
+        *(i32x4*)(Cb + r_out * ldc + col) = v;
       }
     }
     return;
   }
-  if constexpr (MODE == 0 || MODE == 2 || MODE == 3 || MODE == 4) {
+  if constexpr (MODE == 0 || MODE == 2 || MODE == 4) {
     // fp32 rows: one half of the tile's rows at a time (128 KB)
 #pragma unroll
     for (int ha = 0; ha < 2; ++ha) {
@@ -422,7 +456,55 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
     }
     return;
   }
+  if constexpr (MODE == 9) {
+    // Softmax over the columns of C with a fixed reference: bf16 keeps its relative precision over the whole exponent range, so
+    // exp(c) itself serves as the numerator (no maximum, no exchange between the waves before the exponentials) as long as
+    // the row's sum stays within what the row kernel checks.  The sums are taken from the unrounded values.
+    constexpr float LOG2E = 1.4426950408889634f;
+    float* psum = (float*)(smem + EPI_OFFSET);        // [NWAVE_N][BM], behind the staged tile
+    float* stats = (float*)stats_out;
+    __syncthreads();
+#pragma unroll
+    for (int ha = 0; ha < 2; ++ha)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int row = row_of(ha, i);
+        const int d = m0 + row < M ? nf.targets[nf.row_index[m0 + row]] - n0 : -1;
+        float se = 0.f;
+#pragma unroll
+        for (int hb = 0; hb < 2; ++hb)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            const int col = col_of(hb, j);
+            bf16x4 o;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const float z = acc[ha][hb][i][j][r];
+              if (d == col + r) nf.target_value[m0 + row] = z;          // (targets lie in [0, N))
+              const float ex = n0 + col + r < N ? __builtin_amdgcn_exp2f(z * LOG2E) : 0.0f;
+              se += ex;
+              o[r] = (bf16_t)ex;
+            }
+            *(bf16x4*)(smem + row * 512 + (((col >> 3) ^ (row & 15)) << 4) + ((col & 4) << 1)) = o;
+          }
+        se += __shfl_xor(se, 16, WAVE);
+        se += __shfl_xor(se, 32, WAVE);
+        if (lane < 16) psum[wn * BM + row] = se;
+      }
+    __syncthreads();
+    const int c16 = threadIdx.x & 31, col = n0 + c16 * 8;
+#pragma unroll
+    for (int p = 0; p < 16; ++p) {
+      const int row = p * 16 + (threadIdx.x >> 5);
+      const i32x4 v = *(const i32x4*)(smem + row * 512 + ((c16 ^ (row & 15)) << 4));
+      if (m0 + row < M && col < (int)ldc) *(i32x4*)(Cb + (int64_t)(m0 + row) * ldc + col) = v;
+    }
+    if ((int)threadIdx.x < BM && m0 + (int)threadIdx.x < M)
+      stats[(int64_t)(m0 + (int)threadIdx.x) * ((N + BN - 1) / BN) + tn] = (psum[threadIdx.x] + psum[BM + threadIdx.x]) + (psum[2 * BM + threadIdx.x] + psum[3 * BM + threadIdx.x]);
+    return;
+  }
   if constexpr (MODE == 5 || MODE == 7) {
+    float2* stats = (float2*)stats_out;
     // Row statistics for a softmax over the columns of C: every row of the tile gets (max, sum of exp(c - max)) over
     // the tile's 256 columns - in-lane over the lane's 16 columns, two lane exchanges, and the NWAVE_N waves that share a row
     // meet in LDS (free once every wave has left the main loop).
@@ -484,7 +566,7 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
               se += ex;
               o[r] = (bf16_t)ex;
             }
-            if (MODE == 7 && row < M && n0 + col_of(hb, j) < N) *(bf16x4*)(Cb + (int64_t)row * ldc + n0 + col_of(hb, j)) = o;
+            if (MODE == 7 && row < M && n0 + col_of(hb, j) < N && (!nf.row_mask || nf.row_mask[row])) *(bf16x4*)(Cb + (int64_t)row * ldc + n0 + col_of(hb, j)) = o;
           }
         se += __shfl_xor(se, 16, WAVE);
         se += __shfl_xor(se, 32, WAVE);
@@ -541,46 +623,89 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
   }
 }
 
+// How the tiles of a launch are spread over the 256 CUs (one workgroup each): whole rounds of 256 tiles first, each tile by one
+// workgroup; the reduction of the tiles that are left over (or of all of them, where there are fewer than 256) is split
+// `splits` ways, so that the last round is not mostly idle.  Split tiles go to fp32 scratch and are summed in a fixed order.
+// The number of splits weighs the K steps saved against what the partial tiles cost: about 3.5 K steps for the extra launch
+// and 0.09 K step per partial tile (256 KB written and read back at ~4.5 TB/s against 1.45 us per K step).
+constexpr int N_CU = 256;
+constexpr int MAX_SPLITS = 8;
+struct Schedule { int tiles, full, tail, splits; };
+__host__ __device__ __forceinline__ Schedule make_schedule(int tiles, int k_steps, int scratch_tiles) {
+  const int tail = tiles % N_CU;
+  int best = 1;
+  if (tail > 0) {
+    float gain = 0.f;
+    for (int s = 2; s <= MAX_SPLITS && s * tail <= N_CU && s * tail <= scratch_tiles && k_steps / s >= 4; ++s) {
+      const float g = (float)(k_steps - (k_steps + s - 1) / s) - 3.5f - 0.09f * (float)(s * tail);
+      if (g > gain) { gain = g; best = s; }
+    }
+  }
+  return best > 1 ? Schedule{tiles, tiles - tail, tail, best} : Schedule{tiles, tiles, 0, 1};
+}
+// Workgroup -> (tile, split); false: nothing to do
+__device__ __forceinline__ bool scheduled_tile(const Schedule& sc, int block, bool interleaved, int& tile, int& split) {
+  split = 0;
+  if (block < sc.full) { tile = interleaved ? block : xcd_contiguous_id(block, sc.full); return true; }
+  const int q = block - sc.full;
+  if (q >= sc.tail * sc.splits) return false;
+  const int c = xcd_contiguous_id(q, sc.tail * sc.splits);      // an XCD works on one slice of the reduction (its share of K stays in its L2)
+  split = c / sc.tail;
+  tile = sc.full + c % sc.tail;
+  return true;
+}
+
 template <bool TA, bool TB, int MODE>
 __global__ __launch_bounds__(NTHREADS) void gemm_mfma_k(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B,
                                                         void* __restrict__ Cv, int M, int N, int K, int64_t lda,
-                                                        int64_t ldb, int64_t ldc, int k_per_split,
-                                                        const int* __restrict__ rows_dev, int xcds_per_split,
+                                                        int64_t ldb, int64_t ldc, const int* __restrict__ rows_dev,
                                                         const bf16_t* __restrict__ A2, const bf16_t* __restrict__ B2,
-                                                        float2* __restrict__ row_stats, SwigluFuse sw, NumerFuse nf) {
-  __shared__ __attribute__((aligned(1024))) char smem[SMEM_BYTES];
-  const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN, n_tiles = tiles_m * tiles_n;
-  int tm, tn, split = 0;
-  if (MODE == 3 && xcds_per_split > 0) {
-    // Split-K with each slice of the reduction pinned to its own group of XCDs (the grid is 1-D: n_tiles x splits
-    // workgroups, dealt round-robin to the 8 XCDs by the hardware).  Inside a group every XCD takes a contiguous
-    // run of the tile ids, so it touches only its slice of K of the operand panels of that run (measured: 12% less
-    // fabric traffic than with every XCD working on all slices of its tiles).
-    const int xcd = blockIdx.x & 7, q = blockIdx.x >> 3;
-    const int run = n_tiles / xcds_per_split;
-    split = xcd / xcds_per_split;
-    band_coords((xcd % xcds_per_split) * run + q, tiles_m, tiles_n, band_height_for_run(tiles_m, run), tm, tn);
-  } else if (MODE == 3) {
-    split = blockIdx.x / n_tiles;
-    band_coords(xcd_contiguous_id(blockIdx.x % n_tiles, n_tiles), tiles_m, tiles_n, band_height(tiles_m, n_tiles, true), tm, tn);
-  } else {
-    band_coords(mode_accumulates(MODE) ? (int)blockIdx.x : xcd_contiguous_id(blockIdx.x, n_tiles), tiles_m, tiles_n,
-                band_height(tiles_m, n_tiles, !mode_accumulates(MODE)), tm, tn);
-  }
-  if (MODE == 3) Cv = (float*)Cv + (int64_t)split * M * ldc;   // partial slices are laid out for the host-side M
+                                                        float* __restrict__ scratch, int scratch_tiles, void* __restrict__ row_stats,
+                                                        SwigluFuse sw, NumerFuse nf, RowFuse rf) {
+  __shared__ __attribute__((aligned(1024))) char smem[smem_bytes(MODE)];
   if (rows_dev) {                     // run-time row count: rows are M (NT / NN) or the reduction K (dW form)
     const int rows = max(0, *rows_dev);
     if (TA) K = min(K, rows); else M = min(M, rows);
-    if (!TA && tm * BM >= M) return;  // no valid row in this tile
   }
-  int k_begin = split * k_per_split;
-  if (MODE == 3 && A2 != nullptr) {   // two operand pairs instead of two halves of K: slice 1 is A2 B2 over the whole K
-    k_begin = 0;
-    if (split == 1) { A = A2; B = B2; }
+  const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN, k_steps = (K + BK - 1) / BK;
+  const int all_steps = A2 ? 2 * k_steps : k_steps;          // two operand pairs: their reductions follow one another
+  if (mode_accumulates(MODE) && all_steps == 0) return;      // nothing to add
+  const Schedule sc = make_schedule(tiles_m * tiles_n, all_steps, mode_splits(MODE) ? scratch_tiles : 0);
+  int tile, split, tm, tn;
+  if (!scheduled_tile(sc, blockIdx.x, mode_accumulates(MODE), tile, split)) return;
+  band_coords(tile, tiles_m, tiles_n, band_height(tiles_m, sc.tiles, !mode_accumulates(MODE)), tm, tn);
+  int s0 = 0, s1 = all_steps;
+  float* partial = nullptr;
+  if (tile >= sc.full) {
+    const int per = (all_steps + sc.splits - 1) / sc.splits;
+    s0 = split * per;
+    s1 = min(all_steps, s0 + per);
+    partial = scratch + ((int64_t)split * sc.tail + (tile - sc.full)) * PARTIAL_FLOATS;
   }
-  const int k_end = min(K, k_begin + k_per_split);
-  if (k_end <= k_begin && mode_accumulates(MODE)) return;   // nothing to add
-  gemm_tile<TA, TB, MODE>(1, [&](int) { return KSegment{A, B, k_begin, k_end}; }, Cv, M, N, lda, ldb, ldc, tm, tn, smem, row_stats, sw, nf);
+  auto segment = [&](int i) {
+    const int b = max(s0 - i * k_steps, 0) * BK, e = min(min(s1 - i * k_steps, k_steps) * BK, K);
+    return KSegment{i ? A2 : A, i ? B2 : B, b, e};
+  };
+  gemm_tile<TA, TB, MODE>(A2 ? 2 : 1, segment, Cv, M, N, lda, ldb, ldc, tm, tn, smem, partial, row_stats, sw, nf, rf);
+}
+
+// The softmax-numerator product (mode 7) again, only for the row tiles that hold a marked row and storing only those rows: a
+// launch that usually finds no mark and ends at once, hence a grid of one workgroup per CU that walks the tiles.
+__global__ __launch_bounds__(NTHREADS) void gemm_mfma_marked_k(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, void* __restrict__ C,
+                                                               int M, int N, int K, int64_t lda, int64_t ldb, int64_t ldc,
+                                                               const int* __restrict__ rows_dev, const int32_t* __restrict__ tile_marks,
+                                                               void* __restrict__ row_stats, NumerFuse nf) {
+  __shared__ __attribute__((aligned(1024))) char smem[SMEM_BYTES];
+  M = min(M, max(0, *rows_dev));
+  const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
+  for (int tm = 0; tm < tiles_m; ++tm) {
+    if (tile_marks[tm] == 0) continue;
+    for (int tn = blockIdx.x; tn < tiles_n; tn += gridDim.x) {
+      __syncthreads();
+      gemm_tile<false, true, 7>(1, [&](int) { return KSegment{A, B, 0, K}; }, C, M, N, lda, ldb, ldc, tm, tn, smem, nullptr, row_stats,
+                                SwigluFuse{}, nf);
+    }
+  }
 }
 
 // Weight-gradient form with a segmented reduction: C += sum_s A_s^T B_s, every segment with its own run-time row
@@ -611,12 +736,13 @@ struct GroupProblem {
   int64_t lda, ldb, ldc;
   int tile_begin, tiles_m, tiles_n;
 };
-struct GroupArgs { GroupProblem p[MAX_GROUP]; int n; int total_tiles; };
+struct GroupArgs { GroupProblem p[MAX_GROUP]; int n; Schedule sched; float* scratch; };
 
 template <bool TA, bool TB, int MODE>
 __global__ __launch_bounds__(NTHREADS) void gemm_mfma_group_k(const GroupArgs ga) {
   __shared__ __attribute__((aligned(1024))) char smem[SMEM_BYTES];
-  const int id = mode_accumulates(MODE) ? (int)blockIdx.x : xcd_contiguous_id(blockIdx.x, ga.total_tiles);
+  int id, split;
+  if (!scheduled_tile(ga.sched, blockIdx.x, mode_accumulates(MODE), id, split)) return;
   int pi = 0;
 #pragma unroll
   for (int i = 1; i < MAX_GROUP; ++i)
@@ -624,29 +750,67 @@ __global__ __launch_bounds__(NTHREADS) void gemm_mfma_group_k(const GroupArgs ga
   const GroupProblem& g = ga.p[pi];
   int tm, tn;
   band_coords(id - g.tile_begin, g.tiles_m, g.tiles_n, band_height(g.tiles_m, g.tiles_m * g.tiles_n, !mode_accumulates(MODE)), tm, tn);
-  gemm_tile<TA, TB, MODE>(mode_accumulates(MODE) ? g.nseg : 1, [&](int i) { return KSegment{g.A[i], g.B[i], 0, g.K[i]}; }, g.C, g.M, g.N,
-                          g.lda, g.ldb, g.ldc, tm, tn, smem);
+  int b = 0, e = 0x7fffffff;
+  float* partial = nullptr;
+  if (mode_splits(MODE) && id >= ga.sched.full) {     // (split launches have one reduction segment per problem)
+    const int k_steps = (g.K[0] + BK - 1) / BK, per = (k_steps + ga.sched.splits - 1) / ga.sched.splits;
+    b = split * per * BK;
+    e = b + per * BK;
+    partial = ga.scratch + ((int64_t)split * ga.sched.tail + (id - ga.sched.full)) * PARTIAL_FLOATS;
+  }
+  gemm_tile<TA, TB, MODE>(mode_accumulates(MODE) ? g.nseg : 1, [&](int i) { return KSegment{g.A[i], g.B[i], b, min(e, g.K[i])}; }, g.C, g.M, g.N,
+                          g.lda, g.ldb, g.ldc, tm, tn, smem, partial);
 }
 
-// C (=|+=) sum_z partial[z] in a fixed order; OUT_BF16 rounds once at the end.
-template <bool OUT_BF16, bool ACC>
-__global__ void splitk_reduce_k(const float* __restrict__ part, void* __restrict__ C, int64_t n, int splits) {
-  int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4;
-  if (i >= n) return;
-  float4 s = *(const float4*)(part + i);
-  for (int z = 1; z < splits; ++z) {
-    const float4 t = *(const float4*)(part + (int64_t)z * n + i);
-    s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
+// The tiles whose reduction was split: C (=|+=) sum of the partial tiles in a fixed order, rounded once.  Sixteen workgroups per tile.
+struct TailProblem { void* C; int M, N; int64_t ldc; int tile_begin, tiles_m, tiles_n; };
+struct TailArgs {
+  TailProblem p[MAX_GROUP];
+  int n;
+  Schedule sched;
+  const int* rows_dev;          // run-time row count of p[0] (single problems): the schedule is then made again from it
+  int k_steps, scratch_tiles;
+  const float* scratch;
+  RowFuse rf;
+};
+template <int MODE>
+__global__ __launch_bounds__(256) void splitk_tail_k(const TailArgs ta) {
+  Schedule sc = ta.sched;
+  int M0 = ta.p[0].M, tiles_m0 = ta.p[0].tiles_m;
+  if (ta.rows_dev) {
+    M0 = min(M0, max(0, *ta.rows_dev));
+    tiles_m0 = (M0 + BM - 1) / BM;
+    sc = make_schedule(tiles_m0 * ta.p[0].tiles_n, ta.k_steps, ta.scratch_tiles);
   }
-  if (OUT_BF16) {
-    bf16x4* c = (bf16x4*)((bf16_t*)C + i);
-    if (ACC) { const bf16x4 t = *c; s.x += (float)t[0]; s.y += (float)t[1]; s.z += (float)t[2]; s.w += (float)t[3]; }
-    bf16x4 o; o[0] = (bf16_t)s.x; o[1] = (bf16_t)s.y; o[2] = (bf16_t)s.z; o[3] = (bf16_t)s.w;
-    *c = o;
-  } else {
-    float4* c = (float4*)((float*)C + i);
-    if (ACC) { float4 t = *c; s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w; }
-    *c = s;
+  const int t = blockIdx.x >> 4;
+  if (t >= sc.tail) return;
+  const int id = sc.full + t;
+  int pi = 0;
+  for (int i = 1; i < ta.n; ++i)
+    if (id >= ta.p[i].tile_begin) pi = i;
+  const TailProblem& g = ta.p[pi];
+  const int M = pi == 0 ? M0 : g.M, tiles_m = pi == 0 ? tiles_m0 : g.tiles_m;
+  int tm, tn;
+  band_coords(id - g.tile_begin, tiles_m, g.tiles_n, band_height(tiles_m, tiles_m * g.tiles_n, !mode_accumulates(MODE)), tm, tn);
+  const int col_l = 4 * (threadIdx.x & 63), col = tn * BN + col_l;
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    const int row_l = (blockIdx.x & 15) * 16 + p * 4 + (threadIdx.x >> 6), row = tm * BM + row_l;
+    if (row >= M || col >= g.N) continue;
+    const float* src = ta.scratch + (int64_t)t * PARTIAL_FLOATS + row_l * BN + col_l;
+    f32x4 v = *(const f32x4*)src;
+    for (int z = 1; z < sc.splits; ++z) v += *(const f32x4*)(src + (int64_t)z * sc.tail * PARTIAL_FLOATS);
+    if constexpr (MODE == 1 || MODE == 8) {
+      const float f = MODE == 8 ? ta.rf.scale[row] : 1.0f;
+      bf16x4 o;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) o[r] = (bf16_t)(MODE == 8 ? v[r] * f : v[r]);
+      *(bf16x4*)((bf16_t*)g.C + (int64_t)(MODE == 8 ? ta.rf.index[row] : row) * g.ldc + col) = o;
+    } else {
+      f32x4* c = (f32x4*)((float*)g.C + (int64_t)row * g.ldc + col);
+      if (MODE == 2) v += *c;
+      *c = v;
+    }
   }
 }
 
@@ -655,12 +819,12 @@ bool gemm_mfma_eligible(const GemmArgs& g) {
   if (g.acc && g.out_dt != DT_F32 && !(g.out_dt == DT_BF16 && g.ta && !g.tb)) return false;   // bf16 C += : dW form only
   // Output widths need not be multiples of the 256-wide tile: a ragged last tile clamps its loads and masks its stores
   // (16-byte granules: multiples of 8 elements), e.g. a 151936-word vocabulary = 593.5 tiles.
-  if (g.M < 1 || g.N < 8 || g.K < 1) return false;
-  if (g.N % 8 != 0) return false;
+  if (g.M < 1 || g.N < 1 || g.K < 1) return false;
+  if (g.N % 8 != 0 && !g.row_sums) return false;        // (the exponential form pads its rows)
   if (g.ta && !g.tb) {                       // TN: both operands reduction-major; ragged K allowed
-    if (g.M % 8 != 0) return false;
-  } else if (!g.ta) {                        // NT / NN
-    if (g.K % BK != 0) return false;
+    if (g.M % 8 != 0 && !g.a_padded) return false;
+  } else if (!g.ta) {                        // NT / NN; a ragged K needs B reduction-major and A's rows padded with zeros
+    if (g.K % BK != 0 && (g.tb || !g.a_padded)) return false;
   } else {
     return false;                            // TT is never needed
   }
@@ -671,10 +835,16 @@ bool gemm_mfma_eligible(const GemmArgs& g) {
   return true;
 }
 
-// the operand-pair form needs two partial slices and a dense C
-bool gemm_mfma_pair_ok(const GemmArgs& g) {
-  return g.A2 && g.B2 && !g.ta && g.scratch && g.ldc == g.N && g.scratch_bytes >= (size_t)2 * g.M * g.ldc * sizeof(float) &&
-         !((uintptr_t)g.A2 & 15) && !((uintptr_t)g.B2 & 15);
+// the operand-pair form: two reductions, one after the other, in one accumulator
+bool gemm_mfma_pair_ok(const GemmArgs& g) { return g.A2 && g.B2 && !g.ta && !((uintptr_t)g.A2 & 15) && !((uintptr_t)g.B2 & 15); }
+
+// rows scaled and scattered on the way out: bf16 store form
+bool gemm_mfma_scatter_ok(const GemmArgs& g) { return g.row_scale && g.row_index && !g.acc && g.out_dt == DT_BF16 && !g.ta && !g.tb && !g.row_stats && !g.swiglu_gate; }
+
+// exponentials of C = A B^T in bf16 with zero-filled columns up to ldc, a multiple of 64
+bool gemm_mfma_exp_ok(const GemmArgs& g) {
+  return !g.ta && g.tb && g.out_dt == DT_BF16 && !g.acc && !g.A2 && g.row_sums && g.numer_targets && g.numer_target_value && g.numer_row_index &&
+         g.ldc % 64 == 0 && g.ldc >= g.N && g.ldc < g.N + 64;
 }
 
 // the fused SwiGLU adjoint exists for the store form C = A B (input-gradient layout), bf16 tensors that share C's layout
@@ -694,85 +864,81 @@ bool gemm_mfma_numer_ok(const GemmArgs& g) {
          g.numer_targets && g.numer_target_value && !g.swiglu_gate;
 }
 
-constexpr int MAX_SPLITS = 8;
-// Split-K factor (a power of two <= 8) for outputs with too few tiles to fill the chip: the largest split that
-// still fits one round of 256 CUs and leaves every slice at least 8 K steps.  Splitting further does not reduce
-// the fabric traffic: an XCD runs 32 tiles at a time whatever the split, and those pull (rows + columns) operand
-// panels per K step.
-int gemm_mfma_splits(const GemmArgs& g) {
-  const int64_t tiles = cdiv(g.M, BM) * cdiv(g.N, BN);
-  const int k_tiles = (int)cdiv(g.K, BK);
-  if (tiles >= 200 || k_tiles < 16 || (g.ta && g.rows_dev)) return 1;
-  int s = 1;
-  while (s * 2 <= MAX_SPLITS && s * 2 * tiles <= 256 && k_tiles / (s * 2) >= 8) s *= 2;
-  return s;
-}
-
 size_t gemm_scratch_bytes(int max_m, int max_n, int max_splits) {
-  return (size_t)std::min(max_splits, MAX_SPLITS) * max_m * max_n * sizeof(float);
+  // partial tiles: at most one per CU is ever useful
+  const int64_t tiles = cdiv(max_m, BM) * cdiv(max_n, BN);
+  return (size_t)std::min<int64_t>(N_CU, tiles * std::min(max_splits, MAX_SPLITS)) * PARTIAL_FLOATS * sizeof(float);
+}
+static int scratch_tiles_of(const GemmArgs& g) {
+  return g.scratch && !((uintptr_t)g.scratch & 15) ? (int)std::min<size_t>(N_CU, g.scratch_bytes / (PARTIAL_FLOATS * sizeof(float))) : 0;
+}
+static hipError_t launch_tail(int mode, const TailArgs& t, int max_tail, hipStream_t st) {
+  const unsigned blocks = (unsigned)max_tail * 16;
+  if (mode == 0) splitk_tail_k<0><<<blocks, 256, 0, st>>>(t);
+  else if (mode == 1) splitk_tail_k<1><<<blocks, 256, 0, st>>>(t);
+  else if (mode == 2) splitk_tail_k<2><<<blocks, 256, 0, st>>>(t);
+  else splitk_tail_k<8><<<blocks, 256, 0, st>>>(t);
+  return hipGetLastError();
 }
 
 hipError_t gemm_mfma(const GemmArgs& g, hipStream_t st) {
   const int tiles_m = (int)cdiv(g.M, BM), tiles_n = (int)cdiv(g.N, BN);
-  int splits = gemm_mfma_splits(g);
-  if (g.scratch == nullptr || g.ldc != g.N || g.row_stats || g.swiglu_gate) splits = 1;
-  while (splits > 1 && g.scratch_bytes < (size_t)splits * g.M * g.ldc * sizeof(float)) splits /= 2;   // what the scratch holds
-  int k_per_split = g.K;
-  int xcds_per_split = 0;
-  if (g.A2) {               // operand-pair form (gemm_mfma_pair_ok has checked the scratch): slice = pair, each over all of K
-    splits = 2;
-    if ((tiles_m * tiles_n) % 4 == 0) xcds_per_split = 4;
-  } else if (splits > 1) {
-    k_per_split = (int)(cdiv(cdiv(g.K, BK), splits) * BK);
-    if ((int)cdiv(g.K, k_per_split) != splits) splits = (int)cdiv(g.K, k_per_split);
-    if (8 % splits == 0 && (tiles_m * tiles_n) % (8 / splits) == 0) xcds_per_split = 8 / splits;
-  }
-  dim3 grid(tiles_m * tiles_n * splits, 1, 1);
-  const bf16_t* A = (const bf16_t*)g.A;
-  const bf16_t* B = (const bf16_t*)g.B;
-#define LAUNCH(TA, TB, MODE, CPTR) \
-  gemm_mfma_k<TA, TB, MODE><<<grid, NTHREADS, 0, st>>>(A, B, CPTR, g.M, g.N, g.K, g.lda, g.ldb, g.ldc, k_per_split, g.rows_dev, \
-                                                       xcds_per_split, (const bf16_t*)g.A2, (const bf16_t*)g.B2, g.row_stats, \
+  const int k_steps = (int)cdiv(g.K, BK) * (g.A2 ? 2 : 1);
+  const int mode = g.row_sums ? 9 : g.numer_targets ? 7 : g.row_stats ? 5 : g.swiglu_gate ? 6 : g.row_scale ? 8
+                 : g.acc ? (g.out_dt == DT_BF16 ? 4 : 2) : (g.out_dt == DT_BF16 ? 1 : 0);
+  const bool dev_rows = g.rows_dev != nullptr;
+  const int scratch_tiles = mode_splits(mode) && !(g.ta && dev_rows) ? scratch_tiles_of(g) : 0;
+  const Schedule sc = make_schedule(tiles_m * tiles_n, k_steps, scratch_tiles);
+  // with a run-time row count the schedule is made on the device: room for any tail
+  const unsigned grid = dev_rows && scratch_tiles ? (unsigned)(tiles_m * tiles_n + N_CU) : (unsigned)(sc.full + sc.tail * sc.splits);
+  const bool may_split = dev_rows ? scratch_tiles >= 2 : sc.splits > 1;
+#define LAUNCH(TA, TB, MODE) \
+  gemm_mfma_k<TA, TB, MODE><<<grid, NTHREADS, 0, st>>>((const bf16_t*)g.A, (const bf16_t*)g.B, g.C, g.M, g.N, g.K, g.lda, g.ldb, g.ldc, g.rows_dev, \
+                                                       (const bf16_t*)g.A2, (const bf16_t*)g.B2, g.scratch, scratch_tiles, \
+                                                       g.row_sums ? (void*)g.row_sums : (void*)g.row_stats, \
                                                        SwigluFuse{(bf16_t*)g.swiglu_gate, (bf16_t*)g.swiglu_up, (bf16_t*)g.swiglu_act}, \
-                                                       NumerFuse{g.numer_targets, g.numer_row_index, g.numer_target_value})
-#define LAUNCH_LAYOUT(MODE, CPTR)                       \
-  do {                                                  \
-    if (!g.ta && g.tb) LAUNCH(false, true, MODE, CPTR); \
-    else if (!g.ta && !g.tb) LAUNCH(false, false, MODE, CPTR); \
-    else LAUNCH(true, false, MODE, CPTR);               \
+                                                       NumerFuse{g.numer_targets, g.numer_row_index, g.numer_target_value, nullptr}, \
+                                                       RowFuse{g.row_scale, g.row_index})
+#define LAUNCH_LAYOUT(MODE)                       \
+  do {                                            \
+    if (!g.ta && g.tb) LAUNCH(false, true, MODE); \
+    else if (!g.ta && !g.tb) LAUNCH(false, false, MODE); \
+    else LAUNCH(true, false, MODE);               \
   } while (0)
   const int layout = g.ta ? 2 : (g.tb ? 0 : 1);
-  const int mode = splits > 1 ? 3 : (g.acc ? 2 : (g.out_dt == DT_BF16 ? 1 : 0));   // (both accumulate forms are timed as one kind)
-  const int kind = g.numer_targets ? (int)prof::GEMM_NUMER : g.row_stats ? (int)prof::GEMM_STATS : g.swiglu_gate ? (int)prof::GEMM_SWIGLU : prof::GEMM_SINGLE + layout * 4 + mode;
-  const double work = 2.0 * g.M * g.N * g.K * (g.A2 ? 2 : 1);
-  if (splits > 1) {
-    {
-      prof::Scope sc(kind, work, g.rows_dev != nullptr, st);   // times the GEMM kernel, not the reduction after it
-      LAUNCH_LAYOUT(3, (void*)g.scratch);
-    }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const int64_t n = (int64_t)g.M * g.N;
-    const unsigned blocks = (unsigned)cdiv(n / 4, 256);
-    if (g.out_dt == DT_BF16 && g.acc) splitk_reduce_k<true, true><<<blocks, 256, 0, st>>>(g.scratch, g.C, n, splits);
-    else if (g.out_dt == DT_BF16) splitk_reduce_k<true, false><<<blocks, 256, 0, st>>>(g.scratch, g.C, n, splits);
-    else if (g.acc) splitk_reduce_k<false, true><<<blocks, 256, 0, st>>>(g.scratch, g.C, n, splits);
-    else splitk_reduce_k<false, false><<<blocks, 256, 0, st>>>(g.scratch, g.C, n, splits);
-    return hipGetLastError();
+  const int kind = mode == 9 ? (int)prof::GEMM_EXP : mode == 7 ? (int)prof::GEMM_NUMER : mode == 5 ? (int)prof::GEMM_STATS : mode == 6 ? (int)prof::GEMM_SWIGLU
+                 : prof::GEMM_SINGLE + layout * 4 + (mode == 8 ? 3 : mode == 4 ? 2 : mode);   // (both accumulate forms are timed as one kind)
+  {
+    prof::Scope sc_time(kind, 2.0 * g.M * g.N * g.K * (g.A2 ? 2 : 1), dev_rows, st);   // times the GEMM kernel, not the sum of the partial tiles after it
+    if (mode == 9) LAUNCH(false, true, 9);
+    else if (mode == 8) LAUNCH(false, false, 8);
+    else if (mode == 7) LAUNCH(false, true, 7);
+    else if (mode == 5) LAUNCH(false, true, 5);
+    else if (mode == 6) LAUNCH(false, false, 6);
+    else if (mode == 4) LAUNCH(true, false, 4);
+    else if (mode == 1) LAUNCH_LAYOUT(1);
+    else if (mode == 2) LAUNCH_LAYOUT(2);
+    else LAUNCH_LAYOUT(0);
   }
-  prof::Scope sc(kind, work, g.rows_dev != nullptr, st);
-  if (g.numer_targets) LAUNCH(false, true, 7, g.C);
-  else if (g.row_stats) LAUNCH(false, true, 5, g.C);
-  else if (g.swiglu_gate) LAUNCH(false, false, 6, g.C);
-  else if (g.out_dt == DT_BF16 && g.acc) LAUNCH(true, false, 4, g.C);
-  else if (g.out_dt == DT_BF16) LAUNCH_LAYOUT(1, g.C);
-  else if (g.acc) LAUNCH_LAYOUT(2, g.C);
-  else LAUNCH_LAYOUT(0, g.C);
 #undef LAUNCH_LAYOUT
 #undef LAUNCH
-  return hipGetLastError();
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || !may_split) return e;
+  TailArgs t{};
+  t.n = 1;
+  t.p[0] = TailProblem{g.C, g.M, g.N, g.ldc, 0, tiles_m, tiles_n};
+  t.sched = sc; t.rows_dev = g.rows_dev; t.k_steps = k_steps; t.scratch_tiles = scratch_tiles; t.scratch = g.scratch;
+  t.rf = RowFuse{g.row_scale, g.row_index};
+  return launch_tail(mode, t, dev_rows ? std::min(N_CU / 2, tiles_m * tiles_n) : sc.tail, st);
 }
 
+// The product of marked rows (see gemm_mfma_marked_k).
+hipError_t gemm_mfma_marked(const GemmArgs& g, const int32_t* tile_marks, const int32_t* row_marks, hipStream_t st) {
+  gemm_mfma_marked_k<<<(unsigned)std::min<int64_t>(N_CU, cdiv(g.N, BN)), NTHREADS, 0, st>>>(
+      (const bf16_t*)g.A, (const bf16_t*)g.B, g.C, g.M, g.N, g.K, g.lda, g.ldb, g.ldc, g.rows_dev, tile_marks, g.row_stats,
+      NumerFuse{g.numer_targets, g.numer_row_index, g.numer_target_value, row_marks});
+  return hipGetLastError();
+}
 
 // Grouped launch.  Requires every problem to be eligible, of the same layout / output type / accumulate mode.
 // Accumulate-form problems that write the same C (same shape and leading dimensions) are folded into one grouped
@@ -804,7 +970,7 @@ bool gemm_mfma_group_eligible(const GemmArgs* gs, int n, bool small_ok) {
     if (++nseg[owner[i]] > MAX_GSEG) return false;
     if (owner[i] == i) tiles += cdiv(gs[i].M, BM) * cdiv(gs[i].N, BN);
   }
-  // few tiles: per-problem launches with split-K fill the chip better - unless problems share an output, where one
+  // few tiles: per-problem launches, each split over the chip, fill it better - unless problems share an output, where one
   // launch with several reduction segments replaces several passes over it
   // (small_ok: many skinny problems, none of which could fill the chip alone either)
   return (tiles >= 200 || n_out < n || small_ok) && tiles < (1 << 30);
@@ -829,14 +995,19 @@ hipError_t gemm_mfma_group(const GemmArgs* gs, int n, hipStream_t st) {
     ++p.nseg;
   }
   ga.n = np;
-  ga.total_tiles = tiles;
   const GemmArgs& g = gs[0];
+  const int mode = g.acc ? (g.out_dt == DT_BF16 ? 4 : 2) : (g.out_dt == DT_BF16 ? 1 : 0);
+  int min_k = g.K;
+  for (int i = 1; i < n; ++i) min_k = std::min(min_k, gs[i].K);
+  ga.sched = make_schedule(tiles, (int)cdiv(min_k, BK), mode_splits(mode) && np == n ? scratch_tiles_of(g) : 0);
+  ga.scratch = g.scratch;
+  const unsigned grid = (unsigned)(ga.sched.full + ga.sched.tail * ga.sched.splits);
   double work = 0.0;
   for (int i = 0; i < n; ++i) work += 2.0 * gs[i].M * gs[i].N * gs[i].K;
   const int layout = g.ta ? 2 : (g.tb ? 0 : 1);
-  const int mode = g.acc ? 2 : (g.out_dt == DT_BF16 ? 1 : 0);
-  prof::Scope sc(prof::GEMM_GROUP + layout * 4 + mode, work, false, st);
-#define GLAUNCH(TA, TB, MODE) gemm_mfma_group_k<TA, TB, MODE><<<tiles, NTHREADS, 0, st>>>(ga)
+  {
+  prof::Scope sc(prof::GEMM_GROUP + layout * 4 + (mode == 4 ? 2 : mode), work, false, st);
+#define GLAUNCH(TA, TB, MODE) gemm_mfma_group_k<TA, TB, MODE><<<grid, NTHREADS, 0, st>>>(ga)
 #define GLAUNCH_LAYOUT(MODE)                     \
   do {                                           \
     if (!g.ta && g.tb) GLAUNCH(false, true, MODE); \
@@ -849,7 +1020,14 @@ hipError_t gemm_mfma_group(const GemmArgs* gs, int n, hipStream_t st) {
   else GLAUNCH_LAYOUT(0);
 #undef GLAUNCH_LAYOUT
 #undef GLAUNCH
-  return hipGetLastError();
+  }
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || ga.sched.splits == 1) return e;
+  TailArgs t{};
+  t.n = np;
+  for (int i = 0; i < np; ++i) t.p[i] = TailProblem{ga.p[i].C, ga.p[i].M, ga.p[i].N, ga.p[i].ldc, ga.p[i].tile_begin, ga.p[i].tiles_m, ga.p[i].tiles_n};
+  t.sched = ga.sched; t.scratch = ga.scratch;
+  return launch_tail(mode, t, ga.sched.tail, st);
 }
 
 // Segmented weight-gradient launch: gs[0..n) are accumulate-form (TN, fp32 or bf16 C +=) problems that share C, M, N and the
