@@ -48,6 +48,7 @@ typedef bf16_t bf16x8 __attribute__((ext_vector_type(8)));
 typedef bf16_t bf16x4 __attribute__((ext_vector_type(4)));
 typedef short short4v __attribute__((ext_vector_type(4)));
 typedef short short8v __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 #define LDS_AS(p) ((__attribute__((address_space(3))) void*)(p))
@@ -64,11 +65,9 @@ constexpr int TILE64_BYTES = 64 * ROW_BYTES;   // 16 KiB
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
 
-// LDS tile [rows][128 bf16], 16 chunks of 16 B per row, chunk ^= f(row) with
-// f(row) = ((row&3)<<2)|((row>>2)&3): conflict-free both for 128-bit row-fragment
-// reads (16 consecutive rows, same chunk) and for the transposing 64-bit reads
-// (4 consecutive rows x 32 B).
-__device__ __forceinline__ int swz(int row) { return ((row & 3) << 2) | ((row >> 2) & 3); }
+// LDS tile [rows][128 bf16], 16 chunks of 16 B per row, chunk ^= f(row): conflict-free both for 128-bit row-fragment
+// reads (16 consecutive rows, same chunk) and for the transposing 64-bit reads (4 consecutive rows x 64 B, or 8 x 32 B).
+__device__ __forceinline__ int swz(int row) { return ((row & 3) << 2) | ((((row >> 2) ^ (row >> 3)) & 1) << 1) | ((row >> 3) & 1); }
 __device__ __forceinline__ int tile_off(int row, int chunk) { return row * ROW_BYTES + ((chunk ^ swz(row)) << 4); }
 
 __device__ __forceinline__ bf16x8 pack8(const f32x16& v, int ks) {
@@ -174,165 +173,377 @@ __device__ __forceinline__ void mfma_chain(LoadF load, MmaF mma) {
 // row index (within a 32-row accumulator block) held in register r of a lane in half h
 __device__ __forceinline__ int acc_row(int r, int h) { return 8 * (r >> 2) + 4 * h + (r & 3); }
 
+// ---- 16x16x32 MFMA building blocks (forward) -------------------------------------------------------------------
+// S^T blocks of 16 keys x 16 queries: lane l holds query l % 16 and keys 4 (l / 16) + r.  Two such blocks (32 keys) are the B operand
+// of the next product with slot 8 (l / 16) + j <-> key 16 (j >> 2) + 4 (l / 16) + (j & 3), matched on the A side by two
+// transposing reads 16 rows apart.
+#define MFMA16(a, b, c) __builtin_amdgcn_mfma_f32_16x16x32_bf16((a), (b), (c), 0, 0, 0)
+// fragment of 16 rows x 32 elements (one k32 step): row l % 16, elements 8 (l / 16) .. + 7   (row block b: + b * 4096)
+__device__ __forceinline__ uint32_t frag16_rows(int kk) {
+  const int l = threadIdx.x & 63;
+  return (uint32_t)tile_off(l & 15, kk * 4 + (l >> 4));
+}
+// transposed fragment of 16 columns (head_dim block d) x 32 rows: rows 4 (l / 16) .. + 3 here, rows + 16 at + 4096
+__device__ __forceinline__ uint32_t frag16_tr(int d) {
+  const int l = threadIdx.x & 63, p = l & 15, g = l >> 4;
+  const int col = d * 16 + 4 * (p & 3), row = 4 * g + (p >> 2);
+  return (uint32_t)(tile_off(row, col >> 3) + ((col & 7) << 1));
+}
+// maximum over the four lanes that share a query (l % 16)
+__device__ __forceinline__ float max_raw(float a, float b) {      // v_max_f32 without the quieting moves fmaxf adds for unknown operands
+  float r;
+  asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ float max_over_quads(float x) {
+  typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+  u32x2 r = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false));
+  x = max_raw(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  r = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false));
+  return max_raw(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+#define AT_WAIT_VM(n) asm volatile("s_waitcnt vmcnt(%0)" ::"i"(n) : "memory")
+#define AT_SLOT_BARRIER()                     \
+  do {                                        \
+    __builtin_amdgcn_sched_barrier(0);        \
+    asm volatile("s_barrier" ::: "memory");   \
+    __builtin_amdgcn_sched_barrier(0);        \
+  } while (0)
+// Workgroup -> (query tile, head).  The workgroups of an XCD get a contiguous run of (head, query tile) pairs, so that the heads of one
+// K/V group run on one XCD and share its stream through that L2; the tiles with the most keys come first.
+__device__ __forceinline__ void query_tile_of(int n_qt, int Hq, int& qt, int& h) {
+  const int id = (int)blockIdx.x, n = n_qt * Hq, x = id % 8, q = n / 8, r = n % 8;
+  const int c = x * q + min(x, r) + id / 8;
+  h = c / n_qt;
+  qt = n_qt - 1 - c % n_qt;
+}
+
 // ------------------------------------------------------------------ forward --
-// 8 waves x 32 queries; K/V tiles of 64 keys stream through two LDS stages.  The softmax denominator is taken from
-// the matrix pipe as well (one extra MFMA per k16 step against an all-ones operand sums the rounded probabilities
-// of each query), which takes 32 additions per tile off the vector ALU - the busier of the two units here.
+// 8 waves in two groups of four; waves w and w + 4 share a SIMD.  A key tile costs a wave two slots, each closed by a barrier:
+// multiply (O += P V of the previous tile, S = K Q^T of this one: 68 MFMAs, the softmax denominator - one product against an
+// all-ones operand - among them) and softmax (and the loads of later tiles, spread between the exponentials).  Group 1 runs one
+// slot behind group 0, so on every SIMD one wave multiplies while the other does its exponentials.
+//   SPLIT = false: 256 queries, 32 per wave; all waves walk all key tiles, four K and four V stages (128 KB), loads two to three
+//                  tiles ahead.
+//   SPLIT = true : 128 queries, for launches that would leave CUs idle: the groups take the even / odd key tiles of the same
+//                  queries, each with two stages of its own, and meet in LDS at the end.
+// The running maximum lags by up to 2^8 (O and the denominator are rescaled only when a score passes it by more): bf16
+// probabilities keep their relative precision whatever their size, and the rescaling of 72 registers becomes rare.
+// What bounds it: a slot takes about 1600 cycles at 2.0 GHz where the 68 MFMAs take 1088 - the vector instructions of one wave (about
+// 160, 32 of them exponentials) and the MFMAs of the other share the SIMD's issue port and delay each other; without the vector
+// work a slot takes 1050 cycles, without the MFMAs 1150.  Last 2048-query chunk of 32k, 28 heads: 1110 -> 921 us (32x32x16 MFMAs in
+// the same schedule 965; loads in the multiply slot 954; the next slot's first fragments read early 958).
+template <bool SPLIT>
 __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const bf16_t* __restrict__ k,
                                                                  const bf16_t* __restrict__ v, bf16_t* __restrict__ o,
                                                                  float* __restrict__ lse, int Hq, int Hkv, int q_start,
                                                                  int c, float scale, const float2* __restrict__ rope,
                                                                  int window, int kv_first) {
-  __shared__ __attribute__((aligned(1024))) char sT[4][TILE64_BYTES];   // stage st: K = sT[2 st], V = sT[2 st + 1]
+  __shared__ __attribute__((aligned(1024))) char sT[8 * TILE64_BYTES];   // K stages, then V stages
+  constexpr int QW = SPLIT ? TQ / 2 : TQ;                     // queries of the workgroup
+  constexpr int STAGES = SPLIT ? 2 : 4, K_AHEAD = SPLIT ? 2 : 3, V_AHEAD = SPLIT ? 1 : 2;
+  constexpr int LOADERS = SPLIT ? AT_THREADS / 2 : AT_THREADS, LOADS = 1024 / LOADERS;   // threads that load a tile, 16-byte loads of each
 
-  const int q0 = blockIdx.x * TQ, h = blockIdx.y, kvh = h / (Hq / Hkv);
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5;
-  const int qw0 = q0 + wave * 32;
-  const int my_q = qw0 + (lane & 31);
-  const bool q_valid = my_q < c;
-  const int q_row = min(my_q, c - 1);
-  const int qpos = q_start + q_row;
+  int qt, h;
+  query_tile_of((c + QW - 1) / QW, Hq, qt, h);
+  const int q0 = qt * QW, kvh = h / (Hq / Hkv);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
+  const int grp = wave >> 2;
+  const int qw0 = q0 + (SPLIT ? wave & 3 : wave) * 32;
   const int64_t kv_stride = (int64_t)Hkv * DH;
   const bf16_t* kbase = k + (int64_t)kvh * DH;
   const bf16_t* vbase = v + (int64_t)kvh * DH;
   const int n_total = q_start + c;                                    // rows of K/V that exist for this chunk
-  const int n_keys = q_start + min(q0 + TQ, c);                       // keys visible to the workgroup
+  const int n_keys = q_start + min(q0 + QW, c);                       // keys visible to the workgroup
   const int n_tiles = (n_keys + TK - 1) / TK;
   const int wave_last_key = q_start + min(qw0 + 32, c) - 1;           // last key any query of this wave sees
   const int wave_first_qpos = q_start + qw0;
   // left edge of the visible range: first visible key of a query at position p
   auto first_key = [&](int p) { return max(kv_first, window > 0 ? p - window + 1 : 0); };
-  const int lo_q = first_key(qpos);                                   // of this lane's query
   const int wave_lo_min = first_key(wave_first_qpos);                 // lowest first key in the wave (its first query)
   const int wave_lo_max = first_key(wave_last_key);                   // highest one (its last query)
   const int kt0 = first_key(q_start + q0) / TK;                       // first key tile any query of the workgroup sees
+  const int n_it = SPLIT ? (max(0, n_tiles - kt0) + 1) / 2 : max(0, n_tiles - kt0);
+  auto tile_of = [&](int i) { return SPLIT ? kt0 + 2 * i + grp : kt0 + i; };
 
-  const uint32_t lds0 = lds_addr(&sT[0][0]);
-  const FragPre fp = frag_pre(lds0);
-  const TileLoad<AT_THREADS> tl = tile_load_pre<AT_THREADS>(kv_stride);
-
-  bf16x8 bq[8];
-  {
-    bf16_t* qp = q + ((int64_t)q_row * Hq + h) * DH + half * 8;
+  bf16x8 bq[2][4];      // [16-query block][k32 step]: B operands of S^T = K Q^T
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) bq[ks] = *(const bf16x8*)(qp + ks * 16);
-    if (rope) {
-      // Rotary embedding of the query on load: the lane holds elements ks*16 + half*8 + e of its query, and the
-      // rotate-half partner of element j < 64 is j + 64, i.e. the same e of fragment ks + 4 of the same lane.  The
-      // rotated row is written back so that the backward kernels, which read q through LDS, find it rotated.
-      const float2* tr = rope + (int64_t)q_row * (DH / 2) + half * 8;
+  for (int b = 0; b < 2; ++b) {
+    const int q_row = min(qw0 + b * 16 + li, c - 1);
+    const bf16_t* qp = q + ((int64_t)q_row * Hq + h) * DH + lg * 8;
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks)
+    for (int kk = 0; kk < 4; ++kk) bq[b][kk] = *(const bf16x8*)(qp + kk * 32);
+  }
+  if (rope) {
+    // Rotary embedding of the query on load: the rotate-half partner of element j < 64 is j + 64, i.e. the same element of the
+    // fragment two steps on, in the same lane.  The rotated row is written back so that the backward kernels, which read q
+    // through LDS, find it rotated.
+    if (SPLIT) __syncthreads();      // both groups hold the un-rotated rows
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const int my_q = qw0 + b * 16 + li, q_row = min(my_q, c - 1);
+      const float2* tr = rope + (int64_t)q_row * (DH / 2) + lg * 8;
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          const float2 cs = tr[ks * 16 + e];
-          const float x1 = (float)bq[ks][e], x2 = (float)bq[ks + 4][e];
-          bq[ks][e] = (bf16_t)(x1 * cs.x - x2 * cs.y);
-          bq[ks + 4][e] = (bf16_t)(x2 * cs.x + x1 * cs.y);
+          const float2 cs = tr[kk * 32 + e];
+          const float x1 = (float)bq[b][kk][e], x2 = (float)bq[b][kk + 2][e];
+          bq[b][kk][e] = (bf16_t)(x1 * cs.x - x2 * cs.y);
+          bq[b][kk + 2][e] = (bf16_t)(x2 * cs.x + x1 * cs.y);
         }
-      if (q_valid) {
+      if (my_q < c && (!SPLIT || grp == 0)) {
+        bf16_t* qp = q + ((int64_t)my_q * Hq + h) * DH + lg * 8;
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) *(bf16x8*)(qp + ks * 16) = bq[ks];
+        for (int kk = 0; kk < 4; ++kk) *(bf16x8*)(qp + kk * 32) = bq[b][kk];
       }
     }
   }
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) asm volatile("" : "+v"(bq[b][kk]));   // (arrived: the compiler must not wait for them in the loop)
+  AT_WAIT_VM(0);     // from here on the loop counts its own loads only
+
+  // ---- addresses, computed once: LDS fragments (+ stage, the only part that moves), global loads
+  const uint32_t lds0 = lds_addr(sT);
+  const uint32_t lds_k = lds0 + (SPLIT ? (uint32_t)grp * STAGES * TILE64_BYTES : 0u), lds_v = lds_k + 4 * TILE64_BYTES;
+  uint32_t fr[4], ft[8];
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) fr[kk] = pin(lds_k + frag16_rows(kk));
+#pragma unroll
+  for (int d = 0; d < 8; ++d) ft[d] = pin(lds_v + frag16_tr(d));
+  const int tid = SPLIT ? (int)threadIdx.x & (LOADERS - 1) : (int)threadIdx.x;
+  auto load_offset = [&](int i, int rows_valid) {
+    const int id = i * LOADERS + tid, row = id >> 4, chunk = (id & 15) ^ swz(row);
+    return (uint32_t)(((int64_t)min(row, rows_valid - 1) * kv_stride + chunk * 8) * 2);
+  };
+  // loads of tile i of this wave's sequence; past the end the last tile is loaded again, so that the wait counts stay the same.
+  // The last tile may be short: its rows past the end re-read the last one.
+  const int t_max = n_tiles - 1;
+  uint32_t voff[LOADS], voff_last[LOADS];
+#pragma unroll
+  for (int j = 0; j < LOADS; ++j) { voff[j] = pin(load_offset(j, TK)); voff_last[j] = pin(load_offset(j, min(TK, n_total - t_max * TK))); }
+  const uint32_t dst_k = __builtin_amdgcn_readfirstlane(lds_k + (uint32_t)(tid & ~63) * 16u), tile_bytes = (uint32_t)(TK * kv_stride * 2);
+  // load p (of PIECES) of the pair V(i + V_AHEAD), K(i + K_AHEAD); slot = i modulo the stages
+  constexpr int PIECES = 2 * LOADS;
+  auto issue_piece = [&](int p, int i, int slot) __attribute__((always_inline)) {
+    const bool is_k = p >= LOADS;
+    const int j = p % LOADS, ahead = is_k ? K_AHEAD : V_AHEAD, t = min(tile_of(i + ahead), t_max);
+    const char* src = (const char*)(is_k ? kbase : vbase) + (uint64_t)tile_bytes * (uint32_t)t;
+    dma16(src, t == t_max ? voff_last[j] : voff[j],
+          dst_k + (uint32_t)(((is_k ? 0 : 4) + (slot + ahead) % STAGES) * TILE64_BYTES + j * LOADERS * 16));
+  };
+
   bf16x8 ones;
 #pragma unroll
   for (int e = 0; e < 8; ++e) ones[e] = (bf16_t)1.0f;
-  f32x16 acc_o[4];
+  asm volatile("" : "+v"(ones));
+  f32x4 acc[2][8], acc_l[2], s[2][4];     // O^T [query block][16 head_dim rows], denominator, S^T [query block][16 keys]
+  bf16x8 pb[2][2];                        // P^T: [query block][k32 step]
+  float m_floor = -INFINITY;
+  asm volatile("" : "+v"(m_floor));
+  float m_run[2] = {-INFINITY, -INFINITY}, m_lim[2] = {-INFINITY, -INFINITY}, m_neg[2] = {0.f, 0.f};   // maximum (log2 domain); raw score that moves it; what is added
 #pragma unroll
-  for (int i = 0; i < 4; ++i) acc_o[i] = zero16();
-  f32x16 acc_l = zero16();      // every register of a lane: sum over the keys so far of the probabilities of its query
-  float m_run = -INFINITY;
+  for (int b = 0; b < 2; ++b) {
+#pragma unroll
+    for (int d = 0; d < 8; ++d) acc[b][d] = f32x4{0.f, 0.f, 0.f, 0.f};
+    acc_l[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
   const float sl = scale * LOG2E;
+  // steps in which some (query, key) pair of the wave is visible: tiles wave_lo_min / TK .. wave_last_key / TK
+  const int step_t = SPLIT ? 2 : 1, first_t = tile_of(0);
+  const int act0 = max(0, (wave_lo_min / TK - first_t + step_t - 1) / step_t);
+  const int act1 = qw0 < c && wave_last_key >= 0 ? min(n_it, (wave_last_key / TK - first_t + step_t) / step_t) : 0;
+  auto active = [&](int i) { return i >= act0 && i < act1; };
 
-  auto step = [&](int kt, auto stage) {
-    constexpr uint32_t oK = decltype(stage)::value * 2 * TILE64_BYTES, oV = oK + TILE64_BYTES;
-    const int k0 = kt * TK;
-    if (qw0 >= c || k0 > wave_last_key || k0 + TK - 1 < wave_lo_min) return;   // nothing visible to this wave in the tile
-    f32x16 s[2];
-    s[0] = zero16();
-    s[1] = zero16();
-    mfma_chain<16>([&](int i) { return lds_b128(fp.rows[i & 7] + oK + (i >> 3) * 32 * ROW_BYTES); },
-                   [&](int i, const bf16x8& f) { s[i >> 3] = MFMA(f, bq[i & 7], s[i >> 3]); });
-    const bool diag = k0 + TK - 1 > wave_first_qpos || k0 < wave_lo_max;   // some (query, key) pair of the wave is masked
-    if (diag) {                                           // wave-uniform: only tiles on an edge of the visible range pay for the mask
+  // fragment reads run RING - 1 fragments (two MFMAs each) ahead of the products
+  constexpr int RING = 8;
+  bf16x8 f[RING];
+  auto v_frag = [&](int n, uint32_t st) {      // n = k32 step * 8 + head_dim block
+    return lds_tr(ft[n & 7] + (st + (uint32_t)(n >> 3) * 8192), ft[n & 7] + (st + (uint32_t)(n >> 3) * 8192 + 4096));
+  };
+  auto k_frag = [&](int n, uint32_t st) { return lds_b128(fr[n >> 2] + (st + (uint32_t)(n & 3) * 4096)); };   // n = k32 step * 4 + key block
+  auto pv = [&](int slot) __attribute__((always_inline)) {
+    const uint32_t st = (uint32_t)((slot % STAGES) * TILE64_BYTES);
 #pragma unroll
-      for (int b = 0; b < 2; ++b)
+    for (int n = 0; n < RING - 1; ++n) f[n] = v_frag(n, st);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int key = k0 + b * 32 + acc_row(r, half);
-          if (key > qpos || key < lo_q) s[b][r] = -INFINITY;
+    for (int n = 0; n < 16; ++n) {
+      if (n + RING - 1 < 16) f[(n + RING - 1) % RING] = v_frag(n + RING - 1, st);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        acc[b][n & 7] = MFMA16(f[n % RING], pb[b][n >> 3], acc[b][n & 7]);
+        if ((n & 7) == 7) acc_l[b] = MFMA16(ones, pb[b][n >> 3], acc_l[b]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  auto qk = [&](int slot) __attribute__((always_inline)) {
+    const uint32_t st = (uint32_t)((slot % STAGES) * TILE64_BYTES);
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int kb = 0; kb < 4; ++kb) s[b][kb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int n = 0; n < RING - 1; ++n) f[n] = k_frag(n, st);
+#pragma unroll
+    for (int n = 0; n < 16; ++n) {
+      if (n + RING - 1 < 16) f[(n + RING - 1) % RING] = k_frag(n + RING - 1, st);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int b = 0; b < 2; ++b) s[b][n & 3] = MFMA16(f[n % RING], bq[b][n >> 2], s[b][n & 3]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  auto softmax = [&](int i, int slot) __attribute__((always_inline)) {
+    const int k0 = tile_of(i) * TK;
+    if (k0 + TK - 1 > wave_first_qpos || k0 < wave_lo_max) {   // only tiles on an edge of the visible range pay for the mask
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        // key 4 lg + e of the tile is visible for first <= e < first + n: one unsigned comparison
+        const int qpos = q_start + min(qw0 + b * 16 + li, c - 1), lo = first_key(qpos);
+        const int first = lo - k0 - 4 * lg;
+        const uint32_t n = (uint32_t)max(0, qpos - lo + 1);
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) s[b][kb][r] = (uint32_t)(kb * 16 + r - first) < n ? s[b][kb][r] : -INFINITY;
+          __builtin_amdgcn_sched_barrier(0);
         }
+      }
     }
-    float mx = s[0][0];                                   // max of the raw scores (scale > 0 keeps the order)
+    float mx[2];                                            // max of the raw scores (scale > 0 keeps the order)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < 2; ++b) {
+      float m2[2];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[b][r]);
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * sl;
-    // The running max (and with it the rescale of O) only moves when some query of the wave sees a new maximum.
-    if (__builtin_amdgcn_ballot_w64(mx > m_run) != 0) {
-      const float m_new = fmaxf(m_run, mx);
-      const float alpha = m_new == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m_run - m_new);   // a query that has seen no key yet keeps its zeros
-      m_run = m_new;
+      for (int x = 0; x < 2; ++x) {
+        m2[x] = m_floor;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc_l[r] *= alpha;
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc_o[i][r] *= alpha;
+        for (int e = 0; e < 8; ++e) m2[x] = fmaxf(m2[x], s[b][2 * x + (e >> 2)][e & 3]);
+      }
+      mx[b] = max_raw(m2[0], m2[1]);
     }
-    const float m_sub = m_run == -INFINITY ? 0.0f : m_run;    // all scores so far masked: exp2(-inf - 0) = 0, not exp2(-inf + inf)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < 2; ++b) mx[b] = max_over_quads(mx[b]);
+    constexpr float LAG = 8.0f;
+    if (__builtin_amdgcn_ballot_w64(mx[0] > m_lim[0] || mx[1] > m_lim[1]) != 0) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) s[b][r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[b][r], sl, -m_sub));
-    bf16x8 pb[4];     // P^T of the tile as four B operands: index = block * 2 + k16 step
+      for (int b = 0; b < 2; ++b) {
+        const float m_new = mx[b] > m_lim[b] ? mx[b] * sl : m_run[b];     // each query by its own scores alone
+        const float alpha = m_new == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m_run[b] - m_new);   // a query that has seen no key yet keeps its zeros
+        m_run[b] = m_new;
+        m_lim[b] = (m_new + LAG) / sl;
+        m_neg[b] = m_new == -INFINITY ? 0.0f : -m_new;        // all scores so far masked: exp2(-inf - 0) = 0, not exp2(-inf + inf)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) pb[j] = pack8(s[j >> 1], j & 1);
-    mfma_chain<16>([&](int i) { return lds_tr(fp.tr[(i & 3) * 2] + oV + (i >> 2) * 16 * ROW_BYTES, fp.tr[(i & 3) * 2 + 1] + oV + (i >> 2) * 16 * ROW_BYTES); },
-                   [&](int i, const bf16x8& f) {
-                     acc_o[i & 3] = MFMA(f, pb[i >> 2], acc_o[i & 3]);
-                     if ((i & 3) == 3) acc_l = MFMA(ones, pb[i >> 2], acc_l);
-                   });
+        for (int r = 0; r < 4; ++r) acc_l[b][r] *= alpha;
+#pragma unroll
+        for (int d = 0; d < 8; ++d)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) acc[b][d][r] *= alpha;
+      }
+    }
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {        // eight probabilities at a time, the loads spread between them
+      const int b = x >> 1, kk = x & 1;
+#pragma unroll
+      for (int p = 0; p < PIECES / 4; ++p) issue_piece(x * (PIECES / 4) + p, i, slot);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        pb[b][kk][e] = (bf16_t)__builtin_amdgcn_exp2f(__builtin_fmaf(s[b][2 * kk + (e >> 2)][e & 3], sl, m_neg[b]));
+      __builtin_amdgcn_sched_barrier(0);
+    }
   };
-  auto issue = [&](int kt, int st) {
-    const int64_t row0 = (int64_t)kt * TK;
-    dma_tile64(tl, kbase + row0 * kv_stride, kv_stride, n_total - kt * TK, lds0 + (uint32_t)(st * 2 * TILE64_BYTES));
-    dma_tile64(tl, vbase + row0 * kv_stride, kv_stride, n_total - kt * TK, lds0 + (uint32_t)((st * 2 + 1) * TILE64_BYTES));
-  };
-  using S0 = std::integral_constant<int, 0>;
-  using S1 = std::integral_constant<int, 1>;
 
-  if (kt0 < n_tiles) issue(kt0, 0);
-  for (int kt = kt0; kt < n_tiles; kt += 2) {
-    WAIT_VM0();
-    __syncthreads();
-    if (kt + 1 < n_tiles) issue(kt + 1, 1);
-    step(kt, S0{});
-    if (kt + 1 < n_tiles) {
-      WAIT_VM0();
-      __syncthreads();
-      if (kt + 2 < n_tiles) issue(kt + 2, 0);
-      step(kt + 1, S1{});
+  if (n_it > 0) {
+    // loads are issued in the order K(0) | V(0) K(1) | V(1) K(2) ...: per softmax slot i, V(i + V_AHEAD) and K(i + K_AHEAD)
+#pragma unroll
+    for (int j = 0; j <= V_AHEAD; ++j)
+#pragma unroll
+      for (int p = j == 0 ? LOADS : 0; p < PIECES; ++p) issue_piece(p, j - 1 - V_AHEAD, j - 1 - V_AHEAD + 2 * STAGES);
+    AT_WAIT_VM(PIECES * V_AHEAD);
+    AT_SLOT_BARRIER();
+    if (grp == 1) AT_SLOT_BARRIER();        // group 1 falls one slot behind ...
+    auto step = [&](int i, int slot) __attribute__((always_inline)) {      // slot = i % 4, a constant: every stage is an immediate offset
+      __builtin_amdgcn_s_setprio(1);
+      if (active(i - 1)) pv(slot + 3);
+      if (active(i)) qk(slot);
+      __builtin_amdgcn_s_setprio(0);
+      // Before a tile is read every wave has waited for its own share of it and a barrier has passed: V(i), K(i + 1) by group 0 in
+      // its softmax slot, by group 1, one slot behind, at the end of this one (the two later pairs of tiles issued by
+      // then stay in flight, one for group 1 and if SPLIT).
+      if (!SPLIT && grp == 1) AT_WAIT_VM(PIECES * (V_AHEAD - 1));
+      AT_SLOT_BARRIER();
+      if (active(i)) softmax(i, slot);
+      else {
+#pragma unroll
+        for (int p = 0; p < PIECES; ++p) issue_piece(p, i, slot);
+      }
+      if (SPLIT || grp == 0) AT_WAIT_VM(PIECES * V_AHEAD);
+      AT_SLOT_BARRIER();
+    };
+    // whole groups of four steps (a step past the last tile is two barriers and nothing else)
+    int i = 0;
+    for (; i < n_it; i += 4) {
+      step(i, 0);
+      step(i + 1, 1);
+      step(i + 2, 2);
+      step(i + 3, 3);
     }
+    if (active(i - 1)) pv(3);
+    AT_WAIT_VM(0);
+    if (grp == 0) AT_SLOT_BARRIER();        // ... and group 0 waits for it here: both execute the same number of barriers
   }
 
-  const float l_tot = acc_l[0];
-  if (q_valid) {
-    const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.0f;      // a query that saw no key: o = 0, lse = -inf
-    bf16_t* op = o + ((int64_t)my_q * Hq + h) * DH;
+  if constexpr (SPLIT) {
+    // the two halves of the keys meet in LDS: group 1 leaves (maximum, denominator, O), group 0 merges
+    __syncthreads();
+    float* mine = (float*)(sT + (wave & 3) * (72 * 256)) + lane;      // [float][lane]
+    if (grp == 1) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+      for (int b = 0; b < 2; ++b) {
+        mine[(b * 36 + 0) * 64] = m_run[b];
+        mine[(b * 36 + 1) * 64] = acc_l[b][0];
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        bf16x4 w;
+        for (int d = 0; d < 8; ++d)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) w[e] = (bf16_t)(acc_o[i][4 * a + e] * inv);
-        *(bf16x4*)(op + i * 32 + 8 * a + 4 * half) = w;
+          for (int r = 0; r < 4; ++r) mine[(b * 36 + 4 + d * 4 + r) * 64] = acc[b][d][r];
       }
-    if (half == 0) lse[(int64_t)h * c + my_q] = l_tot > 0.f ? (m_run + log2f(l_tot)) * LN2 : -INFINITY;
+    }
+    __syncthreads();
+    if (grp == 1) return;
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const float m1 = mine[(b * 36 + 0) * 64], l1 = mine[(b * 36 + 1) * 64];
+      const float m_new = fmaxf(m_run[b], m1);
+      const float f0 = m_run[b] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m_run[b] - m_new);
+      const float f1 = m1 == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m1 - m_new);
+      m_run[b] = m_new;
+      acc_l[b][0] = acc_l[b][0] * f0 + l1 * f1;
+#pragma unroll
+      for (int d = 0; d < 8; ++d)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[b][d][r] = acc[b][d][r] * f0 + mine[(b * 36 + 4 + d * 4 + r) * 64] * f1;
+    }
+  }
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    const int my_q = qw0 + b * 16 + li;
+    if (my_q >= c) continue;
+    const float l_tot = acc_l[b][0];
+    const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.0f;      // a query that saw no key: o = 0, lse = -inf
+    bf16_t* op = o + ((int64_t)my_q * Hq + h) * DH + 4 * lg;
+#pragma unroll
+    for (int d = 0; d < 8; ++d) {
+      bf16x4 w;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) w[r] = (bf16_t)(acc[b][d][r] * inv);
+      *(bf16x4*)(op + d * 16) = w;
+    }
+    if (lg == 0) lse[(int64_t)h * c + my_q] = l_tot > 0.f ? (m_run[b] + log2f(l_tot)) * LN2 : -INFINITY;
   }
 }
 
@@ -712,9 +923,14 @@ bool attn_mfma_aligned(const AttnArgs& a, bool backward) {
 
 hipError_t attn_forward_mfma(const AttnArgs& a, hipStream_t st) {
   if (a.q_len == 0) return hipSuccess;
-  dim3 grid((unsigned)cdiv(a.q_len, TQ), a.Hq);
-  attn_fwd_mfma_k<<<grid, AT_THREADS, 0, st>>>((bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v, (bf16_t*)a.o, a.lse,
-                                               a.Hq, a.Hkv, a.q_start, a.q_len, a.scale, a.rope_q, a.window, a.kv_first);
+  // rounds of 256 workgroups (one per CU), a half tile costing half a round: the half tiles where they leave fewer CUs idle
+  const int64_t full = cdiv(a.q_len, TQ) * a.Hq, halves = cdiv(a.q_len, TQ / 2) * a.Hq;
+  auto launch = [&](auto kernel, int64_t n) {
+    kernel<<<(unsigned)n, AT_THREADS, 0, st>>>((bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v, (bf16_t*)a.o, a.lse, a.Hq, a.Hkv,
+                                               a.q_start, a.q_len, a.scale, a.rope_q, a.window, a.kv_first);
+  };
+  if (2 * cdiv(full, 256) > cdiv(halves, 256)) launch(attn_fwd_mfma_k<true>, halves);
+  else launch(attn_fwd_mfma_k<false>, full);
   return hipGetLastError();
 }
 
