@@ -513,10 +513,10 @@ def debug_mfma_rate(operands, workgroups=512, iters=10000, repeats=12, lds_reads
 
 def _profile_kind_names():
     lay = (("false, true", "NT"), ("false, false", "NN"), ("true, false", "TN"))
-    names = [f"gemm_mfma_k<{t}, {m}>" for t, _ in lay for m in (0, 1, 2, 8)]
-    names += [f"gemm_mfma_group_k<{t}, {m}>" for t, _ in lay for m in (0, 1, 2, 8)]
+    names = [f"gemm_mfma_k<{t}, {m}>" for t, _ in lay for m in range(4)]
+    names += [f"gemm_mfma_group_k<{t}, {m}>" for t, _ in lay for m in range(4)]
     names += ["gemm_generic_k", "attn_fwd (launch sequence)", "attn_bwd (delta + dq + dkv launch sequence)", "gemm_mfma_seg_k",
-              "gemm_mfma_k<false, true, 5>", "gemm_mfma_k<false, false, 6>", "gemm_mfma_k<false, true, 7>", "gemm_mfma_k<false, true, 9>"]
+              "gemm_mfma_k<false, true, 5>", "gemm_mfma_k<false, false, 6>", "gemm_mfma_k<false, true, 7>"]
     return tuple(names)
 
 

@@ -572,6 +572,7 @@ struct HeadWs {
   int dw_group;
   float* z; void* dz[MAX_DW_GROUP]; float *row_loss, *target_logit, *seq_weight, *ell;
   float2* stats; int n_stat;          // per row and 256-column block of the chunk's logits: (max, sum of exp), written by the logits GEMM
+  int64_t ldz;                        // row stride of z and dz: bf16 rows are padded to the GEMMs' reduction step (zeros), so that any vocabulary fits
   int32_t *index, *chunk_rows; void *hc[MAX_DW_GROUP], *dhc;   // active-row compaction: row list, rows per chunk, gathered h / dh rows
   float* gemm_scratch; size_t gemm_scratch_bytes; size_t bytes;
 };
@@ -580,9 +581,10 @@ static HeadWs carve_head(const sbp_head_cfg* c, void* ws) {
   const size_t cm = (size_t)std::min<int64_t>(c->chunk, rows);
   Carver cv(ws);
   HeadWs h;
-  h.z = cv.take<float>(cm * c->vocab);
+  h.ldz = c->dtype == SBP_BF16 ? (int64_t)align_up((size_t)c->vocab, 64) : c->vocab;
+  h.z = cv.take<float>(cm * (size_t)h.ldz);
   h.dw_group = dw_group_for(cm, c->dw_group_rows, DW_GROUP_ROWS_HEAD);
-  for (int g = 0; g < h.dw_group; ++g) h.dz[g] = cv.take_bytes(cm * c->vocab * dtype_size(c->dtype));
+  for (int g = 0; g < h.dw_group; ++g) h.dz[g] = cv.take_bytes(cm * (size_t)h.ldz * dtype_size(c->dtype));
   h.row_loss = cv.take<float>(cm);
   h.target_logit = cv.take<float>(cm);
   h.n_stat = (int)cdiv(c->vocab, GEMM_STAT_COLS);
@@ -647,12 +649,16 @@ int32_t streambp_lmhead_ce_backward(const sbp_head_cfg* c, const void* w, const 
     // The logits: fp32 with (max, sum of exp) per row and 256-column block out of the GEMM's epilogue where the MFMA kernel
     // takes the problem - or, better, never as logits at all: the numerator form leaves exp(z - block max) in bf16 directly in
     // the chunk's dz buffer plus the target logits, and the row kernel finishes dz in place.
+    // bf16 rows of z and dz are padded to a multiple of 64, dz with zeros: the products with dz need no particular vocabulary.
+    const bool padded = dt == DT_BF16;
     GemmArgs gz = fwd_gemm(hc, w, s.z, n, V, d, dt, DT_F32);
+    gz.ldc = s.ldz; gz.c_padded = padded;
     gz.rows_dev = n_dev;
     gz.row_stats = s.stats;
     bool numer = false;
     if ((fusion_mask() & FUSE_NUMERATORS) && dt == DT_BF16 && s.n_stat > 0) {
       GemmArgs gn = fwd_gemm(hc, w, dz, n, V, d, dt, DT_BF16);
+      gn.ldc = s.ldz;
       gn.rows_dev = n_dev; gn.row_stats = s.stats;
       gn.numer_targets = targets; gn.numer_row_index = idx; gn.numer_target_value = s.target_logit;
       if (gemm_numerators_supported(gn)) { gz = gn; numer = true; }
@@ -663,7 +669,7 @@ int32_t streambp_lmhead_ce_backward(const sbp_head_cfg* c, const void* w, const 
     HeadRowArgs a{};
     a.stats = stats ? s.stats : nullptr; a.n_stat = s.n_stat;
     a.target_logit = numer ? s.target_logit : nullptr;
-    a.dt = dt; a.objective = c->objective; a.z = s.z; a.dz = dz; a.targets = targets;
+    a.dt = dt; a.objective = c->objective; a.z = s.z; a.dz = dz; a.ldz = s.ldz; a.targets = targets;
     a.old_logp = old_logp; a.ref_logp = ref_logp;
     a.advantages = advantages; a.seq_weight = s.seq_weight; a.row0 = 0; a.row_index = idx; a.rows_dev = n_dev;
     a.rows = n; a.V = V; a.T = c->seq_len;
@@ -672,10 +678,12 @@ int32_t streambp_lmhead_ce_backward(const sbp_head_cfg* c, const void* w, const 
     HIPCHK(head_rows(a, st));
     HIPCHK(reduce_add(s.row_loss, n, c->objective == SBP_OBJ_DPO ? s.ell : loss, st, n_dev));
     GemmArgs gh = dx_gemm(dz, w, s.dhc, n, V, d, dt, dt, false);
+    gh.lda = s.ldz; gh.a_padded = padded;
     gh.rows_dev = n_dev;
     HIPCHK(gemm(gh, st));
     HIPCHK(scatter_rows(dt, s.dhc, idx, n_dev, dh, n, d, st));
     pending[n_pending] = dw_gemm(dz, hc, dw, n, V, d, dt, c->grad_dtype);
+    pending[n_pending].lda = s.ldz; pending[n_pending].a_padded = padded;
     pending[n_pending].rows_dev = n_dev;
     if (++n_pending == s.dw_group || ci + 1 == n_chunks) {
       HIPCHK(gemm_batch(pending, n_pending, st));
@@ -742,13 +750,13 @@ int32_t streambp_attn_chunk_backward(const sbp_attn_cfg* c, const void* q, const
 
 // Which kernels a configuration gets.  The bf16 MFMA GEMMs need every matrix dimension of the layer (hidden, the q and
 // k/v widths, mlp_width - resp. hidden and vocab for the head) to be a multiple of 64 (the reduction step; output tiles
-// are 256 wide with a masked ragged last tile), the MFMA attention head_dim 128; anything else runs on the
-// shape-agnostic fp32-ALU kernels, which are a correctness path and orders of magnitude slower.
+// are 256 wide with a masked ragged last tile), the MFMA attention head_dim 128.  64-wide heads and other vocabularies run on MFMA
+// kernels too, below the full rate; anything else runs on the shape-agnostic fp32 kernels, which are much slower.
 int32_t streambp_layer_fast_path(const sbp_layer_cfg* c) {
   if (int32_t rc = check_layer_cfg(c)) return rc;
   if (c->dtype != SBP_BF16) return fail(0, "fp32 storage: the shape-agnostic kernels are the only path"), 0;
   const int qd = c->n_q_heads * c->head_dim, kd = c->n_kv_heads * c->head_dim;
-  if (c->head_dim != 128) return fail(0, "head_dim %d: the MFMA attention kernels take 128 only", c->head_dim), 0;
+  if (c->head_dim != 128) return fail(0, "head_dim %d: the full-rate MFMA attention kernels take 128 only", c->head_dim), 0;
   const int dims[4] = {c->hidden, qd, kd, c->mlp_width};
   const char* names[4] = {"hidden", "n_q_heads*head_dim", "n_kv_heads*head_dim", "mlp_width"};
   for (int i = 0; i < 4; ++i)   // every width is the reduction length of some GEMM of the layer
@@ -759,7 +767,7 @@ int32_t streambp_lmhead_fast_path(const sbp_head_cfg* c) {
   if (int32_t rc = check_head_cfg(c)) return rc;
   if (c->dtype != SBP_BF16) return fail(0, "fp32 storage: the shape-agnostic kernels are the only path"), 0;
   if (c->hidden % 64) return fail(0, "hidden = %d is not a multiple of 64: the head's GEMMs leave the MFMA kernels", c->hidden), 0;
-  if (c->vocab % 64) return fail(0, "vocab = %d is not a multiple of 64: the head's GEMMs leave the MFMA kernels", c->vocab), 0;
+  if (c->vocab % 64) return fail(0, "vocab = %d is not a multiple of 64: its rows are padded, and fp32 logits kept where it is no multiple of 8", c->vocab), 0;
   return 1;
 }
 int64_t streambp_generic_launches(void) { return (int64_t)generic_bf16_launches(); }

@@ -16,9 +16,6 @@ bool gemm_mfma_pair_ok(const GemmArgs& g);
 bool gemm_mfma_stats_ok(const GemmArgs& g);
 bool gemm_mfma_swiglu_ok(const GemmArgs& g);
 bool gemm_mfma_numer_ok(const GemmArgs& g);
-bool gemm_mfma_scatter_ok(const GemmArgs& g);
-bool gemm_mfma_exp_ok(const GemmArgs& g);
-hipError_t gemm_mfma_marked(const GemmArgs& g, const int32_t* tile_marks, const int32_t* row_marks, hipStream_t st);
 bool gemm_mfma_group_eligible(const GemmArgs* gs, int n, bool small_ok);
 hipError_t gemm_mfma_group(const GemmArgs* gs, int n, hipStream_t st);
 bool gemm_mfma_seg_eligible(const GemmArgs* gs, int n);
@@ -46,10 +43,6 @@ void attn_set_force_generic(bool on) { g_force_generic_attn = on; }
 bool gemm_uses_mfma(const GemmArgs& g) { return !g_force_generic_gemm && gemm_mfma_eligible(g); }
 bool gemm_row_stats_supported(const GemmArgs& g) { return gemm_uses_mfma(g) && gemm_mfma_stats_ok(g); }
 bool gemm_numerators_supported(const GemmArgs& g) { return gemm_uses_mfma(g) && gemm_mfma_numer_ok(g); }
-bool gemm_exp_supported(const GemmArgs& g) { return gemm_uses_mfma(g) && gemm_mfma_exp_ok(g); }
-hipError_t gemm_marked_rows(const GemmArgs& g, const int32_t* tile_marks, const int32_t* row_marks, hipStream_t st) {
-  return gemm_numerators_supported(g) && g.rows_dev ? gemm_mfma_marked(g, tile_marks, row_marks, st) : hipErrorInvalidValue;
-}
 bool attn_uses_mfma(int dt, int dh, int Hq, int Hkv) { return !g_force_generic_attn && attn_mfma_eligible(dt, dh, Hq, Hkv); }
 
 // ---- optional per-launch timing (off by default; events are created when profiling is switched on,
@@ -83,11 +76,7 @@ static double causal_pairs(const AttnArgs& a) {   // visible (query, key) pairs 
 }
 
 hipError_t gemm(const GemmArgs& g, hipStream_t st) {
-  if (g.row_sums) {
-    if (!gemm_exp_supported(g)) return hipErrorInvalidValue;
-  } else if (g.row_scale) {
-    if (!(gemm_uses_mfma(g) && gemm_mfma_scatter_ok(g))) return hipErrorInvalidValue;
-  } else if (g.numer_targets) {
+  if (g.numer_targets) {
     if (!gemm_numerators_supported(g)) return hipErrorInvalidValue;               // only the MFMA store form has them
   } else if (g.row_stats && !gemm_row_stats_supported(g)) return hipErrorInvalidValue;   // only the MFMA store form emits them
   if (g.swiglu_gate && !(gemm_uses_mfma(g) && gemm_mfma_swiglu_ok(g))) {   // no fused epilogue for this problem: product, then the elementwise kernel

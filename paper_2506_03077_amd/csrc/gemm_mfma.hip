@@ -146,16 +146,11 @@ __device__ __forceinline__ int xcd_contiguous_id(int id, int n_tiles) {
 //       5 = store fp32 and emit per-row (max, sum of exp) pairs over the tile's columns (`stats`)
 //       6 = C is not stored: the tile is the gradient wrt act = silu(gate) * up and the epilogue writes act, d gate, d up
 //       7 = like 5, but C (bf16) receives exp(c - block max) instead of c, and the value of each row's target column is kept
-//       8 = store bf16 rows scaled by a per-row factor, row m to row index[m] of C
-//       9 = C (bf16) receives exp(c), columns N .. ldc zeros; the tile's row sums and the value of each row's target column are kept
 constexpr bool mode_accumulates(int mode) { return mode == 2 || mode == 4; }
-constexpr bool mode_splits(int mode) { return mode <= 2 || mode == 8; }      // forms whose reduction may be split over workgroups
+constexpr bool mode_splits(int mode) { return mode <= 2; }      // forms whose reduction may be split over workgroups
 constexpr int PARTIAL_FLOATS = BM * BN;
-constexpr int EPI_OFFSET = SMEM_BYTES;                                         // mode 9 keeps 4 KB of row sums behind the staged tile
-constexpr int smem_bytes(int mode) { return SMEM_BYTES + (mode == 9 ? NWAVE_N * BM * 4 : 0); }
 struct SwigluFuse { bf16_t* gate; bf16_t* up; bf16_t* act; };
-struct NumerFuse { const int32_t* targets; const int32_t* row_index; float* target_value; const int32_t* row_mask; };
-struct RowFuse { const float* scale; const int32_t* index; };
+struct NumerFuse { const int32_t* targets; const int32_t* row_index; float* target_value; };
 // The reduction may come in several segments (operand pairs of the same shape and leading dimensions whose products
 // are summed into the same output tile): one accumulator, one epilogue.
 constexpr int MAX_SEG = 8;
@@ -182,7 +177,7 @@ template <bool TA, bool TB, int MODE, typename SegmentF>
 __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void* __restrict__ Cv, int M, int N, int64_t lda,
                                           int64_t ldb, int64_t ldc, int tm, int tn, char* smem,
                                           float* __restrict__ partial = nullptr, void* __restrict__ stats_out = nullptr,
-                                          SwigluFuse sw = SwigluFuse{}, NumerFuse nf = NumerFuse{}, RowFuse rf = RowFuse{}) {
+                                          SwigluFuse sw = SwigluFuse{}, NumerFuse nf = NumerFuse{}) {
   constexpr bool AMN = TA, BMN = !TB;     // operand kept reduction-major in LDS (B stored [N,K] is the K-contiguous case)
   const int m0 = tm * BM, n0 = tn * BN;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -358,13 +353,12 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
       return;
     }
   }
-  if constexpr (MODE == 1 || MODE == 8) {
+  if constexpr (MODE == 1) {
     __syncthreads();
 #pragma unroll
     for (int ha = 0; ha < 2; ++ha)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const float scale = MODE == 8 ? rf.scale[min(m0 + row_of(ha, i), M - 1)] : 1.0f;
 #pragma unroll
         for (int hb = 0; hb < 2; ++hb)
 #pragma unroll
@@ -372,7 +366,7 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
             const int row = row_of(ha, i), col = col_of(hb, j);
             bf16x4 o;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) o[r] = (bf16_t)(MODE == 8 ? acc[ha][hb][i][j][r] * scale : acc[ha][hb][i][j][r]);
+            for (int r = 0; r < 4; ++r) o[r] = (bf16_t)acc[ha][hb][i][j][r];
             *(bf16x4*)(smem + row * 512 + (((col >> 3) ^ (row & 15)) << 4) + ((col & 4) << 1)) = o;
           }
       }
@@ -382,10 +376,7 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
     for (int p = 0; p < 16; ++p) {
       const int row = p * 16 + (threadIdx.x >> 5);
       const i32x4 v = *(const i32x4*)(smem + row * 512 + ((c16 ^ (row & 15)) << 4));
-      if (m0 + row < M && col < N) {
-        const int64_t r_out = MODE == 8 ? (int64_t)rf.index[m0 + row] : (int64_t)(m0 + row);
-        *(i32x4*)(Cb + r_out * ldc + col) = v;
-      }
+      if (m0 + row < M && col < N) *(i32x4*)(Cb + (int64_t)(m0 + row) * ldc + col) = v;
     }
     return;
   }
@@ -456,53 +447,6 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
     }
     return;
   }
-  if constexpr (MODE == 9) {
-    // Softmax over the columns of C with a fixed reference: bf16 keeps its relative precision over the whole exponent range, so
-    // exp(c) itself serves as the numerator (no maximum, no exchange between the waves before the exponentials) as long as
-    // the row's sum stays within what the row kernel checks.  The sums are taken from the unrounded values.
-    constexpr float LOG2E = 1.4426950408889634f;
-    float* psum = (float*)(smem + EPI_OFFSET);        // [NWAVE_N][BM], behind the staged tile
-    float* stats = (float*)stats_out;
-    __syncthreads();
-#pragma unroll
-    for (int ha = 0; ha < 2; ++ha)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int row = row_of(ha, i);
-        const int d = m0 + row < M ? nf.targets[nf.row_index[m0 + row]] - n0 : -1;
-        float se = 0.f;
-#pragma unroll
-        for (int hb = 0; hb < 2; ++hb)
-#pragma unroll
-          for (int j = 0; j < 2; ++j) {
-            const int col = col_of(hb, j);
-            bf16x4 o;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const float z = acc[ha][hb][i][j][r];
-              if (d == col + r) nf.target_value[m0 + row] = z;          // (targets lie in [0, N))
-              const float ex = n0 + col + r < N ? __builtin_amdgcn_exp2f(z * LOG2E) : 0.0f;
-              se += ex;
-              o[r] = (bf16_t)ex;
-            }
-            *(bf16x4*)(smem + row * 512 + (((col >> 3) ^ (row & 15)) << 4) + ((col & 4) << 1)) = o;
-          }
-        se += __shfl_xor(se, 16, WAVE);
-        se += __shfl_xor(se, 32, WAVE);
-        if (lane < 16) psum[wn * BM + row] = se;
-      }
-    __syncthreads();
-    const int c16 = threadIdx.x & 31, col = n0 + c16 * 8;
-#pragma unroll
-    for (int p = 0; p < 16; ++p) {
-      const int row = p * 16 + (threadIdx.x >> 5);
-      const i32x4 v = *(const i32x4*)(smem + row * 512 + ((c16 ^ (row & 15)) << 4));
-      if (m0 + row < M && col < (int)ldc) *(i32x4*)(Cb + (int64_t)(m0 + row) * ldc + col) = v;
-    }
-    if ((int)threadIdx.x < BM && m0 + (int)threadIdx.x < M)
-      stats[(int64_t)(m0 + (int)threadIdx.x) * ((N + BN - 1) / BN) + tn] = (psum[threadIdx.x] + psum[BM + threadIdx.x]) + (psum[2 * BM + threadIdx.x] + psum[3 * BM + threadIdx.x]);
-    return;
-  }
   if constexpr (MODE == 5 || MODE == 7) {
     float2* stats = (float2*)stats_out;
     // Row statistics for a softmax over the columns of C: every row of the tile gets (max, sum of exp(c - max)) over
@@ -529,11 +473,10 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
 #pragma unroll
           for (int j = 0; j < 2; ++j) {
             const int col = col_of(hb, j);
-            if (n0 + col >= N) {               // ragged last column tile: columns past N take no part
+            if (MODE == 5 && row < M && n0 + col < N) *(f32x4*)(Cf + (int64_t)row * ldc + n0 + col) = acc[ha][hb][i][j];
+            if (n0 + col + 3 >= N) {           // ragged last column tile: columns past N take no part
 #pragma unroll
-              for (int r = 0; r < 4; ++r) acc[ha][hb][i][j][r] = -INFINITY;
-            } else if (MODE == 5 && row < M) {
-              *(f32x4*)(Cf + (int64_t)row * ldc + n0 + col) = acc[ha][hb][i][j];
+              for (int r = 0; r < 4; ++r) acc[ha][hb][i][j][r] = n0 + col + r < N ? acc[ha][hb][i][j][r] : -INFINITY;
             }
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
@@ -566,7 +509,7 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
               se += ex;
               o[r] = (bf16_t)ex;
             }
-            if (MODE == 7 && row < M && n0 + col_of(hb, j) < N && (!nf.row_mask || nf.row_mask[row])) *(bf16x4*)(Cb + (int64_t)row * ldc + n0 + col_of(hb, j)) = o;
+            if (MODE == 7 && row < M && n0 + col_of(hb, j) < N) *(bf16x4*)(Cb + (int64_t)row * ldc + n0 + col_of(hb, j)) = o;
           }
         se += __shfl_xor(se, 16, WAVE);
         se += __shfl_xor(se, 32, WAVE);
@@ -661,8 +604,8 @@ __global__ __launch_bounds__(NTHREADS) void gemm_mfma_k(const bf16_t* __restrict
                                                         int64_t ldb, int64_t ldc, const int* __restrict__ rows_dev,
                                                         const bf16_t* __restrict__ A2, const bf16_t* __restrict__ B2,
                                                         float* __restrict__ scratch, int scratch_tiles, void* __restrict__ row_stats,
-                                                        SwigluFuse sw, NumerFuse nf, RowFuse rf) {
-  __shared__ __attribute__((aligned(1024))) char smem[smem_bytes(MODE)];
+                                                        SwigluFuse sw, NumerFuse nf) {
+  __shared__ __attribute__((aligned(1024))) char smem[SMEM_BYTES];
   if (rows_dev) {                     // run-time row count: rows are M (NT / NN) or the reduction K (dW form)
     const int rows = max(0, *rows_dev);
     if (TA) K = min(K, rows); else M = min(M, rows);
@@ -686,26 +629,7 @@ __global__ __launch_bounds__(NTHREADS) void gemm_mfma_k(const bf16_t* __restrict
     const int b = max(s0 - i * k_steps, 0) * BK, e = min(min(s1 - i * k_steps, k_steps) * BK, K);
     return KSegment{i ? A2 : A, i ? B2 : B, b, e};
   };
-  gemm_tile<TA, TB, MODE>(A2 ? 2 : 1, segment, Cv, M, N, lda, ldb, ldc, tm, tn, smem, partial, row_stats, sw, nf, rf);
-}
-
-// The softmax-numerator product (mode 7) again, only for the row tiles that hold a marked row and storing only those rows: a
-// launch that usually finds no mark and ends at once, hence a grid of one workgroup per CU that walks the tiles.
-__global__ __launch_bounds__(NTHREADS) void gemm_mfma_marked_k(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, void* __restrict__ C,
-                                                               int M, int N, int K, int64_t lda, int64_t ldb, int64_t ldc,
-                                                               const int* __restrict__ rows_dev, const int32_t* __restrict__ tile_marks,
-                                                               void* __restrict__ row_stats, NumerFuse nf) {
-  __shared__ __attribute__((aligned(1024))) char smem[SMEM_BYTES];
-  M = min(M, max(0, *rows_dev));
-  const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
-  for (int tm = 0; tm < tiles_m; ++tm) {
-    if (tile_marks[tm] == 0) continue;
-    for (int tn = blockIdx.x; tn < tiles_n; tn += gridDim.x) {
-      __syncthreads();
-      gemm_tile<false, true, 7>(1, [&](int) { return KSegment{A, B, 0, K}; }, C, M, N, lda, ldb, ldc, tm, tn, smem, nullptr, row_stats,
-                                SwigluFuse{}, nf);
-    }
-  }
+  gemm_tile<TA, TB, MODE>(A2 ? 2 : 1, segment, Cv, M, N, lda, ldb, ldc, tm, tn, smem, partial, row_stats, sw, nf);
 }
 
 // Weight-gradient form with a segmented reduction: C += sum_s A_s^T B_s, every segment with its own run-time row
@@ -771,7 +695,6 @@ struct TailArgs {
   const int* rows_dev;          // run-time row count of p[0] (single problems): the schedule is then made again from it
   int k_steps, scratch_tiles;
   const float* scratch;
-  RowFuse rf;
 };
 template <int MODE>
 __global__ __launch_bounds__(256) void splitk_tail_k(const TailArgs ta) {
@@ -800,12 +723,11 @@ __global__ __launch_bounds__(256) void splitk_tail_k(const TailArgs ta) {
     const float* src = ta.scratch + (int64_t)t * PARTIAL_FLOATS + row_l * BN + col_l;
     f32x4 v = *(const f32x4*)src;
     for (int z = 1; z < sc.splits; ++z) v += *(const f32x4*)(src + (int64_t)z * sc.tail * PARTIAL_FLOATS);
-    if constexpr (MODE == 1 || MODE == 8) {
-      const float f = MODE == 8 ? ta.rf.scale[row] : 1.0f;
+    if constexpr (MODE == 1) {
       bf16x4 o;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) o[r] = (bf16_t)(MODE == 8 ? v[r] * f : v[r]);
-      *(bf16x4*)((bf16_t*)g.C + (int64_t)(MODE == 8 ? ta.rf.index[row] : row) * g.ldc + col) = o;
+      for (int r = 0; r < 4; ++r) o[r] = (bf16_t)v[r];
+      *(bf16x4*)((bf16_t*)g.C + (int64_t)row * g.ldc + col) = o;
     } else {
       f32x4* c = (f32x4*)((float*)g.C + (int64_t)row * g.ldc + col);
       if (MODE == 2) v += *c;
@@ -820,7 +742,7 @@ bool gemm_mfma_eligible(const GemmArgs& g) {
   // Output widths need not be multiples of the 256-wide tile: a ragged last tile clamps its loads and masks its stores
   // (16-byte granules: multiples of 8 elements), e.g. a 151936-word vocabulary = 593.5 tiles.
   if (g.M < 1 || g.N < 1 || g.K < 1) return false;
-  if (g.N % 8 != 0 && !g.row_sums) return false;        // (the exponential form pads its rows)
+  if (g.N % 8 != 0 && !(g.c_padded && !g.ta && g.tb && !g.acc && g.ldc % 8 == 0 && g.ldc >= g.N)) return false;
   if (g.ta && !g.tb) {                       // TN: both operands reduction-major; ragged K allowed
     if (g.M % 8 != 0 && !g.a_padded) return false;
   } else if (!g.ta) {                        // NT / NN; a ragged K needs B reduction-major and A's rows padded with zeros
@@ -837,15 +759,6 @@ bool gemm_mfma_eligible(const GemmArgs& g) {
 
 // the operand-pair form: two reductions, one after the other, in one accumulator
 bool gemm_mfma_pair_ok(const GemmArgs& g) { return g.A2 && g.B2 && !g.ta && !((uintptr_t)g.A2 & 15) && !((uintptr_t)g.B2 & 15); }
-
-// rows scaled and scattered on the way out: bf16 store form
-bool gemm_mfma_scatter_ok(const GemmArgs& g) { return g.row_scale && g.row_index && !g.acc && g.out_dt == DT_BF16 && !g.ta && !g.tb && !g.row_stats && !g.swiglu_gate; }
-
-// exponentials of C = A B^T in bf16 with zero-filled columns up to ldc, a multiple of 64
-bool gemm_mfma_exp_ok(const GemmArgs& g) {
-  return !g.ta && g.tb && g.out_dt == DT_BF16 && !g.acc && !g.A2 && g.row_sums && g.numer_targets && g.numer_target_value && g.numer_row_index &&
-         g.ldc % 64 == 0 && g.ldc >= g.N && g.ldc < g.N + 64;
-}
 
 // the fused SwiGLU adjoint exists for the store form C = A B (input-gradient layout), bf16 tensors that share C's layout
 bool gemm_mfma_swiglu_ok(const GemmArgs& g) {
@@ -876,15 +789,14 @@ static hipError_t launch_tail(int mode, const TailArgs& t, int max_tail, hipStre
   const unsigned blocks = (unsigned)max_tail * 16;
   if (mode == 0) splitk_tail_k<0><<<blocks, 256, 0, st>>>(t);
   else if (mode == 1) splitk_tail_k<1><<<blocks, 256, 0, st>>>(t);
-  else if (mode == 2) splitk_tail_k<2><<<blocks, 256, 0, st>>>(t);
-  else splitk_tail_k<8><<<blocks, 256, 0, st>>>(t);
+  else splitk_tail_k<2><<<blocks, 256, 0, st>>>(t);
   return hipGetLastError();
 }
 
 hipError_t gemm_mfma(const GemmArgs& g, hipStream_t st) {
   const int tiles_m = (int)cdiv(g.M, BM), tiles_n = (int)cdiv(g.N, BN);
   const int k_steps = (int)cdiv(g.K, BK) * (g.A2 ? 2 : 1);
-  const int mode = g.row_sums ? 9 : g.numer_targets ? 7 : g.row_stats ? 5 : g.swiglu_gate ? 6 : g.row_scale ? 8
+  const int mode = g.numer_targets ? 7 : g.row_stats ? 5 : g.swiglu_gate ? 6
                  : g.acc ? (g.out_dt == DT_BF16 ? 4 : 2) : (g.out_dt == DT_BF16 ? 1 : 0);
   const bool dev_rows = g.rows_dev != nullptr;
   const int scratch_tiles = mode_splits(mode) && !(g.ta && dev_rows) ? scratch_tiles_of(g) : 0;
@@ -895,10 +807,9 @@ hipError_t gemm_mfma(const GemmArgs& g, hipStream_t st) {
 #define LAUNCH(TA, TB, MODE) \
   gemm_mfma_k<TA, TB, MODE><<<grid, NTHREADS, 0, st>>>((const bf16_t*)g.A, (const bf16_t*)g.B, g.C, g.M, g.N, g.K, g.lda, g.ldb, g.ldc, g.rows_dev, \
                                                        (const bf16_t*)g.A2, (const bf16_t*)g.B2, g.scratch, scratch_tiles, \
-                                                       g.row_sums ? (void*)g.row_sums : (void*)g.row_stats, \
+                                                       (void*)g.row_stats, \
                                                        SwigluFuse{(bf16_t*)g.swiglu_gate, (bf16_t*)g.swiglu_up, (bf16_t*)g.swiglu_act}, \
-                                                       NumerFuse{g.numer_targets, g.numer_row_index, g.numer_target_value, nullptr}, \
-                                                       RowFuse{g.row_scale, g.row_index})
+                                                       NumerFuse{g.numer_targets, g.numer_row_index, g.numer_target_value})
 #define LAUNCH_LAYOUT(MODE)                       \
   do {                                            \
     if (!g.ta && g.tb) LAUNCH(false, true, MODE); \
@@ -906,13 +817,11 @@ hipError_t gemm_mfma(const GemmArgs& g, hipStream_t st) {
     else LAUNCH(true, false, MODE);               \
   } while (0)
   const int layout = g.ta ? 2 : (g.tb ? 0 : 1);
-  const int kind = mode == 9 ? (int)prof::GEMM_EXP : mode == 7 ? (int)prof::GEMM_NUMER : mode == 5 ? (int)prof::GEMM_STATS : mode == 6 ? (int)prof::GEMM_SWIGLU
-                 : prof::GEMM_SINGLE + layout * 4 + (mode == 8 ? 3 : mode == 4 ? 2 : mode);   // (both accumulate forms are timed as one kind)
+  const int kind = mode == 7 ? (int)prof::GEMM_NUMER : mode == 5 ? (int)prof::GEMM_STATS : mode == 6 ? (int)prof::GEMM_SWIGLU
+                 : prof::GEMM_SINGLE + layout * 4 + (mode == 4 ? 2 : mode);   // (both accumulate forms are timed as one kind)
   {
     prof::Scope sc_time(kind, 2.0 * g.M * g.N * g.K * (g.A2 ? 2 : 1), dev_rows, st);   // times the GEMM kernel, not the sum of the partial tiles after it
-    if (mode == 9) LAUNCH(false, true, 9);
-    else if (mode == 8) LAUNCH(false, false, 8);
-    else if (mode == 7) LAUNCH(false, true, 7);
+    if (mode == 7) LAUNCH(false, true, 7);
     else if (mode == 5) LAUNCH(false, true, 5);
     else if (mode == 6) LAUNCH(false, false, 6);
     else if (mode == 4) LAUNCH(true, false, 4);
@@ -928,16 +837,7 @@ hipError_t gemm_mfma(const GemmArgs& g, hipStream_t st) {
   t.n = 1;
   t.p[0] = TailProblem{g.C, g.M, g.N, g.ldc, 0, tiles_m, tiles_n};
   t.sched = sc; t.rows_dev = g.rows_dev; t.k_steps = k_steps; t.scratch_tiles = scratch_tiles; t.scratch = g.scratch;
-  t.rf = RowFuse{g.row_scale, g.row_index};
   return launch_tail(mode, t, dev_rows ? std::min(N_CU / 2, tiles_m * tiles_n) : sc.tail, st);
-}
-
-// The product of marked rows (see gemm_mfma_marked_k).
-hipError_t gemm_mfma_marked(const GemmArgs& g, const int32_t* tile_marks, const int32_t* row_marks, hipStream_t st) {
-  gemm_mfma_marked_k<<<(unsigned)std::min<int64_t>(N_CU, cdiv(g.N, BN)), NTHREADS, 0, st>>>(
-      (const bf16_t*)g.A, (const bf16_t*)g.B, g.C, g.M, g.N, g.K, g.lda, g.ldb, g.ldc, g.rows_dev, tile_marks, g.row_stats,
-      NumerFuse{g.numer_targets, g.numer_row_index, g.numer_target_value, row_marks});
-  return hipGetLastError();
 }
 
 // Grouped launch.  Requires every problem to be eligible, of the same layout / output type / accumulate mode.

@@ -45,18 +45,18 @@ __global__ __launch_bounds__(HR_THREADS) void head_rows_k(HeadRowArgs a) {
   __shared__ float red[16];
   const int row = blockIdx.x, tid = threadIdx.x;
   if (a.rows_dev && row >= *a.rows_dev) return;                 // beyond the valid rows of a compacted chunk
-  const float* z = a.z + (int64_t)row * a.V;
-  T* dz = (T*)a.dz + (int64_t)row * a.V;
+  const float* z = a.z + (int64_t)row * a.ldz;
+  T* dz = (T*)a.dz + (int64_t)row * a.ldz;
   const int64_t orig = a.row_index ? (int64_t)a.row_index[row] : a.row0 + row;   // row in the caller's [B*T] order
   const int64_t aux = a.row_index ? orig : (int64_t)row;        // index into targets / old_logp / ref_logp as passed
   const int tgt = a.targets[aux];
   if (tgt < 0 || tgt >= a.V) {   // ignored row (or an id outside the vocabulary, which is never used as an index): exact zeros, no loss term
-    const int64_t row_bytes = (int64_t)a.V * sizeof(T);
+    const int64_t row_bytes = a.ldz * (int64_t)sizeof(T);
     if ((row_bytes & 15) == 0) {
       uint4* p16 = (uint4*)dz;
       for (int v = tid; v < row_bytes / 16; v += HR_THREADS) p16[v] = make_uint4(0, 0, 0, 0);
     } else {
-      for (int v = tid; v < a.V; v += HR_THREADS) stf(dz + v, 0.f);
+      for (int v = tid; v < a.ldz; v += HR_THREADS) stf(dz + v, 0.f);
     }
     if (tid == 0) a.row_loss[row] = 0.f;
     return;
@@ -64,7 +64,13 @@ __global__ __launch_bounds__(HR_THREADS) void head_rows_k(HeadRowArgs a) {
   // One pass for the statistics: every thread keeps a running (max, sum of exp) pair over its elements
   // and rescales the sum when its max moves; the pairs are then merged across the workgroup.
   float mx = -INFINITY, se = 0.f;
-  const bool vec = (a.V & 3) == 0;
+  const bool vec = (a.ldz & 3) == 0;      // four columns at a time; those from V on (padding) take no part
+  auto load4 = [&](int v) {
+    float4 t = ((const float4*)z)[v];
+    const int n = a.V - v * 4;
+    if (n < 4) { t.w = -INFINITY; if (n < 3) t.z = -INFINITY; if (n < 2) t.y = -INFINITY; }
+    return t;
+  };
   if (a.stats) {   // the logits GEMM left (max, sum of exp) per column block: merge those instead of reading the row
     const float2* ps = a.stats + (int64_t)row * a.n_stat;
     for (int t = tid; t < a.n_stat; t += HR_THREADS) {
@@ -74,9 +80,8 @@ __global__ __launch_bounds__(HR_THREADS) void head_rows_k(HeadRowArgs a) {
       mx = m2;
     }
   } else if (vec) {
-    const float4* z4 = (const float4*)z;
-    for (int v = tid; v < a.V / 4; v += HR_THREADS) {
-      const float4 t = z4[v];
+    for (int v = tid; v < (a.V + 3) / 4; v += HR_THREADS) {
+      const float4 t = load4(v);
       const float m4 = fmaxf(fmaxf(t.x, t.y), fmaxf(t.z, t.w));
       if (m4 > mx) { se *= __expf(mx - m4); mx = m4; }
       se += __expf(t.x - mx) + __expf(t.y - mx) + __expf(t.z - mx) + __expf(t.w - mx);
@@ -101,10 +106,10 @@ __global__ __launch_bounds__(HR_THREADS) void head_rows_k(HeadRowArgs a) {
   if (tid == 0) a.row_loss[row] = loss_term;
   if (vec && sizeof(T) == 2) {
     typedef bf16_t bf16x4 __attribute__((ext_vector_type(4)));
-    const float4* z4 = (const float4*)z;
     bf16x4* dz4 = (bf16x4*)dz;
-    for (int v = tid; v < a.V / 4; v += HR_THREADS) {
-      const float4 t = z4[v];
+    for (int v = tid; v < a.ldz / 4; v += HR_THREADS) {
+      if (v * 4 >= a.V) { dz4[v] = bf16x4{(bf16_t)0.f, (bf16_t)0.f, (bf16_t)0.f, (bf16_t)0.f}; continue; }
+      const float4 t = load4(v);
       const int v0 = v * 4;
       bf16x4 o;
       o[0] = (bf16_t)(coef * ((v0 + 0 == tgt ? 1.0f : 0.0f) - __expf(t.x - lse)));
@@ -123,17 +128,17 @@ __global__ __launch_bounds__(HR_THREADS) void head_rows_k(HeadRowArgs a) {
 
 // Numerator form: the logits GEMM left exp(z - block max) in dz (bf16), the (max, sum) pair of every 256-column block in
 // stats and z[target] in target_logit.  One pass, in place: dz = coef * (onehot - numerator * exp(block max - lse)) -
-// one multiply per element, the factor changes once per block.
+// one multiply per element, the factor changes once per block.  Columns V .. ldz become zeros.
 typedef bf16_t bf16x8h __attribute__((ext_vector_type(8)));
 __global__ __launch_bounds__(HR_THREADS) void head_rows_numer_k(HeadRowArgs a) {
   __shared__ float red[16];
   const int row = blockIdx.x, tid = threadIdx.x;
   if (a.rows_dev && row >= *a.rows_dev) return;
-  bf16x8h* dz8 = (bf16x8h*)((bf16_t*)a.dz + (int64_t)row * a.V);
+  bf16x8h* dz8 = (bf16x8h*)((bf16_t*)a.dz + (int64_t)row * a.ldz);
   const int64_t orig = a.row_index ? (int64_t)a.row_index[row] : a.row0 + row;
   const int64_t aux = a.row_index ? orig : (int64_t)row;
   const int tgt = a.targets[aux];
-  const int n8 = a.V / 8;
+  const int n8 = (int)(a.ldz / 8);
   if (tgt < 0 || tgt >= a.V) {   // ignored row: exact zeros, no loss term
     bf16x8h zero;
 #pragma unroll
@@ -162,6 +167,7 @@ __global__ __launch_bounds__(HR_THREADS) void head_rows_numer_k(HeadRowArgs a) {
   if (tid == 0) a.row_loss[row] = loss_term;
   for (int v = tid; v < n8; v += HR_THREADS) {
     const int v0 = v * 8;
+    if (v0 >= a.V) { dz8[v] = bf16x8h{}; continue; }                  // (V is a multiple of 8)
     const float f = coef * __expf(ps[v0 / GEMM_STAT_COLS].x - lse);   // 8 | 256: the eight elements share a block
     const bf16x8h e = dz8[v];
     bf16x8h o;
@@ -174,7 +180,7 @@ __global__ __launch_bounds__(HR_THREADS) void head_rows_numer_k(HeadRowArgs a) {
 hipError_t head_rows(const HeadRowArgs& a, hipStream_t st) {
   if (a.rows == 0) return hipSuccess;
   if (a.target_logit) {
-    if (a.dt != DT_BF16 || !a.stats || a.V % 8 != 0 || ((uintptr_t)a.dz & 15)) return hipErrorInvalidValue;
+    if (a.dt != DT_BF16 || !a.stats || a.V % 8 != 0 || a.ldz % 8 != 0 || ((uintptr_t)a.dz & 15)) return hipErrorInvalidValue;
     head_rows_numer_k<<<a.rows, HR_THREADS, 0, st>>>(a);
     return hipGetLastError();
   }

@@ -52,22 +52,13 @@ struct GemmArgs {
   // A is padded: its rows (NN: columns K .. next multiple of 64, which hold zeros; TN: columns M .. next multiple of 8, any finite
   // values) reach further than the operand, so K (NN) and M (TN) need not be multiples of anything.
   bool a_padded = false;
-  // Optional store form of C = A B (bf16): row m of the product times row_scale[m] goes to row row_index[m] of C.
-  const float* row_scale = nullptr;
-  const int32_t* row_index = nullptr;
-  // Optional exponential form of the bf16 store C = A B^T (ask gemm_exp_supported first): C receives exp(c), its columns from N up
-  // to ldc (the next multiple of 64) zeros, row_sums[m * ceil(N / GEMM_STAT_COLS) + t] the sum of row m's exponentials
-  // over the t-th block of columns (unrounded), and numer_target_value[m] the product's value in column
-  // numer_targets[numer_row_index[m]].
-  float* row_sums = nullptr;
+  // C = A B^T is padded: its rows reach to ldc, a multiple of 8, so N need not be a multiple of anything (columns N .. next multiple of 4
+  // receive finite values of no meaning).
+  bool c_padded = false;
 };
 constexpr int GEMM_STAT_COLS = 256;
 bool gemm_row_stats_supported(const GemmArgs& g);
 bool gemm_numerators_supported(const GemmArgs& g);
-bool gemm_exp_supported(const GemmArgs& g);
-// The numerator form of `g` (row_stats, numer_*; rows_dev required) once more for marked rows only: row tiles (256 rows) whose entry
-// of tile_marks is not zero are computed, rows whose entry of row_marks is not zero are stored.
-hipError_t gemm_marked_rows(const GemmArgs& g, const int32_t* tile_marks, const int32_t* row_marks, hipStream_t st);
 // upper bound of the scratch a GEMM with M <= max_m rows and N <= max_n columns may use
 size_t gemm_scratch_bytes(int max_m, int max_n, int max_splits);
 hipError_t gemm(const GemmArgs& g, hipStream_t st);
@@ -90,12 +81,12 @@ void note_generic_bf16_launch();
 
 // ---- optional per-launch timing (off unless streambp_debug_profile_begin was called) ----
 namespace prof {
-// kinds 0..11: gemm_mfma_k<layout, mode> with layout NT=0, NN=1, TN=2 and mode 0, 1, 2, 8; 12..23: the grouped kernel;
+// kinds 0..11: gemm_mfma_k<layout, mode> with layout NT=0, NN=1, TN=2 and mode 0, 1, 2 (slot 3 unused); 12..23: the grouped kernel;
 // then the shape-agnostic GEMM, the attention forward / backward launch sequences, the segmented weight-gradient GEMM and the
 // store form with row statistics (gemm_mfma_k<NT, 5>), the input-gradient form with the fused SwiGLU adjoint (gemm_mfma_k<NN, 6>)
-// and the softmax-numerator store (gemm_mfma_k<NT, 7>) and the exponential store (gemm_mfma_k<NT, 9>)
+// and the softmax-numerator store (gemm_mfma_k<NT, 7>)
 enum { GEMM_SINGLE = 0, GEMM_GROUP = 12, GEMM_GENERIC = 24, ATTN_FWD = 25, ATTN_BWD = 26, GEMM_SEG = 27, GEMM_STATS = 28, GEMM_SWIGLU = 29,
-       GEMM_NUMER = 30, GEMM_EXP = 31, N_KIND = 32 };
+       GEMM_NUMER = 30, N_KIND = 31 };
 struct Scope {
   hipStream_t st; bool active = false; int kind = 0; double work = 0; bool bounded = false; hipEvent_t e0{}, e1{};
   // bounded: `work` was computed from a host-side upper bound of a run-time row count
@@ -176,8 +167,9 @@ constexpr int ATTN_TILE_K = 64;    // keys per inner step
 struct HeadRowArgs {
   int dt;                   // type of dz
   int objective;            // 0 SFT, 1 GRPO, 2 DPO
-  const float* z;           // [rows, V] fp32 logits of the chunk (unused in the numerator form)
-  void* dz;                 // [rows, V] dt; numerator form (target_logit != NULL): holds exp(z - block max) on entry
+  const float* z;           // [rows, ldz] fp32 logits of the chunk (unused in the numerator form)
+  void* dz;                 // [rows, ldz] dt, columns V .. ldz become zeros; numerator form (target_logit != NULL): holds exp(z - block max) on entry
+  int64_t ldz;
   const int32_t* targets;   // [rows] (already offset to the chunk)
   const float* old_logp;    // [rows] or NULL
   const float* ref_logp;    // [rows] or NULL
