@@ -1,4 +1,4 @@
-// bf16 MFMA chunk attention for gfx950 (head_dim 128): forward, dQ and dK/dV.
+// bf16 MFMA chunk attention for gfx950 (head_dim DH = 128 or 64): forward, dQ and dK/dV.
 //
 // Query row t of the chunk sits at global position q_start + t and sees keys
 // 0 .. q_start + t of the cached prefix (paper Sec. 3.2.2, partitioned attention;
@@ -53,22 +53,26 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 #define LDS_AS(p) ((__attribute__((address_space(3))) void*)(p))
 
-constexpr int DH = 128;                  // head_dim of the MFMA path
-constexpr int ROW_BYTES = DH * 2;        // 256 B per tile row
 constexpr int AT_THREADS = 512;          // 8 waves (forward, dQ): 2 per SIMD
 constexpr int TQ = ATTN_TILE_Q;          // queries per workgroup (fwd, dQ): 8 waves x 32
 constexpr int TK = ATTN_TILE_K;          // 64 keys per step (fwd, dQ)
 constexpr int KV_TILE = 128;             // keys per workgroup (dK/dV): 4 key blocks x 2 roles = 8 waves
 constexpr int KV_THREADS = 512;
 constexpr int QT = 64;                   // queries per step (dK/dV)
-constexpr int TILE64_BYTES = 64 * ROW_BYTES;   // 16 KiB
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
 
-// LDS tile [rows][128 bf16], 16 chunks of 16 B per row, chunk ^= f(row): conflict-free both for 128-bit row-fragment
-// reads (16 consecutive rows, same chunk) and for the transposing 64-bit reads (4 consecutive rows x 64 B, or 8 x 32 B).
-__device__ __forceinline__ int swz(int row) { return ((row & 3) << 2) | ((((row >> 2) ^ (row >> 3)) & 1) << 1) | ((row >> 3) & 1); }
-__device__ __forceinline__ int tile_off(int row, int chunk) { return row * ROW_BYTES + ((chunk ^ swz(row)) << 4); }
+// LDS tile [64 rows][DH bf16], 16 (DH = 64: 8) chunks of 16 B per row, chunk ^= f(row): conflict-free both for 128-bit
+// row-fragment reads (16 consecutive rows, same chunk) and for the transposing 64-bit reads (4 consecutive rows x 64 B, or 8 x 32 B).
+template <int DH> constexpr int TILE64 = 64 * DH * 2;      // bytes: 16 or 8 KiB
+template <int DH>
+__device__ __forceinline__ int swz(int row) {
+  static_assert(DH == 128 || DH == 64, "head sizes of the MFMA kernels");
+  if (DH == 128) return ((row & 3) << 2) | ((((row >> 2) ^ (row >> 3)) & 1) << 1) | ((row >> 3) & 1);
+  return (((row >> 1) & 1) << 2) | (((row >> 2) & 1) << 1) | ((row >> 3) & 1);      // (two rows per 256 bytes of banks)
+}
+template <int DH>
+__device__ __forceinline__ int tile_off(int row, int chunk) { return row * DH * 2 + ((chunk ^ swz<DH>(row)) << 4); }
 
 __device__ __forceinline__ bf16x8 pack8(const f32x16& v, int ks) {
   bf16x8 o;
@@ -84,6 +88,19 @@ __device__ __forceinline__ f32x16 zero16() {
   return z;
 }
 
+// Probabilities and dS are operands of the second products.  DH = 128 rounds them to bf16; DH = 64 keeps them as a sum of two bf16
+// terms (2^-17 relative, below the rounding of o, dq and - through o - delta and dk), P of dV = P^T dO as three (exact), at the price
+// of a further MFMA each: nothing is lost against the shape-agnostic kernels, which hold them in fp32.  Norm-wise error against
+// fp64 at 16 / 4 heads, 512 queries: o 1.599e-3, dq 1.817e-3, dk 7.13e-4 (fp32 kernels: 1.599e-3, 1.817e-3, 7.14e-4).
+template <int DH> constexpr int TERMS = DH == 64 ? 2 : 1;
+template <int DH> constexpr int DV_TERMS = DH == 64 ? 3 : 1;
+__device__ __forceinline__ bf16x8 rest8(const f32x16& v, int ks, const bf16x8& hi) {      // what pack8 leaves behind
+  bf16x8 o;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) o[j] = (bf16_t)(v[8 * ks + j] - (float)hi[j]);
+  return o;
+}
+
 #define MFMA(a, b, c) __builtin_amdgcn_mfma_f32_32x32x16_bf16((a), (b), (c), 0, 0, 0)
 
 // ---- address work hoisted out of the tile loops --------------------------------------------------------------
@@ -91,23 +108,25 @@ __device__ __forceinline__ f32x16 zero16() {
 // slots, so nothing there computes an address: the per-lane byte offsets of the fragment reads inside a 64-row
 // tile and of the direct-to-LDS loads are computed once per kernel, every tile / row block / stage is reached
 // with immediate offsets, and the global side is an SGPR base plus those per-lane offsets.
+template <int DH>
 struct FragPre {
-  uint32_t rows[8];   // frag_rows: k16 step ks of row block 0            (row block b: + b * 32 * ROW_BYTES)
-  uint32_t tr[8];     // frag_cols_tr: [i * 2 + hi], head_dim block i, tile rows +0 / +8, row_base 0 (+ row_base * ROW_BYTES)
+  uint32_t rows[DH / 16];   // frag_rows: k16 step ks of row block 0            (row block b: + b * 32 rows)
+  uint32_t tr[DH / 16];     // frag_cols_tr: [i * 2 + hi], head_dim block i, tile rows +0 / +8, row_base 0 (+ row_base rows)
 };
-__device__ __forceinline__ FragPre frag_pre(uint32_t lds_base /* LDS address of tile 0 */) {
+template <int DH>
+__device__ __forceinline__ FragPre<DH> frag_pre(uint32_t lds_base /* LDS address of tile 0 */) {
   const int l = threadIdx.x & 63;
-  FragPre f;
+  FragPre<DH> f;
 #pragma unroll
-  for (int ks = 0; ks < 8; ++ks) f.rows[ks] = pin(lds_base + (uint32_t)tile_off(l & 31, ks * 2 + (l >> 5)));
+  for (int ks = 0; ks < DH / 16; ++ks) f.rows[ks] = pin(lds_base + (uint32_t)tile_off<DH>(l & 31, ks * 2 + (l >> 5)));
   const int p = l & 15, g = l >> 4;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < DH / 32; ++i)
 #pragma unroll
     for (int hi = 0; hi < 2; ++hi) {
       const int col = i * 32 + 16 * (g & 1) + 4 * (p & 3);
       const int row = 4 * (g >> 1) + (p >> 2) + 8 * hi;
-      f.tr[i * 2 + hi] = pin(lds_base + (uint32_t)(tile_off(row, col >> 3) + ((col & 7) << 1)));
+      f.tr[i * 2 + hi] = pin(lds_base + (uint32_t)(tile_off<DH>(row, col >> 3) + ((col & 7) << 1)));
     }
   return f;
 }
@@ -122,33 +141,33 @@ __device__ __forceinline__ bf16x8 lds_tr(uint32_t lo_addr, uint32_t hi_addr) {
 }
 
 // Direct-to-LDS load of a 64-row tile by NT threads: rows 0..63 of a [*, stride] bf16 matrix starting at `g`
-// (uniform pointer to the tile's first row, first of its 128 columns).  rows_valid = rows that exist from `g` on:
+// (uniform pointer to the tile's first row, first of its DH columns).  rows_valid = rows that exist from `g` on:
 // a tile that runs past the end (only the last one) clamps its row indices so that nothing out of range is read.
-template <int NT>
-struct TileLoad { uint32_t voff[1024 / NT]; };
-template <int NT>
+template <int DH, int NT>
+struct TileLoad { uint32_t voff[8 * DH / NT]; };
+template <int DH, int NT>
 __device__ __forceinline__ uint32_t tile_load_offset(int i, int64_t stride, int rows_valid) {
   const int id = i * NT + (int)threadIdx.x;
-  const int row = id >> 4, pc = id & 15;
-  const int chunk = pc ^ swz(row);
+  const int row = id / (DH / 8), pc = id % (DH / 8);
+  const int chunk = pc ^ swz<DH>(row);
   return (uint32_t)(((int64_t)min(row, rows_valid - 1) * stride + chunk * 8) * 2);
 }
-template <int NT>
-__device__ __forceinline__ TileLoad<NT> tile_load_pre(int64_t stride) {
-  TileLoad<NT> t;
+template <int DH, int NT>
+__device__ __forceinline__ TileLoad<DH, NT> tile_load_pre(int64_t stride) {
+  TileLoad<DH, NT> t;
 #pragma unroll
-  for (int i = 0; i < 1024 / NT; ++i) t.voff[i] = pin(tile_load_offset<NT>(i, stride, 64));
+  for (int i = 0; i < 8 * DH / NT; ++i) t.voff[i] = pin(tile_load_offset<DH, NT>(i, stride, 64));
   return t;
 }
-template <int NT>
-__device__ __forceinline__ void dma_tile64(const TileLoad<NT>& t, const bf16_t* g, int64_t stride, int rows_valid, uint32_t lds_tile) {
+template <int DH, int NT>
+__device__ __forceinline__ void dma_tile64(const TileLoad<DH, NT>& t, const bf16_t* g, int64_t stride, int rows_valid, uint32_t lds_tile) {
   const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_tile + (uint32_t)(threadIdx.x & ~63) * 16u);
   if (rows_valid >= 64) {
 #pragma unroll
-    for (int i = 0; i < 1024 / NT; ++i) dma16((const char*)g, t.voff[i], dst + (uint32_t)(i * NT * 16));
+    for (int i = 0; i < 8 * DH / NT; ++i) dma16((const char*)g, t.voff[i], dst + (uint32_t)(i * NT * 16));
   } else {
 #pragma unroll
-    for (int i = 0; i < 1024 / NT; ++i) dma16((const char*)g, tile_load_offset<NT>(i, stride, rows_valid), dst + (uint32_t)(i * NT * 16));
+    for (int i = 0; i < 8 * DH / NT; ++i) dma16((const char*)g, tile_load_offset<DH, NT>(i, stride, rows_valid), dst + (uint32_t)(i * NT * 16));
   }
 }
 
@@ -178,16 +197,18 @@ __device__ __forceinline__ int acc_row(int r, int h) { return 8 * (r >> 2) + 4 *
 // of the next product with slot 8 (l / 16) + j <-> key 16 (j >> 2) + 4 (l / 16) + (j & 3), matched on the A side by two
 // transposing reads 16 rows apart.
 #define MFMA16(a, b, c) __builtin_amdgcn_mfma_f32_16x16x32_bf16((a), (b), (c), 0, 0, 0)
-// fragment of 16 rows x 32 elements (one k32 step): row l % 16, elements 8 (l / 16) .. + 7   (row block b: + b * 4096)
+// fragment of 16 rows x 32 elements (one k32 step): row l % 16, elements 8 (l / 16) .. + 7   (row block b: + b * 16 rows)
+template <int DH>
 __device__ __forceinline__ uint32_t frag16_rows(int kk) {
   const int l = threadIdx.x & 63;
-  return (uint32_t)tile_off(l & 15, kk * 4 + (l >> 4));
+  return (uint32_t)tile_off<DH>(l & 15, kk * 4 + (l >> 4));
 }
-// transposed fragment of 16 columns (head_dim block d) x 32 rows: rows 4 (l / 16) .. + 3 here, rows + 16 at + 4096
+// transposed fragment of 16 columns (head_dim block d) x 32 rows: rows 4 (l / 16) .. + 3 here, and 16 rows further
+template <int DH>
 __device__ __forceinline__ uint32_t frag16_tr(int d) {
   const int l = threadIdx.x & 63, p = l & 15, g = l >> 4;
   const int col = d * 16 + 4 * (p & 3), row = 4 * g + (p >> 2);
-  return (uint32_t)(tile_off(row, col >> 3) + ((col & 7) << 1));
+  return (uint32_t)(tile_off<DH>(row, col >> 3) + ((col & 7) << 1));
 }
 // maximum over the four lanes that share a query (l % 16)
 __device__ __forceinline__ float max_raw(float a, float b) {      // v_max_f32 without the quieting moves fmaxf adds for unknown operands
@@ -226,23 +247,24 @@ __device__ __forceinline__ void query_tile_of(int n_qt, int Hq, int& qt, int& h)
 //   SPLIT = false: 256 queries, 32 per wave; all waves walk all key tiles, four K and four V stages (128 KB), loads two to three
 //                  tiles ahead.
 //   SPLIT = true : 128 queries, for launches that would leave CUs idle: the groups take the even / odd key tiles of the same
-//                  queries, each with two stages of its own, and meet in LDS at the end.
-// The running maximum lags by up to 2^8 (O and the denominator are rescaled only when a score passes it by more): bf16
-// probabilities keep their relative precision whatever their size, and the rescaling of 72 registers becomes rare.
+//                  queries, each with two stages of its own, and meet in LDS at the end.  They exchange their running
+//                  maxima tile by tile (a group reads what the other left one slot ago), so that every probability is rounded
+//                  against the maximum it has in the sequential walk.
 // What bounds it: a slot takes about 1600 cycles at 2.0 GHz where the 68 MFMAs take 1088 - the vector instructions of one wave (about
 // 160, 32 of them exponentials) and the MFMAs of the other share the SIMD's issue port and delay each other; without the vector
 // work a slot takes 1050 cycles, without the MFMAs 1150.  Last 2048-query chunk of 32k, 28 heads: 1110 -> 921 us (32x32x16 MFMAs in
 // the same schedule 965; loads in the multiply slot 954; the next slot's first fragments read early 958).
-template <bool SPLIT>
+template <int DH, bool SPLIT>
 __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const bf16_t* __restrict__ k,
                                                                  const bf16_t* __restrict__ v, bf16_t* __restrict__ o,
                                                                  float* __restrict__ lse, int Hq, int Hkv, int q_start,
                                                                  int c, float scale, const float2* __restrict__ rope,
                                                                  int window, int kv_first) {
-  __shared__ __attribute__((aligned(1024))) char sT[8 * TILE64_BYTES];   // K stages, then V stages
+  __shared__ __attribute__((aligned(1024))) char sT[8 * TILE64<DH>];   // K stages, then V stages
+  __shared__ float sM[SPLIT ? 2 : 1][4][32];                  // SPLIT: the running maxima of the groups' queries
   constexpr int QW = SPLIT ? TQ / 2 : TQ;                     // queries of the workgroup
   constexpr int STAGES = SPLIT ? 2 : 4, K_AHEAD = SPLIT ? 2 : 3, V_AHEAD = SPLIT ? 1 : 2;
-  constexpr int LOADERS = SPLIT ? AT_THREADS / 2 : AT_THREADS, LOADS = 1024 / LOADERS;   // threads that load a tile, 16-byte loads of each
+  constexpr int LOADERS = SPLIT ? AT_THREADS / 2 : AT_THREADS, LOADS = 8 * DH / LOADERS;   // threads that load a tile, 16-byte loads of each
 
   int qt, h;
   query_tile_of((c + QW - 1) / QW, Hq, qt, h);
@@ -266,17 +288,18 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
   const int n_it = SPLIT ? (max(0, n_tiles - kt0) + 1) / 2 : max(0, n_tiles - kt0);
   auto tile_of = [&](int i) { return SPLIT ? kt0 + 2 * i + grp : kt0 + i; };
 
-  bf16x8 bq[2][4];      // [16-query block][k32 step]: B operands of S^T = K Q^T
+  constexpr int KS = DH / 32, DB = DH / 16;                   // k32 steps of a score, 16-row blocks of the output
+  bf16x8 bq[2][KS];      // [16-query block][k32 step]: B operands of S^T = K Q^T
 #pragma unroll
   for (int b = 0; b < 2; ++b) {
     const int q_row = min(qw0 + b * 16 + li, c - 1);
     const bf16_t* qp = q + ((int64_t)q_row * Hq + h) * DH + lg * 8;
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) bq[b][kk] = *(const bf16x8*)(qp + kk * 32);
+    for (int kk = 0; kk < KS; ++kk) bq[b][kk] = *(const bf16x8*)(qp + kk * 32);
   }
   if (rope) {
-    // Rotary embedding of the query on load: the rotate-half partner of element j < 64 is j + 64, i.e. the same element of the
-    // fragment two steps on, in the same lane.  The rotated row is written back so that the backward kernels, which read q
+    // Rotary embedding of the query on load: the rotate-half partner of element j < DH / 2 is j + DH / 2, i.e. the same element of
+    // fragment kk + KS / 2, in the same lane.  The rotated row is written back so that the backward kernels, which read q
     // through LDS, find it rotated.
     if (SPLIT) __syncthreads();      // both groups hold the un-rotated rows
 #pragma unroll
@@ -284,38 +307,38 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
       const int my_q = qw0 + b * 16 + li, q_row = min(my_q, c - 1);
       const float2* tr = rope + (int64_t)q_row * (DH / 2) + lg * 8;
 #pragma unroll
-      for (int kk = 0; kk < 2; ++kk)
+      for (int kk = 0; kk < KS / 2; ++kk)
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           const float2 cs = tr[kk * 32 + e];
-          const float x1 = (float)bq[b][kk][e], x2 = (float)bq[b][kk + 2][e];
+          const float x1 = (float)bq[b][kk][e], x2 = (float)bq[b][kk + KS / 2][e];
           bq[b][kk][e] = (bf16_t)(x1 * cs.x - x2 * cs.y);
-          bq[b][kk + 2][e] = (bf16_t)(x2 * cs.x + x1 * cs.y);
+          bq[b][kk + KS / 2][e] = (bf16_t)(x2 * cs.x + x1 * cs.y);
         }
       if (my_q < c && (!SPLIT || grp == 0)) {
         bf16_t* qp = q + ((int64_t)my_q * Hq + h) * DH + lg * 8;
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) *(bf16x8*)(qp + kk * 32) = bq[b][kk];
+        for (int kk = 0; kk < KS; ++kk) *(bf16x8*)(qp + kk * 32) = bq[b][kk];
       }
     }
   }
 #pragma unroll
   for (int b = 0; b < 2; ++b)
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) asm volatile("" : "+v"(bq[b][kk]));   // (arrived: the compiler must not wait for them in the loop)
+    for (int kk = 0; kk < KS; ++kk) asm volatile("" : "+v"(bq[b][kk]));   // (arrived: the compiler must not wait for them in the loop)
   AT_WAIT_VM(0);     // from here on the loop counts its own loads only
 
   // ---- addresses, computed once: LDS fragments (+ stage, the only part that moves), global loads
   const uint32_t lds0 = lds_addr(sT);
-  const uint32_t lds_k = lds0 + (SPLIT ? (uint32_t)grp * STAGES * TILE64_BYTES : 0u), lds_v = lds_k + 4 * TILE64_BYTES;
-  uint32_t fr[4], ft[8];
+  const uint32_t lds_k = lds0 + (SPLIT ? (uint32_t)grp * STAGES * TILE64<DH> : 0u), lds_v = lds_k + 4 * TILE64<DH>;
+  uint32_t fr[KS], ft[DB];
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) fr[kk] = pin(lds_k + frag16_rows(kk));
+  for (int kk = 0; kk < KS; ++kk) fr[kk] = pin(lds_k + frag16_rows<DH>(kk));
 #pragma unroll
-  for (int d = 0; d < 8; ++d) ft[d] = pin(lds_v + frag16_tr(d));
+  for (int d = 0; d < DB; ++d) ft[d] = pin(lds_v + frag16_tr<DH>(d));
   const int tid = SPLIT ? (int)threadIdx.x & (LOADERS - 1) : (int)threadIdx.x;
   auto load_offset = [&](int i, int rows_valid) {
-    const int id = i * LOADERS + tid, row = id >> 4, chunk = (id & 15) ^ swz(row);
+    const int id = i * LOADERS + tid, row = id / (DH / 8), chunk = (id % (DH / 8)) ^ swz<DH>(row);
     return (uint32_t)(((int64_t)min(row, rows_valid - 1) * kv_stride + chunk * 8) * 2);
   };
   // loads of tile i of this wave's sequence; past the end the last tile is loaded again, so that the wait counts stay the same.
@@ -332,22 +355,26 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
     const int j = p % LOADS, ahead = is_k ? K_AHEAD : V_AHEAD, t = min(tile_of(i + ahead), t_max);
     const char* src = (const char*)(is_k ? kbase : vbase) + (uint64_t)tile_bytes * (uint32_t)t;
     dma16(src, t == t_max ? voff_last[j] : voff[j],
-          dst_k + (uint32_t)(((is_k ? 0 : 4) + (slot + ahead) % STAGES) * TILE64_BYTES + j * LOADERS * 16));
+          dst_k + (uint32_t)(((is_k ? 0 : 4) + (slot + ahead) % STAGES) * TILE64<DH> + j * LOADERS * 16));
   };
 
   bf16x8 ones;
 #pragma unroll
   for (int e = 0; e < 8; ++e) ones[e] = (bf16_t)1.0f;
   asm volatile("" : "+v"(ones));
-  f32x4 acc[2][8], acc_l[2], s[2][4];     // O^T [query block][16 head_dim rows], denominator, S^T [query block][16 keys]
-  bf16x8 pb[2][2];                        // P^T: [query block][k32 step]
+  f32x4 acc[2][DB], acc_l[2], s[2][4];     // O^T [query block][16 head_dim rows], denominator, S^T [query block][16 keys]
+  bf16x8 pb[TERMS<DH>][2][2];             // P^T: [term][query block][k32 step]
   float m_floor = -INFINITY;
   asm volatile("" : "+v"(m_floor));
-  float m_run[2] = {-INFINITY, -INFINITY}, m_lim[2] = {-INFINITY, -INFINITY}, m_neg[2] = {0.f, 0.f};   // maximum (log2 domain); raw score that moves it; what is added
+  float m_raw[2] = {-INFINITY, -INFINITY}, m_neg[2] = {0.f, 0.f};   // maximum of the raw scores; what the exponent adds (log2 domain)
+  if (SPLIT) {
+    if (lane < 32) sM[grp][wave & 3][lane] = -INFINITY;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  }
 #pragma unroll
   for (int b = 0; b < 2; ++b) {
 #pragma unroll
-    for (int d = 0; d < 8; ++d) acc[b][d] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int d = 0; d < DB; ++d) acc[b][d] = f32x4{0.f, 0.f, 0.f, 0.f};
     acc_l[b] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
   const float sl = scale * LOG2E;
@@ -359,29 +386,33 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
 
   // fragment reads run RING - 1 fragments (two MFMAs each) ahead of the products
   constexpr int RING = 8;
+  constexpr uint32_t ROWS16 = 16 * DH * 2;
   bf16x8 f[RING];
-  auto v_frag = [&](int n, uint32_t st) {      // n = k32 step * 8 + head_dim block
-    return lds_tr(ft[n & 7] + (st + (uint32_t)(n >> 3) * 8192), ft[n & 7] + (st + (uint32_t)(n >> 3) * 8192 + 4096));
+  auto v_frag = [&](int n, uint32_t st) {      // n = k32 step * DB + head_dim block
+    return lds_tr(ft[n % DB] + (st + (uint32_t)(n / DB) * 2 * ROWS16), ft[n % DB] + (st + (uint32_t)(n / DB) * 2 * ROWS16 + ROWS16));
   };
-  auto k_frag = [&](int n, uint32_t st) { return lds_b128(fr[n >> 2] + (st + (uint32_t)(n & 3) * 4096)); };   // n = k32 step * 4 + key block
+  auto k_frag = [&](int n, uint32_t st) { return lds_b128(fr[n >> 2] + (st + (uint32_t)(n & 3) * ROWS16)); };   // n = k32 step * 4 + key block
   auto pv = [&](int slot) __attribute__((always_inline)) {
-    const uint32_t st = (uint32_t)((slot % STAGES) * TILE64_BYTES);
+    const uint32_t st = (uint32_t)((slot % STAGES) * TILE64<DH>);
 #pragma unroll
     for (int n = 0; n < RING - 1; ++n) f[n] = v_frag(n, st);
 #pragma unroll
-    for (int n = 0; n < 16; ++n) {
-      if (n + RING - 1 < 16) f[(n + RING - 1) % RING] = v_frag(n + RING - 1, st);
+    for (int n = 0; n < 2 * DB; ++n) {
+      if (n + RING - 1 < 2 * DB) f[(n + RING - 1) % RING] = v_frag(n + RING - 1, st);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int b = 0; b < 2; ++b) {
-        acc[b][n & 7] = MFMA16(f[n % RING], pb[b][n >> 3], acc[b][n & 7]);
-        if ((n & 7) == 7) acc_l[b] = MFMA16(ones, pb[b][n >> 3], acc_l[b]);
+#pragma unroll
+        for (int t = 0; t < TERMS<DH>; ++t) {
+          acc[b][n % DB] = MFMA16(f[n % RING], pb[t][b][n / DB], acc[b][n % DB]);
+          if (n % DB == DB - 1) acc_l[b] = MFMA16(ones, pb[t][b][n / DB], acc_l[b]);
+        }
       }
       __builtin_amdgcn_sched_barrier(0);
     }
   };
   auto qk = [&](int slot) __attribute__((always_inline)) {
-    const uint32_t st = (uint32_t)((slot % STAGES) * TILE64_BYTES);
+    const uint32_t st = (uint32_t)((slot % STAGES) * TILE64<DH>);
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
@@ -389,8 +420,8 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
 #pragma unroll
     for (int n = 0; n < RING - 1; ++n) f[n] = k_frag(n, st);
 #pragma unroll
-    for (int n = 0; n < 16; ++n) {
-      if (n + RING - 1 < 16) f[(n + RING - 1) % RING] = k_frag(n + RING - 1, st);
+    for (int n = 0; n < 4 * KS; ++n) {
+      if (n + RING - 1 < 4 * KS) f[(n + RING - 1) % RING] = k_frag(n + RING - 1, st);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int b = 0; b < 2; ++b) s[b][n & 3] = MFMA16(f[n % RING], bq[b][n >> 2], s[b][n & 3]);
@@ -428,32 +459,42 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
     }
 #pragma unroll
     for (int b = 0; b < 2; ++b) mx[b] = max_over_quads(mx[b]);
-    constexpr float LAG = 8.0f;
-    if (__builtin_amdgcn_ballot_w64(mx[0] > m_lim[0] || mx[1] > m_lim[1]) != 0) {
+    if constexpr (SPLIT) {
+#pragma unroll
+      for (int b = 0; b < 2; ++b) mx[b] = max_raw(mx[b], sM[grp ^ 1][wave & 3][b * 16 + li]);
+    }
+    // The maximum (and with it the rescale of O) only moves when some query of the wave sees a new one.
+    if (__builtin_amdgcn_ballot_w64(mx[0] > m_raw[0] || mx[1] > m_raw[1]) != 0) {
 #pragma unroll
       for (int b = 0; b < 2; ++b) {
-        const float m_new = mx[b] > m_lim[b] ? mx[b] * sl : m_run[b];     // each query by its own scores alone
-        const float alpha = m_new == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m_run[b] - m_new);   // a query that has seen no key yet keeps its zeros
-        m_run[b] = m_new;
-        m_lim[b] = (m_new + LAG) / sl;
-        m_neg[b] = m_new == -INFINITY ? 0.0f : -m_new;        // all scores so far masked: exp2(-inf - 0) = 0, not exp2(-inf + inf)
+        const float m_new = mx[b] > m_raw[b] ? mx[b] : m_raw[b];
+        const float alpha = m_new == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m_raw[b] * sl - m_new * sl);   // a query that has seen no key yet keeps its zeros
+        m_raw[b] = m_new;
+        m_neg[b] = m_new == -INFINITY ? 0.0f : -(m_new * sl);        // all scores so far masked: exp2(-inf - 0) = 0, not exp2(-inf + inf)
 #pragma unroll
         for (int r = 0; r < 4; ++r) acc_l[b][r] *= alpha;
 #pragma unroll
-        for (int d = 0; d < 8; ++d)
+        for (int d = 0; d < DB; ++d)
 #pragma unroll
           for (int r = 0; r < 4; ++r) acc[b][d][r] *= alpha;
+      }
+      if (SPLIT && lg < 2) {       // (lanes 0 .. 15 query block 0, 16 .. 31 block 1)
+        sM[grp][wave & 3][lane] = lg == 0 ? m_raw[0] : m_raw[1];
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       }
     }
 #pragma unroll
     for (int x = 0; x < 4; ++x) {        // eight probabilities at a time, the loads spread between them
       const int b = x >> 1, kk = x & 1;
 #pragma unroll
-      for (int p = 0; p < PIECES / 4; ++p) issue_piece(x * (PIECES / 4) + p, i, slot);
+      for (int p = x * PIECES / 4; p < (x + 1) * PIECES / 4; ++p) issue_piece(p, i, slot);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int e = 0; e < 8; ++e)
-        pb[b][kk][e] = (bf16_t)__builtin_amdgcn_exp2f(__builtin_fmaf(s[b][2 * kk + (e >> 2)][e & 3], sl, m_neg[b]));
+      for (int e = 0; e < 8; ++e) {
+        const float pe = __builtin_amdgcn_exp2f(__builtin_fmaf(s[b][2 * kk + (e >> 2)][e & 3], sl, m_neg[b]));
+        pb[0][b][kk][e] = (bf16_t)pe;
+        if (TERMS<DH> == 2) pb[TERMS<DH> - 1][b][kk][e] = (bf16_t)(pe - (float)pb[0][b][kk][e]);
+      }
       __builtin_amdgcn_sched_barrier(0);
     }
   };
@@ -501,32 +542,32 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
   if constexpr (SPLIT) {
     // the two halves of the keys meet in LDS: group 1 leaves (maximum, denominator, O), group 0 merges
     __syncthreads();
-    float* mine = (float*)(sT + (wave & 3) * (72 * 256)) + lane;      // [float][lane]
+    float* mine = (float*)(sT + (wave & 3) * ((4 * DB + 4) * 2 * 256)) + lane;      // [float][lane]
     if (grp == 1) {
 #pragma unroll
       for (int b = 0; b < 2; ++b) {
-        mine[(b * 36 + 0) * 64] = m_run[b];
-        mine[(b * 36 + 1) * 64] = acc_l[b][0];
+        mine[(b * (4 * DB + 4) + 0) * 64] = m_raw[b];
+        mine[(b * (4 * DB + 4) + 1) * 64] = acc_l[b][0];
 #pragma unroll
-        for (int d = 0; d < 8; ++d)
+        for (int d = 0; d < DB; ++d)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) mine[(b * 36 + 4 + d * 4 + r) * 64] = acc[b][d][r];
+          for (int r = 0; r < 4; ++r) mine[(b * (4 * DB + 4) + 4 + d * 4 + r) * 64] = acc[b][d][r];
       }
     }
     __syncthreads();
     if (grp == 1) return;
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
-      const float m1 = mine[(b * 36 + 0) * 64], l1 = mine[(b * 36 + 1) * 64];
-      const float m_new = fmaxf(m_run[b], m1);
-      const float f0 = m_run[b] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m_run[b] - m_new);
-      const float f1 = m1 == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m1 - m_new);
-      m_run[b] = m_new;
+      const float m1 = mine[(b * (4 * DB + 4) + 0) * 64], l1 = mine[(b * (4 * DB + 4) + 1) * 64];
+      const float m_new = fmaxf(m_raw[b], m1);
+      const float f0 = m_raw[b] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((m_raw[b] - m_new) * sl);
+      const float f1 = m1 == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((m1 - m_new) * sl);
+      m_raw[b] = m_new;
       acc_l[b][0] = acc_l[b][0] * f0 + l1 * f1;
 #pragma unroll
-      for (int d = 0; d < 8; ++d)
+      for (int d = 0; d < DB; ++d)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) acc[b][d][r] = acc[b][d][r] * f0 + mine[(b * 36 + 4 + d * 4 + r) * 64] * f1;
+        for (int r = 0; r < 4; ++r) acc[b][d][r] = acc[b][d][r] * f0 + mine[(b * (4 * DB + 4) + 4 + d * 4 + r) * 64] * f1;
     }
   }
 #pragma unroll
@@ -537,24 +578,25 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
     const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.0f;      // a query that saw no key: o = 0, lse = -inf
     bf16_t* op = o + ((int64_t)my_q * Hq + h) * DH + 4 * lg;
 #pragma unroll
-    for (int d = 0; d < 8; ++d) {
+    for (int d = 0; d < DB; ++d) {
       bf16x4 w;
 #pragma unroll
       for (int r = 0; r < 4; ++r) w[r] = (bf16_t)(acc[b][d][r] * inv);
       *(bf16x4*)(op + d * 16) = w;
     }
-    if (lg == 0) lse[(int64_t)h * c + my_q] = l_tot > 0.f ? (m_run[b] + log2f(l_tot)) * LN2 : -INFINITY;
+    if (lg == 0) lse[(int64_t)h * c + my_q] = l_tot > 0.f ? (m_raw[b] * sl + log2f(l_tot)) * LN2 : -INFINITY;
   }
 }
 
 // ----------------------------------------------------------------------- dQ --
+template <int DH>
 __global__ __launch_bounds__(AT_THREADS) void attn_bwd_dq_mfma_k(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                                                     const bf16_t* __restrict__ v, const bf16_t* __restrict__ d_o,
                                                                     const float* __restrict__ lse, const float* __restrict__ delta,
                                                                     bf16_t* __restrict__ dq, int Hq, int Hkv, int q_start, int c,
                                                                     float scale, const float2* __restrict__ rope, int window,
                                                                     int kv_first) {
-  __shared__ __attribute__((aligned(1024))) char sT[4][TILE64_BYTES];   // stage st: K = sT[2 st], V = sT[2 st + 1]
+  __shared__ __attribute__((aligned(1024))) char sT[4][TILE64<DH>];   // stage st: K = sT[2 st], V = sT[2 st + 1]
 
   const int q0 = blockIdx.x * TQ, h = blockIdx.y, kvh = h / (Hq / Hkv);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5;
@@ -577,33 +619,34 @@ __global__ __launch_bounds__(AT_THREADS) void attn_bwd_dq_mfma_k(const bf16_t* _
   const int kt0 = first_key(q_start + q0) / TK;
 
   const uint32_t lds0 = lds_addr(&sT[0][0]);
-  const FragPre fp = frag_pre(lds0);
-  const TileLoad<AT_THREADS> tl = tile_load_pre<AT_THREADS>(kv_stride);
+  const FragPre<DH> fp = frag_pre<DH>(lds0);
+  const TileLoad<DH, AT_THREADS> tl = tile_load_pre<DH, AT_THREADS>(kv_stride);
 
-  bf16x8 bq[8], bdo[8];
+  constexpr int KS = DH / 16, DB = DH / 32;      // k16 steps of a score, 32-row blocks of the output
+  bf16x8 bq[KS], bdo[KS];
   {
     const int64_t off = ((int64_t)q_row * Hq + h) * DH + half * 8;
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) { bq[ks] = *(const bf16x8*)(q + off + ks * 16); bdo[ks] = *(const bf16x8*)(d_o + off + ks * 16); }
+    for (int ks = 0; ks < KS; ++ks) { bq[ks] = *(const bf16x8*)(q + off + ks * 16); bdo[ks] = *(const bf16x8*)(d_o + off + ks * 16); }
   }
   const float lse_q = lse[(int64_t)h * c + q_row];
   const float lse2 = lse_q == -INFINITY ? 0.0f : lse_q * LOG2E;    // a query that saw no key: every score is masked, p = exp2(-inf) = 0
   const float dlt = delta[(int64_t)h * c + q_row];
   const float sl = scale * LOG2E;
-  f32x16 acc[4];
+  f32x16 acc[DB];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) acc[i] = zero16();
+  for (int i = 0; i < DB; ++i) acc[i] = zero16();
 
   auto step = [&](int kt, auto stage) {
-    constexpr uint32_t oK = decltype(stage)::value * 2 * TILE64_BYTES, oV = oK + TILE64_BYTES;
+    constexpr uint32_t oK = decltype(stage)::value * 2 * TILE64<DH>, oV = oK + TILE64<DH>;
     const int k0 = kt * TK;
     if (qw0 >= c || k0 > wave_last_key || k0 + TK - 1 < wave_lo_min) return;
     const bool diag = k0 + TK - 1 > wave_first_qpos || k0 < wave_lo_max;
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
       f32x16 s = zero16(), dp = zero16();
-      mfma_chain<16>([&](int i) { return lds_b128(fp.rows[i & 7] + (i < 8 ? oK : oV) + b * 32 * ROW_BYTES); },
-                     [&](int i, const bf16x8& f) { if (i < 8) s = MFMA(f, bq[i], s); else dp = MFMA(f, bdo[i - 8], dp); });
+      mfma_chain<2 * KS>([&](int i) { return lds_b128(fp.rows[i % KS] + (i < KS ? oK : oV) + b * 32 * (DH * 2)); },
+                         [&](int i, const bf16x8& f) { if (i < KS) s = MFMA(f, bq[i], s); else dp = MFMA(f, bdo[i - KS], dp); });
       if (diag) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
@@ -616,17 +659,22 @@ __global__ __launch_bounds__(AT_THREADS) void attn_bwd_dq_mfma_k(const bf16_t* _
         const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], sl, -lse2));
         s[r] = p * (dp[r] - dlt);                              // dS^T (the factor `scale` is applied at the end)
       }
-      bf16x8 db[2];
-      db[0] = pack8(s, 0);
-      db[1] = pack8(s, 1);
-      mfma_chain<8>([&](int i) { return lds_tr(fp.tr[(i & 3) * 2] + oK + (b * 32 + (i >> 2) * 16) * ROW_BYTES, fp.tr[(i & 3) * 2 + 1] + oK + (b * 32 + (i >> 2) * 16) * ROW_BYTES); },
-                    [&](int i, const bf16x8& f) { acc[i & 3] = MFMA(f, db[i >> 2], acc[i & 3]); });
+      bf16x8 db[TERMS<DH>][2];
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        db[0][ks] = pack8(s, ks);
+        if (TERMS<DH> == 2) db[TERMS<DH> - 1][ks] = rest8(s, ks, db[0][ks]);
+      }
+      mfma_chain<2 * DB>([&](int i) { const uint32_t o = oK + (b * 32 + i / DB * 16) * (DH * 2); return lds_tr(fp.tr[i % DB * 2] + o, fp.tr[i % DB * 2 + 1] + o); },
+                         [&](int i, const bf16x8& f) {
+                           for (int t = 0; t < TERMS<DH>; ++t) acc[i % DB] = MFMA(f, db[t][i / DB], acc[i % DB]);
+                         });
     }
   };
   auto issue = [&](int kt, int st) {
     const int64_t row0 = (int64_t)kt * TK;
-    dma_tile64(tl, kbase + row0 * kv_stride, kv_stride, n_total - kt * TK, lds0 + (uint32_t)(st * 2 * TILE64_BYTES));
-    dma_tile64(tl, vbase + row0 * kv_stride, kv_stride, n_total - kt * TK, lds0 + (uint32_t)((st * 2 + 1) * TILE64_BYTES));
+    dma_tile64(tl, kbase + row0 * kv_stride, kv_stride, n_total - kt * TK, lds0 + (uint32_t)(st * 2 * TILE64<DH>));
+    dma_tile64(tl, vbase + row0 * kv_stride, kv_stride, n_total - kt * TK, lds0 + (uint32_t)((st * 2 + 1) * TILE64<DH>));
   };
   using S0 = std::integral_constant<int, 0>;
   using S1 = std::integral_constant<int, 1>;
@@ -648,27 +696,27 @@ __global__ __launch_bounds__(AT_THREADS) void attn_bwd_dq_mfma_k(const bf16_t* _
   if (q_valid) {
     bf16_t* op = dq + ((int64_t)my_q * Hq + h) * DH;
     if (rope) {
-      // adjoint of the rotary embedding on the way out: element j < 64 (accumulator block i < 2) pairs with j + 64
-      // (block i + 2, same register of the same lane); rotation by the negative angle
+      // adjoint of the rotary embedding on the way out: element j < DH / 2 (accumulator block i < DB / 2) pairs with
+      // j + DH / 2 (block i + DB / 2, same register of the same lane); rotation by the negative angle
       const float2* tr = rope + (int64_t)my_q * (DH / 2) + 4 * half;
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < DB / 2; ++i)
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
           bf16x4 w1, w2;
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             const float2 cs = tr[i * 32 + 8 * a + e];
-            const float d1 = acc[i][4 * a + e] * scale, d2 = acc[i + 2][4 * a + e] * scale;
+            const float d1 = acc[i][4 * a + e] * scale, d2 = acc[i + DB / 2][4 * a + e] * scale;
             w1[e] = (bf16_t)(d1 * cs.x + d2 * cs.y);
             w2[e] = (bf16_t)(d2 * cs.x - d1 * cs.y);
           }
           *(bf16x4*)(op + i * 32 + 8 * a + 4 * half) = w1;
-          *(bf16x4*)(op + (i + 2) * 32 + 8 * a + 4 * half) = w2;
+          *(bf16x4*)(op + (i + DB / 2) * 32 + 8 * a + 4 * half) = w2;
         }
     } else {
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < DB; ++i)
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
           bf16x4 w;
@@ -694,14 +742,15 @@ __global__ __launch_bounds__(AT_THREADS) void attn_bwd_dq_mfma_k(const bf16_t* _
 // The loop walks the query tiles at or below the diagonal and, for each, the query heads of the group.
 constexpr int KV_STAGES = 3;
 
+template <int DH>
 __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                                                   const bf16_t* __restrict__ v, const bf16_t* __restrict__ d_o,
                                                                   const float* __restrict__ lse2, const float* __restrict__ delta,
                                                                   float* __restrict__ dk, float* __restrict__ dv, int Hq, int Hkv,
                                                                   int q_start, int c, float scale, int window, int kv_first,
                                                                   int key_block0) {
-  __shared__ __attribute__((aligned(1024))) char sQD[KV_STAGES][2][TILE64_BYTES];   // [stage][Q | dO]
-  __shared__ __attribute__((aligned(16))) bf16x8 sP[2][4][4][64];   // [tile parity][key block][query block * 2 + k16 step][lane]
+  __shared__ __attribute__((aligned(1024))) char sQD[KV_STAGES][2][TILE64<DH>];   // [stage][Q | dO]
+  __shared__ __attribute__((aligned(16))) bf16x8 sP[2][4][4 * TERMS<DH>][64];   // [tile parity][key block][(query block * 2 + k16 step), term][lane]
   __shared__ __attribute__((aligned(16))) float sL[KV_STAGES][QT];  // log2-domain log-sum-exp of the tile's queries
   __shared__ __attribute__((aligned(16))) float sDl[KV_STAGES][QT]; // delta of the tile's queries
 
@@ -720,19 +769,20 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
   // Fragment addresses: one set reaches 64 KiB (stages 0 and 1), a second one stage 2.  Role P reads Q row-wise and
   // dO transposed, role S the other way round; only the half of each set that the role uses stays live.
   const uint32_t lds0 = lds_addr(&sQD[0][0][0]);
-  const FragPre f0 = frag_pre(lds0 + (role_p ? 0 : TILE64_BYTES));                 // row-wise operand: Q (P) / dO (S)
-  const FragPre g0 = frag_pre(lds0 + (role_p ? TILE64_BYTES : 0));                 // transposed operand: dO (P) / Q (S)
-  const FragPre f2 = frag_pre(lds0 + 2 * 2 * TILE64_BYTES + (role_p ? 0 : TILE64_BYTES));
-  const FragPre g2 = frag_pre(lds0 + 2 * 2 * TILE64_BYTES + (role_p ? TILE64_BYTES : 0));
-  const TileLoad<KV_THREADS> tl = tile_load_pre<KV_THREADS>(q_stride);
-  const uint32_t sp_lane = pin(lds_addr(&sP[0][kb][0][lane]));                      // + parity * 8192 + (b * 2 + ks) * 1024
+  const FragPre<DH> f0 = frag_pre<DH>(lds0 + (role_p ? 0 : TILE64<DH>));                 // row-wise operand: Q (P) / dO (S)
+  const FragPre<DH> g0 = frag_pre<DH>(lds0 + (role_p ? TILE64<DH> : 0));                 // transposed operand: dO (P) / Q (S)
+  const FragPre<DH> f2 = frag_pre<DH>(lds0 + 2 * 2 * TILE64<DH> + (role_p ? 0 : TILE64<DH>));
+  const FragPre<DH> g2 = frag_pre<DH>(lds0 + 2 * 2 * TILE64<DH> + (role_p ? TILE64<DH> : 0));
+  const TileLoad<DH, KV_THREADS> tl = tile_load_pre<DH, KV_THREADS>(q_stride);
+  const uint32_t sp_lane = pin(lds_addr(&sP[0][kb][0][lane]));                      // + parity * sizeof(sP[0]) + ((term * 2 + b) * 2 + ks) * 1024
   const uint32_t stat_lane = pin(lds_addr(role_p ? &sL[0][4 * half] : &sDl[0][4 * half]));   // + stage * 256 + (b * 32 + 8 a) * 4
 
-  bf16x8 breg[8];   // B operand of the first product: K rows (role P) or V rows (role S) of my key
+  constexpr int KS = DH / 16, DB = DH / 32;
+  bf16x8 breg[KS];   // B operand of the first product: K rows (role P) or V rows (role S) of my key
   {
     const bf16_t* src = (role_p ? k : v) + (int64_t)key_row * kv_stride + (int64_t)kvh * DH + half * 8;
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) breg[ks] = *(const bf16x8*)(src + ks * 16);
+    for (int ks = 0; ks < KS; ++ks) breg[ks] = *(const bf16x8*)(src + ks * 16);
   }
   const float sl = scale * LOG2E;
 
@@ -746,8 +796,8 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
   auto issue = [&](int it, int stage) {
     const int qt = qt_first + it / G, hh = kvh * G + it % G;
     const int64_t corner = (int64_t)qt * QT * q_stride + (int64_t)hh * DH;
-    dma_tile64(tl, q + corner, q_stride, c - qt * QT, lds0 + (uint32_t)(stage * 2 * TILE64_BYTES));
-    dma_tile64(tl, d_o + corner, q_stride, c - qt * QT, lds0 + (uint32_t)((stage * 2 + 1) * TILE64_BYTES));
+    dma_tile64(tl, q + corner, q_stride, c - qt * QT, lds0 + (uint32_t)(stage * 2 * TILE64<DH>));
+    dma_tile64(tl, d_o + corner, q_stride, c - qt * QT, lds0 + (uint32_t)((stage * 2 + 1) * TILE64<DH>));
     if (wave < 2) {   // 64 log-sum-exp values (wave 0) and 64 deltas (wave 1), 4 B per lane, also direct to LDS
       const int row = min(qt * QT + lane, c - 1);
       dma4(uniform_ptr((wave == 0 ? lse2 : delta) + (int64_t)hh * c), (uint32_t)row * 4u,
@@ -762,11 +812,11 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
   };
   auto lds_f4 = [](uint32_t addr) { return *(const float4*)(__attribute__((address_space(3))) const char*)(uintptr_t)addr; };
 
-  auto p_step = [&](f32x16 (&acc)[4], int it, auto stage_c, int par) __attribute__((always_inline)) {
+  auto p_step = [&](f32x16 (&acc)[DB], int it, auto stage_c, int par) __attribute__((always_inline)) {
     constexpr int stage = decltype(stage_c)::value;
-    constexpr uint32_t so = (stage & 1) * 2 * TILE64_BYTES;        // offset of the stage from its address set
-    const FragPre& fr = stage < 2 ? f0 : f2;
-    const FragPre& gt = stage < 2 ? g0 : g2;
+    constexpr uint32_t so = (stage & 1) * 2 * TILE64<DH>;        // offset of the stage from its address set
+    const FragPre<DH>& fr = stage < 2 ? f0 : f2;
+    const FragPre<DH>& gt = stage < 2 ? g0 : g2;
     const int qbase = (qt_first + it / G) * QT;
     if (!tile_active(qbase)) return;
     const bool diag = (q_start + qbase < kw0 + 31) || (qbase + QT > c) || kw0 < kv_first ||   // some pair masked, or ragged query tile
@@ -776,7 +826,7 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
     for (int b = 0; b < 2; ++b) {      // one 32-query block at a time: fewer live registers
       f32x16 t = zero16();
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks) t = MFMA(lds_b128(fr.rows[ks] + so + b * 32 * ROW_BYTES), breg[ks], t);
+      for (int ks = 0; ks < KS; ++ks) t = MFMA(lds_b128(fr.rows[ks] + so + b * 32 * (DH * 2)), breg[ks], t);
       // accumulator: column = my key, rows = queries qbase + b*32 + acc_row(r, half)
       if (diag) {
 #pragma unroll
@@ -793,26 +843,35 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
 #pragma unroll
         for (int e = 0; e < 4; ++e) t[4 * a + e] = __builtin_amdgcn_exp2f(__builtin_fmaf(t[4 * a + e], sl, -lv[e]));
       }
-      bf16x8 pb[2];
+      bf16x8 pb[DV_TERMS<DH>][2];
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
-        pb[ks] = pack8(t, ks);
-        *(bf16x8*)(__attribute__((address_space(3))) char*)(uintptr_t)(sp + (b * 2 + ks) * 1024) = pb[ks];
+        pb[0][ks] = pack8(t, ks);
+        if constexpr (DV_TERMS<DH> == 3) {
+          pb[1][ks] = rest8(t, ks, pb[0][ks]);
+#pragma unroll
+          for (int j = 0; j < 8; ++j) pb[2][ks][j] = (bf16_t)((t[8 * ks + j] - (float)pb[0][ks][j]) - (float)pb[1][ks][j]);
+        }
+#pragma unroll
+        for (int u = 0; u < TERMS<DH>; ++u)
+          *(bf16x8*)(__attribute__((address_space(3))) char*)(uintptr_t)(sp + ((u * 2 + b) * 2 + ks) * 1024) = pb[u][ks];
       }
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          acc[i] = MFMA(lds_tr(gt.tr[i * 2] + so + (b * 32 + ks * 16) * ROW_BYTES, gt.tr[i * 2 + 1] + so + (b * 32 + ks * 16) * ROW_BYTES),
-                        pb[ks], acc[i]);
+        for (int i = 0; i < DB; ++i) {
+          const bf16x8 g = lds_tr(gt.tr[i * 2] + so + (b * 32 + ks * 16) * (DH * 2), gt.tr[i * 2 + 1] + so + (b * 32 + ks * 16) * (DH * 2));
+#pragma unroll
+          for (int u = 0; u < DV_TERMS<DH>; ++u) acc[i] = MFMA(g, pb[u][ks], acc[i]);
+        }
     }
   };
 
-  auto s_step = [&](f32x16 (&acc)[4], int it, auto stage_c, int par) __attribute__((always_inline)) {
+  auto s_step = [&](f32x16 (&acc)[DB], int it, auto stage_c, int par) __attribute__((always_inline)) {
     constexpr int stage = decltype(stage_c)::value;
-    constexpr uint32_t so = (stage & 1) * 2 * TILE64_BYTES;
-    const FragPre& fr = stage < 2 ? f0 : f2;
-    const FragPre& gt = stage < 2 ? g0 : g2;
+    constexpr uint32_t so = (stage & 1) * 2 * TILE64<DH>;
+    const FragPre<DH>& fr = stage < 2 ? f0 : f2;
+    const FragPre<DH>& gt = stage < 2 ? g0 : g2;
     const int qbase = (qt_first + it / G) * QT;
     if (!tile_active(qbase)) return;
     const uint32_t sp = sp_lane + (uint32_t)par * (uint32_t)sizeof(sP[0]);
@@ -820,20 +879,27 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
     for (int b = 0; b < 2; ++b) {
       f32x16 t = zero16();
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks) t = MFMA(lds_b128(fr.rows[ks] + so + b * 32 * ROW_BYTES), breg[ks], t);
+      for (int ks = 0; ks < KS; ++ks) t = MFMA(lds_b128(fr.rows[ks] + so + b * 32 * (DH * 2)), breg[ks], t);
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
         const float4 d0 = lds_f4(stat_lane + stage * QT * 4 + (b * 32 + 16 * ks) * 4);
         const float4 d1 = lds_f4(stat_lane + stage * QT * 4 + (b * 32 + 16 * ks + 8) * 4);
         const float dl[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
         const bf16x8 p8 = lds_b128(sp + (b * 2 + ks) * 1024);
+        bf16x8 p8_rest;
+        if (TERMS<DH> == 2) p8_rest = lds_b128(sp + ((2 + b) * 2 + ks) * 1024);
 #pragma unroll
         for (int j = 0; j < 8; ++j)     // dS (the softmax scale is applied once at the end)
-          t[8 * ks + j] = (float)p8[j] * (t[8 * ks + j] - dl[j]);
-        const bf16x8 db = pack8(t, ks);
+          t[8 * ks + j] = (TERMS<DH> == 2 ? (float)p8[j] + (float)p8_rest[j] : (float)p8[j]) * (t[8 * ks + j] - dl[j]);
+        bf16x8 db[TERMS<DH>];
+        db[0] = pack8(t, ks);
+        if (TERMS<DH> == 2) db[TERMS<DH> - 1] = rest8(t, ks, db[0]);
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          acc[i] = MFMA(lds_tr(gt.tr[i * 2] + so + (b * 32 + ks * 16) * ROW_BYTES, gt.tr[i * 2 + 1] + so + (b * 32 + ks * 16) * ROW_BYTES), db, acc[i]);
+        for (int i = 0; i < DB; ++i) {
+          const bf16x8 g = lds_tr(gt.tr[i * 2] + so + (b * 32 + ks * 16) * (DH * 2), gt.tr[i * 2 + 1] + so + (b * 32 + ks * 16) * (DH * 2));
+#pragma unroll
+          for (int u = 0; u < TERMS<DH>; ++u) acc[i] = MFMA(g, db[u], acc[i]);
+        }
       }
     }
   };
@@ -850,9 +916,9 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
   using S2 = std::integral_constant<int, 2>;
   auto run = [&](auto role_c) __attribute__((always_inline)) {
     constexpr bool RP = decltype(role_c)::value;
-    f32x16 acc[4];   // dV^T (role P) or dK^T (role S): rows = head_dim, column = my key
+    f32x16 acc[DB];   // dV^T (role P) or dK^T (role S): rows = head_dim, column = my key
 #pragma unroll
-    for (int i = 0; i < 4; ++i) acc[i] = zero16();
+    for (int i = 0; i < DB; ++i) acc[i] = zero16();
     auto body = [&](int j, auto st_p, auto st_s, int st_next) __attribute__((always_inline)) {
       WAIT_VM0();
       __syncthreads();
@@ -877,7 +943,7 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
       float* out = (RP ? dv : dk) + (int64_t)my_key * kv_stride + (int64_t)kvh * DH;
       const float f = RP ? 1.0f : scale;
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < DB; ++i)
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
           const int d0 = i * 32 + 8 * a + 4 * half;
@@ -894,6 +960,7 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
 // delta[h, t] = sum_j d_o[t,h,j] * o[t,h,j]  (one wave per (t, h))
 // also lse2[h, t] = lse[h, t] * log2(e), the form the dK/dV kernel's exp2 wants (one multiply per (t, h) here
 // instead of one per score there)
+template <int DH>
 __global__ __launch_bounds__(256) void attn_delta_mfma_k(const bf16_t* __restrict__ o, const bf16_t* __restrict__ d_o,
                                                          const float* __restrict__ lse, float* __restrict__ delta,
                                                          float* __restrict__ lse2, int Hq, int c) {
@@ -901,8 +968,11 @@ __global__ __launch_bounds__(256) void attn_delta_mfma_k(const bf16_t* __restric
   if (pair >= (int64_t)c * Hq) return;
   const int lane = threadIdx.x & 63;
   const int t = (int)(pair / Hq), h = (int)(pair % Hq);
-  const int64_t base = pair * DH + lane * 2;
-  float s = (float)o[base] * (float)d_o[base] + (float)o[base + 1] * (float)d_o[base + 1];
+  float s = 0.f;
+  if (lane < DH / 2) {
+    const int64_t base = pair * DH + lane * 2;
+    s = (float)o[base] * (float)d_o[base] + (float)o[base + 1] * (float)d_o[base + 1];
+  }
   s = wave_sum(s);
   if (lane == 0) {
     delta[(int64_t)h * c + t] = s;
@@ -911,7 +981,7 @@ __global__ __launch_bounds__(256) void attn_delta_mfma_k(const bf16_t* __restric
   }
 }
 
-bool attn_mfma_eligible(int dt, int dh, int Hq, int Hkv) { return dt == DT_BF16 && dh == DH && Hq % Hkv == 0; }
+bool attn_mfma_eligible(int dt, int dh, int Hq, int Hkv) { return dt == DT_BF16 && (dh == 128 || dh == 64) && Hq % Hkv == 0; }
 
 static bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
@@ -921,7 +991,8 @@ bool attn_mfma_aligned(const AttnArgs& a, bool backward) {
   return !backward || (aligned16(a.d_o) && aligned16(a.dq) && aligned16(a.dk) && aligned16(a.dv));
 }
 
-hipError_t attn_forward_mfma(const AttnArgs& a, hipStream_t st) {
+template <int DH>
+static hipError_t forward_dh(const AttnArgs& a, hipStream_t st) {
   if (a.q_len == 0) return hipSuccess;
   // rounds of 256 workgroups (one per CU), a half tile costing half a round: the half tiles where they leave fewer CUs idle
   const int64_t full = cdiv(a.q_len, TQ) * a.Hq, halves = cdiv(a.q_len, TQ / 2) * a.Hq;
@@ -929,19 +1000,20 @@ hipError_t attn_forward_mfma(const AttnArgs& a, hipStream_t st) {
     kernel<<<(unsigned)n, AT_THREADS, 0, st>>>((bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v, (bf16_t*)a.o, a.lse, a.Hq, a.Hkv,
                                                a.q_start, a.q_len, a.scale, a.rope_q, a.window, a.kv_first);
   };
-  if (2 * cdiv(full, 256) > cdiv(halves, 256)) launch(attn_fwd_mfma_k<true>, halves);
-  else launch(attn_fwd_mfma_k<false>, full);
+  if (2 * cdiv(full, 256) > cdiv(halves, 256)) launch(attn_fwd_mfma_k<DH, true>, halves);
+  else launch(attn_fwd_mfma_k<DH, false>, full);
   return hipGetLastError();
 }
 
-hipError_t attn_backward_mfma(const AttnArgs& a, hipStream_t st) {
+template <int DH>
+static hipError_t backward_dh(const AttnArgs& a, hipStream_t st) {
   if (a.q_len == 0) return hipSuccess;
   const int64_t pairs = (int64_t)a.q_len * a.Hq;
   float* lse2 = a.delta + pairs;   // second half of the [2, Hq, c] scratch
-  attn_delta_mfma_k<<<(unsigned)cdiv(pairs, 4), 256, 0, st>>>((const bf16_t*)a.o, (const bf16_t*)a.d_o, a.lse, a.delta, lse2, a.Hq,
+  attn_delta_mfma_k<DH><<<(unsigned)cdiv(pairs, 4), 256, 0, st>>>((const bf16_t*)a.o, (const bf16_t*)a.d_o, a.lse, a.delta, lse2, a.Hq,
                                                               a.q_len);
   dim3 gq((unsigned)cdiv(a.q_len, TQ), a.Hq);
-  attn_bwd_dq_mfma_k<<<gq, AT_THREADS, 0, st>>>((const bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v, (const bf16_t*)a.d_o,
+  attn_bwd_dq_mfma_k<DH><<<gq, AT_THREADS, 0, st>>>((const bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v, (const bf16_t*)a.d_o,
                                                 a.lse, a.delta, (bf16_t*)a.dq, a.Hq, a.Hkv, a.q_start, a.q_len, a.scale, a.rope_q,
                                                 a.window, a.kv_first);
   // key blocks that no query of the chunk can see (before the padding ends, or older than the first query's window)
@@ -950,11 +1022,14 @@ hipError_t attn_backward_mfma(const AttnArgs& a, hipStream_t st) {
   const int kb0 = std::max(0, first_visible) / KV_TILE, kb1 = (int)cdiv(a.q_start + a.q_len, KV_TILE);
   if (kb1 > kb0) {
     dim3 gk((unsigned)(kb1 - kb0), a.Hkv);
-    attn_bwd_dkv_mfma_k<<<gk, KV_THREADS, 0, st>>>((const bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v, (const bf16_t*)a.d_o,
+    attn_bwd_dkv_mfma_k<DH><<<gk, KV_THREADS, 0, st>>>((const bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v, (const bf16_t*)a.d_o,
                                                    lse2, a.delta, a.dk, a.dv, a.Hq, a.Hkv, a.q_start, a.q_len, a.scale,
                                                    a.window, a.kv_first, kb0);
   }
   return hipGetLastError();
 }
+
+hipError_t attn_forward_mfma(const AttnArgs& a, hipStream_t st) { return a.dh == 64 ? forward_dh<64>(a, st) : forward_dh<128>(a, st); }
+hipError_t attn_backward_mfma(const AttnArgs& a, hipStream_t st) { return a.dh == 64 ? backward_dh<64>(a, st) : backward_dh<128>(a, st); }
 
 }  // namespace sbp
