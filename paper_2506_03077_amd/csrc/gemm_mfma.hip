@@ -570,16 +570,17 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
 // workgroup; the reduction of the tiles that are left over (or of all of them, where there are fewer than 256) is split
 // `splits` ways, so that the last round is not mostly idle.  Split tiles go to fp32 scratch and are summed in a fixed order.
 // The number of splits weighs the K steps saved against what the partial tiles cost: about 3.5 K steps for the extra launch
-// and 0.09 K step per partial tile (256 KB written and read back at ~4.5 TB/s against 1.45 us per K step).
+// and 0.09 K step per partial tile (256 KB written and read back at ~4.5 TB/s against 1.45 us per K step).  Up to 32 splits: eight
+// tiles with the reduction of a 50257-word vocabulary, or 28 with that of two MLP widths, would keep most CUs idle with four.
 constexpr int N_CU = 256;
-constexpr int MAX_SPLITS = 8;
+constexpr int MAX_SPLITS = 32;
 struct Schedule { int tiles, full, tail, splits; };
 __host__ __device__ __forceinline__ Schedule make_schedule(int tiles, int k_steps, int scratch_tiles) {
   const int tail = tiles % N_CU;
   int best = 1;
   if (tail > 0) {
     float gain = 0.f;
-    for (int s = 2; s <= MAX_SPLITS && s * tail <= N_CU && s * tail <= scratch_tiles && k_steps / s >= 4; ++s) {
+    for (int s = 2; s <= MAX_SPLITS && s * tail <= N_CU && s * tail <= scratch_tiles && k_steps / s >= 4; s += s < 8 ? 1 : s / 4) {
       const float g = (float)(k_steps - (k_steps + s - 1) / s) - 3.5f - 0.09f * (float)(s * tail);
       if (g > gain) { gain = g; best = s; }
     }
@@ -777,10 +778,10 @@ bool gemm_mfma_numer_ok(const GemmArgs& g) {
          g.numer_targets && g.numer_target_value && !g.swiglu_gate;
 }
 
-size_t gemm_scratch_bytes(int max_m, int max_n, int max_splits) {
+size_t gemm_scratch_bytes(int max_m, int max_n) {
   // partial tiles: at most one per CU is ever useful
   const int64_t tiles = cdiv(max_m, BM) * cdiv(max_n, BN);
-  return (size_t)std::min<int64_t>(N_CU, tiles * std::min(max_splits, MAX_SPLITS)) * PARTIAL_FLOATS * sizeof(float);
+  return (size_t)std::min<int64_t>(N_CU, tiles * MAX_SPLITS) * PARTIAL_FLOATS * sizeof(float);
 }
 static int scratch_tiles_of(const GemmArgs& g) {
   return g.scratch && !((uintptr_t)g.scratch & 15) ? (int)std::min<size_t>(N_CU, g.scratch_bytes / (PARTIAL_FLOATS * sizeof(float))) : 0;

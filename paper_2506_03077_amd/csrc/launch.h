@@ -60,7 +60,7 @@ constexpr int GEMM_STAT_COLS = 256;
 bool gemm_row_stats_supported(const GemmArgs& g);
 bool gemm_numerators_supported(const GemmArgs& g);
 // upper bound of the scratch a GEMM with M <= max_m rows and N <= max_n columns may use
-size_t gemm_scratch_bytes(int max_m, int max_n, int max_splits);
+size_t gemm_scratch_bytes(int max_m, int max_n);
 hipError_t gemm(const GemmArgs& g, hipStream_t st);
 // n independent GEMMs (distinct outputs); one grouped launch when the MFMA kernel can take them all
 // group_small: take the grouped launch also when the problems together have few output tiles (skinny problems)
