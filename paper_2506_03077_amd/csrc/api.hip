@@ -340,6 +340,7 @@ int32_t layer_backward_impl(const sbp_layer_cfg* c, const sbp_layer_weights* w, 
       aa.window = c->window; aa.kv_first = kv_first;
       aa.q = s.q; aa.k = s.K; aa.v = s.V; aa.o = s.o; aa.lse = s.lse;
       aa.d_o = s.d_o; aa.dq = s.dq; aa.dk = s.dK; aa.dv = s.dV; aa.delta = s.delta;
+      aa.dkv_scratch = s.gemm_scratch; aa.dkv_scratch_bytes = s.gemm_scratch_bytes;      // (idle between GEMMs)
       if (fusion_mask() & FUSE_ROPE_Q) aa.rope_q = s.rope + (size_t)r0 * half;   // dq leaves the kernel rotated back (RoPE's adjoint)
       HIPCHK(attn_backward(aa, st));
       if (!(fusion_mask() & FUSE_ROPE_Q)) HIPCHK(rope_apply(dt, s.dq, s.rope + (size_t)r0 * half, n, c->n_q_heads, c->head_dim, true, st));

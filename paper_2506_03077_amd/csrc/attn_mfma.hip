@@ -59,6 +59,7 @@ constexpr int TK = ATTN_TILE_K;          // 64 keys per step (fwd, dQ)
 constexpr int KV_TILE = 128;             // keys per workgroup (dK/dV): 4 key blocks x 2 roles = 8 waves
 constexpr int KV_THREADS = 512;
 constexpr int QT = 64;                   // queries per step (dK/dV)
+constexpr int DKV_MIN_STEPS = 4;         // query tiles that make a workgroup of its own worth while (dK/dV)
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
 
@@ -748,7 +749,7 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
                                                                   const float* __restrict__ lse2, const float* __restrict__ delta,
                                                                   float* __restrict__ dk, float* __restrict__ dv, int Hq, int Hkv,
                                                                   int q_start, int c, float scale, int window, int kv_first,
-                                                                  int key_block0) {
+                                                                  int key_block0, float* __restrict__ part) {
   __shared__ __attribute__((aligned(1024))) char sQD[KV_STAGES][2][TILE64<DH>];   // [stage][Q | dO]
   __shared__ __attribute__((aligned(16))) bf16x8 sP[2][4][4 * TERMS<DH>][64];   // [tile parity][key block][(query block * 2 + k16 step), term][lane]
   __shared__ __attribute__((aligned(16))) float sL[KV_STAGES][QT];  // log2-domain log-sum-exp of the tile's queries
@@ -791,10 +792,11 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
   const int qt_first = max(0, key0 - q_start) / QT;
   int n_qt = (c + QT - 1) / QT;
   if (window > 0) n_qt = min(n_qt, max(0, key0 + KV_TILE - 1 + window - 1 - q_start) / QT + 1);
-  const int n_iter = max(0, n_qt - qt_first) * G;
+  const int n_all = max(0, n_qt - qt_first) * G;
+  const int it0 = (int)((int64_t)n_all * blockIdx.z / gridDim.z), n_iter = (int)((int64_t)n_all * (blockIdx.z + 1) / gridDim.z) - it0;   // this workgroup's share
 
-  auto issue = [&](int it, int stage) {
-    const int qt = qt_first + it / G, hh = kvh * G + it % G;
+  auto issue = [&](int j, int stage) {
+    const int it = it0 + j, qt = qt_first + it / G, hh = kvh * G + it % G;
     const int64_t corner = (int64_t)qt * QT * q_stride + (int64_t)hh * DH;
     dma_tile64(tl, q + corner, q_stride, c - qt * QT, lds0 + (uint32_t)(stage * 2 * TILE64<DH>));
     dma_tile64(tl, d_o + corner, q_stride, c - qt * QT, lds0 + (uint32_t)((stage * 2 + 1) * TILE64<DH>));
@@ -924,9 +926,9 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
       __syncthreads();
       if (j + 1 < n_iter) issue(j + 1, st_next);
       if constexpr (RP) {
-        if (j < n_iter) p_step(acc, j, st_p, j & 1);
+        if (j < n_iter) p_step(acc, it0 + j, st_p, j & 1);
       } else {
-        if (j > 0 && j <= n_iter) s_step(acc, j - 1, st_s, (j - 1) & 1);
+        if (j > 0 && j <= n_iter) s_step(acc, it0 + j - 1, st_s, (j - 1) & 1);
       }
     };
     if (n_iter > 0) {
@@ -940,14 +942,17 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
       }
     }
     if (my_key < n_total) {
-      float* out = (RP ? dv : dk) + (int64_t)my_key * kv_stride + (int64_t)kvh * DH;
+      // several workgroups per key block: each leaves its sum in its own slice [workgroup][dk | dv][key][kv head][DH]
+      const int64_t first = (int64_t)key_block0 * KV_TILE;
+      float* out = part ? part + ((int64_t)blockIdx.z * 2 + (RP ? 1 : 0)) * (n_total - first) * kv_stride + (my_key - first) * kv_stride + (int64_t)kvh * DH
+                        : (RP ? dv : dk) + (int64_t)my_key * kv_stride + (int64_t)kvh * DH;
       const float f = RP ? 1.0f : scale;
 #pragma unroll
       for (int i = 0; i < DB; ++i)
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
           const int d0 = i * 32 + 8 * a + 4 * half;
-          float4 u = *(float4*)(out + d0);
+          float4 u = part ? make_float4(0.f, 0.f, 0.f, 0.f) : *(float4*)(out + d0);
           u.x += acc[i][4 * a + 0] * f; u.y += acc[i][4 * a + 1] * f; u.z += acc[i][4 * a + 2] * f; u.w += acc[i][4 * a + 3] * f;
           *(float4*)(out + d0) = u;
         }
@@ -955,6 +960,19 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
   };
   if (role_p) run(std::true_type{});
   else run(std::false_type{});
+}
+
+// dk / dv += sum over the slices of the split form, in their order.  n4: float4s of dk (and of dv)
+__global__ __launch_bounds__(256) void attn_dkv_sum_k(const float4* __restrict__ part, int slices, int64_t n4, float4* __restrict__ dk, float4* __restrict__ dv) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= 2 * n4) return;
+  float4* out = i < n4 ? dk + i : dv + (i - n4);
+  float4 s = *out;
+  for (int z = 0; z < slices; ++z) {
+    const float4 p = part[(int64_t)z * 2 * n4 + i];
+    s.x += p.x; s.y += p.y; s.z += p.z; s.w += p.w;
+  }
+  *out = s;
 }
 
 // delta[h, t] = sum_j d_o[t,h,j] * o[t,h,j]  (one wave per (t, h))
@@ -1021,10 +1039,21 @@ static hipError_t backward_dh(const AttnArgs& a, hipStream_t st) {
   const int first_visible = std::max(a.kv_first, a.window > 0 ? a.q_start - a.window + 1 : 0);
   const int kb0 = std::max(0, first_visible) / KV_TILE, kb1 = (int)cdiv(a.q_start + a.q_len, KV_TILE);
   if (kb1 > kb0) {
-    dim3 gk((unsigned)(kb1 - kb0), a.Hkv);
+    // Fewer key blocks than CUs (short sequences): the query tiles of a block are dealt to as many workgroups as fill the chip, at
+    // least DKV_MIN_STEPS tiles each (a workgroup's own sum is 128 KB to write and read again, about one tile's time).
+    const int64_t blocks = (int64_t)(kb1 - kb0) * a.Hkv, steps = cdiv(a.q_len, QT) * (a.Hq / a.Hkv);
+    const int64_t first = (int64_t)kb0 * KV_TILE, n = (a.q_start + a.q_len - first) * a.Hkv * DH;
+    int64_t split = std::min<int64_t>(256 / blocks, steps / DKV_MIN_STEPS);
+    if (!a.dkv_scratch || ((uintptr_t)a.dkv_scratch & 15)) split = 1;
+    else split = std::min<int64_t>(split, (int64_t)(a.dkv_scratch_bytes / (2 * n * sizeof(float))));
+    if (split < 2) split = 1;
+    dim3 gk((unsigned)(kb1 - kb0), a.Hkv, (unsigned)split);
     attn_bwd_dkv_mfma_k<DH><<<gk, KV_THREADS, 0, st>>>((const bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v, (const bf16_t*)a.d_o,
                                                    lse2, a.delta, a.dk, a.dv, a.Hq, a.Hkv, a.q_start, a.q_len, a.scale,
-                                                   a.window, a.kv_first, kb0);
+                                                   a.window, a.kv_first, kb0, split > 1 ? a.dkv_scratch : nullptr);
+    if (split > 1)
+      attn_dkv_sum_k<<<(unsigned)cdiv(n / 2, 256), 256, 0, st>>>((const float4*)a.dkv_scratch, (int)split, n / 4,
+                                                                  (float4*)(a.dk + first * a.Hkv * DH), (float4*)(a.dv + first * a.Hkv * DH));
   }
   return hipGetLastError();
 }

@@ -149,6 +149,9 @@ struct AttnArgs {
   void* o; float* lse;     // o [c,Hq,dh]; lse [Hq,c]
   const void* d_o; void* dq; float *dk, *dv;
   float* delta;            // [2,Hq,c] scratch (backward): delta, then the log2-domain log-sum-exp
+  // Optional fp32 scratch (backward, 16-byte aligned): lets short sequences deal the queries of a key block to several workgroups
+  float* dkv_scratch = nullptr;
+  size_t dkv_scratch_bytes = 0;
   // Optional rotary embedding of the chunk's queries folded into the attention kernels: cos/sin rows [c, dh/2] of the
   // chunk's positions.  Forward: q arrives un-rotated, is rotated on load and written back rotated (q must then be
   // writable); backward: q is the rotated tensor the forward left, and dq leaves the kernel already rotated back
