@@ -735,13 +735,17 @@ __global__ __launch_bounds__(AT_THREADS) void attn_bwd_dq_mfma_k(const bf16_t* _
 //   role P (waves 0-3): S = Q K^T -> P = exp2(S*sl - lse) (masked), rounded to bf16 -> leaves P in LDS for its
 //                       partner -> dV^T += dO^T P
 //   role S (waves 4-7): dP = dO V^T -> takes P -> dS = P * (dP - delta) -> dK^T += Q^T dS
-// Each role keeps only its own operand fragments (K or V) and its own accumulator (dV or dK) in registers:
-// half the registers of a do-everything wave, so two waves fit per SIMD.  Role S runs one tile behind role P:
-// in step j role P works on tile j while role S works on tile j-1, whose P is already in LDS, so inside a step
-// the two waves of a SIMD never wait for each other and the exponentials of one overlap the MFMAs of the other.
-// That takes three stages of the Q / dO tiles (tile j+1 in flight, j and j-1 in use) and two of P.
+// Each role keeps only its own operand fragments (K or V) and its own accumulator (dV or dK) in registers: half the registers of a
+// do-everything wave, so two waves fit per SIMD.  As in the forward kernel a tile costs a wave two slots, each closed by a barrier:
+// multiply (dV += dO^T P resp. dK += Q^T dS of the previous tile, S = Q K^T resp. dP = dO V^T of this one) and vector work; role S runs
+// one slot behind role P - it then finds the P of its tile in LDS - so on every SIMD one wave multiplies while the other works on
+// exponentials or dS.  Four stages of the Q / dO tiles; role P loads two tiles ahead, role S three.
+// What bounds it: as in the forward kernel, vector work and MFMAs of a SIMD's two waves share the issue port.  Last 2048-query chunk of 32k,
+// 28 / 4 heads: dQ + dK/dV 3.08 -> 2.95 ms, all of it here (about 1.85 -> 1.72), against one barrier per tile and each wave doing its
+// products and its vector work in any order.
 // The loop walks the query tiles at or below the diagonal and, for each, the query heads of the group.
-constexpr int KV_STAGES = 3;
+constexpr int KV_STAGES = 4;
+constexpr int CHAIN = 6;                 // LDS fragments requested ahead of the products (dK/dV)
 
 template <int DH>
 __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
@@ -750,14 +754,14 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
                                                                   float* __restrict__ dk, float* __restrict__ dv, int Hq, int Hkv,
                                                                   int q_start, int c, float scale, int window, int kv_first,
                                                                   int key_block0, float* __restrict__ part) {
-  __shared__ __attribute__((aligned(1024))) char sQD[KV_STAGES][2][TILE64<DH>];   // [stage][Q | dO]
-  __shared__ __attribute__((aligned(16))) bf16x8 sP[2][4][4 * TERMS<DH>][64];   // [tile parity][key block][(query block * 2 + k16 step), term][lane]
+  __shared__ __attribute__((aligned(1024))) char sQD[2][KV_STAGES][TILE64<DH>];   // [Q | dO][stage]
+  __shared__ __attribute__((aligned(16))) bf16x8 sP[4][4 * TERMS<DH>][64];   // [key block][(query block * 2 + k16 step), term][lane]
   __shared__ __attribute__((aligned(16))) float sL[KV_STAGES][QT];  // log2-domain log-sum-exp of the tile's queries
   __shared__ __attribute__((aligned(16))) float sDl[KV_STAGES][QT]; // delta of the tile's queries
 
   const int G = Hq / Hkv;
   const int key0 = (key_block0 + (int)blockIdx.x) * KV_TILE, kvh = blockIdx.y;   // key blocks before key_block0 are visible to no query
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, half = lane >> 5;
   const int kb = wave & 3;
   const bool role_p = wave < 4;
   const int n_total = q_start + c;
@@ -767,15 +771,13 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
   const int64_t kv_stride = (int64_t)Hkv * DH;
   const int64_t q_stride = (int64_t)Hq * DH;
 
-  // Fragment addresses: one set reaches 64 KiB (stages 0 and 1), a second one stage 2.  Role P reads Q row-wise and
-  // dO transposed, role S the other way round; only the half of each set that the role uses stays live.
-  const uint32_t lds0 = lds_addr(&sQD[0][0][0]);
-  const FragPre<DH> f0 = frag_pre<DH>(lds0 + (role_p ? 0 : TILE64<DH>));                 // row-wise operand: Q (P) / dO (S)
-  const FragPre<DH> g0 = frag_pre<DH>(lds0 + (role_p ? TILE64<DH> : 0));                 // transposed operand: dO (P) / Q (S)
-  const FragPre<DH> f2 = frag_pre<DH>(lds0 + 2 * 2 * TILE64<DH> + (role_p ? 0 : TILE64<DH>));
-  const FragPre<DH> g2 = frag_pre<DH>(lds0 + 2 * 2 * TILE64<DH> + (role_p ? TILE64<DH> : 0));
+  // Fragment addresses: one set reaches all stages of its operand with immediate offsets.  Role P reads Q row-wise and dO
+  // transposed, role S the other way round; only the half of each set that the role uses stays live.
+  const uint32_t lds0 = lds_addr(&sQD[0][0][0]), lds_do = lds0 + KV_STAGES * TILE64<DH>;
+  const FragPre<DH> fr = frag_pre<DH>(role_p ? lds0 : lds_do);                 // row-wise operand: Q (P) / dO (S)
+  const FragPre<DH> gt = frag_pre<DH>(role_p ? lds_do : lds0);                 // transposed operand: dO (P) / Q (S)
   const TileLoad<DH, KV_THREADS> tl = tile_load_pre<DH, KV_THREADS>(q_stride);
-  const uint32_t sp_lane = pin(lds_addr(&sP[0][kb][0][lane]));                      // + parity * sizeof(sP[0]) + ((term * 2 + b) * 2 + ks) * 1024
+  const uint32_t sp_lane = pin(lds_addr(&sP[kb][0][lane]));                      // + ((term * 2 + b) * 2 + ks) * 1024
   const uint32_t stat_lane = pin(lds_addr(role_p ? &sL[0][4 * half] : &sDl[0][4 * half]));   // + stage * 256 + (b * 32 + 8 a) * 4
 
   constexpr int KS = DH / 16, DB = DH / 32;
@@ -784,6 +786,9 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
     const bf16_t* src = (role_p ? k : v) + (int64_t)key_row * kv_stride + (int64_t)kvh * DH + half * 8;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) breg[ks] = *(const bf16x8*)(src + ks * 16);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(breg[ks]));   // (arrived: the compiler must not wait for them in the loop)
+    AT_WAIT_VM(0);
   }
   const float sl = scale * LOG2E;
 
@@ -795,16 +800,20 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
   const int n_all = max(0, n_qt - qt_first) * G;
   const int it0 = (int)((int64_t)n_all * blockIdx.z / gridDim.z), n_iter = (int)((int64_t)n_all * (blockIdx.z + 1) / gridDim.z) - it0;   // this workgroup's share
 
-  auto issue = [&](int j, int stage) {
-    const int it = it0 + j, qt = qt_first + it / G, hh = kvh * G + it % G;
+  // Loads of this workgroup's next tile (query tile lq, head lh of the group); past the end the last one again, so that the wait counts
+  // stay the same.
+  int lq = qt_first + it0 / G, lh = it0 % G, left = n_iter;
+  auto issue = [&](int stage) {
+    const int qt = lq, hh = kvh * G + lh;
+    if (--left > 0 && ++lh == G) { lh = 0; ++lq; }
     const int64_t corner = (int64_t)qt * QT * q_stride + (int64_t)hh * DH;
-    dma_tile64(tl, q + corner, q_stride, c - qt * QT, lds0 + (uint32_t)(stage * 2 * TILE64<DH>));
-    dma_tile64(tl, d_o + corner, q_stride, c - qt * QT, lds0 + (uint32_t)((stage * 2 + 1) * TILE64<DH>));
-    if (wave < 2) {   // 64 log-sum-exp values (wave 0) and 64 deltas (wave 1), 4 B per lane, also direct to LDS
-      const int row = min(qt * QT + lane, c - 1);
-      dma4(uniform_ptr((wave == 0 ? lse2 : delta) + (int64_t)hh * c), (uint32_t)row * 4u,
-           __builtin_amdgcn_readfirstlane(lds_addr(wave == 0 ? &sL[stage][0] : &sDl[stage][0])));
-    }
+    dma_tile64(tl, q + corner, q_stride, c - qt * QT, lds0 + (uint32_t)(stage * TILE64<DH>));
+    dma_tile64(tl, d_o + corner, q_stride, c - qt * QT, lds_do + (uint32_t)(stage * TILE64<DH>));
+    // 64 log-sum-exp values (role P) or deltas (role S), 4 B per lane, also direct to LDS (by every wave of the role, the same
+    // values, so that all waves count the same number of loads)
+    const int row = min(qt * QT + lane, c - 1);
+    dma4(uniform_ptr((role_p ? lse2 : delta) + (int64_t)hh * c), (uint32_t)row * 4u,
+         __builtin_amdgcn_readfirstlane(lds_addr(role_p ? &sL[stage][0] : &sDl[stage][0])));
   };
   // One 64-query tile = two 32-query blocks.  `active`: the wave has a valid key and some query of the tile is
   // at or after its first key (the same answer for both waves of a key block).
@@ -814,132 +823,125 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
   };
   auto lds_f4 = [](uint32_t addr) { return *(const float4*)(__attribute__((address_space(3))) const char*)(uintptr_t)addr; };
 
-  auto p_step = [&](f32x16 (&acc)[DB], int it, auto stage_c, int par) __attribute__((always_inline)) {
-    constexpr int stage = decltype(stage_c)::value;
-    constexpr uint32_t so = (stage & 1) * 2 * TILE64<DH>;        // offset of the stage from its address set
-    const FragPre<DH>& fr = stage < 2 ? f0 : f2;
-    const FragPre<DH>& gt = stage < 2 ? g0 : g2;
-    const int qbase = (qt_first + it / G) * QT;
-    if (!tile_active(qbase)) return;
-    const bool diag = (q_start + qbase < kw0 + 31) || (qbase + QT > c) || kw0 < kv_first ||   // some pair masked, or ragged query tile
-                      (window > 0 && q_start + qbase + QT - 1 - window >= kw0);
-    const uint32_t sp = sp_lane + (uint32_t)par * (uint32_t)sizeof(sP[0]);
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {      // one 32-query block at a time: fewer live registers
-      f32x16 t = zero16();
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) t = MFMA(lds_b128(fr.rows[ks] + so + b * 32 * (DH * 2)), breg[ks], t);
-      // accumulator: column = my key, rows = queries qbase + b*32 + acc_row(r, half)
-      if (diag) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int qi = qbase + b * 32 + acc_row(r, half);
-          if (qi >= c || my_key > q_start + qi || my_key < kv_first || (window > 0 && my_key <= q_start + qi - window))
-            t[r] = -INFINITY;                                          // exp2(-inf) = 0
-        }
-      }
-#pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        const float4 l4 = lds_f4(stat_lane + stage * QT * 4 + (b * 32 + 8 * a) * 4);
-        const float lv[4] = {l4.x, l4.y, l4.z, l4.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) t[4 * a + e] = __builtin_amdgcn_exp2f(__builtin_fmaf(t[4 * a + e], sl, -lv[e]));
-      }
-      bf16x8 pb[DV_TERMS<DH>][2];
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        pb[0][ks] = pack8(t, ks);
-        if constexpr (DV_TERMS<DH> == 3) {
-          pb[1][ks] = rest8(t, ks, pb[0][ks]);
-#pragma unroll
-          for (int j = 0; j < 8; ++j) pb[2][ks][j] = (bf16_t)((t[8 * ks + j] - (float)pb[0][ks][j]) - (float)pb[1][ks][j]);
-        }
-#pragma unroll
-        for (int u = 0; u < TERMS<DH>; ++u)
-          *(bf16x8*)(__attribute__((address_space(3))) char*)(uintptr_t)(sp + ((u * 2 + b) * 2 + ks) * 1024) = pb[u][ks];
-      }
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-        for (int i = 0; i < DB; ++i) {
-          const bf16x8 g = lds_tr(gt.tr[i * 2] + so + (b * 32 + ks * 16) * (DH * 2), gt.tr[i * 2 + 1] + so + (b * 32 + ks * 16) * (DH * 2));
-#pragma unroll
-          for (int u = 0; u < DV_TERMS<DH>; ++u) acc[i] = MFMA(g, pb[u][ks], acc[i]);
-        }
-    }
-  };
-
-  auto s_step = [&](f32x16 (&acc)[DB], int it, auto stage_c, int par) __attribute__((always_inline)) {
-    constexpr int stage = decltype(stage_c)::value;
-    constexpr uint32_t so = (stage & 1) * 2 * TILE64<DH>;
-    const FragPre<DH>& fr = stage < 2 ? f0 : f2;
-    const FragPre<DH>& gt = stage < 2 ? g0 : g2;
-    const int qbase = (qt_first + it / G) * QT;
-    if (!tile_active(qbase)) return;
-    const uint32_t sp = sp_lane + (uint32_t)par * (uint32_t)sizeof(sP[0]);
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      f32x16 t = zero16();
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) t = MFMA(lds_b128(fr.rows[ks] + so + b * 32 * (DH * 2)), breg[ks], t);
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        const float4 d0 = lds_f4(stat_lane + stage * QT * 4 + (b * 32 + 16 * ks) * 4);
-        const float4 d1 = lds_f4(stat_lane + stage * QT * 4 + (b * 32 + 16 * ks + 8) * 4);
-        const float dl[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
-        const bf16x8 p8 = lds_b128(sp + (b * 2 + ks) * 1024);
-        bf16x8 p8_rest;
-        if (TERMS<DH> == 2) p8_rest = lds_b128(sp + ((2 + b) * 2 + ks) * 1024);
-#pragma unroll
-        for (int j = 0; j < 8; ++j)     // dS (the softmax scale is applied once at the end)
-          t[8 * ks + j] = (TERMS<DH> == 2 ? (float)p8[j] + (float)p8_rest[j] : (float)p8[j]) * (t[8 * ks + j] - dl[j]);
-        bf16x8 db[TERMS<DH>];
-        db[0] = pack8(t, ks);
-        if (TERMS<DH> == 2) db[TERMS<DH> - 1] = rest8(t, ks, db[0]);
-#pragma unroll
-        for (int i = 0; i < DB; ++i) {
-          const bf16x8 g = lds_tr(gt.tr[i * 2] + so + (b * 32 + ks * 16) * (DH * 2), gt.tr[i * 2 + 1] + so + (b * 32 + ks * 16) * (DH * 2));
-#pragma unroll
-          for (int u = 0; u < TERMS<DH>; ++u) acc[i] = MFMA(g, db[u], acc[i]);
-        }
-      }
-    }
-  };
-
-  // Step j: tile j+1 goes in flight, role P takes tile j, role S takes tile j-1.  The barrier at the top says:
-  // tile j has landed for everyone, P of tile j-1 is written, and the stage and the P slot about to be
-  // overwritten (those of tile j-2) are no longer read.  Tile j lives in stage j % 3; the loop is unrolled by three
-  // so that every stage offset is an immediate.
-  // The whole loop exists once per role (the role is a compile-time constant inside it): with one loop and a role
-  // branch in its body the register allocator gives the accumulator different homes in the two branches and copies
-  // all 64 registers in and out at every step.  Both copies execute the same number of barriers.
-  using S0 = std::integral_constant<int, 0>;
-  using S1 = std::integral_constant<int, 1>;
-  using S2 = std::integral_constant<int, 2>;
+  constexpr int LOADS = 2 * (8 * DH / KV_THREADS) + 1;       // vector-memory operations of one issue
   auto run = [&](auto role_c) __attribute__((always_inline)) {
     constexpr bool RP = decltype(role_c)::value;
-    f32x16 acc[DB];   // dV^T (role P) or dK^T (role S): rows = head_dim, column = my key
+    constexpr int NT = RP ? DV_TERMS<DH> : TERMS<DH>;
+    f32x16 acc[DB];          // dV^T (role P) or dK^T (role S): rows = head_dim, column = my key
+    f32x16 t[2];             // S or dP of the tile's two 32-query blocks: column = my key, rows = queries b * 32 + acc_row(r, half)
+    bf16x8 w[NT][2][2];      // P or dS: [term][query block][k16 step]
 #pragma unroll
     for (int i = 0; i < DB; ++i) acc[i] = zero16();
-    auto body = [&](int j, auto st_p, auto st_s, int st_next) __attribute__((always_inline)) {
-      WAIT_VM0();
-      __syncthreads();
-      if (j + 1 < n_iter) issue(j + 1, st_next);
+    int qbase = (qt_first + it0 / G) * QT, head = it0 % G;      // of the present step's tile
+    bool held = false;                                          // the previous tile left something to multiply
+    auto second = [&](int stage) __attribute__((always_inline)) {
+      const uint32_t so = (uint32_t)(stage * TILE64<DH>);
+      mfma_chain<4 * DB, CHAIN>(
+          [&](int n) { const uint32_t o = so + (n / DB * 16) * (DH * 2); return lds_tr(gt.tr[n % DB * 2] + o, gt.tr[n % DB * 2 + 1] + o); },
+          [&](int n, const bf16x8& g) {
+#pragma unroll
+            for (int u = 0; u < NT; ++u) acc[n % DB] = MFMA(g, w[u][n / DB >> 1][n / DB & 1], acc[n % DB]);
+          });
+    };
+    auto first = [&](int stage) __attribute__((always_inline)) {
+      const uint32_t so = (uint32_t)(stage * TILE64<DH>);
+      t[0] = zero16();
+      t[1] = zero16();
+      mfma_chain<2 * KS, CHAIN>([&](int n) { return lds_b128(fr.rows[n >> 1] + so + (n & 1) * 32 * (DH * 2)); },
+                                [&](int n, const bf16x8& f) { t[n & 1] = MFMA(f, breg[n >> 1], t[n & 1]); });
+    };
+    auto vector = [&](int stage) __attribute__((always_inline)) {
       if constexpr (RP) {
-        if (j < n_iter) p_step(acc, it0 + j, st_p, j & 1);
+        const bool diag = (q_start + qbase < kw0 + 31) || (qbase + QT > c) || kw0 < kv_first ||   // some pair masked, or ragged query tile
+                          (window > 0 && q_start + qbase + QT - 1 - window >= kw0);
+        if (diag) {
+#pragma unroll
+          for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              const int qi = qbase + b * 32 + acc_row(r, half);
+              if (qi >= c || my_key > q_start + qi || my_key < kv_first || (window > 0 && my_key <= q_start + qi - window))
+                t[b][r] = -INFINITY;                                          // exp2(-inf) = 0
+              if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);            // (few comparisons at a time: scalar registers)
+            }
+        }
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+#pragma unroll
+          for (int a = 0; a < 4; ++a) {
+            const float4 l4 = lds_f4(stat_lane + stage * QT * 4 + (b * 32 + 8 * a) * 4);
+            const float lv[4] = {l4.x, l4.y, l4.z, l4.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) t[b][4 * a + e] = __builtin_amdgcn_exp2f(__builtin_fmaf(t[b][4 * a + e], sl, -lv[e]));
+          }
+#pragma unroll
+          for (int ks = 0; ks < 2; ++ks) {
+            w[0][b][ks] = pack8(t[b], ks);
+            if constexpr (NT == 3) {
+              w[1][b][ks] = rest8(t[b], ks, w[0][b][ks]);
+#pragma unroll
+              for (int e = 0; e < 8; ++e) w[2][b][ks][e] = (bf16_t)((t[b][8 * ks + e] - (float)w[0][b][ks][e]) - (float)w[1][b][ks][e]);
+            }
+#pragma unroll
+            for (int u = 0; u < TERMS<DH>; ++u)
+              *(bf16x8*)(__attribute__((address_space(3))) char*)(uintptr_t)(sp_lane + ((u * 2 + b) * 2 + ks) * 1024) = w[u][b][ks];
+          }
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // P is in LDS before the barrier
       } else {
-        if (j > 0 && j <= n_iter) s_step(acc, it0 + j - 1, st_s, (j - 1) & 1);
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+          for (int ks = 0; ks < 2; ++ks) {
+            const float4 d0 = lds_f4(stat_lane + stage * QT * 4 + (b * 32 + 16 * ks) * 4);
+            const float4 d1 = lds_f4(stat_lane + stage * QT * 4 + (b * 32 + 16 * ks + 8) * 4);
+            const float dl[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
+            const bf16x8 p8 = lds_b128(sp_lane + (b * 2 + ks) * 1024);
+            bf16x8 p8_rest;
+            if (TERMS<DH> == 2) p8_rest = lds_b128(sp_lane + ((2 + b) * 2 + ks) * 1024);
+#pragma unroll
+            for (int e = 0; e < 8; ++e)     // dS (the softmax scale is applied once at the end)
+              t[b][8 * ks + e] = (TERMS<DH> == 2 ? (float)p8[e] + (float)p8_rest[e] : (float)p8[e]) * (t[b][8 * ks + e] - dl[e]);
+            w[0][b][ks] = pack8(t[b], ks);
+            if (TERMS<DH> == 2) w[NT - 1][b][ks] = rest8(t[b], ks, w[0][b][ks]);
+          }
       }
     };
     if (n_iter > 0) {
-      issue(0, 0);
-      // always whole groups of three steps (a step past the last tile is a barrier and nothing else): a loop with
-      // exits between the unrolled steps makes the compiler shuttle the accumulator between register sets
-      for (int j = 0; j <= n_iter; j += 3) {
-        body(j, S0{}, S2{}, 1);
-        body(j + 1, S1{}, S0{}, 2);
-        body(j + 2, S2{}, S1{}, 0);
+      // Role P loads tile j + 2 in its vector slot j, role S tile j + 3 in its own: the stage was last read at least one slot before.
+      // Tile j + 1 has landed for everyone before role P multiplies it: role P waits at the end of vector slot j, role S, one slot
+      // behind, at the end of multiply slot j; the one tile issued after it stays in flight.
+      constexpr int AHEAD = RP ? 2 : 3;
+#pragma unroll
+      for (int j = 0; j < AHEAD; ++j) issue(j);
+      AT_WAIT_VM(LOADS * (AHEAD - 1));
+      AT_SLOT_BARRIER();
+      if (!RP) AT_SLOT_BARRIER();
+      auto step = [&](int j, int stage) __attribute__((always_inline)) {      // stage = j % 4, a constant
+        const bool act = j < n_iter && tile_active(qbase);
+        __builtin_amdgcn_s_setprio(1);
+        if (held) second((stage + 3) % KV_STAGES);
+        if (act) first(stage);
+        __builtin_amdgcn_s_setprio(0);
+        if (!RP) AT_WAIT_VM(LOADS);
+        AT_SLOT_BARRIER();
+        issue((stage + AHEAD) % KV_STAGES);
+        if (act) vector(stage);
+        held = act;
+        if (++head == G) { head = 0; qbase += QT; }
+        if (RP) AT_WAIT_VM(LOADS);
+        AT_SLOT_BARRIER();
+      };
+      int j = 0;
+      for (; j < n_iter; j += 4) {      // (a step past the last tile is two barriers and nothing else)
+        step(j, 0);
+        step(j + 1, 1);
+        step(j + 2, 2);
+        step(j + 3, 3);
       }
+      if (held) second(3);
+      AT_WAIT_VM(0);
+      if (RP) AT_SLOT_BARRIER();        // both roles execute the same number of barriers
     }
     if (my_key < n_total) {
       // several workgroups per key block: each leaves its sum in its own slice [workgroup][dk | dv][key][kv head][DH]
