@@ -83,8 +83,26 @@ __device__ __forceinline__ void store8(bf16_t* p, const float (&v)[8]) {
 }
 constexpr int RV_MAX_IT = 8;    // 64 lanes x 8 elements x 8 = 4096 columns (the backward's 4 x d floats of LDS stay under 64 KiB)
 // Vectorised form for d % 8 == 0, d <= 4096: one wave per row, 8 elements per lane per access, the row stays in
-// registers between the sum of squares and the scaling (one read of x instead of two).
-template <typename T>
+// registers between the sum of squares and the scaling (one read of x instead of two).  IT = accesses per lane, a constant, lanes past
+// the row read its last elements and count them as zero: without branches all loads of a row go out together.  With a branch per
+// access the row cost one memory latency each: 512 rows of 3584 8.5 -> 5.7 us.
+template <int IT, typename T>
+__device__ __forceinline__ void load_row(const T* __restrict__ p, int d, int lane, float (&v)[IT][8]) {
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const int j = it * 512 + lane * 8;
+    load8(p + min(j, d - 8), v[it]);
+  }
+}
+#define VEC_ROW_IT(n_it, IT, ...)                                  \
+  do {                                                             \
+    if ((n_it) <= 1) { constexpr int IT = 1; __VA_ARGS__; }        \
+    else if ((n_it) <= 2) { constexpr int IT = 2; __VA_ARGS__; }   \
+    else if ((n_it) <= 4) { constexpr int IT = 4; __VA_ARGS__; }   \
+    else if ((n_it) <= 7) { constexpr int IT = 7; __VA_ARGS__; }   \
+    else { constexpr int IT = RV_MAX_IT; __VA_ARGS__; }            \
+  } while (0)
+template <int IT, typename T>
 __global__ __launch_bounds__(256) void rmsnorm_fwd_vec_k(const T* __restrict__ x, const float* __restrict__ add,
                                                          const T* __restrict__ g, T* __restrict__ out,
                                                          float* __restrict__ sum_out, float* __restrict__ rstd,
@@ -92,22 +110,18 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_vec_k(const T* __restrict__ x
   const int lane = threadIdx.x & 63;
   const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= rows) return;
-  const int n_it = (d + 511) / 512;
-  float v[RV_MAX_IT][8];
+  float v[IT][8], a[IT][8], gv[IT][8];
+  load_row<IT>(x + row * d, d, lane, v);
+  if (add) load_row<IT>(add + row * d, d, lane, a);
+  if (out) load_row<IT>(g, d, lane, gv);
   float ss = 0.f;
 #pragma unroll
-  for (int it = 0; it < RV_MAX_IT; ++it) {
-    const int j = it * 512 + lane * 8;
-    if (it < n_it && j < d) {
-      load8(x + row * d + j, v[it]);
-      if (add) {
-        float a[8];
-        load8(add + row * d + j, a);
+  for (int it = 0; it < IT; ++it) {
+    const bool in = it * 512 + lane * 8 < d;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[it][e] += a[e];
-      }
-#pragma unroll
-      for (int e = 0; e < 8; ++e) ss += v[it][e] * v[it][e];
+    for (int e = 0; e < 8; ++e) {
+      if (add) v[it][e] += a[it][e];
+      ss += in ? v[it][e] * v[it][e] : 0.f;
     }
   }
   ss = wave_sum(ss);
@@ -115,14 +129,13 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_vec_k(const T* __restrict__ x
   if (lane == 0 && rstd) rstd[row] = r;
   if (!out) return;
 #pragma unroll
-  for (int it = 0; it < RV_MAX_IT; ++it) {
+  for (int it = 0; it < IT; ++it) {
     const int j = it * 512 + lane * 8;
-    if (it < n_it && j < d) {
-      float gv[8], o[8];
-      load8(g + j, gv);
+    if (j < d) {
+      float o[8];
       if (sum_out) store8(sum_out + row * d + j, v[it]);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) o[e] = gv[e] * v[it][e] * r;
+      for (int e = 0; e < 8; ++e) o[e] = gv[it][e] * v[it][e] * r;
       store8(out + row * d + j, o);
     }
   }
@@ -160,7 +173,7 @@ hipError_t rmsnorm_fwd(int dt, const void* x, const float* add, const void* g, v
   auto al = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
   const bool vec = d % 8 == 0 && d <= 512 * RV_MAX_IT && al(x) && al(add) && al(g) && al(out) && al(sum_out);
   DISPATCH_DT(dt, T, {
-    if (vec) rmsnorm_fwd_vec_k<T><<<(unsigned)cdiv(rows, 4), 256, 0, st>>>((const T*)x, add, (const T*)g, (T*)out, sum_out, rstd, rows, d, eps);
+    if (vec) VEC_ROW_IT((d + 511) / 512, IT, rmsnorm_fwd_vec_k<IT, T><<<(unsigned)cdiv(rows, 4), 256, 0, st>>>((const T*)x, add, (const T*)g, (T*)out, sum_out, rstd, rows, d, eps));
     else rmsnorm_fwd_k<T><<<rows, 256, 0, st>>>((const T*)x, add, (const T*)g, (T*)out, sum_out, rstd, d, eps);
   });
   return hipGetLastError();
@@ -170,7 +183,7 @@ hipError_t rmsnorm_fwd(int dt, const void* x, const float* add, const void* g, v
 // A workgroup owns RB consecutive rows so that it can emit one partial row of
 // dg = sum_rows dnorm * x * r; a second kernel adds the partial rows in a fixed
 // order (no atomics: the result is reproducible run to run).
-constexpr int RB = 8;
+constexpr int RB = 4;
 template <typename T, typename XT, typename RT, typename DN = float>
 __global__ __launch_bounds__(256) void rmsnorm_bwd_k(const DN* __restrict__ dnorm, const XT* __restrict__ xin,
                                                      const T* __restrict__ g, const float* __restrict__ rstd,
@@ -207,63 +220,53 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_k(const DN* __restrict__ dnor
   }
 }
 
-// Vectorised form for d % 8 == 0, d <= 4096: one wave per row, 8 elements (128 or 256 bits) per lane per access;
-// a workgroup of 4 waves takes RB rows (2 per wave), each wave keeps its share of dg in registers across its rows
-// and the four waves' shares meet in LDS in a fixed order.  Same arithmetic and the same partial-sum layout as the
-// plain kernel above.
-template <typename T, typename XT, typename RT, typename DN>
+// Vectorised form for d % 8 == 0, d <= 4096: one wave per row (a workgroup takes RB rows), 8 elements (128 or 256 bits) per lane per
+// access, the row's loads issued together and kept between the two passes; the four waves' shares of dg meet in LDS in a fixed
+// order.  Same arithmetic and the same partial-sum layout as the plain kernel above.  (512 rows of 3584, with two rows per wave, a branch
+// per access and both passes reading memory: 22 us, now 9; 1024 rows of 4096 28 -> 15.)
+template <int IT, typename T, typename XT, typename RT, typename DN>
 __global__ __launch_bounds__(256) void rmsnorm_bwd_vec_k(const DN* __restrict__ dnorm, const XT* __restrict__ xin,
                                                          const T* __restrict__ g, const float* __restrict__ rstd,
                                                          const RT* __restrict__ res, float* __restrict__ out_f32,
                                                          T* __restrict__ out_t, float* __restrict__ partial,
                                                          int rows, int d) {
+  static_assert(RB == 4, "one row per wave");
   extern __shared__ float sdg[];   // [4][d]
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t row0 = (int64_t)blockIdx.x * RB;
-  const int n_it = (d + 511) / 512;
-  float dg[RV_MAX_IT][8];
-#pragma unroll
-  for (int it = 0; it < RV_MAX_IT; ++it)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) dg[it][e] = 0.f;
-  for (int r = wave; r < RB; r += 4) {
-    const int64_t row = row0 + r;
-    if (row >= rows) break;
+  const int64_t row = (int64_t)blockIdx.x * RB + wave;
+  if (row < rows) {
+    float dn[IT][8], xv[IT][8], gv[IT][8], rv[IT][8];
+    load_row<IT>(dnorm + row * d, d, lane, dn);
+    load_row<IT>(xin + row * d, d, lane, xv);
+    load_row<IT>(g, d, lane, gv);
+    if (res) load_row<IT>(res + row * d, d, lane, rv);
     const float rs = rstd[row];
     float dot = 0.f;
 #pragma unroll
-    for (int it = 0; it < RV_MAX_IT; ++it) {
-      const int j = it * 512 + lane * 8;
-      if (it < n_it && j < d) {
-        float dn[8], gv[8], xv[8];
-        load8(dnorm + row * d + j, dn); load8(g + j, gv); load8(xin + row * d + j, xv);
+    for (int it = 0; it < IT; ++it) {
+      const bool in = it * 512 + lane * 8 < d;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) dot += dn[e] * gv[e] * xv[e];
-      }
+      for (int e = 0; e < 8; ++e) dot += in ? dn[it][e] * gv[it][e] * xv[it][e] : 0.f;
     }
     dot = wave_sum(dot);
     const float coef = rs * rs * rs * dot / (float)d;
 #pragma unroll
-    for (int it = 0; it < RV_MAX_IT; ++it) {
+    for (int it = 0; it < IT; ++it) {
       const int j = it * 512 + lane * 8;
-      if (it < n_it && j < d) {
-        float dn[8], gv[8], xv[8], rv[8], o[8];
-        load8(dnorm + row * d + j, dn); load8(g + j, gv); load8(xin + row * d + j, xv);
-        if (res) load8(res + row * d + j, rv);
+      if (j < d) {
+        float o[8], dg[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          dg[it][e] += dn[e] * xv[e] * rs;
-          o[e] = (res ? rv[e] : 0.f) + dn[e] * gv[e] * rs - xv[e] * coef;
+          dg[e] = dn[it][e] * xv[it][e] * rs;
+          o[e] = (res ? rv[it][e] : 0.f) + dn[it][e] * gv[it][e] * rs - xv[it][e] * coef;
         }
         if (out_f32) store8(out_f32 + row * d + j, o);
         if (out_t) store8(out_t + row * d + j, o);
+        store8(sdg + (int64_t)wave * d + j, dg);
       }
     }
-  }
-#pragma unroll
-  for (int it = 0; it < RV_MAX_IT; ++it) {
-    const int j = it * 512 + lane * 8;
-    if (it < n_it && j < d) store8(sdg + (int64_t)wave * d + j, dg[it]);
+  } else {
+    for (int j = lane; j < d; j += 64) sdg[(int64_t)wave * d + j] = 0.f;
   }
   __syncthreads();
   for (int j = threadIdx.x; j < d; j += blockDim.x)
@@ -274,16 +277,24 @@ static bool rmsnorm_bwd_vec_ok(int d, const void* a, const void* b, const void* 
   return d % 8 == 0 && d <= 512 * RV_MAX_IT && al(a) && al(b) && al(c) && al(e) && al(f) && al(h);
 }
 
-// dg[j] += sum_b partial[b][j]: 64 columns per workgroup, the partial rows dealt to 4 waves, fixed summation order.
-__global__ __launch_bounds__(256) void colsum_accum_k(const float* __restrict__ partial, float* __restrict__ dg, int nblk, int d) {
-  __shared__ float red[4][64];
+// dg[j] += sum_b partial[b][j]: 64 columns per workgroup, the partial rows dealt to 16 waves, fixed summation order.
+constexpr int CS_WAVES = 16;
+__global__ __launch_bounds__(CS_WAVES * 64) void colsum_accum_k(const float* __restrict__ partial, float* __restrict__ dg, int nblk, int d) {
+  __shared__ float red[CS_WAVES][64];
   const int j = blockIdx.x * 64 + (threadIdx.x & 63), part = threadIdx.x >> 6;
   float s = 0.f;
-  if (j < d)
-    for (int b = part; b < nblk; b += 4) s += partial[(int64_t)b * d + j];
+  if (j < d) {
+#pragma unroll 8
+    for (int b = part; b < nblk; b += CS_WAVES) s += partial[(int64_t)b * d + j];
+  }
   red[part][threadIdx.x & 63] = s;
   __syncthreads();
-  if (part == 0 && j < d) dg[j] += (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
+  if (part == 0 && j < d) {
+    float t = 0.f;
+#pragma unroll
+    for (int w = 0; w < CS_WAVES; ++w) t += red[w][threadIdx.x];
+    dg[j] += t;
+  }
 }
 
 size_t rmsnorm_bwd_partial_floats(int rows, int d) { return (size_t)cdiv(rows, RB) * (size_t)d; }
@@ -298,8 +309,8 @@ hipError_t rmsnorm_bwd(int dt, const float* dnorm, const void* xin, bool x_is_f3
 #define RB_LAUNCH(T, XT, RT)                                                                                     \
   do {                                                                                                           \
     if (vec)                                                                                                     \
-      rmsnorm_bwd_vec_k<T, XT, RT, float><<<nblk, 256, shm, st>>>(dnorm, (const XT*)xin, (const T*)g, rstd,      \
-                                                                  (const RT*)res, out_f32, (T*)out_t, partial, rows, d); \
+      VEC_ROW_IT((d + 511) / 512, IT, rmsnorm_bwd_vec_k<IT, T, XT, RT, float><<<nblk, 256, shm, st>>>(dnorm, (const XT*)xin, (const T*)g, rstd, \
+                                                                  (const RT*)res, out_f32, (T*)out_t, partial, rows, d)); \
     else                                                                                                         \
       rmsnorm_bwd_k<T, XT, RT><<<nblk, 256, 0, st>>>(dnorm, (const XT*)xin, (const T*)g, rstd, (const RT*)res,   \
                                                      out_f32, (T*)out_t, partial, rows, d);                      \
@@ -313,7 +324,7 @@ hipError_t rmsnorm_bwd(int dt, const float* dnorm, const void* xin, bool x_is_f3
 #undef RB_LAUNCH
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  colsum_accum_k<<<(unsigned)cdiv(d, 64), 256, 0, st>>>(partial, dg, nblk, d);
+  colsum_accum_k<<<(unsigned)cdiv(d, 64), CS_WAVES * 64, 0, st>>>(partial, dg, nblk, d);
   return hipGetLastError();
 }
 
@@ -327,15 +338,15 @@ hipError_t rmsnorm_bwd_plain(int dt, const void* dy, const void* x, const void* 
   const size_t shm = (size_t)4 * d * sizeof(float);
   DISPATCH_DT(dt, T, {
     if (vec)
-      rmsnorm_bwd_vec_k<T, T, T, T><<<nblk, 256, shm, st>>>((const T*)dy, (const T*)x, (const T*)g, rstd, (const T*)nullptr,
-                                                            nullptr, (T*)dx, partial, rows, d);
+      VEC_ROW_IT((d + 511) / 512, IT, rmsnorm_bwd_vec_k<IT, T, T, T, T><<<nblk, 256, shm, st>>>((const T*)dy, (const T*)x, (const T*)g, rstd, (const T*)nullptr,
+                                                                                                nullptr, (T*)dx, partial, rows, d));
     else
       rmsnorm_bwd_k<T, T, T, T><<<nblk, 256, 0, st>>>((const T*)dy, (const T*)x, (const T*)g, rstd, (const T*)nullptr,
                                                       nullptr, (T*)dx, partial, rows, d);
   });
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  colsum_accum_k<<<(unsigned)cdiv(d, 64), 256, 0, st>>>(partial, dg, nblk, d);
+  colsum_accum_k<<<(unsigned)cdiv(d, 64), CS_WAVES * 64, 0, st>>>(partial, dg, nblk, d);
   return hipGetLastError();
 }
 

@@ -106,7 +106,7 @@ hipError_t rmsnorm_fwd(int dt, const void* x, const float* add, const void* g, v
 // adjoint: dnorm [rows,d] fp32 is the gradient wrt the normalised output.
 //   xin: the tensor that was normalised (x_is_f32 ? fp32 : dt);  res: gradient flowing around the norm
 //   (res_is_f32 ? fp32 : dt);  out_f32 / out_t (either may be NULL) = res + dx_norm;
-//   dg += column sums of dnorm * xin * rstd (two-stage, deterministic; `partial` >= cdiv(rows,8)*d floats)
+//   dg += column sums of dnorm * xin * rstd (two-stage, deterministic; `partial` >= rmsnorm_bwd_partial_floats)
 hipError_t rmsnorm_bwd(int dt, const float* dnorm, const void* xin, bool x_is_f32, const void* g,
                        const float* rstd, const void* res, bool res_is_f32, float* out_f32, void* out_t,
                        float* dg, float* partial, int rows, int d, hipStream_t st);
