@@ -148,7 +148,7 @@ template <int DH, int NT>
 struct TileLoad { uint32_t voff[8 * DH / NT]; };
 template <int DH, int NT>
 __device__ __forceinline__ uint32_t tile_load_offset(int i, int64_t stride, int rows_valid) {
-  const int id = i * NT + (int)threadIdx.x;
+  const int id = i * NT + (int)threadIdx.x % NT;      // (NT = half the workgroup: each half loads tiles of its own)
   const int row = id / (DH / 8), pc = id % (DH / 8);
   const int chunk = pc ^ swz<DH>(row);
   return (uint32_t)(((int64_t)min(row, rows_valid - 1) * stride + chunk * 8) * 2);
@@ -162,7 +162,7 @@ __device__ __forceinline__ TileLoad<DH, NT> tile_load_pre(int64_t stride) {
 }
 template <int DH, int NT>
 __device__ __forceinline__ void dma_tile64(const TileLoad<DH, NT>& t, const bf16_t* g, int64_t stride, int rows_valid, uint32_t lds_tile) {
-  const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_tile + (uint32_t)(threadIdx.x & ~63) * 16u);
+  const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_tile + (uint32_t)(threadIdx.x % NT & ~63) * 16u);
   if (rows_valid >= 64) {
 #pragma unroll
     for (int i = 0; i < 8 * DH / NT; ++i) dma16((const char*)g, t.voff[i], dst + (uint32_t)(i * NT * 16));
@@ -590,18 +590,21 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
 }
 
 // ----------------------------------------------------------------------- dQ --
-template <int DH>
+// SPLIT: 128 queries per workgroup for launches that would leave CUs idle, as in the forward kernel: the two halves of the workgroup
+// take the even / odd key tiles of the same queries and add up in LDS (1024 queries, 32 heads: 128 workgroups of 256 queries).
+template <int DH, bool SPLIT>
 __global__ __launch_bounds__(AT_THREADS) void attn_bwd_dq_mfma_k(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                                                     const bf16_t* __restrict__ v, const bf16_t* __restrict__ d_o,
                                                                     const float* __restrict__ lse, const float* __restrict__ delta,
                                                                     bf16_t* __restrict__ dq, int Hq, int Hkv, int q_start, int c,
                                                                     float scale, const float2* __restrict__ rope, int window,
                                                                     int kv_first) {
-  __shared__ __attribute__((aligned(1024))) char sT[4][TILE64<DH>];   // stage st: K = sT[2 st], V = sT[2 st + 1]
+  __shared__ __attribute__((aligned(1024))) char sT[SPLIT ? 8 : 4][TILE64<DH>];   // stage st (of a half): K = sT[2 st], V = sT[2 st + 1]
+  constexpr int QW = SPLIT ? TQ / 2 : TQ, NT = SPLIT ? AT_THREADS / 2 : AT_THREADS;
 
-  const int q0 = blockIdx.x * TQ, h = blockIdx.y, kvh = h / (Hq / Hkv);
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5;
-  const int qw0 = q0 + wave * 32;
+  const int q0 = blockIdx.x * QW, h = blockIdx.y, kvh = h / (Hq / Hkv);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), grp = SPLIT ? wave >> 2 : 0, lane = threadIdx.x & 63, half = lane >> 5;
+  const int qw0 = q0 + (SPLIT ? wave & 3 : wave) * 32;
   const int my_q = qw0 + (lane & 31);
   const bool q_valid = my_q < c;
   const int q_row = min(my_q, c - 1);
@@ -610,7 +613,7 @@ __global__ __launch_bounds__(AT_THREADS) void attn_bwd_dq_mfma_k(const bf16_t* _
   const bf16_t* kbase = k + (int64_t)kvh * DH;
   const bf16_t* vbase = v + (int64_t)kvh * DH;
   const int n_total = q_start + c;
-  const int n_keys = q_start + min(q0 + TQ, c);
+  const int n_keys = q_start + min(q0 + QW, c);
   const int n_tiles = (n_keys + TK - 1) / TK;
   const int wave_last_key = q_start + min(qw0 + 32, c) - 1;
   const int wave_first_qpos = q_start + qw0;
@@ -619,9 +622,9 @@ __global__ __launch_bounds__(AT_THREADS) void attn_bwd_dq_mfma_k(const bf16_t* _
   const int wave_lo_min = first_key(wave_first_qpos), wave_lo_max = first_key(wave_last_key);
   const int kt0 = first_key(q_start + q0) / TK;
 
-  const uint32_t lds0 = lds_addr(&sT[0][0]);
+  const uint32_t lds0 = lds_addr(&sT[4 * grp][0]);
   const FragPre<DH> fp = frag_pre<DH>(lds0);
-  const TileLoad<DH, AT_THREADS> tl = tile_load_pre<DH, AT_THREADS>(kv_stride);
+  const TileLoad<DH, NT> tl = tile_load_pre<DH, NT>(kv_stride);
 
   constexpr int KS = DH / 16, DB = DH / 32;      // k16 steps of a score, 32-row blocks of the output
   bf16x8 bq[KS], bdo[KS];
@@ -672,7 +675,12 @@ __global__ __launch_bounds__(AT_THREADS) void attn_bwd_dq_mfma_k(const bf16_t* _
                          });
     }
   };
-  auto issue = [&](int kt, int st) {
+  // tile i of this wave's sequence; both halves execute the same number of barriers
+  auto tile_of = [&](int i) { return SPLIT ? kt0 + 2 * i + grp : kt0 + i; };
+  const int n_it = SPLIT ? (max(0, n_tiles - kt0) + 1) / 2 : max(0, n_tiles - kt0);
+  auto issue = [&](int i, int st) {
+    const int kt = tile_of(i);
+    if (kt >= n_tiles) return;
     const int64_t row0 = (int64_t)kt * TK;
     dma_tile64(tl, kbase + row0 * kv_stride, kv_stride, n_total - kt * TK, lds0 + (uint32_t)(st * 2 * TILE64<DH>));
     dma_tile64(tl, vbase + row0 * kv_stride, kv_stride, n_total - kt * TK, lds0 + (uint32_t)((st * 2 + 1) * TILE64<DH>));
@@ -680,20 +688,32 @@ __global__ __launch_bounds__(AT_THREADS) void attn_bwd_dq_mfma_k(const bf16_t* _
   using S0 = std::integral_constant<int, 0>;
   using S1 = std::integral_constant<int, 1>;
 
-  if (kt0 < n_tiles) issue(kt0, 0);
-  for (int kt = kt0; kt < n_tiles; kt += 2) {
+  if (n_it > 0) issue(0, 0);
+  for (int i = 0; i < n_it; i += 2) {
     WAIT_VM0();
     __syncthreads();
-    if (kt + 1 < n_tiles) issue(kt + 1, 1);
-    step(kt, S0{});
-    if (kt + 1 < n_tiles) {
+    if (i + 1 < n_it) issue(i + 1, 1);
+    step(tile_of(i), S0{});
+    if (i + 1 < n_it) {
       WAIT_VM0();
       __syncthreads();
-      if (kt + 2 < n_tiles) issue(kt + 2, 0);
-      step(kt + 1, S1{});
+      if (i + 2 < n_it) issue(i + 2, 0);
+      step(tile_of(i + 1), S1{});
     }
   }
 
+  if constexpr (SPLIT) {
+    __syncthreads();
+    float* mine = (float*)&sT[0][0] + (wave & 3) * (DB * 16 * 64) + lane;      // [float][lane]
+    if (grp == 1) {
+#pragma unroll
+      for (int i = 0; i < DB * 16; ++i) mine[i * 64] = acc[i >> 4][i & 15];
+    }
+    __syncthreads();
+    if (grp == 1) return;
+#pragma unroll
+    for (int i = 0; i < DB * 16; ++i) acc[i >> 4][i & 15] += mine[i * 64];
+  }
   if (q_valid) {
     bf16_t* op = dq + ((int64_t)my_q * Hq + h) * DH;
     if (rope) {
@@ -1011,16 +1031,19 @@ bool attn_mfma_aligned(const AttnArgs& a, bool backward) {
   return !backward || (aligned16(a.d_o) && aligned16(a.dq) && aligned16(a.dk) && aligned16(a.dv));
 }
 
+// Rounds of 256 workgroups (one per CU), a half query tile costing half a round: the half tiles where they leave fewer CUs idle.
+static bool half_tiles_fill_better(const AttnArgs& a) {
+  return 2 * cdiv(cdiv(a.q_len, TQ) * a.Hq, 256) > cdiv(cdiv(a.q_len, TQ / 2) * a.Hq, 256);
+}
 template <int DH>
 static hipError_t forward_dh(const AttnArgs& a, hipStream_t st) {
   if (a.q_len == 0) return hipSuccess;
-  // rounds of 256 workgroups (one per CU), a half tile costing half a round: the half tiles where they leave fewer CUs idle
   const int64_t full = cdiv(a.q_len, TQ) * a.Hq, halves = cdiv(a.q_len, TQ / 2) * a.Hq;
   auto launch = [&](auto kernel, int64_t n) {
     kernel<<<(unsigned)n, AT_THREADS, 0, st>>>((bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v, (bf16_t*)a.o, a.lse, a.Hq, a.Hkv,
                                                a.q_start, a.q_len, a.scale, a.rope_q, a.window, a.kv_first);
   };
-  if (2 * cdiv(full, 256) > cdiv(halves, 256)) launch(attn_fwd_mfma_k<DH, true>, halves);
+  if (half_tiles_fill_better(a)) launch(attn_fwd_mfma_k<DH, true>, halves);
   else launch(attn_fwd_mfma_k<DH, false>, full);
   return hipGetLastError();
 }
@@ -1032,10 +1055,13 @@ static hipError_t backward_dh(const AttnArgs& a, hipStream_t st) {
   float* lse2 = a.delta + pairs;   // second half of the [2, Hq, c] scratch
   attn_delta_mfma_k<DH><<<(unsigned)cdiv(pairs, 4), 256, 0, st>>>((const bf16_t*)a.o, (const bf16_t*)a.d_o, a.lse, a.delta, lse2, a.Hq,
                                                               a.q_len);
-  dim3 gq((unsigned)cdiv(a.q_len, TQ), a.Hq);
-  attn_bwd_dq_mfma_k<DH><<<gq, AT_THREADS, 0, st>>>((const bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v, (const bf16_t*)a.d_o,
-                                                a.lse, a.delta, (bf16_t*)a.dq, a.Hq, a.Hkv, a.q_start, a.q_len, a.scale, a.rope_q,
-                                                a.window, a.kv_first);
+  auto launch_dq = [&](auto kernel, int64_t n) {
+    kernel<<<dim3((unsigned)n, a.Hq), AT_THREADS, 0, st>>>((const bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v, (const bf16_t*)a.d_o,
+                                                           a.lse, a.delta, (bf16_t*)a.dq, a.Hq, a.Hkv, a.q_start, a.q_len, a.scale, a.rope_q,
+                                                           a.window, a.kv_first);
+  };
+  if (half_tiles_fill_better(a)) launch_dq(attn_bwd_dq_mfma_k<DH, true>, cdiv(a.q_len, TQ / 2));
+  else launch_dq(attn_bwd_dq_mfma_k<DH, false>, cdiv(a.q_len, TQ));
   // key blocks that no query of the chunk can see (before the padding ends, or older than the first query's window)
   // are not launched: their dK/dV contribution is zero
   const int first_visible = std::max(a.kv_first, a.window > 0 ? a.q_start - a.window + 1 : 0);
