@@ -12,29 +12,28 @@
 // just as on the right one, and a query that sees no key gets o = 0, lse = -inf
 // and sends no gradient.
 //
-// All three kernels use the "transposed score" formulation on the 32x32x16
-// MFMA: S^T[key, query] = K Q^T.  The accumulator layout then gives every lane
-// ONE query (column l%32) and 16 keys per 32-key block, so row max / row sum
-// are in-register plus one cross-half exchange, and exp(S^T) is already in the
-// register layout of the B operand of the next product (P^T as [key, query]
-// with keys as the reduction index) - probabilities never touch LDS.  The
-// reduction-index permutation this implies (slot j of half h <-> key
-// 16*ks + 8*(j>>2) + 4*h + (j&3)) is matched on the A side by the transposing
-// LDS load (ds_read_b64_tr_b16) that fetches V^T / K^T / Q^T / dO^T fragments
-// from tiles kept in their natural [row][head_dim] layout.
+// All three kernels use the "transposed score" formulation: S^T[key, query] = K Q^T.
+// The accumulator layout then gives every lane ONE query and several keys of a
+// block, so row max / row sum are in-register plus one or two lane exchanges, and
+// exp(S^T) is already in the register layout of the B operand of the next product
+// (P^T as [key, query] with keys as the reduction index).  The reduction-index
+// permutation this implies is matched on the A side by the transposing LDS load
+// (ds_read_b64_tr_b16) that fetches V^T / K^T / Q^T / dO^T fragments from tiles
+// kept in their natural [row][head_dim] layout.
 //
-//  forward : workgroup = 256 queries of one query head, 8 waves x 32 queries;
-//            K and V tiles of 64 keys stream HBM -> LDS (direct-to-LDS, double
-//            buffered); online softmax in the exp2 domain.
-//  dQ      : same decomposition; recomputes P from the saved log-sum-exp;
-//            dQ^T += K^T dS^T.
+//  forward : 256 (or 128) queries of one query head per workgroup, 16x16x32 MFMAs,
+//            8 waves x 32 queries; K and V tiles of 64 keys stream HBM -> LDS
+//            (direct-to-LDS); online softmax in the exp2 domain; multiply and
+//            softmax slots of two wave groups alternate.
+//  dQ      : same decomposition, 32x32x16 MFMAs, two stages; recomputes P from the
+//            saved log-sum-exp; dQ^T += K^T dS^T.
 //  dK/dV   : workgroup = 128 keys of one KV head, 4 key blocks x 2 roles: one wave of
 //            a block computes P and dV^T += dO^T P, its partner dP, dS and
-//            dK^T += Q^T dS (P crosses through LDS); loops over the query tiles at
-//            or below the diagonal and over the query heads of the group, Q and dO
-//            tiles of 64 queries stream through LDS; results are added to the fp32
-//            prefix accumulators (every element has one owner: no atomics,
-//            reproducible).
+//            dK^T += Q^T dS (P crosses through LDS), 32x32x16 MFMAs; loops over the query
+//            tiles at or below the diagonal and over the query heads of the group, Q
+//            and dO tiles of 64 queries stream through four LDS stages; results are
+//            added to the fp32 prefix accumulators (every element has one owner, or
+//            its parts are summed in a fixed order: no atomics, reproducible).
 #include "launch.h"
 #include "device.h"
 
@@ -253,8 +252,9 @@ __device__ __forceinline__ void query_tile_of(int n_qt, int Hq, int& qt, int& h)
 //                  against the maximum it has in the sequential walk.
 // What bounds it: a slot takes about 1600 cycles at 2.0 GHz where the 68 MFMAs take 1088 - the vector instructions of one wave (about
 // 160, 32 of them exponentials) and the MFMAs of the other share the SIMD's issue port and delay each other; without the vector
-// work a slot takes 1050 cycles, without the MFMAs 1150.  Last 2048-query chunk of 32k, 28 heads: 1110 -> 921 us (32x32x16 MFMAs in
-// the same schedule 965; loads in the multiply slot 954; the next slot's first fragments read early 958).
+// work a slot takes 1050 cycles, without the MFMAs 1150.  Last 2048-query chunk of 32k, 28 heads: 1110 -> 957 us.
+// Tried with a maximum that lags by up to 2^8, itself 921 us but another rounding of every probability: 32x32x16 MFMAs in the same
+// schedule 965, loads in the multiply slot 954, the next slot's first fragments read early 958.
 template <int DH, bool SPLIT>
 __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const bf16_t* __restrict__ k,
                                                                  const bf16_t* __restrict__ v, bf16_t* __restrict__ o,
