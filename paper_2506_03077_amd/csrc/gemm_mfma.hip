@@ -133,6 +133,7 @@ __device__ __forceinline__ int xcd_contiguous_id(int id, int n_tiles) {
 // Counted wait / workgroup barrier of the main loop.  Inline assembly (with a memory clobber) so that the compiler neither adds
 // waits of its own nor moves LDS reads across; the scheduling barriers keep the machine scheduler from doing the same.
 #define WAIT_VMCNT(n) asm volatile("s_waitcnt vmcnt(%0)" ::"i"(n) : "memory")
+#define WAIT_LDS() asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory")
 #define SLOT_BARRIER()                        \
   do {                                        \
     __builtin_amdgcn_sched_barrier(0);        \
@@ -164,9 +165,13 @@ struct KSegment {
 // v_mfma_f32_16x16x32_bf16 per wave), in the order (A0,B0) (A0,B1) (A1,B1) (A1,B0), so that each phase needs only one new operand
 // half.  A phase is two slots, each closed by a barrier: fetch (LDS reads of the phase's fragments, the DMA of one half tile) and
 // multiply.  Group 1 runs one slot behind group 0, so on every SIMD one wave multiplies while the other fetches: the matrix pipe
-// does not wait for LDS reads, load issue or barriers.  The half read in phase p is free two phases later and is then refilled
-// for the K step after next: five half tiles (80 KB) stay in flight and a load has six phases to land (a two-stage loop with
-// one barrier and one burst of loads per K step waits for a whole tile's latency each time).
+// does not wait for LDS reads, load issue or barriers.  The half read in phase p is refilled two phases later for the K step after
+// next: five half tiles (80 KB) stay in flight and a load has six phases to land (a two-stage loop with one barrier and one burst
+// of loads per K step waits for a whole tile's latency each time).  A refill may only be issued when both groups' reads of the half
+// have returned, in a slot after a barrier that follows their waits.  A0, B1 and A1 are consumed, and with that waited for, in the
+// multiply slot after their fetch.  B0 is fetched a phase early (phase 3, used in phase 0 of the next K step), where group 1 would
+// wait for it in the very slot in which group 0 refills it: phase 0 therefore opens with a wait for it (two slots after the reads
+// went out: nothing stalls).
 // What bounds it: the matrix pipe at its power-limited clock.  8192^3 bf16, same box: NT 1265 -> 1556, NN 1256 -> 1546, TN 1199
 // -> 1440 TFLOP/s (vendor library 1614 / 1390 / 1202); half of the gain is the slot schedule (1410 with 32x32x16 MFMAs), half the
 // 16x16x32 MFMA, whose operands toggle less: 2.09 PFLOP/s of it sustain on random data against 1.82 of the 32x32x16.
@@ -285,6 +290,7 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
     else if (rem == 1) WAIT_VMCNT(penultimate);       \
     else WAIT_VMCNT(last);                            \
   } while (0)
+      WAIT_LDS();                         // B0 is in registers: the other group refills its half in the slot after next
       read_a(stage, 0);
       if (rem >= 1) issue_a(1, kt + 1);
       WAIT_TAIL(10, 2);
@@ -316,6 +322,7 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
       k_step(S1{}, kt + 1, by, bx);
     }
     if (nk & 1) k_step(S0{}, nk - 1, bx, by);
+    WAIT_LDS();                      // (the read of B0 past the last K step: the next segment's loads refill the stage)
     if (grp == 0) SLOT_BARRIER();    // ... and group 0 waits for it here: both execute the same number of barriers
   }
 
