@@ -761,8 +761,8 @@ bool gemm_mfma_eligible(const GemmArgs& g) {
   if (g.lda % 8 || g.ldb % 8) return false;
   if (g.lda >= (1 << 22) || g.ldb >= (1 << 22)) return false;   // per-lane byte offsets within a tile are 32-bit
   if (((uintptr_t)g.A & 15) || ((uintptr_t)g.B & 15) || ((uintptr_t)g.C & 15)) return false;
-  if (g.ldc % 4) return false;
-  return true;
+  // fp32 rows, the softmax numerators and the fused SwiGLU adjoint move 4 elements at a time, plain and accumulated bf16 rows 8
+  return g.ldc % (g.out_dt == DT_BF16 && !g.numer_targets && !g.swiglu_gate ? 8 : 4) == 0;
 }
 
 // the operand-pair form: two reductions, one after the other, in one accumulator

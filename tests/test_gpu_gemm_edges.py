@@ -66,3 +66,20 @@ def test_segments_of_unequal_length(Ks):
     C = torch.zeros((M, N), dtype=torch.float32, device="cuda")
     assert sb.debug_gemm_dw_segments([o[0] for o in ops], [o[1] for o in ops], C, M, N, list(Ks)) == 1
     _check(C, sum(o[2] for o in ops), sum(Ks))
+
+
+@pytest.mark.parametrize("M,N,K", [(72, 72, 64), (256, 264, 128)])
+@pytest.mark.parametrize("ta,tb,acc", [(False, True, False), (False, False, False), (True, False, True)])
+def test_rows_of_c_that_start_between_16_byte_boundaries(M, N, K, ta, tb, acc):
+    """C a column slice whose rows lie N + 4 elements apart: 16-byte aligned in fp32 (MFMA kernels), 8-byte aligned in bf16, where the
+    MFMA kernels' 16-byte accesses do not fit."""
+    import torch
+    from paper_2506_03077_amd import binding as sb
+    A, B, want = _operands(M, N, K, ta, tb)
+    for dt, mfma in ((torch.float32, 1), (torch.bfloat16, 0)):
+        wide = torch.full((M, N + 4), 3.0, dtype=dt, device="cuda")
+        C = wide[:, :N]
+        C.fill_(1.0)
+        assert sb.debug_gemm(A, B, C, M, N, K, ta, tb, acc=acc) == mfma
+        _check(C, want + (1.0 if acc else 0.0), K)
+        assert bool((wide[:, N:] == 3.0).all())
