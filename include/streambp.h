@@ -113,10 +113,15 @@ typedef struct {
 
 /* Bytes of workspace streambp_layer_backward / streambp_layer_forward need for
  * this config (0 if the config is invalid).  The figure is
- *   alpha * min(chunk, T) + beta * T * n_kv_heads * head_dim + const:
+ *   alpha * min(chunk, T) + beta * T * n_kv_heads * head_dim + const + S:
  * it has no term in T * mlp_width, T * hidden or T^2 (Sec. 3.2.2, memory
  * efficiency: K and V are cached for the whole sequence, everything else is
- * per chunk). */
+ * per chunk).  S (bf16 only, also part of the LM head's figure, there with d
+ * alone) holds the partial sums of reductions that are split over workgroups:
+ *   S = min(256, 27 * ceil(c / 256) * ceil(max(d, n_q_heads * head_dim) / 256))
+ *       * min(c, 256) KiB,   c = min(chunk, T) (LM head: min(chunk, B * T)):
+ * at most 64 MiB, reached by chunks of a few hundred rows, and shrinking with
+ * the chunk below 256 rows. */
 size_t streambp_layer_workspace_bytes(const sbp_layer_cfg *cfg);
 
 /* StreamBP of one layer (Sec. 3.2.2): K and V are computed once for the whole

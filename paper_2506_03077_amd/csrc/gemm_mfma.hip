@@ -22,8 +22,8 @@
 //    ragged K (dW with a ragged chunk) by writing zeros instead of loading.
 //  * Output tiles leave through LDS, so that C is written (or read, added to and written) in whole rows, 16 bytes per lane.
 //  * Split-K for problems with too few output tiles to fill the chip: partial tiles go to
-//    fp32 scratch and a small kernel sums them in a fixed order (deterministic) into C; each K slice is pinned to
-//    its own group of XCDs.
+//    fp32 scratch and a small kernel sums them in a fixed order (deterministic) into C; the workgroups of a K slice are
+//    numbered consecutively, so that an XCD holds one slice or a few.
 //  * Weight gradients: C += acc, fp32 or bf16 C; several reduction segments (operand pairs) per output tile; grouped launches.
 #include "launch.h"
 #include "device.h"
@@ -39,6 +39,7 @@ typedef short short4v __attribute__((ext_vector_type(4)));
 typedef short short8v __attribute__((ext_vector_type(8)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int BM = 256, BN = 256, BK = 64;
@@ -149,7 +150,8 @@ __device__ __forceinline__ int xcd_contiguous_id(int id, int n_tiles) {
 //       7 = like 5, but C (bf16) receives exp(c - block max) instead of c, and the value of each row's target column is kept
 constexpr bool mode_accumulates(int mode) { return mode == 2 || mode == 4; }
 constexpr bool mode_splits(int mode) { return mode <= 2; }      // forms whose reduction may be split over workgroups
-constexpr int PARTIAL_FLOATS = BM * BN;
+// Floats of a partial tile: an output of fewer than 256 rows has partial tiles of as many (the scratch and its traffic shrink with it)
+__host__ __device__ __forceinline__ int partial_floats(int max_m) { return (max_m < BM ? max_m : BM) * BN; }
 struct SwigluFuse { bf16_t* gate; bf16_t* up; bf16_t* act; };
 struct NumerFuse { const int32_t* targets; const int32_t* row_index; float* target_value; };
 // The reduction may come in several segments (operand pairs of the same shape and leading dimensions whose products
@@ -181,7 +183,7 @@ struct KSegment {
 template <bool TA, bool TB, int MODE, typename SegmentF>
 __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void* __restrict__ Cv, int M, int N, int64_t lda,
                                           int64_t ldb, int64_t ldc, int tm, int tn, char* smem,
-                                          float* __restrict__ partial = nullptr, void* __restrict__ stats_out = nullptr,
+                                          float* __restrict__ partial = nullptr, int partial_bytes = 0, void* __restrict__ stats_out = nullptr,
                                           SwigluFuse sw = SwigluFuse{}, NumerFuse nf = NumerFuse{}) {
   constexpr bool AMN = TA, BMN = !TB;     // operand kept reduction-major in LDS (B stored [N,K] is the K-contiguous case)
   const int m0 = tm * BM, n0 = tn * BN;
@@ -336,7 +338,10 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
   // per lane: storing from the accumulator layout directly (32-byte pieces of 16 rows per instruction) measured 2-5 % slower
   // over the whole product at K = 3584.
   if constexpr (mode_splits(MODE)) {
-    if (partial) {     // a slice of the reduction: the whole fp32 tile, masked and combined by splitk_tail_k
+    if (partial) {     // a slice of the reduction: the fp32 tile, masked and combined by splitk_tail_k
+      // stores past the end of a partial tile of fewer than 256 rows fall outside the buffer and are dropped: a branch per row
+      // in their place made every split product 0.5 us slower (small model, 64 of 16 us each)
+      __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(partial, 0, partial_bytes, 0x00027000);
 #pragma unroll
       for (int ha = 0; ha < 2; ++ha) {
         __syncthreads();
@@ -354,7 +359,8 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
 #pragma unroll
         for (int p = 0; p < 16; ++p) {
           const int row_l = p * 8 + (threadIdx.x >> 6);
-          *(f32x4*)(partial + (ha * 128 + row_l) * BN + c4 * 4) = *(const f32x4*)(smem + row_l * 1024 + ((c4 ^ (row_l & 15)) << 4));
+          const f32x4 v = *(const f32x4*)(smem + row_l * 1024 + ((c4 ^ (row_l & 15)) << 4));
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), out, ((ha * 128 + row_l) * BN + c4 * 4) * 4, 0, 0);
         }
       }
       return;
@@ -577,10 +583,10 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
 // workgroup; the reduction of the tiles that are left over (or of all of them, where there are fewer than 256) is split
 // `splits` ways, so that the last round is not mostly idle.  Split tiles go to fp32 scratch and are summed in a fixed order.
 // The number of splits weighs the K steps saved against what the partial tiles cost: about 3.5 K steps for the extra launch
-// and 0.09 K step per partial tile (256 KB written and read back at ~4.5 TB/s against 1.45 us per K step).  Up to 32 splits: eight
+// and 0.09 K step per partial tile (256 KB written and read back at ~4.5 TB/s against 1.45 us per K step).  Up to 27 splits: eight
 // tiles with the reduction of a 50257-word vocabulary, or 28 with that of two MLP widths, would keep most CUs idle with four.
 constexpr int N_CU = 256;
-constexpr int MAX_SPLITS = 32;
+constexpr int MAX_SPLITS = 27;        // the numbers tried: 2 .. 8, 10, 12, 15, 18, 22, 27
 struct Schedule { int tiles, full, tail, splits; };
 __host__ __device__ __forceinline__ Schedule make_schedule(int tiles, int k_steps, int scratch_tiles) {
   const int tail = tiles % N_CU;
@@ -614,6 +620,7 @@ __global__ __launch_bounds__(NTHREADS) void gemm_mfma_k(const bf16_t* __restrict
                                                         float* __restrict__ scratch, int scratch_tiles, void* __restrict__ row_stats,
                                                         SwigluFuse sw, NumerFuse nf) {
   __shared__ __attribute__((aligned(1024))) char smem[SMEM_BYTES];
+  const int part = partial_floats(M);
   if (rows_dev) {                     // run-time row count: rows are M (NT / NN) or the reduction K (dW form)
     const int rows = max(0, *rows_dev);
     if (TA) K = min(K, rows); else M = min(M, rows);
@@ -631,13 +638,13 @@ __global__ __launch_bounds__(NTHREADS) void gemm_mfma_k(const bf16_t* __restrict
     const int per = (all_steps + sc.splits - 1) / sc.splits;
     s0 = split * per;
     s1 = min(all_steps, s0 + per);
-    partial = scratch + ((int64_t)split * sc.tail + (tile - sc.full)) * PARTIAL_FLOATS;
+    partial = scratch + ((int64_t)split * sc.tail + (tile - sc.full)) * part;
   }
   auto segment = [&](int i) {
     const int b = max(s0 - i * k_steps, 0) * BK, e = min(min(s1 - i * k_steps, k_steps) * BK, K);
     return KSegment{i ? A2 : A, i ? B2 : B, b, e};
   };
-  gemm_tile<TA, TB, MODE>(A2 ? 2 : 1, segment, Cv, M, N, lda, ldb, ldc, tm, tn, smem, partial, row_stats, sw, nf);
+  gemm_tile<TA, TB, MODE>(A2 ? 2 : 1, segment, Cv, M, N, lda, ldb, ldc, tm, tn, smem, partial, part * 4, row_stats, sw, nf);
 }
 
 // Weight-gradient form with a segmented reduction: C += sum_s A_s^T B_s, every segment with its own run-time row
@@ -668,7 +675,7 @@ struct GroupProblem {
   int64_t lda, ldb, ldc;
   int tile_begin, tiles_m, tiles_n;
 };
-struct GroupArgs { GroupProblem p[MAX_GROUP]; int n; Schedule sched; float* scratch; };
+struct GroupArgs { GroupProblem p[MAX_GROUP]; int n; Schedule sched; float* scratch; int part; };     // part: floats of a partial tile
 
 template <bool TA, bool TB, int MODE>
 __global__ __launch_bounds__(NTHREADS) void gemm_mfma_group_k(const GroupArgs ga) {
@@ -688,10 +695,10 @@ __global__ __launch_bounds__(NTHREADS) void gemm_mfma_group_k(const GroupArgs ga
     const int k_steps = (g.K[0] + BK - 1) / BK, per = (k_steps + ga.sched.splits - 1) / ga.sched.splits;
     b = split * per * BK;
     e = b + per * BK;
-    partial = ga.scratch + ((int64_t)split * ga.sched.tail + (id - ga.sched.full)) * PARTIAL_FLOATS;
+    partial = ga.scratch + ((int64_t)split * ga.sched.tail + (id - ga.sched.full)) * ga.part;
   }
   gemm_tile<TA, TB, MODE>(mode_accumulates(MODE) ? g.nseg : 1, [&](int i) { return KSegment{g.A[i], g.B[i], b, min(e, g.K[i])}; }, g.C, g.M, g.N,
-                          g.lda, g.ldb, g.ldc, tm, tn, smem, partial);
+                          g.lda, g.ldb, g.ldc, tm, tn, smem, partial, ga.part * 4);
 }
 
 // The tiles whose reduction was split: C (=|+=) sum of the partial tiles in a fixed order, rounded once.  Sixteen workgroups per tile.
@@ -703,6 +710,7 @@ struct TailArgs {
   const int* rows_dev;          // run-time row count of p[0] (single problems): the schedule is then made again from it
   int k_steps, scratch_tiles;
   const float* scratch;
+  int part;                     // floats of a partial tile
 };
 template <int MODE>
 __global__ __launch_bounds__(256) void splitk_tail_k(const TailArgs ta) {
@@ -728,9 +736,9 @@ __global__ __launch_bounds__(256) void splitk_tail_k(const TailArgs ta) {
   for (int p = 0; p < 4; ++p) {
     const int row_l = (blockIdx.x & 15) * 16 + p * 4 + (threadIdx.x >> 6), row = tm * BM + row_l;
     if (row >= M || col >= g.N) continue;
-    const float* src = ta.scratch + (int64_t)t * PARTIAL_FLOATS + row_l * BN + col_l;
+    const float* src = ta.scratch + (int64_t)t * ta.part + row_l * BN + col_l;
     f32x4 v = *(const f32x4*)src;
-    for (int z = 1; z < sc.splits; ++z) v += *(const f32x4*)(src + (int64_t)z * sc.tail * PARTIAL_FLOATS);
+    for (int z = 1; z < sc.splits; ++z) v += *(const f32x4*)(src + (int64_t)z * sc.tail * ta.part);
     if constexpr (MODE == 1) {
       bf16x4 o;
 #pragma unroll
@@ -788,10 +796,10 @@ bool gemm_mfma_numer_ok(const GemmArgs& g) {
 size_t gemm_scratch_bytes(int max_m, int max_n) {
   // partial tiles: at most one per CU is ever useful
   const int64_t tiles = cdiv(max_m, BM) * cdiv(max_n, BN);
-  return (size_t)std::min<int64_t>(N_CU, tiles * MAX_SPLITS) * PARTIAL_FLOATS * sizeof(float);
+  return (size_t)std::min<int64_t>(N_CU, tiles * MAX_SPLITS) * partial_floats(max_m) * sizeof(float);
 }
-static int scratch_tiles_of(const GemmArgs& g) {
-  return g.scratch && !((uintptr_t)g.scratch & 15) ? (int)std::min<size_t>(N_CU, g.scratch_bytes / (PARTIAL_FLOATS * sizeof(float))) : 0;
+static int scratch_tiles_of(const GemmArgs& g, int max_m) {
+  return g.scratch && !((uintptr_t)g.scratch & 15) ? (int)std::min<size_t>(N_CU, g.scratch_bytes / (partial_floats(max_m) * sizeof(float))) : 0;
 }
 static hipError_t launch_tail(int mode, const TailArgs& t, int max_tail, hipStream_t st) {
   const unsigned blocks = (unsigned)max_tail * 16;
@@ -807,7 +815,7 @@ hipError_t gemm_mfma(const GemmArgs& g, hipStream_t st) {
   const int mode = g.numer_targets ? 7 : g.row_stats ? 5 : g.swiglu_gate ? 6
                  : g.acc ? (g.out_dt == DT_BF16 ? 4 : 2) : (g.out_dt == DT_BF16 ? 1 : 0);
   const bool dev_rows = g.rows_dev != nullptr;
-  const int scratch_tiles = mode_splits(mode) && !(g.ta && dev_rows) ? scratch_tiles_of(g) : 0;
+  const int scratch_tiles = mode_splits(mode) && !(g.ta && dev_rows) ? scratch_tiles_of(g, g.M) : 0;
   const Schedule sc = make_schedule(tiles_m * tiles_n, k_steps, scratch_tiles);
   // with a run-time row count the schedule is made on the device: room for any tail
   const unsigned grid = dev_rows && scratch_tiles ? (unsigned)(tiles_m * tiles_n + N_CU) : (unsigned)(sc.full + sc.tail * sc.splits);
@@ -845,6 +853,7 @@ hipError_t gemm_mfma(const GemmArgs& g, hipStream_t st) {
   t.n = 1;
   t.p[0] = TailProblem{g.C, g.M, g.N, g.ldc, 0, tiles_m, tiles_n};
   t.sched = sc; t.rows_dev = g.rows_dev; t.k_steps = k_steps; t.scratch_tiles = scratch_tiles; t.scratch = g.scratch;
+  t.part = partial_floats(g.M);
   return launch_tail(mode, t, dev_rows ? std::min(N_CU / 2, tiles_m * tiles_n) : sc.tail, st);
 }
 
@@ -905,10 +914,11 @@ hipError_t gemm_mfma_group(const GemmArgs* gs, int n, hipStream_t st) {
   ga.n = np;
   const GemmArgs& g = gs[0];
   const int mode = g.acc ? (g.out_dt == DT_BF16 ? 4 : 2) : (g.out_dt == DT_BF16 ? 1 : 0);
-  int min_k = g.K;
-  for (int i = 1; i < n; ++i) min_k = std::min(min_k, gs[i].K);
-  ga.sched = make_schedule(tiles, (int)cdiv(min_k, BK), mode_splits(mode) && np == n ? scratch_tiles_of(g) : 0);
+  int min_k = g.K, max_m = g.M;
+  for (int i = 1; i < n; ++i) { min_k = std::min(min_k, gs[i].K); max_m = std::max(max_m, gs[i].M); }
+  ga.sched = make_schedule(tiles, (int)cdiv(min_k, BK), mode_splits(mode) && np == n ? scratch_tiles_of(g, max_m) : 0);
   ga.scratch = g.scratch;
+  ga.part = partial_floats(max_m);
   const unsigned grid = (unsigned)(ga.sched.full + ga.sched.tail * ga.sched.splits);
   double work = 0.0;
   for (int i = 0; i < n; ++i) work += 2.0 * gs[i].M * gs[i].N * gs[i].K;
@@ -934,7 +944,7 @@ hipError_t gemm_mfma_group(const GemmArgs* gs, int n, hipStream_t st) {
   TailArgs t{};
   t.n = np;
   for (int i = 0; i < np; ++i) t.p[i] = TailProblem{ga.p[i].C, ga.p[i].M, ga.p[i].N, ga.p[i].ldc, ga.p[i].tile_begin, ga.p[i].tiles_m, ga.p[i].tiles_n};
-  t.sched = ga.sched; t.scratch = ga.scratch;
+  t.sched = ga.sched; t.scratch = ga.scratch; t.part = ga.part;
   return launch_tail(mode, t, ga.sched.tail, st);
 }
 

@@ -238,3 +238,19 @@ def test_attn_tile_pairs_follow_the_causal_count():
     chunk_dense = (1 + D) * T * T // (2 * D)
     assert exact <= total <= chunk_dense
     assert total <= exact * 1.01                                  # tile skipping is nearly exact
+
+
+def test_workspace_is_linear_in_the_chunk_up_to_the_partial_tiles_of_split_reductions():
+    """The formula the header states: what is left of the figure without S grows by the same amount per row."""
+    def check(need, widest, slack):
+        rest = {c: need(c) - min(256, 27 * -(-c // 256) * -(-widest // 256)) * min(c, 256) * 1024 for c in (64, 128, 192, 256, 512, 1024)}
+        per_row = (rest[1024] - rest[512]) / 512
+        for lo, hi in ((64, 128), (128, 192), (192, 256), (256, 512)):
+            assert abs(rest[hi] - rest[lo] - per_row * (hi - lo)) <= slack, (lo, hi, rest)
+
+    slack = 64 * 256        # alignment of the carved buffers
+    for d, hq, hkv, dh, F in ((3584, 28, 4, 128, 18944), (256, 4, 2, 128, 512), (1024, 16, 4, 64, 2816)):
+        check(lambda c: sb.streambp_layer_workspace_bytes(sb.layer_cfg(sb.SBP_BF16, 1, 4096, c, d, hq, hkv, dh, F, dw_group_rows=1)),
+              max(d, hq * dh), slack)
+    for d, V in ((256, 1021), (3584, 152064)):
+        check(lambda c: sb.streambp_lmhead_workspace_bytes(sb.head_cfg(sb.SBP_BF16, 1, 4096, c, d, V, dw_group_rows=1)), d, slack)

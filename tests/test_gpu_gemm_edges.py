@@ -83,3 +83,39 @@ def test_rows_of_c_that_start_between_16_byte_boundaries(M, N, K, ta, tb, acc):
         assert sb.debug_gemm(A, B, C, M, N, K, ta, tb, acc=acc) == mfma
         _check(C, want + (1.0 if acc else 0.0), K)
         assert bool((wide[:, N:] == 3.0).all())
+
+
+# (M, N, K, layout, accumulate, tiles, splits): as many ways as the scratch of a whole chip lets the schedule take.  27 slices of 5
+# K steps leave two of 128 steps (one slice ragged, one empty); 15 of 13 leave the last with 10; 27 of 125 ragged steps two empty ones.
+@pytest.mark.parametrize("M,N,K,layout,acc,tiles,splits", [
+    (256, 256, 8192, "nt", False, 1, 27), (40, 256, 8192, "nn", False, 1, 27), (40, 264, 8192, "nt", True, 2, 27),
+    (512, 1024, 12288, "nt", False, 8, 15), (264, 256, 7993, "tn", True, 2, 27)])
+@pytest.mark.parametrize("out", ["f32", "bf16"])
+def test_reductions_split_more_than_eight_ways(M, N, K, layout, acc, tiles, splits, out):
+    import torch
+    from paper_2506_03077_amd import binding as sb
+    if acc and out == "bf16":
+        pytest.skip("bf16 accumulators are added to by whole tiles")
+    A, B, want = _operands(M, N, K, layout == "tn", layout == "nt")
+    scratch = torch.full((256 * 256 * 256,), float("nan"), device="cuda")
+    C = torch.ones((M, N), dtype=torch.float32 if out == "f32" else torch.bfloat16, device="cuda")
+    assert sb.debug_gemm(A, B, C, M, N, K, layout == "tn", layout == "nt", acc=acc, scratch=scratch) == 1
+    _check(C, want + (1.0 if acc else 0.0), K)
+    # one partial tile per tile and slice: 256 columns, of an output of fewer than 256 rows only those rows
+    assert int(torch.isfinite(scratch).sum()) == splits * tiles * min(M, 256) * 256
+
+
+def test_two_operand_pairs_with_slices_across_their_boundary():
+    """C = A B + A2 B2 as one reduction of 34 K steps, split seven ways: slice 3 takes steps 15 .. 19, of which 17 on are the second pair's."""
+    import torch
+    from paper_2506_03077_amd import binding as sb
+    M, N, K = 300, 512, 1088
+    A, B, first = _operands(M, N, K, False, False)
+    A2, B2, _ = _operands(M, N, K + 64, False, False)      # other values
+    A2, B2 = A2[:, :K].contiguous(), B2[:K].contiguous()
+    second = A2.double().cpu() @ B2.double().cpu()
+    scratch = torch.full((256 * 256 * 256,), float("nan"), device="cuda")
+    C = torch.full((M, N), float("nan"), device="cuda")
+    assert sb.debug_gemm(A, B, C, M, N, K, False, False, scratch=scratch, A2=A2, B2=B2) == 1
+    _check(C, first + second, 2 * K)
+    assert int(torch.isfinite(scratch).sum()) == 7 * 4 * 256 * 256
