@@ -11,7 +11,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
-@pytest.mark.parametrize("rows,d", [(1, 8), (5, 504), (3, 512), (4, 520), (7, 1536), (9, 2056), (2, 3584), (6, 3592), (5, 4096), (3, 4104)])
+@pytest.mark.parametrize("rows,d", [(1, 8), (5, 504), (3, 512), (4, 520), (6, 1024), (7, 1536), (9, 2056), (3, 2560), (4, 3072),
+                                    (2, 3584), (6, 3592), (5, 4096), (3, 4104), (9, 5000)])
 def test_rmsnorm_row_widths(rows, d, dtype):
     gen = torch.Generator(device="cuda").manual_seed(d + rows)
     x, dy = (torch.randn((rows, d), generator=gen, device="cuda").to(dtype) for _ in range(2))
