@@ -50,8 +50,6 @@ typedef short short8v __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-#define LDS_AS(p) ((__attribute__((address_space(3))) void*)(p))
-
 constexpr int AT_THREADS = 512;          // 8 waves (forward, dQ): 2 per SIMD
 constexpr int TQ = ATTN_TILE_Q;          // queries per workgroup (fwd, dQ): 8 waves x 32
 constexpr int TK = ATTN_TILE_K;          // 64 keys per step (fwd, dQ)
@@ -88,17 +86,29 @@ __device__ __forceinline__ f32x16 zero16() {
   return z;
 }
 
-// Probabilities and dS are operands of the second products.  DH = 128 rounds them to bf16; DH = 64 keeps them as a sum of two bf16
-// terms (2^-17 relative, below the rounding of o, dq and - through o - delta and dk), P of dV = P^T dO as three (exact), at the price
-// of a further MFMA each: nothing is lost against the shape-agnostic kernels, which hold them in fp32.  Norm-wise error against
-// fp64 at 16 / 4 heads, 512 queries: o 1.599e-3, dq 1.817e-3, dk 7.13e-4 (fp32 kernels: 1.599e-3, 1.817e-3, 7.14e-4).
+// Probabilities and dS are operands of the second products.  DH = 128 rounds them to bf16; DH = 64 keeps them as a sum of bf16 terms, at
+// the price of a further MFMA each: two (2^-17 relative) where the result is rounded to bf16, o and dq, three (exact) for dv = P^T dO
+// and dk = dS^T Q, which leave as fp32.  The statistics of DH = 64 keep fp32 as well: the denominator sums the fp32 probabilities
+// (not the terms, by one more product), P goes to the dK role in fp32, and exponents are differences in the natural domain, scaled
+// to base 2 last (one multiply per score more), so that log-sum-exp and probabilities are rounded where the shape-agnostic kernels
+// round them.  Norm-wise error against fp64, these / the shape-agnostic fp32 kernels, 16 / 4 heads, 512 queries: log-sum-exp 4.3e-8 /
+// 4.5e-8, dv 6.1e-7 / 1.03e-6, dk 6.41e-4 / 6.43e-4, o 1.596e-3 and dq 1.795e-3 both (statistics from the terms, in base 2: log-sum-exp
+// 7.1e-8, at two visible keys 7.2e-7 instead of 4.4e-8).  A 1024-wide two-layer step pays 0.6 % for it.
 template <int DH> constexpr int TERMS = DH == 64 ? 2 : 1;
-template <int DH> constexpr int DV_TERMS = DH == 64 ? 3 : 1;
+template <int DH> constexpr int KV_TERMS = DH == 64 ? 3 : 1;
+template <int DH> constexpr bool FP32_STATS = DH == 64;
 __device__ __forceinline__ bf16x8 rest8(const f32x16& v, int ks, const bf16x8& hi) {      // what pack8 leaves behind
   bf16x8 o;
 #pragma unroll
   for (int j = 0; j < 8; ++j) o[j] = (bf16_t)(v[8 * ks + j] - (float)hi[j]);
   return o;
+}
+
+// exp(x * scale + c): c in log2 units, or in natural ones where the statistics keep fp32
+template <int DH>
+__device__ __forceinline__ float exp_of(float x, float scale, float sl, float c) {
+  if (FP32_STATS<DH>) return __builtin_amdgcn_exp2f(__builtin_fmaf(x, scale, c) * LOG2E);
+  return __builtin_amdgcn_exp2f(__builtin_fmaf(x, sl, c));
 }
 
 #define MFMA(a, b, c) __builtin_amdgcn_mfma_f32_32x32x16_bf16((a), (b), (c), 0, 0, 0)
@@ -241,8 +251,8 @@ __device__ __forceinline__ void query_tile_of(int n_qt, int Hq, int& qt, int& h)
 
 // ------------------------------------------------------------------ forward --
 // 8 waves in two groups of four; waves w and w + 4 share a SIMD.  A key tile costs a wave two slots, each closed by a barrier:
-// multiply (O += P V of the previous tile, S = K Q^T of this one: 68 MFMAs, the softmax denominator - one product against an
-// all-ones operand - among them) and softmax (and the loads of later tiles, spread between the exponentials).  Group 1 runs one
+// multiply (O += P V of the previous tile, S = K Q^T of this one: 68 MFMAs, the softmax denominator - at DH = 128 one product against
+// an all-ones operand - among them) and softmax (and the loads of later tiles, spread between the exponentials).  Group 1 runs one
 // slot behind group 0, so on every SIMD one wave multiplies while the other does its exponentials.
 //   SPLIT = false: 256 queries, 32 per wave; all waves walk all key tiles, four K and four V stages (128 KB), loads two to three
 //                  tiles ahead.
@@ -367,7 +377,7 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
   bf16x8 pb[TERMS<DH>][2][2];             // P^T: [term][query block][k32 step]
   float m_floor = -INFINITY;
   asm volatile("" : "+v"(m_floor));
-  float m_raw[2] = {-INFINITY, -INFINITY}, m_neg[2] = {0.f, 0.f};   // maximum of the raw scores; what the exponent adds (log2 domain)
+  float m_raw[2] = {-INFINITY, -INFINITY}, m_neg[2] = {0.f, 0.f};   // maximum of the raw scores; what the exponent adds (see exp_of)
   if (SPLIT) {
     if (lane < 32) sM[grp][wave & 3][lane] = -INFINITY;
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -406,7 +416,7 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
 #pragma unroll
         for (int t = 0; t < TERMS<DH>; ++t) {
           acc[b][n % DB] = MFMA16(f[n % RING], pb[t][b][n / DB], acc[b][n % DB]);
-          if (n % DB == DB - 1) acc_l[b] = MFMA16(ones, pb[t][b][n / DB], acc_l[b]);
+          if (!FP32_STATS<DH> && n % DB == DB - 1) acc_l[b] = MFMA16(ones, pb[t][b][n / DB], acc_l[b]);
         }
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -469,9 +479,12 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
 #pragma unroll
       for (int b = 0; b < 2; ++b) {
         const float m_new = mx[b] > m_raw[b] ? mx[b] : m_raw[b];
-        const float alpha = m_new == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m_raw[b] * sl - m_new * sl);   // a query that has seen no key yet keeps its zeros
+        const float neg = m_new == -INFINITY ? 0.0f : -(m_new * (FP32_STATS<DH> ? scale : sl));   // all scores so far masked: exp2(-inf - 0) = 0, not exp2(-inf + inf)
+        // a query that has seen no key yet keeps its zeros
+        const float alpha = FP32_STATS<DH> ? (m_raw[b] == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f((neg - m_neg[b]) * LOG2E))
+                                           : (m_new == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m_raw[b] * sl - m_new * sl));
         m_raw[b] = m_new;
-        m_neg[b] = m_new == -INFINITY ? 0.0f : -(m_new * sl);        // all scores so far masked: exp2(-inf - 0) = 0, not exp2(-inf + inf)
+        m_neg[b] = neg;
 #pragma unroll
         for (int r = 0; r < 4; ++r) acc_l[b][r] *= alpha;
 #pragma unroll
@@ -490,12 +503,14 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
 #pragma unroll
       for (int p = x * PIECES / 4; p < (x + 1) * PIECES / 4; ++p) issue_piece(p, i, slot);
       __builtin_amdgcn_sched_barrier(0);
+      float pe[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        const float pe = __builtin_amdgcn_exp2f(__builtin_fmaf(s[b][2 * kk + (e >> 2)][e & 3], sl, m_neg[b]));
-        pb[0][b][kk][e] = (bf16_t)pe;
-        if (TERMS<DH> == 2) pb[TERMS<DH> - 1][b][kk][e] = (bf16_t)(pe - (float)pb[0][b][kk][e]);
+        pe[e] = exp_of<DH>(s[b][2 * kk + (e >> 2)][e & 3], scale, sl, m_neg[b]);
+        pb[0][b][kk][e] = (bf16_t)pe[e];
+        if (TERMS<DH> == 2) pb[TERMS<DH> - 1][b][kk][e] = (bf16_t)(pe[e] - (float)pb[0][b][kk][e]);
       }
+      if (FP32_STATS<DH>) acc_l[b][0] += ((pe[0] + pe[1]) + (pe[2] + pe[3])) + ((pe[4] + pe[5]) + (pe[6] + pe[7]));
       __builtin_amdgcn_sched_barrier(0);
     }
   };
@@ -540,6 +555,13 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
     if (grp == 0) AT_SLOT_BARRIER();        // ... and group 0 waits for it here: both execute the same number of barriers
   }
 
+  if constexpr (FP32_STATS<DH>) {      // the four lanes that share a query hold a quarter of its keys each
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      acc_l[b][0] += __shfl_xor(acc_l[b][0], 16, 64);
+      acc_l[b][0] += __shfl_xor(acc_l[b][0], 32, 64);
+    }
+  }
   if constexpr (SPLIT) {
     // the two halves of the keys meet in LDS: group 1 leaves (maximum, denominator, O), group 0 merges
     __syncthreads();
@@ -549,6 +571,7 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
       for (int b = 0; b < 2; ++b) {
         mine[(b * (4 * DB + 4) + 0) * 64] = m_raw[b];
         mine[(b * (4 * DB + 4) + 1) * 64] = acc_l[b][0];
+        if (FP32_STATS<DH>) mine[(b * (4 * DB + 4) + 2) * 64] = m_neg[b];
 #pragma unroll
         for (int d = 0; d < DB; ++d)
 #pragma unroll
@@ -561,8 +584,15 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
     for (int b = 0; b < 2; ++b) {
       const float m1 = mine[(b * (4 * DB + 4) + 0) * 64], l1 = mine[(b * (4 * DB + 4) + 1) * 64];
       const float m_new = fmaxf(m_raw[b], m1);
-      const float f0 = m_raw[b] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((m_raw[b] - m_new) * sl);
-      const float f1 = m1 == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((m1 - m_new) * sl);
+      float e0 = (m_raw[b] - m_new) * sl, e1 = (m1 - m_new) * sl;
+      if (FP32_STATS<DH>) {      // what the exponents added, as it was rounded
+        const float neg1 = mine[(b * (4 * DB + 4) + 2) * 64], neg = m1 > m_raw[b] ? neg1 : m_neg[b];
+        e0 = (neg - m_neg[b]) * LOG2E;
+        e1 = (neg - neg1) * LOG2E;
+        m_neg[b] = neg;
+      }
+      const float f0 = m_raw[b] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(e0);
+      const float f1 = m1 == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(e1);
       m_raw[b] = m_new;
       acc_l[b][0] = acc_l[b][0] * f0 + l1 * f1;
 #pragma unroll
@@ -585,7 +615,7 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
       for (int r = 0; r < 4; ++r) w[r] = (bf16_t)(acc[b][d][r] * inv);
       *(bf16x4*)(op + d * 16) = w;
     }
-    if (lg == 0) lse[(int64_t)h * c + my_q] = l_tot > 0.f ? (m_raw[b] * sl + log2f(l_tot)) * LN2 : -INFINITY;
+    if (lg == 0) lse[(int64_t)h * c + my_q] = !(l_tot > 0.f) ? -INFINITY : FP32_STATS<DH> ? logf(l_tot) - m_neg[b] : (m_raw[b] * sl + log2f(l_tot)) * LN2;
   }
 }
 
@@ -634,7 +664,7 @@ __global__ __launch_bounds__(AT_THREADS) void attn_bwd_dq_mfma_k(const bf16_t* _
     for (int ks = 0; ks < KS; ++ks) { bq[ks] = *(const bf16x8*)(q + off + ks * 16); bdo[ks] = *(const bf16x8*)(d_o + off + ks * 16); }
   }
   const float lse_q = lse[(int64_t)h * c + q_row];
-  const float lse2 = lse_q == -INFINITY ? 0.0f : lse_q * LOG2E;    // a query that saw no key: every score is masked, p = exp2(-inf) = 0
+  const float lse2 = lse_q == -INFINITY ? 0.0f : FP32_STATS<DH> ? lse_q : lse_q * LOG2E;    // a query that saw no key: every score is masked, p = exp2(-inf) = 0
   const float dlt = delta[(int64_t)h * c + q_row];
   const float sl = scale * LOG2E;
   f32x16 acc[DB];
@@ -660,7 +690,7 @@ __global__ __launch_bounds__(AT_THREADS) void attn_bwd_dq_mfma_k(const bf16_t* _
       }
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], sl, -lse2));
+        const float p = exp_of<DH>(s[r], scale, sl, -lse2);
         s[r] = p * (dp[r] - dlt);                              // dS^T (the factor `scale` is applied at the end)
       }
       bf16x8 db[TERMS<DH>][2];
@@ -752,7 +782,7 @@ __global__ __launch_bounds__(AT_THREADS) void attn_bwd_dq_mfma_k(const bf16_t* _
 // -------------------------------------------------------------------- dK/dV --
 // Workgroup = 128 keys of one KV head, 8 waves = 4 key blocks of 32 x 2 roles, so that each SIMD holds the two
 // waves of one key block:
-//   role P (waves 0-3): S = Q K^T -> P = exp2(S*sl - lse) (masked), rounded to bf16 -> leaves P in LDS for its
+//   role P (waves 0-3): S = Q K^T -> P = exp(S*scale - lse) (masked), DH = 128: rounded to bf16 -> leaves P in LDS for its
 //                       partner -> dV^T += dO^T P
 //   role S (waves 4-7): dP = dO V^T -> takes P -> dS = P * (dP - delta) -> dK^T += Q^T dS
 // Each role keeps only its own operand fragments (K or V) and its own accumulator (dV or dK) in registers: half the registers of a
@@ -775,8 +805,9 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
                                                                   int q_start, int c, float scale, int window, int kv_first,
                                                                   int key_block0, float* __restrict__ part) {
   __shared__ __attribute__((aligned(1024))) char sQD[2][KV_STAGES][TILE64<DH>];   // [Q | dO][stage]
-  __shared__ __attribute__((aligned(16))) bf16x8 sP[4][4 * TERMS<DH>][64];   // [key block][(query block * 2 + k16 step), term][lane]
-  __shared__ __attribute__((aligned(16))) float sL[KV_STAGES][QT];  // log2-domain log-sum-exp of the tile's queries
+  // P of the tile, [key block][slot][lane]: bf16, slot = query block * 2 + k16 step; FP32_STATS: fp32, slot = query block * 4 + r / 4
+  __shared__ __attribute__((aligned(16))) bf16x8 sP[4][FP32_STATS<DH> ? 8 : 4][64];
+  __shared__ __attribute__((aligned(16))) float sL[KV_STAGES][QT];  // (log2-domain) log-sum-exp of the tile's queries
   __shared__ __attribute__((aligned(16))) float sDl[KV_STAGES][QT]; // delta of the tile's queries
 
   const int G = Hq / Hkv;
@@ -797,7 +828,7 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
   const FragPre<DH> fr = frag_pre<DH>(role_p ? lds0 : lds_do);                 // row-wise operand: Q (P) / dO (S)
   const FragPre<DH> gt = frag_pre<DH>(role_p ? lds_do : lds0);                 // transposed operand: dO (P) / Q (S)
   const TileLoad<DH, KV_THREADS> tl = tile_load_pre<DH, KV_THREADS>(q_stride);
-  const uint32_t sp_lane = pin(lds_addr(&sP[kb][0][lane]));                      // + ((term * 2 + b) * 2 + ks) * 1024
+  const uint32_t sp_lane = pin(lds_addr(&sP[kb][0][lane]));                      // + slot * 1024
   const uint32_t stat_lane = pin(lds_addr(role_p ? &sL[0][4 * half] : &sDl[0][4 * half]));   // + stage * 256 + (b * 32 + 8 a) * 4
 
   constexpr int KS = DH / 16, DB = DH / 32;
@@ -846,7 +877,7 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
   constexpr int LOADS = 2 * (8 * DH / KV_THREADS) + 1;       // vector-memory operations of one issue
   auto run = [&](auto role_c) __attribute__((always_inline)) {
     constexpr bool RP = decltype(role_c)::value;
-    constexpr int NT = RP ? DV_TERMS<DH> : TERMS<DH>;
+    constexpr int NT = KV_TERMS<DH>;
     f32x16 acc[DB];          // dV^T (role P) or dK^T (role S): rows = head_dim, column = my key
     f32x16 t[2];             // S or dP of the tile's two 32-query blocks: column = my key, rows = queries b * 32 + acc_row(r, half)
     bf16x8 w[NT][2][2];      // P or dS: [term][query block][k16 step]
@@ -870,6 +901,14 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
       mfma_chain<2 * KS, CHAIN>([&](int n) { return lds_b128(fr.rows[n >> 1] + so + (n & 1) * 32 * (DH * 2)); },
                                 [&](int n, const bf16x8& f) { t[n & 1] = MFMA(f, breg[n >> 1], t[n & 1]); });
     };
+    auto terms = [&](int b, int ks) __attribute__((always_inline)) {      // P resp. dS as operands of the second product
+      w[0][b][ks] = pack8(t[b], ks);
+      if constexpr (NT == 3) {
+        w[1][b][ks] = rest8(t[b], ks, w[0][b][ks]);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) w[2][b][ks][e] = (bf16_t)((t[b][8 * ks + e] - (float)w[0][b][ks][e]) - (float)w[1][b][ks][e]);
+      }
+    };
     auto vector = [&](int stage) __attribute__((always_inline)) {
       if constexpr (RP) {
         const bool diag = (q_start + qbase < kw0 + 31) || (qbase + QT > c) || kw0 < kv_first ||   // some pair masked, or ragged query tile
@@ -892,19 +931,19 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
             const float4 l4 = lds_f4(stat_lane + stage * QT * 4 + (b * 32 + 8 * a) * 4);
             const float lv[4] = {l4.x, l4.y, l4.z, l4.w};
 #pragma unroll
-            for (int e = 0; e < 4; ++e) t[b][4 * a + e] = __builtin_amdgcn_exp2f(__builtin_fmaf(t[b][4 * a + e], sl, -lv[e]));
+            for (int e = 0; e < 4; ++e) t[b][4 * a + e] = exp_of<DH>(t[b][4 * a + e], scale, sl, -lv[e]);
           }
 #pragma unroll
           for (int ks = 0; ks < 2; ++ks) {
-            w[0][b][ks] = pack8(t[b], ks);
-            if constexpr (NT == 3) {
-              w[1][b][ks] = rest8(t[b], ks, w[0][b][ks]);
+            terms(b, ks);
+            if constexpr (!FP32_STATS<DH>)
+              *(bf16x8*)(__attribute__((address_space(3))) char*)(uintptr_t)(sp_lane + (b * 2 + ks) * 1024) = w[0][b][ks];
+          }
+          if constexpr (FP32_STATS<DH>) {
 #pragma unroll
-              for (int e = 0; e < 8; ++e) w[2][b][ks][e] = (bf16_t)((t[b][8 * ks + e] - (float)w[0][b][ks][e]) - (float)w[1][b][ks][e]);
-            }
-#pragma unroll
-            for (int u = 0; u < TERMS<DH>; ++u)
-              *(bf16x8*)(__attribute__((address_space(3))) char*)(uintptr_t)(sp_lane + ((u * 2 + b) * 2 + ks) * 1024) = w[u][b][ks];
+            for (int a = 0; a < 4; ++a)
+              *(f32x4*)(__attribute__((address_space(3))) char*)(uintptr_t)(sp_lane + (b * 4 + a) * 1024) =
+                  f32x4{t[b][4 * a], t[b][4 * a + 1], t[b][4 * a + 2], t[b][4 * a + 3]};
           }
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // P is in LDS before the barrier
@@ -916,14 +955,18 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
             const float4 d0 = lds_f4(stat_lane + stage * QT * 4 + (b * 32 + 16 * ks) * 4);
             const float4 d1 = lds_f4(stat_lane + stage * QT * 4 + (b * 32 + 16 * ks + 8) * 4);
             const float dl[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
-            const bf16x8 p8 = lds_b128(sp_lane + (b * 2 + ks) * 1024);
-            bf16x8 p8_rest;
-            if (TERMS<DH> == 2) p8_rest = lds_b128(sp_lane + ((2 + b) * 2 + ks) * 1024);
+            float pv[8];
+            if constexpr (FP32_STATS<DH>) {
+              const float4 p0 = lds_f4(sp_lane + (b * 4 + 2 * ks) * 1024), p1 = lds_f4(sp_lane + (b * 4 + 2 * ks + 1) * 1024);
+              pv[0] = p0.x; pv[1] = p0.y; pv[2] = p0.z; pv[3] = p0.w; pv[4] = p1.x; pv[5] = p1.y; pv[6] = p1.z; pv[7] = p1.w;
+            } else {
+              const bf16x8 p8 = lds_b128(sp_lane + (b * 2 + ks) * 1024);
 #pragma unroll
-            for (int e = 0; e < 8; ++e)     // dS (the softmax scale is applied once at the end)
-              t[b][8 * ks + e] = (TERMS<DH> == 2 ? (float)p8[e] + (float)p8_rest[e] : (float)p8[e]) * (t[b][8 * ks + e] - dl[e]);
-            w[0][b][ks] = pack8(t[b], ks);
-            if (TERMS<DH> == 2) w[NT - 1][b][ks] = rest8(t[b], ks, w[0][b][ks]);
+              for (int e = 0; e < 8; ++e) pv[e] = (float)p8[e];
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) t[b][8 * ks + e] = pv[e] * (t[b][8 * ks + e] - dl[e]);     // dS (the softmax scale is applied once at the end)
+            terms(b, ks);
           }
       }
     };
@@ -999,7 +1042,7 @@ __global__ __launch_bounds__(256) void attn_dkv_sum_k(const float4* __restrict__
 
 // delta[h, t] = sum_j d_o[t,h,j] * o[t,h,j]  (one wave per (t, h))
 // also lse2[h, t] = lse[h, t] * log2(e), the form the dK/dV kernel's exp2 wants (one multiply per (t, h) here
-// instead of one per score there)
+// instead of one per score there); 64-wide heads, whose exponents are natural differences: lse[h, t] itself
 template <int DH>
 __global__ __launch_bounds__(256) void attn_delta_mfma_k(const bf16_t* __restrict__ o, const bf16_t* __restrict__ d_o,
                                                          const float* __restrict__ lse, float* __restrict__ delta,
@@ -1017,7 +1060,7 @@ __global__ __launch_bounds__(256) void attn_delta_mfma_k(const bf16_t* __restric
   if (lane == 0) {
     delta[(int64_t)h * c + t] = s;
     const float l = lse[(int64_t)h * c + t];
-    lse2[(int64_t)h * c + t] = l == -INFINITY ? 0.0f : l * LOG2E;   // a query that saw no key: its scores are all masked anyway
+    lse2[(int64_t)h * c + t] = l == -INFINITY ? 0.0f : FP32_STATS<DH> ? l : l * LOG2E;   // a query that saw no key: its scores are all masked anyway
   }
 }
 
