@@ -9,6 +9,9 @@
 #include <cstdio>
 #include <cstring>
 #include <mutex>
+#ifdef __SANITIZE_ADDRESS__
+#include <sanitizer/asan_interface.h>
+#endif
 
 using namespace sbp;
 
@@ -31,7 +34,8 @@ int32_t fail(int32_t code, const char* fmt, ...) {
       return fail(SBP_ERR_HIP, "%s failed: %s (%s:%d)", #expr, hipGetErrorString(e__), __FILE__, __LINE__); \
   } while (0)
 
-// Bump allocator over the caller's workspace (256-byte granularity).
+// Bump allocator over the caller's workspace (256-byte granularity).  In a host build under the address sanitizer the bytes between two
+// carved buffers, and a gap added for that, are out of bounds.
 struct Carver {
   char* base; size_t off = 0;
   explicit Carver(void* p) : base((char*)p) {}
@@ -39,6 +43,13 @@ struct Carver {
   void* take_bytes(size_t bytes) {
     void* p = base ? base + off : nullptr;
     off += align_up(bytes, 256);
+#ifdef __SANITIZE_ADDRESS__
+    off += 256;
+    if (base) {
+      ASAN_UNPOISON_MEMORY_REGION(p, bytes);
+      ASAN_POISON_MEMORY_REGION((char*)p + bytes, (size_t)(base + off - (char*)p) - bytes);
+    }
+#endif
     return p;
   }
 };
@@ -204,7 +215,7 @@ int32_t kv_prepass(const sbp_layer_cfg* c, const sbp_layer_weights* w, const Lay
   void* a_rows = s.a;
   int block = cm;
   void* idle = held ? s.dact : s.gate;
-  const size_t idle_rows = (size_t)((const char*)s.dh1_t - (const char*)idle) / ((size_t)d * es);
+  const size_t idle_rows = (size_t)((const char*)s.dact + (size_t)cm * c->mlp_width * es - (const char*)idle) / ((size_t)d * es);
   if (held || idle_rows > (size_t)cm) {
     a_rows = idle;
     block = (int)std::min<size_t>((size_t)T, idle_rows);
@@ -935,10 +946,18 @@ extern "C" int32_t streambp_stack_backward(const sbp_stack_cfg* c, const sbp_lay
 }
 
 // ------------------------------------------------------------ stack glue --
+struct RmsnormWs { float *rstd, *partial; size_t bytes; };
+static RmsnormWs carve_rmsnorm(int n_rows, int hidden, void* ws) {
+  Carver cv(ws);
+  RmsnormWs w;
+  w.rstd = cv.take<float>((size_t)std::max(n_rows, 1));
+  w.partial = cv.take<float>(rmsnorm_bwd_partial_floats(n_rows, hidden) + 64);
+  w.bytes = cv.off;
+  return w;
+}
 size_t streambp_rmsnorm_workspace_bytes(int64_t n_rows, int32_t hidden) {
   if (n_rows < 0 || n_rows > INT32_MAX || hidden < 1) return 0;
-  return align_up((size_t)std::max<int64_t>(n_rows, 1) * sizeof(float), 256) +
-         align_up(rmsnorm_bwd_partial_floats((int)n_rows, hidden) * sizeof(float) + 256, 256);
+  return carve_rmsnorm((int)n_rows, hidden, nullptr).bytes;
 }
 int32_t streambp_rmsnorm_forward(int32_t dtype, int64_t n_rows, int32_t hidden, float eps, const void* x, const void* g,
                                  void* y, void* hip_stream) {
@@ -956,12 +975,10 @@ int32_t streambp_rmsnorm_backward(int32_t dtype, int64_t n_rows, int32_t hidden,
   if (!x || !g || !dy || !dx || !dg || !workspace) return fail(SBP_ERR_NULL, "x, g, dy, dx, dg and workspace must be non-NULL");
   if ((uintptr_t)workspace & 255) return fail(SBP_ERR_WORKSPACE, "workspace must be 256-byte aligned");
   if (workspace_bytes < streambp_rmsnorm_workspace_bytes(n_rows, hidden)) return fail(SBP_ERR_WORKSPACE, "workspace too small");
-  Carver cv(workspace);
-  float* rstd = cv.take<float>((size_t)std::max<int64_t>(n_rows, 1));
-  float* partial = cv.take<float>(rmsnorm_bwd_partial_floats((int)n_rows, hidden) + 64);
+  const RmsnormWs s = carve_rmsnorm((int)n_rows, hidden, workspace);
   hipStream_t st = (hipStream_t)hip_stream;
-  HIPCHK(rmsnorm_fwd(dtype, x, nullptr, g, nullptr, nullptr, rstd, (int)n_rows, hidden, eps, st));
-  HIPCHK(rmsnorm_bwd_plain(dtype, dy, x, g, rstd, dx, dg, partial, (int)n_rows, hidden, st));
+  HIPCHK(rmsnorm_fwd(dtype, x, nullptr, g, nullptr, nullptr, s.rstd, (int)n_rows, hidden, eps, st));
+  HIPCHK(rmsnorm_bwd_plain(dtype, dy, x, g, s.rstd, dx, dg, s.partial, (int)n_rows, hidden, st));
   return SBP_OK;
 }
 int32_t streambp_embedding_forward(int32_t dtype, int64_t n_rows, int32_t hidden, int32_t vocab, const int32_t* ids,

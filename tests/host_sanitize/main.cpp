@@ -10,7 +10,7 @@
 #include <cstring>
 #include <vector>
 
-namespace sbp { long long stub_touches(); }
+namespace sbp { long long stub_touches(); extern bool stub_overrun; }
 
 static void* dmalloc(size_t bytes) {             // "device" memory: 256-byte aligned like a real allocation
   void* p = nullptr;
@@ -151,6 +151,10 @@ static int run_planted() {
 int main(int argc, char** argv) {
   const bool big = argc > 1 && std::strcmp(argv[1], "big") == 0;
   if (argc > 1 && std::strcmp(argv[1], "planted") == 0) return run_planted();
+  if (argc > 1 && std::strcmp(argv[1], "planted_inside") == 0) {   // one byte past a buffer in the middle of the workspace
+    sbp::stub_overrun = true;
+    return run_head(SBP_BF16, 1, 50, 24, 64, 1021, SBP_OBJ_SFT, SBP_F32);
+  }
   int bad = 0;
   // small ragged shapes, both storage types, every mask option, adapter mode
   bad += run_layer(SBP_F32, 1, 256, 64, 64, 4, 4, 16, 172, 0, false, 3);
@@ -158,10 +162,13 @@ int main(int argc, char** argv) {
   bad += run_layer(SBP_BF16, 2, 333, 100, 256, 4, 2, 128, 512, 0, true, 8);
   bad += run_layer(SBP_BF16, 1, 1100, 128, 1024, 8, 2, 128, 4096, 200, false, 32);
   bad += run_layer(SBP_BF16, 1, 1, 1, 256, 4, 2, 128, 512, 0, false, 1);
+  bad += run_layer(SBP_BF16, 9, 70, 64, 256, 4, 2, 64, 512, 0, true, 0);        // weight-gradient groups that span sequences
+  bad += run_layer(SBP_BF16, 5, 130, 200, 256, 4, 2, 128, 128, 0, false, 0);    // ... an MLP narrower than hidden: groups end with the sequence
   bad += run_layer(SBP_BF16, 1, 5, 1000000, 72, 6, 2, 24, 172, 0, false, 5);
   for (int obj = 0; obj < 3; ++obj) {
     bad += run_head(SBP_F32, 2, 50, 24, 64, 512, obj, SBP_F32);
     bad += run_head(SBP_BF16, 2, 300, 128, 256, 1024, obj, obj == 1 ? SBP_BF16 : SBP_F32);
+    for (int V : {1000, 1021, 7}) bad += run_head(SBP_BF16, 2, 70, 64, 256, V, obj, SBP_F32);      // padded rows of logits
   }
   bad += run_head(SBP_BF16, 1, 1, 1, 256, 1, SBP_OBJ_SFT, SBP_F32);
   bad += run_attn(SBP_BF16, 8, 2, 128, 300, 77, 0, 0);

@@ -1,7 +1,8 @@
 // Host stand-ins for every kernel launcher declared in csrc/launch.h.  Nothing is computed: each launcher touches the
 // first and the last byte of every operand extent its kernels would read or write, so that the address sanitizer
 // sees exactly the memory ranges the C-ABI layer (workspace carving, chunk offsets, leading dimensions, ragged last
-// chunks) hands to the kernels.  An extent that leaves its allocation is a heap-buffer-overflow report.
+// chunks) hands to the kernels.  An extent that leaves its allocation is a heap-buffer-overflow report, one that leaves its buffer
+// inside the workspace a use-after-poison report (the carver poisons what lies between two buffers).
 #include "launch.h"
 
 #include <algorithm>
@@ -12,6 +13,8 @@ namespace sbp {
 
 static std::atomic<long long> g_touches{0};
 long long stub_touches() { return g_touches.load(); }
+// a planted mistake: the head's row kernel writes one element past the last padded row of dz
+bool stub_overrun = false;
 
 static void rd(const void* p, size_t bytes) {
   if (!p || bytes == 0) return;
@@ -31,9 +34,12 @@ static size_t es(int dt) { return dtype_size(dt); }
 
 static void touch_gemm(const GemmArgs& g) {
   if (g.M <= 0 || g.N <= 0 || g.K <= 0) return;
-  const size_t a_el = g.ta ? (size_t)(g.K - 1) * g.lda + g.M : (size_t)(g.M - 1) * g.lda + g.K;
+  // padded operands: A is read to the next multiple of 64 reduction columns (NN) resp. of 8 output rows (TN), C written to the next
+  // multiple of 4 columns
+  const size_t a_m = g.ta && g.a_padded ? align_up(g.M, 8) : g.M, a_k = !g.ta && g.a_padded ? align_up(g.K, 64) : g.K;
+  const size_t a_el = g.ta ? (size_t)(g.K - 1) * g.lda + a_m : (size_t)(g.M - 1) * g.lda + a_k;
   const size_t b_el = g.tb ? (size_t)(g.N - 1) * g.ldb + g.K : (size_t)(g.K - 1) * g.ldb + g.N;
-  const size_t c_el = (size_t)(g.M - 1) * g.ldc + g.N;
+  const size_t c_el = (size_t)(g.M - 1) * g.ldc + (g.c_padded ? align_up(g.N, 4) : g.N);
   rd(g.A, a_el * es(g.in_dt)); rd(g.B, b_el * es(g.in_dt));
   if (g.A2) { rd(g.A2, a_el * es(g.in_dt)); rd(g.B2, b_el * es(g.in_dt)); }
   if (g.swiglu_gate) {
@@ -44,14 +50,18 @@ static void touch_gemm(const GemmArgs& g) {
   if (g.row_stats) wr(g.row_stats, (size_t)g.M * cdiv(g.N, GEMM_STAT_COLS) * sizeof(float2));
   if (g.numer_targets) { wr(g.numer_target_value, (size_t)g.M * 4); if (g.numer_row_index) rd(g.numer_row_index, (size_t)g.M * 4); }
   if (g.rows_dev) rd(g.rows_dev, sizeof(int));
-  // split-K partial slices: at most what gemm_scratch_bytes promises for 4 slices of a dense C
-  if (g.scratch && g.ldc == g.N) wr(g.scratch, std::min(g.scratch_bytes, (size_t)4 * g.M * g.N * sizeof(float)));
+  if (g.scratch) wr(g.scratch, g.scratch_bytes);     // split reductions may fill all that they are given
 }
-bool gemm_row_stats_supported(const GemmArgs& g) { return g.in_dt == DT_BF16 && !g.ta && g.tb && g.out_dt == DT_F32 && g.N % 8 == 0 && g.K % 64 == 0; }
+static bool nt_mfma(const GemmArgs& g) {              // the MFMA kernels' rule for C = A B^T
+  return g.in_dt == DT_BF16 && !g.ta && g.tb && !g.acc && g.K % 64 == 0 && (g.N % 8 == 0 || (g.c_padded && g.ldc % 8 == 0 && g.ldc >= g.N));
+}
+bool gemm_row_stats_supported(const GemmArgs& g) { return nt_mfma(g) && g.out_dt == DT_F32; }
 bool gemm_numerators_supported(const GemmArgs& g) {
-  return g.in_dt == DT_BF16 && !g.ta && g.tb && g.out_dt == DT_BF16 && g.N % 8 == 0 && g.K % 64 == 0 && g.row_stats && g.numer_targets && g.numer_target_value;
+  return nt_mfma(g) && g.out_dt == DT_BF16 && g.row_stats && g.numer_targets && g.numer_target_value;
 }
-size_t gemm_scratch_bytes(int max_m, int max_n) { return (size_t)4 * max_m * max_n * sizeof(float); }
+size_t gemm_scratch_bytes(int max_m, int max_n) {     // at most one partial tile per CU, 27 per output tile, of the rows that exist
+  return (size_t)std::min<int64_t>(256, cdiv(max_m, 256) * cdiv(max_n, 256) * 27) * std::min(max_m, 256) * 256 * sizeof(float);
+}
 hipError_t gemm(const GemmArgs& g, hipStream_t) { touch_gemm(g); return hipSuccess; }
 hipError_t gemm_batch(const GemmArgs* gs, int n, hipStream_t, bool) { for (int i = 0; i < n; ++i) touch_gemm(gs[i]); return hipSuccess; }
 bool gemm_uses_mfma(const GemmArgs& g) { return g.in_dt == DT_BF16; }
@@ -67,7 +77,7 @@ hipError_t rope_table(float2* tab, int n_pos, int dh, float, int, hipStream_t) {
 hipError_t rope_apply(int dt, void* x, const float2* tab, int rows, int H, int dh, bool, hipStream_t) {
   wr(x, (size_t)rows * H * dh * es(dt)); rd(tab, (size_t)rows * (dh / 2) * sizeof(float2)); return hipSuccess;
 }
-size_t rmsnorm_bwd_partial_floats(int rows, int d) { return (size_t)cdiv(rows, 8) * (size_t)d; }
+size_t rmsnorm_bwd_partial_floats(int rows, int d) { return (size_t)cdiv(rows, 4) * (size_t)d; }
 hipError_t rmsnorm_fwd(int dt, const void* x, const float* add, const void* g, void* out, float* sum_out, float* rstd, int rows, int d, float, hipStream_t) {
   const size_t n = (size_t)rows * d;
   rd(x, n * es(dt)); rd(add, n * 4); rd(g, (size_t)d * es(dt)); wr(out, n * es(dt)); wr(sum_out, n * 4); wr(rstd, (size_t)rows * 4);
@@ -123,16 +133,18 @@ static void touch_attn(const AttnArgs& a, bool bwd) {
   if (!bwd) { wr(a.o, qn * es(a.dt)); wr(a.lse, (size_t)a.Hq * a.q_len * 4); return; }
   rd(a.o, qn * es(a.dt)); rd(a.lse, (size_t)a.Hq * a.q_len * 4); rd(a.d_o, qn * es(a.dt)); wr(a.dq, qn * es(a.dt));
   wr(a.dk, kn * 4); wr(a.dv, kn * 4); wr(a.delta, (size_t)2 * a.Hq * a.q_len * 4);
+  if (a.dkv_scratch) wr(a.dkv_scratch, a.dkv_scratch_bytes);     // the parts of split key blocks
 }
 hipError_t attn_forward(const AttnArgs& a, hipStream_t) { if (a.q_len > 0) touch_attn(a, false); return hipSuccess; }
 hipError_t attn_backward(const AttnArgs& a, hipStream_t) { if (a.q_len > 0) touch_attn(a, true); return hipSuccess; }
-bool attn_uses_mfma(int dt, int dh, int Hq, int Hkv) { return dt == DT_BF16 && dh == 128 && Hq % Hkv == 0; }
+bool attn_uses_mfma(int dt, int dh, int Hq, int Hkv) { return dt == DT_BF16 && (dh == 128 || dh == 64) && Hq % Hkv == 0; }
 void attn_set_force_generic(bool) {}
 
 hipError_t head_rows(const HeadRowArgs& a, hipStream_t) {
-  const size_t n = (size_t)a.rows * a.V;
-  if (a.target_logit) { rd(a.target_logit, (size_t)a.rows * 4); rd(a.dz, n * es(a.dt)); } else rd(a.z, n * 4);
-  wr(a.dz, n * es(a.dt)); wr(a.row_loss, (size_t)a.rows * 4);
+  const size_t n = (size_t)a.rows * a.ldz;            // rows are padded; dz is written to their end
+  if (a.target_logit) { rd(a.target_logit, (size_t)a.rows * 4); rd(a.dz, n * es(a.dt)); }
+  else rd(a.z, ((size_t)(a.rows - 1) * a.ldz + (a.ldz % 4 == 0 ? align_up(a.V, 4) : a.V)) * 4);
+  wr(a.dz, n * es(a.dt) + (stub_overrun ? 1 : 0)); wr(a.row_loss, (size_t)a.rows * 4);
   if (a.stats) rd(a.stats, (size_t)a.rows * a.n_stat * sizeof(float2));
   if (a.row_index) rd(a.row_index, (size_t)a.rows * 4);
   if (a.rows_dev) rd(a.rows_dev, 4);

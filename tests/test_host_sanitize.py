@@ -48,3 +48,8 @@ def test_host_layer_is_clean_under_sanitizers_at_the_benchmark_shapes(binary):
 def test_a_planted_short_buffer_is_reported(binary):
     p = run(binary, "planted")
     assert p.returncode != 0 and "heap-buffer-overflow" in p.stderr
+
+
+def test_a_planted_overrun_inside_the_workspace_is_reported(binary):
+    p = run(binary, "planted_inside")
+    assert p.returncode != 0 and "use-after-poison" in p.stderr
