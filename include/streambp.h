@@ -24,7 +24,9 @@
  *    the loss are always fp32.
  *  - "+=" arguments are accumulated into (the caller zeroes them before the
  *    first call - "initialised from zero", Sec. 3.2.1); "out" arguments are
- *    overwritten.  Inputs are never modified.
+ *    overwritten.  Inputs are never modified.  An accumulator is read, added to
+ *    and written without atomics: calls that accumulate into the same tensor
+ *    must be ordered (one stream, or an event between two).
  *  - Return value: 0 on success; negative on error, in which case nothing has
  *    been enqueued (except SBP_ERR_HIP, which can surface mid-sequence).
  *    streambp_last_error() returns a thread-local message for the last failure.
@@ -337,12 +339,13 @@ int32_t streambp_stack_backward(const sbp_stack_cfg *cfg, const sbp_layer_weight
 const char *streambp_version(void);
 const char *streambp_last_error(void);
 /* Which kernels a configuration gets (host arithmetic only).  1: every GEMM and the attention of the configuration
- * run on the bf16 MFMA kernels (needs bf16 storage, head_dim 128 and hidden, n_q_heads*head_dim, n_kv_heads*head_dim,
- * mlp_width - for the head: hidden and vocab - multiples of 64, 16-byte aligned tensors; widths that are not multiples
- * of the 256-wide output tile, such as a 151936-word vocabulary, run with a masked last tile).  0: some of it does not
- * (streambp_last_error() says which dimension is the reason): 64-wide heads run on MFMA kernels that keep probabilities in two
- * or three bf16 terms, a vocabulary that is no multiple of 8 keeps fp32 logits, both below the full rate; other sizes run on the
- * shape-agnostic fp32 kernels, which are much slower.  Nothing is refused.  Negative: the configuration itself is invalid. */
+ * run on the bf16 MFMA kernels in their full-rate form (needs bf16 storage, head_dim 128 and hidden, n_q_heads*head_dim,
+ * n_kv_heads*head_dim, mlp_width multiples of 64 - for the head: hidden a multiple of 64, vocab one of 8 - and 16-byte aligned
+ * tensors; widths that are not multiples of the 256-wide output tile, such as a 151936-word vocabulary, run with a masked last
+ * tile).  0: some of it does not (streambp_last_error() says which dimension is the reason): 64-wide heads run on MFMA kernels that
+ * keep probabilities in two or three bf16 terms, a vocabulary that is no multiple of 8 keeps fp32 logits, both below the full rate;
+ * other sizes run on the shape-agnostic fp32 kernels, which are much slower.  Nothing is refused.  Negative: the configuration
+ * itself is invalid. */
 int32_t streambp_layer_fast_path(const sbp_layer_cfg *cfg);
 int32_t streambp_lmhead_fast_path(const sbp_head_cfg *cfg);
 /* Number of bf16 GEMM / attention launches, since the library was loaded, that ran on the shape-agnostic kernels because

@@ -767,8 +767,9 @@ int32_t streambp_attn_chunk_backward(const sbp_attn_cfg* c, const void* q, const
 }
 
 // Which kernels a configuration gets.  The bf16 MFMA GEMMs need every matrix dimension of the layer (hidden, the q and
-// k/v widths, mlp_width - resp. hidden and vocab for the head) to be a multiple of 64 (the reduction step; output tiles
-// are 256 wide with a masked ragged last tile), the MFMA attention head_dim 128.  64-wide heads and other vocabularies run on MFMA
+// k/v widths, mlp_width - resp. the head's hidden) to be a multiple of 64 (the reduction step; output tiles are 256 wide with
+// a masked ragged last tile), the MFMA attention head_dim 128.  The head's rows of logits are padded to 64 columns, so that its
+// products take any vocabulary; the softmax-numerator store needs a multiple of 8.  64-wide heads and other vocabularies run on MFMA
 // kernels too, below the full rate; anything else runs on the shape-agnostic fp32 kernels, which are much slower.
 int32_t streambp_layer_fast_path(const sbp_layer_cfg* c) {
   if (int32_t rc = check_layer_cfg(c)) return rc;
@@ -785,7 +786,7 @@ int32_t streambp_lmhead_fast_path(const sbp_head_cfg* c) {
   if (int32_t rc = check_head_cfg(c)) return rc;
   if (c->dtype != SBP_BF16) return fail(0, "fp32 storage: the shape-agnostic kernels are the only path"), 0;
   if (c->hidden % 64) return fail(0, "hidden = %d is not a multiple of 64: the head's GEMMs leave the MFMA kernels", c->hidden), 0;
-  if (c->vocab % 64) return fail(0, "vocab = %d is not a multiple of 64: its rows are padded, and fp32 logits kept where it is no multiple of 8", c->vocab), 0;
+  if (c->vocab % 8) return fail(0, "vocab = %d is not a multiple of 8: the head keeps fp32 logits instead of softmax numerators", c->vocab), 0;
   return 1;
 }
 int64_t streambp_generic_launches(void) { return (int64_t)generic_bf16_launches(); }

@@ -254,3 +254,8 @@ def test_workspace_is_linear_in_the_chunk_up_to_the_partial_tiles_of_split_reduc
               max(d, hq * dh), slack)
     for d, V in ((256, 1021), (3584, 152064)):
         check(lambda c: sb.streambp_lmhead_workspace_bytes(sb.head_cfg(sb.SBP_BF16, 1, 4096, c, d, V, dw_group_rows=1)), d, slack)
+
+
+@pytest.mark.parametrize("vocab,fast", [(152064, 1), (1000, 1), (50264, 1), (1021, 0), (50260, 0)])
+def test_fast_path_query_of_the_head_follows_the_numerator_store(vocab, fast):
+    assert sb.streambp_lmhead_fast_path(sb.head_cfg(sb.SBP_BF16, 1, 64, 64, 256, vocab)) == fast
