@@ -25,12 +25,15 @@ sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2516.6      # 256 CU x 4096 flop/clk/CU x 2.4 GHz (dense bf16 MFMA); vendor figure ~2.5 PF
 PEAK_HBM_GBS = 8000.0
-# HBM-side bytes per launch of the dominant kernel of the default workload.  Hardware counters cannot be read inside
-# the timed process: the figure is the one two rocprofv3 --pmc runs of this script measured (FETCH_SIZE, WRITE_SIZE, scaled
-# by a 1 GiB copy-like kernel) and is reported together with the file under profiles/ that holds those runs; for any
+# HBM-side bytes per launch of the kernels that can be the dominant one of the default workload.  Hardware counters cannot be read inside
+# the timed process: the figures are those two rocprofv3 --pmc runs of this script measured (FETCH_SIZE, WRITE_SIZE, scaled
+# by a 1 GiB copy-like kernel) and are reported together with the file under profiles/ that holds those runs; for any
 # other kernel or shape the field is null.
+TRAFFIC_RUNS = "profiles/bench_7b_layer_lmhead_32k_hbm_traffic.txt"
 MEASURED_TRAFFIC = {      # kernel symbol -> (bytes per launch, file under profiles/)
-    "gemm_mfma_k<false, false, 3>": (1.374e9, "profiles/bench_7b_layer_lmhead_32k_hbm_traffic.txt"),
+    "gemm_mfma_k<false, false, 1>": (1.405e9, TRAFFIC_RUNS),
+    "gemm_mfma_k<false, true, 7>": (4.785e9, TRAFFIC_RUNS),
+    "gemm_mfma_seg_k": (49.70e9, TRAFFIC_RUNS),
 }
 
 

@@ -542,7 +542,7 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
       if (SPLIT || grp == 0) AT_WAIT_VM(PIECES * V_AHEAD);
       AT_SLOT_BARRIER();
     };
-    // whole groups of four steps (a step past the last tile is two barriers and nothing else)
+    // whole groups of four steps (a step past the last tile loads that tile again, which keeps the wait counts, and passes its barriers)
     int i = 0;
     for (; i < n_it; i += 4) {
       step(i, 0);
@@ -996,7 +996,7 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
         AT_SLOT_BARRIER();
       };
       int j = 0;
-      for (; j < n_iter; j += 4) {      // (a step past the last tile is two barriers and nothing else)
+      for (; j < n_iter; j += 4) {      // (a step past the last tile loads that tile again and passes its barriers)
         step(j, 0);
         step(j + 1, 1);
         step(j + 2, 2);

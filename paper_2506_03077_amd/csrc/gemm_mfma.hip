@@ -176,7 +176,7 @@ struct KSegment {
 // went out: nothing stalls).
 // What bounds it: the matrix pipe at its power-limited clock.  8192^3 bf16, same box: NT 1265 -> 1556, NN 1256 -> 1546, TN 1199
 // -> 1440 TFLOP/s (vendor library 1614 / 1390 / 1202); half of the gain is the slot schedule (1410 with 32x32x16 MFMAs), half the
-// 16x16x32 MFMA, whose operands toggle less: 2.09 PFLOP/s of it sustain on random data against 1.82 of the 32x32x16.
+// 16x16x32 MFMA.  With the wait for B0, on another box: 1559 / 1459 / 1329 (library 1550 / 1327 / 1180).
 // The TN form is closest to the LDS limit (transposing reads of both operands).
 // No vector-ALU address work: global addresses are an SGPR base plus per-lane offsets computed once, LDS fragment
 // addresses are computed once and reached with immediate offsets.

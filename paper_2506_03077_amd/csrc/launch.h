@@ -23,8 +23,8 @@ struct GemmArgs {
   // dW form): the kernels read it at run time and skip the work beyond it; the host-side M (resp. K) is the
   // upper bound the launch is sized for.
   const int* rows_dev = nullptr;
-  // Optional second operand pair of the same shapes and leading dimensions: C (=|+=) A B + A2 B2 in one launch
-  // (the two products become the two slices of a split-K launch; falls back to two launches where that does not fit).
+  // Optional second operand pair of the same shapes and leading dimensions: C (=|+=) A B + A2 B2 in one launch, as one reduction of
+  // twice the length (split over workgroups or not); two launches where the MFMA kernel cannot take it.
   const void* A2 = nullptr;
   const void* B2 = nullptr;
   // Optional row statistics of the output (store form C = A B^T with fp32 C, MFMA kernel only: ask

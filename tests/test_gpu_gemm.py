@@ -73,8 +73,8 @@ def test_mfma_split_k_eight_ways_and_unaligned_groups():
 
 
 def test_two_operand_pairs_in_one_launch():
-    # C = A B + A2 B2 (the shape of dm = dgate W_g + dup W_u): the two products are the two slices of one split-K launch;
-    # where that does not fit (no scratch, odd shapes) the dispatcher runs them one after the other
+    # C = A B + A2 B2 (the shape of dm = dgate W_g + dup W_u): one reduction of twice the length in one launch (with slices across the
+    # pairs' boundary: test_gpu_gemm_edges.py); odd shapes run one after the other
     rng = np.random.default_rng(12)
     for (M, N, K, scratch_ok, expect) in ((300, 512, 1024, True, 1), (300, 512, 1024, False, 1), (70, 45, 33, True, 0)):
         A, A2 = (synth.to_storage(rng.normal(size=(M, K)), "bf16") for _ in range(2))
@@ -146,7 +146,7 @@ def test_mfma_segmented_weight_gradient():
 def test_weight_gradient_into_bf16_accumulator():
     # C (bf16) += A^T B: read, add in fp32, round once
     run(512, 768, 320, True, False, out="bf16", acc=True, expect_mfma=True, seed=6)     # one launch, ragged reduction
-    run(512, 256, 2048, True, False, out="bf16", acc=True, expect_mfma=True, seed=7)    # split-K, reduced into the bf16 C
+    run(512, 256, 2048, True, False, out="bf16", acc=True, expect_mfma=True, seed=7)    # a longer reduction (this form is never split)
     run(130, 172, 64, True, False, out="bf16", acc=True, expect_mfma=False, seed=8)     # shape-agnostic kernel
     rng = np.random.default_rng(9)
     M, N, Ks = 512, 256, (300, 200)
