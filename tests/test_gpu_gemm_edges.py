@@ -87,15 +87,13 @@ def test_rows_of_c_that_start_between_16_byte_boundaries(M, N, K, ta, tb, acc):
 
 # (M, N, K, layout, accumulate, tiles, splits): as many ways as the scratch of a whole chip lets the schedule take.  27 slices of 5
 # K steps leave two of 128 steps (one slice ragged, one empty); 15 of 13 leave the last with 10; 27 of 125 ragged steps two empty ones.
-@pytest.mark.parametrize("M,N,K,layout,acc,tiles,splits", [
-    (256, 256, 8192, "nt", False, 1, 27), (40, 256, 8192, "nn", False, 1, 27), (40, 264, 8192, "nt", True, 2, 27),
-    (512, 1024, 12288, "nt", False, 8, 15), (264, 256, 7993, "tn", True, 2, 27)])
-@pytest.mark.parametrize("out", ["f32", "bf16"])
+@pytest.mark.parametrize("M,N,K,layout,acc,tiles,splits,out", [
+    (256, 256, 8192, "nt", False, 1, 27, "f32"), (256, 256, 8192, "nt", False, 1, 27, "bf16"), (40, 256, 8192, "nn", False, 1, 27, "f32"),
+    (40, 256, 8192, "nn", False, 1, 27, "bf16"), (40, 264, 8192, "nt", True, 2, 27, "f32"), (512, 1024, 12288, "nt", False, 8, 15, "f32"),
+    (512, 1024, 12288, "nt", False, 8, 15, "bf16"), (264, 256, 7993, "tn", True, 2, 27, "f32")])
 def test_reductions_split_more_than_eight_ways(M, N, K, layout, acc, tiles, splits, out):
     import torch
     from paper_2506_03077_amd import binding as sb
-    if acc and out == "bf16":
-        pytest.skip("bf16 accumulators are added to by whole tiles")
     A, B, want = _operands(M, N, K, layout == "tn", layout == "nt")
     scratch = torch.full((256 * 256 * 256,), float("nan"), device="cuda")
     C = torch.ones((M, N), dtype=torch.float32 if out == "f32" else torch.bfloat16, device="cuda")
