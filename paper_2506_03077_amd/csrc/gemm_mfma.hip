@@ -174,9 +174,9 @@ struct KSegment {
 // multiply slot after their fetch.  B0 is fetched a phase early (phase 3, used in phase 0 of the next K step), where group 1 would
 // wait for it in the very slot in which group 0 refills it: phase 0 therefore opens with a wait for it (two slots after the reads
 // went out: nothing stalls).
-// What bounds it: the matrix pipe at its power-limited clock.  8192^3 bf16, same box: NT 1265 -> 1556, NN 1256 -> 1546, TN 1199
+// What bounds it: the matrix pipe at its power-limited clock.  8192^3 bf16, same card: NT 1265 -> 1556, NN 1256 -> 1546, TN 1199
 // -> 1440 TFLOP/s (vendor library 1614 / 1390 / 1202); half of the gain is the slot schedule (1410 with 32x32x16 MFMAs), half the
-// 16x16x32 MFMA.  With the wait for B0, on another box: 1559 / 1459 / 1329 (library 1550 / 1327 / 1180).
+// 16x16x32 MFMA.  With the wait for B0, on another card: 1559 / 1459 / 1329 (library 1550 / 1327 / 1180).
 // The TN form is closest to the LDS limit (transposing reads of both operands).
 // No vector-ALU address work: global addresses are an SGPR base plus per-lane offsets computed once, LDS fragment
 // addresses are computed once and reached with immediate offsets.
