@@ -351,7 +351,8 @@ int32_t layer_backward_impl(const sbp_layer_cfg* c, const sbp_layer_weights* w, 
       aa.window = c->window; aa.kv_first = kv_first;
       aa.q = s.q; aa.k = s.K; aa.v = s.V; aa.o = s.o; aa.lse = s.lse;
       aa.d_o = s.d_o; aa.dq = s.dq; aa.dk = s.dK; aa.dv = s.dV; aa.delta = s.delta;
-      aa.dkv_scratch = s.gemm_scratch; aa.dkv_scratch_bytes = s.gemm_scratch_bytes;      // (idle between GEMMs)
+      if (dt == DT_BF16) aa.dkv_slices = attn_dkv_slices(aa, s.gemm_scratch_bytes);
+      if (aa.dkv_slices > 1) aa.dkv_scratch = s.gemm_scratch;                                   // (idle between GEMMs)
       if (fusion_mask() & FUSE_ROPE_Q) aa.rope_q = s.rope + (size_t)r0 * half;   // dq leaves the kernel rotated back (RoPE's adjoint)
       HIPCHK(attn_backward(aa, st));
       if (!(fusion_mask() & FUSE_ROPE_Q)) HIPCHK(rope_apply(dt, s.dq, s.rope + (size_t)r0 * half, n, c->n_q_heads, c->head_dim, true, st));
@@ -728,9 +729,20 @@ static int32_t check_attn_cfg(const sbp_attn_cfg* c) {
   return SBP_OK;
 }
 
+// delta and log-sum-exp of the chunk's (query, head) pairs: what the backward cannot do without
+static size_t attn_stats_bytes(const sbp_attn_cfg* c) { return align_up((size_t)2 * std::max(c->q_len, 1) * c->n_q_heads * sizeof(float), 256); }
+static AttnArgs attn_args(const sbp_attn_cfg* c) {
+  AttnArgs a{};
+  a.dt = c->dtype; a.Hq = c->n_q_heads; a.Hkv = c->n_kv_heads; a.dh = c->head_dim;
+  a.q_start = c->q_start; a.q_len = c->q_len; a.scale = c->scale; a.window = c->window; a.kv_first = c->kv_first;
+  if (c->dtype == SBP_BF16 && (c->head_dim == 128 || c->head_dim == 64)) a.dkv_slices = attn_dkv_slices(a, SIZE_MAX);
+  return a;
+}
+
 size_t streambp_attn_workspace_bytes(const sbp_attn_cfg* cfg) {
   if (check_attn_cfg(cfg) != SBP_OK) return 0;
-  return align_up((size_t)2 * std::max(cfg->q_len, 1) * cfg->n_q_heads * sizeof(float), 256);
+  const AttnArgs a = attn_args(cfg);
+  return attn_stats_bytes(cfg) + align_up(attn_dkv_scratch_bytes(a, a.dkv_slices), 256);
 }
 
 int32_t streambp_attn_chunk_forward(const sbp_attn_cfg* c, const void* q, const void* k, const void* v, void* o,
@@ -739,9 +751,7 @@ int32_t streambp_attn_chunk_forward(const sbp_attn_cfg* c, const void* q, const 
   if (rc) return rc;
   if (c->q_len == 0) return SBP_OK;   // empty chunk: nothing to do
   if (!q || !k || !v || !o || !lse) return fail(SBP_ERR_NULL, "q, k, v, o and lse must be non-NULL");
-  AttnArgs a{};
-  a.dt = c->dtype; a.Hq = c->n_q_heads; a.Hkv = c->n_kv_heads; a.dh = c->head_dim;
-  a.q_start = c->q_start; a.q_len = c->q_len; a.scale = c->scale; a.window = c->window; a.kv_first = c->kv_first;
+  AttnArgs a = attn_args(c);
   a.q = q; a.k = k; a.v = v; a.o = o; a.lse = lse;
   HIPCHK(attn_forward(a, (hipStream_t)hip_stream));
   return SBP_OK;
@@ -756,10 +766,10 @@ int32_t streambp_attn_chunk_backward(const sbp_attn_cfg* c, const void* q, const
   if (!q || !k || !v || !o || !lse || !d_o || !dq || !dk || !dv || !workspace)
     return fail(SBP_ERR_NULL, "all tensor pointers and workspace must be non-NULL");
   if ((uintptr_t)workspace & 255) return fail(SBP_ERR_WORKSPACE, "workspace must be 256-byte aligned");
-  if (workspace_bytes < streambp_attn_workspace_bytes(c)) return fail(SBP_ERR_WORKSPACE, "workspace too small");
-  AttnArgs a{};
-  a.dt = c->dtype; a.Hq = c->n_q_heads; a.Hkv = c->n_kv_heads; a.dh = c->head_dim;
-  a.q_start = c->q_start; a.q_len = c->q_len; a.scale = c->scale; a.window = c->window; a.kv_first = c->kv_first;
+  if (workspace_bytes < attn_stats_bytes(c)) return fail(SBP_ERR_WORKSPACE, "workspace too small");
+  AttnArgs a = attn_args(c);
+  // with less than the query's bytes the same slices run one after the other: the same results
+  if (a.dkv_slices > 1 && workspace_bytes >= streambp_attn_workspace_bytes(c)) a.dkv_scratch = (float*)((char*)workspace + attn_stats_bytes(c));
   a.q = q; a.k = k; a.v = v; a.o = (void*)o; a.lse = (float*)lse;
   a.d_o = d_o; a.dq = dq; a.dk = dk; a.dv = dv; a.delta = (float*)workspace;
   HIPCHK(attn_backward(a, (hipStream_t)hip_stream));
@@ -828,9 +838,7 @@ int32_t streambp_attn_chunk_backward_noalloc(const sbp_attn_cfg* c, const void* 
     }
     scratch = g_static_scratch_ptr[dev];
   }
-  AttnArgs a{};
-  a.dt = c->dtype; a.Hq = c->n_q_heads; a.Hkv = c->n_kv_heads; a.dh = c->head_dim;
-  a.q_start = c->q_start; a.q_len = c->q_len; a.scale = c->scale; a.window = c->window; a.kv_first = c->kv_first;
+  AttnArgs a = attn_args(c);
   a.q = q; a.k = k; a.v = v; a.o = (void*)o; a.lse = (float*)lse;
   a.d_o = d_o; a.dq = dq; a.dk = dk; a.dv = dv; a.delta = scratch;
   HIPCHK(attn_backward(a, (hipStream_t)hip_stream));

@@ -53,10 +53,9 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 constexpr int AT_THREADS = 512;          // 8 waves (forward, dQ): 2 per SIMD
 constexpr int TQ = ATTN_TILE_Q;          // queries per workgroup (fwd, dQ): 8 waves x 32
 constexpr int TK = ATTN_TILE_K;          // 64 keys per step (fwd, dQ)
-constexpr int KV_TILE = 128;             // keys per workgroup (dK/dV): 4 key blocks x 2 roles = 8 waves
+constexpr int KV_TILE = ATTN_KV_TILE;    // keys per workgroup (dK/dV): 4 key blocks x 2 roles = 8 waves
 constexpr int KV_THREADS = 512;
-constexpr int QT = 64;                   // queries per step (dK/dV)
-constexpr int DKV_MIN_STEPS = 4;         // query tiles that make a workgroup of its own worth while (dK/dV)
+constexpr int QT = ATTN_KV_QUERIES;      // queries per step (dK/dV)
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
 
@@ -803,7 +802,7 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
                                                                   const float* __restrict__ lse2, const float* __restrict__ delta,
                                                                   float* __restrict__ dk, float* __restrict__ dv, int Hq, int Hkv,
                                                                   int q_start, int c, float scale, int window, int kv_first,
-                                                                  int key_block0, float* __restrict__ part) {
+                                                                  int key_block0, int slices, float* __restrict__ part) {
   __shared__ __attribute__((aligned(1024))) char sQD[2][KV_STAGES][TILE64<DH>];   // [Q | dO][stage]
   // P of the tile, [key block][slot][lane]: bf16, slot = query block * 2 + k16 step; FP32_STATS: fp32, slot = query block * 4 + r / 4
   __shared__ __attribute__((aligned(16))) bf16x8 sP[4][FP32_STATS<DH> ? 8 : 4][64];
@@ -849,9 +848,12 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
   int n_qt = (c + QT - 1) / QT;
   if (window > 0) n_qt = min(n_qt, max(0, key0 + KV_TILE - 1 + window - 1 - q_start) / QT + 1);
   const int n_all = max(0, n_qt - qt_first) * G;
-  const int it0 = (int)((int64_t)n_all * blockIdx.z / gridDim.z), n_iter = (int)((int64_t)n_all * (blockIdx.z + 1) / gridDim.z) - it0;   // this workgroup's share
+  // The steps come in `slices` shares: a workgroup each where there is room for the parts, one after the other in this one
+  // otherwise (the same sums in the same order: bit-identical results).
+  for (int z = part ? (int)blockIdx.z : 0, z_end = part ? z + 1 : slices; z < z_end; ++z) {
+  const int it0 = (int)((int64_t)n_all * z / slices), n_iter = (int)((int64_t)n_all * (z + 1) / slices) - it0;
 
-  // Loads of this workgroup's next tile (query tile lq, head lh of the group); past the end the last one again, so that the wait counts
+  // Loads of this share's next tile (query tile lq, head lh of the group); past the end the last one again, so that the wait counts
   // stay the same.
   int lq = qt_first + it0 / G, lh = it0 % G, left = n_iter;
   auto issue = [&](int stage) {
@@ -1009,7 +1011,7 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
     if (my_key < n_total) {
       // several workgroups per key block: each leaves its sum in its own slice [workgroup][dk | dv][key][kv head][DH]
       const int64_t first = (int64_t)key_block0 * KV_TILE;
-      float* out = part ? part + ((int64_t)blockIdx.z * 2 + (RP ? 1 : 0)) * (n_total - first) * kv_stride + (my_key - first) * kv_stride + (int64_t)kvh * DH
+      float* out = part ? part + ((int64_t)z * 2 + (RP ? 1 : 0)) * (n_total - first) * kv_stride + (my_key - first) * kv_stride + (int64_t)kvh * DH
                         : (RP ? dv : dk) + (int64_t)my_key * kv_stride + (int64_t)kvh * DH;
       const float f = RP ? 1.0f : scale;
 #pragma unroll
@@ -1018,13 +1020,18 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
         for (int a = 0; a < 4; ++a) {
           const int d0 = i * 32 + 8 * a + 4 * half;
           float4 u = part ? make_float4(0.f, 0.f, 0.f, 0.f) : *(float4*)(out + d0);
-          u.x += acc[i][4 * a + 0] * f; u.y += acc[i][4 * a + 1] * f; u.z += acc[i][4 * a + 2] * f; u.w += acc[i][4 * a + 3] * f;
+          {
+#pragma clang fp contract(off)      // product and sum rounded separately, with or without parts
+            u.x += acc[i][4 * a + 0] * f; u.y += acc[i][4 * a + 1] * f; u.z += acc[i][4 * a + 2] * f; u.w += acc[i][4 * a + 3] * f;
+          }
           *(float4*)(out + d0) = u;
         }
     }
   };
   if (role_p) run(std::true_type{});
   else run(std::false_type{});
+  if (z + 1 < z_end) __syncthreads();      // the next share loads into the stages of this one
+  }
 }
 
 // dk / dv += sum over the slices of the split form, in their order.  n4: float4s of dk (and of dv)
@@ -1070,7 +1077,7 @@ static bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 // the MFMA kernels move 16 bytes per lane: every tensor they touch must be 16-byte aligned
 bool attn_mfma_aligned(const AttnArgs& a, bool backward) {
-  if (!aligned16(a.q) || !aligned16(a.k) || !aligned16(a.v) || !aligned16(a.o) || ((uintptr_t)a.rope_q & 7)) return false;
+  if (!aligned16(a.q) || !aligned16(a.k) || !aligned16(a.v) || !aligned16(a.o) || !aligned16(a.dkv_scratch) || ((uintptr_t)a.rope_q & 7)) return false;
   return !backward || (aligned16(a.d_o) && aligned16(a.dq) && aligned16(a.dk) && aligned16(a.dv));
 }
 
@@ -1107,23 +1114,17 @@ static hipError_t backward_dh(const AttnArgs& a, hipStream_t st) {
   else launch_dq(attn_bwd_dq_mfma_k<DH, false>, cdiv(a.q_len, TQ));
   // key blocks that no query of the chunk can see (before the padding ends, or older than the first query's window)
   // are not launched: their dK/dV contribution is zero
-  const int first_visible = std::max(a.kv_first, a.window > 0 ? a.q_start - a.window + 1 : 0);
-  const int kb0 = std::max(0, first_visible) / KV_TILE, kb1 = (int)cdiv(a.q_start + a.q_len, KV_TILE);
+  const int kb0 = attn_first_key_block(a), kb1 = (int)cdiv(a.q_start + a.q_len, KV_TILE);
   if (kb1 > kb0) {
-    // Fewer key blocks than CUs (short sequences): the query tiles of a block are dealt to as many workgroups as fill the chip, at
-    // least DKV_MIN_STEPS tiles each (a workgroup's own sum is 128 KB to write and read again, about one tile's time).
-    const int64_t blocks = (int64_t)(kb1 - kb0) * a.Hkv, steps = cdiv(a.q_len, QT) * (a.Hq / a.Hkv);
     const int64_t first = (int64_t)kb0 * KV_TILE, n = (a.q_start + a.q_len - first) * a.Hkv * DH;
-    int64_t split = std::min<int64_t>(256 / blocks, steps / DKV_MIN_STEPS);
-    if (!a.dkv_scratch || ((uintptr_t)a.dkv_scratch & 15)) split = 1;
-    else split = std::min<int64_t>(split, (int64_t)(a.dkv_scratch_bytes / (2 * n * sizeof(float))));
-    if (split < 2) split = 1;
-    dim3 gk((unsigned)(kb1 - kb0), a.Hkv, (unsigned)split);
+    const int slices = std::max(1, a.dkv_slices);
+    float* part = slices > 1 ? a.dkv_scratch : nullptr;
+    dim3 gk((unsigned)(kb1 - kb0), a.Hkv, part ? (unsigned)slices : 1u);
     attn_bwd_dkv_mfma_k<DH><<<gk, KV_THREADS, 0, st>>>((const bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v, (const bf16_t*)a.d_o,
                                                    lse2, a.delta, a.dk, a.dv, a.Hq, a.Hkv, a.q_start, a.q_len, a.scale,
-                                                   a.window, a.kv_first, kb0, split > 1 ? a.dkv_scratch : nullptr);
-    if (split > 1)
-      attn_dkv_sum_k<<<(unsigned)cdiv(n / 2, 256), 256, 0, st>>>((const float4*)a.dkv_scratch, (int)split, n / 4,
+                                                   a.window, a.kv_first, kb0, slices, part);
+    if (part)
+      attn_dkv_sum_k<<<(unsigned)cdiv(n / 2, 256), 256, 0, st>>>((const float4*)part, slices, n / 4,
                                                                   (float4*)(a.dk + first * a.Hkv * DH), (float4*)(a.dv + first * a.Hkv * DH));
   }
   return hipGetLastError();

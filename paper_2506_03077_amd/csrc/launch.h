@@ -149,9 +149,10 @@ struct AttnArgs {
   void* o; float* lse;     // o [c,Hq,dh]; lse [Hq,c]
   const void* d_o; void* dq; float *dk, *dv;
   float* delta;            // [2,Hq,c] scratch (backward): delta, then the log2-domain log-sum-exp
-  // Optional fp32 scratch (backward, 16-byte aligned): lets short sequences deal the queries of a key block to several workgroups
+  // dK/dV: slices that the queries of a key block are cut into (attn_dkv_slices), and the optional fp32 scratch (16-byte aligned,
+  // attn_dkv_scratch_bytes) that lets a workgroup take each
+  int dkv_slices = 1;
   float* dkv_scratch = nullptr;
-  size_t dkv_scratch_bytes = 0;
   // Optional rotary embedding of the chunk's queries folded into the attention kernels: cos/sin rows [c, dh/2] of the
   // chunk's positions.  Forward: q arrives un-rotated, is rotated on load and written back rotated (q must then be
   // writable); backward: q is the rotated tensor the forward left, and dq leaves the kernel already rotated back
@@ -165,6 +166,38 @@ void attn_set_force_generic(bool on);
 constexpr int ATTN_TILE_Q = 256;   // rows of queries per workgroup in the MFMA kernels (8 waves x 32 rows)
 constexpr int ATTN_WAVE_Q = 32;    // rows of queries per wave: the granularity at which key tiles are skipped
 constexpr int ATTN_TILE_K = 64;    // keys per inner step
+constexpr int ATTN_KV_TILE = 128;  // dK/dV: keys per workgroup
+constexpr int ATTN_KV_QUERIES = 64;   // dK/dV: queries per step
+
+// dK/dV of the MFMA kernels: one workgroup per 128 keys and K/V head walks the query tiles of the group's heads.  Where these are not whole
+// rounds of the 256 CUs the walk is cut into slices, a workgroup each: their sums meet in scratch, in a fixed order.  The number of
+// slices is a property of the sizes - without the scratch one workgroup walks them in turn - so the results of the attention entry
+// points do not depend on the scratch.  Cost of s slices in steps (one step, 64 queries, takes about 1.9 us): the rounds, each with the share's steps and about
+// three more for a workgroup's start and the 128 KB that it leaves, and the pass that adds the parts (2 us, 4 TB/s).
+// max_bytes bounds the scratch that the slices need.
+inline int attn_first_key_block(const AttnArgs& a) {
+  const int first_visible = a.window > 0 && a.q_start - a.window + 1 > a.kv_first ? a.q_start - a.window + 1 : a.kv_first;
+  return (first_visible > 0 ? first_visible : 0) / ATTN_KV_TILE;
+}
+constexpr int ATTN_MAX_SLICES = 32;
+inline size_t attn_dkv_scratch_bytes(const AttnArgs& a, int slices) {      // [slice][dk | dv][key][kv head][dh] fp32, keys from the first visible block on
+  const int64_t keys = (int64_t)a.q_start + a.q_len - (int64_t)attn_first_key_block(a) * ATTN_KV_TILE;
+  return slices < 2 || keys <= 0 ? 0 : (size_t)(slices * 2 * keys * a.Hkv * a.dh) * sizeof(float);
+}
+inline int attn_dkv_slices(const AttnArgs& a, size_t max_bytes) {
+  const int64_t blocks = (cdiv((int64_t)a.q_start + a.q_len, ATTN_KV_TILE) - attn_first_key_block(a)) * a.Hkv;
+  if (blocks <= 0) return 1;
+  int64_t tiles = cdiv(a.q_len, ATTN_KV_QUERIES);
+  if (a.window > 0 && tiles > cdiv((int64_t)a.window + ATTN_KV_TILE, ATTN_KV_QUERIES) + 1) tiles = cdiv((int64_t)a.window + ATTN_KV_TILE, ATTN_KV_QUERIES) + 1;
+  const int64_t steps = tiles * (a.Hq / a.Hkv);
+  int best = 1;
+  double best_cost = 0.0;
+  for (int s = 1; s == 1 || (s <= ATTN_MAX_SLICES && blocks * s <= 512 && steps / s >= 2 && attn_dkv_scratch_bytes(a, s) <= max_bytes); ++s) {
+    const double cost = (double)cdiv(blocks * s, 256) * (double)(cdiv(steps, s) + 3) + (s > 1 ? 1.0 + 0.02 * (double)(blocks * s) : 0.0);
+    if (s == 1 || cost < best_cost) { best = s; best_cost = cost; }
+  }
+  return best;
+}
 
 // ---- LM head rows ----
 struct HeadRowArgs {

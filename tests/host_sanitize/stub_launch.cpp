@@ -133,7 +133,7 @@ static void touch_attn(const AttnArgs& a, bool bwd) {
   if (!bwd) { wr(a.o, qn * es(a.dt)); wr(a.lse, (size_t)a.Hq * a.q_len * 4); return; }
   rd(a.o, qn * es(a.dt)); rd(a.lse, (size_t)a.Hq * a.q_len * 4); rd(a.d_o, qn * es(a.dt)); wr(a.dq, qn * es(a.dt));
   wr(a.dk, kn * 4); wr(a.dv, kn * 4); wr(a.delta, (size_t)2 * a.Hq * a.q_len * 4);
-  if (a.dkv_scratch) wr(a.dkv_scratch, a.dkv_scratch_bytes);     // the parts of split key blocks
+  if (a.dkv_scratch) wr(a.dkv_scratch, attn_dkv_scratch_bytes(a, a.dkv_slices));     // the parts of split key blocks
 }
 hipError_t attn_forward(const AttnArgs& a, hipStream_t) { if (a.q_len > 0) touch_attn(a, false); return hipSuccess; }
 hipError_t attn_backward(const AttnArgs& a, hipStream_t) { if (a.q_len > 0) touch_attn(a, true); return hipSuccess; }
