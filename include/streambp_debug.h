@@ -54,6 +54,13 @@ int streambp_debug_gemm_dw_segments(int n, int M, int N, const int *K, const voi
                                     const int *const *rows_dev, void *C, long long lda, long long ldb, long long ldc,
                                     int in_dt, int out_dt, void *hip_stream);
 
+/* The kernels for outputs of few tiles, which the layer entry points use where they are the faster ones, with a given output tile
+ * (tile_m x tile_n: 128 x 128, 128 x 64 or 64 x 64): C[M,N] (fp32 or bf16, row stride ldc) = sum over n <= 3 of A[i] B[i], A[i]
+ * dense [M, K[i]], B[i] dense [N, K[i]] (tb) or [K[i], N], all bf16; host arrays of device pointers.  Returns 1, 0 if these kernels do not
+ * take the problem (nothing is written then), negative on error. */
+int streambp_debug_gemm_few(int n, int M, int N, const int *K, int tb, int out_dt, const void *const *A, const void *const *B,
+                            void *C, long long ldc, int tile_m, int tile_n, void *hip_stream);
+
 /* Per-launch timing with HIP events recorded on the launch stream around each GEMM kernel / attention launch sequence.
  * begin: CREATES 2*max_records events, allocates host records and switches recording on (returns 0; -1 if already on).
  * end: synchronises the events, fills the caller's host arrays of streambp_debug_profile_kinds() entries (launch count,

@@ -143,6 +143,9 @@ def lib():
         L.streambp_debug_gemm_dw_segments.restype = C.c_int
         L.streambp_debug_gemm_dw_segments.argtypes = [C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int), C.POINTER(vp), C.POINTER(vp),
                                                       C.POINTER(vp), vp, C.c_longlong, C.c_longlong, C.c_longlong, C.c_int, C.c_int, vp]
+        L.streambp_debug_gemm_few.restype = C.c_int
+        L.streambp_debug_gemm_few.argtypes = [C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int), C.c_int, C.c_int, C.POINTER(vp), C.POINTER(vp),
+                                              vp, C.c_longlong, C.c_int, C.c_int, vp]
         L.streambp_debug_profile_begin.restype = C.c_int
         L.streambp_debug_profile_begin.argtypes = [C.c_int]
         L.streambp_debug_profile_end.restype = C.c_int
@@ -476,6 +479,16 @@ def debug_gemm_dw_segments(As, Bs, C_out, M, N, Ks, rows_dev=None, stream=None):
     return rc
 
 
+def debug_gemm_few(As, Bs, C_out, tb, tile, stream=None):
+    """C_out [M,N] = sum_s As[s] op(Bs[s]) by the kernels for outputs of few tiles with output tile `tile`; 1, or 0 if they do not take it."""
+    n, (M, N) = len(As), C_out.shape
+    rc = lib().streambp_debug_gemm_few(n, M, N, (C.c_int * n)(*[a.shape[1] for a in As]), int(tb), _dt_code(C_out), (C.c_void_p * n)(*[_ptr(a) for a in As]),
+                                       (C.c_void_p * n)(*[_ptr(b) for b in Bs]), C_out.data_ptr(), C_out.stride(0), tile[0], tile[1], _stream(stream))
+    if rc < 0:
+        raise StreamBPError(rc, "debug_gemm_few launch failed")
+    return rc
+
+
 def debug_gemm_numerators(A, B, E, stats, targets, target_value, row_index=None, stream=None):
     """E (bf16 [M,N]) = exp(A B^T - block max), stats [M, ceil(N/256), 2], target_value [M] (see streambp_debug.h).  Returns 1
     if the MFMA kernel ran."""
@@ -516,7 +529,7 @@ def _profile_kind_names():
     names = [f"gemm_mfma_k<{t}, {m}>" for t, _ in lay for m in range(4)]
     names += [f"gemm_mfma_group_k<{t}, {m}>" for t, _ in lay for m in range(4)]
     names += ["gemm_generic_k", "attn_fwd (launch sequence)", "attn_bwd (delta + dq + dkv launch sequence)", "gemm_mfma_seg_k",
-              "gemm_mfma_k<false, true, 5>", "gemm_mfma_k<false, false, 6>", "gemm_mfma_k<false, true, 7>"]
+              "gemm_mfma_k<false, true, 5>", "gemm_mfma_k<false, false, 6>", "gemm_mfma_k<false, true, 7>", "gemm_few_k"]
     return tuple(names)
 
 

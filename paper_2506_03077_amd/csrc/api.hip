@@ -177,6 +177,7 @@ GemmArgs mk(const void* A, const void* B, void* C, int M, int N, int K, int64_t 
   GemmArgs g{A, B, C, M, N, K, lda, ldb, ldc, ta, tb, in_dt, out_dt, acc};
   g.scratch = t_gemm_scratch;
   g.scratch_bytes = t_gemm_scratch_bytes;
+  g.few_ok = true;
   return g;
 }
 // Y[M,N] = X[M,K] W[N,K]^T
@@ -356,14 +357,13 @@ int32_t layer_backward_impl(const sbp_layer_cfg* c, const sbp_layer_weights* w, 
       if (fusion_mask() & FUSE_ROPE_Q) aa.rope_q = s.rope + (size_t)r0 * half;   // dq leaves the kernel rotated back (RoPE's adjoint)
       HIPCHK(attn_backward(aa, st));
       if (!(fusion_mask() & FUSE_ROPE_Q)) HIPCHK(rope_apply(dt, s.dq, s.rope + (size_t)r0 * half, n, c->n_q_heads, c->head_dim, true, st));
-      HIPCHK(gemm(dx_gemm(s.dq, w->wq, s.da, n, qd, d, dt, DT_F32, false), st));
       // ---- K/V side of rows [r0, r0+n): final now
       HIPCHK(kv_grad_finish(dt, s.dK + (size_t)r0 * kd, s.dV + (size_t)r0 * kd, s.rope + (size_t)r0 * half, s.dkc, s.dvc,
                             n, c->n_kv_heads, c->head_dim, st));
-      {   // da += dkc W_k + dvc W_v: same output, one launch with two reduction segments
-        const GemmArgs kv[2] = {dx_gemm(s.dkc, w->wk, s.da, n, kd, d, dt, DT_F32, true),
-                                dx_gemm(s.dvc, w->wv, s.da, n, kd, d, dt, DT_F32, true)};
-        HIPCHK(gemm_batch(kv, 2, st));
+      {   // da = dq W_q + dkc W_k + dvc W_v
+        const GemmArgs qkv[3] = {dx_gemm(s.dq, w->wq, s.da, n, qd, d, dt, DT_F32, false), dx_gemm(s.dkc, w->wk, s.da, n, kd, d, dt, DT_F32, true),
+                                 dx_gemm(s.dvc, w->wv, s.da, n, kd, d, dt, DT_F32, true)};
+        HIPCHK(gemm_sum(qkv, 3, st));
       }
       if (!lora) {
         // ---- the seven weight gradients of the chunk, dW += dY^T X (Eq. 1 summand): queued, and launched together

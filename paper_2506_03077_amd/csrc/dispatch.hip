@@ -20,6 +20,9 @@ bool gemm_mfma_group_eligible(const GemmArgs* gs, int n, bool small_ok);
 hipError_t gemm_mfma_group(const GemmArgs* gs, int n, hipStream_t st);
 bool gemm_mfma_seg_eligible(const GemmArgs* gs, int n);
 hipError_t gemm_mfma_seg(const GemmArgs* gs, int n, hipStream_t st);
+FewChoice gemm_few_choice(const GemmArgs* gs, int n, bool sum);
+hipError_t gemm_few(const GemmArgs* gs, int n, bool sum, int TM, int TN, hipStream_t st);
+double gemm_mfma_us(const GemmArgs* gs, int n);
 hipError_t attn_forward_generic(const AttnArgs& a, hipStream_t st);
 hipError_t attn_backward_generic(const AttnArgs& a, hipStream_t st);
 hipError_t attn_forward_mfma(const AttnArgs& a, hipStream_t st);
@@ -75,6 +78,15 @@ static double causal_pairs(const AttnArgs& a) {   // visible (query, key) pairs 
   return (double)a.Hq * pairs;
 }
 
+static hipError_t run_few(const GemmArgs* gs, int n, bool sum, const FewChoice& c, hipStream_t st) {
+  double work = 0.0;
+  for (int i = 0; i < n; ++i) work += 2.0 * gs[i].M * gs[i].N * gs[i].K * (gs[i].A2 ? 2 : 1);
+  prof::Scope sc(prof::GEMM_FEW, work, false, st);
+  return gemm_few(gs, n, sum, c.tm, c.tn, st);
+}
+// the kernels for outputs of few tiles, where their estimate is the lower one
+static bool few_is_faster(const FewChoice& c, double us) { return c.tm && c.us < us; }
+
 hipError_t gemm(const GemmArgs& g, hipStream_t st) {
   if (g.numer_targets) {
     if (!gemm_numerators_supported(g)) return hipErrorInvalidValue;               // only the MFMA store form has them
@@ -92,21 +104,43 @@ hipError_t gemm(const GemmArgs& g, hipStream_t st) {
     hipError_t e = gemm(first, st);
     return e != hipSuccess ? e : gemm(second, st);
   }
-  if (gemm_uses_mfma(g)) return gemm_mfma(g, st);      // times itself (it knows which kernel variant it launches)
+  if (gemm_uses_mfma(g)) {
+    const FewChoice few = gemm_few_choice(&g, 1, false);
+    if (few_is_faster(few, gemm_mfma_us(&g, 1))) return run_few(&g, 1, false, few, st);
+    return gemm_mfma(g, st);      // times itself (it knows which kernel variant it launches)
+  }
   if (g.in_dt == DT_BF16) ++g_generic_bf16_launches;
   prof::Scope sc(prof::GEMM_GENERIC, 2.0 * g.M * g.N * g.K, g.rows_dev != nullptr, st);
   return gemm_generic(g, st);
 }
 hipError_t gemm_batch(const GemmArgs* gs, int n, hipStream_t st, bool group_small) {
   if (!g_force_generic_gemm && gemm_mfma_seg_eligible(gs, n)) return gemm_mfma_seg(gs, n, st);   // same C: one pass over it
-  if (!g_force_generic_gemm && gemm_mfma_group_eligible(gs, n, group_small)) {
-    return gemm_mfma_group(gs, n, st);
+  const bool group = !g_force_generic_gemm && gemm_mfma_group_eligible(gs, n, group_small);
+  if (!g_force_generic_gemm) {
+    const FewChoice few = gemm_few_choice(gs, n, false);
+    if (few.tm) {
+      double us = 0.0;
+      if (group) us = gemm_mfma_us(gs, n);
+      else
+        for (int i = 0; i < n; ++i) us += std::min(gemm_few_choice(gs + i, 1, false).us, gemm_mfma_us(gs + i, 1));      // (all can take the first form)
+      if (few_is_faster(few, us)) return run_few(gs, n, false, few, st);
+    }
   }
+  if (group) return gemm_mfma_group(gs, n, st);
   for (int i = 0; i < n; ++i) {
     hipError_t e = gemm(gs[i], st);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
+}
+hipError_t gemm_sum(const GemmArgs* gs, int n, hipStream_t st) {
+  if (n > 1 && !g_force_generic_gemm) {
+    const FewChoice few = gemm_few_choice(gs, n, true);
+    // (the others as one launch that reads and writes C again)
+    if (few_is_faster(few, gemm_mfma_us(gs, 1) + gemm_mfma_us(gs + 1, 1) + 5.0)) return run_few(gs, n, true, few, st);
+  }
+  hipError_t e = gemm(gs[0], st);
+  return e != hipSuccess || n == 1 ? e : gemm_batch(gs + 1, n - 1, st);
 }
 hipError_t attn_forward(const AttnArgs& a, hipStream_t st) {
   prof::Scope sc(prof::ATTN_FWD, 4.0 * a.dh * causal_pairs(a), false, st);
@@ -153,6 +187,17 @@ extern "C" int streambp_debug_gemm(int M, int N, int K, int ta, int tb, int in_d
   g.row_stats = (float2*)row_stats;   // optional [M, N/256] (max, sum of exp) pairs
   hipError_t e = sbp::gemm(g, (hipStream_t)stream);
   return e == hipSuccess ? (sbp::gemm_uses_mfma(g) ? 1 : 0) : -5;
+}
+
+// The kernels for outputs of few tiles with a given tile (128 x 128, 128 x 64 or 64 x 64): C = sum of n <= 3 products over A[i] [M, K[i]] and B[i]
+// ([N, K[i]] if tb, else [K[i], N]), dense rows of A and B.  Returns 1, or 0 where they do not take the problem.
+extern "C" int streambp_debug_gemm_few(int n, int M, int N, const int* K, int tb, int out_dt, const void* const* A, const void* const* B, void* C,
+                                       long long ldc, int tile_m, int tile_n, void* stream) {
+  if (n < 1 || n > 3) return -2;
+  sbp::GemmArgs gs[3];
+  for (int i = 0; i < n; ++i) gs[i] = sbp::GemmArgs{A[i], B[i], C, M, N, K[i], K[i], tb ? K[i] : N, ldc, false, tb != 0, sbp::DT_BF16, out_dt, i > 0};
+  const hipError_t e = sbp::gemm_few(gs, n, true, tile_m, tile_n, (hipStream_t)stream);
+  return e == hipSuccess ? 1 : e == hipErrorInvalidValue ? 0 : -5;
 }
 
 // Weight-gradient form over several reduction segments through gemm_batch: C[M,N] += sum_s A_s^T B_s with

@@ -26,21 +26,12 @@
 //    numbered consecutively, so that an XCD holds one slice or a few.
 //  * Weight gradients: C += acc, fp32 or bf16 C; several reduction segments (operand pairs) per output tile; grouped launches.
 #include "launch.h"
-#include "device.h"
+#include "gemm_tile.h"
 
 #include <algorithm>
 #include <type_traits>
 
 namespace sbp {
-
-typedef bf16_t bf16x8 __attribute__((ext_vector_type(8)));
-typedef bf16_t bf16x4 __attribute__((ext_vector_type(4)));
-typedef short short4v __attribute__((ext_vector_type(4)));
-typedef short short8v __attribute__((ext_vector_type(8)));
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int BM = 256, BN = 256, BK = 64;
 constexpr int NWAVE_N = 4;                             // waves along N; the two waves along M are the two groups of the main loop
@@ -49,13 +40,6 @@ constexpr int HALF_BYTES = 128 * BK * 2;               // 16 KiB: 128 rows (colu
 constexpr int STAGE_BYTES = 2 * HALF_BYTES;            // one operand, one K step
 constexpr int OPERAND_BYTES = 2 * STAGE_BYTES;         // two K steps: 64 KiB, the reach of an LDS read's immediate offset
 constexpr int SMEM_BYTES = 2 * OPERAND_BYTES;          // [operand][K step parity][half]
-
-// ---- LDS layouts of a half tile.  K-contiguous operand: [128 rows][64 k], 128 B per row = 8 chunks of 16 B, chunk ^= (row>>1)&7:
-//      16 consecutive rows at one logical chunk cover all 64 banks exactly once.
-__device__ __forceinline__ int kmaj_swz(int row) { return (row >> 1) & 7; }
-// ---- reduction-major operand: [64 k][128 rows], 256 B per k-row = 8 groups of 32 B, group ^= f(krow): the 32 lanes of a
-//      transposing read touch k-rows {0..3, 8..11} (+ 4 or + 16) at one logical group; f tells those eight apart.
-__device__ __forceinline__ int mnmaj_swz(int krow) { return (krow & 3) | (((krow >> 3) & 1) << 2); }
 
 // Byte offset, relative to the tile's corner element, of load i (0, 1) of this thread's share of half h.
 //   KMAJ : corner = (row r0, column k0); rows clamped so that r0 + row <= r_max
@@ -89,59 +73,6 @@ __device__ __forceinline__ uint32_t frag_off_mnmaj(int col_base, int hi) {
   const int p16 = (((c16 >> 1) ^ mnmaj_swz(krow)) << 1) | (c16 & 1);
   return (uint32_t)(krow * 256 + (p16 << 4) + ((col & 7) << 1));
 }
-__device__ __forceinline__ bf16x8 lds_read_b128(uint32_t addr) {
-  return *(const bf16x8*)(__attribute__((address_space(3))) const char*)(uintptr_t)addr;
-}
-__device__ __forceinline__ bf16x8 lds_read_tr(uint32_t lo_addr, uint32_t hi_addr) {
-  short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v*)(uintptr_t)lo_addr);
-  short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v*)(uintptr_t)hi_addr);
-  short8v r = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-  return __builtin_bit_cast(bf16x8, r);
-}
-
-// Tile id -> (tile_m, tile_n): walk tiles in column bands of group_m row tiles so that the workgroups resident
-// together share A row panels and B column panels in their XCD's L2.
-__device__ __forceinline__ void band_coords(int id, int tiles_m, int tiles_n, int group_m, int& tm, int& tn) {
-  const int band = group_m * tiles_n;
-  const int g = id / band;
-  const int first_m = g * group_m;
-  const int gsz = min(tiles_m - first_m, group_m);
-  const int r = id % band;
-  tm = first_m + r % gsz;
-  tn = r / gsz;
-}
-// Band height.  With XCD-contiguous ids each XCD works on a run of n_tiles/8 consecutive ids, i.e. a block of
-// group_m rows x run/group_m columns of tiles; the fabric traffic of that XCD is proportional to rows + columns,
-// so the block is made as square as the problem allows.  (Interleaved ids, used by the accumulate form, give
-// every XCD one row of each band and all columns; 8 rows per band suit that.)
-__device__ __forceinline__ int band_height_for_run(int tiles_m, int run) {
-  int h = (int)(sqrtf((float)max(1, run)) + 0.5f);
-  return max(1, min(h, min(tiles_m, 8)));
-}
-__device__ __forceinline__ int band_height(int tiles_m, int n_tiles, bool xcd_contiguous) {
-  if (!xcd_contiguous) return 8;
-  return band_height_for_run(tiles_m, n_tiles / 8);
-}
-// Hardware deals consecutive workgroups round-robin to the 8 XCDs (each with its own L2); undo that so each
-// XCD gets a contiguous run of tile ids.  Measured: +3-4% for the store-only forms; the accumulate form is up to 3 % faster with
-// the hardware's interleaved order, so it keeps that.
-__device__ __forceinline__ int xcd_contiguous_id(int id, int n_tiles) {
-  constexpr int NXCD = 8;
-  const int x = id % NXCD, q = n_tiles / NXCD, r = n_tiles % NXCD;   // XCD x owns q (+1 if x < r) consecutive ids
-  return x * q + min(x, r) + id / NXCD;
-}
-
-// Counted wait / workgroup barrier of the main loop.  Inline assembly (with a memory clobber) so that the compiler neither adds
-// waits of its own nor moves LDS reads across; the scheduling barriers keep the machine scheduler from doing the same.
-#define WAIT_VMCNT(n) asm volatile("s_waitcnt vmcnt(%0)" ::"i"(n) : "memory")
-#define WAIT_LDS() asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory")
-#define SLOT_BARRIER()                        \
-  do {                                        \
-    __builtin_amdgcn_sched_barrier(0);        \
-    asm volatile("s_barrier" ::: "memory");   \
-    __builtin_amdgcn_sched_barrier(0);        \
-  } while (0)
-
 // One 256x256 output tile: K range [k_begin, k_end).
 // MODE: 0 = store fp32, 1 = store bf16, 2 = accumulate fp32 (C +=),
 //       4 = accumulate into a bf16 C (read, add in fp32, round once; weight-gradient form only),
@@ -585,7 +516,6 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
 // The number of splits weighs the K steps saved against what the partial tiles cost: about 3.5 K steps for the extra launch
 // and 0.09 K step per partial tile (256 KB written and read back at ~4.5 TB/s against 1.45 us per K step).  Up to 27 splits: eight
 // tiles with the reduction of a 50257-word vocabulary, or 28 with that of two MLP widths, would keep most CUs idle with four.
-constexpr int N_CU = 256;
 constexpr int MAX_SPLITS = 27;        // the numbers tried: 2 .. 8, 10, 12, 15, 18, 22, 27
 struct Schedule { int tiles, full, tail, splits; };
 __host__ __device__ __forceinline__ Schedule make_schedule(int tiles, int k_steps, int scratch_tiles) {
@@ -807,6 +737,27 @@ static hipError_t launch_tail(int mode, const TailArgs& t, int max_tail, hipStre
   else if (mode == 1) splitk_tail_k<1><<<blocks, 256, 0, st>>>(t);
   else splitk_tail_k<2><<<blocks, 256, 0, st>>>(t);
   return hipGetLastError();
+}
+
+// Estimated time in us of a launch of `tiles` 256 x 256 tiles, for the choice between these kernels and those of gemm_few.hip: a K step takes
+// 1.2 us (1.35 where all CUs multiply), a launch 5 us; one with split tiles 14, 0.3 per split and 0.055 per partial tile of 256
+// rows that is written and read.  Measured / estimated: 511 x 1024 x 1024 20.5 / 21.9, 512 x 3584 x 3584 35.0 / 38.9, 1024 x 4096 x 4096 48.8 / 50.9,
+// 2048 x 3584 x 3584 61.1 / 64.7, 512 x 18944 x 3584 85 / 78.
+static double launch_us(int tiles, int k_steps, int scratch_tiles, int max_m) {
+  const Schedule sc = make_schedule(tiles, k_steps, scratch_tiles);
+  const double step = 1.2 + 0.15 * std::min(1.0, (double)tiles * sc.splits / N_CU);
+  const double whole = (double)cdiv(sc.full, N_CU) * k_steps * step;
+  return sc.splits == 1 ? 5.0 + whole
+                        : 14.0 + 0.3 * sc.splits + whole + (double)cdiv(k_steps, sc.splits) * step + 0.055 * sc.tail * sc.splits * partial_floats(max_m) / (BM * BN);
+}
+double gemm_mfma_us(const GemmArgs* gs, int n) {      // n > 1: one grouped launch
+  int tiles = 0, k = 0, max_m = 0;
+  for (int i = 0; i < n; ++i) {
+    tiles += (int)(cdiv(gs[i].M, BM) * cdiv(gs[i].N, BN));
+    k = std::max(k, (int)cdiv(gs[i].K, BK) * (gs[i].A2 ? 2 : 1));
+    max_m = std::max(max_m, gs[i].M);
+  }
+  return launch_us(tiles, k, scratch_tiles_of(gs[0], max_m), max_m);
 }
 
 hipError_t gemm_mfma(const GemmArgs& g, hipStream_t st) {

@@ -55,6 +55,8 @@ struct GemmArgs {
   // C = A B^T is padded: its rows reach to ldc, a multiple of 8, so N need not be a multiple of anything (columns N .. next multiple of 4
   // receive finite values of no meaning).
   bool c_padded = false;
+  // Outputs of few tiles may go to the kernels of gemm_few.hip (which split no reduction over workgroups and leave `scratch` alone)
+  bool few_ok = false;
 };
 constexpr int GEMM_STAT_COLS = 256;
 bool gemm_row_stats_supported(const GemmArgs& g);
@@ -65,6 +67,10 @@ hipError_t gemm(const GemmArgs& g, hipStream_t st);
 // n independent GEMMs (distinct outputs); one grouped launch when the MFMA kernel can take them all
 // group_small: take the grouped launch also when the problems together have few output tiles (skinny problems)
 hipError_t gemm_batch(const GemmArgs* gs, int n, hipStream_t st, bool group_small = false);
+struct FewChoice { int tm, tn; double us; };      // output tile of gemm_few_k (0: not for it) and estimated time
+// C = sum of n products (gs[0] stores, the others, with acc set, add to the same C): one launch where the kernels for few output tiles are the
+// faster ones, otherwise gemm(gs[0]) and gemm_batch of the rest
+hipError_t gemm_sum(const GemmArgs* gs, int n, hipStream_t st);
 // true when the bf16 MFMA kernel can take this problem (used by tests / tile accounting)
 bool gemm_uses_mfma(const GemmArgs& g);
 // force the generic kernel (debug / A-B tests)
@@ -84,9 +90,9 @@ namespace prof {
 // kinds 0..11: gemm_mfma_k<layout, mode> with layout NT=0, NN=1, TN=2 and mode 0, 1, 2 (slot 3 unused); 12..23: the grouped kernel;
 // then the shape-agnostic GEMM, the attention forward / backward launch sequences, the segmented weight-gradient GEMM and the
 // store form with row statistics (gemm_mfma_k<NT, 5>), the input-gradient form with the fused SwiGLU adjoint (gemm_mfma_k<NN, 6>)
-// and the softmax-numerator store (gemm_mfma_k<NT, 7>)
+// and the softmax-numerator store (gemm_mfma_k<NT, 7>), the kernels for outputs of few tiles (gemm_few_k)
 enum { GEMM_SINGLE = 0, GEMM_GROUP = 12, GEMM_GENERIC = 24, ATTN_FWD = 25, ATTN_BWD = 26, GEMM_SEG = 27, GEMM_STATS = 28, GEMM_SWIGLU = 29,
-       GEMM_NUMER = 30, N_KIND = 31 };
+       GEMM_NUMER = 30, GEMM_FEW = 31, N_KIND = 32 };
 struct Scope {
   hipStream_t st; bool active = false; int kind = 0; double work = 0; bool bounded = false; hipEvent_t e0{}, e1{};
   // bounded: `work` was computed from a host-side upper bound of a run-time row count

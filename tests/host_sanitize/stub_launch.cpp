@@ -64,6 +64,7 @@ size_t gemm_scratch_bytes(int max_m, int max_n) {     // at most one partial til
 }
 hipError_t gemm(const GemmArgs& g, hipStream_t) { touch_gemm(g); return hipSuccess; }
 hipError_t gemm_batch(const GemmArgs* gs, int n, hipStream_t, bool) { for (int i = 0; i < n; ++i) touch_gemm(gs[i]); return hipSuccess; }
+hipError_t gemm_sum(const GemmArgs* gs, int n, hipStream_t) { for (int i = 0; i < n; ++i) touch_gemm(gs[i]); return hipSuccess; }
 bool gemm_uses_mfma(const GemmArgs& g) { return g.in_dt == DT_BF16; }
 void gemm_set_force_generic(bool) {}
 static int g_mask = FUSE_ROPE_Q | FUSE_NUMERATORS;
