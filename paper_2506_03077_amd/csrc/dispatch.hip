@@ -9,7 +9,7 @@
 
 namespace sbp {
 
-hipError_t gemm_generic(const GemmArgs& g, hipStream_t st);
+hipError_t gemm_generic(const GemmArgs* gs, int n, bool sum, hipStream_t st);      // hipErrorInvalidValue: not in one launch, nothing done
 hipError_t gemm_mfma(const GemmArgs& g, hipStream_t st);
 bool gemm_mfma_eligible(const GemmArgs& g);
 bool gemm_mfma_pair_ok(const GemmArgs& g);
@@ -84,6 +84,26 @@ static hipError_t run_few(const GemmArgs* gs, int n, bool sum, const FewChoice& 
   prof::Scope sc(prof::GEMM_FEW, work, false, st);
   return gemm_few(gs, n, sum, c.tm, c.tn, st);
 }
+static hipError_t run_generic(const GemmArgs* gs, int n, bool sum, hipStream_t st) {
+  double work = 0.0;
+  bool dev_rows = false;
+  for (int i = 0; i < n; ++i) {
+    work += 2.0 * gs[i].M * gs[i].N * gs[i].K * (gs[i].A2 ? 2 : 1);
+    dev_rows = dev_rows || gs[i].rows_dev;
+  }
+  hipError_t e;
+  {
+    prof::Scope sc(prof::GEMM_GENERIC, work, dev_rows, st);
+    e = gemm_generic(gs, n, sum, st);
+  }
+  if (e == hipSuccess && gs[0].in_dt == DT_BF16) ++g_generic_bf16_launches;
+  return e;
+}
+static bool all_generic(const GemmArgs* gs, int n) {
+  for (int i = 0; i < n; ++i)
+    if (gemm_uses_mfma(gs[i]) || gs[i].swiglu_gate || gs[i].row_stats || gs[i].numer_targets) return false;
+  return true;
+}
 // the kernels for outputs of few tiles, where their estimate is the lower one
 static bool few_is_faster(const FewChoice& c, double us) { return c.tm && c.us < us; }
 
@@ -97,7 +117,7 @@ hipError_t gemm(const GemmArgs& g, hipStream_t st) {
     hipError_t e = gemm(plain, st);
     return e != hipSuccess ? e : swiglu_bwd(g.out_dt, g.swiglu_gate, g.swiglu_up, g.C, g.swiglu_act, (int64_t)g.M * g.N, st);
   }
-  if (g.A2 && !(gemm_uses_mfma(g) && gemm_mfma_pair_ok(g))) {   // two operand pairs, no single launch for them: one after the other
+  if (g.A2 && gemm_uses_mfma(g) && !gemm_mfma_pair_ok(g)) {   // two operand pairs, no single launch for them: one after the other
     GemmArgs first = g, second = g;
     first.A2 = first.B2 = nullptr;
     second.A = g.A2; second.B = g.B2; second.A2 = second.B2 = nullptr; second.acc = true;
@@ -109,9 +129,7 @@ hipError_t gemm(const GemmArgs& g, hipStream_t st) {
     if (few_is_faster(few, gemm_mfma_us(&g, 1))) return run_few(&g, 1, false, few, st);
     return gemm_mfma(g, st);      // times itself (it knows which kernel variant it launches)
   }
-  if (g.in_dt == DT_BF16) ++g_generic_bf16_launches;
-  prof::Scope sc(prof::GEMM_GENERIC, 2.0 * g.M * g.N * g.K, g.rows_dev != nullptr, st);
-  return gemm_generic(g, st);
+  return run_generic(&g, 1, false, st);
 }
 hipError_t gemm_batch(const GemmArgs* gs, int n, hipStream_t st, bool group_small) {
   if (!g_force_generic_gemm && gemm_mfma_seg_eligible(gs, n)) return gemm_mfma_seg(gs, n, st);   // same C: one pass over it
@@ -127,6 +145,10 @@ hipError_t gemm_batch(const GemmArgs* gs, int n, hipStream_t st, bool group_smal
     }
   }
   if (group) return gemm_mfma_group(gs, n, st);
+  if (n > 1 && all_generic(gs, n)) {
+    hipError_t e = run_generic(gs, n, false, st);
+    if (e != hipErrorInvalidValue) return e;
+  }
   for (int i = 0; i < n; ++i) {
     hipError_t e = gemm(gs[i], st);
     if (e != hipSuccess) return e;
@@ -139,6 +161,10 @@ hipError_t gemm_sum(const GemmArgs* gs, int n, hipStream_t st) {
     // (the others as one launch that reads and writes C again)
     if (few_is_faster(few, gemm_mfma_us(gs, 1) + gemm_mfma_us(gs + 1, 1) + 5.0)) return run_few(gs, n, true, few, st);
   }
+  if (n > 1 && all_generic(gs, n)) {
+    hipError_t e = run_generic(gs, n, true, st);
+    if (e != hipErrorInvalidValue) return e;
+  }
   hipError_t e = gemm(gs[0], st);
   return e != hipSuccess || n == 1 ? e : gemm_batch(gs + 1, n - 1, st);
 }
@@ -146,23 +172,13 @@ hipError_t attn_forward(const AttnArgs& a, hipStream_t st) {
   prof::Scope sc(prof::ATTN_FWD, 4.0 * a.dh * causal_pairs(a), false, st);
   if (attn_uses_mfma(a.dt, a.dh, a.Hq, a.Hkv) && attn_mfma_aligned(a, false)) return attn_forward_mfma(a, st);
   if (a.dt == DT_BF16) ++g_generic_bf16_launches;
-  AttnArgs b = a;
-  b.rope_q = nullptr;            // the shape-agnostic kernels take rotated queries: rotate in place first
-  if (a.rope_q) {
-    hipError_t e = rope_apply(a.dt, (void*)a.q, a.rope_q, a.q_len, a.Hq, a.dh, false, st);
-    if (e != hipSuccess) return e;
-  }
-  return attn_forward_generic(b, st);
+  return attn_forward_generic(a, st);
 }
 hipError_t attn_backward(const AttnArgs& a, hipStream_t st) {
   prof::Scope sc(prof::ATTN_BWD, 10.0 * a.dh * causal_pairs(a), false, st);
   if (attn_uses_mfma(a.dt, a.dh, a.Hq, a.Hkv) && attn_mfma_aligned(a, true)) return attn_backward_mfma(a, st);
   if (a.dt == DT_BF16) ++g_generic_bf16_launches;
-  AttnArgs b = a;
-  b.rope_q = nullptr;
-  hipError_t e = attn_backward_generic(b, st);
-  if (e != hipSuccess || !a.rope_q) return e;
-  return rope_apply(a.dt, a.dq, a.rope_q, a.q_len, a.Hq, a.dh, true, st);   // dq back through the rotation
+  return attn_backward_generic(a, st);
 }
 
 }  // namespace sbp

@@ -4,6 +4,9 @@
 #include "launch.h"
 #include "device.h"
 
+#include <algorithm>
+#include <iterator>
+
 namespace sbp {
 
 // 32 x 32 tiles, the reduction dealt to the eight waves of a workgroup in steps of 16, fp32 MFMAs (v_mfma_f32_16x16x4_f32) straight
@@ -41,33 +44,59 @@ __device__ __forceinline__ f32x4 operand(const TI* __restrict__ p, bool k_major,
   }
   return v;
 }
-template <typename TI, typename TO, bool ACC>
-__global__ __launch_bounds__(WAVES * 64) void gemm_generic_k(const TI* __restrict__ A, const TI* __restrict__ B, TO* __restrict__ C, int M,
-                                                              int N, int K, int64_t lda, int64_t ldb, int64_t ldc, int ta, int tb,
-                                                              int vec_a, int vec_b, const int* __restrict__ rows_dev) {
-  if (rows_dev) {   // run-time row count (M for NT / NN, the reduction K for the dW form)
-    const int rows = max(0, *rows_dev);
-    if (ta) K = min(K, rows); else M = min(M, rows);
-  }
+// Several problems in one launch, each with its own layout and one or more reduction segments (operand pairs whose products are summed into
+// one output): a launch of the small configuration costs 4.8 us however little it does, its layer and head issued 86 of them.
+// (NP problems, NS segments: the smallest of three sizes, as the arguments' cache lines are fetched one dependent miss after the other.)
+constexpr int GENERIC_PROBLEMS = 8, GENERIC_SEGMENTS = 56;
+struct GenericSegment { const void* A; const void* B; const int* rows_dev; int K, lda, ldb, vec; };       // vec: bit 0 A, bit 1 B
+struct GenericProblem { void* C; int64_t ldc; int M, N, ta, tb, seg0, nseg, tile0, tiles_n; };
+template <int NP, int NS> struct GenericArgs { int n; GenericProblem p[NP]; GenericSegment s[NS]; };
+using GenericAll = GenericArgs<GENERIC_PROBLEMS, GENERIC_SEGMENTS>;
+
+template <typename TI, typename TO, bool ACC, int NP, int NS>
+__global__ __launch_bounds__(WAVES * 64) void gemm_generic_k(const GenericArgs<NP, NS> ga) {
+  int pi = 0;
+#pragma unroll
+  for (int i = 1; i < NP; ++i)
+    if (i < ga.n && (int)blockIdx.x >= ga.p[i].tile0) pi = i;
+  const GenericProblem& g = ga.p[pi];
+  const int tile = (int)blockIdx.x - g.tile0, m0 = tile / g.tiles_n * TILE, n0 = tile % g.tiles_n * TILE;
+  // run-time row count (M for NT / NN, the reduction K for the dW form)
+  auto rows = [&](const GenericSegment& q) { return q.rows_dev ? max(0, *q.rows_dev) : 0x7fffffff; };
+  const int M = g.ta ? g.M : min(g.M, rows(ga.s[g.seg0])), N = g.N;
   __shared__ float part[WAVES][TILE][TILE + 1];
-  const int m0 = blockIdx.y * TILE, n0 = blockIdx.x * TILE;
   if (m0 >= M) return;
-  const int wave = threadIdx.x >> 6, li = threadIdx.x & 15, lg = (threadIdx.x & 63) >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), li = threadIdx.x & 15, lg = (threadIdx.x & 63) >> 4;
   f32x4 acc[2][2] = {};
   f32x4 a[2], b[2];
-  auto load = [&](int k0) {
+  // the steps of all segments, one after the other, dealt to the waves: seg, k0 = this wave's next one, K its segment's reduction
+  int seg = -1, k0 = 0, K = 0, dealt = 0;
+  auto next = [&]() {
+    k0 += WAVES * KSTEP;
+    while (k0 >= K) {
+      dealt += (K + KSTEP - 1) / KSTEP;
+      if (++seg >= g.nseg) return false;
+      K = ga.s[g.seg0 + seg].K;
+      if (g.ta) K = min(K, rows(ga.s[g.seg0 + seg]));
+      k0 = ((wave - dealt) & (WAVES - 1)) * KSTEP;
+    }
+    return true;
+  };
+  auto load = [&]() {
+    const GenericSegment& q = ga.s[g.seg0 + seg];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      a[i] = operand(A, ta != 0, lda, m0 + i * 16 + li, M, k0 + 4 * lg, K, vec_a != 0);
-      b[i] = operand(B, tb == 0, ldb, n0 + i * 16 + li, N, k0 + 4 * lg, K, vec_b != 0);
+      a[i] = operand((const TI*)q.A, g.ta != 0, q.lda, m0 + i * 16 + li, M, k0 + 4 * lg, K, (q.vec & 1) != 0);
+      b[i] = operand((const TI*)q.B, g.tb == 0, q.ldb, n0 + i * 16 + li, N, k0 + 4 * lg, K, (q.vec & 2) != 0);
     }
   };
-  int k0 = wave * KSTEP;
-  if (k0 < K) load(k0);
-  while (k0 < K) {
+  bool more = next();
+  const bool any = more;
+  if (more) load();
+  while (more) {
     const f32x4 a0 = a[0], a1 = a[1], b0 = b[0], b1 = b[1];
-    k0 += WAVES * KSTEP;
-    if (k0 < K) load(k0);
+    more = next();
+    if (more) load();
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[j], b0[j], acc[0][0], 0, 0, 0);
@@ -76,8 +105,8 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_generic_k(const TI* __restric
       acc[1][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[j], b1[j], acc[1][1], 0, 0, 0);
     }
   }
-  const int waves = min(WAVES, (K + KSTEP - 1) / KSTEP);      // the others had no step
-  if (wave < waves) {
+  const int waves = min(WAVES, dealt);      // the others had no step
+  if (any) {
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -92,27 +121,83 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_generic_k(const TI* __restric
     if (m0 + row >= M || n0 + col >= N) continue;
     float v = 0.f;
     for (int w = 0; w < waves; ++w) v += part[w][row][col];
-    TO* p = C + (int64_t)(m0 + row) * ldc + n0 + col;
+    TO* p = (TO*)g.C + (int64_t)(m0 + row) * g.ldc + n0 + col;
     if (ACC) stf(p, ldf(p) + v); else stf(p, v);
   }
 }
 
-hipError_t gemm_generic(const GemmArgs& g, hipStream_t st) {
-  if (g.M == 0 || g.N == 0) return hipSuccess;
-  const dim3 grid((unsigned)cdiv(g.N, TILE), (unsigned)cdiv(g.M, TILE));
-  // four elements at a time where rows of a K-contiguous operand start at multiples of four
-  const uintptr_t four = 4 * dtype_size(g.in_dt) - 1;
-  const int vec_a = g.lda % 4 == 0 && !((uintptr_t)g.A & four), vec_b = g.ldb % 4 == 0 && !((uintptr_t)g.B & four);
-#define GG(TI, TO, ACC)                                                                                                         \
-  gemm_generic_k<TI, TO, ACC><<<grid, WAVES * 64, 0, st>>>((const TI*)g.A, (const TI*)g.B, (TO*)g.C, g.M, g.N, g.K, g.lda, g.ldb, \
-                                                           g.ldc, g.ta ? 1 : 0, g.tb ? 1 : 0, vec_a, vec_b, g.rows_dev)
+// What one launch takes: problems of the same types that all add to their C or all store it.  Accumulated problems with the same C become
+// segments of one (C is read and written once); sum: all n are segments of one stored output.  False: not in one launch.
+static bool generic_args(const GemmArgs* gs, int n, bool sum, GenericAll& ga, int64_t& tiles) {
+  ga.n = 0;
+  tiles = 0;
+  int seg_of[GENERIC_SEGMENTS], n_seg = 0;       // segments in the order given, and the problem each belongs to
+  GenericSegment segs[GENERIC_SEGMENTS];
+  const uintptr_t four = 4 * dtype_size(gs[0].in_dt) - 1;
+  for (int i = 0; i < n; ++i) {
+    const GemmArgs& g = gs[i];
+    if (g.M == 0 || g.N == 0) continue;
+    if (g.in_dt != gs[0].in_dt || g.out_dt != gs[0].out_dt || (!sum && g.acc != gs[0].acc) || g.lda > INT32_MAX || g.ldb > INT32_MAX) return false;
+    int pi = -1;
+    for (int j = 0; j < ga.n && pi < 0; ++j) {
+      const GenericProblem& p = ga.p[j];
+      if (p.C != g.C) continue;
+      if (!(sum || g.acc) || p.M != g.M || p.N != g.N || p.ldc != g.ldc || p.ta != (g.ta ? 1 : 0) || p.tb != (g.tb ? 1 : 0) || (g.rows_dev && !g.ta)) return false;
+      pi = j;
+    }
+    if (pi < 0) {
+      if (ga.n == GENERIC_PROBLEMS || (sum && ga.n == 1)) return false;
+      pi = ga.n++;
+      ga.p[pi] = GenericProblem{g.C, g.ldc, g.M, g.N, g.ta ? 1 : 0, g.tb ? 1 : 0, 0, 0, (int)tiles, (int)cdiv(g.N, TILE)};
+      tiles += cdiv(g.M, TILE) * cdiv(g.N, TILE);
+      if (tiles > INT32_MAX) return false;
+    }
+    for (int two = 0; two < (g.A2 ? 2 : 1); ++two) {
+      if (n_seg == GENERIC_SEGMENTS) return false;
+      const void *A = two ? g.A2 : g.A, *B = two ? g.B2 : g.B;
+      // four elements at a time where rows of a K-contiguous operand start at multiples of four
+      segs[n_seg] = GenericSegment{A, B, g.rows_dev, g.K, (int)g.lda, (int)g.ldb, (g.lda % 4 == 0 && !((uintptr_t)A & four) ? 1 : 0) | (g.ldb % 4 == 0 && !((uintptr_t)B & four) ? 2 : 0)};
+      seg_of[n_seg++] = pi;
+    }
+  }
+  int at = 0;
+  for (int j = 0; j < ga.n; ++j) {
+    ga.p[j].seg0 = at;
+    for (int i = 0; i < n_seg; ++i)
+      if (seg_of[i] == j) ga.s[at++] = segs[i];
+    ga.p[j].nseg = at - ga.p[j].seg0;
+  }
+  return true;
+}
+// n problems in one launch (see generic_args); hipErrorInvalidValue where they do not fit one, with nothing launched
+hipError_t gemm_generic(const GemmArgs* gs, int n, bool sum, hipStream_t st) {
+  GenericAll ga;
+  int64_t tiles;
+  if (!generic_args(gs, n, sum, ga, tiles)) return hipErrorInvalidValue;
+  if (ga.n == 0) return hipSuccess;
+  const GemmArgs& g = gs[0];
+  int n_seg = 0;
+  for (int i = 0; i < ga.n; ++i) n_seg += ga.p[i].nseg;
+  auto go = [&](auto kernel, auto args) {
+    args.n = ga.n;
+    std::copy_n(ga.p, std::min<size_t>(std::size(args.p), ga.n), args.p);
+    std::copy_n(ga.s, std::min<size_t>(std::size(args.s), n_seg), args.s);
+    kernel<<<(unsigned)tiles, WAVES * 64, 0, st>>>(args);
+  };
+#define GG(TI, TO, ACC)                                                                                        \
+  do {                                                                                                         \
+    if (ga.n == 1 && n_seg == 1) go(gemm_generic_k<TI, TO, ACC, 1, 1>, GenericArgs<1, 1>{});                   \
+    else if (ga.n <= 2 && n_seg <= 3) go(gemm_generic_k<TI, TO, ACC, 2, 3>, GenericArgs<2, 3>{});              \
+    else go(gemm_generic_k<TI, TO, ACC, GENERIC_PROBLEMS, GENERIC_SEGMENTS>, GenericAll{});                    \
+  } while (0)
+  const bool acc = g.acc && !sum;
   if (g.in_dt == DT_BF16) {
-    if (g.out_dt == DT_BF16 && g.acc) GG(bf16_t, bf16_t, true);
+    if (g.out_dt == DT_BF16 && acc) GG(bf16_t, bf16_t, true);
     else if (g.out_dt == DT_BF16) GG(bf16_t, bf16_t, false);
-    else if (g.acc) GG(bf16_t, float, true);
+    else if (acc) GG(bf16_t, float, true);
     else GG(bf16_t, float, false);
   } else {
-    if (g.acc) GG(float, float, true);
+    if (acc) GG(float, float, true);
     else GG(float, float, false);
   }
 #undef GG
