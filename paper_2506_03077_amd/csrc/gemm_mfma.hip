@@ -324,7 +324,7 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
     }
     return;
   }
-  if constexpr (MODE == 0 || MODE == 2 || MODE == 4) {
+  if constexpr (MODE == 0 || MODE == 4) {
     // fp32 rows: one half of the tile's rows at a time (128 KB)
 #pragma unroll
     for (int ha = 0; ha < 2; ++ha) {
@@ -359,26 +359,6 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
           for (int e = 0; e < 4; ++e) { o[e] = (bf16_t)((float)old[p][e] + lo[e]); o[e + 4] = (bf16_t)((float)old[p][e + 4] + hi[e]); }
           if (row < M && col < N) *(bf16x8*)(Cb + (int64_t)row * ldc + col) = o;
         }
-      } else if constexpr (MODE == 2) {
-        // fp32 C += acc: plain read-modify-write, every element has one owner per launch; eight 16-byte loads of C per lane are
-        // in flight before the first add.  (fp32 atomic adds without return, the earlier form, cost 1721 instead of 1139 us
-        // where the pass over C dominates - 152064 x 3584, K = 512 - and the same at K >= 8192.)
-        const int c4 = threadIdx.x & 63, col = n0 + c4 * 4;
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          f32x4 old[8];
-#pragma unroll
-          for (int p = 0; p < 8; ++p) {
-            const int row = m0 + ha * 128 + (q * 8 + p) * 8 + (threadIdx.x >> 6);
-            if (row < M && col < N) old[p] = *(const f32x4*)(Cf + (int64_t)row * ldc + col);
-          }
-#pragma unroll
-          for (int p = 0; p < 8; ++p) {
-            const int row_l = (q * 8 + p) * 8 + (threadIdx.x >> 6), row = m0 + ha * 128 + row_l;
-            const f32x4 v = *(const f32x4*)(smem + row_l * 1024 + ((c4 ^ (row_l & 15)) << 4));
-            if (row < M && col < N) *(f32x4*)(Cf + (int64_t)row * ldc + col) = old[p] + v;
-          }
-        }
       } else {
         const int c4 = threadIdx.x & 63, col = n0 + c4 * 4;
 #pragma unroll
@@ -387,6 +367,52 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
           const f32x4 v = *(const f32x4*)(smem + row_l * 1024 + ((c4 ^ (row_l & 15)) << 4));
           if (row < M && col < N) *(f32x4*)(Cf + (int64_t)row * ldc + col) = v;
         }
+      }
+    }
+    return;
+  }
+  if constexpr (MODE == 2) {
+    // fp32 C += acc, half of the tile's rows at a time: a plain read-modify-write, every element has one owner per launch.  What bounds it is
+    // the latency of the reads of C, not their rate: those of a half (16 accesses of 16 bytes per lane) all go out before the half is
+    // staged, the second half's before the first is added.  Against eight at a time behind the staging: 18944 x 3584, K = 128 134 -> 103
+    // us, K = 1024 253 -> 227; 152064 x 3584, K = 1536 2207 -> 2108, K = 16384 14.90 -> 14.74 ms.  (fp32 atomic adds without return cost 1721
+    // instead of 1139 us where the pass over C dominates - 152064 x 3584, K = 512 - and the same at K >= 8192; the same form for bf16
+    // C, which has half the bytes to wait for: 2 % faster at K = 512, 1-4 % slower from K = 4096 on.)
+    const int c4 = threadIdx.x & 63, r0 = threadIdx.x >> 6;
+    const char* base = uniform_ptr(Cf + (int64_t)m0 * ldc + n0);
+    const uint32_t lane_off = (uint32_t)((r0 * ldc + c4 * 4) * 4);
+    const bool col_in = n0 + c4 * 4 < N;
+    const int rows_in = M - m0 - r0;      // rows of this lane's passes that exist
+    f32x4 old[2][16];
+    auto at = [&](int ha, int p) { return (f32x4*)(base + (int64_t)(ha * 128 + p * 8) * ldc * 4 + lane_off); };
+    auto inside = [&](int ha, int p) { return ha * 128 + p * 8 < rows_in && col_in; };
+    auto fetch = [&](int ha) {
+#pragma unroll
+      for (int p = 0; p < 16; ++p)
+        if (inside(ha, p)) old[ha][p] = *at(ha, p);
+    };
+    fetch(0);
+#pragma unroll
+    for (int ha = 0; ha < 2; ++ha) {
+      WAIT_LDS();
+      SLOT_BARRIER();
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int hb = 0; hb < 2; ++hb)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            const int row = row_of(0, i), cl = col_of(hb, j);
+            *(f32x4*)(smem + row * 1024 + (((cl >> 2) ^ (row & 15)) << 4)) = acc[ha][hb][i][j];
+          }
+      WAIT_LDS();
+      SLOT_BARRIER();
+      if (ha == 0) fetch(1);
+#pragma unroll
+      for (int p = 0; p < 16; ++p) {
+        const int row_l = p * 8 + r0;
+        const f32x4 v = *(const f32x4*)(smem + row_l * 1024 + ((c4 ^ (row_l & 15)) << 4));
+        if (inside(ha, p)) *at(ha, p) = old[ha][p] + v;
       }
     }
     return;
@@ -400,18 +426,29 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
     // per-chunk HBM passes): what the row kernel after the logits GEMM needs of a row is exp(c - lse), and exp(c - max of the
     // 256-column block) differs from it by one factor per block - so the tile stores that, in bf16; the sum is taken from the
     // unrounded values.  The logit of each row's target column, which the loss needs exactly, is kept in fp32 on the side.
+    // The numerators leave through LDS in whole rows, 16 bytes per lane, as the plain stores do, and the target columns are looked up for all
+    // of a lane's rows at once: 2048 x 152064 x 3584 1.75 -> 1.64 ms against 8-byte stores from the accumulator layout and a
+    // dependent pair of loads per row.
     __syncthreads();
-    float* pmax = (float*)smem;                // [NWAVE_N][BM]
+    float* pmax = (float*)(smem + (MODE == 7 ? SMEM_BYTES : 0));      // [NWAVE_N][BM]
     float* psum = pmax + NWAVE_N * BM;         // [NWAVE_N][BM]
     constexpr float LOG2E = 1.4426950408889634f;
+    int d[2][4];                               // MODE 7: target column of the lane's rows, relative to the tile
+    if constexpr (MODE == 7) {
+#pragma unroll
+      for (int x = 0; x < 8; ++x) {
+        const int row = min(m0 + row_of(x >> 2, x & 3), M - 1);
+        d[x >> 2][x & 3] = nf.row_index ? nf.row_index[row] : row;
+      }
+#pragma unroll
+      for (int x = 0; x < 8; ++x) d[x >> 2][x & 3] = nf.targets[d[x >> 2][x & 3]] - n0;
+    }
 #pragma unroll
     for (int ha = 0; ha < 2; ++ha)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int row_l = row_of(ha, i), row = m0 + row_l;
         float mx = -INFINITY;
-        int d = -1;
-        if (MODE == 7 && row < M) d = nf.targets[nf.row_index ? nf.row_index[row] : row] - n0;
 #pragma unroll
         for (int hb = 0; hb < 2; ++hb)
 #pragma unroll
@@ -423,9 +460,13 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
               for (int r = 0; r < 4; ++r) acc[ha][hb][i][j][r] = n0 + col + r < N ? acc[ha][hb][i][j][r] : -INFINITY;
             }
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              mx = fmaxf(mx, acc[ha][hb][i][j][r]);
-              if (MODE == 7 && d == col + r && acc[ha][hb][i][j][r] != -INFINITY) nf.target_value[row] = acc[ha][hb][i][j][r];
+            for (int r = 0; r < 4; ++r) mx = fmaxf(mx, acc[ha][hb][i][j][r]);
+            if constexpr (MODE == 7) {
+              const int r = d[ha][i] - col;    // which of the four, if any, is the target's
+              if (row < M && (uint32_t)r < 4u && n0 + d[ha][i] < N) {
+                const f32x4 v = acc[ha][hb][i][j];
+                nf.target_value[row] = r == 0 ? v[0] : r == 1 ? v[1] : r == 2 ? v[2] : v[3];
+              }
             }
           }
         mx = fmaxf(mx, __shfl_xor(mx, 16, WAVE));
@@ -437,7 +478,7 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
     for (int ha = 0; ha < 2; ++ha)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int row_l = row_of(ha, i), row = m0 + row_l;
+        const int row_l = row_of(ha, i);
         float m = pmax[row_l];
 #pragma unroll
         for (int w = 1; w < NWAVE_N; ++w) m = fmaxf(m, pmax[w * BM + row_l]);   // finite: wave 0 always holds valid columns
@@ -446,6 +487,7 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
         for (int hb = 0; hb < 2; ++hb)
 #pragma unroll
           for (int j = 0; j < 2; ++j) {
+            const int col = col_of(hb, j);
             bf16x4 o;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
@@ -453,13 +495,29 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
               se += ex;
               o[r] = (bf16_t)ex;
             }
-            if (MODE == 7 && row < M && n0 + col_of(hb, j) < N) *(bf16x4*)(Cb + (int64_t)row * ldc + n0 + col_of(hb, j)) = o;
+            if (MODE == 7) *(bf16x4*)(smem + row_l * 512 + (((col >> 3) ^ (row_l & 15)) << 4) + ((col & 4) << 1)) = o;
           }
         se += __shfl_xor(se, 16, WAVE);
         se += __shfl_xor(se, 32, WAVE);
         if (lane < 16) psum[wn * BM + row_l] = se;
       }
     __syncthreads();
+    if constexpr (MODE == 7) {
+      const int c16 = threadIdx.x & 31, col = n0 + c16 * 8;
+#pragma unroll
+      for (int p = 0; p < 16; ++p) {
+        const int row = p * 16 + (threadIdx.x >> 5);
+        const i32x4 v = *(const i32x4*)(smem + row * 512 + ((c16 ^ (row & 15)) << 4));
+        if (m0 + row < M && col < N) {
+          if (ldc % 8 == 0) *(i32x4*)(Cb + (int64_t)(m0 + row) * ldc + col) = v;
+          else {                               // (rows that start between 16-byte boundaries: half of them at a time)
+            typedef int i32x2 __attribute__((ext_vector_type(2)));
+            *(i32x2*)(Cb + (int64_t)(m0 + row) * ldc + col) = i32x2{v[0], v[1]};
+            *(i32x2*)(Cb + (int64_t)(m0 + row) * ldc + col + 4) = i32x2{v[2], v[3]};
+          }
+        }
+      }
+    }
     if ((int)threadIdx.x < BM && m0 + (int)threadIdx.x < M) {
       float m = pmax[threadIdx.x], sum = psum[threadIdx.x];
 #pragma unroll
@@ -549,7 +607,7 @@ __global__ __launch_bounds__(NTHREADS) void gemm_mfma_k(const bf16_t* __restrict
                                                         const bf16_t* __restrict__ A2, const bf16_t* __restrict__ B2,
                                                         float* __restrict__ scratch, int scratch_tiles, void* __restrict__ row_stats,
                                                         SwigluFuse sw, NumerFuse nf) {
-  __shared__ __attribute__((aligned(1024))) char smem[SMEM_BYTES];
+  __shared__ __attribute__((aligned(1024))) char smem[SMEM_BYTES + (MODE == 7 ? 2 * NWAVE_N * BM * 4 : 0)];
   const int part = partial_floats(M);
   if (rows_dev) {                     // run-time row count: rows are M (NT / NN) or the reduction K (dW form)
     const int rows = max(0, *rows_dev);
