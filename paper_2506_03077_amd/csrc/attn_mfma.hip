@@ -56,6 +56,7 @@ constexpr int TK = ATTN_TILE_K;          // 64 keys per step (fwd, dQ)
 constexpr int KV_TILE = ATTN_KV_TILE;    // keys per workgroup (dK/dV): 4 key blocks x 2 roles = 8 waves
 constexpr int KV_THREADS = 512;
 constexpr int QT = ATTN_KV_QUERIES;      // queries per step (dK/dV)
+constexpr int MERGED_MAX = 1024;         // workgroups of a backward that runs as one launch (four rounds of the chip)
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
 
@@ -622,16 +623,16 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
 // SPLIT: 128 queries per workgroup for launches that would leave CUs idle, as in the forward kernel: the two halves of the workgroup
 // take the even / odd key tiles of the same queries and add up in LDS (1024 queries, 32 heads: 128 workgroups of 256 queries).
 template <int DH, bool SPLIT>
-__global__ __launch_bounds__(AT_THREADS) void attn_bwd_dq_mfma_k(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
-                                                                    const bf16_t* __restrict__ v, const bf16_t* __restrict__ d_o,
-                                                                    const float* __restrict__ lse, const float* __restrict__ delta,
-                                                                    bf16_t* __restrict__ dq, int Hq, int Hkv, int q_start, int c,
-                                                                    float scale, const float2* __restrict__ rope, int window,
-                                                                    int kv_first) {
-  __shared__ __attribute__((aligned(1024))) char sT[SPLIT ? 8 : 4][TILE64<DH>];   // stage st (of a half): K = sT[2 st], V = sT[2 st + 1]
+struct DqShared { char sT[SPLIT ? 8 : 4][TILE64<DH>]; };      // stage st (of a half): K = sT[2 st], V = sT[2 st + 1]
+template <int DH, bool SPLIT>
+__device__ __forceinline__ void dq_tile(DqShared<DH, SPLIT>& sh, int q_block, int h, const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
+                                        const bf16_t* __restrict__ v, const bf16_t* __restrict__ d_o, const float* __restrict__ lse,
+                                        const float* __restrict__ delta, bf16_t* __restrict__ dq, int Hq, int Hkv, int q_start, int c,
+                                        float scale, const float2* __restrict__ rope, int window, int kv_first) {
+  auto& sT = sh.sT;
   constexpr int QW = SPLIT ? TQ / 2 : TQ, NT = SPLIT ? AT_THREADS / 2 : AT_THREADS;
 
-  const int q0 = blockIdx.x * QW, h = blockIdx.y, kvh = h / (Hq / Hkv);
+  const int q0 = q_block * QW, kvh = h / (Hq / Hkv);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), grp = SPLIT ? wave >> 2 : 0, lane = threadIdx.x & 63, half = lane >> 5;
   const int qw0 = q0 + (SPLIT ? wave & 3 : wave) * 32;
   const int my_q = qw0 + (lane & 31);
@@ -778,6 +779,17 @@ __global__ __launch_bounds__(AT_THREADS) void attn_bwd_dq_mfma_k(const bf16_t* _
   }
 }
 
+template <int DH, bool SPLIT>
+__global__ __launch_bounds__(AT_THREADS) void attn_bwd_dq_mfma_k(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
+                                                                    const bf16_t* __restrict__ v, const bf16_t* __restrict__ d_o,
+                                                                    const float* __restrict__ lse, const float* __restrict__ delta,
+                                                                    bf16_t* __restrict__ dq, int Hq, int Hkv, int q_start, int c,
+                                                                    float scale, const float2* __restrict__ rope, int window,
+                                                                    int kv_first) {
+  __shared__ __attribute__((aligned(1024))) DqShared<DH, SPLIT> sh;
+  dq_tile<DH, SPLIT>(sh, blockIdx.x, blockIdx.y, q, k, v, d_o, lse, delta, dq, Hq, Hkv, q_start, c, scale, rope, window, kv_first);
+}
+
 // -------------------------------------------------------------------- dK/dV --
 // Workgroup = 128 keys of one KV head, 8 waves = 4 key blocks of 32 x 2 roles, so that each SIMD holds the two
 // waves of one key block:
@@ -797,20 +809,26 @@ constexpr int KV_STAGES = 4;
 constexpr int CHAIN = 6;                 // LDS fragments requested ahead of the products (dK/dV)
 
 template <int DH>
-__global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
-                                                                  const bf16_t* __restrict__ v, const bf16_t* __restrict__ d_o,
-                                                                  const float* __restrict__ lse2, const float* __restrict__ delta,
-                                                                  float* __restrict__ dk, float* __restrict__ dv, int Hq, int Hkv,
-                                                                  int q_start, int c, float scale, int window, int kv_first,
-                                                                  int key_block0, int slices, float* __restrict__ part) {
-  __shared__ __attribute__((aligned(1024))) char sQD[2][KV_STAGES][TILE64<DH>];   // [Q | dO][stage]
+struct DkvShared {
+  char sQD[2][KV_STAGES][TILE64<DH>];             // [Q | dO][stage]
   // P of the tile, [key block][slot][lane]: bf16, slot = query block * 2 + k16 step; FP32_STATS: fp32, slot = query block * 4 + r / 4
-  __shared__ __attribute__((aligned(16))) bf16x8 sP[4][FP32_STATS<DH> ? 8 : 4][64];
-  __shared__ __attribute__((aligned(16))) float sL[KV_STAGES][QT];  // (log2-domain) log-sum-exp of the tile's queries
-  __shared__ __attribute__((aligned(16))) float sDl[KV_STAGES][QT]; // delta of the tile's queries
+  bf16x8 sP[4][FP32_STATS<DH> ? 8 : 4][64];
+  float sL[KV_STAGES][QT];                        // (log2-domain) log-sum-exp of the tile's queries
+  float sDl[KV_STAGES][QT];                       // delta of the tile's queries
+};
+template <int DH>
+__device__ __forceinline__ void dkv_block(DkvShared<DH>& sh, int key_block, int kvh, int slice, const bf16_t* __restrict__ q,
+                                          const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, const bf16_t* __restrict__ d_o,
+                                          const float* __restrict__ lse2, const float* __restrict__ delta, float* __restrict__ dk,
+                                          float* __restrict__ dv, int Hq, int Hkv, int q_start, int c, float scale, int window, int kv_first,
+                                          int key_block0, int slices, float* __restrict__ part) {
+  auto& sQD = sh.sQD;
+  auto& sP = sh.sP;
+  auto& sL = sh.sL;
+  auto& sDl = sh.sDl;
 
   const int G = Hq / Hkv;
-  const int key0 = (key_block0 + (int)blockIdx.x) * KV_TILE, kvh = blockIdx.y;   // key blocks before key_block0 are visible to no query
+  const int key0 = (key_block0 + key_block) * KV_TILE;   // key blocks before key_block0 are visible to no query
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, half = lane >> 5;
   const int kb = wave & 3;
   const bool role_p = wave < 4;
@@ -850,7 +868,7 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
   const int n_all = max(0, n_qt - qt_first) * G;
   // The steps come in `slices` shares: a workgroup each where there is room for the parts, one after the other in this one
   // otherwise (the same sums in the same order: bit-identical results).
-  for (int z = part ? (int)blockIdx.z : 0, z_end = part ? z + 1 : slices; z < z_end; ++z) {
+  for (int z = part ? slice : 0, z_end = part ? z + 1 : slices; z < z_end; ++z) {
   const int it0 = (int)((int64_t)n_all * z / slices), n_iter = (int)((int64_t)n_all * (z + 1) / slices) - it0;
 
   // Loads of this share's next tile (query tile lq, head lh of the group); past the end the last one again, so that the wait counts
@@ -1034,6 +1052,43 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
   }
 }
 
+template <int DH>
+__global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
+                                                                  const bf16_t* __restrict__ v, const bf16_t* __restrict__ d_o,
+                                                                  const float* __restrict__ lse2, const float* __restrict__ delta,
+                                                                  float* __restrict__ dk, float* __restrict__ dv, int Hq, int Hkv,
+                                                                  int q_start, int c, float scale, int window, int kv_first,
+                                                                  int key_block0, int slices, float* __restrict__ part) {
+  __shared__ __attribute__((aligned(1024))) DkvShared<DH> sh;
+  dkv_block<DH>(sh, blockIdx.x, blockIdx.y, blockIdx.z, q, k, v, d_o, lse2, delta, dk, dv, Hq, Hkv, q_start, c, scale, window, kv_first,
+                key_block0, slices, part);
+}
+
+// dK/dV and dQ in one launch, the workgroups of dK/dV, the longer ones, first: for chunks that are a few rounds of the chip, where each
+// launch on its own leaves CUs idle at its end (777 windowed queries, 32 / 8 heads: 76 + 35 -> 102 us, the whole call 154 -> 141; a chunk
+// of many rounds gains nothing).
+template <int DH, bool SPLIT>
+__global__ __launch_bounds__(AT_THREADS) void attn_bwd_mfma_k(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
+                                                              const bf16_t* __restrict__ d_o, const float* __restrict__ lse,
+                                                              const float* __restrict__ lse2, const float* __restrict__ delta,
+                                                              bf16_t* __restrict__ dq, float* __restrict__ dk, float* __restrict__ dv, int Hq,
+                                                              int Hkv, int q_start, int c, float scale, const float2* __restrict__ rope,
+                                                              int window, int kv_first, int key_block0, int key_blocks, int slices,
+                                                              float* __restrict__ part, int q_blocks) {
+  static_assert(AT_THREADS == KV_THREADS, "one workgroup shape");
+  __shared__ __attribute__((aligned(1024))) union { DkvShared<DH> dkv; DqShared<DH, SPLIT> dq; } sh;
+  const int n_dkv = key_blocks * Hkv * (part ? slices : 1), b = blockIdx.x;
+  if (b < n_dkv) {
+    const int r = b / key_blocks;
+    dkv_block<DH>(sh.dkv, b % key_blocks, r % Hkv, r / Hkv, q, k, v, d_o, lse2, delta, dk, dv, Hq, Hkv, q_start, c, scale, window, kv_first,
+                  key_block0, slices, part);
+  } else {
+    // the tiles with the most keys first
+    const int i = b - n_dkv;
+    dq_tile<DH, SPLIT>(sh.dq, q_blocks - 1 - i / Hq, i % Hq, q, k, v, d_o, lse, delta, dq, Hq, Hkv, q_start, c, scale, rope, window, kv_first);
+  }
+}
+
 // dk / dv += sum over the slices of the split form, in their order.  n4: float4s of dk (and of dv)
 __global__ __launch_bounds__(256) void attn_dkv_sum_k(const float4* __restrict__ part, int slices, int64_t n4, float4* __restrict__ dk, float4* __restrict__ dv) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -1047,24 +1102,25 @@ __global__ __launch_bounds__(256) void attn_dkv_sum_k(const float4* __restrict__
   *out = s;
 }
 
-// delta[h, t] = sum_j d_o[t,h,j] * o[t,h,j]  (one wave per (t, h))
+// delta[h, t] = sum_j d_o[t,h,j] * o[t,h,j]  (DH / 8 lanes per (t, h), 16 bytes of each tensor per lane)
 // also lse2[h, t] = lse[h, t] * log2(e), the form the dK/dV kernel's exp2 wants (one multiply per (t, h) here
 // instead of one per score there); 64-wide heads, whose exponents are natural differences: lse[h, t] itself
 template <int DH>
 __global__ __launch_bounds__(256) void attn_delta_mfma_k(const bf16_t* __restrict__ o, const bf16_t* __restrict__ d_o,
                                                          const float* __restrict__ lse, float* __restrict__ delta,
                                                          float* __restrict__ lse2, int Hq, int c) {
-  const int64_t pair = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);      // t * Hq + h
+  constexpr int LANES = DH / 8;
+  const int64_t pair = (int64_t)blockIdx.x * (256 / LANES) + threadIdx.x / LANES;      // t * Hq + h
   if (pair >= (int64_t)c * Hq) return;
-  const int lane = threadIdx.x & 63;
-  const int t = (int)(pair / Hq), h = (int)(pair % Hq);
+  const int lane = threadIdx.x % LANES;
+  const bf16x8 x = *(const bf16x8*)(o + pair * DH + lane * 8), y = *(const bf16x8*)(d_o + pair * DH + lane * 8);
   float s = 0.f;
-  if (lane < DH / 2) {
-    const int64_t base = pair * DH + lane * 2;
-    s = (float)o[base] * (float)d_o[base] + (float)o[base + 1] * (float)d_o[base + 1];
-  }
-  s = wave_sum(s);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) s += (float)x[e] * (float)y[e];
+#pragma unroll
+  for (int off = LANES / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, WAVE);
   if (lane == 0) {
+    const int t = (int)(pair / Hq), h = (int)(pair % Hq);
     delta[(int64_t)h * c + t] = s;
     const float l = lse[(int64_t)h * c + t];
     lse2[(int64_t)h * c + t] = l == -INFINITY ? 0.0f : FP32_STATS<DH> ? l : l * LOG2E;   // a query that saw no key: its scores are all masked anyway
@@ -1103,29 +1159,39 @@ static hipError_t backward_dh(const AttnArgs& a, hipStream_t st) {
   if (a.q_len == 0) return hipSuccess;
   const int64_t pairs = (int64_t)a.q_len * a.Hq;
   float* lse2 = a.delta + pairs;   // second half of the [2, Hq, c] scratch
-  attn_delta_mfma_k<DH><<<(unsigned)cdiv(pairs, 4), 256, 0, st>>>((const bf16_t*)a.o, (const bf16_t*)a.d_o, a.lse, a.delta, lse2, a.Hq,
+  attn_delta_mfma_k<DH><<<(unsigned)cdiv(pairs, 256 / (DH / 8)), 256, 0, st>>>((const bf16_t*)a.o, (const bf16_t*)a.d_o, a.lse, a.delta, lse2, a.Hq,
                                                               a.q_len);
-  auto launch_dq = [&](auto kernel, int64_t n) {
-    kernel<<<dim3((unsigned)n, a.Hq), AT_THREADS, 0, st>>>((const bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v, (const bf16_t*)a.d_o,
-                                                           a.lse, a.delta, (bf16_t*)a.dq, a.Hq, a.Hkv, a.q_start, a.q_len, a.scale, a.rope_q,
-                                                           a.window, a.kv_first);
-  };
-  if (half_tiles_fill_better(a)) launch_dq(attn_bwd_dq_mfma_k<DH, true>, cdiv(a.q_len, TQ / 2));
-  else launch_dq(attn_bwd_dq_mfma_k<DH, false>, cdiv(a.q_len, TQ));
   // key blocks that no query of the chunk can see (before the padding ends, or older than the first query's window)
   // are not launched: their dK/dV contribution is zero
-  const int kb0 = attn_first_key_block(a), kb1 = (int)cdiv(a.q_start + a.q_len, KV_TILE);
-  if (kb1 > kb0) {
+  const int kb0 = attn_first_key_block(a), kb1 = (int)cdiv(a.q_start + a.q_len, KV_TILE), key_blocks = std::max(0, kb1 - kb0);
+  const int slices = std::max(1, a.dkv_slices);
+  float* part = slices > 1 ? a.dkv_scratch : nullptr;
+  const bool halves = half_tiles_fill_better(a);
+  const int64_t n_dkv = (int64_t)key_blocks * a.Hkv * (part ? slices : 1), q_blocks = cdiv(a.q_len, halves ? TQ / 2 : TQ);
+  const bf16_t *q = (const bf16_t*)a.q, *k = (const bf16_t*)a.k, *v = (const bf16_t*)a.v, *d_o = (const bf16_t*)a.d_o;
+  if (n_dkv > 0 && n_dkv + q_blocks * a.Hq <= MERGED_MAX) {
+    auto launch = [&](auto kernel) {
+      kernel<<<(unsigned)(n_dkv + q_blocks * a.Hq), AT_THREADS, 0, st>>>(q, k, v, d_o, a.lse, lse2, a.delta, (bf16_t*)a.dq, a.dk, a.dv, a.Hq, a.Hkv, a.q_start,
+                                                                         a.q_len, a.scale, a.rope_q, a.window, a.kv_first, kb0, key_blocks, slices, part,
+                                                                         (int)q_blocks);
+    };
+    if (halves) launch(attn_bwd_mfma_k<DH, true>);
+    else launch(attn_bwd_mfma_k<DH, false>);
+  } else {
+    auto launch_dq = [&](auto kernel) {
+      kernel<<<dim3((unsigned)q_blocks, a.Hq), AT_THREADS, 0, st>>>(q, k, v, d_o, a.lse, a.delta, (bf16_t*)a.dq, a.Hq, a.Hkv, a.q_start, a.q_len, a.scale,
+                                                                    a.rope_q, a.window, a.kv_first);
+    };
+    if (halves) launch_dq(attn_bwd_dq_mfma_k<DH, true>);
+    else launch_dq(attn_bwd_dq_mfma_k<DH, false>);
+    if (n_dkv > 0)
+      attn_bwd_dkv_mfma_k<DH><<<dim3((unsigned)key_blocks, a.Hkv, part ? (unsigned)slices : 1u), KV_THREADS, 0, st>>>(
+          q, k, v, d_o, lse2, a.delta, a.dk, a.dv, a.Hq, a.Hkv, a.q_start, a.q_len, a.scale, a.window, a.kv_first, kb0, slices, part);
+  }
+  if (part) {
     const int64_t first = (int64_t)kb0 * KV_TILE, n = (a.q_start + a.q_len - first) * a.Hkv * DH;
-    const int slices = std::max(1, a.dkv_slices);
-    float* part = slices > 1 ? a.dkv_scratch : nullptr;
-    dim3 gk((unsigned)(kb1 - kb0), a.Hkv, part ? (unsigned)slices : 1u);
-    attn_bwd_dkv_mfma_k<DH><<<gk, KV_THREADS, 0, st>>>((const bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v, (const bf16_t*)a.d_o,
-                                                   lse2, a.delta, a.dk, a.dv, a.Hq, a.Hkv, a.q_start, a.q_len, a.scale,
-                                                   a.window, a.kv_first, kb0, slices, part);
-    if (part)
-      attn_dkv_sum_k<<<(unsigned)cdiv(n / 2, 256), 256, 0, st>>>((const float4*)part, slices, n / 4,
-                                                                  (float4*)(a.dk + first * a.Hkv * DH), (float4*)(a.dv + first * a.Hkv * DH));
+    attn_dkv_sum_k<<<(unsigned)cdiv(n / 2, 256), 256, 0, st>>>((const float4*)part, slices, n / 4, (float4*)(a.dk + first * a.Hkv * DH),
+                                                               (float4*)(a.dv + first * a.Hkv * DH));
   }
   return hipGetLastError();
 }

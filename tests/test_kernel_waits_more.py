@@ -1,0 +1,13 @@
+"""The waits of further kernels whose LDS is refilled by direct-to-LDS loads, walked as in test_kernel_waits: the attention backward in one
+launch and the GEMM for outputs of few tiles consume every fragment (or wait for it) within the slot in which it is read."""
+import pytest
+
+from test_kernel_waits import _named, barriers_passed_unwaited, built  # noqa: F401
+
+
+@pytest.mark.parametrize("part,instances", [("15attn_bwd_mfma_k", 4), ("10gemm_few_k", 12)])
+def test_reads_are_waited_for_within_the_slot(built, part, instances):  # noqa: F811
+    found = _named(built, (part,))
+    assert len(found) == instances
+    worst = {n: barriers_passed_unwaited(c) for n, c in found.items()}
+    assert max(worst.values()) == 0, {n: w for n, w in worst.items() if w}
