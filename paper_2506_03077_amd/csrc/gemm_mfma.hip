@@ -689,7 +689,10 @@ __global__ __launch_bounds__(NTHREADS) void gemm_mfma_group_k(const GroupArgs ga
                           g.lda, g.ldb, g.ldc, tm, tn, smem, partial, ga.part * 4);
 }
 
-// The tiles whose reduction was split: C (=|+=) sum of the partial tiles in a fixed order, rounded once.  Sixteen workgroups per tile.
+// The tiles whose reduction was split: C (=|+=) sum of the partial tiles in a fixed order, rounded once.  Few tiles of many parts are bound by the
+// latency of the parts' reads: up to TAIL_AHEAD of them are under way at once, and a tile is dealt to 64 workgroups (one access per lane and part)
+// where 16 per tile, four accesses per lane one after the other, would leave CUs idle (8 tiles of 27 parts 34.8 -> 12.5 us; 112 of 2: 15.7 both).
+constexpr int TAIL_AHEAD = 8;
 struct TailProblem { void* C; int M, N; int64_t ldc; int tile_begin, tiles_m, tiles_n; };
 struct TailArgs {
   TailProblem p[MAX_GROUP];
@@ -699,6 +702,7 @@ struct TailArgs {
   int k_steps, scratch_tiles;
   const float* scratch;
   int part;                     // floats of a partial tile
+  int blocks;                   // workgroups per tile: 16 or 64
 };
 template <int MODE>
 __global__ __launch_bounds__(256) void splitk_tail_k(const TailArgs ta) {
@@ -709,7 +713,7 @@ __global__ __launch_bounds__(256) void splitk_tail_k(const TailArgs ta) {
     tiles_m0 = (M0 + BM - 1) / BM;
     sc = make_schedule(tiles_m0 * ta.p[0].tiles_n, ta.k_steps, ta.scratch_tiles);
   }
-  const int t = blockIdx.x >> 4;
+  const int t = blockIdx.x / ta.blocks, block = blockIdx.x % ta.blocks;
   if (t >= sc.tail) return;
   const int id = sc.full + t;
   int pi = 0;
@@ -720,13 +724,20 @@ __global__ __launch_bounds__(256) void splitk_tail_k(const TailArgs ta) {
   int tm, tn;
   band_coords(id - g.tile_begin, tiles_m, g.tiles_n, band_height(tiles_m, tiles_m * g.tiles_n, !mode_accumulates(MODE)), tm, tn);
   const int col_l = 4 * (threadIdx.x & 63), col = tn * BN + col_l;
-#pragma unroll
-  for (int p = 0; p < 4; ++p) {
-    const int row_l = (blockIdx.x & 15) * 16 + p * 4 + (threadIdx.x >> 6), row = tm * BM + row_l;
+  for (int row_l = block * 4 + (threadIdx.x >> 6); row_l < BM; row_l += ta.blocks * 4) {
+    const int row = tm * BM + row_l;
     if (row >= M || col >= g.N) continue;
     const float* src = ta.scratch + (int64_t)t * ta.part + row_l * BN + col_l;
-    f32x4 v = *(const f32x4*)src;
-    for (int z = 1; z < sc.splits; ++z) v += *(const f32x4*)(src + (int64_t)z * sc.tail * ta.part);
+    const int64_t step = (int64_t)sc.tail * ta.part;
+    f32x4 v = {0.f, 0.f, 0.f, 0.f}, in[TAIL_AHEAD];
+    for (int z0 = 0; z0 < sc.splits; z0 += TAIL_AHEAD) {
+#pragma unroll
+      for (int z = 0; z < TAIL_AHEAD; ++z)
+        if (z0 + z < sc.splits) in[z] = *(const f32x4*)(src + (z0 + z) * step);
+#pragma unroll
+      for (int z = 0; z < TAIL_AHEAD; ++z)
+        if (z0 + z < sc.splits) v = z0 + z == 0 ? in[z] : v + in[z];
+    }
     if constexpr (MODE == 1) {
       bf16x4 o;
 #pragma unroll
@@ -789,8 +800,9 @@ size_t gemm_scratch_bytes(int max_m, int max_n) {
 static int scratch_tiles_of(const GemmArgs& g, int max_m) {
   return g.scratch && !((uintptr_t)g.scratch & 15) ? (int)std::min<size_t>(N_CU, g.scratch_bytes / (partial_floats(max_m) * sizeof(float))) : 0;
 }
-static hipError_t launch_tail(int mode, const TailArgs& t, int max_tail, hipStream_t st) {
-  const unsigned blocks = (unsigned)max_tail * 16;
+static hipError_t launch_tail(int mode, TailArgs t, int max_tail, hipStream_t st) {
+  t.blocks = max_tail < 64 ? 64 : 16;
+  const unsigned blocks = (unsigned)(max_tail * t.blocks);
   if (mode == 0) splitk_tail_k<0><<<blocks, 256, 0, st>>>(t);
   else if (mode == 1) splitk_tail_k<1><<<blocks, 256, 0, st>>>(t);
   else splitk_tail_k<2><<<blocks, 256, 0, st>>>(t);
