@@ -82,7 +82,8 @@ struct LayerWs {
   float2* rope;                // [T, dh/2] cos/sin
   void *a, *q, *o, *m, *gate, *up, *act, *dact, *dh1_t, *d_o, *dq, *dkc, *dvc;   // per chunk, dt
   float *h1, *dm, *dh1, *da, *proj;                                       // per chunk, fp32 [c, d]
-  float *rstd1, *rstd2, *lse, *delta, *partial;
+  float *rstd1, *rstd2, *lse, *delta;
+  float* partial[MAX_DW_GROUP][2];      // rows that the norm gains' gradients are the column sums of, per chunk of a weight-gradient group: g1, g2
   float* gemm_scratch; size_t gemm_scratch_bytes;
   // Further copies of the operands of the chunk's weight-gradient GEMMs (a, o, m, gate, up, act, dh1_t, dq, dkc, dvc):
   // the weight gradients of dw_group consecutive chunks are added in one launch, so a chunk's operands stay alive
@@ -154,13 +155,14 @@ LayerWs carve_layer(const sbp_layer_cfg* c, void* ws) {
   w.rstd2 = cv.take<float>(cm);
   w.lse = cv.take<float>(cm * c->n_q_heads);
   w.delta = cv.take<float>(2 * cm * c->n_q_heads);
-  w.partial = cv.take<float>(rmsnorm_bwd_partial_floats((int)cm, (int)d));
   w.gemm_scratch_bytes = c->dtype == SBP_BF16 ? gemm_scratch_bytes((int)cm, (int)std::max(d, qd)) : 0;
   w.gemm_scratch = (float*)cv.take_bytes(w.gemm_scratch_bytes);
   {
     const size_t sizes[10] = {cm * d * es, cm * qd * es, cm * d * es, cm * F * es, cm * F * es, cm * F * es,
                               cm * d * es, cm * qd * es, cm * kd * es, cm * kd * es};   // a, o, m, gate, up, act, dh1_t, dq, dkc, dvc
     w.dw_group = dw_group_for(cm, c->dw_group_rows, DW_GROUP_ROWS_LAYER);
+    for (int g = 0; g < w.dw_group; ++g)
+      for (float*& p : w.partial[g]) p = cv.take<float>(rmsnorm_bwd_partial_floats((int)cm, (int)d));
     for (int g = 1; g < w.dw_group; ++g)
       for (int i = 0; i < 10; ++i) w.alt[g - 1][i] = cv.take_bytes(sizes[i]);
   }
@@ -286,7 +288,6 @@ struct LoraCtx {
   void *a_pad[7], *b_pad[7];       // [pad, in], [out, pad] in the storage type, zero beyond the rank
   float *da_pad[7], *db_pad[7];    // fp32 accumulators of the same shapes
   void *P[7], *Q[7];               // [chunk, pad] per adapted matrix
-  float* dg_sink;                  // the norm gains are frozen: their gradient goes nowhere
 };
 } // extern "C"
 
@@ -299,9 +300,6 @@ int32_t layer_backward_impl(const sbp_layer_cfg* c, const sbp_layer_weights* w, 
   const size_t es = dtype_size(dt);
   const int T = c->seq_len, cm = std::min(c->chunk, T), d = c->hidden, F = c->mlp_width;
   const int qd = c->n_q_heads * c->head_dim, kd = c->n_kv_heads * c->head_dim, half = c->head_dim / 2;
-  float* dg1 = lora ? lora->dg_sink : g->g1;
-  float* dg2 = lora ? lora->dg_sink + d : g->g2;
-
   HIPCHK(rope_table(s_all.rope, T, c->head_dim, c->rope_theta, c->pos_offset, st));
   // Weight-gradient GEMMs waiting for their launch (a group of chunks' worth).  A group may span sequences: short samples would
   // otherwise read and write every dW once each (four samples of 640 tokens at 7B widths: 2.3 of 8.8 ms).  The K/V pass of the next
@@ -309,28 +307,31 @@ int32_t layer_backward_impl(const sbp_layer_cfg* c, const sbp_layer_weights* w, 
   const bool across = (size_t)cm * F / d >= (size_t)cm;
   GemmArgs dws[7 * MAX_DW_GROUP];
   int n_dws = 0;
+  ColumnSums gains{};          // of the same chunks (adapter mode: the gains are frozen)
+  if (!lora) { gains.dg[0] = g->g1; gains.dg[1] = g->g2; }
   for (int b = 0; b < c->batch; ++b) {
     const char* xb = at(x, (size_t)b * T, d, es);
     const char* dyb = at(dy, (size_t)b * T, d, es);
     char* dxb = at(dx, (size_t)b * T, d, es);
     const int kv_first = c->seq_first ? c->seq_first[b] : 0;      // rows before it are padding in front of the sequence
     if ((rc = kv_prepass(c, w, s_all, xb, n_dws > 0, st))) return rc;
-    HIPCHK(fill_zero(s_all.dK, (size_t)T * kd * sizeof(float), st));
-    HIPCHK(fill_zero(s_all.dV, (size_t)T * kd * sizeof(float), st));
+    HIPCHK(fill_zero(s_all.dK, (size_t)((char*)(s_all.dV + (size_t)T * kd) - (char*)s_all.dK), st));      // (dV follows dK)
     // Chunks run last to first: rows of dK/dV belonging to chunk i are final once
     // chunks >= i are done (later queries are the only other readers of those
     // keys), so the K/V-side gradient and dx of the chunk can be finished at once.
     const int n_chunks = (int)cdiv(T, cm);
     for (int ci = n_chunks - 1; ci >= 0; --ci) {
       const int r0 = ci * cm, n = std::min(cm, T - r0);
-      const LayerWs s = chunk_view(s_all, n_dws / 7);
+      const int set = n_dws / 7;
+      const LayerWs s = chunk_view(s_all, set);
+      float *partial1 = lora ? nullptr : s_all.partial[set][0], *partial2 = lora ? nullptr : s_all.partial[set][1];
       if ((rc = chunk_reforward(c, w, s, xb, r0, n, kv_first, false, st))) return rc;
       const char* dyc = at(dyb, r0, d, es);
       // ---- MLP backward (the weight-gradient GEMMs of the chunk are deferred to one grouped launch below)
       {   // dact = dy W_d, then the SwiGLU adjoint: gate <- dgate, up <- dup, act <- silu(gate) up.  The adjoint can run as
           // the GEMM's epilogue (dact is then never stored); measured slower than the elementwise pass, so off by default.
         GemmArgs gd = dx_gemm(dyc, w->wdown, s.dact, n, d, F, dt, dt, false);
-        if (fusion_mask() & FUSE_SWIGLU) {
+        if ((fusion_mask() & FUSE_SWIGLU) || !gemm_uses_mfma(gd)) {      // (the shape-agnostic kernel's launches are what it costs)
           gd.swiglu_gate = s.gate; gd.swiglu_up = s.up; gd.swiglu_act = s.act;
           HIPCHK(gemm(gd, st));
         } else {
@@ -343,7 +344,7 @@ int32_t layer_backward_impl(const sbp_layer_cfg* c, const sbp_layer_weights* w, 
         gm.A2 = s.up; gm.B2 = w->wup;
         HIPCHK(gemm(gm, st));
       }
-      HIPCHK(rmsnorm_bwd(dt, s.dm, s.h1, true, w->g2, s.rstd2, dyc, false, s.dh1, s.dh1_t, dg2, s.partial, n, d, st));
+      HIPCHK(rmsnorm_bwd(dt, s.dm, s.h1, true, w->g2, s.rstd2, dyc, false, s.dh1, s.dh1_t, partial2, n, d, st));
       // ---- attention-side backward
       HIPCHK(gemm(dx_gemm(s.dh1_t, w->wo, s.d_o, n, d, qd, dt, dt, false), st));
       AttnArgs aa{};
@@ -355,11 +356,10 @@ int32_t layer_backward_impl(const sbp_layer_cfg* c, const sbp_layer_weights* w, 
       if (dt == DT_BF16) aa.dkv_slices = attn_dkv_slices(aa, s.gemm_scratch_bytes);
       if (aa.dkv_slices > 1) aa.dkv_scratch = s.gemm_scratch;                                   // (idle between GEMMs)
       if (fusion_mask() & FUSE_ROPE_Q) aa.rope_q = s.rope + (size_t)r0 * half;   // dq leaves the kernel rotated back (RoPE's adjoint)
+      // K/V side of rows [r0, r0+n): final now
+      aa.dkc = s.dkc; aa.dvc = s.dvc; aa.rope_k = s.rope + (size_t)r0 * half;
       HIPCHK(attn_backward(aa, st));
       if (!(fusion_mask() & FUSE_ROPE_Q)) HIPCHK(rope_apply(dt, s.dq, s.rope + (size_t)r0 * half, n, c->n_q_heads, c->head_dim, true, st));
-      // ---- K/V side of rows [r0, r0+n): final now
-      HIPCHK(kv_grad_finish(dt, s.dK + (size_t)r0 * kd, s.dV + (size_t)r0 * kd, s.rope + (size_t)r0 * half, s.dkc, s.dvc,
-                            n, c->n_kv_heads, c->head_dim, st));
       {   // da = dq W_q + dkc W_k + dvc W_v
         const GemmArgs qkv[3] = {dx_gemm(s.dq, w->wq, s.da, n, qd, d, dt, DT_F32, false), dx_gemm(s.dkc, w->wk, s.da, n, kd, d, dt, DT_F32, true),
                                  dx_gemm(s.dvc, w->wv, s.da, n, kd, d, dt, DT_F32, true)};
@@ -413,7 +413,16 @@ int32_t layer_backward_impl(const sbp_layer_cfg* c, const sbp_layer_weights* w, 
         }
       }
       HIPCHK(rmsnorm_bwd(dt, s.da, at(xb, r0, d, es), false, w->g1, s.rstd1, s.dh1, true, nullptr, at(dxb, r0, d, es),
-                         dg1, s.partial, n, d, st));
+                         partial1, n, d, st));
+      if (!lora) {
+        gains.partial[0][set] = partial1; gains.partial[1][set] = partial2;
+        gains.blocks[set] = rmsnorm_bwd_partial_rows(n);
+        gains.n = set + 1;
+        if (n_dws == 0) {      // the group's weight gradients are launched
+          HIPCHK(column_sums(gains, 2, d, st));
+          gains.n = 0;
+        }
+      }
     }
   }
   return SBP_OK;
@@ -482,7 +491,6 @@ LoraWs carve_lora(const sbp_layer_cfg* c, const sbp_layer_weights* w, const sbp_
     x.P[j] = cv.take_bytes(cm * rp * es);
     x.Q[j] = cv.take_bytes(cm * rp * es);
   }
-  x.dg_sink = cv.take<float>((size_t)2 * d);
   L.layer_cfg = *c;
   L.layer_cfg.dw_group_rows = 1;          // no weight-gradient passes to group: one set of chunk buffers
   L.layer_ws = cv.take_bytes(0);
@@ -604,14 +612,14 @@ static HeadWs carve_head(const sbp_head_cfg* c, void* ws) {
   h.z = cv.take<float>(cm * (size_t)h.ldz);
   h.dw_group = dw_group_for(cm, c->dw_group_rows, DW_GROUP_ROWS_HEAD);
   for (int g = 0; g < h.dw_group; ++g) h.dz[g] = cv.take_bytes(cm * (size_t)h.ldz * dtype_size(c->dtype));
-  h.row_loss = cv.take<float>(cm);
+  h.row_loss = cv.take<float>(cm * (size_t)dw_group_for(cm, c->dw_group_rows, DW_GROUP_ROWS_HEAD));
   h.target_logit = cv.take<float>(cm);
   h.n_stat = (int)cdiv(c->vocab, GEMM_STAT_COLS);
   h.stats = cv.take<float2>(cm * (size_t)h.n_stat);
   h.seq_weight = cv.take<float>(c->batch);
   h.ell = cv.take<float>(1);
   h.index = cv.take<int32_t>((size_t)rows);
-  h.chunk_rows = cv.take<int32_t>((size_t)cdiv(rows, (int64_t)cm));
+  h.chunk_rows = cv.take<int32_t>((size_t)cdiv(rows, (int64_t)cm) + 1);
   for (int g = 0; g < h.dw_group; ++g) h.hc[g] = cv.take_bytes(cm * c->hidden * dtype_size(c->dtype));
   h.dhc = cv.take_bytes(cm * c->hidden * dtype_size(c->dtype));
   h.gemm_scratch_bytes = c->dtype == SBP_BF16 ? gemm_scratch_bytes((int)cm, c->hidden) : 0;
@@ -664,7 +672,7 @@ int32_t streambp_lmhead_ce_backward(const sbp_head_cfg* c, const void* w, const 
     const int n = (int)std::min<int64_t>(cm, rows - (int64_t)ci * cm);      // upper bound of the chunk's rows
     void* hc = s.hc[n_pending];
     void* dz = s.dz[n_pending];
-    HIPCHK(gather_rows(dt, h, idx, n_dev, hc, n, d, st));
+    if (ci == 0) HIPCHK(gather_rows(dt, h, idx, n_dev, hc, n, d, st));      // (the following chunks': together with the scatter of the chunk before)
     // The logits: fp32 with (max, sum of exp) per row and 256-column block out of the GEMM's epilogue where the MFMA kernel
     // takes the problem - or, better, never as logits at all: the numerator form leaves exp(z - block max) in bf16 directly in
     // the chunk's dz buffer plus the target logits, and the row kernel finishes dz in place.
@@ -693,21 +701,26 @@ int32_t streambp_lmhead_ce_backward(const sbp_head_cfg* c, const void* w, const 
     a.advantages = advantages; a.seq_weight = s.seq_weight; a.row0 = 0; a.row_index = idx; a.rows_dev = n_dev;
     a.rows = n; a.V = V; a.T = c->seq_len;
     a.loss_scale = c->loss_scale; a.clip_eps = c->clip_eps; a.kl_beta = c->kl_beta; a.kl_mode = c->kl_mode;
-    a.row_loss = s.row_loss;
+    a.row_loss = s.row_loss + (size_t)n_pending * cm;
     HIPCHK(head_rows(a, st));
-    HIPCHK(reduce_add(s.row_loss, n, c->objective == SBP_OBJ_DPO ? s.ell : loss, st, n_dev));
     GemmArgs gh = dx_gemm(dz, w, s.dhc, n, V, d, dt, dt, false);
     gh.lda = s.ldz; gh.a_padded = padded;
     gh.rows_dev = n_dev;
     HIPCHK(gemm(gh, st));
-    HIPCHK(scatter_rows(dt, s.dhc, idx, n_dev, dh, n, d, st));
     pending[n_pending] = dw_gemm(dz, hc, dw, n, V, d, dt, c->grad_dtype);
     pending[n_pending].lda = s.ldz; pending[n_pending].a_padded = padded;
     pending[n_pending].rows_dev = n_dev;
     if (++n_pending == s.dw_group || ci + 1 == n_chunks) {
       HIPCHK(gemm_batch(pending, n_pending, st));
+      // the active rows of the group's chunks are one list: its loss terms are summed together
+      const int64_t first = (int64_t)(ci + 1 - n_pending) * cm;
+      HIPCHK(reduce_add(s.row_loss, n_pending * cm, c->objective == SBP_OBJ_DPO ? s.ell : loss, st, s.chunk_rows + n_chunks, (int)std::min<int64_t>(first, INT32_MAX)));
       n_pending = 0;
     }
+    const RowMove out{s.dhc, idx, n_dev, dh, n};
+    if (ci + 1 < n_chunks)
+      HIPCHK(move_rows(dt, out, RowMove{h, idx + cm, n_dev + 1, s.hc[n_pending], (int)std::min<int64_t>(cm, rows - (int64_t)(ci + 1) * cm)}, d, st));
+    else HIPCHK(move_rows(dt, out, RowMove{}, d, st));
   }
   if (c->objective == SBP_OBJ_DPO)
     HIPCHK(dpo_finish(dt, s.ell, c->kl_beta, dh, rows * d, dw, c->grad_dtype, (int64_t)V * d, loss, st));

@@ -317,12 +317,12 @@ __global__ __launch_bounds__(AG_THREADS) void attn_dq_generic_k(const T* __restr
   }
 }
 
-// ---- dK/dV: 16 keys of one KV head; the waves walk blocks of 16 queries that see some of them, for every query head of the group
+// ---- dK/dV (and dkc, dvc of the chunk's own rows, final with this call): 16 keys of one KV head; the waves walk blocks of 16 queries that see some of them, for every query head of the group
 template <typename T, int DB>
 __global__ __launch_bounds__(AG_THREADS) void attn_dkv_generic_k(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
                                                                  const T* __restrict__ d_o, const float* __restrict__ lse,
                                                                  const float* __restrict__ delta, float* __restrict__ dk, float* __restrict__ dv,
-                                                                 AgShape a) {
+                                                                 AgShape a, T* __restrict__ dkc, T* __restrict__ dvc, const float2* __restrict__ rope) {
   __shared__ float sD[AG_WAVES][DB * 16][17];
   const int kvh = blockIdx.y, u0 = blockIdx.x * 16, G = a.Hq / a.Hkv;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), li = threadIdx.x & 15, lg = (threadIdx.x & 63) >> 4;
@@ -386,24 +386,39 @@ __global__ __launch_bounds__(AG_THREADS) void attn_dkv_generic_k(const T* __rest
     second_product<DB>(av, dt, s, edge, seen, a.dh, at_row(db));
     second_product<DB>(ak, qt, dp, edge, seen, a.dh, at_row(qb));
   }
-  auto leave = [&](const f32x4 (&acc)[DB], float* __restrict__ out) {
+  auto leave = [&](const f32x4 (&acc)[DB], float* __restrict__ out, T* __restrict__ fin, bool rotate) {
 #pragma unroll
     for (int d = 0; d < DB; ++d)
 #pragma unroll
       for (int r = 0; r < 4; ++r) sD[wave][d * 16 + 4 * lg + r][li] = acc[d][r];
     __syncthreads();
-    for (int i = threadIdx.x; i < 16 * a.dh; i += AG_THREADS) {
-      const int row = i / a.dh, e = i % a.dh;
-      if (u0 + row >= n_total) continue;
+    auto total = [&](int row, int e) {
       float x = 0.f;
 #pragma unroll
       for (int w = 0; w < AG_WAVES; ++w) x += sD[w][e][row];
-      out[((int64_t)(u0 + row) * a.Hkv + kvh) * a.dh + e] += x;
+      float* p = out + ((int64_t)(u0 + row) * a.Hkv + kvh) * a.dh + e;
+      return *p += x;
+    };
+    if (!fin) {
+      for (int i = threadIdx.x; i < 16 * a.dh; i += AG_THREADS)
+        if (u0 + i / a.dh < n_total) total(i / a.dh, i % a.dh);
+    } else {                             // (an even head size: what the rotary embedding pairs)
+      const int half = a.dh / 2;
+      for (int i = threadIdx.x; i < 16 * half; i += AG_THREADS) {
+        const int row = i / half, e = i % half, t = u0 + row - a.q_start;
+        if (u0 + row >= n_total) continue;
+        const float x = total(row, e), y = total(row, e + half);
+        if (t < 0) continue;
+        const float2 cs = rotate ? rope[(int64_t)t * half + e] : make_float2(1.f, 0.f);
+        T* f = fin + ((int64_t)t * a.Hkv + kvh) * a.dh + e;
+        stf(f, rotate ? x * cs.x + y * cs.y : x);               // rotation by the negative angle
+        stf(f + half, rotate ? y * cs.x - x * cs.y : y);
+      }
     }
     __syncthreads();
   };
-  leave(ak, dk);
-  leave(av, dv);
+  leave(ak, dk, dkc, true);
+  leave(av, dv, dvc, false);
 }
 
 static AgShape shape_of(const AttnArgs& a, std::initializer_list<const void*> tensors) {
@@ -438,7 +453,8 @@ static hipError_t backward_t(const AttnArgs& a, hipStream_t st) {
     constexpr int DB = decltype(db)::value;
     attn_dq_generic_k<T, DB><<<gq, AG_THREADS, 0, st>>>((const T*)a.q, (const T*)a.k, (const T*)a.v, (const T*)a.o, (const T*)a.d_o, a.lse, a.delta,
                                                         (T*)a.dq, s, a.rope_q);
-    attn_dkv_generic_k<T, DB><<<gk, AG_THREADS, 0, st>>>((const T*)a.q, (const T*)a.k, (const T*)a.v, (const T*)a.d_o, a.lse, a.delta, a.dk, a.dv, s);
+    attn_dkv_generic_k<T, DB><<<gk, AG_THREADS, 0, st>>>((const T*)a.q, (const T*)a.k, (const T*)a.v, (const T*)a.d_o, a.lse, a.delta, a.dk, a.dv, s,
+                                                         (T*)a.dkc, (T*)a.dvc, a.rope_k);
   });
   return hipGetLastError();
 }

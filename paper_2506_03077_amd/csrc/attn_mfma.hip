@@ -1089,17 +1089,41 @@ __global__ __launch_bounds__(AT_THREADS) void attn_bwd_mfma_k(const bf16_t* __re
   }
 }
 
-// dk / dv += sum over the slices of the split form, in their order.  n4: float4s of dk (and of dv)
-__global__ __launch_bounds__(256) void attn_dkv_sum_k(const float4* __restrict__ part, int slices, int64_t n4, float4* __restrict__ dk, float4* __restrict__ dv) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= 2 * n4) return;
-  float4* out = i < n4 ? dk + i : dv + (i - n4);
-  float4 s = *out;
+// dk / dv += sum over the slices of the split form, in their order, keys from `first` on.  A thread takes elements e .. e + 3 and e + DH / 2 .. of a
+// (key, head): what the rotary embedding pairs, so that the chunk's own rows, final with this call, leave as dkc = RoPE^T(dk) and dvc = dv
+// too (optional).
+template <int DH>
+__global__ __launch_bounds__(256) void attn_dkv_sum_k(const float* __restrict__ part, int slices, int64_t pairs, int first, int Hkv, float* __restrict__ dk,
+                                                      float* __restrict__ dv, int q_start, bf16_t* __restrict__ dkc, bf16_t* __restrict__ dvc,
+                                                      const float2* __restrict__ rope) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;      // dk, then dv
+  if (i >= 2 * pairs) return;
+  const bool is_dk = i < pairs;
+  const int64_t p = is_dk ? i : i - pairs, rh = p / (DH / 8);
+  const int e = (int)(p % (DH / 8)) * 4;
+  const int64_t at = rh * DH + e, n = pairs * 8;                  // floats of dk (and of dv)
+  float* out = (is_dk ? dk : dv) + (int64_t)first * Hkv * DH + at;
+  f32x4 x = *(const f32x4*)out, y = *(const f32x4*)(out + DH / 2);
+  const float* src = part + (is_dk ? 0 : n) + at;
+#pragma unroll 4
   for (int z = 0; z < slices; ++z) {
-    const float4 p = part[(int64_t)z * 2 * n4 + i];
-    s.x += p.x; s.y += p.y; s.z += p.z; s.w += p.w;
+    x += *(const f32x4*)(src + z * 2 * n);
+    y += *(const f32x4*)(src + z * 2 * n + DH / 2);
   }
-  *out = s;
+  *(f32x4*)out = x;
+  *(f32x4*)(out + DH / 2) = y;
+  const int64_t row = first + rh / Hkv - q_start;
+  if (!dkc || row < 0) return;
+  bf16x4 u, w;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const float2 cs = is_dk ? rope[row * (DH / 2) + e + r] : make_float2(1.f, 0.f);
+    u[r] = (bf16_t)(is_dk ? x[r] * cs.x + y[r] * cs.y : x[r]);    // rotation by the negative angle
+    w[r] = (bf16_t)(is_dk ? y[r] * cs.x - x[r] * cs.y : y[r]);
+  }
+  bf16_t* fin = (is_dk ? dkc : dvc) + (row * Hkv + rh % Hkv) * DH + e;
+  *(bf16x4*)fin = u;
+  *(bf16x4*)(fin + DH / 2) = w;
 }
 
 // delta[h, t] = sum_j d_o[t,h,j] * o[t,h,j]  (DH / 8 lanes per (t, h), 16 bytes of each tensor per lane)
@@ -1134,7 +1158,7 @@ static bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 // the MFMA kernels move 16 bytes per lane: every tensor they touch must be 16-byte aligned
 bool attn_mfma_aligned(const AttnArgs& a, bool backward) {
   if (!aligned16(a.q) || !aligned16(a.k) || !aligned16(a.v) || !aligned16(a.o) || !aligned16(a.dkv_scratch) || ((uintptr_t)a.rope_q & 7)) return false;
-  return !backward || (aligned16(a.d_o) && aligned16(a.dq) && aligned16(a.dk) && aligned16(a.dv));
+  return !backward || (aligned16(a.d_o) && aligned16(a.dq) && aligned16(a.dk) && aligned16(a.dv) && aligned16(a.dkc) && aligned16(a.dvc));
 }
 
 // Rounds of 256 workgroups (one per CU), a half query tile costing half a round: the half tiles where they leave fewer CUs idle.
@@ -1189,9 +1213,15 @@ static hipError_t backward_dh(const AttnArgs& a, hipStream_t st) {
           q, k, v, d_o, lse2, a.delta, a.dk, a.dv, a.Hq, a.Hkv, a.q_start, a.q_len, a.scale, a.window, a.kv_first, kb0, slices, part);
   }
   if (part) {
-    const int64_t first = (int64_t)kb0 * KV_TILE, n = (a.q_start + a.q_len - first) * a.Hkv * DH;
-    attn_dkv_sum_k<<<(unsigned)cdiv(n / 2, 256), 256, 0, st>>>((const float4*)part, slices, n / 4, (float4*)(a.dk + first * a.Hkv * DH),
-                                                               (float4*)(a.dv + first * a.Hkv * DH));
+    const int first = kb0 * KV_TILE;
+    const int64_t pairs = (int64_t)(a.q_start + a.q_len - first) * a.Hkv * (DH / 8);
+    attn_dkv_sum_k<DH><<<(unsigned)cdiv(2 * pairs, 256), 256, 0, st>>>(part, slices, pairs, first, a.Hkv, a.dk, a.dv, a.q_start, (bf16_t*)a.dkc, (bf16_t*)a.dvc,
+                                                                       a.rope_k);
+    if (first <= a.q_start) return hipGetLastError();
+  }
+  if (a.dkc) {      // (also where some of the chunk's own keys, all hidden, come before the first visible block)
+    hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : kv_grad_finish(a.dt, a.dk + (int64_t)a.q_start * a.Hkv * DH, a.dv + (int64_t)a.q_start * a.Hkv * DH, a.rope_k, a.dkc, a.dvc, a.q_len, a.Hkv, DH, st);
   }
   return hipGetLastError();
 }

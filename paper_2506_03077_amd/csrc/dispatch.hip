@@ -111,7 +111,7 @@ hipError_t gemm(const GemmArgs& g, hipStream_t st) {
   if (g.numer_targets) {
     if (!gemm_numerators_supported(g)) return hipErrorInvalidValue;               // only the MFMA store form has them
   } else if (g.row_stats && !gemm_row_stats_supported(g)) return hipErrorInvalidValue;   // only the MFMA store form emits them
-  if (g.swiglu_gate && !(gemm_uses_mfma(g) && gemm_mfma_swiglu_ok(g))) {   // no fused epilogue for this problem: product, then the elementwise kernel
+  if (g.swiglu_gate && (gemm_uses_mfma(g) ? !gemm_mfma_swiglu_ok(g) : g.acc || g.A2)) {   // no fused epilogue for this problem: product, then the elementwise kernel
     GemmArgs plain = g;
     plain.swiglu_gate = plain.swiglu_up = plain.swiglu_act = nullptr;
     hipError_t e = gemm(plain, st);

@@ -225,7 +225,7 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_k(const DN* __restrict__ dnor
       if (out_f32) out_f32[row * d + j] = v;
       if (out_t) stf(out_t + row * d + j, v);
     }
-    partial[(int64_t)blockIdx.x * d + j] = dgj;
+    if (partial) partial[(int64_t)blockIdx.x * d + j] = dgj;
   }
 }
 
@@ -271,12 +271,13 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_vec_k(const DN* __restrict__ 
         }
         if (out_f32) store8(out_f32 + row * d + j, o);
         if (out_t) store8(out_t + row * d + j, o);
-        store8(sdg + (int64_t)wave * d + j, dg);
+        if (partial) store8(sdg + (int64_t)wave * d + j, dg);
       }
     }
-  } else {
+  } else if (partial) {
     for (int j = lane; j < d; j += 64) sdg[(int64_t)wave * d + j] = 0.f;
   }
+  if (!partial) return;
   __syncthreads();
   for (int j = threadIdx.x; j < d; j += blockDim.x)
     partial[(int64_t)blockIdx.x * d + j] = (sdg[j] + sdg[d + j]) + (sdg[2 * d + j] + sdg[3 * d + j]);
@@ -286,15 +287,20 @@ static bool rmsnorm_bwd_vec_ok(int d, const void* a, const void* b, const void* 
   return d % 8 == 0 && d <= 512 * RV_MAX_IT && al(a) && al(b) && al(c) && al(e) && al(f) && al(h);
 }
 
-// dg[j] += sum_b partial[b][j]: 64 columns per workgroup, the partial rows dealt to 16 waves, fixed summation order.
+// dg[j] += sum over the given partial rows, in their order: 64 columns per workgroup, the rows of a buffer dealt to 16 waves, fixed summation
+// order.  The buffers of a group of chunks and of both norms of a layer go in one launch (a launch per chunk and norm took 4 to 5 us each).
 constexpr int CS_WAVES = 16;
-__global__ __launch_bounds__(CS_WAVES * 64) void colsum_accum_k(const float* __restrict__ partial, float* __restrict__ dg, int nblk, int d) {
+__global__ __launch_bounds__(CS_WAVES * 64) void colsum_accum_k(const ColumnSums cs, int d) {
   __shared__ float red[CS_WAVES][64];
-  const int j = blockIdx.x * 64 + (threadIdx.x & 63), part = threadIdx.x >> 6;
+  const int j = blockIdx.x * 64 + (threadIdx.x & 63), part = threadIdx.x >> 6, which = blockIdx.y;
   float s = 0.f;
   if (j < d) {
+    for (int i = 0; i < cs.n; ++i) {
+      const float* partial = cs.partial[which][i];
+      const int nblk = cs.blocks[i];
 #pragma unroll 8
-    for (int b = part; b < nblk; b += CS_WAVES) s += partial[(int64_t)b * d + j];
+      for (int b = part; b < nblk; b += CS_WAVES) s += partial[(int64_t)b * d + j];
+    }
   }
   red[part][threadIdx.x & 63] = s;
   __syncthreads();
@@ -302,15 +308,21 @@ __global__ __launch_bounds__(CS_WAVES * 64) void colsum_accum_k(const float* __r
     float t = 0.f;
 #pragma unroll
     for (int w = 0; w < CS_WAVES; ++w) t += red[w][threadIdx.x];
-    dg[j] += t;
+    cs.dg[which][j] += t;
   }
 }
+hipError_t column_sums(const ColumnSums& cs, int n_dg, int d, hipStream_t st) {
+  if (cs.n == 0) return hipSuccess;
+  colsum_accum_k<<<dim3((unsigned)cdiv(d, 64), (unsigned)n_dg), CS_WAVES * 64, 0, st>>>(cs, d);
+  return hipGetLastError();
+}
+int rmsnorm_bwd_partial_rows(int rows) { return (int)cdiv(rows, RB); }
 
 size_t rmsnorm_bwd_partial_floats(int rows, int d) { return (size_t)cdiv(rows, RB) * (size_t)d; }
 
 hipError_t rmsnorm_bwd(int dt, const float* dnorm, const void* xin, bool x_is_f32, const void* g,
                        const float* rstd, const void* res, bool res_is_f32, float* out_f32, void* out_t,
-                       float* dg, float* partial, int rows, int d, hipStream_t st) {
+                       float* partial, int rows, int d, hipStream_t st) {
   if (rows == 0) return hipSuccess;
   const int nblk = (int)cdiv(rows, RB);
   const bool vec = rmsnorm_bwd_vec_ok(d, dnorm, xin, g, res, out_f32, out_t);
@@ -331,9 +343,6 @@ hipError_t rmsnorm_bwd(int dt, const float* dnorm, const void* xin, bool x_is_f3
     else RB_LAUNCH(T, T, T);
   });
 #undef RB_LAUNCH
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  colsum_accum_k<<<(unsigned)cdiv(d, 64), CS_WAVES * 64, 0, st>>>(partial, dg, nblk, d);
   return hipGetLastError();
 }
 
@@ -355,8 +364,9 @@ hipError_t rmsnorm_bwd_plain(int dt, const void* dy, const void* x, const void* 
   });
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  colsum_accum_k<<<(unsigned)cdiv(d, 64), CS_WAVES * 64, 0, st>>>(partial, dg, nblk, d);
-  return hipGetLastError();
+  ColumnSums cs{};
+  cs.n = 1; cs.partial[0][0] = partial; cs.blocks[0] = nblk; cs.dg[0] = dg;
+  return column_sums(cs, 1, d, st);
 }
 
 // ---------------------------------------------------------------- SwiGLU --

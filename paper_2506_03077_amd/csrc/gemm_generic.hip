@@ -53,8 +53,11 @@ struct GenericProblem { void* C; int64_t ldc; int M, N, ta, tb, seg0, nseg, tile
 template <int NP, int NS> struct GenericArgs { int n; GenericProblem p[NP]; GenericSegment s[NS]; };
 using GenericAll = GenericArgs<GENERIC_PROBLEMS, GENERIC_SEGMENTS>;
 
+// gate (optional; rows of ldc elements, like C, which is then not written): the product is the gradient wrt act = silu(gate) * up; act gets that
+// value, gate and up their gradients, in place.
+struct GenericSwiglu { void *gate, *up, *act; };
 template <typename TI, typename TO, bool ACC, int NP, int NS>
-__global__ __launch_bounds__(WAVES * 64) void gemm_generic_k(const GenericArgs<NP, NS> ga) {
+__global__ __launch_bounds__(WAVES * 64) void gemm_generic_k(const GenericArgs<NP, NS> ga, const GenericSwiglu sw) {
   int pi = 0;
 #pragma unroll
   for (int i = 1; i < NP; ++i)
@@ -121,7 +124,16 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_generic_k(const GenericArgs<N
     if (m0 + row >= M || n0 + col >= N) continue;
     float v = 0.f;
     for (int w = 0; w < waves; ++w) v += part[w][row][col];
-    TO* p = (TO*)g.C + (int64_t)(m0 + row) * g.ldc + n0 + col;
+    const int64_t at = (int64_t)(m0 + row) * g.ldc + n0 + col;
+    if (NP == 1 && !ACC && sw.gate) {
+      TO *gate = (TO*)sw.gate + at, *up = (TO*)sw.up + at;
+      const float z = ldf(gate), u = ldf(up), s = 1.0f / (1.0f + __expf(-z));
+      if (sw.act) stf((TO*)sw.act + at, z * s * u);
+      stf(gate, v * u * s * (1.0f + z * (1.0f - s)));
+      stf(up, v * z * s);
+      continue;
+    }
+    TO* p = (TO*)g.C + at;
     if (ACC) stf(p, ldf(p) + v); else stf(p, v);
   }
 }
@@ -173,6 +185,7 @@ static bool generic_args(const GemmArgs* gs, int n, bool sum, GenericAll& ga, in
 hipError_t gemm_generic(const GemmArgs* gs, int n, bool sum, hipStream_t st) {
   GenericAll ga;
   int64_t tiles;
+  if (gs[0].swiglu_gate && (n != 1 || gs[0].acc || gs[0].A2)) return hipErrorInvalidValue;
   if (!generic_args(gs, n, sum, ga, tiles)) return hipErrorInvalidValue;
   if (ga.n == 0) return hipSuccess;
   const GemmArgs& g = gs[0];
@@ -182,7 +195,7 @@ hipError_t gemm_generic(const GemmArgs* gs, int n, bool sum, hipStream_t st) {
     args.n = ga.n;
     std::copy_n(ga.p, std::min<size_t>(std::size(args.p), ga.n), args.p);
     std::copy_n(ga.s, std::min<size_t>(std::size(args.s), n_seg), args.s);
-    kernel<<<(unsigned)tiles, WAVES * 64, 0, st>>>(args);
+    kernel<<<(unsigned)tiles, WAVES * 64, 0, st>>>(args, GenericSwiglu{gs[0].swiglu_gate, gs[0].swiglu_up, gs[0].swiglu_act});
   };
 #define GG(TI, TO, ACC)                                                                                        \
   do {                                                                                                         \

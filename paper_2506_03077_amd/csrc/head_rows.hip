@@ -190,18 +190,19 @@ hipError_t head_rows(const HeadRowArgs& a, hipStream_t st) {
 }
 
 // out += sum(v[0..n)) with a fixed summation tree (one workgroup).
-__global__ __launch_bounds__(256) void reduce_add_k(const float* __restrict__ v, int n, float* __restrict__ out,
-                                                    const int* __restrict__ n_dev) {
+__global__ __launch_bounds__(1024) void reduce_add_k(const float* __restrict__ v, int n, float* __restrict__ out,
+                                                     const int* __restrict__ n_dev, int first) {
   __shared__ float red[16];
-  if (n_dev) n = min(n, max(0, *n_dev));
+  if (n_dev) n = min(n, max(0, *n_dev - first));
   float s = 0.f;
-  for (int i = threadIdx.x; i < n; i += 256) s += v[i];
+#pragma unroll 4
+  for (int i = threadIdx.x; i < n; i += 1024) s += v[i];
   s = block_sum(s, red);
   if (threadIdx.x == 0) *out += s;
 }
-hipError_t reduce_add(const float* v, int n, float* out, hipStream_t st, const int* n_dev) {
+hipError_t reduce_add(const float* v, int n, float* out, hipStream_t st, const int* n_dev, int first) {
   if (n == 0) return hipSuccess;
-  reduce_add_k<<<1, 256, 0, st>>>(v, n, out, n_dev);
+  reduce_add_k<<<1, 1024, 0, st>>>(v, n, out, n_dev, first);
   return hipGetLastError();
 }
 
@@ -229,6 +230,7 @@ __global__ __launch_bounds__(1024) void compact_active_k(const int32_t* __restri
     if ((uint32_t)targets[r] < (uint32_t)V) index[pos++] = (int32_t)r;
   const int total = cnt[1023];
   for (int i = tid; i < n_chunks; i += 1024) chunk_rows[i] = min(chunk, max(0, total - i * chunk));
+  if (tid == 0) chunk_rows[n_chunks] = total;
 }
 hipError_t compact_active(const int32_t* targets, int64_t rows, int chunk, int V, int32_t* index, int32_t* chunk_rows, int n_chunks,
                           hipStream_t st) {
@@ -236,31 +238,35 @@ hipError_t compact_active(const int32_t* targets, int64_t rows, int chunk, int V
   return hipGetLastError();
 }
 
-template <typename T, bool SCATTER>
-__global__ __launch_bounds__(256) void move_rows_k(const T* __restrict__ src, const int32_t* __restrict__ index,
-                                                   const int* __restrict__ rows_dev, T* __restrict__ dst, int d) {
-  const int r = blockIdx.x;
-  const bool valid = r < *rows_dev;
-  if (SCATTER) {
-    if (!valid) return;
-    const int64_t o = index[r];
-    for (int j = threadIdx.x; j < d; j += 256) dst[o * d + j] = src[(int64_t)r * d + j];
+// One workgroup per row: the rows of a scatter, then those of a gather.
+template <typename T>
+__global__ __launch_bounds__(256) void move_rows_k(RowMove sc, RowMove ga, int d) {
+  const bool scatter = (int)blockIdx.x < sc.max_rows;
+  const int r = scatter ? blockIdx.x : blockIdx.x - sc.max_rows;
+  const RowMove& m = scatter ? sc : ga;
+  const bool valid = r < *m.rows_dev;
+  if (scatter && !valid) return;
+  const int64_t o = valid ? m.index[r] : 0;
+  const T* src = (const T*)m.src + (scatter ? (int64_t)r : o) * d;
+  T* dst = (T*)m.dst + (scatter ? o : (int64_t)r) * d;
+  if (d % 8 == 0 && sizeof(T) == 2 && !(((uintptr_t)src | (uintptr_t)dst) & 15)) {
+    for (int j = threadIdx.x; j < d / 8; j += 256) ((uint4*)dst)[j] = valid ? ((const uint4*)src)[j] : make_uint4(0, 0, 0, 0);
   } else {
-    const int64_t o = valid ? index[r] : 0;
-    for (int j = threadIdx.x; j < d; j += 256) dst[(int64_t)r * d + j] = valid ? src[o * d + j] : (T)0.0f;
+    for (int j = threadIdx.x; j < d; j += 256) dst[j] = valid ? src[j] : (T)0.0f;
   }
 }
-hipError_t gather_rows(int dt, const void* src, const int32_t* index, const int* rows_dev, void* dst, int max_rows, int d, hipStream_t st) {
-  if (max_rows == 0) return hipSuccess;
-  if (dt == DT_BF16) move_rows_k<bf16_t, false><<<max_rows, 256, 0, st>>>((const bf16_t*)src, index, rows_dev, (bf16_t*)dst, d);
-  else move_rows_k<float, false><<<max_rows, 256, 0, st>>>((const float*)src, index, rows_dev, (float*)dst, d);
+hipError_t move_rows(int dt, const RowMove& scatter, const RowMove& gather, int d, hipStream_t st) {
+  const unsigned n = (unsigned)(scatter.max_rows + gather.max_rows);
+  if (n == 0) return hipSuccess;
+  if (dt == DT_BF16) move_rows_k<bf16_t><<<n, 256, 0, st>>>(scatter, gather, d);
+  else move_rows_k<float><<<n, 256, 0, st>>>(scatter, gather, d);
   return hipGetLastError();
 }
+hipError_t gather_rows(int dt, const void* src, const int32_t* index, const int* rows_dev, void* dst, int max_rows, int d, hipStream_t st) {
+  return move_rows(dt, RowMove{}, RowMove{src, index, rows_dev, dst, max_rows}, d, st);
+}
 hipError_t scatter_rows(int dt, const void* src, const int32_t* index, const int* rows_dev, void* dst, int max_rows, int d, hipStream_t st) {
-  if (max_rows == 0) return hipSuccess;
-  if (dt == DT_BF16) move_rows_k<bf16_t, true><<<max_rows, 256, 0, st>>>((const bf16_t*)src, index, rows_dev, (bf16_t*)dst, d);
-  else move_rows_k<float, true><<<max_rows, 256, 0, st>>>((const float*)src, index, rows_dev, (float*)dst, d);
-  return hipGetLastError();
+  return move_rows(dt, RowMove{src, index, rows_dev, dst, max_rows}, RowMove{}, d, st);
 }
 
 // Active rows are those with 0 <= target < V.  A target >= V is a caller error the host cannot see (the ids live on

@@ -112,11 +112,16 @@ hipError_t rmsnorm_fwd(int dt, const void* x, const float* add, const void* g, v
 // adjoint: dnorm [rows,d] fp32 is the gradient wrt the normalised output.
 //   xin: the tensor that was normalised (x_is_f32 ? fp32 : dt);  res: gradient flowing around the norm
 //   (res_is_f32 ? fp32 : dt);  out_f32 / out_t (either may be NULL) = res + dx_norm;
-//   dg += column sums of dnorm * xin * rstd (two-stage, deterministic; `partial` >= rmsnorm_bwd_partial_floats)
+//   partial (may be NULL; rmsnorm_bwd_partial_floats floats) = rows whose column sums are those of dnorm * xin * rstd: what dg grows by, through
+//   column_sums (two-stage, deterministic)
 hipError_t rmsnorm_bwd(int dt, const float* dnorm, const void* xin, bool x_is_f32, const void* g,
                        const float* rstd, const void* res, bool res_is_f32, float* out_f32, void* out_t,
-                       float* dg, float* partial, int rows, int d, hipStream_t st);
+                       float* partial, int rows, int d, hipStream_t st);
 size_t rmsnorm_bwd_partial_floats(int rows, int d);
+int rmsnorm_bwd_partial_rows(int rows);
+// dg[w] += column sums of n buffers partial[w][i] of blocks[i] rows, w < n_dg
+struct ColumnSums { int n; int blocks[8]; const float* partial[2][8]; float* dg[2]; };
+hipError_t column_sums(const ColumnSums& cs, int n_dg, int d, hipStream_t st);
 // dy, x, dx in dt; no residual branch
 hipError_t rmsnorm_bwd_plain(int dt, const void* dy, const void* x, const void* g, const float* rstd, void* dx,
                              float* dg, float* partial, int rows, int d, hipStream_t st);
@@ -164,6 +169,10 @@ struct AttnArgs {
   // writable); backward: q is the rotated tensor the forward left, and dq leaves the kernel already rotated back
   // (the adjoint rotation), i.e. as the gradient wrt the un-rotated projection.
   const float2* rope_q = nullptr;
+  // Optional (backward): the chunk's own rows of dK and dV are final after this call; dkc = T(RoPE^T(dK rows)), dvc = T(dV rows), with the
+  // cos/sin rows [c, dh/2] of the chunk's positions
+  void *dkc = nullptr, *dvc = nullptr;
+  const float2* rope_k = nullptr;
 };
 hipError_t attn_forward(const AttnArgs& a, hipStream_t st);
 hipError_t attn_backward(const AttnArgs& a, hipStream_t st);
@@ -229,15 +238,19 @@ struct HeadRowArgs {
   float* row_loss;          // [rows] scratch: per-row loss term (DPO: per-row signed log-ratio)
 };
 hipError_t head_rows(const HeadRowArgs& a, hipStream_t st);
-// loss += sum(row_loss[0..rows)) in a fixed order
-hipError_t reduce_add(const float* v, int n, float* out, hipStream_t st, const int* n_dev = nullptr);
+// out += sum(v[0..n)) in a fixed order; n_dev (optional): device-side count of the list that v[0] is entry `first` of
+hipError_t reduce_add(const float* v, int n, float* out, hipStream_t st, const int* n_dev = nullptr, int first = 0);
 // per-sequence active counts (0 <= target < V) -> seq_weight[j] = 1/(B*T_o,j) (0 if empty), n_active total - or minus the
 // number of targets >= V if there is any
 hipError_t count_active(const int32_t* targets, int B, int T, int V, float* seq_weight, int64_t* n_active, hipStream_t st);
-// index[0..n_active) = rows with 0 <= target < V in increasing order; chunk_rows[i] = clamp(n_active - i*chunk, 0, chunk)
+// index[0..n_active) = rows with 0 <= target < V in increasing order; chunk_rows[i] = clamp(n_active - i*chunk, 0, chunk) for i < n_chunks,
+// chunk_rows[n_chunks] = n_active
 hipError_t compact_active(const int32_t* targets, int64_t rows, int chunk, int V, int32_t* index, int32_t* chunk_rows, int n_chunks,
                           hipStream_t st);
 // dst[r,:] = src[index[r],:] for r < *rows_dev, zero rows after;  scatter: dst[index[r],:] = src[r,:] for r < *rows_dev
+// move_rows: a scatter and a gather, independent of each other, in one launch
+struct RowMove { const void* src; const int32_t* index; const int* rows_dev; void* dst; int max_rows; };
+hipError_t move_rows(int dt, const RowMove& scatter, const RowMove& gather, int d, hipStream_t st);
 hipError_t gather_rows(int dt, const void* src, const int32_t* index, const int* rows_dev, void* dst, int max_rows, int d, hipStream_t st);
 hipError_t scatter_rows(int dt, const void* src, const int32_t* index, const int* rows_dev, void* dst, int max_rows, int d, hipStream_t st);
 // DPO fix-up: factor = sigmoid(beta*ell)-1 ; scales dh (dt) and dw (fp32) in place, loss += -log sigmoid(beta*ell)

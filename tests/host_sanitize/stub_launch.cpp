@@ -84,12 +84,20 @@ hipError_t rmsnorm_fwd(int dt, const void* x, const float* add, const void* g, v
   rd(x, n * es(dt)); rd(add, n * 4); rd(g, (size_t)d * es(dt)); wr(out, n * es(dt)); wr(sum_out, n * 4); wr(rstd, (size_t)rows * 4);
   return hipSuccess;
 }
+int rmsnorm_bwd_partial_rows(int rows) { return (int)cdiv(rows, 4); }
 hipError_t rmsnorm_bwd(int dt, const float* dnorm, const void* xin, bool x_is_f32, const void* g, const float* rstd, const void* res,
-                       bool res_is_f32, float* out_f32, void* out_t, float* dg, float* partial, int rows, int d, hipStream_t) {
+                       bool res_is_f32, float* out_f32, void* out_t, float* partial, int rows, int d, hipStream_t) {
   const size_t n = (size_t)rows * d;
   rd(dnorm, n * 4); rd(xin, n * (x_is_f32 ? 4 : es(dt))); rd(g, (size_t)d * es(dt)); rd(rstd, (size_t)rows * 4);
-  rd(res, n * (res_is_f32 ? 4 : es(dt))); wr(out_f32, n * 4); wr(out_t, n * es(dt)); wr(dg, (size_t)d * 4);
+  rd(res, n * (res_is_f32 ? 4 : es(dt))); wr(out_f32, n * 4); wr(out_t, n * es(dt));
   wr(partial, rmsnorm_bwd_partial_floats(rows, d) * 4);
+  return hipSuccess;
+}
+hipError_t column_sums(const ColumnSums& cs, int n_dg, int d, hipStream_t) {
+  for (int w = 0; w < n_dg; ++w) {
+    for (int i = 0; i < cs.n; ++i) rd(cs.partial[w][i], (size_t)cs.blocks[i] * d * 4);
+    wr(cs.dg[w], (size_t)d * 4);
+  }
   return hipSuccess;
 }
 hipError_t rmsnorm_bwd_plain(int dt, const void* dy, const void* x, const void* g, const float* rstd, void* dx, float* dg, float* partial,
@@ -134,6 +142,10 @@ static void touch_attn(const AttnArgs& a, bool bwd) {
   if (!bwd) { wr(a.o, qn * es(a.dt)); wr(a.lse, (size_t)a.Hq * a.q_len * 4); return; }
   rd(a.o, qn * es(a.dt)); rd(a.lse, (size_t)a.Hq * a.q_len * 4); rd(a.d_o, qn * es(a.dt)); wr(a.dq, qn * es(a.dt));
   wr(a.dk, kn * 4); wr(a.dv, kn * 4); wr(a.delta, (size_t)2 * a.Hq * a.q_len * 4);
+  if (a.dkc) {
+    const size_t cn = (size_t)a.q_len * a.Hkv * a.dh * es(a.dt);
+    wr(a.dkc, cn); wr(a.dvc, cn); rd(a.rope_k, (size_t)a.q_len * (a.dh / 2) * sizeof(float2));
+  }
   if (a.dkv_scratch) wr(a.dkv_scratch, attn_dkv_scratch_bytes(a, a.dkv_slices));     // the parts of split key blocks
 }
 hipError_t attn_forward(const AttnArgs& a, hipStream_t) { if (a.q_len > 0) touch_attn(a, false); return hipSuccess; }
@@ -151,18 +163,23 @@ hipError_t head_rows(const HeadRowArgs& a, hipStream_t) {
   if (a.rows_dev) rd(a.rows_dev, 4);
   return hipSuccess;
 }
-hipError_t reduce_add(const float* v, int n, float* out, hipStream_t, const int* n_dev) { rd(v, (size_t)n * 4); wr(out, 4); rd(n_dev, 4); return hipSuccess; }
+hipError_t reduce_add(const float* v, int n, float* out, hipStream_t, const int* n_dev, int) { rd(v, (size_t)n * 4); wr(out, 4); rd(n_dev, 4); return hipSuccess; }
 hipError_t count_active(const int32_t* targets, int B, int T, int, float* seq_weight, int64_t* n_active, hipStream_t) {
   rd(targets, (size_t)B * T * 4); wr(seq_weight, (size_t)B * 4); wr(n_active, 8); return hipSuccess;
 }
 hipError_t compact_active(const int32_t* targets, int64_t rows, int, int, int32_t* index, int32_t* chunk_rows, int n_chunks, hipStream_t) {
-  rd(targets, rows * 4); wr(index, rows * 4); wr(chunk_rows, (size_t)n_chunks * 4); return hipSuccess;
+  rd(targets, rows * 4); wr(index, rows * 4); wr(chunk_rows, (size_t)(n_chunks + 1) * 4); return hipSuccess;
 }
-hipError_t gather_rows(int dt, const void* src, const int32_t* index, const int* rows_dev, void* dst, int max_rows, int d, hipStream_t) {
-  (void)src; rd(index, (size_t)max_rows * 4); rd(rows_dev, 4); wr(dst, (size_t)max_rows * d * es(dt)); return hipSuccess;
+hipError_t move_rows(int dt, const RowMove& scatter, const RowMove& gather, int d, hipStream_t) {
+  if (scatter.max_rows > 0) { rd(scatter.src, (size_t)scatter.max_rows * d * es(dt)); rd(scatter.index, (size_t)scatter.max_rows * 4); rd(scatter.rows_dev, 4); }
+  if (gather.max_rows > 0) { rd(gather.index, (size_t)gather.max_rows * 4); rd(gather.rows_dev, 4); wr(gather.dst, (size_t)gather.max_rows * d * es(dt)); }
+  return hipSuccess;
 }
-hipError_t scatter_rows(int dt, const void* src, const int32_t* index, const int* rows_dev, void* dst, int max_rows, int d, hipStream_t) {
-  (void)dst; rd(src, (size_t)max_rows * d * es(dt)); rd(index, (size_t)max_rows * 4); rd(rows_dev, 4); return hipSuccess;
+hipError_t gather_rows(int dt, const void* src, const int32_t* index, const int* rows_dev, void* dst, int max_rows, int d, hipStream_t st) {
+  return move_rows(dt, RowMove{}, RowMove{src, index, rows_dev, dst, max_rows}, d, st);
+}
+hipError_t scatter_rows(int dt, const void* src, const int32_t* index, const int* rows_dev, void* dst, int max_rows, int d, hipStream_t st) {
+  return move_rows(dt, RowMove{src, index, rows_dev, dst, max_rows}, RowMove{}, d, st);
 }
 hipError_t dpo_finish(int dt, const float* ell, float, void* dh, int64_t n_dh, void* dw, int dw_dt, int64_t n_dw, float* loss, hipStream_t) {
   rd(ell, 4); wr(dh, n_dh * es(dt)); wr(dw, n_dw * es(dw_dt)); wr(loss, 4); return hipSuccess;
