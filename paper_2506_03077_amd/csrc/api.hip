@@ -254,6 +254,14 @@ int32_t chunk_reforward(const sbp_layer_cfg* c, const sbp_layer_weights* w, cons
   HIPCHK(attn_forward(aa, st));
   HIPCHK(gemm(fwd_gemm(s.o, w->wo, s.proj, n, d, qd, dt, DT_F32), st));
   HIPCHK(rmsnorm_fwd(dt, xc, s.proj, w->g2, s.m, s.h1, s.rstd2, n, d, c->rms_eps, st));
+  if (with_act) {      // the forward needs neither gate nor up: one product of both whose store applies the gate
+    GemmArgs ga = fwd_gemm(s.m, w->wgate, s.act, n, F, d, dt, dt);
+    ga.glu_up = w->wup;
+    if (gemm_glu_supported(ga)) {
+      HIPCHK(gemm(ga, st));
+      return SBP_OK;
+    }
+  }
   {
     const GemmArgs gu[2] = {fwd_gemm(s.m, w->wgate, s.gate, n, F, d, dt, dt), fwd_gemm(s.m, w->wup, s.up, n, F, d, dt, dt)};
     HIPCHK(gemm_batch(gu, 2, st));
@@ -486,10 +494,12 @@ LoraWs carve_lora(const sbp_layer_cfg* c, const sbp_layer_weights* w, const sbp_
     x.a_pad[j] = cv.take_bytes(rp * ins[i] * es);
     x.b_pad[j] = cv.take_bytes((size_t)outs[i] * rp * es);
     L.bt[j] = cv.take_bytes((size_t)ad->rank * outs[i] * es);                    // s B^T, the merge GEMM's operand
-    x.da_pad[j] = cv.take<float>(rp * ins[i]);
-    x.db_pad[j] = cv.take<float>((size_t)outs[i] * rp);
     x.P[j] = cv.take_bytes(cm * rp * es);
     x.Q[j] = cv.take_bytes(cm * rp * es);
+  }
+  for (int j = 0; j < x.n; ++j) {       // (one after the other: cleared by one launch)
+    x.da_pad[j] = cv.take<float>(rp * x.in_dim[j]);
+    x.db_pad[j] = cv.take<float>((size_t)x.out_dim[j] * rp);
   }
   L.layer_cfg = *c;
   L.layer_cfg.dw_group_rows = 1;          // no weight-gradient passes to group: one set of chunk buffers
@@ -526,25 +536,30 @@ int32_t streambp_layer_lora_backward(const sbp_layer_cfg* c, const sbp_layer_wei
   const void* eff[7] = {L.w_eff.wq, L.w_eff.wk, L.w_eff.wv, L.w_eff.wo, L.w_eff.wgate, L.w_eff.wup, L.w_eff.wdown};
   const LoraCtx& X = L.ctx;
   t_gemm_scratch = nullptr; t_gemm_scratch_bytes = 0;
+  // Operands with the rank rounded up to a multiple of 8, and the effective matrices W + s B A: one pass that reads W, adds the rank-r product
+  // in fp32 and rounds once
+  PadJobs pads{};
+  GemmArgs merge[7];
   for (int j = 0; j < X.n; ++j) {
     const int i = X.which[j], out = X.out_dim[j], in = X.in_dim[j], r = ad->rank;
-    // operands with the rank rounded up to a multiple of 8, and the effective matrix W + s B A: a copy of W, then one pass that reads
-    // it, adds the rank-r product in fp32 and rounds once
-    HIPCHK(pad_matrix(dt, ad->a[i], r, in, false, 1.0f, X.a_pad[j], X.pad, in, st));
-    HIPCHK(pad_matrix(dt, ad->b[i], out, r, false, 1.0f, X.b_pad[j], out, X.pad, st));
-    HIPCHK(pad_matrix(dt, ad->b[i], r, out, true, ad->scale, L.bt[j], r, out, st));
-    HIPCHK(copy_bytes((void*)eff[i], base[i], (size_t)out * in * es, st));
-    HIPCHK(gemm(mk(L.bt[j], X.a_pad[j], (void*)eff[i], out, in, r, out, in, in, true, false, dt, dt, true), st));
-    HIPCHK(fill_zero(X.da_pad[j], (size_t)X.pad * in * sizeof(float), st));
-    HIPCHK(fill_zero(X.db_pad[j], (size_t)out * X.pad * sizeof(float), st));
+    pads.job[pads.n++] = PadJob{ad->a[i], X.a_pad[j], r, in, 0, X.pad, in, 1.0f, 0};
+    pads.job[pads.n++] = PadJob{ad->b[i], X.b_pad[j], out, r, 0, out, X.pad, 1.0f, 0};
+    pads.job[pads.n++] = PadJob{ad->b[i], L.bt[j], r, out, 1, r, out, ad->scale, 0};
+    merge[j] = mk(L.bt[j], X.a_pad[j], (void*)eff[i], out, in, r, out, in, in, true, false, dt, dt, true);
+    merge[j].C0 = base[i];
   }
+  HIPCHK(pad_matrices(dt, pads, st));
+  HIPCHK(gemm_batch(merge, X.n, st));
+  if (X.n > 0) HIPCHK(fill_zero(X.da_pad[0], (size_t)((char*)(X.db_pad[X.n - 1] + (size_t)X.out_dim[X.n - 1] * X.pad) - (char*)X.da_pad[0]), st));
   const LayerWs s_all = carve_layer(&L.layer_cfg, L.layer_ws);
   if ((rc = layer_backward_impl(&L.layer_cfg, &L.w_eff, x, dy, dx, nullptr, &X, s_all, st))) return rc;
+  AddJobs adds{};
   for (int j = 0; j < X.n; ++j) {
     const int i = X.which[j];
-    HIPCHK(add_scaled_block(X.da_pad[j], X.in_dim[j], ad->scale, g->da[i], ad->rank, X.in_dim[j], st));
-    HIPCHK(add_scaled_block(X.db_pad[j], X.pad, ad->scale, g->db[i], X.out_dim[j], ad->rank, st));
+    adds.job[adds.n++] = AddJob{X.da_pad[j], X.in_dim[j], g->da[i], ad->rank, X.in_dim[j], 0};
+    adds.job[adds.n++] = AddJob{X.db_pad[j], X.pad, g->db[i], X.out_dim[j], ad->rank, 0};
   }
+  HIPCHK(add_scaled_blocks(adds, ad->scale, st));
   return SBP_OK;
 }
 

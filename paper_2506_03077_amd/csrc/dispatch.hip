@@ -16,6 +16,7 @@ bool gemm_mfma_pair_ok(const GemmArgs& g);
 bool gemm_mfma_stats_ok(const GemmArgs& g);
 bool gemm_mfma_swiglu_ok(const GemmArgs& g);
 bool gemm_mfma_numer_ok(const GemmArgs& g);
+bool gemm_mfma_glu_ok(const GemmArgs& g);
 bool gemm_mfma_group_eligible(const GemmArgs* gs, int n, bool small_ok);
 hipError_t gemm_mfma_group(const GemmArgs* gs, int n, hipStream_t st);
 bool gemm_mfma_seg_eligible(const GemmArgs* gs, int n);
@@ -46,6 +47,7 @@ void attn_set_force_generic(bool on) { g_force_generic_attn = on; }
 bool gemm_uses_mfma(const GemmArgs& g) { return !g_force_generic_gemm && gemm_mfma_eligible(g); }
 bool gemm_row_stats_supported(const GemmArgs& g) { return gemm_uses_mfma(g) && gemm_mfma_stats_ok(g); }
 bool gemm_numerators_supported(const GemmArgs& g) { return gemm_uses_mfma(g) && gemm_mfma_numer_ok(g); }
+bool gemm_glu_supported(const GemmArgs& g) { return gemm_uses_mfma(g) && gemm_mfma_glu_ok(g); }
 bool attn_uses_mfma(int dt, int dh, int Hq, int Hkv) { return !g_force_generic_attn && attn_mfma_eligible(dt, dh, Hq, Hkv); }
 
 // ---- optional per-launch timing (off by default; events are created when profiling is switched on,
@@ -101,13 +103,21 @@ static hipError_t run_generic(const GemmArgs* gs, int n, bool sum, hipStream_t s
 }
 static bool all_generic(const GemmArgs* gs, int n) {
   for (int i = 0; i < n; ++i)
-    if (gemm_uses_mfma(gs[i]) || gs[i].swiglu_gate || gs[i].row_stats || gs[i].numer_targets) return false;
+    if (gemm_uses_mfma(gs[i]) || gs[i].C0 || gs[i].swiglu_gate || gs[i].row_stats || gs[i].numer_targets) return false;
   return true;
 }
 // the kernels for outputs of few tiles, where their estimate is the lower one
 static bool few_is_faster(const FewChoice& c, double us) { return c.tm && c.us < us; }
 
 hipError_t gemm(const GemmArgs& g, hipStream_t st) {
+  if (g.glu_up) return gemm_glu_supported(g) ? gemm_mfma(g, st) : hipErrorInvalidValue;
+  if (g.C0 && !gemm_uses_mfma(g)) {   // (C0 is as dense as C)
+    hipError_t e = copy_bytes(g.C, g.C0, (size_t)g.M * g.ldc * dtype_size(g.out_dt), st);
+    if (e != hipSuccess) return e;
+    GemmArgs plain = g;
+    plain.C0 = nullptr;
+    return gemm(plain, st);
+  }
   if (g.numer_targets) {
     if (!gemm_numerators_supported(g)) return hipErrorInvalidValue;               // only the MFMA store form has them
   } else if (g.row_stats && !gemm_row_stats_supported(g)) return hipErrorInvalidValue;   // only the MFMA store form emits them

@@ -524,31 +524,45 @@ hipError_t copy_bytes(void* dst, const void* src, size_t bytes, hipStream_t st) 
   return hipGetLastError();
 }
 
-template <typename T>
-__global__ void pad_matrix_k(const T* __restrict__ src, int R, int C, int transposed, float scale, T* __restrict__ dst, int R2, int C2) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (int64_t)R2 * C2) return;
-  const int r = (int)(i / C2), c = (int)(i % C2);
-  float v = 0.f;
-  if (r < R && c < C) v = scale * ldf(transposed ? src + (int64_t)c * R + r : src + (int64_t)r * C + c);
-  stf(dst + i, v);
+// element i of a launch over several jobs -> its job (they follow one another from job[x].begin on)
+template <typename J> __device__ __forceinline__ int job_of(const J& jobs, int64_t i) {
+  int x = 0;
+  for (int k = 1; k < jobs.n; ++k)
+    if (i >= jobs.job[k].begin) x = k;
+  return x;
 }
-hipError_t pad_matrix(int dt, const void* src, int R, int C, bool transposed, float scale, void* dst, int R2, int C2, hipStream_t st) {
-  const int64_t n = (int64_t)R2 * C2;
+template <typename T>
+__global__ __launch_bounds__(256) void pad_matrices_k(const PadJobs jobs, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  const PadJob& p = jobs.job[job_of(jobs, i)];
+  const int64_t at = i - p.begin;
+  const int r = (int)(at / p.C2), c = (int)(at % p.C2);
+  const T* src = (const T*)p.src;
+  float v = 0.f;
+  if (r < p.R && c < p.C) v = p.scale * ldf(p.transposed ? src + (int64_t)c * p.R + r : src + (int64_t)r * p.C + c);
+  stf((T*)p.dst + at, v);
+}
+hipError_t pad_matrices(int dt, PadJobs jobs, hipStream_t st) {
+  int64_t n = 0;
+  for (int k = 0; k < jobs.n; ++k) { jobs.job[k].begin = n; n += (int64_t)jobs.job[k].R2 * jobs.job[k].C2; }
   if (n == 0) return hipSuccess;
-  DISPATCH_DT(dt, T, (pad_matrix_k<T><<<(unsigned)cdiv(n, 256), 256, 0, st>>>((const T*)src, R, C, transposed ? 1 : 0, scale, (T*)dst, R2, C2)));
+  DISPATCH_DT(dt, T, (pad_matrices_k<T><<<(unsigned)cdiv(n, 256), 256, 0, st>>>(jobs, n)));
   return hipGetLastError();
 }
-__global__ void add_scaled_block_k(const float* __restrict__ src, int64_t ld, float scale, float* __restrict__ dst, int R, int C) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (int64_t)R * C) return;
-  const int r = (int)(i / C), c = (int)(i % C);
-  dst[i] += scale * src[(int64_t)r * ld + c];
+__global__ __launch_bounds__(256) void add_scaled_blocks_k(const AddJobs jobs, float scale, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  const AddJob& p = jobs.job[job_of(jobs, i)];
+  const int64_t at = i - p.begin;
+  const int r = (int)(at / p.C), c = (int)(at % p.C);
+  p.dst[at] += scale * p.src[(int64_t)r * p.ld + c];
 }
-hipError_t add_scaled_block(const float* src, int64_t ld, float scale, float* dst, int R, int C, hipStream_t st) {
-  const int64_t n = (int64_t)R * C;
+hipError_t add_scaled_blocks(AddJobs jobs, float scale, hipStream_t st) {
+  int64_t n = 0;
+  for (int k = 0; k < jobs.n; ++k) { jobs.job[k].begin = n; n += (int64_t)jobs.job[k].R * jobs.job[k].C; }
   if (n == 0) return hipSuccess;
-  add_scaled_block_k<<<(unsigned)cdiv(n, 256), 256, 0, st>>>(src, ld, scale, dst, R, C);
+  add_scaled_blocks_k<<<(unsigned)cdiv(n, 256), 256, 0, st>>>(jobs, scale, n);
   return hipGetLastError();
 }
 

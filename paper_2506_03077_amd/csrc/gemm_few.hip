@@ -246,7 +246,7 @@ static bool few_operands_ok(const GemmArgs& g) {
          g.lda < (1 << 22) && g.ldb < (1 << 22) && !((uintptr_t)g.A & 15) && !((uintptr_t)g.B & 15) && !((uintptr_t)g.C & 15) &&
          g.ldc % (g.out_dt == DT_BF16 ? 8 : 4) == 0;
 }
-static bool few_plain(const GemmArgs& g) { return !g.rows_dev && !g.row_stats && !g.numer_targets && !g.swiglu_gate; }
+static bool few_plain(const GemmArgs& g) { return !g.rows_dev && !g.row_stats && !g.numer_targets && !g.swiglu_gate && !g.glu_up && !g.C0; }
 static bool few_segment(FewProblem& p, const GemmArgs& g, const void* A, const void* B) {
   if (p.nseg == FEW_SEG) return false;
   p.seg[p.nseg++] = FewSegment{(const bf16_t*)A, (const bf16_t*)B, g.K, (int)g.lda, (int)g.ldb};

@@ -78,6 +78,7 @@ __device__ __forceinline__ uint32_t frag_off_mnmaj(int col_base, int hi) {
 //       4 = accumulate into a bf16 C (read, add in fp32, round once; weight-gradient form only),
 //       5 = store fp32 and emit per-row (max, sum of exp) pairs over the tile's columns (`stats`)
 //       6 = C is not stored: the tile is the gradient wrt act = silu(gate) * up and the epilogue writes act, d gate, d up
+//       8 = C (bf16) receives silu(A B^T) * (A B2^T): 128 columns of each product per tile, in the halves of B
 //       7 = like 5, but C (bf16) receives exp(c - block max) instead of c, and the value of each row's target column is kept
 constexpr bool mode_accumulates(int mode) { return mode == 2 || mode == 4; }
 constexpr bool mode_splits(int mode) { return mode <= 2; }      // forms whose reduction may be split over workgroups
@@ -115,9 +116,11 @@ template <bool TA, bool TB, int MODE, typename SegmentF>
 __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void* __restrict__ Cv, int M, int N, int64_t lda,
                                           int64_t ldb, int64_t ldc, int tm, int tn, char* smem,
                                           float* __restrict__ partial = nullptr, int partial_bytes = 0, void* __restrict__ stats_out = nullptr,
-                                          SwigluFuse sw = SwigluFuse{}, NumerFuse nf = NumerFuse{}) {
+                                          SwigluFuse sw = SwigluFuse{}, NumerFuse nf = NumerFuse{}, const void* __restrict__ C0 = nullptr,
+                                          const bf16_t* __restrict__ Bu = nullptr) {
   constexpr bool AMN = TA, BMN = !TB;     // operand kept reduction-major in LDS (B stored [N,K] is the K-contiguous case)
-  const int m0 = tm * BM, n0 = tn * BN;
+  constexpr bool GLU = MODE == 8;
+  const int m0 = tm * BM, n0 = tn * (GLU ? BN / 2 : BN);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int grp = wave / NWAVE_N, wn = wave % NWAVE_N;
 
@@ -135,7 +138,7 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       offA[h][i] = pin(load_offset<AMN>(i, h, lda, m0, (AMN ? (M + 7) & ~7 : M) - 1));   // (padded A: whole 8-column granules)
-      offB[h][i] = pin(load_offset<BMN>(i, h, ldb, n0, N - 1));
+      offB[h][i] = pin(load_offset<BMN>(i, GLU ? 0 : h, ldb, n0, N - 1));
     }
   const uint32_t lds0 = lds_addr(smem);
   const uint32_t lds_wave = __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)(threadIdx.x & ~63) * 16u);
@@ -159,6 +162,7 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
     if (nk <= 0) continue;
     const char* gA = uniform_ptr(seg.A + (AMN ? (int64_t)k_begin * lda + m0 : (int64_t)m0 * lda + k_begin));
     const char* gB = uniform_ptr(seg.B + (BMN ? (int64_t)k_begin * ldb + n0 : (int64_t)n0 * ldb + k_begin));
+    const char* gB1 = GLU ? uniform_ptr(Bu + (int64_t)n0 * ldb + k_begin) : gB;      // second half
     // DMA of half h of K step kt (two 16-byte slots per thread).  Reduction rows past the end (the last K step of a ragged
     // reduction) are not loaded: the lane writes zeros into its slot instead.
     auto issue_half = [&](const char* base, const uint32_t (&off)[2], bool mnmaj, int kt, uint32_t dst) {
@@ -180,7 +184,7 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
       issue_half(gA + (int64_t)kt * stepA, offA[h], AMN, kt, lds_wave + (uint32_t)((kt & 1) * STAGE_BYTES + h * HALF_BYTES));
     };
     auto issue_b = [&](int h, int kt) {
-      issue_half(gB + (int64_t)kt * stepB, offB[h], BMN, kt, lds_wave + (uint32_t)(OPERAND_BYTES + (kt & 1) * STAGE_BYTES + h * HALF_BYTES));
+      issue_half((h ? gB1 : gB) + (int64_t)kt * stepB, offB[h], BMN, kt, lds_wave + (uint32_t)(OPERAND_BYTES + (kt & 1) * STAGE_BYTES + h * HALF_BYTES));
     };
     auto read_a = [&](auto stage, int h) {
       const uint32_t O = decltype(stage)::value * STAGE_BYTES + h * HALF_BYTES;
@@ -324,6 +328,34 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
     }
     return;
   }
+  if constexpr (GLU) {
+    // gate and up of a column are the same registers of the two halves
+    __syncthreads();
+#pragma unroll
+    for (int ha = 0; ha < 2; ++ha)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const int row = row_of(ha, i), col = col_of(0, j);
+          bf16x4 o;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const float z = acc[ha][0][i][j][r];
+            o[r] = (bf16_t)(z / (1.0f + __expf(-z)) * acc[ha][1][i][j][r]);
+          }
+          *(bf16x4*)(smem + row * 256 + (((col >> 3) ^ (row & 15)) << 4) + ((col & 4) << 1)) = o;
+        }
+    __syncthreads();
+    const int c16 = threadIdx.x & 15, col = n0 + c16 * 8;
+#pragma unroll
+    for (int p = 0; p < 8; ++p) {
+      const int row = p * 32 + (threadIdx.x >> 4);
+      const i32x4 v = *(const i32x4*)(smem + row * 256 + ((c16 ^ (row & 15)) << 4));
+      if (m0 + row < M && col < N) *(i32x4*)(Cb + (int64_t)(m0 + row) * ldc + col) = v;
+    }
+    return;
+  }
   if constexpr (MODE == 0 || MODE == 4) {
     // fp32 rows: one half of the tile's rows at a time (128 KB)
 #pragma unroll
@@ -341,13 +373,14 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
       __syncthreads();
       if constexpr (MODE == 4) {
         // bf16 C += acc: every element has exactly one owner per launch; the sum is formed in fp32 and rounded once.  The loads
-        // of C (16 bytes per lane) go out before the first use.
+        // of C (16 bytes per lane), or of the C0 that it starts from, go out before the first use.
+        const bf16_t* from = C0 ? (const bf16_t*)C0 : Cb;
         const int c8 = threadIdx.x & 31, col = n0 + c8 * 8;
         bf16x8 old[8];
 #pragma unroll
         for (int p = 0; p < 8; ++p) {
           const int row = m0 + ha * 128 + p * 16 + (threadIdx.x >> 5);
-          if (row < M && col < N) old[p] = *(const bf16x8*)(Cb + (int64_t)row * ldc + col);
+          if (row < M && col < N) old[p] = *(const bf16x8*)(from + (int64_t)row * ldc + col);
         }
 #pragma unroll
         for (int p = 0; p < 8; ++p) {
@@ -606,14 +639,15 @@ __global__ __launch_bounds__(NTHREADS) void gemm_mfma_k(const bf16_t* __restrict
                                                         int64_t ldb, int64_t ldc, const int* __restrict__ rows_dev,
                                                         const bf16_t* __restrict__ A2, const bf16_t* __restrict__ B2,
                                                         float* __restrict__ scratch, int scratch_tiles, void* __restrict__ row_stats,
-                                                        SwigluFuse sw, NumerFuse nf) {
+                                                        SwigluFuse sw, NumerFuse nf, const void* __restrict__ C0) {
   __shared__ __attribute__((aligned(1024))) char smem[SMEM_BYTES + (MODE == 7 ? 2 * NWAVE_N * BM * 4 : 0)];
   const int part = partial_floats(M);
   if (rows_dev) {                     // run-time row count: rows are M (NT / NN) or the reduction K (dW form)
     const int rows = max(0, *rows_dev);
     if (TA) K = min(K, rows); else M = min(M, rows);
   }
-  const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN, k_steps = (K + BK - 1) / BK;
+  constexpr int WIDE = MODE == 8 ? BN / 2 : BN;
+  const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + WIDE - 1) / WIDE, k_steps = (K + BK - 1) / BK;
   const int all_steps = A2 ? 2 * k_steps : k_steps;          // two operand pairs: their reductions follow one another
   if (mode_accumulates(MODE) && all_steps == 0) return;      // nothing to add
   const Schedule sc = make_schedule(tiles_m * tiles_n, all_steps, mode_splits(MODE) ? scratch_tiles : 0);
@@ -632,7 +666,7 @@ __global__ __launch_bounds__(NTHREADS) void gemm_mfma_k(const bf16_t* __restrict
     const int b = max(s0 - i * k_steps, 0) * BK, e = min(min(s1 - i * k_steps, k_steps) * BK, K);
     return KSegment{i ? A2 : A, i ? B2 : B, b, e};
   };
-  gemm_tile<TA, TB, MODE>(A2 ? 2 : 1, segment, Cv, M, N, lda, ldb, ldc, tm, tn, smem, partial, part * 4, row_stats, sw, nf);
+  gemm_tile<TA, TB, MODE>(A2 ? 2 : 1, segment, Cv, M, N, lda, ldb, ldc, tm, tn, smem, partial, part * 4, row_stats, sw, nf, C0, MODE == 8 ? B2 : nullptr);
 }
 
 // Weight-gradient form with a segmented reduction: C += sum_s A_s^T B_s, every segment with its own run-time row
@@ -658,7 +692,7 @@ __global__ __launch_bounds__(NTHREADS) void gemm_mfma_seg_k(const SegLaunch sl, 
 constexpr int MAX_GROUP = 8;
 constexpr int MAX_GSEG = MAX_SEG;   // reduction segments per grouped problem (accumulate form: several chunks' operands)
 struct GroupProblem {
-  const bf16_t* A[MAX_GSEG]; const bf16_t* B[MAX_GSEG]; void* C;
+  const bf16_t* A[MAX_GSEG]; const bf16_t* B[MAX_GSEG]; void* C; const void* C0;
   int M, N, K[MAX_GSEG], nseg;
   int64_t lda, ldb, ldc;
   int tile_begin, tiles_m, tiles_n;
@@ -686,7 +720,7 @@ __global__ __launch_bounds__(NTHREADS) void gemm_mfma_group_k(const GroupArgs ga
     partial = ga.scratch + ((int64_t)split * ga.sched.tail + (id - ga.sched.full)) * ga.part;
   }
   gemm_tile<TA, TB, MODE>(mode_accumulates(MODE) ? g.nseg : 1, [&](int i) { return KSegment{g.A[i], g.B[i], b, min(e, g.K[i])}; }, g.C, g.M, g.N,
-                          g.lda, g.ldb, g.ldc, tm, tn, smem, partial, ga.part * 4);
+                          g.lda, g.ldb, g.ldc, tm, tn, smem, partial, ga.part * 4, nullptr, SwigluFuse{}, NumerFuse{}, MODE == 4 ? g.C0 : nullptr);
 }
 
 // The tiles whose reduction was split: C (=|+=) sum of the partial tiles in a fixed order, rounded once.  Few tiles of many parts are bound by the
@@ -767,7 +801,8 @@ bool gemm_mfma_eligible(const GemmArgs& g) {
   }
   if (g.lda % 8 || g.ldb % 8) return false;
   if (g.lda >= (1 << 22) || g.ldb >= (1 << 22)) return false;   // per-lane byte offsets within a tile are 32-bit
-  if (((uintptr_t)g.A & 15) || ((uintptr_t)g.B & 15) || ((uintptr_t)g.C & 15)) return false;
+  if (((uintptr_t)g.A & 15) || ((uintptr_t)g.B & 15) || ((uintptr_t)g.C & 15) || ((uintptr_t)g.C0 & 15)) return false;
+  if (g.C0 && !(g.acc && g.out_dt == DT_BF16)) return false;
   // fp32 rows, the softmax numerators and the fused SwiGLU adjoint move 4 elements at a time, plain and accumulated bf16 rows 8
   return g.ldc % (g.out_dt == DT_BF16 && !g.numer_targets && !g.swiglu_gate ? 8 : 4) == 0;
 }
@@ -830,10 +865,16 @@ double gemm_mfma_us(const GemmArgs* gs, int n) {      // n > 1: one grouped laun
   return launch_us(tiles, k, scratch_tiles_of(gs[0], max_m), max_m);
 }
 
+// C = silu(A B^T) * (A glu_up^T): from as many tiles on as a grouped launch of both products takes (fewer fill the chip better apart)
+bool gemm_mfma_glu_ok(const GemmArgs& g) {
+  return g.glu_up && !g.ta && g.tb && !g.acc && g.out_dt == DT_BF16 && !g.A2 && !g.row_stats && !g.numer_targets && !g.swiglu_gate && !g.rows_dev &&
+         !((uintptr_t)g.glu_up & 15) && cdiv(g.M, BM) * cdiv(g.N, BN / 2) >= 200;
+}
+
 hipError_t gemm_mfma(const GemmArgs& g, hipStream_t st) {
-  const int tiles_m = (int)cdiv(g.M, BM), tiles_n = (int)cdiv(g.N, BN);
+  const int tiles_m = (int)cdiv(g.M, BM), tiles_n = (int)cdiv(g.N, g.glu_up ? BN / 2 : BN);
   const int k_steps = (int)cdiv(g.K, BK) * (g.A2 ? 2 : 1);
-  const int mode = g.numer_targets ? 7 : g.row_stats ? 5 : g.swiglu_gate ? 6
+  const int mode = g.glu_up ? 8 : g.numer_targets ? 7 : g.row_stats ? 5 : g.swiglu_gate ? 6
                  : g.acc ? (g.out_dt == DT_BF16 ? 4 : 2) : (g.out_dt == DT_BF16 ? 1 : 0);
   const bool dev_rows = g.rows_dev != nullptr;
   const int scratch_tiles = mode_splits(mode) && !(g.ta && dev_rows) ? scratch_tiles_of(g, g.M) : 0;
@@ -843,10 +884,10 @@ hipError_t gemm_mfma(const GemmArgs& g, hipStream_t st) {
   const bool may_split = dev_rows ? scratch_tiles >= 2 : sc.splits > 1;
 #define LAUNCH(TA, TB, MODE) \
   gemm_mfma_k<TA, TB, MODE><<<grid, NTHREADS, 0, st>>>((const bf16_t*)g.A, (const bf16_t*)g.B, g.C, g.M, g.N, g.K, g.lda, g.ldb, g.ldc, g.rows_dev, \
-                                                       (const bf16_t*)g.A2, (const bf16_t*)g.B2, g.scratch, scratch_tiles, \
+                                                       (const bf16_t*)g.A2, (const bf16_t*)(g.glu_up ? g.glu_up : g.B2), g.scratch, scratch_tiles, \
                                                        (void*)g.row_stats, \
                                                        SwigluFuse{(bf16_t*)g.swiglu_gate, (bf16_t*)g.swiglu_up, (bf16_t*)g.swiglu_act}, \
-                                                       NumerFuse{g.numer_targets, g.numer_row_index, g.numer_target_value})
+                                                       NumerFuse{g.numer_targets, g.numer_row_index, g.numer_target_value}, g.C0)
 #define LAUNCH_LAYOUT(MODE)                       \
   do {                                            \
     if (!g.ta && g.tb) LAUNCH(false, true, MODE); \
@@ -854,11 +895,12 @@ hipError_t gemm_mfma(const GemmArgs& g, hipStream_t st) {
     else LAUNCH(true, false, MODE);               \
   } while (0)
   const int layout = g.ta ? 2 : (g.tb ? 0 : 1);
-  const int kind = mode == 7 ? (int)prof::GEMM_NUMER : mode == 5 ? (int)prof::GEMM_STATS : mode == 6 ? (int)prof::GEMM_SWIGLU
+  const int kind = mode == 8 ? (int)prof::GEMM_GLU : mode == 7 ? (int)prof::GEMM_NUMER : mode == 5 ? (int)prof::GEMM_STATS : mode == 6 ? (int)prof::GEMM_SWIGLU
                  : prof::GEMM_SINGLE + layout * 4 + (mode == 4 ? 2 : mode);   // (both accumulate forms are timed as one kind)
   {
-    prof::Scope sc_time(kind, 2.0 * g.M * g.N * g.K * (g.A2 ? 2 : 1), dev_rows, st);   // times the GEMM kernel, not the sum of the partial tiles after it
-    if (mode == 7) LAUNCH(false, true, 7);
+    prof::Scope sc_time(kind, 2.0 * g.M * g.N * g.K * (g.A2 || g.glu_up ? 2 : 1), dev_rows, st);   // times the GEMM kernel, not the sum of the partial tiles after it
+    if (mode == 8) LAUNCH(false, true, 8);
+    else if (mode == 7) LAUNCH(false, true, 7);
     else if (mode == 5) LAUNCH(false, true, 5);
     else if (mode == 6) LAUNCH(false, false, 6);
     else if (mode == 4) LAUNCH(true, false, 4);
@@ -882,7 +924,7 @@ hipError_t gemm_mfma(const GemmArgs& g, hipStream_t st) {
 // Accumulate-form problems that write the same C (same shape and leading dimensions) are folded into one grouped
 // problem with several reduction segments: one pass over that C.
 static bool same_output(const GemmArgs& a, const GemmArgs& b) {
-  return a.C == b.C && a.M == b.M && a.N == b.N && a.lda == b.lda && a.ldb == b.ldb && a.ldc == b.ldc;
+  return !a.C0 && !b.C0 && a.C == b.C && a.M == b.M && a.N == b.N && a.lda == b.lda && a.ldb == b.ldb && a.ldc == b.ldc;
 }
 static int group_fold(const GemmArgs* gs, int n, int* owner /* [n]: index of the first problem with the same output */) {
   int n_out = 0;
@@ -923,7 +965,7 @@ hipError_t gemm_mfma_group(const GemmArgs* gs, int n, hipStream_t st) {
     if (owner[i] == i) {
       slot[i] = np;
       GroupProblem& p = ga.p[np++];
-      p.C = gs[i].C; p.M = gs[i].M; p.N = gs[i].N; p.lda = gs[i].lda; p.ldb = gs[i].ldb; p.ldc = gs[i].ldc;
+      p.C = gs[i].C; p.C0 = gs[i].C0; p.M = gs[i].M; p.N = gs[i].N; p.lda = gs[i].lda; p.ldb = gs[i].ldb; p.ldc = gs[i].ldc;
       p.nseg = 0;
       p.tiles_m = (int)cdiv(gs[i].M, BM); p.tiles_n = (int)cdiv(gs[i].N, BN); p.tile_begin = tiles;
       tiles += p.tiles_m * p.tiles_n;
@@ -976,7 +1018,7 @@ bool gemm_mfma_seg_eligible(const GemmArgs* gs, int n) {
   for (int i = 0; i < n; ++i) {
     const GemmArgs& g = gs[i];
     if (!gemm_mfma_eligible(g) || !g.ta || g.tb || !g.acc || g.out_dt != gs[0].out_dt || g.A2) return false;
-    if (g.C != gs[0].C || g.M != gs[0].M || g.N != gs[0].N || g.lda != gs[0].lda || g.ldb != gs[0].ldb || g.ldc != gs[0].ldc) return false;
+    if (g.C0 || g.C != gs[0].C || g.M != gs[0].M || g.N != gs[0].N || g.lda != gs[0].lda || g.ldb != gs[0].ldb || g.ldc != gs[0].ldc) return false;
   }
   return true;
 }

@@ -55,12 +55,18 @@ struct GemmArgs {
   // C = A B^T is padded: its rows reach to ldc, a multiple of 8, so N need not be a multiple of anything (columns N .. next multiple of 4
   // receive finite values of no meaning).
   bool c_padded = false;
+  // Optional second B of the store form C = A B^T (bf16): C receives silu(A B^T) * (A glu_up^T), neither product is stored (MFMA kernel only: ask
+  // gemm_glu_supported first)
+  const void* glu_up = nullptr;
+  // Accumulated bf16 C: C = C0 + A B instead (C0 laid out like C)
+  const void* C0 = nullptr;
   // Outputs of few tiles may go to the kernels of gemm_few.hip (which split no reduction over workgroups and leave `scratch` alone)
   bool few_ok = false;
 };
 constexpr int GEMM_STAT_COLS = 256;
 bool gemm_row_stats_supported(const GemmArgs& g);
 bool gemm_numerators_supported(const GemmArgs& g);
+bool gemm_glu_supported(const GemmArgs& g);
 // upper bound of the scratch a GEMM with M <= max_m rows and N <= max_n columns may use
 size_t gemm_scratch_bytes(int max_m, int max_n);
 hipError_t gemm(const GemmArgs& g, hipStream_t st);
@@ -90,9 +96,10 @@ namespace prof {
 // kinds 0..11: gemm_mfma_k<layout, mode> with layout NT=0, NN=1, TN=2 and mode 0, 1, 2 (slot 3 unused); 12..23: the grouped kernel;
 // then the shape-agnostic GEMM, the attention forward / backward launch sequences, the segmented weight-gradient GEMM and the
 // store form with row statistics (gemm_mfma_k<NT, 5>), the input-gradient form with the fused SwiGLU adjoint (gemm_mfma_k<NN, 6>)
-// and the softmax-numerator store (gemm_mfma_k<NT, 7>), the kernels for outputs of few tiles (gemm_few_k)
+// and the softmax-numerator store (gemm_mfma_k<NT, 7>), the kernels for outputs of few tiles (gemm_few_k), the gated
+// store (gemm_mfma_k<NT, 8>)
 enum { GEMM_SINGLE = 0, GEMM_GROUP = 12, GEMM_GENERIC = 24, ATTN_FWD = 25, ATTN_BWD = 26, GEMM_SEG = 27, GEMM_STATS = 28, GEMM_SWIGLU = 29,
-       GEMM_NUMER = 30, GEMM_FEW = 31, N_KIND = 32 };
+       GEMM_NUMER = 30, GEMM_FEW = 31, GEMM_GLU = 32, N_KIND = 33 };
 struct Scope {
   hipStream_t st; bool active = false; int kind = 0; double work = 0; bool bounded = false; hipEvent_t e0{}, e1{};
   // bounded: `work` was computed from a host-side upper bound of a run-time row count
@@ -140,10 +147,14 @@ hipError_t fill_zero(void* p, size_t bytes, hipStream_t st);
 // eight A fragments of a round re-read from LDS
 hipError_t mfma_rate_probe(const void* operands, float* sink, int workgroups, int iters, int lds_reads, hipStream_t st);
 hipError_t copy_bytes(void* dst, const void* src, size_t bytes, hipStream_t st);     // 16-byte aligned, bytes % 16 == 0 fast path
-// dst [R2, C2] (dt, dense) = zero-padded scale * src, src [R, C] (dt, dense) or its transpose (src [C, R]) - small matrices
-hipError_t pad_matrix(int dt, const void* src, int R, int C, bool transposed, float scale, void* dst, int R2, int C2, hipStream_t st);
-// dst [R, C] fp32 (dense) += scale * src[i * ld + j]
-hipError_t add_scaled_block(const float* src, int64_t ld, float scale, float* dst, int R, int C, hipStream_t st);
+// Small matrices, up to 21 in one launch: dst [R2, C2] (dt, dense) = zero-padded scale * src, src [R, C] (dt, dense) or its transpose (src [C, R])
+struct PadJob { const void* src; void* dst; int R, C, transposed, R2, C2; float scale; int64_t begin; };      // begin: set by pad_matrices
+struct PadJobs { int n; PadJob job[21]; };
+hipError_t pad_matrices(int dt, PadJobs jobs, hipStream_t st);
+// ... up to 14: dst [R, C] fp32 (dense) += scale * src[i * ld + j]
+struct AddJob { const float* src; int64_t ld; float* dst; int R, C; int64_t begin; };
+struct AddJobs { int n; AddJob job[14]; };
+hipError_t add_scaled_blocks(AddJobs jobs, float scale, hipStream_t st);
 // ids outside [0, vocab) are never used as an index: their x row is zero, their dx row is dropped
 hipError_t embedding_fwd(int dt, const int32_t* ids, const void* emb, void* x, int64_t rows, int d, int vocab, hipStream_t st);
 hipError_t embedding_bwd(int dt, const int32_t* ids, const void* dx, float* demb, int64_t rows, int d, int vocab, hipStream_t st);

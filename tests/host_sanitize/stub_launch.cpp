@@ -41,6 +41,8 @@ static void touch_gemm(const GemmArgs& g) {
   const size_t b_el = g.tb ? (size_t)(g.N - 1) * g.ldb + g.K : (size_t)(g.K - 1) * g.ldb + g.N;
   const size_t c_el = (size_t)(g.M - 1) * g.ldc + (g.c_padded ? align_up(g.N, 4) : g.N);
   rd(g.A, a_el * es(g.in_dt)); rd(g.B, b_el * es(g.in_dt));
+  if (g.glu_up) rd(g.glu_up, b_el * es(g.in_dt));
+  if (g.C0) rd(g.C0, c_el * es(g.out_dt));
   if (g.A2) { rd(g.A2, a_el * es(g.in_dt)); rd(g.B2, b_el * es(g.in_dt)); }
   if (g.swiglu_gate) {
     wr(g.swiglu_gate, c_el * es(g.out_dt)); wr(g.swiglu_up, c_el * es(g.out_dt)); wr(g.swiglu_act, c_el * es(g.out_dt));
@@ -59,6 +61,7 @@ bool gemm_row_stats_supported(const GemmArgs& g) { return nt_mfma(g) && g.out_dt
 bool gemm_numerators_supported(const GemmArgs& g) {
   return nt_mfma(g) && g.out_dt == DT_BF16 && g.row_stats && g.numer_targets && g.numer_target_value;
 }
+bool gemm_glu_supported(const GemmArgs& g) { return g.glu_up && nt_mfma(g) && cdiv(g.M, 256) * cdiv(g.N, 128) >= 200; }
 size_t gemm_scratch_bytes(int max_m, int max_n) {     // at most one partial tile per CU, 27 per output tile, of the rows that exist
   return (size_t)std::min<int64_t>(256, cdiv(max_m, 256) * cdiv(max_n, 256) * 27) * std::min(max_m, 256) * 256 * sizeof(float);
 }
@@ -119,12 +122,18 @@ hipError_t kv_grad_finish(int dt, const float* dK, const float* dV, const float2
   rd(dK, n * 4); rd(dV, n * 4); rd(tab, (size_t)rows * (dh / 2) * sizeof(float2)); wr(dkc, n * es(dt)); wr(dvc, n * es(dt)); return hipSuccess;
 }
 hipError_t fill_zero(void* p, size_t bytes, hipStream_t) { wr(p, bytes); return hipSuccess; }
-hipError_t copy_bytes(void* dst, const void* src, size_t bytes, hipStream_t) { wr(dst, bytes); rd(src, bytes); return hipSuccess; }
-hipError_t pad_matrix(int dt, const void* src, int R, int C, bool, float, void* dst, int R2, int C2, hipStream_t) {
-  rd(src, (size_t)R * C * es(dt)); wr(dst, (size_t)R2 * C2 * es(dt)); return hipSuccess;
+hipError_t pad_matrices(int dt, PadJobs jobs, hipStream_t) {
+  for (int k = 0; k < jobs.n; ++k) {
+    const PadJob& p = jobs.job[k];
+    rd(p.src, (size_t)p.R * p.C * es(dt)); wr(p.dst, (size_t)p.R2 * p.C2 * es(dt));
+  }
+  return hipSuccess;
 }
-hipError_t add_scaled_block(const float* src, int64_t ld, float, float* dst, int R, int C, hipStream_t) {
-  if (R > 0 && C > 0) { rd(src, ((size_t)(R - 1) * ld + C) * 4); wr(dst, (size_t)R * C * 4); }
+hipError_t add_scaled_blocks(AddJobs jobs, float, hipStream_t) {
+  for (int k = 0; k < jobs.n; ++k) {
+    const AddJob& p = jobs.job[k];
+    if (p.R > 0 && p.C > 0) { rd(p.src, ((size_t)(p.R - 1) * p.ld + p.C) * 4); wr(p.dst, (size_t)p.R * p.C * 4); }
+  }
   return hipSuccess;
 }
 hipError_t embedding_fwd(int dt, const int32_t* ids, const void* emb, void* x, int64_t rows, int d, int vocab, hipStream_t) {
