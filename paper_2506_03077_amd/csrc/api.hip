@@ -616,6 +616,8 @@ struct HeadWs {
   float2* stats; int n_stat;          // per row and 256-column block of the chunk's logits: (max, sum of exp), written by the logits GEMM
   int64_t ldz;                        // row stride of z and dz: bf16 rows are padded to the GEMMs' reduction step (zeros), so that any vocabulary fits
   int32_t *index, *chunk_rows; void *hc[MAX_DW_GROUP], *dhc;   // active-row compaction: row list, rows per chunk, gathered h / dh rows
+  bool ht;                            // the weight gradient's h rows are kept transposed, hT [hidden, ldt] per chunk of the group (hc is then one buffer)
+  int64_t ldt; void* hT[MAX_DW_GROUP];
   float* gemm_scratch; size_t gemm_scratch_bytes; size_t bytes;
 };
 static HeadWs carve_head(const sbp_head_cfg* c, void* ws) {
@@ -635,7 +637,15 @@ static HeadWs carve_head(const sbp_head_cfg* c, void* ws) {
   h.ell = cv.take<float>(1);
   h.index = cv.take<int32_t>((size_t)rows);
   h.chunk_rows = cv.take<int32_t>((size_t)cdiv(rows, (int64_t)cm) + 1);
-  for (int g = 0; g < h.dw_group; ++g) h.hc[g] = cv.take_bytes(cm * c->hidden * dtype_size(c->dtype));
+  // With h^T the weight gradient's GEMM reads one operand instead of two through transposing LDS loads: 152064 x 3584, 8192 rows: 7.50 -> 7.20 ms;
+  // the copy takes 8 us per 2048-row chunk.  Whole call, 3584 x 152064: 32768 rows 86.2 -> 85.4 ms, 6000 13.10 -> 12.88, 1500 4.58 -> 4.53, 300 the
+  // same.  Smaller outputs do not repay the launch: 2048 x 32000 722 -> 718 us (1500 rows), 1024 x 50257 745 -> 752, 512 x 32000 339 -> 343.
+  h.ht = c->dtype == SBP_BF16 && c->hidden % 8 == 0 && (int64_t)c->vocab * c->hidden >= 100000000;
+  h.ldt = (int64_t)align_up(cm, 64);
+  for (int g = 0; g < h.dw_group; ++g) {
+    h.hc[g] = h.ht && g > 0 ? h.hc[0] : cv.take_bytes(cm * c->hidden * dtype_size(c->dtype));
+    h.hT[g] = h.ht ? cv.take_bytes((size_t)c->hidden * h.ldt * 2) : nullptr;
+  }
   h.dhc = cv.take_bytes(cm * c->hidden * dtype_size(c->dtype));
   h.gemm_scratch_bytes = c->dtype == SBP_BF16 ? gemm_scratch_bytes((int)cm, c->hidden) : 0;
   h.gemm_scratch = (float*)cv.take_bytes(h.gemm_scratch_bytes);
@@ -688,6 +698,7 @@ int32_t streambp_lmhead_ce_backward(const sbp_head_cfg* c, const void* w, const 
     void* hc = s.hc[n_pending];
     void* dz = s.dz[n_pending];
     if (ci == 0) HIPCHK(gather_rows(dt, h, idx, n_dev, hc, n, d, st));      // (the following chunks': together with the scatter of the chunk before)
+    if (s.ht) HIPCHK(transpose_rows(hc, n_dev, n, d, s.hT[n_pending], s.ldt, st));
     // The logits: fp32 with (max, sum of exp) per row and 256-column block out of the GEMM's epilogue where the MFMA kernel
     // takes the problem - or, better, never as logits at all: the numerator form leaves exp(z - block max) in bf16 directly in
     // the chunk's dz buffer plus the target logits, and the row kernel finishes dz in place.
@@ -723,6 +734,10 @@ int32_t streambp_lmhead_ce_backward(const sbp_head_cfg* c, const void* w, const 
     gh.rows_dev = n_dev;
     HIPCHK(gemm(gh, st));
     pending[n_pending] = dw_gemm(dz, hc, dw, n, V, d, dt, c->grad_dtype);
+    if (s.ht) {
+      pending[n_pending].B = s.hT[n_pending]; pending[n_pending].tb = true;
+      pending[n_pending].ldb = s.ldt; pending[n_pending].b_padded = true;
+    }
     pending[n_pending].lda = s.ldz; pending[n_pending].a_padded = padded;
     pending[n_pending].rows_dev = n_dev;
     if (++n_pending == s.dw_group || ci + 1 == n_chunks) {

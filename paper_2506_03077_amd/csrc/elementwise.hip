@@ -524,6 +524,36 @@ hipError_t copy_bytes(void* dst, const void* src, size_t bytes, hipStream_t st) 
   return hipGetLastError();
 }
 
+// 64 x 64 tiles through LDS, 16 bytes per lane on both sides (a tile's rows are 33 dwords apart)
+__global__ __launch_bounds__(256) void transpose_rows_k(const bf16_t* __restrict__ src, const int32_t* __restrict__ rows_dev, int R, int C, bf16_t* __restrict__ dst, int64_t ld) {
+  __shared__ bf16_t tile[64][66];
+  const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64, t = threadIdx.x;
+  if (rows_dev) R = min(R, *rows_dev);
+  if (r0 >= R) return;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int row = (i * 256 + t) >> 3, col = (t & 7) * 8;
+    bf16x8 v = {};
+    if (r0 + row < R && c0 + col < C) v = *(const bf16x8*)(src + (int64_t)(r0 + row) * C + c0 + col);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) tile[row][col + e] = v[e];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int col = (i * 256 + t) >> 3, row = (t & 7) * 8;
+    bf16x8 v;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = tile[row + e][col];
+    if (c0 + col < C) *(bf16x8*)(dst + (int64_t)(c0 + col) * ld + r0 + row) = v;
+  }
+}
+hipError_t transpose_rows(const void* src, const int32_t* rows_dev, int R, int C, void* dst, int64_t ld, hipStream_t st) {
+  if (R == 0 || C == 0) return hipSuccess;
+  transpose_rows_k<<<dim3((unsigned)cdiv(C, 64), (unsigned)cdiv(R, 64)), 256, 0, st>>>((const bf16_t*)src, rows_dev, R, C, (bf16_t*)dst, ld);
+  return hipGetLastError();
+}
+
 // element i of a launch over several jobs -> its job (they follow one another from job[x].begin on)
 template <typename J> __device__ __forceinline__ int job_of(const J& jobs, int64_t i) {
   int x = 0;

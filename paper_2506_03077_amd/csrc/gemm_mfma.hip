@@ -109,7 +109,7 @@ struct KSegment {
 // What bounds it: the matrix pipe at its power-limited clock.  8192^3 bf16, same card: NT 1265 -> 1556, NN 1256 -> 1546, TN 1199
 // -> 1440 TFLOP/s (vendor library 1614 / 1390 / 1202); half of the gain is the slot schedule (1410 with 32x32x16 MFMAs), half the
 // 16x16x32 MFMA.  With the wait for B0, on another card: 1559 / 1459 / 1329 (library 1550 / 1327 / 1180).
-// The TN form is closest to the LDS limit (transposing reads of both operands).
+// The TN form is closest to the LDS limit (transposing reads of both operands); with B stored [N, K] (TT) 8192^3 takes 868 us against 909.
 // No vector-ALU address work: global addresses are an SGPR base plus per-lane offsets computed once, LDS fragment
 // addresses are computed once and reached with immediate offsets.
 template <bool TA, bool TB, int MODE, typename SegmentF>
@@ -669,10 +669,10 @@ __global__ __launch_bounds__(NTHREADS) void gemm_mfma_k(const bf16_t* __restrict
   gemm_tile<TA, TB, MODE>(A2 ? 2 : 1, segment, Cv, M, N, lda, ldb, ldc, tm, tn, smem, partial, part * 4, row_stats, sw, nf, C0, MODE == 8 ? B2 : nullptr);
 }
 
-// Weight-gradient form with a segmented reduction: C += sum_s A_s^T B_s, every segment with its own run-time row
+// Weight-gradient form with a segmented reduction: C += sum_s A_s^T B_s (TB: B_s^T stored), every segment with its own run-time row
 // count.  One pass over C for several chunks' worth of rows.
 struct SegLaunch { const bf16_t* A[MAX_SEG]; const bf16_t* B[MAX_SEG]; const int* rows_dev[MAX_SEG]; int K[MAX_SEG]; int n; };
-template <bool C_BF16>
+template <bool C_BF16, bool TB>
 __global__ __launch_bounds__(NTHREADS) void gemm_mfma_seg_k(const SegLaunch sl, void* __restrict__ C, int M, int N, int64_t lda,
                                                             int64_t ldb, int64_t ldc) {
   __shared__ __attribute__((aligned(1024))) char smem[SMEM_BYTES];
@@ -683,7 +683,7 @@ __global__ __launch_bounds__(NTHREADS) void gemm_mfma_seg_k(const SegLaunch sl, 
   int total = 0;
   for (int i = 0; i < sl.n; ++i) total += rows(i);
   if (total == 0) return;   // nothing to add
-  gemm_tile<true, false, C_BF16 ? 4 : 2>(sl.n, [&](int i) { return KSegment{sl.A[i], sl.B[i], 0, rows(i)}; }, C, M, N, lda, ldb,
+  gemm_tile<true, TB, C_BF16 ? 4 : 2>(sl.n, [&](int i) { return KSegment{sl.A[i], sl.B[i], 0, rows(i)}; }, C, M, N, lda, ldb,
                                          ldc, tm, tn, smem);
 }
 
@@ -787,7 +787,7 @@ __global__ __launch_bounds__(256) void splitk_tail_k(const TailArgs ta) {
 
 bool gemm_mfma_eligible(const GemmArgs& g) {
   if (g.in_dt != DT_BF16) return false;
-  if (g.acc && g.out_dt != DT_F32 && !(g.out_dt == DT_BF16 && g.ta && !g.tb)) return false;   // bf16 C += : dW form only
+  if (g.acc && g.out_dt != DT_F32 && !(g.out_dt == DT_BF16 && g.ta)) return false;   // bf16 C += : dW forms only
   // Output widths need not be multiples of the 256-wide tile: a ragged last tile clamps its loads and masks its stores
   // (16-byte granules: multiples of 8 elements), e.g. a 151936-word vocabulary = 593.5 tiles.
   if (g.M < 1 || g.N < 1 || g.K < 1) return false;
@@ -796,8 +796,8 @@ bool gemm_mfma_eligible(const GemmArgs& g) {
     if (g.M % 8 != 0 && !g.a_padded) return false;
   } else if (!g.ta) {                        // NT / NN; a ragged K needs B reduction-major and A's rows padded with zeros
     if (g.K % BK != 0 && (g.tb || !g.a_padded)) return false;
-  } else {
-    return false;                            // TT is never needed
+  } else {                                   // TT: weight gradients only, B^T stored; a ragged K needs B's rows padded
+    if (!g.acc || g.A2 || (g.M % 8 != 0 && !g.a_padded) || (g.K % BK != 0 && !g.b_padded)) return false;
   }
   if (g.lda % 8 || g.ldb % 8) return false;
   if (g.lda >= (1 << 22) || g.ldb >= (1 << 22)) return false;   // per-lane byte offsets within a tile are 32-bit
@@ -903,6 +903,8 @@ hipError_t gemm_mfma(const GemmArgs& g, hipStream_t st) {
     else if (mode == 7) LAUNCH(false, true, 7);
     else if (mode == 5) LAUNCH(false, true, 5);
     else if (mode == 6) LAUNCH(false, false, 6);
+    else if (g.ta && g.tb && mode == 4) LAUNCH(true, true, 4);
+    else if (g.ta && g.tb) LAUNCH(true, true, 2);
     else if (mode == 4) LAUNCH(true, false, 4);
     else if (mode == 1) LAUNCH_LAYOUT(1);
     else if (mode == 2) LAUNCH_LAYOUT(2);
@@ -945,7 +947,7 @@ bool gemm_mfma_group_eligible(const GemmArgs* gs, int n, bool small_ok) {
   const int n_out = group_fold(gs, n, owner);
   if (n_out > MAX_GROUP) return false;
   for (int i = 0; i < n; ++i) {
-    if (!gemm_mfma_eligible(gs[i]) || gs[i].rows_dev || gs[i].A2) return false;
+    if (!gemm_mfma_eligible(gs[i]) || gs[i].rows_dev || gs[i].A2 || (gs[i].ta && gs[i].tb)) return false;
     if (gs[i].ta != gs[0].ta || gs[i].tb != gs[0].tb || gs[i].out_dt != gs[0].out_dt || gs[i].acc != gs[0].acc) return false;
     if (++nseg[owner[i]] > MAX_GSEG) return false;
     if (owner[i] == i) tiles += cdiv(gs[i].M, BM) * cdiv(gs[i].N, BN);
@@ -1017,7 +1019,7 @@ bool gemm_mfma_seg_eligible(const GemmArgs* gs, int n) {
   if (n < 2 || n > MAX_SEG) return false;
   for (int i = 0; i < n; ++i) {
     const GemmArgs& g = gs[i];
-    if (!gemm_mfma_eligible(g) || !g.ta || g.tb || !g.acc || g.out_dt != gs[0].out_dt || g.A2) return false;
+    if (!gemm_mfma_eligible(g) || !g.ta || g.tb != gs[0].tb || !g.acc || g.out_dt != gs[0].out_dt || g.A2) return false;
     if (g.C0 || g.C != gs[0].C || g.M != gs[0].M || g.N != gs[0].N || g.lda != gs[0].lda || g.ldb != gs[0].ldb || g.ldc != gs[0].ldc) return false;
   }
   return true;
@@ -1035,8 +1037,9 @@ hipError_t gemm_mfma_seg(const GemmArgs* gs, int n, hipStream_t st) {
   const GemmArgs& g = gs[0];
   const int tiles = (int)cdiv(g.M, BM) * (int)cdiv(g.N, BN);
   prof::Scope sc(prof::GEMM_SEG, work, bounded, st);
-  if (g.out_dt == DT_BF16) gemm_mfma_seg_k<true><<<tiles, NTHREADS, 0, st>>>(sl, g.C, g.M, g.N, g.lda, g.ldb, g.ldc);
-  else gemm_mfma_seg_k<false><<<tiles, NTHREADS, 0, st>>>(sl, g.C, g.M, g.N, g.lda, g.ldb, g.ldc);
+  auto go = [&](auto kernel) { kernel<<<tiles, NTHREADS, 0, st>>>(sl, g.C, g.M, g.N, g.lda, g.ldb, g.ldc); };
+  if (g.out_dt == DT_BF16) g.tb ? go(gemm_mfma_seg_k<true, true>) : go(gemm_mfma_seg_k<true, false>);
+  else g.tb ? go(gemm_mfma_seg_k<false, true>) : go(gemm_mfma_seg_k<false, false>);
   return hipGetLastError();
 }
 

@@ -52,6 +52,8 @@ struct GemmArgs {
   // A is padded: its rows (NN: columns K .. next multiple of 64, which hold zeros; TN: columns M .. next multiple of 8, any finite
   // values) reach further than the operand, so K (NN) and M (TN) need not be multiples of anything.
   bool a_padded = false;
+  // B of C += A^T B^T (stored [N, K]) is padded: its rows reach to the next multiple of 64 with finite values
+  bool b_padded = false;
   // C = A B^T is padded: its rows reach to ldc, a multiple of 8, so N need not be a multiple of anything (columns N .. next multiple of 4
   // receive finite values of no meaning).
   bool c_padded = false;
@@ -260,6 +262,9 @@ hipError_t compact_active(const int32_t* targets, int64_t rows, int chunk, int V
                           hipStream_t st);
 // dst[r,:] = src[index[r],:] for r < *rows_dev, zero rows after;  scatter: dst[index[r],:] = src[r,:] for r < *rows_dev
 // move_rows: a scatter and a gather, independent of each other, in one launch
+// dst [C, ld] = src [R, C]^T (bf16, C % 8 == 0, 16-byte aligned); rows_dev: only the first *rows_dev rows count.  Columns from there to the next
+// multiple of 64 become zeros (ld reaches to R's next multiple of 64, % 8 == 0); those after it are not written.
+hipError_t transpose_rows(const void* src, const int32_t* rows_dev, int R, int C, void* dst, int64_t ld, hipStream_t st);
 struct RowMove { const void* src; const int32_t* index; const int* rows_dev; void* dst; int max_rows; };
 hipError_t move_rows(int dt, const RowMove& scatter, const RowMove& gather, int d, hipStream_t st);
 hipError_t gather_rows(int dt, const void* src, const int32_t* index, const int* rows_dev, void* dst, int max_rows, int d, hipStream_t st);

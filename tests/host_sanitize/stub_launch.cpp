@@ -38,7 +38,7 @@ static void touch_gemm(const GemmArgs& g) {
   // multiple of 4 columns
   const size_t a_m = g.ta && g.a_padded ? align_up(g.M, 8) : g.M, a_k = !g.ta && g.a_padded ? align_up(g.K, 64) : g.K;
   const size_t a_el = g.ta ? (size_t)(g.K - 1) * g.lda + a_m : (size_t)(g.M - 1) * g.lda + a_k;
-  const size_t b_el = g.tb ? (size_t)(g.N - 1) * g.ldb + g.K : (size_t)(g.K - 1) * g.ldb + g.N;
+  const size_t b_el = g.tb ? (size_t)(g.N - 1) * g.ldb + (g.b_padded ? align_up(g.K, 64) : g.K) : (size_t)(g.K - 1) * g.ldb + g.N;
   const size_t c_el = (size_t)(g.M - 1) * g.ldc + (g.c_padded ? align_up(g.N, 4) : g.N);
   rd(g.A, a_el * es(g.in_dt)); rd(g.B, b_el * es(g.in_dt));
   if (g.glu_up) rd(g.glu_up, b_el * es(g.in_dt));
@@ -122,6 +122,11 @@ hipError_t kv_grad_finish(int dt, const float* dK, const float* dV, const float2
   rd(dK, n * 4); rd(dV, n * 4); rd(tab, (size_t)rows * (dh / 2) * sizeof(float2)); wr(dkc, n * es(dt)); wr(dvc, n * es(dt)); return hipSuccess;
 }
 hipError_t fill_zero(void* p, size_t bytes, hipStream_t) { wr(p, bytes); return hipSuccess; }
+hipError_t transpose_rows(const void* src, const int32_t* rows_dev, int R, int C, void* dst, int64_t ld, hipStream_t) {
+  if (rows_dev) rd(rows_dev, 4);
+  rd(src, (size_t)R * C * 2); wr(dst, ((size_t)(C - 1) * ld + align_up(R, 64)) * 2);
+  return hipSuccess;
+}
 hipError_t pad_matrices(int dt, PadJobs jobs, hipStream_t) {
   for (int k = 0; k < jobs.n; ++k) {
     const PadJob& p = jobs.job[k];
