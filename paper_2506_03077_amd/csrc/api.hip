@@ -612,12 +612,12 @@ static int32_t check_head_cfg(const sbp_head_cfg* c) {
 // chunk.  The fp32 logits - the dominant term - still exist for one chunk only.
 struct HeadWs {
   int dw_group;
-  float* z; void* dz[MAX_DW_GROUP]; float *row_loss, *target_logit, *seq_weight, *ell;
+  float* z; void* dz; float *row_loss, *target_logit, *seq_weight, *ell;      // dz, row_loss: the group's rows
   float2* stats; int n_stat;          // per row and 256-column block of the chunk's logits: (max, sum of exp), written by the logits GEMM
   int64_t ldz;                        // row stride of z and dz: bf16 rows are padded to the GEMMs' reduction step (zeros), so that any vocabulary fits
-  int32_t *index, *chunk_rows; void *hc[MAX_DW_GROUP], *dhc;   // active-row compaction: row list, rows per chunk, gathered h / dh rows
-  bool ht;                            // the weight gradient's h rows are kept transposed, hT [hidden, ldt] per chunk of the group (hc is then one buffer)
-  int64_t ldt; void* hT[MAX_DW_GROUP];
+  int32_t *index, *chunk_rows; void *hc, *dhc;   // active-row compaction: row list, rows per chunk; gathered rows of h (the group's; ht: a chunk's), rows of dh
+  bool ht;                            // the weight gradient's h rows are kept transposed, hT [hidden, ldt] per chunk of the group
+  int64_t ldt; void* hT;
   float* gemm_scratch; size_t gemm_scratch_bytes; size_t bytes;
 };
 static HeadWs carve_head(const sbp_head_cfg* c, void* ws) {
@@ -628,24 +628,23 @@ static HeadWs carve_head(const sbp_head_cfg* c, void* ws) {
   h.ldz = c->dtype == SBP_BF16 ? (int64_t)align_up((size_t)c->vocab, 64) : c->vocab;
   h.z = cv.take<float>(cm * (size_t)h.ldz);
   h.dw_group = dw_group_for(cm, c->dw_group_rows, DW_GROUP_ROWS_HEAD);
-  for (int g = 0; g < h.dw_group; ++g) h.dz[g] = cv.take_bytes(cm * (size_t)h.ldz * dtype_size(c->dtype));
-  h.row_loss = cv.take<float>(cm * (size_t)dw_group_for(cm, c->dw_group_rows, DW_GROUP_ROWS_HEAD));
+  const size_t group = (size_t)std::min<int64_t>((int64_t)cm * h.dw_group, rows);      // rows of a weight-gradient group
+  h.dz = cv.take_bytes(group * (size_t)h.ldz * dtype_size(c->dtype));
+  h.row_loss = cv.take<float>(group);
   h.target_logit = cv.take<float>(cm);
   h.n_stat = (int)cdiv(c->vocab, GEMM_STAT_COLS);
   h.stats = cv.take<float2>(cm * (size_t)h.n_stat);
   h.seq_weight = cv.take<float>(c->batch);
   h.ell = cv.take<float>(1);
   h.index = cv.take<int32_t>((size_t)rows);
-  h.chunk_rows = cv.take<int32_t>((size_t)cdiv(rows, (int64_t)cm) + 1);
+  h.chunk_rows = cv.take<int32_t>(2 * (size_t)cdiv(rows, (int64_t)cm) + 1);
   // With h^T the weight gradient's GEMM reads one operand instead of two through transposing LDS loads: 152064 x 3584, 8192 rows: 7.50 -> 7.20 ms;
-  // the copy takes 8 us per 2048-row chunk.  Whole call, 3584 x 152064: 32768 rows 86.2 -> 85.4 ms, 6000 13.10 -> 12.88, 1500 4.58 -> 4.53, 300 the
+  // the copy takes 6 us per 2048-row chunk.  Whole call, 3584 x 152064: 32768 rows 86.2 -> 85.4 ms, 6000 13.10 -> 12.88, 1500 4.58 -> 4.53, 300 the
   // same.  Smaller outputs do not repay the launch: 2048 x 32000 722 -> 718 us (1500 rows), 1024 x 50257 745 -> 752, 512 x 32000 339 -> 343.
   h.ht = c->dtype == SBP_BF16 && c->hidden % 8 == 0 && (int64_t)c->vocab * c->hidden >= 100000000;
   h.ldt = (int64_t)align_up(cm, 64);
-  for (int g = 0; g < h.dw_group; ++g) {
-    h.hc[g] = h.ht && g > 0 ? h.hc[0] : cv.take_bytes(cm * c->hidden * dtype_size(c->dtype));
-    h.hT[g] = h.ht ? cv.take_bytes((size_t)c->hidden * h.ldt * 2) : nullptr;
-  }
+  h.hc = cv.take_bytes((h.ht ? cm : group) * c->hidden * dtype_size(c->dtype));
+  h.hT = h.ht ? cv.take_bytes((rows > (int64_t)cm ? h.dw_group : 1) * (size_t)c->hidden * h.ldt * 2) : nullptr;      // (or, a multiple of ldt wide, per unit of several chunks)
   h.dhc = cv.take_bytes(cm * c->hidden * dtype_size(c->dtype));
   h.gemm_scratch_bytes = c->dtype == SBP_BF16 ? gemm_scratch_bytes((int)cm, c->hidden) : 0;
   h.gemm_scratch = (float*)cv.take_bytes(h.gemm_scratch_bytes);
@@ -686,71 +685,122 @@ int32_t streambp_lmhead_ce_backward(const sbp_head_cfg* c, const void* w, const 
   // GEMMs.  Positions are independent (Sec. 3.2.1), so the active rows of all sequences are chunked as one
   // flat list; the list and the per-chunk row counts live on the device (no host synchronisation), and the
   // kernels of a chunk read their row count at run time.
-  const int n_chunks = (int)cdiv(rows, (int64_t)cm);
-  HIPCHK(compact_active(targets, rows, cm, V, s.index, s.chunk_rows, n_chunks, st));
+  // How many rows the products run on at once: one chunk, or as many chunks as make HEAD_SPAN_ROWS.  dz is kept for them anyway, and the buffer of the
+  // fp32 logits has room for what else they need: the numerator form never holds logits (there it takes the statistics and the rows of h and dh of
+  // the whole span, and every product runs on the span), else they are dead when the span's last chunk is done (it takes dh, and that product
+  // alone runs on the span).  Small chunks are what this is for: the logits of 1024 rows at 7B widths are 2376 output tiles, a tenth round
+  // of the CUs for 72 of them.  GRPO group of 8 x 1111 rows, chunk 1024, 18.8 -> 18.0 ms; fp32 layer and head of 256 rows, chunk 64 (five launches a
+  // chunk) 371 -> 335 us; two-layer stack of 1024 wide layers, vocabulary 50257, chunk 512, 3.36 -> 3.30 ms.
+  // More rows than this gain no more: all 16384 of a group at once, dh takes 26.0 instead of 26.9 ms per 32768 rows, the row
+  // kernel, which finds less of dz in the caches, 4.2 instead of 3.65, and the whole call the same.
+  constexpr int HEAD_SPAN_ROWS = 2048;
+  const bool padded = dt == DT_BF16;      // bf16 rows of z and dz are padded to a multiple of 64, dz with zeros: the products with dz need no particular vocabulary
+  auto numerators = [&](const void* hc, void* dz, int n, const int* n_dev, const int32_t* idx, float2* stats, float* target_logit) {
+    GemmArgs g = fwd_gemm(hc, w, dz, n, V, d, dt, DT_BF16);
+    g.ldc = s.ldz;
+    g.rows_dev = n_dev; g.row_stats = stats;
+    g.numer_targets = targets; g.numer_row_index = idx; g.numer_target_value = target_logit;
+    return g;
+  };
+  const bool numer = (fusion_mask() & FUSE_NUMERATORS) && dt == DT_BF16 && s.n_stat > 0 &&
+                     gemm_numerators_supported(numerators(s.hc, s.dz, cm, s.chunk_rows, s.index, s.stats, s.target_logit));
+  void *hc = s.hc, *dhc = s.dhc;
+  float2* stats = s.stats;
+  float* target_logit = s.target_logit;
+  int chunks = std::max(1, std::min(s.dw_group, HEAD_SPAN_ROWS / cm));
+  while (s.dw_group % chunks != 0) --chunks;              // whole spans per weight-gradient group
+  const int span = (int)std::min<int64_t>(rows, (int64_t)cm * chunks);
+  if (span > cm) {
+    auto carve = [&](void* base) {
+      if (!numer) { dhc = base; return (size_t)span * d * es; }
+      Carver cv(base);
+      dhc = cv.take_bytes((size_t)span * d * es);
+      stats = cv.take<float2>((size_t)span * s.n_stat);
+      target_logit = cv.take<float>(span);
+      if (s.ht) hc = cv.take_bytes((size_t)span * d * es);
+      return cv.off;
+    };
+    if (carve(nullptr) <= (size_t)cm * s.ldz * sizeof(float)) carve(s.z);
+    else { dhc = s.dhc; stats = s.stats; target_logit = s.target_logit; hc = s.hc; chunks = 1; }
+  } else chunks = 1;
+  const int cu = chunks > 1 && numer ? span : cm;         // rows of a unit: what the logits are formed of at once
+  const int dh_units = chunks > 1 && !numer ? chunks : 1, per_group = numer ? s.dw_group / chunks : s.dw_group;      // units of a span of dh, of a weight-gradient group
+  const int64_t ldt = (int64_t)align_up((size_t)cu, 64);
+  const bool gather_span = dh_units > 1 && !s.ht;         // all rows of a span fetched at once
+  const int n_units = (int)cdiv(rows, (int64_t)cu);
+  int32_t* unit_rows = s.chunk_rows;                      // [n_units], then all active rows, then the rows per span
+  int32_t* span_rows = unit_rows + n_units + 1;
+  HIPCHK(compact_active(targets, rows, cu, V, s.index, unit_rows, n_units, span, span_rows, dh_units > 1 ? (int)cdiv(rows, (int64_t)span) : 0, st));
   HIPCHK(fill_zero(dh, (size_t)rows * d * es, st));          // ignored rows of dh: exact zeros
   GemmArgs pending[MAX_DW_GROUP];
   int n_pending = 0;
-  for (int ci = 0; ci < n_chunks; ++ci) {
-    const int32_t* idx = s.index + (size_t)ci * cm;
-    const int* n_dev = s.chunk_rows + ci;
-    const int n = (int)std::min<int64_t>(cm, rows - (int64_t)ci * cm);      // upper bound of the chunk's rows
-    void* hc = s.hc[n_pending];
-    void* dz = s.dz[n_pending];
-    if (ci == 0) HIPCHK(gather_rows(dt, h, idx, n_dev, hc, n, d, st));      // (the following chunks': together with the scatter of the chunk before)
-    if (s.ht) HIPCHK(transpose_rows(hc, n_dev, n, d, s.hT[n_pending], s.ldt, st));
+  // rows [first, first + n) of the list of active rows: at most n, the rest of them on the device
+  auto moved = [&](bool scatter, int64_t first, int64_t n, const int32_t* n_dev, void* buf) {
+    const int m = (int)std::max<int64_t>(0, std::min<int64_t>(n, rows - first));
+    return m == 0 ? RowMove{} : scatter ? RowMove{buf, s.index + first, n_dev, dh, m} : RowMove{h, s.index + first, n_dev, buf, m};
+  };
+  for (int ci = 0; ci < n_units; ++ci) {
+    const int64_t first = (int64_t)ci * cu, group_first = (int64_t)(ci - n_pending) * cu, span_first = first - (int64_t)(ci % dh_units) * cu;
+    const int32_t* idx = s.index + first;
+    const int* n_dev = unit_rows + ci;
+    const int n = (int)std::min<int64_t>(cu, rows - first);      // upper bound of the unit's rows
+    void* hcu = s.ht ? hc : at(hc, (size_t)n_pending * cu, d, es);
+    void* dz = at(s.dz, (size_t)n_pending * cu, s.ldz, es);
+    void* hT = s.ht ? (char*)s.hT + (size_t)n_pending * d * ldt * 2 : nullptr;
+    if (ci == 0) HIPCHK(move_rows(dt, RowMove{}, gather_span ? moved(false, 0, span, span_rows, hc) : moved(false, 0, cu, n_dev, hcu), d, st));
+    if (s.ht) HIPCHK(transpose_rows(hcu, n_dev, n, d, hT, ldt, st));
     // The logits: fp32 with (max, sum of exp) per row and 256-column block out of the GEMM's epilogue where the MFMA kernel
     // takes the problem - or, better, never as logits at all: the numerator form leaves exp(z - block max) in bf16 directly in
     // the chunk's dz buffer plus the target logits, and the row kernel finishes dz in place.
-    // bf16 rows of z and dz are padded to a multiple of 64, dz with zeros: the products with dz need no particular vocabulary.
-    const bool padded = dt == DT_BF16;
-    GemmArgs gz = fwd_gemm(hc, w, s.z, n, V, d, dt, DT_F32);
-    gz.ldc = s.ldz; gz.c_padded = padded;
-    gz.rows_dev = n_dev;
-    gz.row_stats = s.stats;
-    bool numer = false;
-    if ((fusion_mask() & FUSE_NUMERATORS) && dt == DT_BF16 && s.n_stat > 0) {
-      GemmArgs gn = fwd_gemm(hc, w, dz, n, V, d, dt, DT_BF16);
-      gn.ldc = s.ldz;
-      gn.rows_dev = n_dev; gn.row_stats = s.stats;
-      gn.numer_targets = targets; gn.numer_row_index = idx; gn.numer_target_value = s.target_logit;
-      if (gemm_numerators_supported(gn)) { gz = gn; numer = true; }
+    GemmArgs gz = numerators(hcu, dz, n, n_dev, idx, stats, target_logit);
+    if (!numer) {
+      gz = fwd_gemm(hcu, w, s.z, n, V, d, dt, DT_F32);
+      gz.ldc = s.ldz; gz.c_padded = padded;
+      gz.rows_dev = n_dev;
+      gz.row_stats = s.stats;
     }
-    const bool stats = numer || (s.n_stat > 0 && gemm_row_stats_supported(gz));   // the LSE statistics come out of the GEMM's epilogue
-    if (!stats) gz.row_stats = nullptr;
+    const bool has_stats = numer || (s.n_stat > 0 && gemm_row_stats_supported(gz));   // the LSE statistics come out of the GEMM's epilogue
+    if (!has_stats) gz.row_stats = nullptr;
     HIPCHK(gemm(gz, st));
     HeadRowArgs a{};
-    a.stats = stats ? s.stats : nullptr; a.n_stat = s.n_stat;
-    a.target_logit = numer ? s.target_logit : nullptr;
+    a.stats = has_stats ? stats : nullptr; a.n_stat = s.n_stat;
+    a.target_logit = numer ? target_logit : nullptr;
     a.dt = dt; a.objective = c->objective; a.z = s.z; a.dz = dz; a.ldz = s.ldz; a.targets = targets;
     a.old_logp = old_logp; a.ref_logp = ref_logp;
     a.advantages = advantages; a.seq_weight = s.seq_weight; a.row0 = 0; a.row_index = idx; a.rows_dev = n_dev;
     a.rows = n; a.V = V; a.T = c->seq_len;
     a.loss_scale = c->loss_scale; a.clip_eps = c->clip_eps; a.kl_beta = c->kl_beta; a.kl_mode = c->kl_mode;
-    a.row_loss = s.row_loss + (size_t)n_pending * cm;
+    a.row_loss = s.row_loss + (size_t)n_pending * cu;
     HIPCHK(head_rows(a, st));
-    GemmArgs gh = dx_gemm(dz, w, s.dhc, n, V, d, dt, dt, false);
-    gh.lda = s.ldz; gh.a_padded = padded;
-    gh.rows_dev = n_dev;
-    HIPCHK(gemm(gh, st));
-    pending[n_pending] = dw_gemm(dz, hc, dw, n, V, d, dt, c->grad_dtype);
+    pending[n_pending] = dw_gemm(dz, hcu, dw, n, V, d, dt, c->grad_dtype);
     if (s.ht) {
-      pending[n_pending].B = s.hT[n_pending]; pending[n_pending].tb = true;
-      pending[n_pending].ldb = s.ldt; pending[n_pending].b_padded = true;
+      pending[n_pending].B = hT; pending[n_pending].tb = true;
+      pending[n_pending].ldb = ldt; pending[n_pending].b_padded = true;
     }
     pending[n_pending].lda = s.ldz; pending[n_pending].a_padded = padded;
     pending[n_pending].rows_dev = n_dev;
-    if (++n_pending == s.dw_group || ci + 1 == n_chunks) {
+    const bool span_done = (ci + 1) % dh_units == 0 || ci + 1 == n_units;
+    const int* span_dev = dh_units > 1 ? span_rows + ci / dh_units : n_dev;
+    if (span_done) {
+      GemmArgs gh = dx_gemm((char*)dz - (size_t)(first - span_first) * s.ldz * es, w, dhc, (int)(first + n - span_first), V, d, dt, dt, false);
+      gh.lda = s.ldz; gh.a_padded = padded;
+      gh.rows_dev = span_dev;
+      HIPCHK(gemm(gh, st));
+    }
+    if (++n_pending == per_group || ci + 1 == n_units) {
       HIPCHK(gemm_batch(pending, n_pending, st));
       // the active rows of the group's chunks are one list: its loss terms are summed together
-      const int64_t first = (int64_t)(ci + 1 - n_pending) * cm;
-      HIPCHK(reduce_add(s.row_loss, n_pending * cm, c->objective == SBP_OBJ_DPO ? s.ell : loss, st, s.chunk_rows + n_chunks, (int)std::min<int64_t>(first, INT32_MAX)));
+      HIPCHK(reduce_add(s.row_loss, (int)(first + n - group_first), c->objective == SBP_OBJ_DPO ? s.ell : loss, st, unit_rows + n_units,
+                        (int)std::min<int64_t>(group_first, INT32_MAX)));
       n_pending = 0;
     }
-    const RowMove out{s.dhc, idx, n_dev, dh, n};
-    if (ci + 1 < n_chunks)
-      HIPCHK(move_rows(dt, out, RowMove{h, idx + cm, n_dev + 1, s.hc[n_pending], (int)std::min<int64_t>(cm, rows - (int64_t)(ci + 1) * cm)}, d, st));
-    else HIPCHK(move_rows(dt, out, RowMove{}, d, st));
+    // rows of dh out, the next rows of h in: independent of each other
+    const RowMove out = span_done ? moved(true, span_first, first + n - span_first, span_dev, dhc) : RowMove{};
+    void* next = s.ht ? hc : at(hc, (size_t)n_pending * cu, d, es);
+    RowMove in{};
+    if (!gather_span) in = moved(false, first + cu, cu, n_dev + 1, next);
+    else if (span_done) in = moved(false, first + cu, span, span_dev + 1, next);
+    if (out.max_rows + in.max_rows > 0) HIPCHK(move_rows(dt, out, in, d, st));
   }
   if (c->objective == SBP_OBJ_DPO)
     HIPCHK(dpo_finish(dt, s.ell, c->kl_beta, dh, rows * d, dw, c->grad_dtype, (int64_t)V * d, loss, st));

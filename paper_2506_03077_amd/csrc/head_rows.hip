@@ -210,7 +210,7 @@ hipError_t reduce_add(const float* v, int n, float* out, hipStream_t st, const i
 // slice, an exclusive scan of the 1024 counts in LDS, then each thread writes its slice's indices in order.
 __global__ __launch_bounds__(1024) void compact_active_k(const int32_t* __restrict__ targets, int64_t rows, int chunk, int V,
                                                          int32_t* __restrict__ index, int32_t* __restrict__ chunk_rows,
-                                                         int n_chunks) {
+                                                         int n_chunks, int group, int32_t* __restrict__ group_rows, int n_groups) {
   __shared__ int cnt[1024];
   const int tid = threadIdx.x;
   const int64_t per = (rows + 1023) / 1024;
@@ -230,11 +230,12 @@ __global__ __launch_bounds__(1024) void compact_active_k(const int32_t* __restri
     if ((uint32_t)targets[r] < (uint32_t)V) index[pos++] = (int32_t)r;
   const int total = cnt[1023];
   for (int i = tid; i < n_chunks; i += 1024) chunk_rows[i] = min(chunk, max(0, total - i * chunk));
+  for (int i = tid; i < n_groups; i += 1024) group_rows[i] = min(group, max(0, total - i * group));
   if (tid == 0) chunk_rows[n_chunks] = total;
 }
 hipError_t compact_active(const int32_t* targets, int64_t rows, int chunk, int V, int32_t* index, int32_t* chunk_rows, int n_chunks,
-                          hipStream_t st) {
-  compact_active_k<<<1, 1024, 0, st>>>(targets, rows, chunk, V, index, chunk_rows, n_chunks);
+                          int group, int32_t* group_rows, int n_groups, hipStream_t st) {
+  compact_active_k<<<1, 1024, 0, st>>>(targets, rows, chunk, V, index, chunk_rows, n_chunks, group, group_rows, n_groups);
   return hipGetLastError();
 }
 

@@ -257,9 +257,9 @@ hipError_t reduce_add(const float* v, int n, float* out, hipStream_t st, const i
 // number of targets >= V if there is any
 hipError_t count_active(const int32_t* targets, int B, int T, int V, float* seq_weight, int64_t* n_active, hipStream_t st);
 // index[0..n_active) = rows with 0 <= target < V in increasing order; chunk_rows[i] = clamp(n_active - i*chunk, 0, chunk) for i < n_chunks,
-// chunk_rows[n_chunks] = n_active
+// chunk_rows[n_chunks] = n_active; group_rows: the same for n_groups groups of `group` rows
 hipError_t compact_active(const int32_t* targets, int64_t rows, int chunk, int V, int32_t* index, int32_t* chunk_rows, int n_chunks,
-                          hipStream_t st);
+                          int group, int32_t* group_rows, int n_groups, hipStream_t st);
 // dst[r,:] = src[index[r],:] for r < *rows_dev, zero rows after;  scatter: dst[index[r],:] = src[r,:] for r < *rows_dev
 // move_rows: a scatter and a gather, independent of each other, in one launch
 // dst [C, ld] = src [R, C]^T (bf16, C % 8 == 0, 16-byte aligned); rows_dev: only the first *rows_dev rows count.  Columns from there to the next

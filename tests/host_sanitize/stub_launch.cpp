@@ -181,8 +181,9 @@ hipError_t reduce_add(const float* v, int n, float* out, hipStream_t, const int*
 hipError_t count_active(const int32_t* targets, int B, int T, int, float* seq_weight, int64_t* n_active, hipStream_t) {
   rd(targets, (size_t)B * T * 4); wr(seq_weight, (size_t)B * 4); wr(n_active, 8); return hipSuccess;
 }
-hipError_t compact_active(const int32_t* targets, int64_t rows, int, int, int32_t* index, int32_t* chunk_rows, int n_chunks, hipStream_t) {
-  rd(targets, rows * 4); wr(index, rows * 4); wr(chunk_rows, (size_t)(n_chunks + 1) * 4); return hipSuccess;
+hipError_t compact_active(const int32_t* targets, int64_t rows, int, int, int32_t* index, int32_t* chunk_rows, int n_chunks, int, int32_t* group_rows, int n_groups, hipStream_t) {
+  rd(targets, rows * 4); wr(index, rows * 4); wr(chunk_rows, (size_t)(n_chunks + 1) * 4);
+  if (n_groups) wr(group_rows, (size_t)n_groups * 4); return hipSuccess;
 }
 hipError_t move_rows(int dt, const RowMove& scatter, const RowMove& gather, int d, hipStream_t) {
   if (scatter.max_rows > 0) { rd(scatter.src, (size_t)scatter.max_rows * d * es(dt)); rd(scatter.index, (size_t)scatter.max_rows * 4); rd(scatter.rows_dev, 4); }
