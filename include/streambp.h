@@ -243,6 +243,9 @@ typedef struct {
                                     gets o = 0, lse = -inf and no gradient             */
 } sbp_attn_cfg;
 
+/* What streambp_attn_chunk_backward makes full use of: row statistics, and up to 64 MiB of partial dK/dV where the key
+ * blocks alone would leave the chip idle.  A workspace with room for the statistics alone (2 * Hq * c floats, 256-byte
+ * aligned) is accepted too and gives the same results, more slowly. */
 size_t streambp_attn_workspace_bytes(const sbp_attn_cfg *cfg);
 
 /* q [c, Hq, dh] (rotated); k, v [>= s + c, Hkv, dh]; o [c, Hq, dh] out;

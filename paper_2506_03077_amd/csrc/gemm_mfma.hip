@@ -1,7 +1,8 @@
-// bf16 MFMA GEMM for gfx950, fp32 accumulation, three operand layouts:
+// bf16 MFMA GEMM for gfx950, fp32 accumulation, four operand layouts:
 //   NT  C[M,N] = A[M,K] B[N,K]^T     (forward projections: both operands K-contiguous)
 //   NN  C[M,N] = A[M,K] B[K,N]       (input gradients dX = dY W)
 //   TN  C[M,N] = A[K,M]^T B[K,N]     (weight gradients dW += dY^T X; K = chunk rows)
+//   TT  C[M,N] += A[K,M]^T B[N,K]^T  (the same from a transposed copy of X, where the caller keeps one)
 //
 // Design (CDNA4):
 //  * 256x256 output tile per workgroup, 8 wavefronts in two groups of four that alternate between fetching and multiplying
@@ -11,7 +12,7 @@
 //  * K-contiguous operands are read from LDS with ds_read_b128; operands whose
 //    reduction index is the slow dimension in memory are kept in their natural
 //    [k][m|n] layout in LDS and fetched with the transposing LDS load
-//    (ds_read_b64_tr_b16), so no transposed copy ever exists in HBM.
+//    (ds_read_b64_tr_b16), so no transposed copy has to exist in HBM.
 //  * Both LDS layouts are XOR-swizzled (at 16-byte / 32-byte granularity) so that
 //    the fragment reads are bank-conflict free; because a direct-to-LDS load
 //    writes lane-linear, the swizzle is applied on the global-address side.
@@ -329,7 +330,8 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
     return;
   }
   if constexpr (GLU) {
-    // gate and up of a column are the same registers of the two halves
+    // Gate and up of a column are the same registers of the two halves.  Against storing both and reading them again (2048 x 18944 x 3584: 430 us
+    // and 37 for the elementwise pass) the product is bound as before and the pass is gone: forward of 8192 rows, four chunks, 4.02 -> 3.81 ms.
     __syncthreads();
 #pragma unroll
     for (int ha = 0; ha < 2; ++ha)
@@ -373,7 +375,8 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
       __syncthreads();
       if constexpr (MODE == 4) {
         // bf16 C += acc: every element has exactly one owner per launch; the sum is formed in fp32 and rounded once.  The loads
-        // of C (16 bytes per lane), or of the C0 that it starts from, go out before the first use.
+        // of C (16 bytes per lane), or of the C0 that it starts from, go out before the first use.  (C0: a copy of 24 us before and 39 us of
+        // product per 18944 x 3584 matrix, 222 us for seven matrices in one launch now.)
         const bf16_t* from = C0 ? (const bf16_t*)C0 : Cb;
         const int c8 = threadIdx.x & 31, col = n0 + c8 * 8;
         bf16x8 old[8];

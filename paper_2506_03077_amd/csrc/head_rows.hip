@@ -263,12 +263,6 @@ hipError_t move_rows(int dt, const RowMove& scatter, const RowMove& gather, int 
   else move_rows_k<float><<<n, 256, 0, st>>>(scatter, gather, d);
   return hipGetLastError();
 }
-hipError_t gather_rows(int dt, const void* src, const int32_t* index, const int* rows_dev, void* dst, int max_rows, int d, hipStream_t st) {
-  return move_rows(dt, RowMove{}, RowMove{src, index, rows_dev, dst, max_rows}, d, st);
-}
-hipError_t scatter_rows(int dt, const void* src, const int32_t* index, const int* rows_dev, void* dst, int max_rows, int d, hipStream_t st) {
-  return move_rows(dt, RowMove{src, index, rows_dev, dst, max_rows}, RowMove{}, d, st);
-}
 
 // Active rows are those with 0 <= target < V.  A target >= V is a caller error the host cannot see (the ids live on
 // the device): such rows are treated as ignored everywhere - the id is never used as an index - and the call reports

@@ -260,15 +260,13 @@ hipError_t count_active(const int32_t* targets, int B, int T, int V, float* seq_
 // chunk_rows[n_chunks] = n_active; group_rows: the same for n_groups groups of `group` rows
 hipError_t compact_active(const int32_t* targets, int64_t rows, int chunk, int V, int32_t* index, int32_t* chunk_rows, int n_chunks,
                           int group, int32_t* group_rows, int n_groups, hipStream_t st);
-// dst[r,:] = src[index[r],:] for r < *rows_dev, zero rows after;  scatter: dst[index[r],:] = src[r,:] for r < *rows_dev
-// move_rows: a scatter and a gather, independent of each other, in one launch
+// A gather, dst[r,:] = src[index[r],:] for r < *rows_dev, zero rows after, and a scatter, dst[index[r],:] = src[r,:] for r < *rows_dev, independent of
+// each other, in one launch; max_rows 0: none
+struct RowMove { const void* src; const int32_t* index; const int* rows_dev; void* dst; int max_rows; };
+hipError_t move_rows(int dt, const RowMove& scatter, const RowMove& gather, int d, hipStream_t st);
 // dst [C, ld] = src [R, C]^T (bf16, C % 8 == 0, 16-byte aligned); rows_dev: only the first *rows_dev rows count.  Columns from there to the next
 // multiple of 64 become zeros (ld reaches to R's next multiple of 64, % 8 == 0); those after it are not written.
 hipError_t transpose_rows(const void* src, const int32_t* rows_dev, int R, int C, void* dst, int64_t ld, hipStream_t st);
-struct RowMove { const void* src; const int32_t* index; const int* rows_dev; void* dst; int max_rows; };
-hipError_t move_rows(int dt, const RowMove& scatter, const RowMove& gather, int d, hipStream_t st);
-hipError_t gather_rows(int dt, const void* src, const int32_t* index, const int* rows_dev, void* dst, int max_rows, int d, hipStream_t st);
-hipError_t scatter_rows(int dt, const void* src, const int32_t* index, const int* rows_dev, void* dst, int max_rows, int d, hipStream_t st);
 // DPO fix-up: factor = sigmoid(beta*ell)-1 ; scales dh (dt) and dw (fp32) in place, loss += -log sigmoid(beta*ell)
 hipError_t dpo_finish(int dt, const float* ell, float beta, void* dh, int64_t n_dh, void* dw, int dw_dt, int64_t n_dw,
                       float* loss, hipStream_t st);

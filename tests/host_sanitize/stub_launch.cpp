@@ -190,12 +190,6 @@ hipError_t move_rows(int dt, const RowMove& scatter, const RowMove& gather, int 
   if (gather.max_rows > 0) { rd(gather.index, (size_t)gather.max_rows * 4); rd(gather.rows_dev, 4); wr(gather.dst, (size_t)gather.max_rows * d * es(dt)); }
   return hipSuccess;
 }
-hipError_t gather_rows(int dt, const void* src, const int32_t* index, const int* rows_dev, void* dst, int max_rows, int d, hipStream_t st) {
-  return move_rows(dt, RowMove{}, RowMove{src, index, rows_dev, dst, max_rows}, d, st);
-}
-hipError_t scatter_rows(int dt, const void* src, const int32_t* index, const int* rows_dev, void* dst, int max_rows, int d, hipStream_t st) {
-  return move_rows(dt, RowMove{src, index, rows_dev, dst, max_rows}, RowMove{}, d, st);
-}
 hipError_t dpo_finish(int dt, const float* ell, float, void* dh, int64_t n_dh, void* dw, int dw_dt, int64_t n_dw, float* loss, hipStream_t) {
   rd(ell, 4); wr(dh, n_dh * es(dt)); wr(dw, n_dw * es(dw_dt)); wr(loss, 4); return hipSuccess;
 }
