@@ -6,7 +6,7 @@ from test_gpu_parity_small import head_case
 
 pytestmark = pytest.mark.gpu
 
-CFG = dict(dtype="bf16", hidden=16384, n_q_heads=4, n_kv_heads=2, head_dim=64, mlp_width=512, vocab=6107)
+CFG = dict(dtype="bf16", n_q_heads=4, n_kv_heads=2, head_dim=64, mlp_width=512)
 
 
 @pytest.mark.parametrize("grad", ["f32", "bf16"])
@@ -22,7 +22,8 @@ def test_both_operands_transposed(K, M, N, grad):
     _check(C, want, K)
 
 
+@pytest.mark.parametrize("hidden,vocab", [(16384, 6107), (16384, 6112), (4096, 24424)])      # fp32 logits; numerators chunk by chunk; numerators in spans
 @pytest.mark.parametrize("T,chunk,group", [(1, 64, 0), (65, 64, 0), (200, 65, 0), (200, 65, 130), (130, 63, 63)])
-def test_head_with_transposed_rows(T, chunk, group):
+def test_head_with_transposed_rows(T, chunk, group, hidden, vocab):
     # a chunk of one row, chunks one row longer and shorter than the transposed copy's 64-column tiles, groups of every size; some rows are ignored
-    head_case(CFG, 1, T, chunk, "sft", loss_scale=1.0 / max(1, T), dw_group_rows=group, grad_dtype="f32" if T != 130 else "bf16")
+    head_case(dict(CFG, hidden=hidden, vocab=vocab), 1, T, chunk, "sft", loss_scale=1.0 / max(1, T), dw_group_rows=group, grad_dtype="f32" if T != 130 else "bf16")
