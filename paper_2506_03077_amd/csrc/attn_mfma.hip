@@ -805,6 +805,15 @@ __global__ __launch_bounds__(AT_THREADS) void attn_bwd_dq_mfma_k(const bf16_t* _
 // 28 / 4 heads: dQ + dK/dV 3.08 -> 2.95 ms, all of it here (about 1.85 -> 1.72), against one barrier per tile and each wave doing its
 // products and its vector work in any order.
 // The loop walks the query tiles at or below the diagonal and, for each, the query heads of the group.
+//
+// Its steps come in `slices` shares, whose sums are added to dK / dV in their order.  Where there is room for them a workgroup takes each share
+// and leaves its sum in `part`.  Without that room a workgroup takes one share after the other, with the same sums in the same order.  It empties
+// its pipeline between them, which costs about three steps each time; IN_TURN, for the chunks of few key blocks that come in many shares,
+// walks them without a break and keeps the total beside the present sum, in registers.  Both only fit for half of the head's columns, so two
+// workgroups share a key block, each with all scores and half of the second product.  Whole backward, without / with a break | one share, dQ
+// apart | with room, 28 / 4 heads: 512 queries from 0 228 / 123 | 143 | 41 us, 2048 from 0 401 / 357 | 459 | 177; 512 from 2560 (96 blocks) 135 /
+// 124 | 184 | 123, from 2816 (104 blocks, whose 208 workgroups leave dQ too few CUs) 136 / 152 | 188 | 127, from 3500 145 / 198 | 205 | 146.
+constexpr int IN_TURN_BLOCKS = 96;       // key blocks times K/V heads up to which shares are taken without a break
 constexpr int KV_STAGES = 4;
 constexpr int CHAIN = 6;                 // LDS fragments requested ahead of the products (dK/dV)
 
@@ -816,7 +825,7 @@ struct DkvShared {
   float sL[KV_STAGES][QT];                        // (log2-domain) log-sum-exp of the tile's queries
   float sDl[KV_STAGES][QT];                       // delta of the tile's queries
 };
-template <int DH>
+template <int DH, bool IN_TURN>
 __device__ __forceinline__ void dkv_block(DkvShared<DH>& sh, int key_block, int kvh, int slice, const bf16_t* __restrict__ q,
                                           const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, const bf16_t* __restrict__ d_o,
                                           const float* __restrict__ lse2, const float* __restrict__ delta, float* __restrict__ dk,
@@ -848,7 +857,26 @@ __device__ __forceinline__ void dkv_block(DkvShared<DH>& sh, int key_block, int 
   const uint32_t sp_lane = pin(lds_addr(&sP[kb][0][lane]));                      // + slot * 1024
   const uint32_t stat_lane = pin(lds_addr(role_p ? &sL[0][4 * half] : &sDl[0][4 * half]));   // + stage * 256 + (b * 32 + 8 a) * 4
 
-  constexpr int KS = DH / 16, DB = DH / 32;
+  constexpr int KS = DH / 16, DB = DH / 32 / (IN_TURN ? 2 : 1);
+  const int col0 = IN_TURN ? slice * (DH / 2) : 0;       // IN_TURN: `slice` is the half of the columns
+  uint32_t g_tr[2 * DB];
+#pragma unroll
+  for (int i = 0; i < 2 * DB; ++i) g_tr[i] = IN_TURN && slice ? gt.tr[(2 * DB + i) % (DH / 16)] : gt.tr[i];
+  // what this lane's key grows by, rows = head_dim col0 + 32 i + 8 a + 4 half .. + 3
+  float* out = (role_p ? dv : dk) + (int64_t)key_row * kv_stride + (int64_t)kvh * DH + col0;
+  f32x16 sum[IN_TURN ? DB : 1];
+  if constexpr (IN_TURN) {
+#pragma unroll
+    for (int i = 0; i < DB; ++i)
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        const f32x4 u = *(const f32x4*)(out + i * 32 + 8 * a + 4 * half);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum[i][4 * a + e] = u[e];
+      }
+#pragma unroll
+    for (int i = 0; i < DB; ++i) asm volatile("" : "+v"(sum[i]));
+  }
   bf16x8 breg[KS];   // B operand of the first product: K rows (role P) or V rows (role S) of my key
   {
     const bf16_t* src = (role_p ? k : v) + (int64_t)key_row * kv_stride + (int64_t)kvh * DH + half * 8;
@@ -866,12 +894,11 @@ __device__ __forceinline__ void dkv_block(DkvShared<DH>& sh, int key_block, int 
   int n_qt = (c + QT - 1) / QT;
   if (window > 0) n_qt = min(n_qt, max(0, key0 + KV_TILE - 1 + window - 1 - q_start) / QT + 1);
   const int n_all = max(0, n_qt - qt_first) * G;
-  // The steps come in `slices` shares: a workgroup each where there is room for the parts, one after the other in this one
-  // otherwise (the same sums in the same order: bit-identical results).
-  for (int z = part ? slice : 0, z_end = part ? z + 1 : slices; z < z_end; ++z) {
-  const int it0 = (int)((int64_t)n_all * z / slices), n_iter = (int)((int64_t)n_all * (z + 1) / slices) - it0;
+  auto share = [&](int z) { return (int)((int64_t)n_all * z / slices); };      // first step of share z
+  for (int z = part ? slice : 0, z_last = IN_TURN ? 0 : part ? slice : slices - 1; z <= z_last; ++z) {
+  const int it0 = IN_TURN ? 0 : share(z), n_iter = (IN_TURN ? n_all : share(z + 1)) - it0;
 
-  // Loads of this share's next tile (query tile lq, head lh of the group); past the end the last one again, so that the wait counts
+  // Loads of the next tile (query tile lq, head lh of the group); past the end the last one again, so that the wait counts
   // stay the same.
   int lq = qt_first + it0 / G, lh = it0 % G, left = n_iter;
   auto issue = [&](int stage) {
@@ -903,12 +930,24 @@ __device__ __forceinline__ void dkv_block(DkvShared<DH>& sh, int key_block, int 
     bf16x8 w[NT][2][2];      // P or dS: [term][query block][k16 step]
 #pragma unroll
     for (int i = 0; i < DB; ++i) acc[i] = zero16();
+    const float f = RP ? 1.0f : scale;
+    int present = 0, present_end = IN_TURN ? share(1) : 0;      // IN_TURN: the share that is being summed, and the step after it
+    auto close = [&]() __attribute__((always_inline)) {         // total += the share's sum
+#pragma unroll
+      for (int i = 0; i < (IN_TURN ? DB : 0); ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+#pragma clang fp contract(off)      // product and sum rounded separately, with or without parts
+          sum[i][r] += acc[i][r] * f;
+          acc[i][r] = 0.f;
+        }
+    };
     int qbase = (qt_first + it0 / G) * QT, head = it0 % G;      // of the present step's tile
     bool held = false;                                          // the previous tile left something to multiply
     auto second = [&](int stage) __attribute__((always_inline)) {
       const uint32_t so = (uint32_t)(stage * TILE64<DH>);
       mfma_chain<4 * DB, CHAIN>(
-          [&](int n) { const uint32_t o = so + (n / DB * 16) * (DH * 2); return lds_tr(gt.tr[n % DB * 2] + o, gt.tr[n % DB * 2 + 1] + o); },
+          [&](int n) { const uint32_t o = so + (n / DB * 16) * (DH * 2); return lds_tr(g_tr[n % DB * 2] + o, g_tr[n % DB * 2 + 1] + o); },
           [&](int n, const bf16x8& g) {
 #pragma unroll
             for (int u = 0; u < NT; ++u) acc[n % DB] = MFMA(g, w[u][n / DB >> 1][n / DB & 1], acc[n % DB]);
@@ -1004,6 +1043,10 @@ __device__ __forceinline__ void dkv_block(DkvShared<DH>& sh, int key_block, int 
         const bool act = j < n_iter && tile_active(qbase);
         __builtin_amdgcn_s_setprio(1);
         if (held) second((stage + 3) % KV_STAGES);
+        if (IN_TURN && j == present_end) {
+          close();
+          while (present_end == j && present + 1 < slices) present_end = share(++present + 1);      // (shares without steps add nothing)
+        }
         if (act) first(stage);
         __builtin_amdgcn_s_setprio(0);
         if (!RP) AT_WAIT_VM(LOADS);
@@ -1026,29 +1069,35 @@ __device__ __forceinline__ void dkv_block(DkvShared<DH>& sh, int key_block, int 
       AT_WAIT_VM(0);
       if (RP) AT_SLOT_BARRIER();        // both roles execute the same number of barriers
     }
-    if (my_key < n_total) {
+    if (my_key >= n_total) return;
+    if constexpr (IN_TURN) {
+      close();
+#pragma unroll
+      for (int i = 0; i < DB; ++i)
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+          *(f32x4*)(out + i * 32 + 8 * a + 4 * half) = f32x4{sum[i][4 * a], sum[i][4 * a + 1], sum[i][4 * a + 2], sum[i][4 * a + 3]};
+    } else {
       // several workgroups per key block: each leaves its sum in its own slice [workgroup][dk | dv][key][kv head][DH]
       const int64_t first = (int64_t)key_block0 * KV_TILE;
-      float* out = part ? part + ((int64_t)z * 2 + (RP ? 1 : 0)) * (n_total - first) * kv_stride + (my_key - first) * kv_stride + (int64_t)kvh * DH
-                        : (RP ? dv : dk) + (int64_t)my_key * kv_stride + (int64_t)kvh * DH;
-      const float f = RP ? 1.0f : scale;
+      float* to = part ? part + ((int64_t)z * 2 + (RP ? 1 : 0)) * (n_total - first) * kv_stride + (my_key - first) * kv_stride + (int64_t)kvh * DH : out;
 #pragma unroll
       for (int i = 0; i < DB; ++i)
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
           const int d0 = i * 32 + 8 * a + 4 * half;
-          float4 u = part ? make_float4(0.f, 0.f, 0.f, 0.f) : *(float4*)(out + d0);
+          float4 u = part ? make_float4(0.f, 0.f, 0.f, 0.f) : *(float4*)(to + d0);
           {
-#pragma clang fp contract(off)      // product and sum rounded separately, with or without parts
+#pragma clang fp contract(off)
             u.x += acc[i][4 * a + 0] * f; u.y += acc[i][4 * a + 1] * f; u.z += acc[i][4 * a + 2] * f; u.w += acc[i][4 * a + 3] * f;
           }
-          *(float4*)(out + d0) = u;
+          *(float4*)(to + d0) = u;
         }
     }
   };
   if (role_p) run(std::true_type{});
   else run(std::false_type{});
-  if (z + 1 < z_end) __syncthreads();      // the next share loads into the stages of this one
+  if (z < z_last) __syncthreads();      // the next share loads into the stages of this one
   }
 }
 
@@ -1060,34 +1109,41 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
                                                                   int q_start, int c, float scale, int window, int kv_first,
                                                                   int key_block0, int slices, float* __restrict__ part) {
   __shared__ __attribute__((aligned(1024))) DkvShared<DH> sh;
-  dkv_block<DH>(sh, blockIdx.x, blockIdx.y, blockIdx.z, q, k, v, d_o, lse2, delta, dk, dv, Hq, Hkv, q_start, c, scale, window, kv_first,
-                key_block0, slices, part);
+  dkv_block<DH, false>(sh, blockIdx.x, blockIdx.y, blockIdx.z, q, k, v, d_o, lse2, delta, dk, dv, Hq, Hkv, q_start, c, scale, window,
+                       kv_first, key_block0, slices, part);
 }
 
 // dK/dV and dQ in one launch, the workgroups of dK/dV, the longer ones, first: for chunks that are a few rounds of the chip, where each
 // launch on its own leaves CUs idle at its end (777 windowed queries, 32 / 8 heads: 76 + 35 -> 102 us, the whole call 154 -> 141; a chunk
 // of many rounds gains nothing).
-template <int DH, bool SPLIT>
-__global__ __launch_bounds__(AT_THREADS) void attn_bwd_mfma_k(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
-                                                              const bf16_t* __restrict__ d_o, const float* __restrict__ lse,
-                                                              const float* __restrict__ lse2, const float* __restrict__ delta,
-                                                              bf16_t* __restrict__ dq, float* __restrict__ dk, float* __restrict__ dv, int Hq,
-                                                              int Hkv, int q_start, int c, float scale, const float2* __restrict__ rope,
-                                                              int window, int kv_first, int key_block0, int key_blocks, int slices,
-                                                              float* __restrict__ part, int q_blocks) {
+template <int DH, bool SPLIT, bool IN_TURN>
+__device__ __forceinline__ void bwd_block(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
+                                          const bf16_t* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ lse2,
+                                          const float* __restrict__ delta, bf16_t* __restrict__ dq, float* __restrict__ dk, float* __restrict__ dv,
+                                          int Hq, int Hkv, int q_start, int c, float scale, const float2* __restrict__ rope, int window,
+                                          int kv_first, int key_block0, int key_blocks, int slices, float* __restrict__ part, int q_blocks) {
   static_assert(AT_THREADS == KV_THREADS, "one workgroup shape");
   __shared__ __attribute__((aligned(1024))) union { DkvShared<DH> dkv; DqShared<DH, SPLIT> dq; } sh;
-  const int n_dkv = key_blocks * Hkv * (part ? slices : 1), b = blockIdx.x;
+  const int n_dkv = key_blocks * Hkv * (IN_TURN ? 2 : part ? slices : 1), b = blockIdx.x;
   if (b < n_dkv) {
     const int r = b / key_blocks;
-    dkv_block<DH>(sh.dkv, b % key_blocks, r % Hkv, r / Hkv, q, k, v, d_o, lse2, delta, dk, dv, Hq, Hkv, q_start, c, scale, window, kv_first,
-                  key_block0, slices, part);
+    dkv_block<DH, IN_TURN>(sh.dkv, b % key_blocks, r % Hkv, r / Hkv, q, k, v, d_o, lse2, delta, dk, dv, Hq, Hkv, q_start, c, scale, window, kv_first,
+                           key_block0, slices, part);
   } else {
     // the tiles with the most keys first
     const int i = b - n_dkv;
     dq_tile<DH, SPLIT>(sh.dq, q_blocks - 1 - i / Hq, i % Hq, q, k, v, d_o, lse, delta, dq, Hq, Hkv, q_start, c, scale, rope, window, kv_first);
   }
 }
+#define BWD_PARAMS const bf16_t *__restrict__ q, const bf16_t *__restrict__ k, const bf16_t *__restrict__ v, const bf16_t *__restrict__ d_o, \
+                   const float *__restrict__ lse, const float *__restrict__ lse2, const float *__restrict__ delta, bf16_t *__restrict__ dq, \
+                   float *__restrict__ dk, float *__restrict__ dv, int Hq, int Hkv, int q_start, int c, float scale, \
+                   const float2 *__restrict__ rope, int window, int kv_first, int key_block0, int key_blocks, int slices, float *__restrict__ part, int q_blocks
+#define BWD_ARGS q, k, v, d_o, lse, lse2, delta, dq, dk, dv, Hq, Hkv, q_start, c, scale, rope, window, kv_first, key_block0, key_blocks, slices, part, q_blocks
+template <int DH, bool SPLIT> __global__ __launch_bounds__(AT_THREADS) void attn_bwd_mfma_k(BWD_PARAMS) { bwd_block<DH, SPLIT, false>(BWD_ARGS); }
+template <int DH, bool SPLIT> __global__ __launch_bounds__(AT_THREADS) void attn_bwd_in_turn_k(BWD_PARAMS) { bwd_block<DH, SPLIT, true>(BWD_ARGS); }
+#undef BWD_PARAMS
+#undef BWD_ARGS
 
 // dk / dv += sum over the slices of the split form, in their order, keys from `first` on.  A thread takes elements e .. e + 3 and e + DH / 2 .. of a
 // (key, head): what the rotary embedding pairs, so that the chunk's own rows, final with this call, leave as dkc = RoPE^T(dk) and dvc = dv
@@ -1191,15 +1247,19 @@ static hipError_t backward_dh(const AttnArgs& a, hipStream_t st) {
   const int slices = std::max(1, a.dkv_slices);
   float* part = slices > 1 ? a.dkv_scratch : nullptr;
   const bool halves = half_tiles_fill_better(a);
-  const int64_t n_dkv = (int64_t)key_blocks * a.Hkv * (part ? slices : 1), q_blocks = cdiv(a.q_len, halves ? TQ / 2 : TQ);
+  const int64_t blocks = (int64_t)key_blocks * a.Hkv, q_blocks = cdiv(a.q_len, halves ? TQ / 2 : TQ);
+  const bool in_turn = !part && slices > 1 && blocks <= IN_TURN_BLOCKS;      // two workgroups per key block
+  const int64_t n_dkv = blocks * (in_turn ? 2 : part ? slices : 1);
   const bf16_t *q = (const bf16_t*)a.q, *k = (const bf16_t*)a.k, *v = (const bf16_t*)a.v, *d_o = (const bf16_t*)a.d_o;
-  if (n_dkv > 0 && n_dkv + q_blocks * a.Hq <= MERGED_MAX) {
+  if (n_dkv > 0 && (in_turn || n_dkv + q_blocks * a.Hq <= MERGED_MAX)) {
     auto launch = [&](auto kernel) {
       kernel<<<(unsigned)(n_dkv + q_blocks * a.Hq), AT_THREADS, 0, st>>>(q, k, v, d_o, a.lse, lse2, a.delta, (bf16_t*)a.dq, a.dk, a.dv, a.Hq, a.Hkv, a.q_start,
                                                                          a.q_len, a.scale, a.rope_q, a.window, a.kv_first, kb0, key_blocks, slices, part,
                                                                          (int)q_blocks);
     };
-    if (halves) launch(attn_bwd_mfma_k<DH, true>);
+    if (in_turn && halves) launch(attn_bwd_in_turn_k<DH, true>);
+    else if (in_turn) launch(attn_bwd_in_turn_k<DH, false>);
+    else if (halves) launch(attn_bwd_mfma_k<DH, true>);
     else launch(attn_bwd_mfma_k<DH, false>);
   } else {
     auto launch_dq = [&](auto kernel) {

@@ -11,3 +11,11 @@ def test_reads_are_waited_for_within_the_slot(built, part, instances):  # noqa: 
     assert len(found) == instances
     worst = {n: barriers_passed_unwaited(c) for n, c in found.items()}
     assert max(worst.values()) == 0, {n: w for n, w in worst.items() if w}
+
+
+def test_shares_taken_without_a_break_have_kernels_that_keep_the_schedule(built):  # noqa: F811
+    """dK/dV without room for the sums of its shares: a loop around the pipeline refilled it for every share (143 -> 228 us for 512 queries)."""
+    found = _named(built, ("18attn_bwd_in_turn_k",))
+    assert len(found) == 4
+    worst = {n: barriers_passed_unwaited(c) for n, c in found.items()}
+    assert max(worst.values()) == 0, {n: w for n, w in worst.items() if w}
