@@ -14,41 +14,81 @@ namespace sbp {
 // load -> barrier -> multiply per slice of the reduction - so there is no LDS staging and no barrier before the sum over the waves (a
 // fixed order), and the loads of a wave's next step go out before it multiplies the present one.  Against 64 x 64 tiles staged
 // through LDS (the earlier form): 64 x 64 x 64 10.7 -> 3.2 us, 64 x 64 x 512 67 -> 6.5, 256 x 1500 x 256 36 -> 7.4; what reads of the
-// operands bound later is no worse: 1024^3 178 -> 35, 2048^3 416 -> 228 us (75 TFLOP/s).
+// operands bound later is no worse: 1024^3 178 -> 35, 2048^3 416 -> 232 us (74 TFLOP/s).
 // Lane l holds, of a 16-row block, row l % 16 at k 4 (l / 16) .. + 3 of the step; MFMA j of the step takes element j of both operands.
 constexpr int TILE = 32, WAVES = 8, KSTEP = 16;
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+// An operand's four elements of a row and step, held as they were loaded until the product that takes them (a conversion would wait for them in front of the
+// present step's products): bf16 in pairs where they lie side by side, else one by one.
+template <typename TI> struct Held;
+template <> struct Held<float> {
+  typedef f32x4 type;
+  typedef f32x4 four __attribute__((aligned(4)));      // rows may start anywhere
+  static __device__ __forceinline__ type pack(f32x4 v) { return v; }
+  static __device__ __forceinline__ float one(float x) { return x; }
+  static __device__ __forceinline__ f32x4 value(type v, bool) { return v; }
+};
+template <> struct Held<bf16_t> {
+  typedef u32x4 type;
+  typedef uint32_t two __attribute__((ext_vector_type(2)));
+  typedef two four __attribute__((aligned(2)));
+  static __device__ __forceinline__ type pack(two v) { return type{v[0], v[1], 0u, 0u}; }
+  static __device__ __forceinline__ uint32_t one(bf16_t x) { return (uint32_t)__builtin_bit_cast(uint16_t, x); }
+  static __device__ __forceinline__ f32x4 value(type v, bool pairs) {
+    f32x4 f;
+    f[0] = __uint_as_float(v[0] << 16);
+    f[1] = __uint_as_float(pairs ? v[0] & 0xffff0000u : v[1] << 16);
+    f[2] = __uint_as_float(pairs ? v[1] << 16 : v[2] << 16);
+    f[3] = __uint_as_float(pairs ? v[1] & 0xffff0000u : v[3] << 16);
+    return f;
+  }
+};
+// Both 16-row blocks of an operand for the step at k0: element (row, k + j), row-contiguous reductions at p[row * ld + k], reduction-major operands at
+// p[k * ld + row]; past the last row: the last row again (its products are not stored); past the end of the reduction: its last element
+// again (see step_values).  No load hangs on a lane condition, so that all of a step are under way at once: with one branch per element, the
+// earlier form, each was waited for before the next (1025 x 4097 x 4097, fp32 NN 1000 -> 607 us, bf16 TN 1106 -> 640; 4097 x 4097 x 129, bf16 NN 155 -> 139;
+// 4096^3 fp32 NN, which the L2 bounds, 2398 -> 2199).
 template <typename TI>
-__device__ __forceinline__ f32x4 operand(const TI* __restrict__ p, bool k_major, int64_t ld, int row, int rows, int k, int K, bool vec) {
-  // element (row, k + j): row-contiguous reductions at p[row * ld + k], reduction-major operands at p[k * ld + row]; past the end of
-  // the reduction: zeros; past the last row: the last row again (its products are not stored)
-  const int r = min(row, rows - 1);
-  f32x4 v = {0.f, 0.f, 0.f, 0.f};
-  if (!k_major) {
-    const TI* q = p + (int64_t)r * ld + k;
-    if (vec && k + 4 <= K) {
-      if constexpr (sizeof(TI) == 4) v = *(const f32x4*)q;
-      else {
-        typedef bf16_t bf16x4 __attribute__((ext_vector_type(4)));
-        const bf16x4 w = *(const bf16x4*)q;
+__device__ __forceinline__ void load_step(typename Held<TI>::type (&v)[2], const TI* __restrict__ p, int64_t ld, bool k_major, int r0, int rows, int k0, int K,
+                                          int li, int lg) {
+  const bool whole = k0 + KSTEP <= K;
+  const int k = k0 + 4 * lg;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = (float)w[j];
+  for (int i = 0; i < 2; ++i) {
+    const int r = min(r0 + i * 16 + li, rows - 1);
+    if (whole) {
+      if (k_major) {
+        const TI* q = p + (int64_t)k * ld + r;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[i][j] = Held<TI>::one(q[j * ld]);
+      } else {
+        v[i] = Held<TI>::pack(*(const typename Held<TI>::four*)(p + (int64_t)r * ld + k));
       }
     } else {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) if (k + j < K) v[j] = ldf(q + j);
+      for (int j = 0; j < 4; ++j) {
+        const int64_t kk = min(k + j, K - 1);
+        v[i][j] = Held<TI>::one(p[k_major ? kk * ld + r : (int64_t)r * ld + kk]);
+      }
     }
-  } else {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) if (k + j < K) v[j] = ldf(p + (int64_t)(k + j) * ld + r);
   }
-  return v;
+}
+template <typename TI>
+__device__ __forceinline__ f32x4 step_values(typename Held<TI>::type v, bool k_major, int k0, int K, int lg) {
+  const bool whole = k0 + KSTEP <= K;
+  f32x4 f = Held<TI>::value(v, whole && !k_major);
+  if (!whole) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) f[j] = k0 + 4 * lg + j < K ? f[j] : 0.f;
+  }
+  return f;
 }
 // Several problems in one launch, each with its own layout and one or more reduction segments (operand pairs whose products are summed into
 // one output): a launch of the small configuration costs 4.8 us however little it does, its layer and head issued 86 of them.
 // (NP problems, NS segments: the smallest of three sizes, as the arguments' cache lines are fetched one dependent miss after the other.)
 constexpr int GENERIC_PROBLEMS = 8, GENERIC_SEGMENTS = 56;
-struct GenericSegment { const void* A; const void* B; const int* rows_dev; int K, lda, ldb, vec; };       // vec: bit 0 A, bit 1 B
+struct GenericSegment { const void* A; const void* B; const int* rows_dev; int K, lda, ldb; };
 struct GenericProblem { void* C; int64_t ldc; int M, N, ta, tb, seg0, nseg, tile0, tiles_n; };
 template <int NP, int NS> struct GenericArgs { int n; GenericProblem p[NP]; GenericSegment s[NS]; };
 using GenericAll = GenericArgs<GENERIC_PROBLEMS, GENERIC_SEGMENTS>;
@@ -71,33 +111,40 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_generic_k(const GenericArgs<N
   if (m0 >= M) return;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), li = threadIdx.x & 15, lg = (threadIdx.x & 63) >> 4;
   f32x4 acc[2][2] = {};
-  f32x4 a[2], b[2];
-  // the steps of all segments, one after the other, dealt to the waves: seg, k0 = this wave's next one, K its segment's reduction
-  int seg = -1, k0 = 0, K = 0, dealt = 0;
+  // The steps of all segments, one after the other, dealt to the waves: k0 = this wave's next one.  What a step reads by is kept in registers and
+  // changes with the segment (NS == 1: never).
+  int seg = -1, k0 = 0, dealt = 0;
+  const TI *A = nullptr, *B = nullptr;
+  int K = 0, lda = 0, ldb = 0;
+  const bool ta = g.ta != 0, tb = g.tb != 0;
+  typename Held<TI>::type a[2], b[2];
+  auto enter = [&]() {
+    const GenericSegment& q = ga.s[NS == 1 ? 0 : g.seg0 + seg];
+    A = (const TI*)q.A; B = (const TI*)q.B; lda = q.lda; ldb = q.ldb;
+    K = ta ? min(q.K, rows(q)) : q.K;
+    k0 = ((wave - dealt) & (WAVES - 1)) * KSTEP;
+    dealt += (K + KSTEP - 1) / KSTEP;
+  };
   auto next = [&]() {
     k0 += WAVES * KSTEP;
     while (k0 >= K) {
-      dealt += (K + KSTEP - 1) / KSTEP;
-      if (++seg >= g.nseg) return false;
-      K = ga.s[g.seg0 + seg].K;
-      if (g.ta) K = min(K, rows(ga.s[g.seg0 + seg]));
-      k0 = ((wave - dealt) & (WAVES - 1)) * KSTEP;
+      if (NS == 1 || ++seg >= g.nseg) return false;
+      enter();
     }
     return true;
   };
   auto load = [&]() {
-    const GenericSegment& q = ga.s[g.seg0 + seg];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      a[i] = operand((const TI*)q.A, g.ta != 0, q.lda, m0 + i * 16 + li, M, k0 + 4 * lg, K, (q.vec & 1) != 0);
-      b[i] = operand((const TI*)q.B, g.tb == 0, q.ldb, n0 + i * 16 + li, N, k0 + 4 * lg, K, (q.vec & 2) != 0);
-    }
+    if (NS == 1) asm volatile("" : "+s"(lda), "+s"(ldb));      // (row times stride anew for each step: kept, all of them take 50 registers)
+    load_step<TI>(a, A, lda, ta, m0, M, k0, K, li, lg);
+    load_step<TI>(b, B, ldb, !tb, n0, N, k0, K, li, lg);
   };
+  if (NS == 1) { enter(); k0 -= WAVES * KSTEP; }
   bool more = next();
   const bool any = more;
   if (more) load();
   while (more) {
-    const f32x4 a0 = a[0], a1 = a[1], b0 = b[0], b1 = b[1];
+    const f32x4 a0 = step_values<TI>(a[0], ta, k0, K, lg), a1 = step_values<TI>(a[1], ta, k0, K, lg);
+    const f32x4 b0 = step_values<TI>(b[0], !tb, k0, K, lg), b1 = step_values<TI>(b[1], !tb, k0, K, lg);
     more = next();
     if (more) load();
 #pragma unroll
@@ -145,7 +192,6 @@ static bool generic_args(const GemmArgs* gs, int n, bool sum, GenericAll& ga, in
   tiles = 0;
   int seg_of[GENERIC_SEGMENTS], n_seg = 0;       // segments in the order given, and the problem each belongs to
   GenericSegment segs[GENERIC_SEGMENTS];
-  const uintptr_t four = 4 * dtype_size(gs[0].in_dt) - 1;
   for (int i = 0; i < n; ++i) {
     const GemmArgs& g = gs[i];
     if (g.M == 0 || g.N == 0) continue;
@@ -167,8 +213,7 @@ static bool generic_args(const GemmArgs* gs, int n, bool sum, GenericAll& ga, in
     for (int two = 0; two < (g.A2 ? 2 : 1); ++two) {
       if (n_seg == GENERIC_SEGMENTS) return false;
       const void *A = two ? g.A2 : g.A, *B = two ? g.B2 : g.B;
-      // four elements at a time where rows of a K-contiguous operand start at multiples of four
-      segs[n_seg] = GenericSegment{A, B, g.rows_dev, g.K, (int)g.lda, (int)g.ldb, (g.lda % 4 == 0 && !((uintptr_t)A & four) ? 1 : 0) | (g.ldb % 4 == 0 && !((uintptr_t)B & four) ? 2 : 0)};
+      segs[n_seg] = GenericSegment{A, B, g.rows_dev, g.K, (int)g.lda, (int)g.ldb};
       seg_of[n_seg++] = pi;
     }
   }

@@ -16,10 +16,11 @@ def most_loads_under_way(code):
     return best
 
 
-# at least: a piece of K and the elements of V across its rows; ... of q and d_o, and the statistics
-@pytest.mark.parametrize("part,instances,loads", [("18attn_fwd_generic_k", 24, 5), ("17attn_dq_generic_k", 20, 5), ("18attn_dkv_generic_k", 14, 17)])
+# at least: a GEMM operand's four elements of a row; attention: a piece of K and the elements of V across its rows; ... of q and d_o, and the statistics
+@pytest.mark.parametrize("part,instances,loads", [("14gemm_generic_k", 18, 4), ("18attn_fwd_generic_k", 24, 5), ("17attn_dq_generic_k", 20, 5),
+                                                  ("18attn_dkv_generic_k", 14, 17)])
 def test_loads_of_a_step_are_under_way_together(built, part, instances, loads):  # noqa: F811
-    """One wait per pair of 16-wide pieces made 64 keys of a 256-wide head take three times as long."""
+    """One wait per element or per pair of 16-wide pieces made a step of the GEMM up to 2.5 times, 64 keys of a 256-wide head 3 times as long."""
     found = _named(built, (part,))
     assert len(found) == instances
     few = {n: most_loads_under_way(c) for n, c in found.items() if most_loads_under_way(c) < loads}
