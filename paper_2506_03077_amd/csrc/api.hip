@@ -620,6 +620,13 @@ struct HeadWs {
   int64_t ldt; void* hT;
   float* gemm_scratch; size_t gemm_scratch_bytes; size_t bytes;
 };
+// Chunks whose rows the products of a small chunk run on at once (see streambp_lmhead_ce_backward): whole spans per weight-gradient group
+constexpr int HEAD_SPAN_ROWS = 2048;
+static int head_span_chunks(int dw_group, int cm) {
+  int chunks = std::max(1, std::min(dw_group, HEAD_SPAN_ROWS / cm));
+  while (dw_group % chunks != 0) --chunks;
+  return chunks;
+}
 static HeadWs carve_head(const sbp_head_cfg* c, void* ws) {
   const int64_t rows = (int64_t)c->batch * c->seq_len;
   const size_t cm = (size_t)std::min<int64_t>(c->chunk, rows);
@@ -644,7 +651,9 @@ static HeadWs carve_head(const sbp_head_cfg* c, void* ws) {
   h.ht = c->dtype == SBP_BF16 && c->hidden % 8 == 0 && (int64_t)c->vocab * c->hidden >= 100000000;
   h.ldt = (int64_t)align_up(cm, 64);
   h.hc = cv.take_bytes((h.ht ? cm : group) * c->hidden * dtype_size(c->dtype));
-  h.hT = h.ht ? cv.take_bytes((rows > (int64_t)cm ? h.dw_group : 1) * (size_t)c->hidden * h.ldt * 2) : nullptr;      // (or, a multiple of ldt wide, per unit of several chunks)
+  // (or, a multiple of ldt wide, per unit of several chunks: as many copies as the chunks of the call, whole units)
+  const int64_t chunks = align_up((size_t)cdiv(rows, (int64_t)cm), (size_t)head_span_chunks(h.dw_group, (int)cm));
+  h.hT = h.ht ? cv.take_bytes((size_t)std::min<int64_t>(h.dw_group, chunks) * c->hidden * h.ldt * 2) : nullptr;
   h.dhc = cv.take_bytes(cm * c->hidden * dtype_size(c->dtype));
   h.gemm_scratch_bytes = c->dtype == SBP_BF16 ? gemm_scratch_bytes((int)cm, c->hidden) : 0;
   h.gemm_scratch = (float*)cv.take_bytes(h.gemm_scratch_bytes);
@@ -691,9 +700,8 @@ int32_t streambp_lmhead_ce_backward(const sbp_head_cfg* c, const void* w, const 
   // alone runs on the span).  Small chunks are what this is for: the logits of 1024 rows at 7B widths are 2376 output tiles, a tenth round
   // of the CUs for 72 of them.  GRPO group of 8 x 1111 rows, chunk 1024, 18.8 -> 18.0 ms; fp32 layer and head of 256 rows, chunk 64 (five launches a
   // chunk) 371 -> 335 us; two-layer stack of 1024 wide layers, vocabulary 50257, chunk 512, 3.36 -> 3.30 ms.
-  // More rows than this gain no more: all 16384 of a group at once, dh takes 26.0 instead of 26.9 ms per 32768 rows, the row
+  // More rows than HEAD_SPAN_ROWS gain no more: all 16384 of a group at once, dh takes 26.0 instead of 26.9 ms per 32768 rows, the row
   // kernel, which finds less of dz in the caches, 4.2 instead of 3.65, and the whole call the same.
-  constexpr int HEAD_SPAN_ROWS = 2048;
   const bool padded = dt == DT_BF16;      // bf16 rows of z and dz are padded to a multiple of 64, dz with zeros: the products with dz need no particular vocabulary
   auto numerators = [&](const void* hc, void* dz, int n, const int* n_dev, const int32_t* idx, float2* stats, float* target_logit) {
     GemmArgs g = fwd_gemm(hc, w, dz, n, V, d, dt, DT_BF16);
@@ -707,8 +715,7 @@ int32_t streambp_lmhead_ce_backward(const sbp_head_cfg* c, const void* w, const 
   void *hc = s.hc, *dhc = s.dhc;
   float2* stats = s.stats;
   float* target_logit = s.target_logit;
-  int chunks = std::max(1, std::min(s.dw_group, HEAD_SPAN_ROWS / cm));
-  while (s.dw_group % chunks != 0) --chunks;              // whole spans per weight-gradient group
+  int chunks = head_span_chunks(s.dw_group, cm);
   const int span = (int)std::min<int64_t>(rows, (int64_t)cm * chunks);
   if (span > cm) {
     auto carve = [&](void* base) {

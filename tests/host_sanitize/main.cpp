@@ -181,6 +181,9 @@ int main(int argc, char** argv) {
     bad += run_layer(SBP_BF16, 1, 70001, 4096, 256, 4, 2, 128, 512, 0, false, 0);
     bad += run_head(SBP_BF16, 1, 32768, 2048, 3584, 152064, SBP_OBJ_SFT, SBP_F32);
     bad += run_head(SBP_BF16, 8, 16384, 2048, 3584, 152064, SBP_OBJ_GRPO, SBP_F32);
+    // transposed rows of h and products over spans: a last span and a last chunk of few rows, chunks that make no whole span
+    const int sizes[][2] = {{2049, 2048}, {2049, 1024}, {3073, 1024}, {2048, 512}, {700, 512}, {1300, 600}, {16385, 600}, {5000, 700}, {100, 1024}};
+    for (auto& s : sizes) bad += run_head(SBP_BF16, 1, s[0], s[1], 2048, 50257, SBP_OBJ_SFT, SBP_F32) + run_head(SBP_BF16, 1, s[0], s[1], 2048, 50264, SBP_OBJ_SFT, SBP_F32);
   }
   std::printf("%s: %d failing cases, %lld operand extents touched\n", bad ? "FAILED" : "OK", bad, sbp::stub_touches());
   return bad ? 1 : 0;

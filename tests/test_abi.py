@@ -94,6 +94,15 @@ def test_head_workspace_is_per_chunk():
     assert lean < 32768 * 152064 * 4 / 9     # with the weight gradient added chunk by chunk: a ninth
 
 
+def test_head_workspace_follows_the_chunks_of_the_call():
+    """One row more than a chunk: two copies of the transposed rows (14.7 MB each here), not as many as a weight-gradient group may have chunks."""
+    one, two, three = (sb.streambp_lmhead_workspace_bytes(sb.head_cfg(sb.SBP_BF16, 1, T, 2048, 3584, 152064)) for T in (2048, 2049, 4097))
+    copy = 2048 * 3584 * 2
+    assert two - one < 1.1 * copy and three - two < 1.1 * copy + 2048 * 152064 * 2
+    few, more = (sb.streambp_lmhead_workspace_bytes(sb.head_cfg(sb.SBP_BF16, 1, T, 512, 3584, 152064)) for T in (512, 2048))
+    assert more - few < 1536 * 152064 * 2 + 1.1 * copy
+
+
 def test_weight_gradient_group_rows_only_change_the_workspace():
     # dw_group_rows = 0 is the default (layer: 8192 rows, head: 16384); more rows keep more chunks' GEMM operands alive (at most eight chunks)
     big = dict(dtype=sb.SBP_BF16, hidden=3584, n_q_heads=28, n_kv_heads=4, head_dim=128, mlp_width=18944, chunk=2048, seq_len=32768)
