@@ -54,6 +54,22 @@ struct Carver {
   }
 };
 
+// fp32 buffers that one fill clears: a region of its own, so that nothing else can come to lie between them.
+struct Cleared { void* p = nullptr; size_t bytes = 0; };
+struct ClearedCarver {
+  Carver& cv; Cleared r;
+  explicit ClearedCarver(Carver& c) : cv(c) { r.p = c.base ? c.base + c.off : nullptr; }
+  float* take(size_t n) {
+    float* p = (float*)(r.p ? (char*)r.p + r.bytes : nullptr);
+    r.bytes += align_up(n * sizeof(float), 256);
+    return p;
+  }
+  Cleared close() {
+    cv.take_bytes(r.bytes);
+    return r;
+  }
+};
+
 bool valid_dtype(int32_t dt) { return dt == SBP_F32 || dt == SBP_BF16; }
 // weight gradients: fp32, or bf16 next to bf16 weights
 int32_t check_grad_dtype(int32_t dt, int32_t grad_dt) {
@@ -79,6 +95,7 @@ int dw_group_for(size_t chunk_rows, int32_t cfg_rows, int default_rows) {   // c
 struct LayerWs {
   void *K, *V;                 // [T, Hkv*dh] dt   cached for the whole sequence
   float *dK, *dV;              // [T, Hkv*dh] fp32 prefix accumulators
+  Cleared kv_grads;            // both
   float2* rope;                // [T, dh/2] cos/sin
   void *a, *q, *o, *m, *gate, *up, *act, *dact, *dh1_t, *d_o, *dq, *dkc, *dvc;   // per chunk, dt
   float *h1, *dm, *dh1, *da, *proj;                                       // per chunk, fp32 [c, d]
@@ -130,8 +147,10 @@ LayerWs carve_layer(const sbp_layer_cfg* c, void* ws) {
   LayerWs w;
   w.K = cv.take_bytes(T * kd * es);
   w.V = cv.take_bytes(T * kd * es);
-  w.dK = cv.take<float>(T * kd);
-  w.dV = cv.take<float>(T * kd);
+  ClearedCarver grads(cv);
+  w.dK = grads.take(T * kd);
+  w.dV = grads.take(T * kd);
+  w.kv_grads = grads.close();
   w.rope = cv.take<float2>(T * (c->head_dim / 2));
   w.a = cv.take_bytes(cm * d * es);
   w.q = cv.take_bytes(cm * qd * es);
@@ -234,8 +253,8 @@ int32_t kv_prepass(const sbp_layer_cfg* c, const sbp_layer_weights* w, const Lay
   return SBP_OK;
 }
 
-// Partitioned reforward of rows [r0, r0+n): fills a, q, o, lse, h1, m, gate, up, act.
-// with_act = false leaves s.act unwritten: the backward gets it from swiglu_bwd, which reads gate and up anyway
+// Partitioned reforward of rows [r0, r0+n): fills a, q, o, lse, h1, m, gate, up (with_act = false: the backward, which gets act from swiglu_bwd).
+// with_act = true (the plain forward): fills act, and gate and up only where the gated store does not take the products.
 int32_t chunk_reforward(const sbp_layer_cfg* c, const sbp_layer_weights* w, const LayerWs& s, const char* xb,
                         int r0, int n, int kv_first, bool with_act, hipStream_t st) {
   const int dt = c->dtype;
@@ -295,6 +314,7 @@ struct LoraCtx {
   int out_dim[7], in_dim[7];
   void *a_pad[7], *b_pad[7];       // [pad, in], [out, pad] in the storage type, zero beyond the rank
   float *da_pad[7], *db_pad[7];    // fp32 accumulators of the same shapes
+  Cleared grads;                   // all of them
   void *P[7], *Q[7];               // [chunk, pad] per adapted matrix
 };
 } // extern "C"
@@ -323,7 +343,7 @@ int32_t layer_backward_impl(const sbp_layer_cfg* c, const sbp_layer_weights* w, 
     char* dxb = at(dx, (size_t)b * T, d, es);
     const int kv_first = c->seq_first ? c->seq_first[b] : 0;      // rows before it are padding in front of the sequence
     if ((rc = kv_prepass(c, w, s_all, xb, n_dws > 0, st))) return rc;
-    HIPCHK(fill_zero(s_all.dK, (size_t)((char*)(s_all.dV + (size_t)T * kd) - (char*)s_all.dK), st));      // (dV follows dK)
+    HIPCHK(fill_zero(s_all.kv_grads.p, s_all.kv_grads.bytes, st));
     // Chunks run last to first: rows of dK/dV belonging to chunk i are final once
     // chunks >= i are done (later queries are the only other readers of those
     // keys), so the K/V-side gradient and dx of the chunk can be finished at once.
@@ -497,10 +517,12 @@ LoraWs carve_lora(const sbp_layer_cfg* c, const sbp_layer_weights* w, const sbp_
     x.P[j] = cv.take_bytes(cm * rp * es);
     x.Q[j] = cv.take_bytes(cm * rp * es);
   }
-  for (int j = 0; j < x.n; ++j) {       // (one after the other: cleared by one launch)
-    x.da_pad[j] = cv.take<float>(rp * x.in_dim[j]);
-    x.db_pad[j] = cv.take<float>((size_t)x.out_dim[j] * rp);
+  ClearedCarver grads(cv);
+  for (int j = 0; j < x.n; ++j) {
+    x.da_pad[j] = grads.take(rp * x.in_dim[j]);
+    x.db_pad[j] = grads.take((size_t)x.out_dim[j] * rp);
   }
+  x.grads = grads.close();
   L.layer_cfg = *c;
   L.layer_cfg.dw_group_rows = 1;          // no weight-gradient passes to group: one set of chunk buffers
   L.layer_ws = cv.take_bytes(0);
@@ -550,7 +572,7 @@ int32_t streambp_layer_lora_backward(const sbp_layer_cfg* c, const sbp_layer_wei
   }
   HIPCHK(pad_matrices(dt, pads, st));
   HIPCHK(gemm_batch(merge, X.n, st));
-  if (X.n > 0) HIPCHK(fill_zero(X.da_pad[0], (size_t)((char*)(X.db_pad[X.n - 1] + (size_t)X.out_dim[X.n - 1] * X.pad) - (char*)X.da_pad[0]), st));
+  if (X.n > 0) HIPCHK(fill_zero(X.grads.p, X.grads.bytes, st));
   const LayerWs s_all = carve_layer(&L.layer_cfg, L.layer_ws);
   if ((rc = layer_backward_impl(&L.layer_cfg, &L.w_eff, x, dy, dx, nullptr, &X, s_all, st))) return rc;
   AddJobs adds{};
