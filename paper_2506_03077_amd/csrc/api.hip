@@ -669,7 +669,8 @@ static HeadWs carve_head(const sbp_head_cfg* c, void* ws) {
   h.chunk_rows = cv.take<int32_t>(2 * (size_t)cdiv(rows, (int64_t)cm) + 1);
   // With h^T the weight gradient's GEMM reads one operand instead of two through transposing LDS loads: 152064 x 3584, 8192 rows: 7.50 -> 7.20 ms;
   // the copy takes 6 us per 2048-row chunk.  Whole call, 3584 x 152064: 32768 rows 86.2 -> 85.4 ms, 6000 13.10 -> 12.88, 1500 4.58 -> 4.53, 300 the
-  // same.  Smaller outputs do not repay the launch: 2048 x 32000 722 -> 718 us (1500 rows), 1024 x 50257 745 -> 752, 512 x 32000 339 -> 343.
+  // same.  With / without it, 8192 rows and 1500: 51 million outputs 0.985-0.989 and 1.00, 66 0.99 and 0.995, 84 0.98-0.99 and 0.995, 102 0.977 and 0.99, 263
+  // 0.99, 545 0.99: the line lies where the gain passes the spread of the runs (1.5 %) and pays for the copies' room.
   h.ht = c->dtype == SBP_BF16 && c->hidden % 8 == 0 && (int64_t)c->vocab * c->hidden >= 100000000;
   h.ldt = (int64_t)align_up(cm, 64);
   h.hc = cv.take_bytes((h.ht ? cm : group) * c->hidden * dtype_size(c->dtype));

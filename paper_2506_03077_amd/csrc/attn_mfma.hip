@@ -56,7 +56,9 @@ constexpr int TK = ATTN_TILE_K;          // 64 keys per step (fwd, dQ)
 constexpr int KV_TILE = ATTN_KV_TILE;    // keys per workgroup (dK/dV): 4 key blocks x 2 roles = 8 waves
 constexpr int KV_THREADS = 512;
 constexpr int QT = ATTN_KV_QUERIES;      // queries per step (dK/dV)
-constexpr int MERGED_MAX = 1024;         // workgroups of a backward that runs as one launch (four rounds of the chip)
+// Workgroups of a backward that runs as one launch (four rounds of the chip).  Whole backward in one launch against two, prefixes of 0 to 30720: up to 256
+// workgroups 0.52-0.98, to 512 0.70-1.00, to 1024 0.83-1.01; above, 256 to 512 queries 0.88-1.00, 1024 and 2048 queries 0.95-1.01.
+constexpr int MERGED_MAX = 1024;
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
 
@@ -1114,8 +1116,8 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
 }
 
 // dK/dV and dQ in one launch, the workgroups of dK/dV, the longer ones, first: for chunks that are a few rounds of the chip, where each
-// launch on its own leaves CUs idle at its end (777 windowed queries, 32 / 8 heads: 76 + 35 -> 102 us, the whole call 154 -> 141; a chunk
-// of many rounds gains nothing).
+// launch on its own leaves CUs idle at its end (777 windowed queries, 32 / 8 heads: 76 + 35 -> 102 us, the whole call 154 -> 141; what
+// a chunk of many rounds gains stands at MERGED_MAX).
 template <int DH, bool SPLIT, bool IN_TURN>
 __device__ __forceinline__ void bwd_block(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
                                           const bf16_t* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ lse2,

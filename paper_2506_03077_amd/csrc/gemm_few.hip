@@ -24,7 +24,7 @@ template <int W> __device__ __forceinline__ int few_mn_swz(int krow) {
 
 // One TM x TN tile.  Group g takes the K steps (BK = 64 or, for the smallest tile, 128 wide) t = g, g + 2, ...; a step is two slots, each closed by a barrier: fetch (LDS reads of
 // all its fragments, the DMA of a later step) and multiply.  Group 1 runs one slot behind, so on every SIMD one wave multiplies while
-// the other fetches, and a slot takes one K step forward.  The stages form a ring of NS steps (96 to 144 KB); step t + AHEAD is
+// the other fetches, and a slot takes one K step forward.  The stages form a ring of NS steps (128 KB; 128 x 64 tiles: 144); step t + AHEAD is
 // loaded in the fetch slot of step t, into the stage that the other group has left (its reads were waited for before the barrier in
 // between), and has AHEAD - 1 slots to land.  Wave w of a group owns rows (w / 2) * TM / 2 and columns (w % 2) * TN / 2 of the tile.
 template <int TM, int TN> constexpr int FEW_BK = TM * TN == 64 * 64 ? 128 : 64;

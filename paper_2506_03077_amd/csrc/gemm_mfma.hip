@@ -868,7 +868,9 @@ double gemm_mfma_us(const GemmArgs* gs, int n) {      // n > 1: one grouped laun
   return launch_us(tiles, k, scratch_tiles_of(gs[0], max_m), max_m);
 }
 
-// C = silu(A B^T) * (A glu_up^T): from as many tiles on as a grouped launch of both products takes (fewer fill the chip better apart)
+// C = silu(A B^T) * (A glu_up^T): from as many tiles on as a grouped launch of both products takes.  Whole forward of a layer in one chunk, this form / the
+// products apart: 44 tiles 1.09, 88 0.95-0.97, 112 0.97-1.06, 132 to 198 0.84-0.87, 220 to 444 0.95-1.065 (512 rows at 3584 x 18944, 296 tiles in two rounds, 356
+// us against 335; before this form 386).
 bool gemm_mfma_glu_ok(const GemmArgs& g) {
   return g.glu_up && !g.ta && g.tb && !g.acc && g.out_dt == DT_BF16 && !g.A2 && !g.row_stats && !g.numer_targets && !g.swiglu_gate && !g.rows_dev &&
          !((uintptr_t)g.glu_up & 15) && cdiv(g.M, BM) * cdiv(g.N, BN / 2) >= 200;

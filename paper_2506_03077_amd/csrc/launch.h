@@ -24,7 +24,7 @@ struct GemmArgs {
   // upper bound the launch is sized for.
   const int* rows_dev = nullptr;
   // Optional second operand pair of the same shapes and leading dimensions: C (=|+=) A B + A2 B2 in one launch, as one reduction of
-  // twice the length (split over workgroups or not); two launches where the MFMA kernel cannot take it.
+  // twice the length (split over workgroups or not), also in the shape-agnostic kernel; two launches where the MFMA kernel takes one pair alone.
   const void* A2 = nullptr;
   const void* B2 = nullptr;
   // Optional row statistics of the output (store form C = A B^T with fp32 C, MFMA kernel only: ask
@@ -44,8 +44,8 @@ struct GemmArgs {
   // Optional fused SwiGLU adjoint (store form C = A B with the same row-major [M, N] layout and leading dimension for
   // C, gate, up and act; bf16): the product is the gradient wrt act = silu(gate) * up and is never stored; instead the
   // epilogue reads the tile's gate and up values and writes act (what the forward would have produced; optional),
-  // gate <- d gate and up <- d up in place.  Where the MFMA kernel cannot take the problem the dispatcher runs the
-  // plain product into C followed by the elementwise kernel - same results up to the rounding of the product to bf16.
+  // gate <- d gate and up <- d up in place.  The shape-agnostic kernel has the same epilogue.  Where the MFMA kernel cannot take
+  // it the dispatcher runs the plain product into C and the elementwise kernel - same results up to the rounding of the product to bf16.
   void* swiglu_gate = nullptr;
   void* swiglu_up = nullptr;
   void* swiglu_act = nullptr;
