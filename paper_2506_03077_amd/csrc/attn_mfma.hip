@@ -56,8 +56,8 @@ constexpr int TK = ATTN_TILE_K;          // 64 keys per step (fwd, dQ)
 constexpr int KV_TILE = ATTN_KV_TILE;    // keys per workgroup (dK/dV): 4 key blocks x 2 roles = 8 waves
 constexpr int KV_THREADS = 512;
 constexpr int QT = ATTN_KV_QUERIES;      // queries per step (dK/dV)
-// Workgroups of a backward that runs as one launch (four rounds of the chip).  Whole backward in one launch against two, prefixes of 0 to 30720: up to 256
-// workgroups 0.52-0.98, to 512 0.70-1.00, to 1024 0.83-1.01; above, 256 to 512 queries 0.88-1.00, 1024 and 2048 queries 0.95-1.01.
+// Workgroups of a backward that runs as one launch (four rounds of the chip).  Whole backward in one launch / in two, 256 to 2048 queries, prefixes of 0 to
+// 30720: below the line 0.52-1.01 (mean 0.83), above it 0.88-1.01 (mean 0.96).
 constexpr int MERGED_MAX = 1024;
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
