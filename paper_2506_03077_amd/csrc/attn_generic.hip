@@ -184,11 +184,11 @@ struct AgShape { int Hq, Hkv, dh, q_start, c; float scale; int window, kv_first;
 __device__ __forceinline__ int first_key(const AgShape& a, int pos) { return max(a.kv_first, a.window > 0 ? pos - a.window + 1 : 0); }
 
 // What a wave is: a slot takes every SLOTS-th block, its waves a share of the head each
-#define AG_WAVE_SETUP                                                                                            \
+#define AG_WAVE_SETUP(N)                                                                                          \
   using Pt = Parts<DB, P, W>;                                                                                    \
   constexpr int SLOTS = Pt::SLOTS;                                                                               \
   constexpr bool FIRST = P == 1;                                                                                 \
-  __shared__ __attribute__((aligned(16))) float part[Pt::FLOATS];                                                \
+  __shared__ __attribute__((aligned(16))) float part[N * Pt::FLOATS];                                            \
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), slot = wave / P, share = wave % P, d0 = share * DB; \
   const int li = threadIdx.x & 15, lg4 = (threadIdx.x & 63) >> 4 << 2
 // (P == 1: a wave's own number of rounds; else all waves run the same, for the barrier in each)
@@ -198,7 +198,7 @@ __device__ __forceinline__ int first_key(const AgShape& a, int pos) { return max
 template <typename T, int DB, int P, int W>
 __global__ __launch_bounds__(W * 64) void attn_fwd_generic_k(T* q, const T* __restrict__ k, const T* __restrict__ v, T* __restrict__ o,
                                                                  float* __restrict__ lse, AgShape a, const float2* __restrict__ rope) {
-  AG_WAVE_SETUP;
+  AG_WAVE_SETUP(1);
   __shared__ f32x4 sX[EXCHANGE<P, 1, W>];
   __shared__ float sM[SLOTS][16], sL[SLOTS][16], sF[SLOTS][16], sT[16];
   const int h = blockIdx.y, t0 = blockIdx.x * 16, kvh = h / (a.Hq / a.Hkv);
@@ -340,7 +340,7 @@ __global__ __launch_bounds__(W * 64) void attn_dq_generic_k(const T* __restrict_
                                                                 const T* __restrict__ o, const T* __restrict__ d_o, const float* __restrict__ lse,
                                                                 float* __restrict__ delta, T* __restrict__ dq, AgShape a,
                                                                 const float2* __restrict__ rope) {
-  AG_WAVE_SETUP;
+  AG_WAVE_SETUP(1);
   __shared__ f32x4 sX[EXCHANGE<P, 2, W>];
   __shared__ float sD[P][16];
   const int h = blockIdx.y, t0 = blockIdx.x * 16, kvh = h / (a.Hq / a.Hkv);
@@ -441,12 +441,13 @@ __global__ __launch_bounds__(W * 64) void attn_dq_generic_k(const T* __restrict_
 }
 
 // ---- dK/dV (and dkc, dvc of the chunk's own rows, final with this call): 16 keys of one KV head; the slots walk blocks of 16 queries that see some of them, for every query head of the group
+// (Launch bounds: fp32 heads of 65 to 128 elements need 129 registers otherwise, one more than lets two workgroups share a CU.)
 template <typename T, int DB, int P, int W>
-__global__ __launch_bounds__(W * 64) void attn_dkv_generic_k(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
-                                                                 const T* __restrict__ d_o, const float* __restrict__ lse,
-                                                                 const float* __restrict__ delta, float* __restrict__ dk, float* __restrict__ dv,
-                                                                 AgShape a, T* __restrict__ dkc, T* __restrict__ dvc, const float2* __restrict__ rope) {
-  AG_WAVE_SETUP;
+__global__ __launch_bounds__(W * 64, DB * P == 8 ? 4 : 1) void attn_dkv_generic_k(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
+                                                                                  const T* __restrict__ d_o, const float* __restrict__ lse,
+                                                                                  const float* __restrict__ delta, float* __restrict__ dk, float* __restrict__ dv,
+                                                                                  AgShape a, T* __restrict__ dkc, T* __restrict__ dvc, const float2* __restrict__ rope) {
+  AG_WAVE_SETUP(2);
   __shared__ f32x4 sX[EXCHANGE<P, 2, W>];
   const int kvh = blockIdx.y, u0 = blockIdx.x * 16, G = a.Hq / a.Hkv;
   const int n_total = a.q_start + a.c, u = min(u0 + li, n_total - 1);          // my key
@@ -490,6 +491,19 @@ __global__ __launch_bounds__(W * 64) void attn_dkv_generic_k(const T* __restrict
     vf[d] = row_piece<T, DB>(Raw<T>::value(raw_v[d]), FIRST, d0, d, lg4, a.dh);
     ak[d] = av[d] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
+  // Two slots instead of eight (P > 1): what four blocks gave goes to LDS, so that the sums stay as close to fp64 as eight shorter ones (bf16, 300 queries, heads of
+  // 130: 4.5e-7 -> 3.5e-7; eight slots 3.9e-7).  Kept in registers the totals cost heads of 65 to 128 elements 20 to 50 %.
+  bool left = false;
+  auto leave = [&]() {
+#pragma unroll
+    for (int d = 0; d < DB; ++d) {
+      f32x4 *pk = (f32x4*)(part + slot * Pt::SLOT + li * Pt::ROW + (d0 + d) * 16 + lg4), *pv = (f32x4*)((float*)pk + Pt::FLOATS);
+      *pk = left ? *pk + ak[d] : ak[d];
+      *pv = left ? *pv + av[d] : av[d];
+      ak[d] = av[d] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    left = true;
+  };
   const int rounds = AG_ROUNDS(n_it);
   for (int n = 0; n < rounds; ++n, it += SLOTS) {
     const int t0 = query_of(it), h = head_of(it), next = it + SLOTS;
@@ -524,40 +538,43 @@ __global__ __launch_bounds__(W * 64) void attn_dkv_generic_k(const T* __restrict
     second_product<T, DB>(av, d0, dt, s, edge, seen, a.dh, at_row(d_o));
     second_product<T, DB>(ak, d0, qt, dp, edge, seen, a.dh, at_row(q));
     if (next < n_it) load_cols(next);
+    if (P > 1 && (n & 3) == 3) leave();
   }
   const int half = (a.dh + 1) / 2;
-  auto leave = [&](const f32x4 (&acc)[DB], float* __restrict__ out, T* __restrict__ fin, bool rotate) {
-    float old_x[Pt::PAIRS], old_y[Pt::PAIRS], x[Pt::PAIRS], y[Pt::PAIRS];
-    auto at = [&](const typename Pt::Pair& p) { return out + ((int64_t)(u0 + p.row) * a.Hkv + kvh) * a.dh + p.e; };
+  float old[2][2][Pt::PAIRS];                  // of dk and dv
+  auto at = [&](float* __restrict__ out, const typename Pt::Pair& p) { return out + ((int64_t)(u0 + p.row) * a.Hkv + kvh) * a.dh + p.e; };
+#pragma unroll
+  for (int which = 0; which < 2; ++which)
 #pragma unroll
     for (int n = 0; n < Pt::PAIRS; ++n) {
       const auto p = Pt::pair(n, half);
       const bool in = p.in && u0 + p.row < n_total;
-      old_x[n] = in ? at(p)[0] : 0.f;
-      old_y[n] = in && p.e + half < a.dh ? at(p)[half] : 0.f;
+      float* x = at(which ? dv : dk, p);
+      old[which][0][n] = in ? x[0] : 0.f;
+      old[which][1][n] = in && p.e + half < a.dh ? x[half] : 0.f;
     }
-    Pt::leave(part, slot, d0, acc, li, lg4);
-    __syncthreads();
-    Pt::sums(part, half, x, y, [](int, int) { return 1.f; });
+  leave();
+  __syncthreads();
+  auto finish = [&](int which, float* __restrict__ out, T* __restrict__ fin) {
+    float x[Pt::PAIRS], y[Pt::PAIRS];
+    Pt::sums(part + which * Pt::FLOATS, half, x, y, [](int, int) { return 1.f; });
 #pragma unroll
     for (int n = 0; n < Pt::PAIRS; ++n) {
       const auto p = Pt::pair(n, half);
       if (!p.in || u0 + p.row >= n_total) continue;
-      const bool two = p.e + half < a.dh;
-      const float r = old_x[n] + x[n], w = old_y[n] + y[n];
-      at(p)[0] = r;
-      if (two) at(p)[half] = w;
+      const float r = old[which][0][n] + x[n], w = old[which][1][n] + y[n];
+      at(out, p)[0] = r;
+      if (p.e + half < a.dh) at(out, p)[half] = w;
       const int t = u0 + p.row - a.q_start;
       if (!fin || t < 0) continue;             // (an even head size: what the rotary embedding pairs)
-      const float2 cs = rotate ? rope[(int64_t)t * half + p.e] : make_float2(1.f, 0.f);
+      const float2 cs = which == 0 ? rope[(int64_t)t * half + p.e] : make_float2(1.f, 0.f);
       T* f = fin + ((int64_t)t * a.Hkv + kvh) * a.dh + p.e;
-      stf(f, rotate ? r * cs.x + w * cs.y : r);                 // rotation by the negative angle
-      stf(f + half, rotate ? w * cs.x - r * cs.y : w);
+      stf(f, which == 0 ? r * cs.x + w * cs.y : r);             // rotation by the negative angle
+      stf(f + half, which == 0 ? w * cs.x - r * cs.y : w);
     }
-    __syncthreads();
   };
-  leave(ak, dk, dkc, true);
-  leave(av, dv, dvc, false);
+  finish(0, dk, dkc);
+  finish(1, dv, dvc);
 }
 
 static AgShape shape_of(const AttnArgs& a) { return AgShape{a.Hq, a.Hkv, a.dh, a.q_start, a.q_len, a.scale, a.window, a.kv_first}; }
