@@ -61,6 +61,12 @@ int streambp_debug_gemm_dw_segments(int n, int M, int N, const int *K, const voi
 int streambp_debug_gemm_few(int n, int M, int N, const int *K, int tb, int out_dt, const void *const *A, const void *const *B,
                             void *C, long long ldc, int tile_m, int tile_n, void *hip_stream);
 
+/* The same kernels over n <= 8 problems of their own sizes and outputs in one launch: C[i] (row stride ldc[i]) = A[i] B[i] [+ A2[i] B2[i]], operands
+ * dense as above and A2 / B2 (or single entries of A2) NULL where there is no second pair.  Returns as above. */
+int streambp_debug_gemm_few_problems(int n, const int *M, const int *N, const int *K, int tb, int out_dt, const void *const *A, const void *const *B,
+                                     const void *const *A2, const void *const *B2, void *const *C, const long long *ldc, int tile_m, int tile_n,
+                                     void *hip_stream);
+
 /* Per-launch timing with HIP events recorded on the launch stream around each GEMM kernel / attention launch sequence.
  * begin: CREATES 2*max_records events, allocates host records and switches recording on (returns 0; -1 if already on).
  * end: synchronises the events, fills the caller's host arrays of streambp_debug_profile_kinds() entries (launch count,

@@ -146,6 +146,9 @@ def lib():
         L.streambp_debug_gemm_few.restype = C.c_int
         L.streambp_debug_gemm_few.argtypes = [C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int), C.c_int, C.c_int, C.POINTER(vp), C.POINTER(vp),
                                               vp, C.c_longlong, C.c_int, C.c_int, vp]
+        L.streambp_debug_gemm_few_problems.restype = C.c_int
+        L.streambp_debug_gemm_few_problems.argtypes = [C.c_int] + [C.POINTER(C.c_int)] * 3 + [C.c_int, C.c_int] + [C.POINTER(vp)] * 5 + \
+            [C.POINTER(C.c_longlong), C.c_int, C.c_int, vp]
         L.streambp_debug_profile_begin.restype = C.c_int
         L.streambp_debug_profile_begin.argtypes = [C.c_int]
         L.streambp_debug_profile_end.restype = C.c_int
@@ -486,6 +489,19 @@ def debug_gemm_few(As, Bs, C_out, tb, tile, stream=None):
                                        (C.c_void_p * n)(*[_ptr(b) for b in Bs]), C_out.data_ptr(), C_out.stride(0), tile[0], tile[1], _stream(stream))
     if rc < 0:
         raise StreamBPError(rc, "debug_gemm_few launch failed")
+    return rc
+
+
+def debug_gemm_few_problems(As, Bs, Cs, tb, tile, A2s=None, B2s=None, stream=None):
+    """Cs[i] = As[i] op(Bs[i]) [+ A2s[i] op(B2s[i])], problems of their own sizes in one launch of the same kernels; 1, or 0 if they do not take it."""
+    n = len(As)
+    ints = lambda xs: (C.c_int * n)(*xs)
+    ptrs = lambda ts: (C.c_void_p * n)(*[_ptr(t) for t in ts]) if ts else None
+    rc = lib().streambp_debug_gemm_few_problems(n, ints(c.shape[0] for c in Cs), ints(c.shape[1] for c in Cs), ints(a.shape[1] for a in As), int(tb),
+                                                _dt_code(Cs[0]), ptrs(As), ptrs(Bs), ptrs(A2s), ptrs(B2s), (C.c_void_p * n)(*[c.data_ptr() for c in Cs]),
+                                                (C.c_longlong * n)(*[c.stride(0) for c in Cs]), tile[0], tile[1], _stream(stream))
+    if rc < 0:
+        raise StreamBPError(rc, "debug_gemm_few_problems launch failed")
     return rc
 
 

@@ -226,6 +226,19 @@ extern "C" int streambp_debug_gemm_few(int n, int M, int N, const int* K, int tb
   return e == hipSuccess ? 1 : e == hipErrorInvalidValue ? 0 : -5;
 }
 
+extern "C" int streambp_debug_gemm_few_problems(int n, const int* M, const int* N, const int* K, int tb, int out_dt, const void* const* A,
+                                                const void* const* B, const void* const* A2, const void* const* B2, void* const* C,
+                                                const long long* ldc, int tile_m, int tile_n, void* stream) {
+  if (n < 1 || n > 8) return -2;
+  sbp::GemmArgs gs[8];
+  for (int i = 0; i < n; ++i) {
+    gs[i] = sbp::GemmArgs{A[i], B[i], C[i], M[i], N[i], K[i], K[i], tb ? K[i] : N[i], ldc[i], false, tb != 0, sbp::DT_BF16, out_dt, false};
+    if (A2 && A2[i]) { gs[i].A2 = A2[i]; gs[i].B2 = B2[i]; }
+  }
+  const hipError_t e = sbp::gemm_few(gs, n, false, tile_m, tile_n, (hipStream_t)stream);
+  return e == hipSuccess ? 1 : e == hipErrorInvalidValue ? 0 : -5;
+}
+
 // Weight-gradient form over several reduction segments through gemm_batch: C[M,N] += sum_s A_s^T B_s with
 // A_s [K_s, M], B_s [K_s, N] (row counts optionally limited by device integers), C fp32 or bf16 (out_dt).  Returns 1 if
 // the segmented MFMA kernel took it, 0 if it ran as separate launches.
