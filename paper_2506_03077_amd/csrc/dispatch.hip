@@ -17,7 +17,7 @@ bool gemm_mfma_stats_ok(const GemmArgs& g);
 bool gemm_mfma_swiglu_ok(const GemmArgs& g);
 bool gemm_mfma_numer_ok(const GemmArgs& g);
 bool gemm_mfma_glu_ok(const GemmArgs& g);
-bool gemm_mfma_group_eligible(const GemmArgs* gs, int n, bool small_ok);
+bool gemm_mfma_group_eligible(const GemmArgs* gs, int n, bool small_ok, double separate_us);
 hipError_t gemm_mfma_group(const GemmArgs* gs, int n, hipStream_t st);
 bool gemm_mfma_seg_eligible(const GemmArgs* gs, int n);
 hipError_t gemm_mfma_seg(const GemmArgs* gs, int n, hipStream_t st);
@@ -143,16 +143,17 @@ hipError_t gemm(const GemmArgs& g, hipStream_t st) {
 }
 hipError_t gemm_batch(const GemmArgs* gs, int n, hipStream_t st, bool group_small) {
   if (!g_force_generic_gemm && gemm_mfma_seg_eligible(gs, n)) return gemm_mfma_seg(gs, n, st);   // same C: one pass over it
-  const bool group = !g_force_generic_gemm && gemm_mfma_group_eligible(gs, n, group_small);
+  bool group = false;
   if (!g_force_generic_gemm) {
-    const FewChoice few = gemm_few_choice(gs, n, false);
-    if (few.tm) {
-      double us = 0.0;
-      if (group) us = gemm_mfma_us(gs, n);
-      else
-        for (int i = 0; i < n; ++i) us += std::min(gemm_few_choice(gs + i, 1, false).us, gemm_mfma_us(gs + i, 1));      // (all can take the first form)
-      if (few_is_faster(few, us)) return run_few(gs, n, false, few, st);
+    double separate = 0.0;      // each in the better form of its own
+    for (int i = 0; i < n; ++i) {
+      const double us = gemm_mfma_us(gs + i, 1);
+      const FewChoice one = gemm_few_choice(gs + i, 1, false);
+      separate += one.tm ? std::min(one.us, us) : us;
     }
+    group = gemm_mfma_group_eligible(gs, n, group_small, separate);
+    const FewChoice few = gemm_few_choice(gs, n, false);
+    if (few_is_faster(few, group ? gemm_mfma_us(gs, n) : separate)) return run_few(gs, n, false, few, st);
   }
   if (group) return gemm_mfma_group(gs, n, st);
   if (n > 1 && all_generic(gs, n)) {

@@ -945,7 +945,8 @@ static int group_fold(const GemmArgs* gs, int n, int* owner /* [n]: index of the
   return n_out;
 }
 constexpr int MAX_BATCH = MAX_GROUP * MAX_GSEG;
-bool gemm_mfma_group_eligible(const GemmArgs* gs, int n, bool small_ok) {
+// separate_us: estimated time of the problems on their own
+bool gemm_mfma_group_eligible(const GemmArgs* gs, int n, bool small_ok, double separate_us) {
   if (n < 2 || n > MAX_BATCH) return false;
   int64_t tiles = 0;
   int owner[MAX_BATCH], nseg[MAX_BATCH] = {0};
@@ -957,10 +958,12 @@ bool gemm_mfma_group_eligible(const GemmArgs* gs, int n, bool small_ok) {
     if (++nseg[owner[i]] > MAX_GSEG) return false;
     if (owner[i] == i) tiles += cdiv(gs[i].M, BM) * cdiv(gs[i].N, BN);
   }
-  // few tiles: per-problem launches, each split over the chip, fill it better - unless problems share an output, where one
-  // launch with several reduction segments replaces several passes over it
-  // (small_ok: many skinny problems, none of which could fill the chip alone either)
-  return (tiles >= 200 || n_out < n || small_ok) && tiles < (1 << 30);
+  if (tiles >= (1 << 30)) return false;
+  // Few tiles: launches of their own, each split over the chip, may fill it better - where the reductions are long enough to make up for a launch and a
+  // sum of partial tiles each, which the estimates say.  The seven weight gradients of a 1024-wide layer, 172 tiles: 2046 rows 244 us apart, 86 in
+  // one launch, 660 rows 208 and 48.  Problems that share an output are one pass over it in one launch, and several
+  // passes apart.  (small_ok: many skinny problems, none of which could fill the chip alone either)
+  return tiles >= 200 || n_out < n || small_ok || gemm_mfma_us(gs, n) < separate_us;
 }
 
 hipError_t gemm_mfma_group(const GemmArgs* gs, int n, hipStream_t st) {
