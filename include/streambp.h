@@ -123,12 +123,16 @@ typedef struct {
  *   S = min(256, 27 * ceil(c / 256) * ceil(max(d, n_q_heads * head_dim) / 256))
  *       * min(c, 256) KiB,   c = min(chunk, T) (LM head: min(chunk, B * T)):
  * at most 64 MiB, reached by chunks of a few hundred rows, and shrinking with
- * the chunk below 256 rows. */
+ * the chunk below 256 rows.
+ * Chunk and dw_group_rows set the bytes; how the rows are dealt inside them is
+ * the library's: a pass may take more rows than a chunk, or several short
+ * sequences of the batch at once, where that is faster (Eq. 1 holds for any
+ * partition; every result stays within the rounding of its types). */
 size_t streambp_layer_workspace_bytes(const sbp_layer_cfg *cfg);
 
 /* StreamBP of one layer (Sec. 3.2.2): K and V are computed once for the whole
- * sequence and cached in the workspace; then for every chunk of rows the
- * chunk's forward is recomputed against the prefix K/V only and its backward
+ * sequence and cached in the workspace; then for every partition of the rows
+ * its forward is recomputed against the prefix K/V only and its backward
  * is run, with dW += per-chunk term (Eq. 1), dK/dV of the prefix accumulated in
  * fp32 in the workspace and dx rows written as soon as they are final.
  *   x  [B, T, d] in  : layer input (the gradient checkpoint)

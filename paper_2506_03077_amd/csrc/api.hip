@@ -4,6 +4,7 @@
 #include "../../include/streambp.h"
 #include "launch.h"
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -92,25 +93,31 @@ int dw_group_for(size_t chunk_rows, int32_t cfg_rows, int default_rows) {   // c
 }
 
 // ------------------------------------------------------------- layer ------
+// A pass of the chunk loop works on `rows` rows of a sequence, or on `seqs` whole sequences (then rows = seq_len), the rows of which are one
+// behind the other; `sets` passes share a weight-gradient launch.
+struct LayerPlan { int seqs, rows, sets; };
 struct LayerWs {
-  void *K, *V;                 // [T, Hkv*dh] dt   cached for the whole sequence
-  float *dK, *dV;              // [T, Hkv*dh] fp32 prefix accumulators
+  void *K, *V;                 // [seqs, T, Hkv*dh] dt   cached for the whole sequence(s)
+  float *dK, *dV;              // [seqs, T, Hkv*dh] fp32 prefix accumulators
   Cleared kv_grads;            // both
   float2* rope;                // [T, dh/2] cos/sin
-  void *a, *q, *o, *m, *gate, *up, *act, *dact, *dh1_t, *d_o, *dq, *dkc, *dvc;   // per chunk, dt
-  float *h1, *dm, *dh1, *da, *proj;                                       // per chunk, fp32 [c, d]
+  // Rows of a pass, dt.  a, o, m, gate, up, act, dh1_t, dq, dkc and dvc are the operands of its weight-gradient GEMMs; act holds dact before
+  // the SwiGLU adjoint replaces it.
+  void *q, *d_o;
+  void *a, *o, *m, *gate, *up, *act, *dh1_t, *dq, *dkc, *dvc;
+  // fp32 [rows, d].  f0: output projection, then h1 (the sum of the attention side, in place), at the end da; f1: dm, then dh1 (in place); the
+  // plain forward's down projection
+  float *f0, *f1;
   float *rstd1, *rstd2, *lse, *delta;
-  float* partial[MAX_DW_GROUP][2];      // rows that the norm gains' gradients are the column sums of, per chunk of a weight-gradient group: g1, g2
+  float* partial[MAX_DW_GROUP][2];      // rows that the norm gains' gradients are the column sums of, per pass of a weight-gradient group: g1, g2
   float* gemm_scratch; size_t gemm_scratch_bytes;
-  // Further copies of the operands of the chunk's weight-gradient GEMMs (a, o, m, gate, up, act, dh1_t, dq, dkc, dvc):
-  // the weight gradients of dw_group consecutive chunks are added in one launch, so a chunk's operands stay alive
-  // while the next chunks are processed.
-  int dw_group;
+  // Further copies of the operands of the weight-gradient GEMMs: a pass's operands stay alive while the next passes of its group run.
+  LayerPlan plan;
   void* alt[MAX_DW_GROUP - 1][10];
   size_t bytes;
 };
-// The workspace view a chunk uses: set 0 = the primary operand buffers, sets 1.. the further copies.
-LayerWs chunk_view(const LayerWs& s, int set) {
+// The workspace view a pass uses: set 0 = the primary operand buffers, sets 1.. the further copies.
+LayerWs pass_view(const LayerWs& s, int set) {
   LayerWs v = s;
   if (set > 0) {
     void** ptrs[10] = {&v.a, &v.o, &v.m, &v.gate, &v.up, &v.act, &v.dh1_t, &v.dq, &v.dkc, &v.dvc};
@@ -139,54 +146,143 @@ int32_t check_layer_cfg(const sbp_layer_cfg* c) {
   return SBP_OK;
 }
 
-LayerWs carve_layer(const sbp_layer_cfg* c, void* ws) {
+// The workspace a layer call asks for: K, V and their gradients, and what a chunk of `chunk` rows at a time needs with every intermediate in a buffer
+// of its own and a copy of the ten operand buffers per chunk of a weight-gradient group.  The passes are planned inside these bytes (plan_layer).
+size_t layer_budget(const sbp_layer_cfg* c) {
   const size_t es = dtype_size(c->dtype);
   const size_t T = c->seq_len, cm = (size_t)std::min(c->chunk, c->seq_len);
   const size_t d = c->hidden, F = c->mlp_width, qd = (size_t)c->n_q_heads * c->head_dim, kd = (size_t)c->n_kv_heads * c->head_dim;
+  Carver cv(nullptr);
+  for (int i = 0; i < 2; ++i) cv.take_bytes(T * kd * es);
+  cv.take_bytes(2 * align_up(T * kd * sizeof(float), 256));
+  cv.take<float2>(T * (c->head_dim / 2));
+  const size_t operands[10] = {cm * d * es, cm * qd * es, cm * d * es, cm * F * es, cm * F * es, cm * F * es, cm * d * es, cm * qd * es, cm * kd * es, cm * kd * es};
+  const int sets = dw_group_for(cm, c->dw_group_rows, DW_GROUP_ROWS_LAYER);
+  for (int g = 0; g < sets; ++g) {
+    for (int i = 0; i < 2; ++i) cv.take<float>(rmsnorm_bwd_partial_floats((int)cm, (int)d));
+    for (size_t bytes : operands) cv.take_bytes(bytes);
+  }
+  for (size_t bytes : {cm * qd * es, cm * F * es, cm * qd * es}) cv.take_bytes(bytes);      // q, dact, do
+  for (int i = 0; i < 5; ++i) cv.take<float>(cm * d);                                        // h1, dm, dh1, da, the output projection
+  for (int i = 0; i < 2; ++i) cv.take<float>(cm);
+  cv.take<float>(cm * c->n_q_heads);
+  cv.take<float>(2 * cm * c->n_q_heads);
+  cv.take_bytes(c->dtype == SBP_BF16 ? gemm_scratch_bytes((int)cm, (int)std::max(d, qd)) : 0);
+  return cv.off;
+}
+
+// backward = false: the plain forward, which keeps no operands and no gradients
+LayerWs carve_layer(const sbp_layer_cfg* c, void* ws, const LayerPlan& plan, bool backward) {
+  const size_t es = dtype_size(c->dtype);
+  const size_t T = (size_t)c->seq_len * plan.seqs, n = (size_t)plan.rows * plan.seqs;
+  const size_t d = c->hidden, F = c->mlp_width, qd = (size_t)c->n_q_heads * c->head_dim, kd = (size_t)c->n_kv_heads * c->head_dim;
   Carver cv(ws);
-  LayerWs w;
+  LayerWs w{};
+  w.plan = plan;
   w.K = cv.take_bytes(T * kd * es);
   w.V = cv.take_bytes(T * kd * es);
-  ClearedCarver grads(cv);
-  w.dK = grads.take(T * kd);
-  w.dV = grads.take(T * kd);
-  w.kv_grads = grads.close();
-  w.rope = cv.take<float2>(T * (c->head_dim / 2));
-  w.a = cv.take_bytes(cm * d * es);
-  w.q = cv.take_bytes(cm * qd * es);
-  w.o = cv.take_bytes(cm * qd * es);
-  w.m = cv.take_bytes(cm * d * es);
-  w.gate = cv.take_bytes(cm * F * es);
-  w.up = cv.take_bytes(cm * F * es);
-  w.act = cv.take_bytes(cm * F * es);
-  w.dact = cv.take_bytes(cm * F * es);
-  w.dh1_t = cv.take_bytes(cm * d * es);
-  w.d_o = cv.take_bytes(cm * qd * es);
-  w.dq = cv.take_bytes(cm * qd * es);
-  w.dkc = cv.take_bytes(cm * kd * es);
-  w.dvc = cv.take_bytes(cm * kd * es);
-  w.h1 = cv.take<float>(cm * d);
-  w.dm = cv.take<float>(cm * d);
-  w.dh1 = cv.take<float>(cm * d);
-  w.da = cv.take<float>(cm * d);
-  w.proj = cv.take<float>(cm * d);
-  w.rstd1 = cv.take<float>(cm);
-  w.rstd2 = cv.take<float>(cm);
-  w.lse = cv.take<float>(cm * c->n_q_heads);
-  w.delta = cv.take<float>(2 * cm * c->n_q_heads);
-  w.gemm_scratch_bytes = c->dtype == SBP_BF16 ? gemm_scratch_bytes((int)cm, (int)std::max(d, qd)) : 0;
+  w.rope = cv.take<float2>((size_t)c->seq_len * (c->head_dim / 2));
+  w.q = cv.take_bytes(n * qd * es);
+  w.a = cv.take_bytes(n * d * es);
+  w.o = cv.take_bytes(n * qd * es);
+  w.m = cv.take_bytes(n * d * es);
+  w.gate = cv.take_bytes(n * F * es);
+  w.up = cv.take_bytes(n * F * es);
+  w.act = cv.take_bytes(n * F * es);
+  w.f0 = cv.take<float>(n * d);
+  w.f1 = cv.take<float>(n * d);
+  w.rstd1 = cv.take<float>(n);
+  w.rstd2 = cv.take<float>(n);
+  w.lse = cv.take<float>(n * c->n_q_heads);
+  // (a chunk's worth: products of more rows have less to split)
+  w.gemm_scratch_bytes = c->dtype == SBP_BF16 ? gemm_scratch_bytes((int)std::min(n, (size_t)std::min(c->chunk, c->seq_len)), (int)std::max(d, qd)) : 0;
   w.gemm_scratch = (float*)cv.take_bytes(w.gemm_scratch_bytes);
-  {
-    const size_t sizes[10] = {cm * d * es, cm * qd * es, cm * d * es, cm * F * es, cm * F * es, cm * F * es,
-                              cm * d * es, cm * qd * es, cm * kd * es, cm * kd * es};   // a, o, m, gate, up, act, dh1_t, dq, dkc, dvc
-    w.dw_group = dw_group_for(cm, c->dw_group_rows, DW_GROUP_ROWS_LAYER);
-    for (int g = 0; g < w.dw_group; ++g)
-      for (float*& p : w.partial[g]) p = cv.take<float>(rmsnorm_bwd_partial_floats((int)cm, (int)d));
-    for (int g = 1; g < w.dw_group; ++g)
+  if (backward) {
+    ClearedCarver grads(cv);
+    w.dK = grads.take(T * kd);
+    w.dV = grads.take(T * kd);
+    w.kv_grads = grads.close();
+    w.d_o = cv.take_bytes(n * qd * es);
+    w.dh1_t = cv.take_bytes(n * d * es);
+    w.dq = cv.take_bytes(n * qd * es);
+    w.dkc = cv.take_bytes(n * kd * es);
+    w.dvc = cv.take_bytes(n * kd * es);
+    w.delta = cv.take<float>(2 * n * c->n_q_heads);
+    const size_t sizes[10] = {n * d * es, n * qd * es, n * d * es, n * F * es, n * F * es, n * F * es,
+                              n * d * es, n * qd * es, n * kd * es, n * kd * es};   // a, o, m, gate, up, act, dh1_t, dq, dkc, dvc
+    for (int g = 0; g < plan.sets; ++g)
+      for (float*& p : w.partial[g]) p = cv.take<float>(rmsnorm_bwd_partial_floats((int)n, (int)d));
+    for (int g = 1; g < plan.sets; ++g)
       for (int i = 0; i < 10; ++i) w.alt[g - 1][i] = cv.take_bytes(sizes[i]);
   }
   w.bytes = cv.off;
   return w;
+}
+
+// How the rows of a call are dealt to passes.  The paper's partition bounds the memory; inside those bytes fewer and larger passes are faster: every
+// pass streams all weights and is some twenty dependent launches.  fits(plan): the plan's buffers are within the call's workspace.
+//
+// Candidates: for every number of sets, whole sequences, as many as fit, or, where not even one does, the longest stretch of a sequence; both evened
+// out, and with up to two passes more, which may waste less of the last row of tiles.  Taken is the one with the least estimated time: a pass costs
+// its launches, two readings of the weights and the products of its rows, rounded up to tiles; a weight-gradient launch a reading and a
+// writing of the gradients.  `products`: multiples of 2 flops per weight and row.
+//
+// Measured, chunk by chunk as the config says / in planned passes of the same bytes: four sequences of 640 tokens at 7B widths, chunk 512, eight passes / one
+// 5.47 -> 3.63 ms; 8192 tokens at 4096 / 14336, chunk 1024, eight / two 11.92 -> 10.98; 32768 at 7B widths, chunk 2048, sixteen / eight 70.9 -> 69.9; a
+// 1024-wide stack of two layers, 2 x 1023 tokens, chunk 512, 3.27 -> 2.65.  SPAN_ROWS: 8192 rows a pass are slower again (8192 tokens at
+// 4096 / 14336 11.85 ms, 32768 at 7B widths 71.7): the MLP's tensors, 230 to 310 MB each, no longer stay in the 256 MB cache from one product to the next.
+constexpr int SPAN_ROWS = 4096;
+constexpr int SPAN_SEQS = 32;
+template <typename Fits>
+LayerPlan plan_layer(const sbp_layer_cfg* c, int max_sets, double products, bool dw, Fits fits) {
+  const int T = c->seq_len, cm = std::min(c->chunk, T), rows_max = std::max(cm, SPAN_ROWS), grain = c->dtype == SBP_BF16 ? 256 : 32;
+  const double d = c->hidden, qd = (double)c->n_q_heads * c->head_dim, kd = (double)c->n_kv_heads * c->head_dim;
+  const double weights = 2.0 * d * qd + 2.0 * d * kd + 3.0 * d * c->mlp_width;
+  const double row_us = 2.0 * products * weights / (c->dtype == SBP_BF16 ? 1.3e9 : 7e7);
+  const double pass_us = 60.0 + weights * 2.0 * dtype_size(c->dtype) / 5e6, dw_us = dw ? weights * 2.0 * dtype_size(c->grad_dtype) / 5e6 : 0.0;
+  auto largest = [&](int hi, auto ok) {      // largest n <= hi with ok(n), or 0
+    int lo = 0;
+    while (lo < hi) {
+      const int mid = lo + (hi - lo + 1) / 2;
+      if (ok(mid)) lo = mid; else hi = mid - 1;
+    }
+    return lo;
+  };
+  LayerPlan best{1, cm, 1};
+  double best_us = -1.0;
+  for (int sets = 1; sets <= max_sets; ++sets) {
+    const int seqs = T > rows_max ? 0 : largest(std::min(std::min(c->batch, SPAN_SEQS), rows_max / T), [&](int n) { return fits(LayerPlan{n, T, sets}); });
+    const int rows = seqs > 0 ? T : largest(std::min(T, rows_max), [&](int n) { return fits(LayerPlan{1, n, sets}); });
+    if (rows < 1) break;                                 // (more sets need more)
+    const int64_t least = seqs > 0 ? cdiv(c->batch, seqs) : cdiv(T, rows);
+    for (int64_t parts = least; parts <= least + 2; ++parts) {
+      LayerPlan p{1, rows, sets};
+      int64_t passes, tiles;                             // tiles: rows of all passes, in units of `grain`
+      if (seqs > 0) {
+        p.seqs = (int)cdiv(c->batch, parts);
+        passes = cdiv(c->batch, p.seqs);
+        tiles = (passes - 1) * cdiv((int64_t)p.seqs * T, grain) + cdiv((c->batch - (passes - 1) * p.seqs) * T, grain);
+      } else {
+        const int even = (int)cdiv(T, parts), up = (int)align_up((size_t)even, (size_t)grain);
+        p.rows = up <= rows ? up : even;
+        passes = cdiv(T, p.rows);
+        tiles = ((passes - 1) * cdiv(p.rows, grain) + cdiv(T - (passes - 1) * p.rows, grain)) * c->batch;
+        passes *= c->batch;
+      }
+      if (sets > 1 && sets > passes) continue;
+      const double us = (double)passes * pass_us + (double)(tiles * grain) * row_us + (double)cdiv(passes, sets) * dw_us;
+      if (best_us < 0.0 || us < best_us) { best = p; best_us = us; }
+    }
+  }
+  return best;
+}
+LayerPlan plan_backward(const sbp_layer_cfg* c) {
+  const size_t budget = layer_budget(c);
+  return plan_layer(c, MAX_DW_GROUP, 3.0, true, [&](const LayerPlan& p) { return carve_layer(c, nullptr, p, true).bytes <= budget; });
+}
+LayerPlan plan_forward(const sbp_layer_cfg* c) {
+  const size_t budget = layer_budget(c);
+  return plan_layer(c, 1, 1.0, false, [&](const LayerPlan& p) { return carve_layer(c, nullptr, p, false).bytes <= budget; });
 }
 
 // split-K scratch of the entry point currently running on this host thread
@@ -224,22 +320,24 @@ int32_t check_layer_ptrs(const sbp_layer_weights* w) {
   return SBP_OK;
 }
 
-// K and V of the whole sequence, once (cached for all chunks of the layer).  The pass runs in row blocks as large as
-// the chunk buffers that are idle at this point allow (gate, up, act, dact are contiguous: 4 c F elements hold the
-// normalised rows of 4 c F / d positions), so that the two projections are GEMMs with enough output tiles to fill
-// the chip on their own; nothing proportional to T is added to the workspace.
-// held: gate, up and act still hold operands of weight-gradient GEMMs that wait for their launch; dact alone is idle then.
-int32_t kv_prepass(const sbp_layer_cfg* c, const sbp_layer_weights* w, const LayerWs& s, const char* xb, bool held, hipStream_t st) {
+// The rows of one pass: n rows from r0 on of sequence b0, or (r0 = 0, n = T) the sequences b0 .. b0 + seqs - 1
+struct Pass { int b0, seqs, r0, n; bool whole; };      // whole: all rows of its sequences
+int64_t pass_rows(const Pass& p) { return (int64_t)p.seqs * p.n; }
+
+// K and V of the pass's sequences, once (cached for all passes over them).  Where a pass takes whole sequences it does so itself, from
+// the rows normalised for q (chunk_reforward).  Else row blocks as large as the operand buffers that the coming pass will fill allow (gate, up,
+// act are contiguous: 3 n F elements hold the normalised rows of 3 n F / d positions), so that the two projections are GEMMs with enough output
+// tiles to fill the chip on their own; nothing proportional to T is added to the workspace.
+int32_t kv_prepass(const sbp_layer_cfg* c, const sbp_layer_weights* w, const LayerWs& s, const char* xb, hipStream_t st) {
   const int dt = c->dtype;
   const size_t es = dtype_size(dt);
-  const int T = c->seq_len, cm = std::min(c->chunk, T), d = c->hidden;
+  const int T = c->seq_len, d = c->hidden;
   const int kd = c->n_kv_heads * c->head_dim;
   void* a_rows = s.a;
-  int block = cm;
-  void* idle = held ? s.dact : s.gate;
-  const size_t idle_rows = (size_t)((const char*)s.dact + (size_t)cm * c->mlp_width * es - (const char*)idle) / ((size_t)d * es);
-  if (held || idle_rows > (size_t)cm) {
-    a_rows = idle;
+  int block = s.plan.rows;
+  const size_t idle_rows = (size_t)((const char*)s.act + (size_t)s.plan.rows * c->mlp_width * es - (const char*)s.gate) / ((size_t)d * es);
+  if (idle_rows > (size_t)block) {
+    a_rows = s.gate;
     block = (int)std::min<size_t>((size_t)T, idle_rows);
   }
   for (int r0 = 0; r0 < T; r0 += block) {
@@ -248,31 +346,42 @@ int32_t kv_prepass(const sbp_layer_cfg* c, const sbp_layer_weights* w, const Lay
     const GemmArgs kv[2] = {fwd_gemm(a_rows, w->wk, at(s.K, r0, kd, es), n, kd, d, dt, dt),
                             fwd_gemm(a_rows, w->wv, at(s.V, r0, kd, es), n, kd, d, dt, dt)};
     HIPCHK(gemm_batch(kv, 2, st));
-    HIPCHK(rope_apply(dt, at(s.K, r0, kd, es), s.rope + (size_t)r0 * (c->head_dim / 2), n, c->n_kv_heads, c->head_dim, false, st));
+    HIPCHK(rope_apply(dt, at(s.K, r0, kd, es), s.rope + (size_t)r0 * (c->head_dim / 2), n, n, c->n_kv_heads, c->head_dim, false, st));
   }
   return SBP_OK;
 }
 
-// Partitioned reforward of rows [r0, r0+n): fills a, q, o, lse, h1, m, gate, up (with_act = false: the backward, which gets act from swiglu_bwd).
+// The attention call of a pass; backward adds its own tensors
+AttnArgs pass_attn(const sbp_layer_cfg* c, const LayerWs& s, const Pass& p) {
+  AttnArgs aa{};
+  aa.dt = c->dtype; aa.Hq = c->n_q_heads; aa.Hkv = c->n_kv_heads; aa.dh = c->head_dim;
+  aa.batch = p.seqs; aa.q_start = p.r0; aa.q_len = p.n; aa.scale = 1.0f / std::sqrt((float)c->head_dim);
+  aa.window = c->window; aa.kv_first = c->seq_first ? c->seq_first[p.b0] : 0;      // rows before it are padding in front of the sequence
+  aa.kv_firsts = c->seq_first && p.seqs > 1 ? c->seq_first + p.b0 : nullptr;
+  aa.q = s.q; aa.k = s.K; aa.v = s.V; aa.o = s.o; aa.lse = s.lse;
+  if (fusion_mask() & FUSE_ROPE_Q) aa.rope_q = s.rope + (size_t)p.r0 * (c->head_dim / 2);
+  return aa;
+}
+
+// Partitioned reforward of a pass's rows: fills a, q, o, lse, f0 = h1, m, gate, up (with_act = false: the backward, which gets act from swiglu_bwd), and
+// K and V where the pass takes whole sequences.
 // with_act = true (the plain forward): fills act, and gate and up only where the gated store does not take the products.
-int32_t chunk_reforward(const sbp_layer_cfg* c, const sbp_layer_weights* w, const LayerWs& s, const char* xb,
-                        int r0, int n, int kv_first, bool with_act, hipStream_t st) {
+int32_t chunk_reforward(const sbp_layer_cfg* c, const sbp_layer_weights* w, const LayerWs& s, const char* xc, const Pass& p, bool with_act, hipStream_t st) {
   const int dt = c->dtype;
-  const size_t es = dtype_size(dt);
-  const int d = c->hidden, F = c->mlp_width, qd = c->n_q_heads * c->head_dim;
-  const char* xc = at(xb, r0, d, es);
+  const int d = c->hidden, F = c->mlp_width, qd = c->n_q_heads * c->head_dim, kd = c->n_kv_heads * c->head_dim;
+  const int n = (int)pass_rows(p);
   HIPCHK(rmsnorm_fwd(dt, xc, nullptr, w->g1, s.a, nullptr, s.rstd1, n, d, c->rms_eps, st));
   HIPCHK(gemm(fwd_gemm(s.a, w->wq, s.q, n, qd, d, dt, dt), st));
-  AttnArgs aa{};
-  aa.dt = dt; aa.Hq = c->n_q_heads; aa.Hkv = c->n_kv_heads; aa.dh = c->head_dim;
-  aa.q_start = r0; aa.q_len = n; aa.scale = 1.0f / std::sqrt((float)c->head_dim);
-  aa.window = c->window; aa.kv_first = kv_first;
-  aa.q = s.q; aa.k = s.K; aa.v = s.V; aa.o = s.o; aa.lse = s.lse;
-  if (fusion_mask() & FUSE_ROPE_Q) aa.rope_q = s.rope + (size_t)r0 * (c->head_dim / 2);   // RoPE(q) inside the attention kernel, which leaves s.q rotated
-  else HIPCHK(rope_apply(dt, s.q, s.rope + (size_t)r0 * (c->head_dim / 2), n, c->n_q_heads, c->head_dim, false, st));
+  if (p.whole) {
+    const GemmArgs kv[2] = {fwd_gemm(s.a, w->wk, s.K, n, kd, d, dt, dt), fwd_gemm(s.a, w->wv, s.V, n, kd, d, dt, dt)};
+    HIPCHK(gemm_batch(kv, 2, st));
+    HIPCHK(rope_apply(dt, s.K, s.rope, n, p.n, c->n_kv_heads, c->head_dim, false, st));
+  }
+  const AttnArgs aa = pass_attn(c, s, p);      // with RoPE(q) inside the kernel, which leaves s.q rotated
+  if (!aa.rope_q) HIPCHK(rope_apply(dt, s.q, s.rope + (size_t)p.r0 * (c->head_dim / 2), n, p.n, c->n_q_heads, c->head_dim, false, st));
   HIPCHK(attn_forward(aa, st));
-  HIPCHK(gemm(fwd_gemm(s.o, w->wo, s.proj, n, d, qd, dt, DT_F32), st));
-  HIPCHK(rmsnorm_fwd(dt, xc, s.proj, w->g2, s.m, s.h1, s.rstd2, n, d, c->rms_eps, st));
+  HIPCHK(gemm(fwd_gemm(s.o, w->wo, s.f0, n, d, qd, dt, DT_F32), st));
+  HIPCHK(rmsnorm_fwd(dt, xc, s.f0, w->g2, s.m, s.f0, s.rstd2, n, d, c->rms_eps, st));
   if (with_act) {      // the forward needs neither gate nor up: one product of both whose store applies the gate
     GemmArgs ga = fwd_gemm(s.m, w->wgate, s.act, n, F, d, dt, dt);
     ga.glu_up = w->wup;
@@ -298,7 +407,7 @@ const char* streambp_last_error(void) { return g_err; }
 
 size_t streambp_layer_workspace_bytes(const sbp_layer_cfg* cfg) {
   if (check_layer_cfg(cfg) != SBP_OK) return 0;
-  return carve_layer(cfg, nullptr).bytes;
+  return layer_budget(cfg);
 }
 
 // Low-rank adapter mode of the layer backward (App. D, experiment setup: rank-32 adapters, adapter gradients only).
@@ -326,71 +435,62 @@ int32_t layer_backward_impl(const sbp_layer_cfg* c, const sbp_layer_weights* w, 
   t_gemm_scratch = s_all.gemm_scratch; t_gemm_scratch_bytes = s_all.gemm_scratch_bytes;
   const int dt = c->dtype, gdt = c->grad_dtype;
   const size_t es = dtype_size(dt);
-  const int T = c->seq_len, cm = std::min(c->chunk, T), d = c->hidden, F = c->mlp_width;
+  const int T = c->seq_len, d = c->hidden, F = c->mlp_width;
   const int qd = c->n_q_heads * c->head_dim, kd = c->n_kv_heads * c->head_dim, half = c->head_dim / 2;
+  const LayerPlan plan = s_all.plan;
   HIPCHK(rope_table(s_all.rope, T, c->head_dim, c->rope_theta, c->pos_offset, st));
-  // Weight-gradient GEMMs waiting for their launch (a group of chunks' worth).  A group may span sequences: short samples would
-  // otherwise read and write every dW once each (four samples of 640 tokens at 7B widths: 2.3 of 8.8 ms).  The K/V pass of the next
-  // sequence then has only dact to work in; where that holds less than a chunk of rows the group ends with the sequence.
-  const bool across = (size_t)cm * F / d >= (size_t)cm;
+  // Weight-gradient GEMMs waiting for their launch (a group of passes' worth).  A group may span sequences: short samples would
+  // otherwise read and write every dW once each (four samples of 640 tokens at 7B widths: 2.3 of 8.8 ms).
   GemmArgs dws[7 * MAX_DW_GROUP];
   int n_dws = 0;
-  ColumnSums gains{};          // of the same chunks (adapter mode: the gains are frozen)
+  ColumnSums gains{};          // of the same passes (adapter mode: the gains are frozen)
   if (!lora) { gains.dg[0] = g->g1; gains.dg[1] = g->g2; }
-  for (int b = 0; b < c->batch; ++b) {
-    const char* xb = at(x, (size_t)b * T, d, es);
-    const char* dyb = at(dy, (size_t)b * T, d, es);
-    char* dxb = at(dx, (size_t)b * T, d, es);
-    const int kv_first = c->seq_first ? c->seq_first[b] : 0;      // rows before it are padding in front of the sequence
-    if ((rc = kv_prepass(c, w, s_all, xb, n_dws > 0, st))) return rc;
+  for (int b0 = 0; b0 < c->batch; b0 += plan.seqs) {
+    const int n_chunks = (int)cdiv(T, plan.rows), seqs = std::min(plan.seqs, c->batch - b0);
+    if (n_chunks > 1 && (rc = kv_prepass(c, w, pass_view(s_all, n_dws / 7), at(x, (size_t)b0 * T, d, es), st))) return rc;
     HIPCHK(fill_zero(s_all.kv_grads.p, s_all.kv_grads.bytes, st));
     // Chunks run last to first: rows of dK/dV belonging to chunk i are final once
     // chunks >= i are done (later queries are the only other readers of those
     // keys), so the K/V-side gradient and dx of the chunk can be finished at once.
-    const int n_chunks = (int)cdiv(T, cm);
     for (int ci = n_chunks - 1; ci >= 0; --ci) {
-      const int r0 = ci * cm, n = std::min(cm, T - r0);
-      const int set = n_dws / 7;
-      const LayerWs s = chunk_view(s_all, set);
+      const Pass p{b0, seqs, ci * plan.rows, std::min(plan.rows, T - ci * plan.rows), n_chunks == 1};
+      const int n = (int)pass_rows(p), set = n_dws / 7;
+      const LayerWs s = pass_view(s_all, set);
+      const size_t row0 = (size_t)b0 * T + p.r0;
+      const char *xc = at(x, row0, d, es), *dyc = at(dy, row0, d, es);
       float *partial1 = lora ? nullptr : s_all.partial[set][0], *partial2 = lora ? nullptr : s_all.partial[set][1];
-      if ((rc = chunk_reforward(c, w, s, xb, r0, n, kv_first, false, st))) return rc;
-      const char* dyc = at(dyb, r0, d, es);
+      if ((rc = chunk_reforward(c, w, s, xc, p, false, st))) return rc;
       // ---- MLP backward (the weight-gradient GEMMs of the chunk are deferred to one grouped launch below)
-      {   // dact = dy W_d, then the SwiGLU adjoint: gate <- dgate, up <- dup, act <- silu(gate) up.  The adjoint can run as
+      {   // dact = dy W_d (in act), then the SwiGLU adjoint: gate <- dgate, up <- dup, act <- silu(gate) up.  The adjoint can run as
           // the GEMM's epilogue (dact is then never stored); measured slower than the elementwise pass, so off by default.
-        GemmArgs gd = dx_gemm(dyc, w->wdown, s.dact, n, d, F, dt, dt, false);
+        GemmArgs gd = dx_gemm(dyc, w->wdown, s.act, n, d, F, dt, dt, false);
         if ((fusion_mask() & FUSE_SWIGLU) || !gemm_uses_mfma(gd)) {      // (the shape-agnostic kernel's launches are what it costs)
           gd.swiglu_gate = s.gate; gd.swiglu_up = s.up; gd.swiglu_act = s.act;
           HIPCHK(gemm(gd, st));
         } else {
           HIPCHK(gemm(gd, st));
-          HIPCHK(swiglu_bwd(dt, s.gate, s.up, s.dact, s.act, (int64_t)n * F, st));
+          HIPCHK(swiglu_bwd(dt, s.gate, s.up, s.act, s.act, (int64_t)n * F, st));
         }
       }
       {   // dm = dgate W_g + dup W_u: two operand pairs, one launch
-        GemmArgs gm = dx_gemm(s.gate, w->wgate, s.dm, n, F, d, dt, DT_F32, false);
+        GemmArgs gm = dx_gemm(s.gate, w->wgate, s.f1, n, F, d, dt, DT_F32, false);
         gm.A2 = s.up; gm.B2 = w->wup;
         HIPCHK(gemm(gm, st));
       }
-      HIPCHK(rmsnorm_bwd(dt, s.dm, s.h1, true, w->g2, s.rstd2, dyc, false, s.dh1, s.dh1_t, partial2, n, d, st));
+      HIPCHK(rmsnorm_bwd(dt, s.f1, s.f0, true, w->g2, s.rstd2, dyc, false, s.f1, s.dh1_t, partial2, n, d, st));      // f1: dm -> dh1
       // ---- attention-side backward
       HIPCHK(gemm(dx_gemm(s.dh1_t, w->wo, s.d_o, n, d, qd, dt, dt, false), st));
-      AttnArgs aa{};
-      aa.dt = dt; aa.Hq = c->n_q_heads; aa.Hkv = c->n_kv_heads; aa.dh = c->head_dim;
-      aa.q_start = r0; aa.q_len = n; aa.scale = 1.0f / std::sqrt((float)c->head_dim);
-      aa.window = c->window; aa.kv_first = kv_first;
-      aa.q = s.q; aa.k = s.K; aa.v = s.V; aa.o = s.o; aa.lse = s.lse;
+      AttnArgs aa = pass_attn(c, s, p);            // (with rope_q dq leaves the kernel rotated back, RoPE's adjoint)
       aa.d_o = s.d_o; aa.dq = s.dq; aa.dk = s.dK; aa.dv = s.dV; aa.delta = s.delta;
       if (dt == DT_BF16) aa.dkv_slices = attn_dkv_slices(aa, s.gemm_scratch_bytes);
       if (aa.dkv_slices > 1) aa.dkv_scratch = s.gemm_scratch;                                   // (idle between GEMMs)
-      if (fusion_mask() & FUSE_ROPE_Q) aa.rope_q = s.rope + (size_t)r0 * half;   // dq leaves the kernel rotated back (RoPE's adjoint)
-      // K/V side of rows [r0, r0+n): final now
-      aa.dkc = s.dkc; aa.dvc = s.dvc; aa.rope_k = s.rope + (size_t)r0 * half;
+      // K/V side of the pass's rows: final now
+      aa.dkc = s.dkc; aa.dvc = s.dvc; aa.rope_k = s.rope + (size_t)p.r0 * half;
       HIPCHK(attn_backward(aa, st));
-      if (!(fusion_mask() & FUSE_ROPE_Q)) HIPCHK(rope_apply(dt, s.dq, s.rope + (size_t)r0 * half, n, c->n_q_heads, c->head_dim, true, st));
+      if (!aa.rope_q) HIPCHK(rope_apply(dt, s.dq, s.rope + (size_t)p.r0 * half, n, p.n, c->n_q_heads, c->head_dim, true, st));
       {   // da = dq W_q + dkc W_k + dvc W_v
-        const GemmArgs qkv[3] = {dx_gemm(s.dq, w->wq, s.da, n, qd, d, dt, DT_F32, false), dx_gemm(s.dkc, w->wk, s.da, n, kd, d, dt, DT_F32, true),
-                                 dx_gemm(s.dvc, w->wv, s.da, n, kd, d, dt, DT_F32, true)};
+        const GemmArgs qkv[3] = {dx_gemm(s.dq, w->wq, s.f0, n, qd, d, dt, DT_F32, false), dx_gemm(s.dkc, w->wk, s.f0, n, kd, d, dt, DT_F32, true),
+                                 dx_gemm(s.dvc, w->wv, s.f0, n, kd, d, dt, DT_F32, true)};
         HIPCHK(gemm_sum(qkv, 3, st));
       }
       if (!lora) {
@@ -401,7 +501,7 @@ int32_t layer_backward_impl(const sbp_layer_cfg* c, const sbp_layer_weights* w, 
                                   dw_gemm(s.dq, s.a, g->wq, n, qd, d, dt, gdt),    dw_gemm(s.dkc, s.a, g->wk, n, kd, d, dt, gdt),
                                   dw_gemm(s.dvc, s.a, g->wv, n, kd, d, dt, gdt)};
         for (int i = 0; i < 7; ++i) dws[n_dws++] = mine[i];
-        if (n_dws == 7 * s_all.dw_group || (ci == 0 && (b + 1 == c->batch || !across))) {
+        if (n_dws == 7 * plan.sets || (ci == 0 && b0 + seqs == c->batch)) {
           HIPCHK(gemm_batch(dws, n_dws, st));
           n_dws = 0;
         }
@@ -440,8 +540,7 @@ int32_t layer_backward_impl(const sbp_layer_cfg* c, const sbp_layer_weights* w, 
           HIPCHK(gemm_batch(ga, lora->n, st, true));
         }
       }
-      HIPCHK(rmsnorm_bwd(dt, s.da, at(xb, r0, d, es), false, w->g1, s.rstd1, s.dh1, true, nullptr, at(dxb, r0, d, es),
-                         partial1, n, d, st));
+      HIPCHK(rmsnorm_bwd(dt, s.f0, xc, false, w->g1, s.rstd1, s.f1, true, nullptr, at(dx, row0, d, es), partial1, n, d, st));
       if (!lora) {
         gains.partial[0][set] = partial1; gains.partial[1][set] = partial2;
         gains.blocks[set] = rmsnorm_bwd_partial_rows(n);
@@ -472,8 +571,9 @@ int32_t streambp_layer_backward(const sbp_layer_cfg* c, const sbp_layer_weights*
   }
   if (dx == x || dx == dy) return fail(SBP_ERR_SHAPE, "dx may not alias x or dy");
   if ((uintptr_t)workspace & 255) return fail(SBP_ERR_WORKSPACE, "workspace must be 256-byte aligned");
-  const LayerWs s_all = carve_layer(c, workspace);
-  if (workspace_bytes < s_all.bytes) return fail(SBP_ERR_WORKSPACE, "workspace too small: %zu < %zu", workspace_bytes, s_all.bytes);
+  const size_t need = layer_budget(c);
+  if (workspace_bytes < need) return fail(SBP_ERR_WORKSPACE, "workspace too small: %zu < %zu", workspace_bytes, need);
+  const LayerWs s_all = carve_layer(c, workspace, plan_backward(c), true);
   return layer_backward_impl(c, w, x, dy, dx, g, nullptr, s_all, (hipStream_t)hip_stream);
 }
 
@@ -492,12 +592,11 @@ int32_t check_lora(const sbp_layer_cfg* c, const sbp_lora_adapters* ad) {
   if (n == 0) return fail(SBP_ERR_NULL, "no matrix is adapted");
   return SBP_OK;
 }
-struct LoraWs { LoraCtx ctx; sbp_layer_weights w_eff; void* bt[7]; sbp_layer_cfg layer_cfg; void* layer_ws; size_t layer_bytes; size_t bytes; };
-LoraWs carve_lora(const sbp_layer_cfg* c, const sbp_layer_weights* w, const sbp_lora_adapters* ad, void* ws) {
+struct LoraWs { LoraCtx ctx; sbp_layer_weights w_eff; void* bt[7]; sbp_layer_cfg layer_cfg; void* layer_ws; size_t bytes; };      // bytes: up to layer_ws
+LoraWs carve_lora(const sbp_layer_cfg* c, const sbp_layer_weights* w, const sbp_lora_adapters* ad, void* ws, size_t rows) {
   const size_t es = dtype_size(c->dtype);
   const int d = c->hidden, F = c->mlp_width, qd = c->n_q_heads * c->head_dim, kd = c->n_kv_heads * c->head_dim;
   const int outs[7] = {qd, kd, kd, d, F, F, d}, ins[7] = {d, d, d, qd, d, d, F};
-  const size_t cm = (size_t)std::min(c->chunk, c->seq_len);
   Carver cv(ws);
   LoraWs L{};
   if (w) L.w_eff = *w;
@@ -514,8 +613,8 @@ LoraWs carve_lora(const sbp_layer_cfg* c, const sbp_layer_weights* w, const sbp_
     x.a_pad[j] = cv.take_bytes(rp * ins[i] * es);
     x.b_pad[j] = cv.take_bytes((size_t)outs[i] * rp * es);
     L.bt[j] = cv.take_bytes((size_t)ad->rank * outs[i] * es);                    // s B^T, the merge GEMM's operand
-    x.P[j] = cv.take_bytes(cm * rp * es);
-    x.Q[j] = cv.take_bytes(cm * rp * es);
+    x.P[j] = cv.take_bytes(rows * rp * es);
+    x.Q[j] = cv.take_bytes(rows * rp * es);
   }
   ClearedCarver grads(cv);
   for (int j = 0; j < x.n; ++j) {
@@ -526,15 +625,24 @@ LoraWs carve_lora(const sbp_layer_cfg* c, const sbp_layer_weights* w, const sbp_
   L.layer_cfg = *c;
   L.layer_cfg.dw_group_rows = 1;          // no weight-gradient passes to group: one set of chunk buffers
   L.layer_ws = cv.take_bytes(0);
-  L.layer_bytes = carve_layer(&L.layer_cfg, nullptr).bytes;
-  L.bytes = cv.off + L.layer_bytes;
+  L.bytes = cv.off;
   return L;
+}
+size_t lora_budget(const sbp_layer_cfg* c, const sbp_lora_adapters* ad) {
+  const LoraWs L = carve_lora(c, nullptr, ad, nullptr, (size_t)std::min(c->chunk, c->seq_len));
+  return L.bytes + layer_budget(&L.layer_cfg);
+}
+LayerPlan plan_lora(const sbp_layer_cfg* c, const sbp_lora_adapters* ad) {
+  const size_t budget = lora_budget(c, ad);
+  return plan_layer(c, 1, 2.0, false, [&](const LayerPlan& p) {
+    return carve_lora(c, nullptr, ad, nullptr, (size_t)p.seqs * p.rows).bytes + carve_layer(c, nullptr, p, true).bytes <= budget;
+  });
 }
 }  // namespace
 
 size_t streambp_layer_lora_workspace_bytes(const sbp_layer_cfg* cfg, const sbp_lora_adapters* ad) {
   if (check_layer_cfg(cfg) != SBP_OK || check_lora(cfg, ad) != SBP_OK) return 0;
-  return carve_lora(cfg, nullptr, ad, nullptr).bytes;
+  return lora_budget(cfg, ad);
 }
 
 int32_t streambp_layer_lora_backward(const sbp_layer_cfg* c, const sbp_layer_weights* w, const sbp_lora_adapters* ad,
@@ -549,8 +657,10 @@ int32_t streambp_layer_lora_backward(const sbp_layer_cfg* c, const sbp_layer_wei
     if (ad->a[i] && (!g->da[i] || !g->db[i])) return fail(SBP_ERR_NULL, "adapter %d: da and db must be non-NULL", i);
   if (dx == x || dx == dy) return fail(SBP_ERR_SHAPE, "dx may not alias x or dy");
   if ((uintptr_t)workspace & 255) return fail(SBP_ERR_WORKSPACE, "workspace must be 256-byte aligned");
-  const LoraWs L = carve_lora(c, w, ad, workspace);
-  if (workspace_bytes < L.bytes) return fail(SBP_ERR_WORKSPACE, "workspace too small: %zu < %zu", workspace_bytes, L.bytes);
+  const size_t need = lora_budget(c, ad);
+  if (workspace_bytes < need) return fail(SBP_ERR_WORKSPACE, "workspace too small: %zu < %zu", workspace_bytes, need);
+  const LayerPlan plan = plan_lora(c, ad);
+  const LoraWs L = carve_lora(c, w, ad, workspace, (size_t)plan.seqs * plan.rows);
   hipStream_t st = (hipStream_t)hip_stream;
   const int dt = c->dtype;
   const size_t es = dtype_size(dt);
@@ -573,7 +683,7 @@ int32_t streambp_layer_lora_backward(const sbp_layer_cfg* c, const sbp_layer_wei
   HIPCHK(pad_matrices(dt, pads, st));
   HIPCHK(gemm_batch(merge, X.n, st));
   if (X.n > 0) HIPCHK(fill_zero(X.grads.p, X.grads.bytes, st));
-  const LayerWs s_all = carve_layer(&L.layer_cfg, L.layer_ws);
+  const LayerWs s_all = carve_layer(&L.layer_cfg, L.layer_ws, plan, true);
   if ((rc = layer_backward_impl(&L.layer_cfg, &L.w_eff, x, dy, dx, nullptr, &X, s_all, st))) return rc;
   AddJobs adds{};
   for (int j = 0; j < X.n; ++j) {
@@ -592,24 +702,26 @@ int32_t streambp_layer_forward(const sbp_layer_cfg* c, const sbp_layer_weights* 
   if ((rc = check_layer_ptrs(w))) return rc;
   if (!x || !y || !workspace) return fail(SBP_ERR_NULL, "x, y and workspace must be non-NULL");
   if ((uintptr_t)workspace & 255) return fail(SBP_ERR_WORKSPACE, "workspace must be 256-byte aligned");
-  const LayerWs s = carve_layer(c, workspace);
-  if (workspace_bytes < s.bytes) return fail(SBP_ERR_WORKSPACE, "workspace too small: %zu < %zu", workspace_bytes, s.bytes);
+  const size_t need = layer_budget(c);
+  if (workspace_bytes < need) return fail(SBP_ERR_WORKSPACE, "workspace too small: %zu < %zu", workspace_bytes, need);
+  const LayerWs s = carve_layer(c, workspace, plan_forward(c), false);
   hipStream_t st = (hipStream_t)hip_stream;
   t_gemm_scratch = s.gemm_scratch; t_gemm_scratch_bytes = s.gemm_scratch_bytes;
   const int dt = c->dtype;
   const size_t es = dtype_size(dt);
-  const int T = c->seq_len, cm = std::min(c->chunk, T), d = c->hidden, F = c->mlp_width;
+  const int T = c->seq_len, d = c->hidden, F = c->mlp_width;
   HIPCHK(rope_table(s.rope, T, c->head_dim, c->rope_theta, c->pos_offset, st));
-  for (int b = 0; b < c->batch; ++b) {
-    const char* xb = at(x, (size_t)b * T, d, es);
-    char* yb = at(y, (size_t)b * T, d, es);
-    const int kv_first = c->seq_first ? c->seq_first[b] : 0;
-    if ((rc = kv_prepass(c, w, s, xb, false, st))) return rc;
-    for (int r0 = 0; r0 < T; r0 += cm) {
-      const int n = std::min(cm, T - r0);
-      if ((rc = chunk_reforward(c, w, s, xb, r0, n, kv_first, true, st))) return rc;
-      HIPCHK(gemm(fwd_gemm(s.act, w->wdown, s.proj, n, d, F, dt, DT_F32), st));
-      HIPCHK(add_store(dt, s.h1, s.proj, at(yb, r0, d, es), (int64_t)n * d, st));
+  for (int b0 = 0; b0 < c->batch; b0 += s.plan.seqs) {
+    const int seqs = std::min(s.plan.seqs, c->batch - b0);
+    const bool whole = s.plan.rows >= T;
+    if (!whole && (rc = kv_prepass(c, w, s, at(x, (size_t)b0 * T, d, es), st))) return rc;
+    for (int r0 = 0; r0 < T; r0 += s.plan.rows) {
+      const Pass p{b0, seqs, r0, std::min(s.plan.rows, T - r0), whole};
+      const int n = (int)pass_rows(p);
+      const size_t row0 = (size_t)b0 * T + r0;
+      if ((rc = chunk_reforward(c, w, s, at(x, row0, d, es), p, true, st))) return rc;
+      HIPCHK(gemm(fwd_gemm(s.act, w->wdown, s.f1, n, d, F, dt, DT_F32), st));
+      HIPCHK(add_store(dt, s.f0, s.f1, at(y, row0, d, es), (int64_t)n * d, st));
     }
   }
   return SBP_OK;

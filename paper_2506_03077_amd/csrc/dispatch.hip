@@ -179,13 +179,35 @@ hipError_t gemm_sum(const GemmArgs* gs, int n, hipStream_t st) {
   hipError_t e = gemm(gs[0], st);
   return e != hipSuccess || n == 1 ? e : gemm_batch(gs + 1, n - 1, st);
 }
+static AttnArgs attn_sequence(const AttnArgs& a, int b) {      // sequence b of the call
+  AttnArgs s = a;
+  const size_t qn = (size_t)b * a.q_len * a.Hq * a.dh, kn = (size_t)b * a.q_len * a.Hkv * a.dh, es = dtype_size(a.dt);
+  s.batch = 1; s.kv_firsts = nullptr;
+  if (a.kv_firsts) s.kv_first = a.kv_firsts[b];
+  s.q = (const char*)a.q + qn * es; s.k = (const char*)a.k + kn * es; s.v = (const char*)a.v + kn * es;
+  s.o = (char*)a.o + qn * es; s.lse = a.lse + (size_t)b * a.Hq * a.q_len;
+  if (a.d_o) {
+    s.d_o = (const char*)a.d_o + qn * es; s.dq = (char*)a.dq + qn * es; s.dk = a.dk + kn; s.dv = a.dv + kn;
+    s.delta = a.delta + (size_t)b * 2 * a.Hq * a.q_len;
+  }
+  if (a.dkc) { s.dkc = (char*)a.dkc + kn * es; s.dvc = (char*)a.dvc + kn * es; }
+  return s;
+}
+template <typename F>
+static hipError_t each_sequence(const AttnArgs& a, F f) {
+  for (int b = 0; b < a.batch; ++b)
+    if (hipError_t e = f(attn_sequence(a, b)); e != hipSuccess) return e;
+  return hipSuccess;
+}
 hipError_t attn_forward(const AttnArgs& a, hipStream_t st) {
+  if (a.batch > 1) return each_sequence(a, [&](const AttnArgs& s) { return attn_forward(s, st); });
   prof::Scope sc(prof::ATTN_FWD, 4.0 * a.dh * causal_pairs(a), false, st);
   if (attn_uses_mfma(a.dt, a.dh, a.Hq, a.Hkv) && attn_mfma_aligned(a, false)) return attn_forward_mfma(a, st);
   if (a.dt == DT_BF16) ++g_generic_bf16_launches;
   return attn_forward_generic(a, st);
 }
 hipError_t attn_backward(const AttnArgs& a, hipStream_t st) {
+  if (a.batch > 1) return each_sequence(a, [&](const AttnArgs& s) { return attn_backward(s, st); });
   prof::Scope sc(prof::ATTN_BWD, 10.0 * a.dh * causal_pairs(a), false, st);
   if (attn_uses_mfma(a.dt, a.dh, a.Hq, a.Hkv) && attn_mfma_aligned(a, true)) return attn_backward_mfma(a, st);
   if (a.dt == DT_BF16) ++g_generic_bf16_launches;

@@ -38,13 +38,13 @@ hipError_t rope_table(float2* tab, int n_pos, int dh, float theta, int pos_offse
 }
 
 template <typename T>
-__global__ void rope_apply_k(T* x, const float2* tab, int64_t n_pairs, int H, int half, int inverse) {
+__global__ void rope_apply_k(T* x, const float2* tab, int64_t n_pairs, int period, int H, int half, int inverse) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n_pairs) return;
   int j = (int)(i % half);
   int64_t rh = i / half;              // row * H + head
-  int64_t row = rh / H;
-  float2 cs = tab[row * half + j];
+  int row = (int)(rh / H) % period;
+  float2 cs = tab[(int64_t)row * half + j];
   float sn = inverse ? -cs.y : cs.y;
   T* p = x + rh * (2 * half);
   float a = ldf(p + j), b = ldf(p + j + half);
@@ -52,10 +52,10 @@ __global__ void rope_apply_k(T* x, const float2* tab, int64_t n_pairs, int H, in
   stf(p + j + half, b * cs.x + a * sn);
 }
 
-hipError_t rope_apply(int dt, void* x, const float2* tab, int rows, int H, int dh, bool inverse, hipStream_t st) {
+hipError_t rope_apply(int dt, void* x, const float2* tab, int rows, int period, int H, int dh, bool inverse, hipStream_t st) {
   int64_t n = (int64_t)rows * H * (dh / 2);
   if (n == 0) return hipSuccess;
-  DISPATCH_DT(dt, T, (rope_apply_k<T><<<(unsigned)cdiv(n, 256), 256, 0, st>>>((T*)x, tab, n, H, dh / 2, inverse ? 1 : 0)));
+  DISPATCH_DT(dt, T, (rope_apply_k<T><<<(unsigned)cdiv(n, 256), 256, 0, st>>>((T*)x, tab, n, period, H, dh / 2, inverse ? 1 : 0)));
   return hipGetLastError();
 }
 
@@ -109,9 +109,9 @@ __device__ __forceinline__ void load_row(const T* __restrict__ p, int d, int lan
     }                                                    \
   } while (0)
 template <int IT, typename T>
-__global__ __launch_bounds__(256) void rmsnorm_fwd_vec_k(const T* __restrict__ x, const float* __restrict__ add,
+__global__ __launch_bounds__(256) void rmsnorm_fwd_vec_k(const T* __restrict__ x, const float* add,
                                                          const T* __restrict__ g, T* __restrict__ out,
-                                                         float* __restrict__ sum_out, float* __restrict__ rstd,
+                                                         float* sum_out, float* __restrict__ rstd,
                                                          int rows, int d, float eps) {
   const int lane = threadIdx.x & 63;
   const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -149,9 +149,9 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_vec_k(const T* __restrict__ x
 
 // One workgroup per row.  r = 1/sqrt(mean(v^2) + eps) with v = x (+ add).
 template <typename T>
-__global__ __launch_bounds__(256) void rmsnorm_fwd_k(const T* __restrict__ x, const float* __restrict__ add,
+__global__ __launch_bounds__(256) void rmsnorm_fwd_k(const T* __restrict__ x, const float* add,
                                                      const T* __restrict__ g, T* __restrict__ out,
-                                                     float* __restrict__ sum_out, float* __restrict__ rstd,
+                                                     float* sum_out, float* __restrict__ rstd,
                                                      int d, float eps) {
   __shared__ float red[16];
   const int64_t row = blockIdx.x;
@@ -194,9 +194,9 @@ hipError_t rmsnorm_fwd(int dt, const void* x, const float* add, const void* g, v
 // 5120 78 -> 45 us, 8192 rows of 8192 469 -> 283, with the column sums on sixteen waves).
 constexpr int RB = 4;
 template <typename T, typename XT, typename RT, typename DN = float>
-__global__ __launch_bounds__(256) void rmsnorm_bwd_k(const DN* __restrict__ dnorm, const XT* __restrict__ xin,
+__global__ __launch_bounds__(256) void rmsnorm_bwd_k(const DN* dnorm, const XT* __restrict__ xin,
                                                      const T* __restrict__ g, const float* __restrict__ rstd,
-                                                     const RT* __restrict__ res, float* __restrict__ out_f32,
+                                                     const RT* __restrict__ res, float* out_f32,
                                                      T* __restrict__ out_t, float* __restrict__ partial,
                                                      int rows, int d) {
   __shared__ float red[16];
@@ -234,9 +234,9 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_k(const DN* __restrict__ dnor
 // order.  Same arithmetic and the same partial-sum layout as the plain kernel above.  (512 rows of 3584, with two rows per wave, a branch
 // per access and both passes reading memory: 22 us, now 9; 1024 rows of 4096 28 -> 15.)
 template <int IT, typename T, typename XT, typename RT, typename DN>
-__global__ __launch_bounds__(256) void rmsnorm_bwd_vec_k(const DN* __restrict__ dnorm, const XT* __restrict__ xin,
+__global__ __launch_bounds__(256) void rmsnorm_bwd_vec_k(const DN* dnorm, const XT* __restrict__ xin,
                                                          const T* __restrict__ g, const float* __restrict__ rstd,
-                                                         const RT* __restrict__ res, float* __restrict__ out_f32,
+                                                         const RT* __restrict__ res, float* out_f32,
                                                          T* __restrict__ out_t, float* __restrict__ partial,
                                                          int rows, int d) {
   static_assert(RB == 4, "one row per wave");
@@ -382,7 +382,7 @@ __global__ void swiglu_fwd_k(const T* __restrict__ gate, const T* __restrict__ u
   }
 }
 template <typename T>
-__global__ void swiglu_bwd_k(T* __restrict__ gate, T* __restrict__ up, const T* __restrict__ dact, T* __restrict__ act, int64_t n) {
+__global__ void swiglu_bwd_k(T* __restrict__ gate, T* __restrict__ up, const T* dact, T* act, int64_t n) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (; i < n; i += stride) {
@@ -408,7 +408,7 @@ __global__ void swiglu_fwd_bf16x8_k(const bf16x8* __restrict__ gate, const bf16x
 }
 template <bool WITH_ACT>
 __global__ void swiglu_bwd_bf16x8_k(bf16x8* __restrict__ gate, bf16x8* __restrict__ up,
-                                    const bf16x8* __restrict__ dact, bf16x8* __restrict__ act, int64_t n8) {
+                                    const bf16x8* dact, bf16x8* act, int64_t n8) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (; i < n8; i += stride) {

@@ -113,14 +113,14 @@ struct Scope {
 // ---- elementwise / row kernels (dt = storage type of the T-typed tensors) ----
 // cos/sin table [n_pos, dh/2] (float2), angles evaluated in fp64.
 hipError_t rope_table(float2* tab, int n_pos, int dh, float theta, int pos_offset, hipStream_t st);
-// in-place rotation of x [rows, H, dh]; tab points at the row of position 0 of these rows.
-hipError_t rope_apply(int dt, void* x, const float2* tab, int rows, int H, int dh, bool inverse, hipStream_t st);
-// out = g * (x + add) * rstd ; sum_out = x + add (fp32, optional) ; rstd per row
+// in-place rotation of x [rows, H, dh]; tab points at the row of position 0 of these rows, which starts again after `period` of them.
+hipError_t rope_apply(int dt, void* x, const float2* tab, int rows, int period, int H, int dh, bool inverse, hipStream_t st);
+// out = g * (x + add) * rstd ; sum_out = x + add (fp32, optional, may be add itself) ; rstd per row
 hipError_t rmsnorm_fwd(int dt, const void* x, const float* add, const void* g, void* out, float* sum_out,
                        float* rstd, int rows, int d, float eps, hipStream_t st);
 // adjoint: dnorm [rows,d] fp32 is the gradient wrt the normalised output.
 //   xin: the tensor that was normalised (x_is_f32 ? fp32 : dt);  res: gradient flowing around the norm
-//   (res_is_f32 ? fp32 : dt);  out_f32 / out_t (either may be NULL) = res + dx_norm;
+//   (res_is_f32 ? fp32 : dt);  out_f32 / out_t (either may be NULL) = res + dx_norm; out_f32 may be dnorm itself;
 //   partial (may be NULL; rmsnorm_bwd_partial_floats floats) = rows whose column sums are those of dnorm * xin * rstd: what dg grows by, through
 //   column_sums (two-stage, deterministic)
 hipError_t rmsnorm_bwd(int dt, const float* dnorm, const void* xin, bool x_is_f32, const void* g,
@@ -136,7 +136,7 @@ hipError_t rmsnorm_bwd_plain(int dt, const void* dy, const void* x, const void* 
                              float* dg, float* partial, int rows, int d, hipStream_t st);
 // recompute rstd only (used when the statistic was not kept): not needed by the layer path
 hipError_t swiglu_fwd(int dt, const void* gate, const void* up, void* act, int64_t n, hipStream_t st);
-// in place: gate <- dgate, up <- dup, given dact; act (optional) <- silu(gate) * up of the incoming values, the same
+// in place: gate <- dgate, up <- dup, given dact; act (optional, may be dact itself) <- silu(gate) * up of the incoming values, the same
 // numbers swiglu_fwd writes (for callers that need act only in the backward)
 hipError_t swiglu_bwd(int dt, void* gate, void* up, const void* dact, void* act, int64_t n, hipStream_t st);
 // y = T(a + b) with a, b fp32
@@ -169,6 +169,10 @@ struct AttnArgs {
   float scale;
   int window = 0;          // > 0: a query at position t sees only keys t - window < u <= t
   int kv_first = 0;        // key positions before this one are padding: never visible
+  // Several sequences in one call: `batch` of q_len queries and keys each, one behind the other (q_start = 0; lse [batch, Hq, c], delta [batch, 2, Hq, c]),
+  // kv_firsts their kv_first on the host (or NULL: kv_first for all).
+  int batch = 1;
+  const int32_t* kv_firsts = nullptr;
   const void *q, *k, *v;   // q [c,Hq,dh]; k,v [>=s+c,Hkv,dh]
   void* o; float* lse;     // o [c,Hq,dh]; lse [Hq,c]
   const void* d_o; void* dq; float *dk, *dv;

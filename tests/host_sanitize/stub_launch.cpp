@@ -78,8 +78,8 @@ void note_generic_bf16_launch() {}
 namespace prof { Scope::Scope(int, double, bool, hipStream_t s) : st(s) {} Scope::~Scope() {} }
 
 hipError_t rope_table(float2* tab, int n_pos, int dh, float, int, hipStream_t) { wr(tab, (size_t)n_pos * (dh / 2) * sizeof(float2)); return hipSuccess; }
-hipError_t rope_apply(int dt, void* x, const float2* tab, int rows, int H, int dh, bool, hipStream_t) {
-  wr(x, (size_t)rows * H * dh * es(dt)); rd(tab, (size_t)rows * (dh / 2) * sizeof(float2)); return hipSuccess;
+hipError_t rope_apply(int dt, void* x, const float2* tab, int rows, int period, int H, int dh, bool, hipStream_t) {
+  wr(x, (size_t)rows * H * dh * es(dt)); rd(tab, (size_t)std::min(rows, period) * (dh / 2) * sizeof(float2)); return hipSuccess;
 }
 size_t rmsnorm_bwd_partial_floats(int rows, int d) { return (size_t)cdiv(rows, 4) * (size_t)d; }
 hipError_t rmsnorm_fwd(int dt, const void* x, const float* add, const void* g, void* out, float* sum_out, float* rstd, int rows, int d, float, hipStream_t) {
@@ -149,15 +149,15 @@ hipError_t embedding_bwd(int dt, const int32_t* ids, const void* dx, float* demb
 }
 
 static void touch_attn(const AttnArgs& a, bool bwd) {
-  const size_t qn = (size_t)a.q_len * a.Hq * a.dh, kn = (size_t)(a.q_start + a.q_len) * a.Hkv * a.dh;
+  const size_t nb = a.batch, qn = nb * a.q_len * a.Hq * a.dh, kn = nb * (a.q_start + a.q_len) * a.Hkv * a.dh;
   if (a.rope_q && !bwd) wr((void*)a.q, qn * es(a.dt)); else rd(a.q, qn * es(a.dt));
   rd(a.k, kn * es(a.dt)); rd(a.v, kn * es(a.dt));
   if (a.rope_q) rd(a.rope_q, (size_t)a.q_len * (a.dh / 2) * sizeof(float2));
-  if (!bwd) { wr(a.o, qn * es(a.dt)); wr(a.lse, (size_t)a.Hq * a.q_len * 4); return; }
-  rd(a.o, qn * es(a.dt)); rd(a.lse, (size_t)a.Hq * a.q_len * 4); rd(a.d_o, qn * es(a.dt)); wr(a.dq, qn * es(a.dt));
-  wr(a.dk, kn * 4); wr(a.dv, kn * 4); wr(a.delta, (size_t)2 * a.Hq * a.q_len * 4);
+  if (!bwd) { wr(a.o, qn * es(a.dt)); wr(a.lse, nb * a.Hq * a.q_len * 4); return; }
+  rd(a.o, qn * es(a.dt)); rd(a.lse, nb * a.Hq * a.q_len * 4); rd(a.d_o, qn * es(a.dt)); wr(a.dq, qn * es(a.dt));
+  wr(a.dk, kn * 4); wr(a.dv, kn * 4); wr(a.delta, nb * 2 * a.Hq * a.q_len * 4);
   if (a.dkc) {
-    const size_t cn = (size_t)a.q_len * a.Hkv * a.dh * es(a.dt);
+    const size_t cn = nb * a.q_len * a.Hkv * a.dh * es(a.dt);
     wr(a.dkc, cn); wr(a.dvc, cn); rd(a.rope_k, (size_t)a.q_len * (a.dh / 2) * sizeof(float2));
   }
   if (a.dkv_scratch) wr(a.dkv_scratch, attn_dkv_scratch_bytes(a, a.dkv_slices));     // the parts of split key blocks
