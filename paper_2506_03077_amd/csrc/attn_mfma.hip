@@ -25,7 +25,7 @@
 //            8 waves x 32 queries; K and V tiles of 64 keys stream HBM -> LDS
 //            (direct-to-LDS); online softmax in the exp2 domain; multiply and
 //            softmax slots of two wave groups alternate.
-//  dQ      : same decomposition, 32x32x16 MFMAs, two stages; recomputes P from the
+//  dQ      : same decomposition and slots, 32x32x16 MFMAs; recomputes P from the
 //            saved log-sum-exp; dQ^T += K^T dS^T.
 //  dK/dV   : workgroup = 128 keys of one KV head, 4 key blocks x 2 roles: one wave of
 //            a block computes P and dV^T += dO^T P, its partner dP, dS and
@@ -622,20 +622,29 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
 }
 
 // ----------------------------------------------------------------------- dQ --
-// SPLIT: 128 queries per workgroup for launches that would leave CUs idle, as in the forward kernel: the two halves of the workgroup
-// take the even / odd key tiles of the same queries and add up in LDS (1024 queries, 32 heads: 128 workgroups of 256 queries).
+// The slots of the forward kernel: multiply (dQ^T += K^T dS of the previous tile, S = K Q^T and dP = V dO^T of this one) and vector work (dS, and
+// the loads of a later tile), group 1 of the waves one slot behind group 0, four K and V stages.
+//   SPLIT = false: 256 queries, tiles of 64 keys.  A tile is loaded by all waves; group 0 loads two tiles ahead, group 1 three.
+//   SPLIT = true : 128 queries per workgroup for launches that would leave CUs idle, as in the forward kernel: the groups take the even /
+//                  odd tiles, of 32 keys, of the same queries and add up in LDS (1024 queries, 32 heads: 128 workgroups of 256 queries).
+// What bounds it: the clock that the power limit leaves.  The slots keep the matrix pipe busier than two stages behind one barrier per tile did, and the
+// clock falls by most of what that gives: backward and forward of the last 2048-query chunk of 32k, 28 heads, 3.68 -> 3.64 ms; a 32k layer at 7B widths
+// 69.5 -> 67.9; 777 windowed queries 141.5 -> 139.0 us.  Tiles of 32 keys without SPLIT: 3.66 ms, the layer 70.0 (a slot of 24 MFMAs does not cover its start).
 template <int DH, bool SPLIT>
-struct DqShared { char sT[SPLIT ? 8 : 4][TILE64<DH>]; };      // stage st (of a half): K = sT[2 st], V = sT[2 st + 1]
+struct DqShared { char sT[8][TILE64<DH>]; };      // K stages, then V stages; SPLIT: of group 0, then of group 1
+constexpr int DQ_CHAIN = 5;                       // LDS fragments requested ahead of the products (4 and 6 the same within 0.3 %; 6 has no register left)
 template <int DH, bool SPLIT>
 __device__ __forceinline__ void dq_tile(DqShared<DH, SPLIT>& sh, int q_block, int h, const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                         const bf16_t* __restrict__ v, const bf16_t* __restrict__ d_o, const float* __restrict__ lse,
                                         const float* __restrict__ delta, bf16_t* __restrict__ dq, int Hq, int Hkv, int q_start, int c,
                                         float scale, const float2* __restrict__ rope, int window, int kv_first) {
   auto& sT = sh.sT;
-  constexpr int QW = SPLIT ? TQ / 2 : TQ, NT = SPLIT ? AT_THREADS / 2 : AT_THREADS;
+  constexpr int QW = SPLIT ? TQ / 2 : TQ, NK = SPLIT ? TK / 2 : TK, NB = NK / 32;      // queries of the workgroup; keys of a tile, its 32-key blocks
+  constexpr int STAGES = 4, TILE = NK * DH * 2;
+  constexpr int LOADERS = SPLIT ? AT_THREADS / 2 : AT_THREADS, LOADS = NK * DH / 8 / LOADERS;      // threads that load a tile, 16-byte loads of each
 
   const int q0 = q_block * QW, kvh = h / (Hq / Hkv);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), grp = SPLIT ? wave >> 2 : 0, lane = threadIdx.x & 63, half = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), grp = wave >> 2, lane = threadIdx.x & 63, half = lane >> 5;
   const int qw0 = q0 + (SPLIT ? wave & 3 : wave) * 32;
   const int my_q = qw0 + (lane & 31);
   const bool q_valid = my_q < c;
@@ -646,17 +655,16 @@ __device__ __forceinline__ void dq_tile(DqShared<DH, SPLIT>& sh, int q_block, in
   const bf16_t* vbase = v + (int64_t)kvh * DH;
   const int n_total = q_start + c;
   const int n_keys = q_start + min(q0 + QW, c);
-  const int n_tiles = (n_keys + TK - 1) / TK;
+  const int n_tiles = (n_keys + NK - 1) / NK;
   const int wave_last_key = q_start + min(qw0 + 32, c) - 1;
   const int wave_first_qpos = q_start + qw0;
   auto first_key = [&](int p) { return max(kv_first, window > 0 ? p - window + 1 : 0); };   // left edge of the visible range
   const int lo_q = first_key(qpos);
   const int wave_lo_min = first_key(wave_first_qpos), wave_lo_max = first_key(wave_last_key);
-  const int kt0 = first_key(q_start + q0) / TK;
-
-  const uint32_t lds0 = lds_addr(&sT[4 * grp][0]);
-  const FragPre<DH> fp = frag_pre<DH>(lds0);
-  const TileLoad<DH, NT> tl = tile_load_pre<DH, NT>(kv_stride);
+  const int kt0 = first_key(q_start + q0) / NK;
+  // tile i of this wave's sequence
+  auto tile_of = [&](int i) { return SPLIT ? kt0 + 2 * i + grp : kt0 + i; };
+  const int n_it = SPLIT ? (max(0, n_tiles - kt0) + 1) / 2 : max(0, n_tiles - kt0);
 
   constexpr int KS = DH / 16, DB = DH / 32;      // k16 steps of a score, 32-row blocks of the output
   bf16x8 bq[KS], bdo[KS];
@@ -666,72 +674,146 @@ __device__ __forceinline__ void dq_tile(DqShared<DH, SPLIT>& sh, int q_block, in
     for (int ks = 0; ks < KS; ++ks) { bq[ks] = *(const bf16x8*)(q + off + ks * 16); bdo[ks] = *(const bf16x8*)(d_o + off + ks * 16); }
   }
   const float lse_q = lse[(int64_t)h * c + q_row];
-  const float lse2 = lse_q == -INFINITY ? 0.0f : FP32_STATS<DH> ? lse_q : lse_q * LOG2E;    // a query that saw no key: every score is masked, p = exp2(-inf) = 0
-  const float dlt = delta[(int64_t)h * c + q_row];
+  float lse2 = lse_q == -INFINITY ? 0.0f : FP32_STATS<DH> ? lse_q : lse_q * LOG2E;    // a query that saw no key: every score is masked, p = exp2(-inf) = 0
+  float dlt = delta[(int64_t)h * c + q_row];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(bq[ks]), "+v"(bdo[ks]));      // (arrived: the compiler must not wait for them in the loop)
+  asm volatile("" : "+v"(lse2), "+v"(dlt));
+  AT_WAIT_VM(0);     // from here on the loop counts its own loads only
   const float sl = scale * LOG2E;
+
+  // ---- addresses, computed once
+  const uint32_t lds_k = lds_addr(&sT[0][0]) + (SPLIT ? (uint32_t)grp * 2 * STAGES * TILE : 0u);
+  constexpr uint32_t TO_V = STAGES * TILE;
+  const FragPre<DH> fp = frag_pre<DH>(lds_k);
+  const int tid = (int)threadIdx.x % LOADERS;
+  auto load_offset = [&](int i, int rows_valid) {
+    const int id = i * LOADERS + tid, row = id / (DH / 8), chunk = (id % (DH / 8)) ^ swz<DH>(row);
+    return (uint32_t)(((int64_t)min(row, rows_valid - 1) * kv_stride + chunk * 8) * 2);
+  };
+  // loads of tile i; past the end the last tile is loaded again, so that the wait counts stay the same.  The last tile may be short: its rows
+  // past the end re-read the last one.
+  const int t_max = n_tiles - 1;
+  uint32_t voff[LOADS], voff_last[LOADS];
+#pragma unroll
+  for (int j = 0; j < LOADS; ++j) { voff[j] = pin(load_offset(j, NK)); voff_last[j] = pin(load_offset(j, min(NK, n_total - t_max * NK))); }
+  const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_k + (uint32_t)(tid & ~63) * 16u), tile_bytes = (uint32_t)(NK * kv_stride * 2);
+  auto issue = [&](int i, int stage) __attribute__((always_inline)) {
+    const int t = min(tile_of(i), t_max);
+    const char *ks = (const char*)kbase + (uint64_t)tile_bytes * (uint32_t)t, *vs = (const char*)vbase + (uint64_t)tile_bytes * (uint32_t)t;
+#pragma unroll
+    for (int j = 0; j < LOADS; ++j) {
+      const uint32_t off = t == t_max ? voff_last[j] : voff[j], to = dst + (uint32_t)(stage * TILE + j * LOADERS * 16);
+      dma16(ks, off, to);
+      dma16(vs, off, to + TO_V);
+    }
+  };
+  // steps in which some (query, key) pair of the wave is visible
+  const int step_t = SPLIT ? 2 : 1, first_t = tile_of(0);
+  const int act0 = max(0, (wave_lo_min / NK - first_t + step_t - 1) / step_t);
+  const int act1 = qw0 < c && wave_last_key >= 0 ? min(n_it, (wave_last_key / NK - first_t + step_t) / step_t) : 0;
+  auto active = [&](int i) { return i >= act0 && i < act1; };
+
+  struct Scores { f32x16 s[NB], dp[NB]; };
+  struct Operand { bf16x8 w[TERMS<DH>][NB][2]; };      // dS^T: [term][key block][k16 step]
   f32x16 acc[DB];
 #pragma unroll
   for (int i = 0; i < DB; ++i) acc[i] = zero16();
-
-  auto step = [&](int kt, auto stage) {
-    constexpr uint32_t oK = decltype(stage)::value * 2 * TILE64<DH>, oV = oK + TILE64<DH>;
-    const int k0 = kt * TK;
-    if (qw0 >= c || k0 > wave_last_key || k0 + TK - 1 < wave_lo_min) return;
-    const bool diag = k0 + TK - 1 > wave_first_qpos || k0 < wave_lo_max;
+  auto second = [&](const Operand& ds, int stage) __attribute__((always_inline)) {
+    const uint32_t so = (uint32_t)(stage * TILE);
+    mfma_chain<NB * 2 * DB, DQ_CHAIN>(
+        [&](int n) { const uint32_t o = so + (n / DB * 16) * (DH * 2); return lds_tr(fp.tr[n % DB * 2] + o, fp.tr[n % DB * 2 + 1] + o); },
+        [&](int n, const bf16x8& f) {
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      f32x16 s = zero16(), dp = zero16();
-      mfma_chain<2 * KS>([&](int i) { return lds_b128(fp.rows[i % KS] + (i < KS ? oK : oV) + b * 32 * (DH * 2)); },
-                         [&](int i, const bf16x8& f) { if (i < KS) s = MFMA(f, bq[i], s); else dp = MFMA(f, bdo[i - KS], dp); });
-      if (diag) {
+          for (int t = 0; t < TERMS<DH>; ++t) acc[n % DB] = MFMA(f, ds.w[t][n / DB >> 1][n / DB & 1], acc[n % DB]);
+        });
+  };
+  auto first = [&](Scores& x, int stage) __attribute__((always_inline)) {
+    const uint32_t so = (uint32_t)(stage * TILE);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) { x.s[b] = zero16(); x.dp[b] = zero16(); }
+    // n = k16 step * 2 NB + which: S of the blocks, then dP of the blocks
+    mfma_chain<2 * NB * KS, DQ_CHAIN>(
+        [&](int n) { const int b = n % (2 * NB); return lds_b128(fp.rows[n / (2 * NB)] + so + (b >= NB ? TO_V : 0u) + b % NB * 32 * (DH * 2)); },
+        [&](int n, const bf16x8& f) {
+          const int b = n % (2 * NB), ks = n / (2 * NB);
+          if (b < NB) x.s[b] = MFMA(f, bq[ks], x.s[b]); else x.dp[b - NB] = MFMA(f, bdo[ks], x.dp[b - NB]);
+        });
+  };
+  auto vector = [&](Scores& x, Operand& ds, int i) __attribute__((always_inline)) {
+    const int k0 = tile_of(i) * NK;
+    if (k0 + NK - 1 > wave_first_qpos || k0 < wave_lo_max) {      // only tiles on an edge of the visible range pay for the mask
+      // key 4 half + e of the tile is visible for first <= e < first + n: one unsigned comparison
+      const int from = lo_q - k0 - 4 * half;
+      const uint32_t n = (uint32_t)max(0, qpos - lo_q + 1);
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int key = k0 + b * 32 + acc_row(r, half);
-          if (key > qpos || key < lo_q) s[r] = -INFINITY;     // exp2(-inf) = 0
+          x.s[b][r] = (uint32_t)(b * 32 + acc_row(r, 0) - from) < n ? x.s[b][r] : -INFINITY;     // exp2(-inf) = 0
+          if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);
         }
-      }
+    }
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float p = exp_of<DH>(s[r], scale, sl, -lse2);
-        s[r] = p * (dp[r] - dlt);                              // dS^T (the factor `scale` is applied at the end)
-      }
-      bf16x8 db[TERMS<DH>][2];
+    for (int b = 0; b < NB; ++b)
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
-        db[0][ks] = pack8(s, ks);
-        if (TERMS<DH> == 2) db[TERMS<DH> - 1][ks] = rest8(s, ks, db[0][ks]);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float p = exp_of<DH>(x.s[b][8 * ks + e], scale, sl, -lse2);
+          x.s[b][8 * ks + e] = p * (x.dp[b][8 * ks + e] - dlt);                          // dS^T (the factor `scale` is applied at the end)
+        }
+        ds.w[0][b][ks] = pack8(x.s[b], ks);
+        if (TERMS<DH> == 2) ds.w[TERMS<DH> - 1][b][ks] = rest8(x.s[b], ks, ds.w[0][b][ks]);
       }
-      mfma_chain<2 * DB>([&](int i) { const uint32_t o = oK + (b * 32 + i / DB * 16) * (DH * 2); return lds_tr(fp.tr[i % DB * 2] + o, fp.tr[i % DB * 2 + 1] + o); },
-                         [&](int i, const bf16x8& f) {
-                           for (int t = 0; t < TERMS<DH>; ++t) acc[i % DB] = MFMA(f, db[t][i / DB], acc[i % DB]);
-                         });
-    }
   };
-  // tile i of this wave's sequence; both halves execute the same number of barriers
-  auto tile_of = [&](int i) { return SPLIT ? kt0 + 2 * i + grp : kt0 + i; };
-  const int n_it = SPLIT ? (max(0, n_tiles - kt0) + 1) / 2 : max(0, n_tiles - kt0);
-  auto issue = [&](int i, int st) {
-    const int kt = tile_of(i);
-    if (kt >= n_tiles) return;
-    const int64_t row0 = (int64_t)kt * TK;
-    dma_tile64(tl, kbase + row0 * kv_stride, kv_stride, n_total - kt * TK, lds0 + (uint32_t)(st * 2 * TILE64<DH>));
-    dma_tile64(tl, vbase + row0 * kv_stride, kv_stride, n_total - kt * TK, lds0 + (uint32_t)((st * 2 + 1) * TILE64<DH>));
-  };
-  using S0 = std::integral_constant<int, 0>;
-  using S1 = std::integral_constant<int, 1>;
 
-  if (n_it > 0) issue(0, 0);
-  for (int i = 0; i < n_it; i += 2) {
-    WAIT_VM0();
-    __syncthreads();
-    if (i + 1 < n_it) issue(i + 1, 1);
-    step(tile_of(i), S0{});
-    if (i + 1 < n_it) {
-      WAIT_VM0();
-      __syncthreads();
-      if (i + 2 < n_it) issue(i + 2, 0);
-      step(tile_of(i + 1), S1{});
-    }
+  if (n_it > 0) {
+    auto run = [&](auto grp_c) __attribute__((always_inline)) {
+      // Before a tile is read every wave has waited for its own share of it and a barrier has passed: tile j + 1 by the end of vector slot j, or,
+      // where group 1 loads for group 0 as well, by the end of its multiply slot j; what was issued after it stays in flight.  A stage is
+      // loaded again once the slot is over in which its K was last read, for the second product: by group 0 two tiles ahead, as group 1 reads
+      // K of tile j - 2 in the slot before vector slot j of group 0; else three.
+      constexpr bool G1 = decltype(grp_c)::value;
+      constexpr int AHEAD = SPLIT || G1 ? 3 : 2, PAIR = 2 * LOADS;
+#pragma unroll
+      for (int j = 0; j < AHEAD; ++j) issue(j, j);
+      AT_WAIT_VM(PAIR * (AHEAD - 1));
+      AT_SLOT_BARRIER();
+      if (G1) AT_SLOT_BARRIER();
+      Operand ds;                // of the previous tile
+      bool held = false;         // there is one
+      auto step = [&](int i, int stage) __attribute__((always_inline)) {      // stage = i % 4, a constant
+        const bool act = active(i);
+        Scores x;                // (without a value where the tile is skipped: nothing is kept alive for it)
+        Operand next;
+        __builtin_amdgcn_s_setprio(1);
+        if (held) second(ds, (stage + 3) % STAGES);
+        if (act) first(x, stage);
+        __builtin_amdgcn_s_setprio(0);
+        if (!SPLIT && G1) AT_WAIT_VM(PAIR);
+        AT_SLOT_BARRIER();
+        issue(i + AHEAD, (stage + AHEAD) % STAGES);
+        if (act) vector(x, next, i);
+        ds = next;
+        held = act;
+        if (SPLIT || !G1) AT_WAIT_VM(PAIR * (AHEAD - 1));
+        AT_SLOT_BARRIER();
+      };
+      // whole groups of four steps (a step past the last tile loads that tile again and passes its barriers)
+      int i = 0;
+      for (; i < n_it; i += 4) {
+        step(i, 0);
+        step(i + 1, 1);
+        step(i + 2, 2);
+        step(i + 3, 3);
+      }
+      if (held) second(ds, 3);
+      AT_WAIT_VM(0);
+      if (!G1) AT_SLOT_BARRIER();        // both groups execute the same number of barriers
+    };
+    if (grp == 0) run(std::false_type{});
+    else run(std::true_type{});
   }
 
   if constexpr (SPLIT) {
