@@ -624,6 +624,30 @@ __host__ __device__ __forceinline__ Schedule make_schedule(int tiles, int k_step
   }
   return best > 1 ? Schedule{tiles, tiles - tail, tail, best} : Schedule{tiles, tiles, 0, 1};
 }
+// The other way to fill the last round, for fp32 stores whose sizes the host knows and 129 to 160 tiles left over, which no whole number of splits
+// fits: each of these `tail` tiles keeps a workgroup of its own, which stops after `main` K steps and stores to C, and the `helpers` CUs without
+// a tile form the `rest` of the reductions.  First of a tile each, in step with their neighbours, so that they share operand panels in their L2;
+// then of the `last` tiles, in `parts` pieces each.  Each piece is a workgroup, dispatched as CUs become free, and leaves a partial tile
+// (at most one per CU in all), which shared_tail_k adds to C in the order of the reduction.
+// What bounds it: the clock, which falls as more CUs multiply (a K step of 140 tiles takes 1.18 us, of 252 1.52), and the sum.  Whole product, tiles
+// unshared / shared, 3584 columns, K = 2 x 18944: 140 tiles 683 / 570 us, 154 691 / 628, 406 1615 / 1521 (126, in two splits, 575); K = 18944: 140 319 /
+// 274, 154 326 / 307; 4096 columns, K = 2 x 14336: 144 530 / 445, 160 537 / 500; 2048 columns, K = 2 x 5632: 136 215 / 195.  From 168 tiles on, where
+// a helper takes the rest of two tiles and more, it loses: 168 724 / 814, 196 780 / 846.
+struct SharedTail { int full, tail, main, rest, helpers, last, parts; };
+constexpr int SHARED_TAIL_MAX = 160, SHARED_PARTS = 8;
+__host__ __device__ __forceinline__ int shared_pieces(const SharedTail& sh) { return sh.helpers + sh.last * sh.parts; }
+// Cost in K steps as for the splits above: 5 for the start and the end of the second piece, 3.5 for the launch of the sum and 0.09 per tile written
+// and read, C itself among them.
+static bool shared_schedule(int tiles, int k_steps, int scratch_tiles, SharedTail& sh) {
+  const int tail = tiles % N_CU;
+  if (2 * tail <= N_CU || tail > SHARED_TAIL_MAX || scratch_tiles < N_CU) return false;
+  sh.full = tiles - tail; sh.tail = tail;
+  sh.helpers = N_CU - tail; sh.last = tail - sh.helpers;
+  sh.parts = std::min(sh.helpers / sh.last, SHARED_PARTS);
+  sh.rest = (int)((k_steps - 5) / (2.0 + 1.0 / sh.parts));
+  sh.main = k_steps - sh.rest;
+  return sh.rest >= 32 && sh.rest - 3.5 - 0.09 * (shared_pieces(sh) + tail) > 0.0;
+}
 // Workgroup -> (tile, split); false: nothing to do
 __device__ __forceinline__ bool scheduled_tile(const Schedule& sc, int block, bool interleaved, int& tile, int& split) {
   split = 0;
@@ -670,6 +694,61 @@ __global__ __launch_bounds__(NTHREADS) void gemm_mfma_k(const bf16_t* __restrict
     return KSegment{i ? A2 : A, i ? B2 : B, b, e};
   };
   gemm_tile<TA, TB, MODE>(A2 ? 2 : 1, segment, Cv, M, N, lda, ldb, ldc, tm, tn, smem, partial, part * 4, row_stats, sw, nf, C0, MODE == 8 ? B2 : nullptr);
+}
+
+// C = A B (TB: B^T stored), fp32, the last round of tiles shared (SharedTail)
+template <bool TB>
+__global__ __launch_bounds__(NTHREADS) void gemm_mfma_shared_k(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, float* __restrict__ C, int M, int N, int K,
+                                                               int64_t lda, int64_t ldb, int64_t ldc, const bf16_t* __restrict__ A2,
+                                                               const bf16_t* __restrict__ B2, float* __restrict__ scratch, const SharedTail sh) {
+  __shared__ __attribute__((aligned(1024))) char smem[SMEM_BYTES];
+  const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN, k_steps = (K + BK - 1) / BK, part = partial_floats(M);
+  const int all_steps = A2 ? 2 * k_steps : k_steps, q = (int)blockIdx.x - sh.full, p = q - sh.tail;
+  int tile, s0 = 0, s1 = all_steps;
+  float* partial = nullptr;
+  if (q < 0) tile = xcd_contiguous_id(blockIdx.x, sh.full);
+  else if (p < 0) { tile = sh.full + xcd_contiguous_id(q, sh.tail); s1 = sh.main; }
+  else {
+    int t, slot;
+    s0 = sh.main;
+    if (p < sh.helpers) t = slot = xcd_contiguous_id(p, sh.helpers);
+    else {      // piece of a last tile
+      const int i = p - sh.helpers, u = i % sh.last, piece = i / sh.last, per = (sh.rest + sh.parts - 1) / sh.parts;
+      t = sh.helpers + u;
+      slot = sh.helpers + u * sh.parts + piece;
+      s0 += piece * per;
+      s1 = min(all_steps, s0 + per);
+    }
+    tile = sh.full + t;
+    partial = scratch + (int64_t)slot * part;
+  }
+  int tm, tn;
+  band_coords(tile, tiles_m, tiles_n, band_height(tiles_m, tiles_m * tiles_n, true), tm, tn);
+  auto segment = [&](int i) {
+    const int b = max(s0 - i * k_steps, 0) * BK, e = min(min(s1 - i * k_steps, k_steps) * BK, K);
+    return KSegment{i ? A2 : A, i ? B2 : B, b, e};
+  };
+  gemm_tile<false, TB, 0>(A2 ? 2 : 1, segment, C, M, N, lda, ldb, ldc, tm, tn, smem, partial, part * 4);
+}
+// C += the pieces of its tiles (64 workgroups each) in the order of the reduction
+__global__ __launch_bounds__(256) void shared_tail_k(const SharedTail sh, const float* __restrict__ scratch, float* __restrict__ C, int M, int N, int64_t ldc) {
+  const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN, part = partial_floats(M);
+  const int t = blockIdx.x / 64, u = t - sh.helpers;
+  int tm, tn;
+  band_coords(sh.full + t, tiles_m, tiles_n, band_height(tiles_m, tiles_m * tiles_n, true), tm, tn);
+  const int row_l = (blockIdx.x % 64) * 4 + (threadIdx.x >> 6), col_l = 4 * (threadIdx.x & 63), row = tm * BM + row_l, col = tn * BN + col_l;
+  if (row >= M || col >= N) return;
+  const int first = u < 0 ? t : sh.helpers + u * sh.parts, n = u < 0 ? 1 : sh.parts;
+  float* c = C + (int64_t)row * ldc + col;
+  const float* src = scratch + (int64_t)first * part + row_l * BN + col_l;
+  f32x4 v = *(const f32x4*)c, in[SHARED_PARTS];
+#pragma unroll
+  for (int z = 0; z < SHARED_PARTS; ++z)
+    if (z < n) in[z] = *(const f32x4*)(src + (int64_t)z * part);
+#pragma unroll
+  for (int z = 0; z < SHARED_PARTS; ++z)
+    if (z < n) v += in[z];
+  *(f32x4*)c = v;
 }
 
 // Weight-gradient form with a segmented reduction: C += sum_s A_s^T B_s (TB: B_s^T stored), every segment with its own run-time row
@@ -838,6 +917,11 @@ size_t gemm_scratch_bytes(int max_m, int max_n) {
 static int scratch_tiles_of(const GemmArgs& g, int max_m) {
   return g.scratch && !((uintptr_t)g.scratch & 15) ? (int)std::min<size_t>(N_CU, g.scratch_bytes / (partial_floats(max_m) * sizeof(float))) : 0;
 }
+// fp32 store of one product (or pair) with the sizes on the host
+static bool shares_tail(const GemmArgs& g, int scratch_tiles, SharedTail& sh) {
+  return !g.ta && !g.acc && g.out_dt == DT_F32 && !g.rows_dev && !g.glu_up && !g.numer_targets && !g.row_stats && !g.swiglu_gate &&
+         shared_schedule((int)(cdiv(g.M, BM) * cdiv(g.N, BN)), (int)cdiv(g.K, BK) * (g.A2 ? 2 : 1), scratch_tiles, sh);
+}
 static hipError_t launch_tail(int mode, TailArgs t, int max_tail, hipStream_t st) {
   t.blocks = max_tail < 64 ? 64 : 16;
   const unsigned blocks = (unsigned)(max_tail * t.blocks);
@@ -865,7 +949,10 @@ double gemm_mfma_us(const GemmArgs* gs, int n) {      // n > 1: one grouped laun
     k = std::max(k, (int)cdiv(gs[i].K, BK) * (gs[i].A2 ? 2 : 1));
     max_m = std::max(max_m, gs[i].M);
   }
-  return launch_us(tiles, k, scratch_tiles_of(gs[0], max_m), max_m);
+  const int scratch_tiles = scratch_tiles_of(gs[0], max_m);
+  if (SharedTail sh; n == 1 && shares_tail(gs[0], scratch_tiles, sh))
+    return 14.0 + 1.35 * ((double)(sh.full / N_CU) * k + sh.main) + 0.055 * (shared_pieces(sh) + sh.tail);
+  return launch_us(tiles, k, scratch_tiles, max_m);
 }
 
 // C = silu(A B^T) * (A glu_up^T): from as many tiles on as a grouped launch of both products takes.  Whole forward of a layer in one chunk, this form / the
@@ -883,6 +970,20 @@ hipError_t gemm_mfma(const GemmArgs& g, hipStream_t st) {
                  : g.acc ? (g.out_dt == DT_BF16 ? 4 : 2) : (g.out_dt == DT_BF16 ? 1 : 0);
   const bool dev_rows = g.rows_dev != nullptr;
   const int scratch_tiles = mode_splits(mode) && !(g.ta && dev_rows) ? scratch_tiles_of(g, g.M) : 0;
+  if (SharedTail sh; shares_tail(g, scratch_tiles, sh)) {
+    {
+      prof::Scope sc_time(prof::GEMM_SINGLE + (g.tb ? 0 : 4), 2.0 * g.M * g.N * g.K * (g.A2 ? 2 : 1), false, st);
+      auto launch = [&](auto kernel) {
+        kernel<<<(unsigned)(sh.full + sh.tail + shared_pieces(sh)), NTHREADS, 0, st>>>((const bf16_t*)g.A, (const bf16_t*)g.B, (float*)g.C, g.M, g.N, g.K, g.lda, g.ldb, g.ldc,
+                                                                (const bf16_t*)g.A2, (const bf16_t*)g.B2, g.scratch, sh);
+      };
+      if (g.tb) launch(gemm_mfma_shared_k<true>);
+      else launch(gemm_mfma_shared_k<false>);
+    }
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) shared_tail_k<<<(unsigned)sh.tail * 64, 256, 0, st>>>(sh, g.scratch, (float*)g.C, g.M, g.N, g.ldc);
+    return e != hipSuccess ? e : hipGetLastError();
+  }
   const Schedule sc = make_schedule(tiles_m * tiles_n, k_steps, scratch_tiles);
   // with a run-time row count the schedule is made on the device: room for any tail
   const unsigned grid = dev_rows && scratch_tiles ? (unsigned)(tiles_m * tiles_n + N_CU) : (unsigned)(sc.full + sc.tail * sc.splits);

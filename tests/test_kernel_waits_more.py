@@ -19,3 +19,10 @@ def test_shares_taken_without_a_break_have_kernels_that_keep_the_schedule(built)
     assert len(found) == 4
     worst = {n: barriers_passed_unwaited(c) for n, c in found.items()}
     assert max(worst.values()) == 0, {n: w for n, w in worst.items() if w}
+
+
+def test_shared_last_rounds_keep_the_gemm_schedule(built):  # noqa: F811
+    found = _named(built, ("18gemm_mfma_shared_k",))
+    assert len(found) == 2
+    worst = {n: barriers_passed_unwaited(c) for n, c in found.items()}
+    assert max(worst.values()) <= 2, {n: w for n, w in worst.items() if w > 2}
