@@ -232,7 +232,7 @@ LayerWs carve_layer(const sbp_layer_cfg* c, void* ws, const LayerPlan& plan, boo
 // 1024-wide stack of two layers, 2 x 1023 tokens, chunk 512, 3.27 -> 2.65.  SPAN_ROWS: 8192 rows a pass are slower again (8192 tokens at
 // 4096 / 14336 11.85 ms, 32768 at 7B widths 71.7): the MLP's tensors, 230 to 310 MB each, no longer stay in the 256 MB cache from one product to the next.
 constexpr int SPAN_ROWS = 4096;
-constexpr int SPAN_SEQS = 32;
+constexpr int SPAN_SEQS = ATTN_MAX_SEQS;
 template <typename Fits>
 LayerPlan plan_layer(const sbp_layer_cfg* c, int max_sets, double products, bool dw, Fits fits) {
   const int T = c->seq_len, cm = std::min(c->chunk, T), rows_max = std::max(cm, SPAN_ROWS), grain = c->dtype == SBP_BF16 ? 256 : 32;
@@ -356,7 +356,7 @@ AttnArgs pass_attn(const sbp_layer_cfg* c, const LayerWs& s, const Pass& p) {
   AttnArgs aa{};
   aa.dt = c->dtype; aa.Hq = c->n_q_heads; aa.Hkv = c->n_kv_heads; aa.dh = c->head_dim;
   aa.batch = p.seqs; aa.q_start = p.r0; aa.q_len = p.n; aa.scale = 1.0f / std::sqrt((float)c->head_dim);
-  aa.window = c->window; aa.kv_first = c->seq_first ? c->seq_first[p.b0] : 0;      // rows before it are padding in front of the sequence
+  aa.window = c->window; aa.kv_first = c->seq_first ? *std::min_element(c->seq_first + p.b0, c->seq_first + p.b0 + p.seqs) : 0;      // rows before it are padding in front of the sequence
   aa.kv_firsts = c->seq_first && p.seqs > 1 ? c->seq_first + p.b0 : nullptr;
   aa.q = s.q; aa.k = s.K; aa.v = s.V; aa.o = s.o; aa.lse = s.lse;
   if (fusion_mask() & FUSE_ROPE_Q) aa.rope_q = s.rope + (size_t)p.r0 * (c->head_dim / 2);

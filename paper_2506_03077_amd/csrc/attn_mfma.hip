@@ -242,10 +242,10 @@ __device__ __forceinline__ float max_over_quads(float x) {
     asm volatile("s_barrier" ::: "memory");   \
     __builtin_amdgcn_sched_barrier(0);        \
   } while (0)
-// Workgroup -> (query tile, head).  The workgroups of an XCD get a contiguous run of (head, query tile) pairs, so that the heads of one
+// Workgroup -> (query tile, head of a sequence).  The workgroups of an XCD get a contiguous run of (head, query tile) pairs, so that the heads of one
 // K/V group run on one XCD and share its stream through that L2; the tiles with the most keys come first.
-__device__ __forceinline__ void query_tile_of(int n_qt, int Hq, int& qt, int& h) {
-  const int id = (int)blockIdx.x, n = n_qt * Hq, x = id % 8, q = n / 8, r = n % 8;
+__device__ __forceinline__ void query_tile_of(int n_qt, int heads, int& qt, int& h) {
+  const int id = (int)blockIdx.x, n = n_qt * heads, x = id % 8, q = n / 8, r = n % 8;
   const int c = x * q + min(x, r) + id / 8;
   h = c / n_qt;
   qt = n_qt - 1 - c % n_qt;
@@ -272,15 +272,18 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
                                                                  const bf16_t* __restrict__ v, bf16_t* __restrict__ o,
                                                                  float* __restrict__ lse, int Hq, int Hkv, int q_start,
                                                                  int c, float scale, const float2* __restrict__ rope,
-                                                                 int window, int kv_first) {
+                                                                 int window, const AttnSeqs seqs) {
   __shared__ __attribute__((aligned(1024))) char sT[8 * TILE64<DH>];   // K stages, then V stages
   __shared__ float sM[SPLIT ? 2 : 1][4][32];                  // SPLIT: the running maxima of the groups' queries
   constexpr int QW = SPLIT ? TQ / 2 : TQ;                     // queries of the workgroup
   constexpr int STAGES = SPLIT ? 2 : 4, K_AHEAD = SPLIT ? 2 : 3, V_AHEAD = SPLIT ? 1 : 2;
   constexpr int LOADERS = SPLIT ? AT_THREADS / 2 : AT_THREADS, LOADS = 8 * DH / LOADERS;   // threads that load a tile, 16-byte loads of each
 
-  int qt, h;
-  query_tile_of((c + QW - 1) / QW, Hq, qt, h);
+  int qt, bh;
+  query_tile_of((c + QW - 1) / QW, Hq * seqs.n, qt, bh);
+  const int b = bh / Hq, h = bh - b * Hq, kv_first = seqs.first[b];
+  q += (int64_t)b * c * Hq * DH; o += (int64_t)b * c * Hq * DH; lse += (int64_t)b * c * Hq;
+  k += (int64_t)b * c * Hkv * DH; v += (int64_t)b * c * Hkv * DH;
   const int q0 = qt * QW, kvh = h / (Hq / Hkv);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
   const int grp = wave >> 2;
@@ -634,11 +637,15 @@ template <int DH, bool SPLIT>
 struct DqShared { char sT[8][TILE64<DH>]; };      // K stages, then V stages; SPLIT: of group 0, then of group 1
 constexpr int DQ_CHAIN = 5;                       // LDS fragments requested ahead of the products (4 and 6 the same within 0.3 %; 6 has no register left)
 template <int DH, bool SPLIT>
-__device__ __forceinline__ void dq_tile(DqShared<DH, SPLIT>& sh, int q_block, int h, const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
+__device__ __forceinline__ void dq_tile(DqShared<DH, SPLIT>& sh, int q_block, int bh, const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                         const bf16_t* __restrict__ v, const bf16_t* __restrict__ d_o, const float* __restrict__ lse,
                                         const float* __restrict__ delta, bf16_t* __restrict__ dq, int Hq, int Hkv, int q_start, int c,
-                                        float scale, const float2* __restrict__ rope, int window, int kv_first) {
+                                        float scale, const float2* __restrict__ rope, int window, const AttnSeqs& seqs) {
   auto& sT = sh.sT;
+  const int b = bh / Hq, h = bh - b * Hq, kv_first = seqs.first[b];
+  q += (int64_t)b * c * Hq * DH; d_o += (int64_t)b * c * Hq * DH; dq += (int64_t)b * c * Hq * DH;
+  k += (int64_t)b * c * Hkv * DH; v += (int64_t)b * c * Hkv * DH;
+  lse += (int64_t)b * c * Hq; delta += (int64_t)b * 2 * c * Hq;
   constexpr int QW = SPLIT ? TQ / 2 : TQ, NK = SPLIT ? TK / 2 : TK, NB = NK / 32;      // queries of the workgroup; keys of a tile, its 32-key blocks
   constexpr int STAGES = 4, TILE = NK * DH * 2;
   constexpr int LOADERS = SPLIT ? AT_THREADS / 2 : AT_THREADS, LOADS = NK * DH / 8 / LOADERS;      // threads that load a tile, 16-byte loads of each
@@ -869,9 +876,9 @@ __global__ __launch_bounds__(AT_THREADS) void attn_bwd_dq_mfma_k(const bf16_t* _
                                                                     const float* __restrict__ lse, const float* __restrict__ delta,
                                                                     bf16_t* __restrict__ dq, int Hq, int Hkv, int q_start, int c,
                                                                     float scale, const float2* __restrict__ rope, int window,
-                                                                    int kv_first) {
+                                                                    const AttnSeqs seqs) {
   __shared__ __attribute__((aligned(1024))) DqShared<DH, SPLIT> sh;
-  dq_tile<DH, SPLIT>(sh, blockIdx.x, blockIdx.y, q, k, v, d_o, lse, delta, dq, Hq, Hkv, q_start, c, scale, rope, window, kv_first);
+  dq_tile<DH, SPLIT>(sh, blockIdx.x, blockIdx.y, q, k, v, d_o, lse, delta, dq, Hq, Hkv, q_start, c, scale, rope, window, seqs);
 }
 
 // -------------------------------------------------------------------- dK/dV --
@@ -910,11 +917,18 @@ struct DkvShared {
   float sDl[KV_STAGES][QT];                       // delta of the tile's queries
 };
 template <int DH, bool IN_TURN>
-__device__ __forceinline__ void dkv_block(DkvShared<DH>& sh, int key_block, int kvh, int slice, const bf16_t* __restrict__ q,
+__device__ __forceinline__ void dkv_block(DkvShared<DH>& sh, int key_block, int bh, int slice, const bf16_t* __restrict__ q,
                                           const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, const bf16_t* __restrict__ d_o,
                                           const float* __restrict__ lse2, const float* __restrict__ delta, float* __restrict__ dk,
-                                          float* __restrict__ dv, int Hq, int Hkv, int q_start, int c, float scale, int window, int kv_first,
+                                          float* __restrict__ dv, int Hq, int Hkv, int q_start, int c, float scale, int window, const AttnSeqs& seqs,
                                           int key_block0, int slices, float* __restrict__ part) {
+  const int sq = bh / Hkv, kvh = bh - sq * Hkv, kv_first = seqs.first[sq];
+  {
+    const int64_t nq = (int64_t)sq * c * Hq, nk = (int64_t)sq * c * Hkv * DH;
+    q += nq * DH; d_o += nq * DH; lse2 += 2 * nq; delta += 2 * nq;
+    k += nk; v += nk; dk += nk; dv += nk;
+    if (part) part += (int64_t)sq * slices * 2 * (q_start + c - key_block0 * KV_TILE) * Hkv * DH;
+  }
   auto& sQD = sh.sQD;
   auto& sP = sh.sP;
   auto& sL = sh.sL;
@@ -977,7 +991,7 @@ __device__ __forceinline__ void dkv_block(DkvShared<DH>& sh, int key_block, int 
   const int qt_first = max(0, key0 - q_start) / QT;
   int n_qt = (c + QT - 1) / QT;
   if (window > 0) n_qt = min(n_qt, max(0, key0 + KV_TILE - 1 + window - 1 - q_start) / QT + 1);
-  const int n_all = max(0, n_qt - qt_first) * G;
+  const int n_all = key0 + KV_TILE <= kv_first ? 0 : max(0, n_qt - qt_first) * G;      // (a sequence of several may hide blocks that others see)
   auto share = [&](int z) { return (int)((int64_t)n_all * z / slices); };      // first step of share z
   for (int z = part ? slice : 0, z_last = IN_TURN ? 0 : part ? slice : slices - 1; z <= z_last; ++z) {
   const int it0 = IN_TURN ? 0 : share(z), n_iter = (IN_TURN ? n_all : share(z + 1)) - it0;
@@ -1190,11 +1204,11 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
                                                                   const bf16_t* __restrict__ v, const bf16_t* __restrict__ d_o,
                                                                   const float* __restrict__ lse2, const float* __restrict__ delta,
                                                                   float* __restrict__ dk, float* __restrict__ dv, int Hq, int Hkv,
-                                                                  int q_start, int c, float scale, int window, int kv_first,
+                                                                  int q_start, int c, float scale, int window, const AttnSeqs seqs,
                                                                   int key_block0, int slices, float* __restrict__ part) {
   __shared__ __attribute__((aligned(1024))) DkvShared<DH> sh;
   dkv_block<DH, false>(sh, blockIdx.x, blockIdx.y, blockIdx.z, q, k, v, d_o, lse2, delta, dk, dv, Hq, Hkv, q_start, c, scale, window,
-                       kv_first, key_block0, slices, part);
+                       seqs, key_block0, slices, part);
 }
 
 // dK/dV and dQ in one launch, the workgroups of dK/dV, the longer ones, first: for chunks that are a few rounds of the chip, where each
@@ -1205,31 +1219,31 @@ __device__ __forceinline__ void bwd_block(const bf16_t* __restrict__ q, const bf
                                           const bf16_t* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ lse2,
                                           const float* __restrict__ delta, bf16_t* __restrict__ dq, float* __restrict__ dk, float* __restrict__ dv,
                                           int Hq, int Hkv, int q_start, int c, float scale, const float2* __restrict__ rope, int window,
-                                          int kv_first, int key_block0, int key_blocks, int slices, float* __restrict__ part, int q_blocks) {
+                                          const AttnSeqs& seqs, int key_block0, int key_blocks, int slices, float* __restrict__ part, int q_blocks) {
   static_assert(AT_THREADS == KV_THREADS, "one workgroup shape");
   __shared__ __attribute__((aligned(1024))) union { DkvShared<DH> dkv; DqShared<DH, SPLIT> dq; } sh;
-  const int n_dkv = key_blocks * Hkv * (IN_TURN ? 2 : part ? slices : 1), b = blockIdx.x;
+  const int kv_heads = Hkv * seqs.n, heads = Hq * seqs.n, n_dkv = key_blocks * kv_heads * (IN_TURN ? 2 : part ? slices : 1), b = blockIdx.x;
   if (b < n_dkv) {
     const int r = b / key_blocks;
-    dkv_block<DH, IN_TURN>(sh.dkv, b % key_blocks, r % Hkv, r / Hkv, q, k, v, d_o, lse2, delta, dk, dv, Hq, Hkv, q_start, c, scale, window, kv_first,
+    dkv_block<DH, IN_TURN>(sh.dkv, b % key_blocks, r % kv_heads, r / kv_heads, q, k, v, d_o, lse2, delta, dk, dv, Hq, Hkv, q_start, c, scale, window, seqs,
                            key_block0, slices, part);
   } else {
     // the tiles with the most keys first
     const int i = b - n_dkv;
-    dq_tile<DH, SPLIT>(sh.dq, q_blocks - 1 - i / Hq, i % Hq, q, k, v, d_o, lse, delta, dq, Hq, Hkv, q_start, c, scale, rope, window, kv_first);
+    dq_tile<DH, SPLIT>(sh.dq, q_blocks - 1 - i / heads, i % heads, q, k, v, d_o, lse, delta, dq, Hq, Hkv, q_start, c, scale, rope, window, seqs);
   }
 }
 #define BWD_PARAMS const bf16_t *__restrict__ q, const bf16_t *__restrict__ k, const bf16_t *__restrict__ v, const bf16_t *__restrict__ d_o, \
                    const float *__restrict__ lse, const float *__restrict__ lse2, const float *__restrict__ delta, bf16_t *__restrict__ dq, \
                    float *__restrict__ dk, float *__restrict__ dv, int Hq, int Hkv, int q_start, int c, float scale, \
-                   const float2 *__restrict__ rope, int window, int kv_first, int key_block0, int key_blocks, int slices, float *__restrict__ part, int q_blocks
-#define BWD_ARGS q, k, v, d_o, lse, lse2, delta, dq, dk, dv, Hq, Hkv, q_start, c, scale, rope, window, kv_first, key_block0, key_blocks, slices, part, q_blocks
+                   const float2 *__restrict__ rope, int window, const AttnSeqs seqs, int key_block0, int key_blocks, int slices, float *__restrict__ part, int q_blocks
+#define BWD_ARGS q, k, v, d_o, lse, lse2, delta, dq, dk, dv, Hq, Hkv, q_start, c, scale, rope, window, seqs, key_block0, key_blocks, slices, part, q_blocks
 template <int DH, bool SPLIT> __global__ __launch_bounds__(AT_THREADS) void attn_bwd_mfma_k(BWD_PARAMS) { bwd_block<DH, SPLIT, false>(BWD_ARGS); }
 template <int DH, bool SPLIT> __global__ __launch_bounds__(AT_THREADS) void attn_bwd_in_turn_k(BWD_PARAMS) { bwd_block<DH, SPLIT, true>(BWD_ARGS); }
 #undef BWD_PARAMS
 #undef BWD_ARGS
 
-// dk / dv += sum over the slices of the split form, in their order, keys from `first` on.  A thread takes elements e .. e + 3 and e + DH / 2 .. of a
+// dk / dv += sum over the slices of the split form, in their order, keys from `first` on (blockIdx.y: sequence).  A thread takes elements e .. e + 3 and e + DH / 2 .. of a
 // (key, head): what the rotary embedding pairs, so that the chunk's own rows, final with this call, leave as dkc = RoPE^T(dk) and dvc = dv
 // too (optional).
 template <int DH>
@@ -1238,6 +1252,10 @@ __global__ __launch_bounds__(256) void attn_dkv_sum_k(const float* __restrict__ 
                                                       const float2* __restrict__ rope) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;      // dk, then dv
   if (i >= 2 * pairs) return;
+  const int64_t keys = first + pairs * 8 / ((int64_t)Hkv * DH), sq = blockIdx.y;      // of a sequence
+  part += sq * slices * 2 * pairs * 8;
+  dk += sq * keys * Hkv * DH; dv += sq * keys * Hkv * DH;
+  if (dkc) { dkc += sq * (keys - q_start) * Hkv * DH; dvc += sq * (keys - q_start) * Hkv * DH; }
   const bool is_dk = i < pairs;
   const int64_t p = is_dk ? i : i - pairs, rh = p / (DH / 8);
   const int e = (int)(p % (DH / 8)) * 4;
@@ -1272,10 +1290,13 @@ __global__ __launch_bounds__(256) void attn_dkv_sum_k(const float* __restrict__ 
 template <int DH>
 __global__ __launch_bounds__(256) void attn_delta_mfma_k(const bf16_t* __restrict__ o, const bf16_t* __restrict__ d_o,
                                                          const float* __restrict__ lse, float* __restrict__ delta,
-                                                         float* __restrict__ lse2, int Hq, int c) {
+                                                         int Hq, int c) {
   constexpr int LANES = DH / 8;
+  const int64_t first = (int64_t)blockIdx.y * c * Hq;      // blockIdx.y: sequence
   const int64_t pair = (int64_t)blockIdx.x * (256 / LANES) + threadIdx.x / LANES;      // t * Hq + h
   if (pair >= (int64_t)c * Hq) return;
+  o += first * DH; d_o += first * DH; lse += first; delta += 2 * first;
+  float* lse2 = delta + (int64_t)c * Hq;      // second half of the [2, Hq, c] scratch
   const int lane = threadIdx.x % LANES;
   const bf16x8 x = *(const bf16x8*)(o + pair * DH + lane * 8), y = *(const bf16x8*)(d_o + pair * DH + lane * 8);
   float s = 0.f;
@@ -1301,17 +1322,28 @@ bool attn_mfma_aligned(const AttnArgs& a, bool backward) {
   return !backward || (aligned16(a.d_o) && aligned16(a.dq) && aligned16(a.dk) && aligned16(a.dv) && aligned16(a.dkc) && aligned16(a.dvc));
 }
 
+// Several sequences in one launch: with their first keys in its arguments, from the first position on.  A sequence of a batch of short ones is a
+// fraction of a round of the chip: four of 640 tokens, 28 / 4 heads, forward, backward, delta and the sum of the parts 320 -> 210 us; with 2 x 1023
+// tokens and 16 / 4 heads of 64 a stack of two layers 2290 -> 2130 us.
+bool attn_sequences_fit(const AttnArgs& a) { return a.batch <= ATTN_MAX_SEQS && a.q_start == 0; }
+
 // Rounds of 256 workgroups (one per CU), a half query tile costing half a round: the half tiles where they leave fewer CUs idle.
 static bool half_tiles_fill_better(const AttnArgs& a) {
-  return 2 * cdiv(cdiv(a.q_len, TQ) * a.Hq, 256) > cdiv(cdiv(a.q_len, TQ / 2) * a.Hq, 256);
+  return 2 * cdiv(cdiv(a.q_len, TQ) * a.Hq * a.batch, 256) > cdiv(cdiv(a.q_len, TQ / 2) * a.Hq * a.batch, 256);
+}
+static AttnSeqs sequences(const AttnArgs& a) {
+  AttnSeqs s{};
+  s.n = a.batch;
+  for (int b = 0; b < a.batch; ++b) s.first[b] = a.kv_firsts ? a.kv_firsts[b] : a.kv_first;
+  return s;
 }
 template <int DH>
 static hipError_t forward_dh(const AttnArgs& a, hipStream_t st) {
   if (a.q_len == 0) return hipSuccess;
-  const int64_t full = cdiv(a.q_len, TQ) * a.Hq, halves = cdiv(a.q_len, TQ / 2) * a.Hq;
+  const int64_t heads = (int64_t)a.Hq * a.batch, full = cdiv(a.q_len, TQ) * heads, halves = cdiv(a.q_len, TQ / 2) * heads;
   auto launch = [&](auto kernel, int64_t n) {
     kernel<<<(unsigned)n, AT_THREADS, 0, st>>>((bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v, (bf16_t*)a.o, a.lse, a.Hq, a.Hkv,
-                                               a.q_start, a.q_len, a.scale, a.rope_q, a.window, a.kv_first);
+                                               a.q_start, a.q_len, a.scale, a.rope_q, a.window, sequences(a));
   };
   if (half_tiles_fill_better(a)) launch(attn_fwd_mfma_k<DH, true>, halves);
   else launch(attn_fwd_mfma_k<DH, false>, full);
@@ -1322,23 +1354,24 @@ template <int DH>
 static hipError_t backward_dh(const AttnArgs& a, hipStream_t st) {
   if (a.q_len == 0) return hipSuccess;
   const int64_t pairs = (int64_t)a.q_len * a.Hq;
-  float* lse2 = a.delta + pairs;   // second half of the [2, Hq, c] scratch
-  attn_delta_mfma_k<DH><<<(unsigned)cdiv(pairs, 256 / (DH / 8)), 256, 0, st>>>((const bf16_t*)a.o, (const bf16_t*)a.d_o, a.lse, a.delta, lse2, a.Hq,
-                                                              a.q_len);
+  const float* lse2 = a.delta + pairs;   // second half of the [2, Hq, c] scratch
+  const AttnSeqs seqs = sequences(a);
+  attn_delta_mfma_k<DH><<<dim3((unsigned)cdiv(pairs, 256 / (DH / 8)), a.batch), 256, 0, st>>>((const bf16_t*)a.o, (const bf16_t*)a.d_o, a.lse, a.delta, a.Hq,
+                                                                                               a.q_len);
   // key blocks that no query of the chunk can see (before the padding ends, or older than the first query's window)
   // are not launched: their dK/dV contribution is zero
   const int kb0 = attn_first_key_block(a), kb1 = (int)cdiv(a.q_start + a.q_len, KV_TILE), key_blocks = std::max(0, kb1 - kb0);
   const int slices = std::max(1, a.dkv_slices);
   float* part = slices > 1 ? a.dkv_scratch : nullptr;
   const bool halves = half_tiles_fill_better(a);
-  const int64_t blocks = (int64_t)key_blocks * a.Hkv, q_blocks = cdiv(a.q_len, halves ? TQ / 2 : TQ);
+  const int64_t blocks = (int64_t)key_blocks * a.Hkv * a.batch, q_blocks = cdiv(a.q_len, halves ? TQ / 2 : TQ), q_tiles = q_blocks * a.Hq * a.batch;
   const bool in_turn = !part && slices > 1 && blocks <= IN_TURN_BLOCKS;      // two workgroups per key block
   const int64_t n_dkv = blocks * (in_turn ? 2 : part ? slices : 1);
   const bf16_t *q = (const bf16_t*)a.q, *k = (const bf16_t*)a.k, *v = (const bf16_t*)a.v, *d_o = (const bf16_t*)a.d_o;
-  if (n_dkv > 0 && (in_turn || n_dkv + q_blocks * a.Hq <= MERGED_MAX)) {
+  if (n_dkv > 0 && (in_turn || n_dkv + q_tiles <= MERGED_MAX)) {
     auto launch = [&](auto kernel) {
-      kernel<<<(unsigned)(n_dkv + q_blocks * a.Hq), AT_THREADS, 0, st>>>(q, k, v, d_o, a.lse, lse2, a.delta, (bf16_t*)a.dq, a.dk, a.dv, a.Hq, a.Hkv, a.q_start,
-                                                                         a.q_len, a.scale, a.rope_q, a.window, a.kv_first, kb0, key_blocks, slices, part,
+      kernel<<<(unsigned)(n_dkv + q_tiles), AT_THREADS, 0, st>>>(q, k, v, d_o, a.lse, lse2, a.delta, (bf16_t*)a.dq, a.dk, a.dv, a.Hq, a.Hkv, a.q_start,
+                                                                         a.q_len, a.scale, a.rope_q, a.window, seqs, kb0, key_blocks, slices, part,
                                                                          (int)q_blocks);
     };
     if (in_turn && halves) launch(attn_bwd_in_turn_k<DH, true>);
@@ -1347,25 +1380,29 @@ static hipError_t backward_dh(const AttnArgs& a, hipStream_t st) {
     else launch(attn_bwd_mfma_k<DH, false>);
   } else {
     auto launch_dq = [&](auto kernel) {
-      kernel<<<dim3((unsigned)q_blocks, a.Hq), AT_THREADS, 0, st>>>(q, k, v, d_o, a.lse, a.delta, (bf16_t*)a.dq, a.Hq, a.Hkv, a.q_start, a.q_len, a.scale,
-                                                                    a.rope_q, a.window, a.kv_first);
+      kernel<<<dim3((unsigned)q_blocks, a.Hq * a.batch), AT_THREADS, 0, st>>>(q, k, v, d_o, a.lse, a.delta, (bf16_t*)a.dq, a.Hq, a.Hkv, a.q_start, a.q_len, a.scale,
+                                                                    a.rope_q, a.window, seqs);
     };
     if (halves) launch_dq(attn_bwd_dq_mfma_k<DH, true>);
     else launch_dq(attn_bwd_dq_mfma_k<DH, false>);
     if (n_dkv > 0)
-      attn_bwd_dkv_mfma_k<DH><<<dim3((unsigned)key_blocks, a.Hkv, part ? (unsigned)slices : 1u), KV_THREADS, 0, st>>>(
-          q, k, v, d_o, lse2, a.delta, a.dk, a.dv, a.Hq, a.Hkv, a.q_start, a.q_len, a.scale, a.window, a.kv_first, kb0, slices, part);
+      attn_bwd_dkv_mfma_k<DH><<<dim3((unsigned)key_blocks, a.Hkv * a.batch, part ? (unsigned)slices : 1u), KV_THREADS, 0, st>>>(
+          q, k, v, d_o, lse2, a.delta, a.dk, a.dv, a.Hq, a.Hkv, a.q_start, a.q_len, a.scale, a.window, seqs, kb0, slices, part);
   }
   if (part) {
     const int first = kb0 * KV_TILE;
     const int64_t pairs = (int64_t)(a.q_start + a.q_len - first) * a.Hkv * (DH / 8);
-    attn_dkv_sum_k<DH><<<(unsigned)cdiv(2 * pairs, 256), 256, 0, st>>>(part, slices, pairs, first, a.Hkv, a.dk, a.dv, a.q_start, (bf16_t*)a.dkc, (bf16_t*)a.dvc,
+    attn_dkv_sum_k<DH><<<dim3((unsigned)cdiv(2 * pairs, 256), a.batch), 256, 0, st>>>(part, slices, pairs, first, a.Hkv, a.dk, a.dv, a.q_start, (bf16_t*)a.dkc, (bf16_t*)a.dvc,
                                                                        a.rope_k);
     if (first <= a.q_start) return hipGetLastError();
   }
   if (a.dkc) {      // (also where some of the chunk's own keys, all hidden, come before the first visible block)
     hipError_t e = hipGetLastError();
-    return e != hipSuccess ? e : kv_grad_finish(a.dt, a.dk + (int64_t)a.q_start * a.Hkv * DH, a.dv + (int64_t)a.q_start * a.Hkv * DH, a.rope_k, a.dkc, a.dvc, a.q_len, a.Hkv, DH, st);
+    const int64_t own = (int64_t)a.q_len * a.Hkv * DH, keys = own + (int64_t)a.q_start * a.Hkv * DH;      // elements of a sequence's rows of the chunk, of all its keys
+    for (int b = 0; b < a.batch && e == hipSuccess; ++b)
+      e = kv_grad_finish(a.dt, a.dk + b * keys + (keys - own), a.dv + b * keys + (keys - own), a.rope_k, (bf16_t*)a.dkc + b * own, (bf16_t*)a.dvc + b * own, a.q_len, a.Hkv,
+                         DH, st);
+    return e;
   }
   return hipGetLastError();
 }

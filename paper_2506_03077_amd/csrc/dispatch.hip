@@ -30,6 +30,7 @@ hipError_t attn_forward_mfma(const AttnArgs& a, hipStream_t st);
 hipError_t attn_backward_mfma(const AttnArgs& a, hipStream_t st);
 bool attn_mfma_eligible(int dt, int dh, int Hq, int Hkv);
 bool attn_mfma_aligned(const AttnArgs& a, bool backward);
+bool attn_sequences_fit(const AttnArgs& a);
 
 static std::atomic<bool> g_force_generic_gemm{false};
 static std::atomic<bool> g_force_generic_attn{false};
@@ -71,12 +72,13 @@ Scope::~Scope() {
 
 static double causal_pairs(const AttnArgs& a) {   // visible (query, key) pairs of the chunk, all query heads
   const double c = a.q_len, s = a.q_start;
-  if (a.window == 0 && a.kv_first == 0) return (double)a.Hq * (c * s + c * (c + 1.0) / 2.0);
+  if (a.window == 0 && a.kv_first == 0 && !a.kv_firsts) return (double)a.batch * a.Hq * (c * s + c * (c + 1.0) / 2.0);
   double pairs = 0.0;
-  for (int t = 0; t < a.q_len; ++t) {
-    const int p = a.q_start + t, lo = std::max(a.kv_first, a.window > 0 ? p - a.window + 1 : 0);
-    pairs += std::max(0, p - lo + 1);
-  }
+  for (int b = 0; b < a.batch; ++b)
+    for (int t = 0; t < a.q_len; ++t) {
+      const int p = a.q_start + t, lo = std::max(a.kv_firsts ? a.kv_firsts[b] : a.kv_first, a.window > 0 ? p - a.window + 1 : 0);
+      pairs += std::max(0, p - lo + 1);
+    }
   return (double)a.Hq * pairs;
 }
 
@@ -200,16 +202,18 @@ static hipError_t each_sequence(const AttnArgs& a, F f) {
   return hipSuccess;
 }
 hipError_t attn_forward(const AttnArgs& a, hipStream_t st) {
-  if (a.batch > 1) return each_sequence(a, [&](const AttnArgs& s) { return attn_forward(s, st); });
+  const bool mfma = attn_uses_mfma(a.dt, a.dh, a.Hq, a.Hkv) && attn_mfma_aligned(a, false);
+  if (a.batch > 1 && !(mfma && attn_sequences_fit(a))) return each_sequence(a, [&](const AttnArgs& s) { return attn_forward(s, st); });
   prof::Scope sc(prof::ATTN_FWD, 4.0 * a.dh * causal_pairs(a), false, st);
-  if (attn_uses_mfma(a.dt, a.dh, a.Hq, a.Hkv) && attn_mfma_aligned(a, false)) return attn_forward_mfma(a, st);
+  if (mfma) return attn_forward_mfma(a, st);
   if (a.dt == DT_BF16) ++g_generic_bf16_launches;
   return attn_forward_generic(a, st);
 }
 hipError_t attn_backward(const AttnArgs& a, hipStream_t st) {
-  if (a.batch > 1) return each_sequence(a, [&](const AttnArgs& s) { return attn_backward(s, st); });
+  const bool mfma = attn_uses_mfma(a.dt, a.dh, a.Hq, a.Hkv) && attn_mfma_aligned(a, true);
+  if (a.batch > 1 && !(mfma && attn_sequences_fit(a))) return each_sequence(a, [&](const AttnArgs& s) { return attn_backward(s, st); });
   prof::Scope sc(prof::ATTN_BWD, 10.0 * a.dh * causal_pairs(a), false, st);
-  if (attn_uses_mfma(a.dt, a.dh, a.Hq, a.Hkv) && attn_mfma_aligned(a, true)) return attn_backward_mfma(a, st);
+  if (mfma) return attn_backward_mfma(a, st);
   if (a.dt == DT_BF16) ++g_generic_bf16_launches;
   return attn_backward_generic(a, st);
 }

@@ -162,6 +162,8 @@ hipError_t embedding_fwd(int dt, const int32_t* ids, const void* emb, void* x, i
 hipError_t embedding_bwd(int dt, const int32_t* ids, const void* dx, float* demb, int64_t rows, int d, int vocab, hipStream_t st);
 
 // ---- chunk attention ----
+constexpr int ATTN_MAX_SEQS = 32;
+struct AttnSeqs { int n; int first[ATTN_MAX_SEQS]; };      // sequences of a launch, the first visible key of each
 struct AttnArgs {
   int dt;
   int Hq, Hkv, dh;
@@ -169,8 +171,8 @@ struct AttnArgs {
   float scale;
   int window = 0;          // > 0: a query at position t sees only keys t - window < u <= t
   int kv_first = 0;        // key positions before this one are padding: never visible
-  // Several sequences in one call: `batch` of q_len queries and keys each, one behind the other (q_start = 0; lse [batch, Hq, c], delta [batch, 2, Hq, c]),
-  // kv_firsts their kv_first on the host (or NULL: kv_first for all).
+  // Several sequences in one call, up to ATTN_MAX_SEQS: `batch` of q_len queries and keys each, one behind the other (q_start = 0; lse [batch, Hq, c],
+  // delta [batch, 2, Hq, c]), kv_firsts their kv_first on the host (or NULL: kv_first for all; else kv_first is the least of them).
   int batch = 1;
   const int32_t* kv_firsts = nullptr;
   const void *q, *k, *v;   // q [c,Hq,dh]; k,v [>=s+c,Hkv,dh]
@@ -212,12 +214,12 @@ inline int attn_first_key_block(const AttnArgs& a) {
   return (first_visible > 0 ? first_visible : 0) / ATTN_KV_TILE;
 }
 constexpr int ATTN_MAX_SLICES = 32;
-inline size_t attn_dkv_scratch_bytes(const AttnArgs& a, int slices) {      // [slice][dk | dv][key][kv head][dh] fp32, keys from the first visible block on
+inline size_t attn_dkv_scratch_bytes(const AttnArgs& a, int slices) {      // [sequence][slice][dk | dv][key][kv head][dh] fp32, keys from the first visible block on
   const int64_t keys = (int64_t)a.q_start + a.q_len - (int64_t)attn_first_key_block(a) * ATTN_KV_TILE;
-  return slices < 2 || keys <= 0 ? 0 : (size_t)(slices * 2 * keys * a.Hkv * a.dh) * sizeof(float);
+  return slices < 2 || keys <= 0 ? 0 : (size_t)(a.batch * slices * 2 * keys * a.Hkv * a.dh) * sizeof(float);
 }
 inline int attn_dkv_slices(const AttnArgs& a, size_t max_bytes) {
-  const int64_t blocks = (cdiv((int64_t)a.q_start + a.q_len, ATTN_KV_TILE) - attn_first_key_block(a)) * a.Hkv;
+  const int64_t blocks = (cdiv((int64_t)a.q_start + a.q_len, ATTN_KV_TILE) - attn_first_key_block(a)) * a.Hkv * a.batch;
   if (blocks <= 0) return 1;
   int64_t tiles = cdiv(a.q_len, ATTN_KV_QUERIES);
   if (a.window > 0 && tiles > cdiv((int64_t)a.window + ATTN_KV_TILE, ATTN_KV_QUERIES) + 1) tiles = cdiv((int64_t)a.window + ATTN_KV_TILE, ATTN_KV_QUERIES) + 1;
