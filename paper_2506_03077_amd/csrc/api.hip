@@ -823,18 +823,16 @@ int32_t streambp_lmhead_ce_backward(const sbp_head_cfg* c, const void* w, const 
   const int cm = (int)std::min<int64_t>(c->chunk, rows);
   const int d = c->hidden, V = c->vocab;
 
-  HIPCHK(count_active(targets, c->batch, c->seq_len, V, s.seq_weight, n_active, st));
-  if (c->objective == SBP_OBJ_DPO) HIPCHK(fill_zero(s.ell, sizeof(float), st));
   // Rows with an ignored target contribute nothing (dz = 0): only the active rows are pushed through the
   // GEMMs.  Positions are independent (Sec. 3.2.1), so the active rows of all sequences are chunked as one
   // flat list; the list and the per-chunk row counts live on the device (no host synchronisation), and the
   // kernels of a chunk read their row count at run time.
   // How many rows the products run on at once: one chunk, or as many chunks as make HEAD_SPAN_ROWS.  dz is kept for them anyway, and the buffer of the
   // fp32 logits has room for what else they need: the numerator form never holds logits (there it takes the statistics and the rows of h and dh of
-  // the whole span, and every product runs on the span), else they are dead when the span's last chunk is done (it takes dh, and that product
-  // alone runs on the span).  Small chunks are what this is for: the logits of 1024 rows at 7B widths are 2376 output tiles, a tenth round
+  // the whole span, and every product runs on the span), the logits of fp32 heads are formed where their dz will be (the same, without statistics),
+  // else they are dead when the span's last chunk is done (it takes dh, and that product alone runs on the span).  Small chunks are what this is for: the logits of 1024 rows at 7B widths are 2376 output tiles, a tenth round
   // of the CUs for 72 of them.  GRPO group of 8 x 1111 rows, chunk 1024, 18.8 -> 18.0 ms; fp32 layer and head of 256 rows, chunk 64 (five launches a
-  // chunk) 371 -> 335 us; two-layer stack of 1024 wide layers, vocabulary 50257, chunk 512, 3.36 -> 3.30 ms.
+  // chunk) 371 -> 335 us with dh alone, later 138 -> 108 with all products and fewer launches around them; two-layer stack of 1024 wide layers, vocabulary 50257, chunk 512, 3.36 -> 3.30 ms.
   // More rows than HEAD_SPAN_ROWS gain no more: all 16384 of a group at once, dh takes 26.0 instead of 26.9 ms per 32768 rows, the row
   // kernel, which finds less of dz in the caches, 4.2 instead of 3.65, and the whole call the same.
   const bool padded = dt == DT_BF16;      // bf16 rows of z and dz are padded to a multiple of 64, dz with zeros: the products with dz need no particular vocabulary
@@ -847,6 +845,7 @@ int32_t streambp_lmhead_ce_backward(const sbp_head_cfg* c, const void* w, const 
   };
   const bool numer = (fusion_mask() & FUSE_NUMERATORS) && dt == DT_BF16 && s.n_stat > 0 &&
                      gemm_numerators_supported(numerators(s.hc, s.dz, cm, s.chunk_rows, s.index, s.stats, s.target_logit));
+  const bool in_place = dt == SBP_F32, wide = numer || in_place;      // fp32 dz takes the place of the logits; wide: a unit may be a span
   void *hc = s.hc, *dhc = s.dhc;
   float2* stats = s.stats;
   float* target_logit = s.target_logit;
@@ -865,15 +864,22 @@ int32_t streambp_lmhead_ce_backward(const sbp_head_cfg* c, const void* w, const 
     if (carve(nullptr) <= (size_t)cm * s.ldz * sizeof(float)) carve(s.z);
     else { dhc = s.dhc; stats = s.stats; target_logit = s.target_logit; hc = s.hc; chunks = 1; }
   } else chunks = 1;
-  const int cu = chunks > 1 && numer ? span : cm;         // rows of a unit: what the logits are formed of at once
-  const int dh_units = chunks > 1 && !numer ? chunks : 1, per_group = numer ? s.dw_group / chunks : s.dw_group;      // units of a span of dh, of a weight-gradient group
+  const int cu = chunks > 1 && wide ? span : cm;          // rows of a unit: what the logits are formed of at once
+  const int dh_units = chunks > 1 && !wide ? chunks : 1, per_group = wide ? s.dw_group / chunks : s.dw_group;      // units of a span of dh, of a weight-gradient group
   const int64_t ldt = (int64_t)align_up((size_t)cu, 64);
   const bool gather_span = dh_units > 1 && !s.ht;         // all rows of a span fetched at once
   const int n_units = (int)cdiv(rows, (int64_t)cu);
   int32_t* unit_rows = s.chunk_rows;                      // [n_units], then all active rows, then the rows per span
   int32_t* span_rows = unit_rows + n_units + 1;
-  HIPCHK(compact_active(targets, rows, cu, V, s.index, unit_rows, n_units, span, span_rows, dh_units > 1 ? (int)cdiv(rows, (int64_t)span) : 0, st));
-  HIPCHK(fill_zero(dh, (size_t)rows * d * es, st));          // ignored rows of dh: exact zeros
+  {
+    HeadBegin b{};
+    b.targets = targets; b.B = c->batch; b.T = c->seq_len; b.V = V;
+    b.seq_weight = s.seq_weight; b.n_active = n_active; b.ell = c->objective == SBP_OBJ_DPO ? s.ell : nullptr;
+    b.index = s.index; b.unit_rows = unit_rows; b.unit = cu; b.n_units = n_units;
+    b.span_rows = span_rows; b.span = span; b.n_spans = dh_units > 1 ? (int)cdiv(rows, (int64_t)span) : 0;
+    b.dh = dh; b.dh_bytes = (size_t)rows * d * es;           // ignored rows of dh: exact zeros
+    HIPCHK(head_begin(b, st));
+  }
   GemmArgs pending[MAX_DW_GROUP];
   int n_pending = 0;
   // rows [first, first + n) of the list of active rows: at most n, the rest of them on the device
@@ -896,7 +902,7 @@ int32_t streambp_lmhead_ce_backward(const sbp_head_cfg* c, const void* w, const 
     // the chunk's dz buffer plus the target logits, and the row kernel finishes dz in place.
     GemmArgs gz = numerators(hcu, dz, n, n_dev, idx, stats, target_logit);
     if (!numer) {
-      gz = fwd_gemm(hcu, w, s.z, n, V, d, dt, DT_F32);
+      gz = fwd_gemm(hcu, w, in_place ? dz : s.z, n, V, d, dt, DT_F32);
       gz.ldc = s.ldz; gz.c_padded = padded;
       gz.rows_dev = n_dev;
       gz.row_stats = s.stats;
@@ -907,7 +913,7 @@ int32_t streambp_lmhead_ce_backward(const sbp_head_cfg* c, const void* w, const 
     HeadRowArgs a{};
     a.stats = has_stats ? stats : nullptr; a.n_stat = s.n_stat;
     a.target_logit = numer ? target_logit : nullptr;
-    a.dt = dt; a.objective = c->objective; a.z = s.z; a.dz = dz; a.ldz = s.ldz; a.targets = targets;
+    a.dt = dt; a.objective = c->objective; a.z = in_place ? (const float*)dz : s.z; a.dz = dz; a.ldz = s.ldz; a.targets = targets;
     a.old_logp = old_logp; a.ref_logp = ref_logp;
     a.advantages = advantages; a.seq_weight = s.seq_weight; a.row0 = 0; a.row_index = idx; a.rows_dev = n_dev;
     a.rows = n; a.V = V; a.T = c->seq_len;
@@ -929,11 +935,12 @@ int32_t streambp_lmhead_ce_backward(const sbp_head_cfg* c, const void* w, const 
       gh.rows_dev = span_dev;
       HIPCHK(gemm(gh, st));
     }
+    LossSum sum{};
     if (++n_pending == per_group || ci + 1 == n_units) {
       HIPCHK(gemm_batch(pending, n_pending, st));
       // the active rows of the group's chunks are one list: its loss terms are summed together
-      HIPCHK(reduce_add(s.row_loss, (int)(first + n - group_first), c->objective == SBP_OBJ_DPO ? s.ell : loss, st, unit_rows + n_units,
-                        (int)std::min<int64_t>(group_first, INT32_MAX)));
+      sum = LossSum{s.row_loss, (int)(first + n - group_first), c->objective == SBP_OBJ_DPO ? s.ell : loss, unit_rows + n_units,
+                    (int)std::min<int64_t>(group_first, INT32_MAX)};
       n_pending = 0;
     }
     // rows of dh out, the next rows of h in: independent of each other
@@ -942,7 +949,7 @@ int32_t streambp_lmhead_ce_backward(const sbp_head_cfg* c, const void* w, const 
     RowMove in{};
     if (!gather_span) in = moved(false, first + cu, cu, n_dev + 1, next);
     else if (span_done) in = moved(false, first + cu, span, span_dev + 1, next);
-    if (out.max_rows + in.max_rows > 0) HIPCHK(move_rows(dt, out, in, d, st));
+    HIPCHK(move_rows(dt, out, in, d, st, sum));
   }
   if (c->objective == SBP_OBJ_DPO)
     HIPCHK(dpo_finish(dt, s.ell, c->kl_beta, dh, rows * d, dw, c->grad_dtype, (int64_t)V * d, loss, st));

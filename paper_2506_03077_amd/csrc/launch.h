@@ -237,7 +237,7 @@ inline int attn_dkv_slices(const AttnArgs& a, size_t max_bytes) {
 struct HeadRowArgs {
   int dt;                   // type of dz
   int objective;            // 0 SFT, 1 GRPO, 2 DPO
-  const float* z;           // [rows, ldz] fp32 logits of the chunk (unused in the numerator form)
+  const float* z;           // [rows, ldz] fp32 logits (unused in the numerator form); fp32 dz may be the same buffer
   void* dz;                 // [rows, ldz] dt, columns V .. ldz become zeros; numerator form (target_logit != NULL): holds exp(z - block max) on entry
   int64_t ldz;
   const int32_t* targets;   // [rows] (already offset to the chunk)
@@ -257,19 +257,23 @@ struct HeadRowArgs {
   float* row_loss;          // [rows] scratch: per-row loss term (DPO: per-row signed log-ratio)
 };
 hipError_t head_rows(const HeadRowArgs& a, hipStream_t st);
-// out += sum(v[0..n)) in a fixed order; n_dev (optional): device-side count of the list that v[0] is entry `first` of
-hipError_t reduce_add(const float* v, int n, float* out, hipStream_t st, const int* n_dev = nullptr, int first = 0);
-// per-sequence active counts (0 <= target < V) -> seq_weight[j] = 1/(B*T_o,j) (0 if empty), n_active total - or minus the
-// number of targets >= V if there is any
-hipError_t count_active(const int32_t* targets, int B, int T, int V, float* seq_weight, int64_t* n_active, hipStream_t st);
-// index[0..n_active) = rows with 0 <= target < V in increasing order; chunk_rows[i] = clamp(n_active - i*chunk, 0, chunk) for i < n_chunks,
-// chunk_rows[n_chunks] = n_active; group_rows: the same for n_groups groups of `group` rows
-hipError_t compact_active(const int32_t* targets, int64_t rows, int chunk, int V, int32_t* index, int32_t* chunk_rows, int n_chunks,
-                          int group, int32_t* group_rows, int n_groups, hipStream_t st);
+// What a head call starts with.  Active rows: 0 <= target < V; seq_weight[j] = 1/(B*T_o,j) of the active rows T_o,j of sequence j (0 if there are none);
+// n_active: their total - or minus the number of targets >= V if there is any; index[0..n_active): the active rows in increasing order;
+// unit_rows[i] = clamp(n_active - i*unit, 0, unit) for i < n_units, unit_rows[n_units] = n_active; span_rows: the same for n_spans spans of `span` rows;
+// ell (or NULL) and dh_bytes of dh become zeros
+struct HeadBegin {
+  const int32_t* targets; int B, T, V;
+  float* seq_weight; int64_t* n_active; float* ell;
+  int32_t* index; int32_t* unit_rows; int unit, n_units; int32_t* span_rows; int span, n_spans;
+  void* dh; size_t dh_bytes;
+};
+hipError_t head_begin(const HeadBegin& a, hipStream_t st);
 // A gather, dst[r,:] = src[index[r],:] for r < *rows_dev, zero rows after, and a scatter, dst[index[r],:] = src[r,:] for r < *rows_dev, independent of
-// each other, in one launch; max_rows 0: none
+// each other, in one launch; max_rows 0: none.  With them out += sum(v[0..n)), n > 0, in a fixed order; n_dev: device-side count of the list that v[0]
+// is entry `first` of
 struct RowMove { const void* src; const int32_t* index; const int* rows_dev; void* dst; int max_rows; };
-hipError_t move_rows(int dt, const RowMove& scatter, const RowMove& gather, int d, hipStream_t st);
+struct LossSum { const float* v; int n; float* out; const int* n_dev; int first; };
+hipError_t move_rows(int dt, const RowMove& scatter, const RowMove& gather, int d, hipStream_t st, const LossSum& sum = LossSum{});
 // dst [C, ld] = src [R, C]^T (bf16, C % 8 == 0, 16-byte aligned); rows_dev: only the first *rows_dev rows count.  Columns from there to the next
 // multiple of 64 become zeros (ld reaches to R's next multiple of 64, % 8 == 0); those after it are not written.
 hipError_t transpose_rows(const void* src, const int32_t* rows_dev, int R, int C, void* dst, int64_t ld, hipStream_t st);

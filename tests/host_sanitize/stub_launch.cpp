@@ -177,15 +177,14 @@ hipError_t head_rows(const HeadRowArgs& a, hipStream_t) {
   if (a.rows_dev) rd(a.rows_dev, 4);
   return hipSuccess;
 }
-hipError_t reduce_add(const float* v, int n, float* out, hipStream_t, const int* n_dev, int) { rd(v, (size_t)n * 4); wr(out, 4); rd(n_dev, 4); return hipSuccess; }
-hipError_t count_active(const int32_t* targets, int B, int T, int, float* seq_weight, int64_t* n_active, hipStream_t) {
-  rd(targets, (size_t)B * T * 4); wr(seq_weight, (size_t)B * 4); wr(n_active, 8); return hipSuccess;
+hipError_t head_begin(const HeadBegin& a, hipStream_t) {
+  const size_t rows = (size_t)a.B * a.T;
+  rd(a.targets, rows * 4); wr(a.seq_weight, (size_t)a.B * 4); wr(a.n_active, 8); wr(a.ell, 4); wr(a.index, rows * 4); wr(a.unit_rows, (size_t)(a.n_units + 1) * 4);
+  if (a.n_spans) wr(a.span_rows, (size_t)a.n_spans * 4);
+  wr(a.dh, a.dh_bytes); return hipSuccess;
 }
-hipError_t compact_active(const int32_t* targets, int64_t rows, int, int, int32_t* index, int32_t* chunk_rows, int n_chunks, int, int32_t* group_rows, int n_groups, hipStream_t) {
-  rd(targets, rows * 4); wr(index, rows * 4); wr(chunk_rows, (size_t)(n_chunks + 1) * 4);
-  if (n_groups) wr(group_rows, (size_t)n_groups * 4); return hipSuccess;
-}
-hipError_t move_rows(int dt, const RowMove& scatter, const RowMove& gather, int d, hipStream_t) {
+hipError_t move_rows(int dt, const RowMove& scatter, const RowMove& gather, int d, hipStream_t, const LossSum& sum) {
+  if (sum.n > 0) { rd(sum.v, (size_t)sum.n * 4); wr(sum.out, 4); rd(sum.n_dev, 4); }
   if (scatter.max_rows > 0) { rd(scatter.src, (size_t)scatter.max_rows * d * es(dt)); rd(scatter.index, (size_t)scatter.max_rows * 4); rd(scatter.rows_dev, 4); }
   if (gather.max_rows > 0) { rd(gather.index, (size_t)gather.max_rows * 4); rd(gather.rows_dev, 4); wr(gather.dst, (size_t)gather.max_rows * d * es(dt)); }
   return hipSuccess;
