@@ -371,10 +371,9 @@ int32_t chunk_reforward(const sbp_layer_cfg* c, const sbp_layer_weights* w, cons
   const int d = c->hidden, F = c->mlp_width, qd = c->n_q_heads * c->head_dim, kd = c->n_kv_heads * c->head_dim;
   const int n = (int)pass_rows(p);
   HIPCHK(rmsnorm_fwd(dt, xc, nullptr, w->g1, s.a, nullptr, s.rstd1, n, d, c->rms_eps, st));
-  HIPCHK(gemm(fwd_gemm(s.a, w->wq, s.q, n, qd, d, dt, dt), st));
+  const GemmArgs qkv[3] = {fwd_gemm(s.a, w->wq, s.q, n, qd, d, dt, dt), fwd_gemm(s.a, w->wk, s.K, n, kd, d, dt, dt), fwd_gemm(s.a, w->wv, s.V, n, kd, d, dt, dt)};
+  HIPCHK(gemm_batch(qkv, p.whole ? 3 : 1, st));
   if (p.whole) {
-    const GemmArgs kv[2] = {fwd_gemm(s.a, w->wk, s.K, n, kd, d, dt, dt), fwd_gemm(s.a, w->wv, s.V, n, kd, d, dt, dt)};
-    HIPCHK(gemm_batch(kv, 2, st));
     HIPCHK(rope_apply(dt, s.K, s.rope, n, p.n, c->n_kv_heads, c->head_dim, false, st));
   }
   const AttnArgs aa = pass_attn(c, s, p);      // with RoPE(q) inside the kernel, which leaves s.q rotated
@@ -438,7 +437,7 @@ int32_t layer_backward_impl(const sbp_layer_cfg* c, const sbp_layer_weights* w, 
   const int T = c->seq_len, d = c->hidden, F = c->mlp_width;
   const int qd = c->n_q_heads * c->head_dim, kd = c->n_kv_heads * c->head_dim, half = c->head_dim / 2;
   const LayerPlan plan = s_all.plan;
-  HIPCHK(rope_table(s_all.rope, T, c->head_dim, c->rope_theta, c->pos_offset, st));
+  HIPCHK(rope_table(s_all.rope, T, c->head_dim, c->rope_theta, c->pos_offset, s_all.kv_grads.p, s_all.kv_grads.bytes, st));
   // Weight-gradient GEMMs waiting for their launch (a group of passes' worth).  A group may span sequences: short samples would
   // otherwise read and write every dW once each (four samples of 640 tokens at 7B widths: 2.3 of 8.8 ms).
   GemmArgs dws[7 * MAX_DW_GROUP];
@@ -448,7 +447,7 @@ int32_t layer_backward_impl(const sbp_layer_cfg* c, const sbp_layer_weights* w, 
   for (int b0 = 0; b0 < c->batch; b0 += plan.seqs) {
     const int n_chunks = (int)cdiv(T, plan.rows), seqs = std::min(plan.seqs, c->batch - b0);
     if (n_chunks > 1 && (rc = kv_prepass(c, w, pass_view(s_all, n_dws / 7), at(x, (size_t)b0 * T, d, es), st))) return rc;
-    HIPCHK(fill_zero(s_all.kv_grads.p, s_all.kv_grads.bytes, st));
+    if (b0 > 0) HIPCHK(fill_zero(s_all.kv_grads.p, s_all.kv_grads.bytes, st));      // (of the first: with the table)
     // Chunks run last to first: rows of dK/dV belonging to chunk i are final once
     // chunks >= i are done (later queries are the only other readers of those
     // keys), so the K/V-side gradient and dx of the chunk can be finished at once.
@@ -710,7 +709,7 @@ int32_t streambp_layer_forward(const sbp_layer_cfg* c, const sbp_layer_weights* 
   const int dt = c->dtype;
   const size_t es = dtype_size(dt);
   const int T = c->seq_len, d = c->hidden, F = c->mlp_width;
-  HIPCHK(rope_table(s.rope, T, c->head_dim, c->rope_theta, c->pos_offset, st));
+  HIPCHK(rope_table(s.rope, T, c->head_dim, c->rope_theta, c->pos_offset, nullptr, 0, st));
   for (int b0 = 0; b0 < c->batch; b0 += s.plan.seqs) {
     const int seqs = std::min(s.plan.seqs, c->batch - b0);
     const bool whole = s.plan.rows >= T;

@@ -18,7 +18,14 @@ namespace sbp {
 // Rotate-half pairing (j, j + dh/2), angle (t + pos_offset) * theta^(-2j/dh).
 // Angles go through fp64: an fp32 product pos*inv_freq has an absolute error of
 // ~2e-3 rad at position 32768, which the fp32 path's tolerance cannot absorb.
-__global__ void rope_table_k(float2* tab, int n_pos, int half, double theta, int pos_offset) {
+static inline unsigned ew_grid(int64_t n) { return (unsigned)std::min<int64_t>(cdiv(n, 256), 256 * 16); }
+// (the workgroups after the table's: zeros for what the call accumulates into, n16 pieces of 16 bytes)
+__global__ void rope_table_k(float2* tab, int n_pos, int half, double theta, int pos_offset, unsigned table_blocks, uint4* zeros, int64_t n16) {
+  if (blockIdx.x >= table_blocks) {
+    const int64_t stride = (int64_t)(gridDim.x - table_blocks) * blockDim.x;
+    for (int64_t i = (int64_t)(blockIdx.x - table_blocks) * blockDim.x + threadIdx.x; i < n16; i += stride) zeros[i] = make_uint4(0, 0, 0, 0);
+    return;
+  }
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= (int64_t)n_pos * half) return;
   int t = (int)(i / half), j = (int)(i % half);
@@ -29,11 +36,14 @@ __global__ void rope_table_k(float2* tab, int n_pos, int half, double theta, int
   tab[i] = make_float2((float)c, (float)s);
 }
 
-hipError_t rope_table(float2* tab, int n_pos, int dh, float theta, int pos_offset, hipStream_t st) {
-  int half = dh / 2;
-  int64_t n = (int64_t)n_pos * half;
-  if (n == 0) return hipSuccess;
-  rope_table_k<<<(unsigned)cdiv(n, 256), 256, 0, st>>>(tab, n_pos, half, (double)theta, pos_offset);
+hipError_t rope_table(float2* tab, int n_pos, int dh, float theta, int pos_offset, void* zeros, size_t zero_bytes, hipStream_t st) {
+  const int half = dh / 2;
+  const unsigned table = (unsigned)cdiv((int64_t)n_pos * half, 256);
+  if (((uintptr_t)zeros | zero_bytes) & 15) return hipErrorInvalidValue;      // (a region of the workspace)
+  const int64_t n16 = (int64_t)(zero_bytes / 16);
+  const unsigned fill = n16 > 0 ? ew_grid(n16) : 0;
+  if (table + fill == 0) return hipSuccess;
+  rope_table_k<<<table + fill, 256, 0, st>>>(tab, n_pos, half, (double)theta, pos_offset, table, (uint4*)zeros, n16);
   return hipGetLastError();
 }
 
@@ -426,7 +436,6 @@ __global__ void swiglu_bwd_bf16x8_k(bf16x8* __restrict__ gate, bf16x8* __restric
   }
 }
 
-static inline unsigned ew_grid(int64_t n) { return (unsigned)std::min<int64_t>(cdiv(n, 256), 256 * 16); }
 
 hipError_t swiglu_fwd(int dt, const void* gate, const void* up, void* act, int64_t n, hipStream_t st) {
   if (n == 0) return hipSuccess;

@@ -111,8 +111,8 @@ struct Scope {
 }  // namespace prof
 
 // ---- elementwise / row kernels (dt = storage type of the T-typed tensors) ----
-// cos/sin table [n_pos, dh/2] (float2), angles evaluated in fp64.
-hipError_t rope_table(float2* tab, int n_pos, int dh, float theta, int pos_offset, hipStream_t st);
+// cos/sin table [n_pos, dh/2] (float2), angles evaluated in fp64; in the same launch zeros (16-byte aligned, zero_bytes % 16 == 0) become zero.
+hipError_t rope_table(float2* tab, int n_pos, int dh, float theta, int pos_offset, void* zeros, size_t zero_bytes, hipStream_t st);
 // in-place rotation of x [rows, H, dh]; tab points at the row of position 0 of these rows, which starts again after `period` of them.
 hipError_t rope_apply(int dt, void* x, const float2* tab, int rows, int period, int H, int dh, bool inverse, hipStream_t st);
 // out = g * (x + add) * rstd ; sum_out = x + add (fp32, optional, may be add itself) ; rstd per row

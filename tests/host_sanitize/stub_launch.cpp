@@ -77,7 +77,9 @@ long long generic_bf16_launches() { return 0; }
 void note_generic_bf16_launch() {}
 namespace prof { Scope::Scope(int, double, bool, hipStream_t s) : st(s) {} Scope::~Scope() {} }
 
-hipError_t rope_table(float2* tab, int n_pos, int dh, float, int, hipStream_t) { wr(tab, (size_t)n_pos * (dh / 2) * sizeof(float2)); return hipSuccess; }
+hipError_t rope_table(float2* tab, int n_pos, int dh, float, int, void* zeros, size_t zero_bytes, hipStream_t) {
+  wr(tab, (size_t)n_pos * (dh / 2) * sizeof(float2)); wr(zeros, zero_bytes); return hipSuccess;
+}
 hipError_t rope_apply(int dt, void* x, const float2* tab, int rows, int period, int H, int dh, bool, hipStream_t) {
   wr(x, (size_t)rows * H * dh * es(dt)); rd(tab, (size_t)std::min(rows, period) * (dh / 2) * sizeof(float2)); return hipSuccess;
 }
