@@ -31,9 +31,9 @@ PEAK_HBM_GBS = 8000.0
 # other kernel or shape the field is null.
 TRAFFIC_RUNS = "profiles/bench_7b_layer_lmhead_32k_hbm_traffic.txt"
 MEASURED_TRAFFIC = {      # kernel symbol -> (bytes per launch, file under profiles/)
-    "gemm_mfma_k<false, false, 1>": (1.404e9, TRAFFIC_RUNS),
-    "gemm_mfma_k<false, true, 7>": (4.628e9, TRAFFIC_RUNS),
-    "gemm_mfma_seg_k": (42.24e9, TRAFFIC_RUNS),
+    "gemm_mfma_k<false, false, 1>": (2.089e9, TRAFFIC_RUNS),
+    "gemm_mfma_k<false, true, 7>": (4.668e9, TRAFFIC_RUNS),
+    "gemm_mfma_seg_k": (42.32e9, TRAFFIC_RUNS),
 }
 
 
