@@ -254,7 +254,7 @@ __device__ __forceinline__ void query_tile_of(int n_qt, int heads, int& qt, int&
 // ------------------------------------------------------------------ forward --
 // 8 waves in two groups of four; waves w and w + 4 share a SIMD.  A key tile costs a wave two slots, each closed by a barrier:
 // multiply (O += P V of the previous tile, S = K Q^T of this one: 68 MFMAs, the softmax denominator - at DH = 128 one product against
-// an all-ones operand - among them) and softmax (and the loads of later tiles, spread between the exponentials).  Group 1 runs one
+// an all-ones operand - among them; then the maxima of S) and softmax (and the loads of later tiles, spread between the exponentials).  Group 1 runs one
 // slot behind group 0, so on every SIMD one wave multiplies while the other does its exponentials.
 //   SPLIT = false: 256 queries, 32 per wave; all waves walk all key tiles, four K and four V stages (128 KB), loads two to three
 //                  tiles ahead.
@@ -265,6 +265,8 @@ __device__ __forceinline__ void query_tile_of(int n_qt, int heads, int& qt, int&
 // What bounds it: a slot takes about 1600 cycles at 2.0 GHz where the 68 MFMAs take 1088 - the vector instructions of one wave (about
 // 160, 32 of them exponentials) and the MFMAs of the other share the SIMD's issue port and delay each other; without the vector
 // work a slot takes 1050 cycles, without the MFMAs 1150.  Last 2048-query chunk of 32k, 28 heads: 1110 -> 957 us.
+// The masks and the rows' maxima close the multiply slot, which is the shorter one where few workgroups leave the clock high: 128 queries behind 4096 keys,
+// 28 heads, 69.1 -> 64.9 us, 1024 from the first on 23.8 -> 22.6, 16 heads of 64 23.3 -> 21.5; the same where the chip is full.
 // Tried with a maximum that lags by up to 2^8, itself 921 us but another rounding of every probability: 32x32x16 MFMAs in the same
 // schedule 965, loads in the multiply slot 954, the next slot's first fragments read early 958.
 template <int DH, bool SPLIT>
@@ -444,7 +446,7 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  auto softmax = [&](int i, int slot) __attribute__((always_inline)) {
+  auto row_max = [&](int i, float (&mx)[2]) __attribute__((always_inline)) {      // masks, and the maxima of the raw scores (scale > 0 keeps the order)
     const int k0 = tile_of(i) * TK;
     if (k0 + TK - 1 > wave_first_qpos || k0 < wave_lo_max) {   // only tiles on an edge of the visible range pay for the mask
 #pragma unroll
@@ -461,7 +463,6 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
         }
       }
     }
-    float mx[2];                                            // max of the raw scores (scale > 0 keeps the order)
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
       float m2[2];
@@ -475,6 +476,8 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
     }
 #pragma unroll
     for (int b = 0; b < 2; ++b) mx[b] = max_over_quads(mx[b]);
+  };
+  auto softmax = [&](int i, int slot, float (&mx)[2]) __attribute__((always_inline)) {
     if constexpr (SPLIT) {
 #pragma unroll
       for (int b = 0; b < 2; ++b) mx[b] = max_raw(mx[b], sM[grp ^ 1][wave & 3][b * 16 + li]);
@@ -532,14 +535,19 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
     auto step = [&](int i, int slot) __attribute__((always_inline)) {      // slot = i % 4, a constant: every stage is an immediate offset
       __builtin_amdgcn_s_setprio(1);
       if (active(i - 1)) pv(slot + 3);
-      if (active(i)) qk(slot);
+      float mx[2];
+      if (active(i)) {
+        qk(slot);
+        __builtin_amdgcn_s_setprio(0);
+        row_max(i, mx);
+      }
       __builtin_amdgcn_s_setprio(0);
       // Before a tile is read every wave has waited for its own share of it and a barrier has passed: V(i), K(i + 1) by group 0 in
       // its softmax slot, by group 1, one slot behind, at the end of this one (the two later pairs of tiles issued by
       // then stay in flight, one for group 1 and if SPLIT).
       if (!SPLIT && grp == 1) AT_WAIT_VM(PIECES * (V_AHEAD - 1));
       AT_SLOT_BARRIER();
-      if (active(i)) softmax(i, slot);
+      if (active(i)) softmax(i, slot, mx);
       else {
 #pragma unroll
         for (int p = 0; p < PIECES; ++p) issue_piece(p, i, slot);
