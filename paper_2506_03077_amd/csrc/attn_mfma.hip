@@ -242,13 +242,26 @@ __device__ __forceinline__ float max_over_quads(float x) {
     asm volatile("s_barrier" ::: "memory");   \
     __builtin_amdgcn_sched_barrier(0);        \
   } while (0)
-// Workgroup -> (query tile, head of a sequence).  The workgroups of an XCD get a contiguous run of (head, query tile) pairs, so that the heads of one
-// K/V group run on one XCD and share its stream through that L2; the tiles with the most keys come first.
-__device__ __forceinline__ void query_tile_of(int n_qt, int heads, int& qt, int& h) {
-  const int id = (int)blockIdx.x, n = n_qt * heads, x = id % 8, q = n / 8, r = n % 8;
-  const int c = x * q + min(x, r) + id / 8;
-  h = c / n_qt;
-  qt = n_qt - 1 - c % n_qt;
+// Workgroup `id` -> (query tile, head of a sequence).  An XCD gets a contiguous run of (head, tile) pairs, so that the heads of one K/V group run on one XCD
+// and share its stream through that L2, and walks them tile by tile, all of its heads side by side, the tiles with the most keys first: the heads
+// of a group are then in step, and what comes last is short.  Forward and dQ of more than a round, against head after head and tile after tile over all heads:
+// 32k layer at 7B widths 68.7 -> 67.8 ms, 8192 tokens, 32 / 8 heads, 11.01 -> 10.92.
+__device__ __forceinline__ void query_tile_of(int id, int n_qt, int heads, int& qt, int& h) {
+  const int n = n_qt * heads, x = id % 8, q = n / 8, r = n % 8, first = x * q + min(x, r), last = first + q + (x < r ? 1 : 0) - 1;
+  if (n <= 256) {      // one round: no order
+    const int c = first + id / 8;
+    h = c / n_qt;
+    qt = n_qt - 1 - c % n_qt;
+    return;
+  }
+  const int h0 = first / n_qt, row0 = first % n_qt, h1 = last / n_qt, row1 = last % n_qt;      // the run: from row row0 of head h0 to row row1 of head h1
+  int k = id / 8, row = 0;
+  for (;; ++row) {
+    const int from = h0 + (row < row0 ? 1 : 0), heads_in = h1 - (row > row1 ? 1 : 0) - from + 1;
+    if (k < heads_in) { h = from + k; break; }
+    k -= heads_in;
+  }
+  qt = n_qt - 1 - row;
 }
 
 // ------------------------------------------------------------------ forward --
@@ -282,7 +295,7 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
   constexpr int LOADERS = SPLIT ? AT_THREADS / 2 : AT_THREADS, LOADS = 8 * DH / LOADERS;   // threads that load a tile, 16-byte loads of each
 
   int qt, bh;
-  query_tile_of((c + QW - 1) / QW, Hq * seqs.n, qt, bh);
+  query_tile_of(blockIdx.x, (c + QW - 1) / QW, Hq * seqs.n, qt, bh);
   const int b = bh / Hq, h = bh - b * Hq, kv_first = seqs.first[b];
   q += (int64_t)b * c * Hq * DH; o += (int64_t)b * c * Hq * DH; lse += (int64_t)b * c * Hq;
   k += (int64_t)b * c * Hkv * DH; v += (int64_t)b * c * Hkv * DH;
@@ -884,9 +897,11 @@ __global__ __launch_bounds__(AT_THREADS) void attn_bwd_dq_mfma_k(const bf16_t* _
                                                                     const float* __restrict__ lse, const float* __restrict__ delta,
                                                                     bf16_t* __restrict__ dq, int Hq, int Hkv, int q_start, int c,
                                                                     float scale, const float2* __restrict__ rope, int window,
-                                                                    const AttnSeqs seqs) {
+                                                                    const AttnSeqs seqs, int q_blocks) {
   __shared__ __attribute__((aligned(1024))) DqShared<DH, SPLIT> sh;
-  dq_tile<DH, SPLIT>(sh, blockIdx.x, blockIdx.y, q, k, v, d_o, lse, delta, dq, Hq, Hkv, q_start, c, scale, rope, window, seqs);
+  int qt = blockIdx.x % q_blocks, bh = blockIdx.x / q_blocks;
+  if ((int)gridDim.x > 256) query_tile_of(blockIdx.x, q_blocks, Hq * seqs.n, qt, bh);
+  dq_tile<DH, SPLIT>(sh, qt, bh, q, k, v, d_o, lse, delta, dq, Hq, Hkv, q_start, c, scale, rope, window, seqs);
 }
 
 // -------------------------------------------------------------------- dK/dV --
@@ -1236,9 +1251,10 @@ __device__ __forceinline__ void bwd_block(const bf16_t* __restrict__ q, const bf
     dkv_block<DH, IN_TURN>(sh.dkv, b % key_blocks, r % kv_heads, r / kv_heads, q, k, v, d_o, lse2, delta, dk, dv, Hq, Hkv, q_start, c, scale, window, seqs,
                            key_block0, slices, part);
   } else {
-    // the tiles with the most keys first
     const int i = b - n_dkv;
-    dq_tile<DH, SPLIT>(sh.dq, q_blocks - 1 - i / heads, i % heads, q, k, v, d_o, lse, delta, dq, Hq, Hkv, q_start, c, scale, rope, window, seqs);
+    int qt = q_blocks - 1 - i / heads, bh = i % heads;      // less than a round: the tiles with the most keys first
+    if (q_blocks * heads > 256) query_tile_of(i, q_blocks, heads, qt, bh);
+    dq_tile<DH, SPLIT>(sh.dq, qt, bh, q, k, v, d_o, lse, delta, dq, Hq, Hkv, q_start, c, scale, rope, window, seqs);
   }
 }
 #define BWD_PARAMS const bf16_t *__restrict__ q, const bf16_t *__restrict__ k, const bf16_t *__restrict__ v, const bf16_t *__restrict__ d_o, \
@@ -1388,8 +1404,8 @@ static hipError_t backward_dh(const AttnArgs& a, hipStream_t st) {
     else launch(attn_bwd_mfma_k<DH, false>);
   } else {
     auto launch_dq = [&](auto kernel) {
-      kernel<<<dim3((unsigned)q_blocks, a.Hq * a.batch), AT_THREADS, 0, st>>>(q, k, v, d_o, a.lse, a.delta, (bf16_t*)a.dq, a.Hq, a.Hkv, a.q_start, a.q_len, a.scale,
-                                                                    a.rope_q, a.window, seqs);
+      kernel<<<(unsigned)q_tiles, AT_THREADS, 0, st>>>(q, k, v, d_o, a.lse, a.delta, (bf16_t*)a.dq, a.Hq, a.Hkv, a.q_start, a.q_len, a.scale,
+                                                                    a.rope_q, a.window, seqs, (int)q_blocks);
     };
     if (halves) launch_dq(attn_bwd_dq_mfma_k<DH, true>);
     else launch_dq(attn_bwd_dq_mfma_k<DH, false>);
