@@ -227,8 +227,13 @@ LayerWs carve_layer(const sbp_layer_cfg* c, void* ws, const LayerPlan& plan, boo
 // its launches, two readings of the weights and the products of its rows, rounded up to tiles; a weight-gradient launch a reading and a
 // writing of the gradients.  `products`: multiples of 2 flops per weight and row.
 //
+// bf16 gradients are rounded once per weight-gradient launch (per pass where a launch cannot take several), so no plan makes more launches than groups of
+// dw_group_rows rows, chunk by chunk, would, nor more passes than there are chunks.  Error of dW_gate against fp64 and time, chunk by chunk / with more launches where
+// that is faster / with this bound: 8192 tokens at 4096 / 14336, chunk 1024, 4.529e-3 12.2 ms / 4.679e-3 10.9 / 4.529e-3 11.6; 32768 at 2048 / 5632, chunk 1024,
+// 4.688e-3 39.3 / 5.240e-3 27.8 / 4.689e-3 29.1; 4 x 500 at 2048 / 5632, chunk 128, 4.450e-3 / 4.748e-3 / 4.450e-3.
+//
 // Measured, chunk by chunk as the config says / in planned passes of the same bytes: four sequences of 640 tokens at 7B widths, chunk 512, eight passes / one
-// 5.47 -> 3.63 ms; 8192 tokens at 4096 / 14336, chunk 1024, eight / two 11.92 -> 10.98; 32768 at 7B widths, chunk 2048, sixteen / eight 70.9 -> 69.9; a
+// 5.47 -> 3.63 ms; 8192 tokens at 4096 / 14336, chunk 1024, bf16 gradients, eight / four 12.2 -> 11.6; 32768 at 7B widths, chunk 2048, sixteen / eight 70.9 -> 69.9; a
 // 1024-wide stack of two layers, 2 x 1023 tokens, chunk 512, 3.27 -> 2.65.  SPAN_ROWS: 8192 rows a pass are slower again (8192 tokens at
 // 4096 / 14336 11.85 ms, 32768 at 7B widths 71.7): the MLP's tensors, 230 to 310 MB each, no longer stay in the 256 MB cache from one product to the next.
 constexpr int SPAN_ROWS = 4096;
@@ -248,7 +253,10 @@ LayerPlan plan_layer(const sbp_layer_cfg* c, int max_sets, double products, bool
     }
     return lo;
   };
-  LayerPlan best{1, cm, 1};
+  const bool rounds = dw && c->grad_dtype == SBP_BF16;
+  const int group = dw ? dw_group_for((size_t)cm, c->dw_group_rows, DW_GROUP_ROWS_LAYER) : 1;
+  const int64_t most_passes = c->batch * cdiv(T, cm), most_launches = cdiv(most_passes, group);      // of a plan that `rounds`
+  LayerPlan best{1, cm, group};      // (chunk by chunk: what the bytes are made for)
   double best_us = -1.0;
   for (int sets = 1; sets <= max_sets; ++sets) {
     const int seqs = T > rows_max ? 0 : largest(std::min(std::min(c->batch, SPAN_SEQS), rows_max / T), [&](int n) { return fits(LayerPlan{n, T, sets}); });
@@ -270,6 +278,7 @@ LayerPlan plan_layer(const sbp_layer_cfg* c, int max_sets, double products, bool
         passes *= c->batch;
       }
       if (sets > 1 && sets > passes) continue;
+      if (rounds && (passes > most_passes || cdiv(passes, sets) > most_launches)) continue;
       const double us = (double)passes * pass_us + (double)(tiles * grain) * row_us + (double)cdiv(passes, sets) * dw_us;
       if (best_us < 0.0 || us < best_us) { best = p; best_us = us; }
     }

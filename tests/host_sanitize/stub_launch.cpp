@@ -8,8 +8,13 @@
 #include <algorithm>
 #include <atomic>
 #include <cstdio>
+#include <functional>
 
 namespace sbp {
+
+// what a driver wants to see of the calls (plans.cpp): attention calls (backward or not), and the problems of a launch
+std::function<void(const AttnArgs&, bool)> stub_on_attn;
+std::function<void(const GemmArgs*, int)> stub_on_gemm_batch;
 
 static std::atomic<long long> g_touches{0};
 long long stub_touches() { return g_touches.load(); }
@@ -66,7 +71,11 @@ size_t gemm_scratch_bytes(int max_m, int max_n) {     // at most one partial til
   return (size_t)std::min<int64_t>(256, cdiv(max_m, 256) * cdiv(max_n, 256) * 27) * std::min(max_m, 256) * 256 * sizeof(float);
 }
 hipError_t gemm(const GemmArgs& g, hipStream_t) { touch_gemm(g); return hipSuccess; }
-hipError_t gemm_batch(const GemmArgs* gs, int n, hipStream_t, bool) { for (int i = 0; i < n; ++i) touch_gemm(gs[i]); return hipSuccess; }
+hipError_t gemm_batch(const GemmArgs* gs, int n, hipStream_t, bool) {
+  if (stub_on_gemm_batch) stub_on_gemm_batch(gs, n);
+  for (int i = 0; i < n; ++i) touch_gemm(gs[i]);
+  return hipSuccess;
+}
 hipError_t gemm_sum(const GemmArgs* gs, int n, hipStream_t) { for (int i = 0; i < n; ++i) touch_gemm(gs[i]); return hipSuccess; }
 bool gemm_uses_mfma(const GemmArgs& g) { return g.in_dt == DT_BF16; }
 void gemm_set_force_generic(bool) {}
@@ -151,6 +160,7 @@ hipError_t embedding_bwd(int dt, const int32_t* ids, const void* dx, float* demb
 }
 
 static void touch_attn(const AttnArgs& a, bool bwd) {
+  if (stub_on_attn) stub_on_attn(a, bwd);
   const size_t nb = a.batch, qn = nb * a.q_len * a.Hq * a.dh, kn = nb * (a.q_start + a.q_len) * a.Hkv * a.dh;
   if (a.rope_q && !bwd) wr((void*)a.q, qn * es(a.dt)); else rd(a.q, qn * es(a.dt));
   rd(a.k, kn * es(a.dt)); rd(a.v, kn * es(a.dt));
