@@ -381,13 +381,11 @@ int32_t chunk_reforward(const sbp_layer_cfg* c, const sbp_layer_weights* w, cons
   const int n = (int)pass_rows(p);
   HIPCHK(rmsnorm_fwd(dt, xc, nullptr, w->g1, s.a, nullptr, s.rstd1, n, d, c->rms_eps, st));
   const GemmArgs qkv[3] = {fwd_gemm(s.a, w->wq, s.q, n, qd, d, dt, dt), fwd_gemm(s.a, w->wk, s.K, n, kd, d, dt, dt), fwd_gemm(s.a, w->wv, s.V, n, kd, d, dt, dt)};
-  // q with K and V in one launch: fp32, where the launches are what a call costs, and from 1024 rows on (with the zeros of dK/dV in the table's launch: 7B layer of
-  // 2560 rows 3330 -> 3279 us, 1024-wide stack of 2046 rows 2109 -> 2084).  bf16 layers of fewer rows keep the two launches that
-  // their count of launches on the kernels for few tiles is pinned to.
-  const bool with_kv = p.whole && (dt == DT_F32 || n >= 1024);
-  HIPCHK(gemm_batch(qkv, with_kv ? 3 : 1, st));
+  // q with K and V in one launch, as a grouped one or on the kernels for few tiles.  Whole layer, q apart / in one: 64 rows at 7B widths 923 -> 895 us
+  // (forward 213 -> 192), 300 rows 1181 -> 1167 (320 -> 303), 640 at 4096 / 14336 1448 -> 1428 (412 -> 385), 1023 at 2048 / 5632 581 -> 574
+  // (175 -> 167), 1023 at 1024 / 2816 283 -> 278 (104 -> 100), 2560 at 7B widths 3330 -> 3279; 900 rows at 4096 / 14336 and 7B widths the same.
+  HIPCHK(gemm_batch(qkv, p.whole ? 3 : 1, st));
   if (p.whole) {
-    if (!with_kv) HIPCHK(gemm_batch(qkv + 1, 2, st));
     HIPCHK(rope_apply(dt, s.K, s.rope, n, p.n, c->n_kv_heads, c->head_dim, false, st));
   }
   const AttnArgs aa = pass_attn(c, s, p);      // with RoPE(q) inside the kernel, which leaves s.q rotated

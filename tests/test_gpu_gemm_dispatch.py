@@ -21,8 +21,8 @@ def test_both_operands_transposed_add_to_what_is_there(M, N, K, grad):
     _check(C, want + start.double().cpu(), K)
 
 
-# one chunk: K with V, q, o, gate with up, dact, dm (two operand pairs), do, da (three segments)
-@pytest.mark.parametrize("cfg,T,few", [(MID16, 640, 8), (dict(MID16, hidden=1024, head_dim=128, mlp_width=1408), 300, 8)])
+# one pass: q, K and V in one launch, o, gate with up, dact, dm (two operand pairs), do, da (three segments)
+@pytest.mark.parametrize("cfg,T,few", [(MID16, 640, 7), (dict(MID16, hidden=1024, head_dim=128, mlp_width=1408), 300, 7)])
 def test_a_layer_of_few_tiles_runs_on_their_kernels(cfg, T, few):
     sb.debug_profile_begin()
     try:
