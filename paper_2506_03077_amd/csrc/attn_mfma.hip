@@ -809,12 +809,24 @@ __device__ __forceinline__ void dq_tile(DqShared<DH, SPLIT>& sh, int q_block, in
       AT_WAIT_VM(PAIR * (AHEAD - 1));
       AT_SLOT_BARRIER();
       if (G1) AT_SLOT_BARRIER();
-      Operand ds;                // of the previous tile
-      bool held = false;         // there is one
+      // What a skipped tile leaves in ds: any value, read by nothing (`held`).  Keeping the last one instead takes more registers than there are (14 spilled);
+      // zeros are instructions.
+      auto any_operand = []() __attribute__((always_inline)) {
+        Operand x;
+#pragma unroll
+        for (int t = 0; t < TERMS<DH>; ++t)
+#pragma unroll
+          for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) x.w[t][b][ks] = __builtin_nondeterministic_value(bf16x8{});
+        return x;
+      };
+      Operand ds = any_operand();      // of the previous tile
+      bool held = false;               // there is one
       auto step = [&](int i, int stage) __attribute__((always_inline)) {      // stage = i % 4, a constant
         const bool act = active(i);
-        Scores x;                // (without a value where the tile is skipped: nothing is kept alive for it)
-        Operand next;
+        Scores x;                // (used where the tile is not skipped)
+        Operand next = any_operand();
         __builtin_amdgcn_s_setprio(1);
         if (held) second(ds, (stage + 3) % STAGES);
         if (act) first(x, stage);
