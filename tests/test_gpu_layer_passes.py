@@ -1,5 +1,6 @@
 """How a layer call deals its rows to passes: several sequences at once with a last pass of fewer, a sequence in uneven parts, groups of passes that
-share a weight-gradient launch - backward and forward against the fp64 oracle, with and without front padding and a window."""
+share a weight-gradient launch - backward and forward against the fp64 oracle, with and without front padding and a window.  That the calls are
+dealt so test_layer_plans.py reads off the host layer."""
 import numpy as np
 import pytest
 import torch
@@ -9,22 +10,11 @@ from paper_2506_03077_amd import binding as sb
 from paper_2506_03077_amd import synth
 
 from gpu_util import TOL, assert_close, dev, host, lib_layer_cfg, oracle_cfg
+from layer_plan_cases import PASSES
 
 pytestmark = pytest.mark.gpu
 
-MID16 = dict(dtype="bf16", hidden=256, n_q_heads=4, n_kv_heads=2, head_dim=128, mlp_width=512)
-NARROW = dict(dtype="bf16", hidden=256, n_q_heads=4, n_kv_heads=2, head_dim=64, mlp_width=64)      # an MLP that has no room for the rows of the K/V pass
-TINY = synth.CONFIGS["tiny"]
-
-
-@pytest.mark.parametrize("cfg,B,T,chunk,group,window,first", [
-    (MID16, 5, 130, 64, 0, 0, [0, 129, 7, 130, 64]),    # two sequences, two, one
-    (MID16, 7, 100, 100, 250, 0, None),                 # one sequence a pass, two passes a weight-gradient launch, forward two a pass
-    (MID16, 2, 333, 64, 1, 50, [0, 70]),                # four parts of a sequence
-    (NARROW, 3, 257, 64, 1, 0, None),
-    (TINY, 5, 50, 40, 0, 16, [3, 0, 50, 49, 1]),        # three sequences, two
-    (TINY, 2, 200, 40, 1, 0, None),
-])
+@pytest.mark.parametrize("cfg,B,T,chunk,group,window,first", [c[:7] for c in PASSES])
 def test_passes_of_a_layer_vs_oracle(cfg, B, T, chunk, group, window, first):
     cfg, dt = dict(cfg, window=window), cfg["dtype"]
     inp = synth.layer_inputs(cfg, seed=11, seq_len=T, batch=B)

@@ -2,10 +2,13 @@
 import itertools
 import json
 import os
+import re
 import shutil
 import subprocess
 
 import pytest
+
+from layer_plan_cases import PASSES, SEQUENCES
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SRC = os.path.join(ROOT, "tests", "host_sanitize")
@@ -69,3 +72,23 @@ def test_every_row_is_in_one_pass(plans, grad):
         for calls in (got["backward"], got["forward"]):
             assert sum(n * q for n, _, q, _, _ in calls) == c["B"] * c["T"], (c, calls)
             assert all(n == 1 or (s == 0 and q == c["T"] and n <= 32) for n, s, q, _, _ in calls), (c, calls)
+
+
+def test_calls_that_share_attention_launches_are_dealt_as_their_tests_say(plans):
+    """... and their sizes pick the kernels that the tests name: one launch for dQ and dK/dV up to MERGED_MAX workgroups, either query tile counted."""
+    with open(os.path.join(CSRC, "attn_mfma.hip")) as f:
+        merged_max = int(re.search(r"MERGED_MAX = (\d+);", f.read()).group(1))
+    for c, got in zip(SEQUENCES, plans([dict(c["cfg"], B=c["B"], T=c["T"], chunk=c["T"], first=c["first"]) for c in SEQUENCES])):
+        assert [a[:3] for a in got["backward"]] == [[n, 0, c["T"]] for n in c["passes"]] and {a[3] for a in got["backward"]} == {c["slices"]}, (c, got)
+        assert all(side_by_side == int(c["slices"] > 1) for *_, side_by_side in got["backward"]), (c, got)
+        n, T = max(c["passes"]), c["T"]
+        tiles = [-(-T // q) * c["cfg"]["n_q_heads"] * n for q in (256, 128)]
+        hidden = min(c["first"]) // 128 if c["first"] else 0
+        dkv = (-(-T // 128) - hidden) * c["cfg"]["n_kv_heads"] * n * c["slices"]
+        assert dkv + min(tiles) > merged_max if c["separate"] else dkv + max(tiles) <= merged_max, (c, dkv, tiles)
+
+
+def test_passes_of_a_layer_are_dealt_as_their_test_says(plans):
+    configs = [dict(cfg, B=B, T=T, chunk=chunk, group=group, window=window, first=first) for cfg, B, T, chunk, group, window, first, _, _ in PASSES]
+    for (*_, dw, forward), got in zip(PASSES, plans(configs)):
+        assert got["dw"] == dw and [a[:3] for a in got["forward"]] == forward, got
