@@ -646,7 +646,9 @@ static bool shared_schedule(int tiles, int k_steps, int scratch_tiles, SharedTai
   sh.parts = std::min(sh.helpers / sh.last, SHARED_PARTS);
   sh.rest = (int)((k_steps - 5) / (2.0 + 1.0 / sh.parts));
   sh.main = k_steps - sh.rest;
-  return sh.rest >= 32 && sh.rest - 3.5 - 0.09 * (shared_pieces(sh) + tail) > 0.0;
+  if (sh.rest < 32) return false;
+  sh.parts = (int)cdiv(sh.rest, cdiv(sh.rest, sh.parts));      // as many as pieces of that length make: none without a step (33 steps: seven of five, not eight)
+  return sh.rest - 3.5 - 0.09 * (shared_pieces(sh) + tail) > 0.0;
 }
 // Workgroup -> (tile, split); false: nothing to do
 __device__ __forceinline__ bool scheduled_tile(const Schedule& sc, int block, bool interleaved, int& tile, int& split) {

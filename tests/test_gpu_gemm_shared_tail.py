@@ -33,6 +33,25 @@ def test_shared_tail(M, N, K, layout, pair):
     assert torch.equal(got[0], got[1])
 
 
+# 129 tiles, two of them cut up; steps of their rest: 33, 42 and 49 do not make eight pieces of equal length, 35 in two operand pairs, 48 does
+@pytest.mark.parametrize("steps,pair,pieces", [(76, False, 7), (95, False, 7), (110, False, 7), (80, True, 7), (107, False, 8)])
+def test_no_piece_is_without_a_step(steps, pair, pieces):
+    """A piece that starts behind the last step would write a tile of zeros, which the sum then adds."""
+    M, N, K = 700, 11008, 64 * steps // (2 if pair else 1)
+    gen = torch.Generator(device="cuda").manual_seed(steps)
+    r = lambda *s: torch.randn(s, generator=gen, device="cuda").bfloat16()
+    ops = [(r(M, K), r(N, K)) for _ in range(2 if pair else 1)]
+    want = sum(a.double() @ b.double().t() for a, b in ops)
+    scratch, C = torch.full((64 << 20,), 0xFF, dtype=torch.uint8, device="cuda"), torch.full((M, N), float("nan"), device="cuda")
+    more = dict(A2=ops[1][0], B2=ops[1][1]) if pair else {}
+    assert sb.debug_gemm(ops[0][0], ops[0][1], C, M, N, K, False, True, scratch=scratch, **more) == 1
+    slots = scratch.view(torch.int32).view(256, -1)
+    written = (slots != -1).any(dim=1)
+    assert int(written.sum()) == 127 + 2 * pieces and bool((slots[written] != 0).any(dim=1).all())
+    terms = 64 * steps
+    assert float((C.double() - want).abs().max()) <= terms * 2.0 ** -23 * terms ** 0.5
+
+
 def test_other_tails_are_not_shared():
     """128 tiles split evenly, 161 and more are left whole."""
     for tiles_m, tiles_n in ((8, 16), (7, 23)):
