@@ -1,5 +1,5 @@
 """Layer calls of the tests of passes, and how their rows are dealt: test_layer_plans.py reads the passes off the host layer on the CPU,
-test_gpu_attn_sequences.py and test_gpu_layer_passes.py run them."""
+test_gpu_attn_sequences.py, test_gpu_attn_tile_order.py and test_gpu_layer_passes.py run them."""
 from paper_2506_03077_amd import synth
 
 
@@ -17,10 +17,13 @@ SEQUENCES = [
     _seq(4, 4, 64, 5, 130, [0, 1, 2, 64, 129], [5], 1, window=33),
     _seq(4, 2, 128, 33, 20, list(range(20)) + [0] * 13, [4] * 8 + [1], 1),
     _seq(32, 8, 64, 32, 128, None, [4] * 8, 4),                    # many heads, still one launch of the backward
+    _seq(20, 4, 64, 7, 260, [0, 3, 0, 130, 259, 1, 64], [4, 3], 5),
     _seq(32, 16, 64, 3, 1300, [0, 130, 1299], [3], 1, True),
     _seq(32, 16, 128, 3, 1300, [0, 130, 1299], [3], 1, True),
     _seq(32, 2, 64, 3, 1300, None, [3], 7, True),                  # ... and sums of parts
 ]
+# 90 heads of all sequences, which do not divide among eight XCDs; more query tiles than a round of 256 workgroups, of 256 queries or of 128
+MORE_THAN_A_ROUND = _seq(30, 6, 64, 3, 520, [0, 130, 519], [3], 2)
 
 _MID = dict(dtype="bf16", hidden=256, n_q_heads=4, n_kv_heads=2, head_dim=128, mlp_width=512)
 _NARROW = dict(dtype="bf16", hidden=256, n_q_heads=4, n_kv_heads=2, head_dim=64, mlp_width=64)      # an MLP that has no room for the rows of the K/V pass

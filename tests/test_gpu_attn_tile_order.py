@@ -2,7 +2,8 @@
 sequences, against the fp64 oracle."""
 import pytest
 
-from test_gpu_attn_sequences import _cfg, test_sequences_share_the_attention_launches as sequences
+from layer_plan_cases import MORE_THAN_A_ROUND
+from test_gpu_attn_sequences import test_sequences_share_the_attention_launches as sequences
 from test_gpu_masks import masked_attn_case
 
 pytestmark = pytest.mark.gpu
@@ -16,4 +17,4 @@ def test_more_than_a_round(hq, hkv, s, c, window, kv_first, dh):
 
 
 def test_sequences():
-    sequences(_cfg(20, 4, 64), 7, 260, [0, 3, 0, 130, 259, 1, 64])
+    sequences(MORE_THAN_A_ROUND)

@@ -8,7 +8,7 @@ import subprocess
 
 import pytest
 
-from layer_plan_cases import PASSES, SEQUENCES
+from layer_plan_cases import MORE_THAN_A_ROUND, PASSES, SEQUENCES
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SRC = os.path.join(ROOT, "tests", "host_sanitize")
@@ -78,13 +78,15 @@ def test_calls_that_share_attention_launches_are_dealt_as_their_tests_say(plans)
     """... and their sizes pick the kernels that the tests name: one launch for dQ and dK/dV up to MERGED_MAX workgroups, either query tile counted."""
     with open(os.path.join(CSRC, "attn_mfma.hip")) as f:
         merged_max = int(re.search(r"MERGED_MAX = (\d+);", f.read()).group(1))
-    for c, got in zip(SEQUENCES, plans([dict(c["cfg"], B=c["B"], T=c["T"], chunk=c["T"], first=c["first"]) for c in SEQUENCES])):
+    calls = SEQUENCES + [MORE_THAN_A_ROUND]
+    for c, got in zip(calls, plans([dict(c["cfg"], B=c["B"], T=c["T"], chunk=c["T"], first=c["first"]) for c in calls])):
         assert [a[:3] for a in got["backward"]] == [[n, 0, c["T"]] for n in c["passes"]] and {a[3] for a in got["backward"]} == {c["slices"]}, (c, got)
         assert all(side_by_side == int(c["slices"] > 1) for *_, side_by_side in got["backward"]), (c, got)
         n, T = max(c["passes"]), c["T"]
         tiles = [-(-T // q) * c["cfg"]["n_q_heads"] * n for q in (256, 128)]
         hidden = min(c["first"]) // 128 if c["first"] else 0
         dkv = (-(-T // 128) - hidden) * c["cfg"]["n_kv_heads"] * n * c["slices"]
+        assert c is not MORE_THAN_A_ROUND or min(tiles) > 256
         assert dkv + min(tiles) > merged_max if c["separate"] else dkv + max(tiles) <= merged_max, (c, dkv, tiles)
 
 
