@@ -89,3 +89,8 @@ def lib_layer_cfg(cfg, seq_len, chunk, batch=1, grad_dtype="f32", dw_group_rows=
                         cfg["n_kv_heads"], cfg["head_dim"], cfg["mlp_width"], cfg.get("rms_eps", 1e-6),
                         cfg.get("rope_theta", 1e4), cfg.get("pos_offset", 0), code(grad_dtype), dw_group_rows,
                         cfg.get("window", 0), seq_first)
+
+
+def lib_part_cfg(p, **kw):
+    """The call of an entry of layer_plan_cases.PARTS."""
+    return lib_layer_cfg(p["cfg"], p["T"], p["chunk"], dw_group_rows=p["group"], **kw)

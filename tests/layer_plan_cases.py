@@ -1,5 +1,5 @@
 """Layer calls of the tests of passes, and how their rows are dealt: test_layer_plans.py reads the passes off the host layer on the CPU,
-test_gpu_attn_sequences.py, test_gpu_attn_tile_order.py and test_gpu_layer_passes.py run them."""
+the GPU tests that import from here run them."""
 from paper_2506_03077_amd import synth
 
 
@@ -33,6 +33,36 @@ _TINY = synth.CONFIGS["tiny"]
 def _one(*rows):      # a weight-gradient launch a pass
     return [[r] for r in rows]
 
+
+# bf16 weight gradients.  Config, batch, tokens, chunk, dw_group_rows; passes of each weight-gradient launch
+GROUPS = [
+    (_MID, 1, 1100, 64, 256, [2, 2, 2, 2, 1]),          # parts of a sequence
+    (_MID, 4, 300, 64, 0, [3, 3, 2]),                   # parts of several
+    (_MID, 5, 130, 64, 256, [4, 4, 2]),
+    (_MID, 9, 100, 100, 512, [5, 4]),                   # whole sequences
+    (dict(_MID, hidden=64, n_q_heads=8, n_kv_heads=8, head_dim=64, mlp_width=64), 4, 300, 256, 1, [8]),      # as many as a launch takes
+]
+
+
+def _part(cfg, T, chunk, group, backward, forward=None):
+    """One sequence.  backward, forward: rows of its passes, in the order of the rows."""
+    return dict(cfg=cfg, T=T, chunk=chunk, group=group, backward=backward, forward=forward)
+
+
+_7B, _LLAMA = synth.CONFIGS["7b"], synth.CONFIGS["llama_layer"]
+PARTS = {
+    "7b benchmark": _part(_7B, 32768, 2048, 0, [4096] * 8),
+    "7b small chunks": _part(_7B, 32768, 512, 0, [3328] * 9 + [2816]),
+    "7b two in one launch": _part(_7B, 4608, 2048, 0, [2304] * 2),
+    "7b ragged": _part(_7B, 4608, 512, 1, [659] * 6 + [654]),
+    "7b whole": _part(_7B, 4608, 4608, 0, [4608]),
+    "llama": _part(_LLAMA, 8192, 1024, 0, [4096] * 2),
+    "llama ragged": _part(_LLAMA, 8192, 1000, 1, [1280] * 6 + [512]),
+    "llama oracle": _part(_LLAMA, 2560, 1024, 1, [1280] * 2),
+    "mid": _part(_MID, 640, 256, 1, [320] * 2),
+    "mid small": _part(_MID, 640, 128, 1, [160] * 4, [320] * 2),
+    "mid whole": _part(_MID, 640, 640, 1, [640]),
+}
 
 # config, batch, tokens, chunk, dw_group_rows, window, first; weight-gradient launches as [first row, rows] of their passes, in order; passes of the
 # forward as [sequences, first row, rows]

@@ -56,10 +56,10 @@ def test_hidden_rows_reach_nothing(dtype, dh, bad):
     assert not bool(torch.isfinite(o3[-1].float()).all())
 
 
-# 2 and 9 chunks (one and two groups of weight gradients), widths that are no multiple of the GEMM's 32 x 32 tiles or 16-deep steps
+# two passes of a sequence and seven, widths that are no multiple of the GEMM's 32 x 32 tiles or 16-deep steps
 @pytest.mark.parametrize("cfg,T,chunk,batch", [
     (dict(dtype="f32", hidden=40, n_q_heads=4, n_kv_heads=2, head_dim=10, mlp_width=53, vocab=64), 33, 20, 2),
     (dict(dtype="f32", hidden=65, n_q_heads=2, n_kv_heads=1, head_dim=34, mlp_width=129, vocab=64), 70, 8, 1),
     (dict(dtype="bf16", hidden=72, n_q_heads=6, n_kv_heads=2, head_dim=24, mlp_width=100, vocab=64), 90, 10, 1)])
 def test_layer_on_the_shape_agnostic_kernels(cfg, T, chunk, batch):
-    run_layer_case(cfg, T, chunk, batch=batch, seed=11)
+    run_layer_case(cfg, T, chunk, batch=batch, seed=11, dw_group_rows=1)

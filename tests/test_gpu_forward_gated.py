@@ -22,5 +22,5 @@ def test_layer_forward_with_many_gate_tiles(T, chunk, mlp):
     got = sb.streambp_layer_forward(lib_layer_cfg(cfg, T, chunk), w, x)
     torch.cuda.synchronize()
     assert_close(host(got).reshape(want.shape), want, TOL["bf16"], "y")
-    apart = sb.streambp_layer_forward(lib_layer_cfg(cfg, T, 64), w, x)
+    apart = sb.streambp_layer_forward(lib_layer_cfg(cfg, T, 64, dw_group_rows=1), w, x)      # (passes of 75 and 86 rows)
     assert_close(host(apart), host(got), TOL["bf16"], "chunk 64")

@@ -10,7 +10,8 @@ from paper_2506_03077_amd import binding as sb
 from paper_2506_03077_amd import synth
 
 from gpu_util import TOL, assert_close, dev, host, lib_layer_cfg, oracle_cfg
-from layer_plan_cases import PASSES
+from layer_plan_cases import GROUPS, PASSES
+from test_gpu_parity_small import run_layer_case
 
 pytestmark = pytest.mark.gpu
 
@@ -29,3 +30,8 @@ def test_passes_of_a_layer_vs_oracle(cfg, B, T, chunk, group, window, first):
         assert_close(host(dw[n]), g_ref[n], TOL[dt], f"d{n}")
     y_ref = np.stack([o_layer.layer_forward(inp["x"][b], inp["w"], dict(oracle_cfg(cfg), first_valid=first[b] if first else 0))[0] for b in range(B)])
     assert_close(host(y), y_ref, TOL[dt], "y")
+
+
+@pytest.mark.parametrize("cfg,B,T,chunk,group", [c[:5] for c in GROUPS])
+def test_passes_that_share_a_launch_of_bf16_weight_gradients_vs_oracle(cfg, B, T, chunk, group):
+    run_layer_case(cfg, T, chunk, batch=B, grad_dtype="bf16", dw_group_rows=group)

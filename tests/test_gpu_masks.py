@@ -114,7 +114,7 @@ def test_layer_backward_with_window_and_front_padding(cfg, T, chunk, window, fir
 
 
 def test_layer_with_a_window_at_7b_widths_vs_oracle():
-    # the bench's launch configuration (chunk 2048, 7B widths) with a 1024-token sliding window and 300 rows of padding
+    # 7B widths at the bench's chunk (two passes of 2304 rows) with a 1024-token sliding window and 300 rows of padding
     cfg = dict(synth.CONFIGS["7b"], window=1024)
     T, chunk, first = 4608, 2048, [300]
     inp = synth.layer_inputs(cfg, seed=8, seq_len=T)

@@ -1,12 +1,12 @@
-"""GPU parity at the workloads' real widths, in the launch configuration bench.py times
+"""GPU parity at the workloads' real widths, those that bench.py times
 (bf16, d=3584, 28q/4kv x128, F=18944, V=152064, chunk 2048).
 
 The fp64 oracle cannot run a 32k-token layer (it is a plain full-sequence backprop), so:
-  * layer and head are compared element by element against the oracle at the real widths AND the real chunk size
-    (2048 rows; also 512 and no partition), at a sequence length the oracle finishes in tens of seconds
-    (T = 4608 for the layer: two full chunks and a ragged one; 8792 rows for the head: four full chunks and a
-    ragged one), so that the kernels' launch shapes - split-K factors, operand pairs, grouped multi-segment
-    weight-gradient passes - are those of the benchmark;
+  * layer and head are compared element by element against the oracle at the real widths, at a sequence length the
+    oracle finishes in tens of seconds: 4608 tokens for the layer, in two passes of 2304 rows with one grouped launch
+    of weight gradients, seven ragged ones and a single one (the benchmark's 32768 tokens take eight passes of 4096 rows, two a
+    launch, which a test below holds against passes of other sizes); 8792 rows for the head at the real chunk size: four full
+    chunks and a ragged one, with the split-K factors, operand pairs and multi-segment weight-gradient passes of the benchmark;
   * at the full 32k length, chunk attention is compared element by element against the oracle
     for one whole KV group (the oracle's cost there is small), and the layer / head are checked
     through properties that hold at any size (chunk-size invariance, exact zeros of ignored
@@ -21,7 +21,8 @@ from oracle import layer as o_layer
 from paper_2506_03077_amd import binding as sb
 from paper_2506_03077_amd import synth
 
-from gpu_util import assert_close, dev, host, lib_layer_cfg, oracle_cfg, relerr
+from gpu_util import assert_close, dev, host, lib_layer_cfg, lib_part_cfg, oracle_cfg, relerr
+from layer_plan_cases import PARTS
 
 pytestmark = pytest.mark.gpu
 
@@ -42,18 +43,17 @@ def layer_reference(cfg, T, seed):
     return _LAYER_REF[key]
 
 
-@pytest.mark.parametrize("chunk", [2048, 512, 4608])
-def test_layer_7b_widths_vs_oracle(chunk):
-    # 7B widths, T = 4608 = 2.25 chunks of 2048 (the chunk bench.py times; the last chunk ragged).  At chunk 2048 the layer
-    # runs what the bench runs: the two-way XCD-pinned split-K input-gradient GEMMs over 112 output tiles, the operand-pair
-    # dm GEMM, and ONE grouped weight-gradient launch with three reduction segments of 2048, 2048 and 512 rows; chunk 512
-    # takes the 8-way split-K and groups of four chunks, chunk = T no partition at all.
-    T = 4608
-    assert sb.streambp_layer_fast_path(lib_layer_cfg(C7B, T, chunk)) == 1
+@pytest.mark.parametrize("part", ["7b two in one launch", "7b ragged", "7b whole"])
+def test_layer_7b_widths_vs_oracle(part):
+    # 7B widths, 4608 tokens: chunk 2048, two passes of 2304 rows with their input-gradient products split over 126 output tiles, the
+    # operand-pair dm GEMM and ONE grouped weight-gradient launch of two reduction segments; chunk 512, room for one, seven passes of up to 659
+    # rows; chunk = T no partition at all.
+    lc, T, chunk = lib_part_cfg(PARTS[part]), 4608, PARTS[part]["chunk"]
+    assert sb.streambp_layer_fast_path(lc) == 1
     inp, dx_ref, g_ref = layer_reference(C7B, T, 0)
     w = {k: dev(v, "bf16") for k, v in inp["w"].items()}
     before = sb.streambp_generic_launches()
-    dx, dw = sb.streambp_layer_backward(lib_layer_cfg(C7B, T, chunk), w, dev(inp["x"], "bf16"), dev(inp["dy"], "bf16"))
+    dx, dw = sb.streambp_layer_backward(lc, w, dev(inp["x"], "bf16"), dev(inp["dy"], "bf16"))
     torch.cuda.synchronize()
     assert sb.streambp_generic_launches() == before        # nothing left the MFMA kernels
     assert_close(host(dx), dx_ref, TOL, f"dx (chunk {chunk})")
@@ -165,8 +165,8 @@ def test_layer_32k_chunk_invariance_and_structure():
              wgate=rn((F, d), 0.02), wup=rn((F, d), 0.02), wdown=rn((d, F), 0.02), g1=rn((d,), 0.02, 1.0), g2=rn((d,), 0.02, 1.0))
     x, dy = rn((1, T, d), 1.0), rn((1, T, d), 1e-3)
     dy[:, T // 2:] = 0                                   # no loss on the second half ...
-    dx_a, dw_a = sb.streambp_layer_backward(lib_layer_cfg(C7B, T, 2048), w, x, dy)
-    dx_b, dw_b = sb.streambp_layer_backward(lib_layer_cfg(C7B, T, 4096), w, x, dy)
+    dx_a, dw_a = sb.streambp_layer_backward(lib_part_cfg(PARTS["7b benchmark"]), w, x, dy)
+    dx_b, dw_b = sb.streambp_layer_backward(lib_part_cfg(PARTS["7b small chunks"]), w, x, dy)
     torch.cuda.synchronize()
     assert torch.all(dx_a[:, T // 2:] == 0)              # ... so causality makes dx of those rows exactly zero
     assert bool(torch.isfinite(dx_a.float()).all())
@@ -216,12 +216,12 @@ LLAMA = synth.CONFIGS["llama_layer"]
 
 def test_llama_layer_widths_vs_oracle_and_8k_chunk_invariance():
     # Llama-style layer (d=4096, 32q/8kv x128, F=14336): element by element against the oracle at the config's own chunk
-    # of 1024 rows (T = 2560: two chunks and a ragged third, one three-segment weight-gradient launch), then the real shape
-    # (T=8192, chunk 1024) against itself at another chunk size.
-    T, chunk = 2560, LLAMA["chunk"]
+    # of 1024 rows (T = 2560: two passes), then the real shape (T=8192, chunk 1024: two passes of 4096 rows) against itself in seven
+    # ragged ones.
+    T = 2560
     inp, dx_ref, g_ref = layer_reference(LLAMA, T, 4)
     w = {k: dev(v, "bf16") for k, v in inp["w"].items()}
-    dx, dw = sb.streambp_layer_backward(lib_layer_cfg(LLAMA, T, chunk), w, dev(inp["x"], "bf16"), dev(inp["dy"], "bf16"))
+    dx, dw = sb.streambp_layer_backward(lib_part_cfg(PARTS["llama oracle"]), w, dev(inp["x"], "bf16"), dev(inp["dy"], "bf16"))
     torch.cuda.synchronize()
     assert_close(host(dx), dx_ref, TOL, "dx")
     for n in sb.WEIGHT_NAMES:
@@ -230,8 +230,8 @@ def test_llama_layer_widths_vs_oracle_and_8k_chunk_invariance():
     gen = torch.Generator(device="cuda"); gen.manual_seed(5)
     x = torch.randn((1, T, LLAMA["hidden"]), generator=gen, device="cuda").to(torch.bfloat16)
     dy = (torch.randn((1, T, LLAMA["hidden"]), generator=gen, device="cuda") * 1e-3).to(torch.bfloat16)
-    dx_a, dw_a = sb.streambp_layer_backward(lib_layer_cfg(LLAMA, T, LLAMA["chunk"]), w, x, dy)
-    dx_b, dw_b = sb.streambp_layer_backward(lib_layer_cfg(LLAMA, T, 3000), w, x, dy)       # ragged chunks
+    dx_a, dw_a = sb.streambp_layer_backward(lib_part_cfg(PARTS["llama"]), w, x, dy)
+    dx_b, dw_b = sb.streambp_layer_backward(lib_part_cfg(PARTS["llama ragged"]), w, x, dy)
     torch.cuda.synchronize()
     assert bool(torch.isfinite(dx_a.float()).all())
     assert relerr(host(dx_b), host(dx_a)) < 1e-2

@@ -12,7 +12,8 @@ from oracle import layer as o_layer
 from paper_2506_03077_amd import binding as sb
 from paper_2506_03077_amd import synth
 
-from gpu_util import TOL, assert_close, code, dev, host, lib_layer_cfg, oracle_cfg, relerr, tdtype
+from gpu_util import TOL, assert_close, code, dev, host, lib_layer_cfg, lib_part_cfg, oracle_cfg, relerr, tdtype
+from layer_plan_cases import PARTS
 
 pytestmark = pytest.mark.gpu
 
@@ -53,11 +54,11 @@ def test_layer_backward_tiny_fp32_batch_and_offset():
 
 @pytest.mark.parametrize("chunk", [128, 256, 640])
 def test_layer_backward_mid_bf16(chunk):
-    run_layer_case(MID16, 640, chunk)
+    run_layer_case(MID16, 640, chunk, dw_group_rows=1)      # four passes, two, one
 
 
 def test_layer_backward_mid_bf16_ragged_rows():
-    run_layer_case(MID16, 333, 100, batch=2, seed=1)
+    run_layer_case(MID16, 333, 100, batch=2, seed=1, dw_group_rows=1)      # three passes of each sequence
 
 
 # shapes whose weight gradients have enough output tiles for the grouped launch
@@ -71,9 +72,9 @@ def test_layer_backward_grouped_weight_gradients(grad_dtype):
 
 @pytest.mark.parametrize("rows", [1, 128, 256, 384, 512, 640, 768, 896, 100000])
 def test_weight_gradient_group_size_is_a_free_choice(rows):
-    # Eq. 1: the per-chunk summands of a weight gradient may be added in any grouping.  dw_group_rows picks how many chunks'
-    # operands stay alive for one pass over every dW: 1 chunk (rows <= chunk), 2, ..., 7, 8 (the cap); 9 chunks of 128 rows, the
-    # last one ragged, so groups of every size end on a partial group.  Layer and head, fp32 and bf16 accumulators.
+    # Eq. 1: the per-chunk summands of a weight gradient may be added in any grouping.  dw_group_rows picks how many chunks' operands the
+    # workspace has room for: 1 (rows <= chunk), 2, ..., 7, 8 (the cap).  The head adds so many at a time, of 9 chunks of 128 rows, the last
+    # one ragged, so groups of every size end on a partial group; the layer makes two to seven passes of them.  fp32 and bf16 accumulators.
     run_layer_case(BIG16, 1100, 128, dw_group_rows=rows)
     run_layer_case(MID16, 1100, 128, grad_dtype="bf16", dw_group_rows=rows)
     head_case(MID16, 2, 600, 128, "sft", loss_scale=1.0 / 900, dw_group_rows=rows)
@@ -173,10 +174,10 @@ def test_layer_backward_is_reproducible_and_chunk_invariant():
     inp = synth.layer_inputs(cfg, seed=4, seq_len=T)
     w = {k: dev(v, "bf16") for k, v in inp["w"].items()}
     x, dy = dev(inp["x"], "bf16"), dev(inp["dy"], "bf16")
-    a = sb.streambp_layer_backward(lib_layer_cfg(cfg, T, 256), w, x, dy)
-    b = sb.streambp_layer_backward(lib_layer_cfg(cfg, T, 256), w, x, dy)
+    a = sb.streambp_layer_backward(lib_part_cfg(PARTS["mid"]), w, x, dy)
+    b = sb.streambp_layer_backward(lib_part_cfg(PARTS["mid"]), w, x, dy)
     assert torch.equal(a[0], b[0]) and all(torch.equal(a[1][n], b[1][n]) for n in sb.WEIGHT_NAMES)
-    c = sb.streambp_layer_backward(lib_layer_cfg(cfg, T, 128), w, x, dy)
+    c = sb.streambp_layer_backward(lib_part_cfg(PARTS["mid small"]), w, x, dy)
     for n in sb.WEIGHT_NAMES:       # chunk size changes only the rounding order
         assert_close(host(c[1][n]), host(a[1][n]), 1e-2, n)
 
@@ -378,15 +379,15 @@ def test_causality_is_bit_exact_inside_the_visible_range():
     # Property 3.1 / the causal mask as integer arithmetic: query t never sees key u > t, also when u lies inside the chunk's
     # visible range (same chunk, same 64-key tile, same 32-query wave).  Changing x rows (resp. q, k, v rows) after t must
     # leave the rows up to t of the layer's output (resp. of o and lse) bit-identical.
-    cfg, T, chunk = MID16, 640, 256
+    cfg, T, lc = MID16, 640, lib_part_cfg(PARTS["mid small"])      # two passes of 320 rows
     inp = synth.layer_inputs(cfg, seed=9, seq_len=T)
     w = {k: dev(v, "bf16") for k, v in inp["w"].items()}
     x = dev(inp["x"], "bf16")
-    y = sb.streambp_layer_forward(lib_layer_cfg(cfg, T, chunk), w, x)
-    for t in (0, 31, 63, 300, 511, 638):            # wave, tile and chunk boundaries and the middle of a tile
+    y = sb.streambp_layer_forward(lc, w, x)
+    for t in (0, 31, 63, 300, 319, 320, 511, 638):  # wave, tile and pass boundaries and the middle of a tile
         x2 = x.clone()
         x2[:, t + 1:] = (x2[:, t + 1:].float() * -3.0 + 0.5).to(torch.bfloat16)     # finite, very different values
-        y2 = sb.streambp_layer_forward(lib_layer_cfg(cfg, T, chunk), w, x2)
+        y2 = sb.streambp_layer_forward(lc, w, x2)
         torch.cuda.synchronize()
         assert torch.equal(y2[:, :t + 1], y[:, :t + 1]), f"rows <= {t} changed"
         assert not torch.equal(y2[:, t + 1:], y[:, t + 1:])

@@ -10,7 +10,8 @@ from oracle import layer as o_layer
 from paper_2506_03077_amd import binding as sb
 from paper_2506_03077_amd import synth
 
-from gpu_util import TOL, assert_close, code, dev, host, lib_layer_cfg, oracle_cfg
+from gpu_util import TOL, assert_close, code, dev, host, lib_layer_cfg, lib_part_cfg, oracle_cfg
+from layer_plan_cases import PARTS
 
 pytestmark = pytest.mark.gpu
 
@@ -101,8 +102,8 @@ def test_stack_of_four_7b_layers_at_32k_structure_and_chunk_invariance():
     targets[:, last + 1:] = -1                                    # no loss after position `last`
     n_act = last + 1
     results = []
-    for chunk in (2048, 4096):
-        sc = sb.stack_cfg(lib_layer_cfg(cfg, T, chunk), L, V, 2048, sb.SBP_OBJ_SFT, 1.0 / n_act)
+    for part in (PARTS["7b benchmark"], PARTS["7b small chunks"]):
+        sc = sb.stack_cfg(lib_part_cfg(part), L, V, 2048, sb.SBP_OBJ_SFT, 1.0 / n_act)
         ckpt = [torch.empty((1, T, d), dtype=bf, device="cuda") for _ in range(L + 1)]
         sb.streambp_stack_forward(sc, layers, ckpt, emb, ids)
         out = sb.streambp_stack_backward(sc, layers, g_final, w_head, ckpt, targets, ids=ids)

@@ -8,7 +8,7 @@ import subprocess
 
 import pytest
 
-from layer_plan_cases import MORE_THAN_A_ROUND, PASSES, SEQUENCES
+from layer_plan_cases import GROUPS, MORE_THAN_A_ROUND, PARTS, PASSES, SEQUENCES
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SRC = os.path.join(ROOT, "tests", "host_sanitize")
@@ -94,3 +94,12 @@ def test_passes_of_a_layer_are_dealt_as_their_test_says(plans):
     configs = [dict(cfg, B=B, T=T, chunk=chunk, group=group, window=window, first=first) for cfg, B, T, chunk, group, window, first, _, _ in PASSES]
     for (*_, dw, forward), got in zip(PASSES, plans(configs)):
         assert got["dw"] == dw and [a[:3] for a in got["forward"]] == forward, got
+
+
+def test_groups_of_passes_and_parts_of_a_sequence_are_dealt_as_their_tests_say(plans):
+    configs = [dict(cfg, B=B, T=T, chunk=chunk, group=group, grad="bf16") for cfg, B, T, chunk, group, _ in GROUPS]
+    for (*_, sizes), got in zip(GROUPS, plans(configs)):
+        assert [len(launch) for launch in got["dw"]] == sizes, got
+    for p, got in zip(PARTS.values(), plans([dict(p["cfg"], B=1, T=p["T"], chunk=p["chunk"], group=p["group"]) for p in PARTS.values()])):
+        assert [rows for _, _, rows, *_ in reversed(got["backward"])] == p["backward"], (p, got)
+        assert not p["forward"] or [rows for _, _, rows, *_ in got["forward"]] == p["forward"], (p, got)
