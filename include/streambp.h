@@ -82,13 +82,17 @@ typedef struct {
                            SBP_BF16; App. D (experiment setup) of the paper uses bf16
                            weights and gradients).  A bf16 gradient is read,
                            added to in fp32 and rounded once per pass over it. */
-  int32_t dw_group_rows; /* rows of chunk operands kept alive so that one pass over
-                           the weight gradients adds several chunks' products
-                           (Eq. 1: the summands may be added in any grouping):
-                           the group is min(8, max(1, dw_group_rows / chunk))
-                           chunks.  0 = default (8192).  More rows: fewer passes
-                           over every dW, more workspace (one more copy of a
-                           chunk's ten GEMM operand buffers per chunk of the group) */
+  int32_t dw_group_rows; /* rows of chunk operands the workspace has room for, so that
+                           one pass over the weight gradients can add several
+                           chunks' products (Eq. 1: the summands may be added in any
+                           grouping): a group of min(8, max(1, dw_group_rows / chunk))
+                           chunks, with one more copy of a chunk's ten GEMM operand
+                           buffers per chunk of the group.  0 = default (8192).
+                           Inside that room the library deals the rows itself (see
+                           streambp_layer_workspace_bytes): fp32 gradients may be
+                           passed over more or less often than once per group, bf16
+                           ones, which every pass rounds, are rounded no more often
+                           than groups of chunks would round them                    */
   int32_t window;       /* attention mask (Sec. 3.2.2 allows a general mask M, "padding /
                            sliding window"): 0 = plain causal; > 0 = the token at row t
                            attends to rows t - window < u <= t only                 */
@@ -127,7 +131,10 @@ typedef struct {
  * Chunk and dw_group_rows set the bytes; how the rows are dealt inside them is
  * the library's: a pass may take more rows than a chunk, or several short
  * sequences of the batch at once, where that is faster (Eq. 1 holds for any
- * partition; every result stays within the rounding of its types). */
+ * partition; every result stays within the rounding of its types).  Rows that
+ * share a pass share its products, and how a product adds its terms depends on
+ * its number of rows: the last bits of a sequence's y and dx may depend on the
+ * batch it is in and on chunk.  The same call gives the same bits every time. */
 size_t streambp_layer_workspace_bytes(const sbp_layer_cfg *cfg);
 
 /* StreamBP of one layer (Sec. 3.2.2): K and V are computed once for the whole

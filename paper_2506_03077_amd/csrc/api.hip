@@ -79,12 +79,13 @@ int32_t check_grad_dtype(int32_t dt, int32_t grad_dt) {
   return SBP_OK;
 }
 
-// Weight gradients are added once per group of chunks (one read-modify-write pass over every dW per group instead of
-// one per chunk): as many chunks as it takes to reach dw_group_rows rows, at most MAX_DW_GROUP (the GEMM kernels take
-// up to eight reduction segments per output).  The operands of the group's chunks stay alive until the launch.
+// Weight gradients are added once per group (one read-modify-write pass over every dW per group instead of one per chunk), at most MAX_DW_GROUP chunks
+// or passes (the GEMM kernels take up to eight reduction segments per output), the operands of which stay alive until the launch.  Head: as many chunks
+// as it takes to reach dw_group_rows rows.  Layer: that group sets the bytes, and how often bf16 gradients may be rounded; how many passes share a launch
+// is plan_layer's.
 constexpr int MAX_DW_GROUP = 8;
 // Defaults (dw_group_rows == 0).  Measured at 7B widths, chunk 2048: the head's dW pass (2.2 GB read-modify-written) still
-// gains from eight chunks per pass over four; the layer's seven dW (0.93 GB) do not, so the layer keeps four.
+// gains from eight chunks per pass over four; the layer's seven dW (0.93 GB) do not, so the layer has room for four.
 constexpr int DW_GROUP_ROWS_LAYER = 8192;
 constexpr int DW_GROUP_ROWS_HEAD = 16384;
 int dw_group_for(size_t chunk_rows, int32_t cfg_rows, int default_rows) {   // cfg_rows: the config's dw_group_rows (0 = default)
@@ -194,7 +195,8 @@ LayerWs carve_layer(const sbp_layer_cfg* c, void* ws, const LayerPlan& plan, boo
   w.rstd1 = cv.take<float>(n);
   w.rstd2 = cv.take<float>(n);
   w.lse = cv.take<float>(n * c->n_q_heads);
-  // (a chunk's worth: products of more rows have less to split)
+  // (a chunk's worth, as the call's bytes have it: a partial tile per CU from chunks of 256 rows at widths of 2560 on.  Smaller ones leave room for fewer - 64
+  // for 64 rows at 7B widths, 27 for 256 rows at 256 - so that the products of their passes split less, and share no last round)
   w.gemm_scratch_bytes = c->dtype == SBP_BF16 ? gemm_scratch_bytes((int)std::min(n, (size_t)std::min(c->chunk, c->seq_len)), (int)std::max(d, qd)) : 0;
   w.gemm_scratch = (float*)cv.take_bytes(w.gemm_scratch_bytes);
   if (backward) {
