@@ -25,11 +25,11 @@
 //            8 waves x 32 queries; K and V tiles of 64 keys stream HBM -> LDS
 //            (direct-to-LDS); online softmax in the exp2 domain; multiply and
 //            softmax slots of two wave groups alternate.
-//  dQ      : same decomposition and slots, 32x32x16 MFMAs; recomputes P from the
+//  dQ      : same decomposition, slots and MFMAs; recomputes P from the
 //            saved log-sum-exp; dQ^T += K^T dS^T.
 //  dK/dV   : workgroup = 128 keys of one KV head, 4 key blocks x 2 roles: one wave of
 //            a block computes P and dV^T += dO^T P, its partner dP, dS and
-//            dK^T += Q^T dS (P crosses through LDS), 32x32x16 MFMAs; loops over the query
+//            dK^T += Q^T dS (P crosses through LDS); loops over the query
 //            tiles at or below the diagonal and over the query heads of the group, Q
 //            and dO tiles of 64 queries stream through four LDS stages; results are
 //            added to the fp32 prefix accumulators (every element has one owner, or
@@ -48,7 +48,6 @@ typedef bf16_t bf16x4 __attribute__((ext_vector_type(4)));
 typedef short short4v __attribute__((ext_vector_type(4)));
 typedef short short8v __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int AT_THREADS = 512;          // 8 waves (forward, dQ): 2 per SIMD
 constexpr int TQ = ATTN_TILE_Q;          // queries per workgroup (fwd, dQ): 8 waves x 32
@@ -74,20 +73,6 @@ __device__ __forceinline__ int swz(int row) {
 template <int DH>
 __device__ __forceinline__ int tile_off(int row, int chunk) { return row * DH * 2 + ((chunk ^ swz<DH>(row)) << 4); }
 
-__device__ __forceinline__ bf16x8 pack8(const f32x16& v, int ks) {
-  bf16x8 o;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) o[j] = (bf16_t)v[8 * ks + j];
-  return o;
-}
-
-__device__ __forceinline__ f32x16 zero16() {
-  f32x16 z;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) z[r] = 0.f;
-  return z;
-}
-
 // Probabilities and dS are operands of the second products.  DH = 128 rounds them to bf16; DH = 64 keeps them as a sum of bf16 terms, at
 // the price of a further MFMA each: two (2^-17 relative) where the result is rounded to bf16, o and dq, three (exact) for dv = P^T dO
 // and dk = dS^T Q, which leave as fp32.  The statistics of DH = 64 keep fp32 as well: the denominator sums the fp32 probabilities
@@ -99,12 +84,6 @@ __device__ __forceinline__ f32x16 zero16() {
 template <int DH> constexpr int TERMS = DH == 64 ? 2 : 1;
 template <int DH> constexpr int KV_TERMS = DH == 64 ? 3 : 1;
 template <int DH> constexpr bool FP32_STATS = DH == 64;
-__device__ __forceinline__ bf16x8 rest8(const f32x16& v, int ks, const bf16x8& hi) {      // what pack8 leaves behind
-  bf16x8 o;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) o[j] = (bf16_t)(v[8 * ks + j] - (float)hi[j]);
-  return o;
-}
 
 // exp(x * scale + c): c in log2 units, or in natural ones where the statistics keep fp32
 template <int DH>
@@ -113,35 +92,12 @@ __device__ __forceinline__ float exp_of(float x, float scale, float sl, float c)
   return __builtin_amdgcn_exp2f(__builtin_fmaf(x, sl, c));
 }
 
-#define MFMA(a, b, c) __builtin_amdgcn_mfma_f32_32x32x16_bf16((a), (b), (c), 0, 0, 0)
-
 // ---- address work hoisted out of the tile loops --------------------------------------------------------------
 // In the tile loops every vector-ALU instruction competes with the softmax arithmetic for the SIMD's VALU issue
 // slots, so nothing there computes an address: the per-lane byte offsets of the fragment reads inside a 64-row
-// tile and of the direct-to-LDS loads are computed once per kernel, every tile / row block / stage is reached
-// with immediate offsets, and the global side is an SGPR base plus those per-lane offsets.
-template <int DH>
-struct FragPre {
-  uint32_t rows[DH / 16];   // frag_rows: k16 step ks of row block 0            (row block b: + b * 32 rows)
-  uint32_t tr[DH / 16];     // frag_cols_tr: [i * 2 + hi], head_dim block i, tile rows +0 / +8, row_base 0 (+ row_base rows)
-};
-template <int DH>
-__device__ __forceinline__ FragPre<DH> frag_pre(uint32_t lds_base /* LDS address of tile 0 */) {
-  const int l = threadIdx.x & 63;
-  FragPre<DH> f;
-#pragma unroll
-  for (int ks = 0; ks < DH / 16; ++ks) f.rows[ks] = pin(lds_base + (uint32_t)tile_off<DH>(l & 31, ks * 2 + (l >> 5)));
-  const int p = l & 15, g = l >> 4;
-#pragma unroll
-  for (int i = 0; i < DH / 32; ++i)
-#pragma unroll
-    for (int hi = 0; hi < 2; ++hi) {
-      const int col = i * 32 + 16 * (g & 1) + 4 * (p & 3);
-      const int row = 4 * (g >> 1) + (p >> 2) + 8 * hi;
-      f.tr[i * 2 + hi] = pin(lds_base + (uint32_t)(tile_off<DH>(row, col >> 3) + ((col & 7) << 1)));
-    }
-  return f;
-}
+// tile and of the direct-to-LDS loads are computed once per kernel, every row block is reached with an immediate
+// offset (every stage too in the forward; the backward moves its addresses on, one addition per address and
+// tile), and the global side is an SGPR base plus those per-lane offsets.
 __device__ __forceinline__ bf16x8 lds_b128(uint32_t addr) {
   return *(const bf16x8*)(__attribute__((address_space(3))) const char*)(uintptr_t)addr;
 }
@@ -183,8 +139,8 @@ __device__ __forceinline__ void dma_tile64(const TileLoad<DH, NT>& t, const bf16
   }
 }
 
-// A chain of N MFMAs whose A operands come from LDS: the fragment of step i+DEPTH is requested before the MFMA of
-// step i issues (ring of DEPTH+1 fragments), and scheduling barriers keep that order - left alone, the compiler
+// A chain of N steps, an MFMA or two each, whose A operands come from LDS: the fragment of step i+DEPTH is requested before the MFMAs of
+// step i issue (ring of DEPTH+1 fragments), and scheduling barriers keep that order - left alone, the compiler
 // sinks every LDS read to just before its MFMA and the wave eats one LDS latency per MFMA.
 template <int N, int DEPTH = 3, typename LoadF, typename MmaF>
 __device__ __forceinline__ void mfma_chain(LoadF load, MmaF mma) {
@@ -201,10 +157,9 @@ __device__ __forceinline__ void mfma_chain(LoadF load, MmaF mma) {
 }
 #define WAIT_VM0() __builtin_amdgcn_s_waitcnt(0x0f70)
 
-// row index (within a 32-row accumulator block) held in register r of a lane in half h
-__device__ __forceinline__ int acc_row(int r, int h) { return 8 * (r >> 2) + 4 * h + (r & 3); }
-
-// ---- 16x16x32 MFMA building blocks (forward) -------------------------------------------------------------------
+// ---- 16x16x32 MFMA building blocks -----------------------------------------------------------------------------
+// A product of 16 x 16 x 32 reads and writes its accumulators half as often as one of 32 x 32 x 16, and the chip is at its power limit: from registers alone, on
+// random data, the one holds 2020 TFLOP/s here, the other 1370 (1800 in the first 0.1 s).
 // S^T blocks of 16 keys x 16 queries: lane l holds query l % 16 and keys 4 (l / 16) + r.  Two such blocks (32 keys) are the B operand
 // of the next product with slot 8 (l / 16) + j <-> key 16 (j >> 2) + 4 (l / 16) + (j & 3), matched on the A side by two
 // transposing reads 16 rows apart.
@@ -654,9 +609,12 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
 // What bounds it: the clock that the power limit leaves.  The slots keep the matrix pipe busier than two stages behind one barrier per tile did, and the
 // clock falls by most of what that gives: backward and forward of the last 2048-query chunk of 32k, 28 heads, 3.68 -> 3.64 ms; a 32k layer at 7B widths
 // 69.5 -> 67.9; 777 windowed queries 141.5 -> 139.0 us.  Tiles of 32 keys without SPLIT: 3.66 ms, the layer 70.0 (a slot of 24 MFMAs does not cover its start).
+// 16x16x32 MFMAs take less of that power than 32x32x16 ones: the kernel itself on that chunk 1123 -> 1050 us.
+// A wave's tiles are one loop without branches around the products, the stages moving with the addresses: with four steps unrolled, each skipping its products by a
+// branch, the accumulators of four registers are moved about and 130 registers spill (1925 us).
 template <int DH, bool SPLIT>
-struct DqShared { char sT[8][TILE64<DH>]; };      // K stages, then V stages; SPLIT: of group 0, then of group 1
-constexpr int DQ_CHAIN = 5;                       // LDS fragments requested ahead of the products (4 and 6 the same within 0.3 %; 6 has no register left)
+struct DqShared { char sT[8][TILE64<DH>]; };      // K and V of stage after stage; SPLIT: of group 0, then of group 1
+constexpr int DQ_CHAIN = 5;                       // LDS fragments requested ahead of the products (4: the same within 0.3 %)
 template <int DH, bool SPLIT>
 __device__ __forceinline__ void dq_tile(DqShared<DH, SPLIT>& sh, int q_block, int bh, const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                         const bf16_t* __restrict__ v, const bf16_t* __restrict__ d_o, const float* __restrict__ lse,
@@ -667,17 +625,13 @@ __device__ __forceinline__ void dq_tile(DqShared<DH, SPLIT>& sh, int q_block, in
   q += (int64_t)b * c * Hq * DH; d_o += (int64_t)b * c * Hq * DH; dq += (int64_t)b * c * Hq * DH;
   k += (int64_t)b * c * Hkv * DH; v += (int64_t)b * c * Hkv * DH;
   lse += (int64_t)b * c * Hq; delta += (int64_t)b * 2 * c * Hq;
-  constexpr int QW = SPLIT ? TQ / 2 : TQ, NK = SPLIT ? TK / 2 : TK, NB = NK / 32;      // queries of the workgroup; keys of a tile, its 32-key blocks
+  constexpr int QW = SPLIT ? TQ / 2 : TQ, NK = SPLIT ? TK / 2 : TK, NB = NK / 16;      // queries of the workgroup; keys of a tile, its 16-key blocks
   constexpr int STAGES = 4, TILE = NK * DH * 2;
   constexpr int LOADERS = SPLIT ? AT_THREADS / 2 : AT_THREADS, LOADS = NK * DH / 8 / LOADERS;      // threads that load a tile, 16-byte loads of each
 
   const int q0 = q_block * QW, kvh = h / (Hq / Hkv);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), grp = wave >> 2, lane = threadIdx.x & 63, half = lane >> 5;
-  const int qw0 = q0 + (SPLIT ? wave & 3 : wave) * 32;
-  const int my_q = qw0 + (lane & 31);
-  const bool q_valid = my_q < c;
-  const int q_row = min(my_q, c - 1);
-  const int qpos = q_start + q_row;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), grp = wave >> 2, lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
+  const int qw0 = q0 + (SPLIT ? wave & 3 : wave) * 32;      // a lane has the queries li and 16 + li from there on
   const int64_t kv_stride = (int64_t)Hkv * DH;
   const bf16_t* kbase = k + (int64_t)kvh * DH;
   const bf16_t* vbase = v + (int64_t)kvh * DH;
@@ -687,218 +641,246 @@ __device__ __forceinline__ void dq_tile(DqShared<DH, SPLIT>& sh, int q_block, in
   const int wave_last_key = q_start + min(qw0 + 32, c) - 1;
   const int wave_first_qpos = q_start + qw0;
   auto first_key = [&](int p) { return max(kv_first, window > 0 ? p - window + 1 : 0); };   // left edge of the visible range
-  const int lo_q = first_key(qpos);
   const int wave_lo_min = first_key(wave_first_qpos), wave_lo_max = first_key(wave_last_key);
   const int kt0 = first_key(q_start + q0) / NK;
   // tile i of this wave's sequence
   auto tile_of = [&](int i) { return SPLIT ? kt0 + 2 * i + grp : kt0 + i; };
   const int n_it = SPLIT ? (max(0, n_tiles - kt0) + 1) / 2 : max(0, n_tiles - kt0);
 
-  constexpr int KS = DH / 16, DB = DH / 32;      // k16 steps of a score, 32-row blocks of the output
-  bf16x8 bq[KS], bdo[KS];
-  {
-    const int64_t off = ((int64_t)q_row * Hq + h) * DH + half * 8;
+  constexpr int KS = DH / 32, DB = DH / 16;      // k32 steps of a score, 16-row blocks of the output
+  bf16x8 bq[2][KS], bdo[2][KS];                  // [16-query block][k32 step]
+  float lse2[2], dlt[2];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) { bq[ks] = *(const bf16x8*)(q + off + ks * 16); bdo[ks] = *(const bf16x8*)(d_o + off + ks * 16); }
+  for (int b = 0; b < 2; ++b) {
+    const int q_row = min(qw0 + b * 16 + li, c - 1);
+    const int64_t off = ((int64_t)q_row * Hq + h) * DH + lg * 8;
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) { bq[b][kk] = *(const bf16x8*)(q + off + kk * 32); bdo[b][kk] = *(const bf16x8*)(d_o + off + kk * 32); }
+    const float lse_q = lse[(int64_t)h * c + q_row];
+    lse2[b] = lse_q == -INFINITY ? 0.0f : FP32_STATS<DH> ? lse_q : lse_q * LOG2E;    // a query that saw no key: every score is masked, p = exp2(-inf) = 0
+    dlt[b] = delta[(int64_t)h * c + q_row];
   }
-  const float lse_q = lse[(int64_t)h * c + q_row];
-  float lse2 = lse_q == -INFINITY ? 0.0f : FP32_STATS<DH> ? lse_q : lse_q * LOG2E;    // a query that saw no key: every score is masked, p = exp2(-inf) = 0
-  float dlt = delta[(int64_t)h * c + q_row];
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(bq[ks]), "+v"(bdo[ks]));      // (arrived: the compiler must not wait for them in the loop)
-  asm volatile("" : "+v"(lse2), "+v"(dlt));
+  for (int b = 0; b < 2; ++b) {
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) asm volatile("" : "+v"(bq[b][kk]), "+v"(bdo[b][kk]));      // (arrived: the compiler must not wait for them in the loop)
+    asm volatile("" : "+v"(lse2[b]), "+v"(dlt[b]));
+  }
   AT_WAIT_VM(0);     // from here on the loop counts its own loads only
-  const float sl = scale * LOG2E;
+  const float sl = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(scale * LOG2E)));
 
   // ---- addresses, computed once
   const uint32_t lds_k = lds_addr(&sT[0][0]) + (SPLIT ? (uint32_t)grp * 2 * STAGES * TILE : 0u);
-  constexpr uint32_t TO_V = STAGES * TILE;
-  const FragPre<DH> fp = frag_pre<DH>(lds_k);
-  const int tid = (int)threadIdx.x % LOADERS;
-  auto load_offset = [&](int i, int rows_valid) {
-    const int id = i * LOADERS + tid, row = id / (DH / 8), chunk = (id % (DH / 8)) ^ swz<DH>(row);
-    return (uint32_t)(((int64_t)min(row, rows_valid - 1) * kv_stride + chunk * 8) * 2);
-  };
+  constexpr uint32_t STAGE = 2 * TILE;           // K, then V
+  const uint32_t tid = threadIdx.x % LOADERS;
+  auto load_offset = [&](uint32_t id, uint32_t row) { return (row * (uint32_t)kv_stride + ((id % (DH / 8)) ^ (uint32_t)swz<DH>((int)(id / (DH / 8)))) * 8) * 2; };      // (within a tile)
   // loads of tile i; past the end the last tile is loaded again, so that the wait counts stay the same.  The last tile may be short: its rows
-  // past the end re-read the last one.
-  const int t_max = n_tiles - 1;
-  uint32_t voff[LOADS], voff_last[LOADS];
-#pragma unroll
-  for (int j = 0; j < LOADS; ++j) { voff[j] = pin(load_offset(j, NK)); voff_last[j] = pin(load_offset(j, min(NK, n_total - t_max * NK))); }
+  // past the end re-read the last one.  (Load j: LOADERS / (DH / 8) rows, a multiple of 16, further.)
+  constexpr int ROWS_J = LOADERS / (DH / 8);
+  const int t_max = n_tiles - 1, row_last = n_total - 1 - t_max * NK;
+  const uint32_t voff = pin(load_offset(tid, tid / (DH / 8)));
   const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_k + (uint32_t)(tid & ~63) * 16u), tile_bytes = (uint32_t)(NK * kv_stride * 2);
-  auto issue = [&](int i, int stage) __attribute__((always_inline)) {
+  auto issue = [&](int i) __attribute__((always_inline)) {
     const int t = min(tile_of(i), t_max);
     const char *ks = (const char*)kbase + (uint64_t)tile_bytes * (uint32_t)t, *vs = (const char*)vbase + (uint64_t)tile_bytes * (uint32_t)t;
+    const uint32_t to = dst + (uint32_t)(i % STAGES) * STAGE;
+    if (t < t_max || row_last >= NK - 1) {
 #pragma unroll
-    for (int j = 0; j < LOADS; ++j) {
-      const uint32_t off = t == t_max ? voff_last[j] : voff[j], to = dst + (uint32_t)(stage * TILE + j * LOADERS * 16);
-      dma16(ks, off, to);
-      dma16(vs, off, to + TO_V);
+      for (int j = 0; j < LOADS; ++j) {
+        const int64_t rows = (int64_t)j * ROWS_J * kv_stride * 2;
+        dma16(ks + rows, voff, to + (uint32_t)(j * LOADERS * 16));
+        dma16(vs + rows, voff, to + (uint32_t)(TILE + j * LOADERS * 16));
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < LOADS; ++j) {
+        const uint32_t id = pin(threadIdx.x) % LOADERS;      // (opaque: nothing of this is kept in a register from tile to tile)
+        const uint32_t off = load_offset(id, min(id / (DH / 8) + j * ROWS_J, (uint32_t)row_last));
+        dma16(ks, off, to + (uint32_t)(j * LOADERS * 16));
+        dma16(vs, off, to + (uint32_t)(TILE + j * LOADERS * 16));
+      }
     }
   };
   // steps in which some (query, key) pair of the wave is visible
   const int step_t = SPLIT ? 2 : 1, first_t = tile_of(0);
   const int act0 = max(0, (wave_lo_min / NK - first_t + step_t - 1) / step_t);
   const int act1 = qw0 < c && wave_last_key >= 0 ? min(n_it, (wave_last_key / NK - first_t + step_t) / step_t) : 0;
-  auto active = [&](int i) { return i >= act0 && i < act1; };
 
-  struct Scores { f32x16 s[NB], dp[NB]; };
-  struct Operand { bf16x8 w[TERMS<DH>][NB][2]; };      // dS^T: [term][key block][k16 step]
-  f32x16 acc[DB];
+  // LDS addresses of fragments, one step after the other: of K (and V) rows of the present tile, of K transposed of the previous one
+  uint32_t fr[KS], ft[DB];
 #pragma unroll
-  for (int i = 0; i < DB; ++i) acc[i] = zero16();
-  auto second = [&](const Operand& ds, int stage) __attribute__((always_inline)) {
-    const uint32_t so = (uint32_t)(stage * TILE);
-    mfma_chain<NB * 2 * DB, DQ_CHAIN>(
-        [&](int n) { const uint32_t o = so + (n / DB * 16) * (DH * 2); return lds_tr(fp.tr[n % DB * 2] + o, fp.tr[n % DB * 2 + 1] + o); },
+  for (int kk = 0; kk < KS; ++kk) fr[kk] = pin(lds_k + frag16_rows<DH>(kk) + (uint32_t)(act0 % STAGES) * STAGE);
+#pragma unroll
+  for (int d = 0; d < DB; ++d) ft[d] = pin(lds_k + frag16_tr<DH>(d) + (uint32_t)(act0 % STAGES) * STAGE);
+  auto to_next = [&](int i) { return i % STAGES == STAGES - 1 ? (uint32_t)-(int)((STAGES - 1) * STAGE) : STAGE; };      // from the stage of tile i
+
+  struct Scores { f32x4 s[2][NB], dp[2][NB]; };        // S^T, dP^T [query block][16 keys]
+  struct Operand { bf16x8 w[TERMS<DH>][2][NB / 2]; };  // dS^T: [term][query block][k32 step]
+  f32x4 acc[2][DB];                                    // dQ^T [query block][16 head_dim rows]
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int d = 0; d < DB; ++d) acc[b][d] = f32x4{0.f, 0.f, 0.f, 0.f};
+  constexpr uint32_t ROWS16 = 16 * DH * 2;
+  auto second = [&](const Operand& ds, int i) __attribute__((always_inline)) {
+    // n = k32 step * DB + head_dim block
+    mfma_chain<NB / 2 * DB, DQ_CHAIN>(
+        [&](int n) { const uint32_t o = (uint32_t)(n / DB) * 2 * ROWS16; return lds_tr(ft[n % DB] + o, ft[n % DB] + (o + ROWS16)); },
         [&](int n, const bf16x8& f) {
 #pragma unroll
-          for (int t = 0; t < TERMS<DH>; ++t) acc[n % DB] = MFMA(f, ds.w[t][n / DB >> 1][n / DB & 1], acc[n % DB]);
+          for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int t = 0; t < TERMS<DH>; ++t) acc[b][n % DB] = MFMA16(f, ds.w[t][b][n / DB], acc[b][n % DB]);
         });
+    const uint32_t move = to_next(i);
+#pragma unroll
+    for (int d = 0; d < DB; ++d) ft[d] = pin(ft[d] + move);
   };
-  auto first = [&](Scores& x, int stage) __attribute__((always_inline)) {
-    const uint32_t so = (uint32_t)(stage * TILE);
+  auto first = [&](Scores& x, int i) __attribute__((always_inline)) {
 #pragma unroll
-    for (int b = 0; b < NB; ++b) { x.s[b] = zero16(); x.dp[b] = zero16(); }
-    // n = k16 step * 2 NB + which: S of the blocks, then dP of the blocks
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int kb = 0; kb < NB; ++kb) { x.s[b][kb] = f32x4{0.f, 0.f, 0.f, 0.f}; x.dp[b][kb] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+    // n = k32 step * 2 NB + which: S of the key blocks, then dP of the key blocks
     mfma_chain<2 * NB * KS, DQ_CHAIN>(
-        [&](int n) { const int b = n % (2 * NB); return lds_b128(fp.rows[n / (2 * NB)] + so + (b >= NB ? TO_V : 0u) + b % NB * 32 * (DH * 2)); },
+        [&](int n) { const int kb = n % (2 * NB); return lds_b128(fr[n / (2 * NB)] + (kb >= NB ? (uint32_t)TILE : 0u) + (uint32_t)(kb % NB) * ROWS16); },
         [&](int n, const bf16x8& f) {
-          const int b = n % (2 * NB), ks = n / (2 * NB);
-          if (b < NB) x.s[b] = MFMA(f, bq[ks], x.s[b]); else x.dp[b - NB] = MFMA(f, bdo[ks], x.dp[b - NB]);
+          const int kb = n % (2 * NB), kk = n / (2 * NB);
+#pragma unroll
+          for (int b = 0; b < 2; ++b)
+            if (kb < NB) x.s[b][kb] = MFMA16(f, bq[b][kk], x.s[b][kb]); else x.dp[b][kb - NB] = MFMA16(f, bdo[b][kk], x.dp[b][kb - NB]);
         });
+    const uint32_t move = to_next(i);
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) fr[kk] = pin(fr[kk] + move);
   };
   auto vector = [&](Scores& x, Operand& ds, int i) __attribute__((always_inline)) {
     const int k0 = tile_of(i) * NK;
     if (k0 + NK - 1 > wave_first_qpos || k0 < wave_lo_max) {      // only tiles on an edge of the visible range pay for the mask
-      // key 4 half + e of the tile is visible for first <= e < first + n: one unsigned comparison
-      const int from = lo_q - k0 - 4 * half;
-      const uint32_t n = (uint32_t)max(0, qpos - lo_q + 1);
+      const int l = (int)pin(threadIdx.x) & 63;
 #pragma unroll
-      for (int b = 0; b < NB; ++b)
+      for (int b = 0; b < 2; ++b) {
+        // key 4 lg + e of the tile is visible for first <= e < first + n: one unsigned comparison
+        const int qpos = q_start + min(qw0 + b * 16 + (l & 15), c - 1), lo = first_key(qpos), from = lo - k0 - 4 * (l >> 4);
+        const uint32_t n = (uint32_t)max(0, qpos - lo + 1);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          x.s[b][r] = (uint32_t)(b * 32 + acc_row(r, 0) - from) < n ? x.s[b][r] : -INFINITY;     // exp2(-inf) = 0
-          if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+        for (int kb = 0; kb < NB; ++kb) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) x.s[b][kb][r] = (uint32_t)(kb * 16 + r - from) < n ? x.s[b][kb][r] : -INFINITY;     // exp2(-inf) = 0
+          __builtin_amdgcn_sched_barrier(0);
         }
+      }
     }
 #pragma unroll
-    for (int b = 0; b < NB; ++b)
+    for (int b = 0; b < 2; ++b)
 #pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
+      for (int ks = 0; ks < NB / 2; ++ks) {
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          const float p = exp_of<DH>(x.s[b][8 * ks + e], scale, sl, -lse2);
-          x.s[b][8 * ks + e] = p * (x.dp[b][8 * ks + e] - dlt);                          // dS^T (the factor `scale` is applied at the end)
+          const int kb = 2 * ks + (e >> 2), r = e & 3;
+          const float p = exp_of<DH>(x.s[b][kb][r], scale, sl, -lse2[b]);
+          const float y = p * (x.dp[b][kb][r] - dlt[b]);                          // dS^T (the factor `scale` is applied at the end)
+          ds.w[0][b][ks][e] = (bf16_t)y;
+          if (TERMS<DH> == 2) ds.w[TERMS<DH> - 1][b][ks][e] = (bf16_t)(y - (float)ds.w[0][b][ks][e]);
         }
-        ds.w[0][b][ks] = pack8(x.s[b], ks);
-        if (TERMS<DH> == 2) ds.w[TERMS<DH> - 1][b][ks] = rest8(x.s[b], ks, ds.w[0][b][ks]);
       }
+    __builtin_amdgcn_sched_barrier(0);
   };
 
   if (n_it > 0) {
-    auto run = [&](auto grp_c) __attribute__((always_inline)) {
-      // Before a tile is read every wave has waited for its own share of it and a barrier has passed: tile j + 1 by the end of vector slot j, or,
-      // where group 1 loads for group 0 as well, by the end of its multiply slot j; what was issued after it stays in flight.  A stage is
-      // loaded again once the slot is over in which its K was last read, for the second product: by group 0 two tiles ahead, as group 1 reads
-      // K of tile j - 2 in the slot before vector slot j of group 0; else three.
-      constexpr bool G1 = decltype(grp_c)::value;
-      constexpr int AHEAD = SPLIT || G1 ? 3 : 2, PAIR = 2 * LOADS;
-#pragma unroll
-      for (int j = 0; j < AHEAD; ++j) issue(j, j);
-      AT_WAIT_VM(PAIR * (AHEAD - 1));
-      AT_SLOT_BARRIER();
-      if (G1) AT_SLOT_BARRIER();
-      // What a skipped tile leaves in ds: any value, read by nothing (`held`).  Keeping the last one instead takes more registers than there are (14 spilled);
-      // zeros are instructions.
-      auto any_operand = []() __attribute__((always_inline)) {
-        Operand x;
-#pragma unroll
-        for (int t = 0; t < TERMS<DH>; ++t)
-#pragma unroll
-          for (int b = 0; b < NB; ++b)
-#pragma unroll
-            for (int ks = 0; ks < 2; ++ks) x.w[t][b][ks] = __builtin_nondeterministic_value(bf16x8{});
-        return x;
-      };
-      Operand ds = any_operand();      // of the previous tile
-      bool held = false;               // there is one
-      auto step = [&](int i, int stage) __attribute__((always_inline)) {      // stage = i % 4, a constant
-        const bool act = active(i);
-        Scores x;                // (used where the tile is not skipped)
-        Operand next = any_operand();
-        __builtin_amdgcn_s_setprio(1);
-        if (held) second(ds, (stage + 3) % STAGES);
-        if (act) first(x, stage);
-        __builtin_amdgcn_s_setprio(0);
-        if (!SPLIT && G1) AT_WAIT_VM(PAIR);
-        AT_SLOT_BARRIER();
-        issue(i + AHEAD, (stage + AHEAD) % STAGES);
-        if (act) vector(x, next, i);
-        ds = next;
-        held = act;
-        if (SPLIT || !G1) AT_WAIT_VM(PAIR * (AHEAD - 1));
-        AT_SLOT_BARRIER();
-      };
-      // whole groups of four steps (a step past the last tile loads that tile again and passes its barriers)
-      int i = 0;
-      for (; i < n_it; i += 4) {
-        step(i, 0);
-        step(i + 1, 1);
-        step(i + 2, 2);
-        step(i + 3, 3);
-      }
-      if (held) second(ds, 3);
-      AT_WAIT_VM(0);
-      if (!G1) AT_SLOT_BARRIER();        // both groups execute the same number of barriers
+    // Before a tile is read every wave has waited for its own share of it and a barrier has passed: tile j + 1 by the end of vector slot j, or,
+    // where group 1 loads for group 0 as well, by the end of its multiply slot j; what was issued after it stays in flight.  A stage is
+    // loaded again once the slot is over in which its K was last read, for the second product: by group 0 two tiles ahead, as group 1 reads
+    // K of tile j - 2 in the slot before vector slot j of group 0; else three.
+    constexpr int PAIR = 2 * LOADS;
+    const bool late = !SPLIT && grp == 1;
+    const int ahead = SPLIT || late ? 3 : 2;
+    auto wait_late = [&]() __attribute__((always_inline)) { if (late) AT_WAIT_VM(PAIR); };
+    auto wait_early = [&]() __attribute__((always_inline)) {
+      if (SPLIT) AT_WAIT_VM(2 * PAIR);
+      else if (!late) AT_WAIT_VM(PAIR);
     };
-    if (grp == 0) run(std::false_type{});
-    else run(std::true_type{});
+    for (int j = 0; j < ahead; ++j) issue(j);
+    if (late) AT_WAIT_VM(2 * PAIR);
+    wait_early();
+    AT_SLOT_BARRIER();
+    if (grp == 1) AT_SLOT_BARRIER();
+    int i = 0;
+    auto into_vector = [&]() __attribute__((always_inline)) {
+      __builtin_amdgcn_s_setprio(0);
+      wait_late();
+      AT_SLOT_BARRIER();
+      issue(i + ahead);
+    };
+    auto into_multiply = [&]() __attribute__((always_inline)) {
+      wait_early();
+      AT_SLOT_BARRIER();
+      ++i;
+    };
+    auto skip = [&]() __attribute__((always_inline)) { into_vector(); into_multiply(); };      // a tile that no query of the wave sees
+    while (i < min(act0, n_it)) skip();
+    if (i < act1) {
+      __builtin_amdgcn_s_setprio(1);
+      do {
+        Scores x;
+        Operand ds;
+        first(x, i);
+        into_vector();
+        vector(x, ds, i);
+        into_multiply();
+        __builtin_amdgcn_s_setprio(1);
+        second(ds, i - 1);
+      } while (i < act1);
+      __builtin_amdgcn_s_setprio(0);
+    }
+    while (i < n_it) skip();
+    AT_WAIT_VM(0);
+    if (grp == 0) AT_SLOT_BARRIER();        // both groups execute the same number of barriers
   }
 
   if constexpr (SPLIT) {
     __syncthreads();
-    float* mine = (float*)&sT[0][0] + (wave & 3) * (DB * 16 * 64) + lane;      // [float][lane]
+    float* mine = (float*)&sT[0][0] + (wave & 3) * (DB * 8 * 64) + lane;      // [float][lane]
     if (grp == 1) {
 #pragma unroll
-      for (int i = 0; i < DB * 16; ++i) mine[i * 64] = acc[i >> 4][i & 15];
+      for (int i = 0; i < DB * 8; ++i) mine[i * 64] = acc[i / (DB * 4)][(i >> 2) % DB][i & 3];
     }
     __syncthreads();
     if (grp == 1) return;
 #pragma unroll
-    for (int i = 0; i < DB * 16; ++i) acc[i >> 4][i & 15] += mine[i * 64];
+    for (int i = 0; i < DB * 8; ++i) acc[i / (DB * 4)][(i >> 2) % DB][i & 3] += mine[i * 64];
   }
-  if (q_valid) {
-    bf16_t* op = dq + ((int64_t)my_q * Hq + h) * DH;
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    const int my_q = qw0 + b * 16 + li;
+    if (my_q >= c) continue;
+    bf16_t* op = dq + ((int64_t)my_q * Hq + h) * DH + 4 * lg;
     if (rope) {
-      // adjoint of the rotary embedding on the way out: element j < DH / 2 (accumulator block i < DB / 2) pairs with
-      // j + DH / 2 (block i + DB / 2, same register of the same lane); rotation by the negative angle
-      const float2* tr = rope + (int64_t)my_q * (DH / 2) + 4 * half;
+      // adjoint of the rotary embedding on the way out: element j < DH / 2 (accumulator block d < DB / 2) pairs with
+      // j + DH / 2 (block d + DB / 2, same register of the same lane); rotation by the negative angle
+      const float2* tr = rope + (int64_t)my_q * (DH / 2) + 4 * lg;
 #pragma unroll
-      for (int i = 0; i < DB / 2; ++i)
+      for (int d = 0; d < DB / 2; ++d) {
+        bf16x4 w1, w2;
 #pragma unroll
-        for (int a = 0; a < 4; ++a) {
-          bf16x4 w1, w2;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float2 cs = tr[i * 32 + 8 * a + e];
-            const float d1 = acc[i][4 * a + e] * scale, d2 = acc[i + DB / 2][4 * a + e] * scale;
-            w1[e] = (bf16_t)(d1 * cs.x + d2 * cs.y);
-            w2[e] = (bf16_t)(d2 * cs.x - d1 * cs.y);
-          }
-          *(bf16x4*)(op + i * 32 + 8 * a + 4 * half) = w1;
-          *(bf16x4*)(op + (i + DB / 2) * 32 + 8 * a + 4 * half) = w2;
+        for (int r = 0; r < 4; ++r) {
+          const float2 cs = tr[d * 16 + r];
+          const float d1 = acc[b][d][r] * scale, d2 = acc[b][d + DB / 2][r] * scale;
+          w1[r] = (bf16_t)(d1 * cs.x + d2 * cs.y);
+          w2[r] = (bf16_t)(d2 * cs.x - d1 * cs.y);
         }
+        *(bf16x4*)(op + d * 16) = w1;
+        *(bf16x4*)(op + (d + DB / 2) * 16) = w2;
+      }
     } else {
 #pragma unroll
-      for (int i = 0; i < DB; ++i)
+      for (int d = 0; d < DB; ++d) {
+        bf16x4 w;
 #pragma unroll
-        for (int a = 0; a < 4; ++a) {
-          bf16x4 w;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) w[e] = (bf16_t)(acc[i][4 * a + e] * scale);
-          *(bf16x4*)(op + i * 32 + 8 * a + 4 * half) = w;
-        }
+        for (int r = 0; r < 4; ++r) w[r] = (bf16_t)(acc[b][d][r] * scale);
+        *(bf16x4*)(op + d * 16) = w;
+      }
     }
   }
 }
@@ -927,9 +909,10 @@ __global__ __launch_bounds__(AT_THREADS) void attn_bwd_dq_mfma_k(const bf16_t* _
 // multiply (dV += dO^T P resp. dK += Q^T dS of the previous tile, S = Q K^T resp. dP = dO V^T of this one) and vector work; role S runs
 // one slot behind role P - it then finds the P of its tile in LDS - so on every SIMD one wave multiplies while the other works on
 // exponentials or dS.  Four stages of the Q / dO tiles; role P loads two tiles ahead, role S three.
-// What bounds it: as in the forward kernel, vector work and MFMAs of a SIMD's two waves share the issue port.  Last 2048-query chunk of 32k,
-// 28 / 4 heads: dQ + dK/dV 3.08 -> 2.95 ms, all of it here (about 1.85 -> 1.72), against one barrier per tile and each wave doing its
-// products and its vector work in any order.
+// What bounds it: as in the forward kernel, vector work and MFMAs of a SIMD's two waves share the issue port, and the power limit leaves 2.0 GHz.  Last
+// 2048-query chunk of 32k, 28 / 4 heads: dQ + dK/dV 3.08 -> 2.95 ms, all of it here (about 1.85 -> 1.72), against one barrier per tile and each wave doing its
+// products and its vector work in any order; 1740 -> 1655 us with 16x16x32 MFMAs in place of 32x32x16, -> 1610 with a loop whose stages move with the
+// addresses in place of four steps unrolled (a quarter of the code).  Half of its LDS reads left out: 1745 -> 1630, its exponentials left out: 1705.
 // The loop walks the query tiles at or below the diagonal and, for each, the query heads of the group.
 //
 // Its steps come in `slices` shares, whose sums are added to dK / dV in their order.  Where there is room for them a workgroup takes each share
@@ -971,54 +954,50 @@ __device__ __forceinline__ void dkv_block(DkvShared<DH>& sh, int key_block, int 
 
   const int G = Hq / Hkv;
   const int key0 = (key_block0 + key_block) * KV_TILE;   // key blocks before key_block0 are visible to no query
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, half = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
   const int kb = wave & 3;
   const bool role_p = wave < 4;
   const int n_total = q_start + c;
-  const int kw0 = key0 + kb * 32;
-  const int my_key = kw0 + (lane & 31);
-  const int key_row = min(my_key, n_total - 1);
+  const int kw0 = key0 + kb * 32;      // a lane has the keys li and 16 + li from there on
+  auto key_of = [&](int b) { return kw0 + b * 16 + li; };
+  auto key_row = [&](int b) { return (int64_t)min(key_of(b), n_total - 1); };
   const int64_t kv_stride = (int64_t)Hkv * DH;
   const int64_t q_stride = (int64_t)Hq * DH;
 
   // Fragment addresses: one set reaches all stages of its operand with immediate offsets.  Role P reads Q row-wise and dO
   // transposed, role S the other way round; only the half of each set that the role uses stays live.
   const uint32_t lds0 = lds_addr(&sQD[0][0][0]), lds_do = lds0 + KV_STAGES * TILE64<DH>;
-  const FragPre<DH> fr = frag_pre<DH>(role_p ? lds0 : lds_do);                 // row-wise operand: Q (P) / dO (S)
-  const FragPre<DH> gt = frag_pre<DH>(role_p ? lds_do : lds0);                 // transposed operand: dO (P) / Q (S)
+  constexpr int KS = DH / 32, DB = DH / 16 / (IN_TURN ? 2 : 1);      // k32 steps of a score, 16-row blocks of the output
+  const int col0 = IN_TURN ? slice * (DH / 2) : 0;       // IN_TURN: `slice` is the half of the columns
   const TileLoad<DH, KV_THREADS> tl = tile_load_pre<DH, KV_THREADS>(q_stride);
   const uint32_t sp_lane = pin(lds_addr(&sP[kb][0][lane]));                      // + slot * 1024
-  const uint32_t stat_lane = pin(lds_addr(role_p ? &sL[0][4 * half] : &sDl[0][4 * half]));   // + stage * 256 + (b * 32 + 8 a) * 4
+  const uint32_t stat_lane = pin(lds_addr(role_p ? &sL[0][4 * lg] : &sDl[0][4 * lg]));   // + stage * 256 + query block * 64
 
-  constexpr int KS = DH / 16, DB = DH / 32 / (IN_TURN ? 2 : 1);
-  const int col0 = IN_TURN ? slice * (DH / 2) : 0;       // IN_TURN: `slice` is the half of the columns
-  uint32_t g_tr[2 * DB];
-#pragma unroll
-  for (int i = 0; i < 2 * DB; ++i) g_tr[i] = IN_TURN && slice ? gt.tr[(2 * DB + i) % (DH / 16)] : gt.tr[i];
-  // what this lane's key grows by, rows = head_dim col0 + 32 i + 8 a + 4 half .. + 3
-  float* out = (role_p ? dv : dk) + (int64_t)key_row * kv_stride + (int64_t)kvh * DH + col0;
-  f32x16 sum[IN_TURN ? DB : 1];
+  // what this lane's keys grow by, rows = head_dim col0 + 16 d + 4 lg .. + 3
+  auto out_of = [&](int b) { return (role_p ? dv : dk) + key_row(b) * kv_stride + (int64_t)kvh * DH + col0 + 4 * lg; };
+  f32x4 sum[2][IN_TURN ? DB : 1];
   if constexpr (IN_TURN) {
 #pragma unroll
-    for (int i = 0; i < DB; ++i)
+    for (int b = 0; b < 2; ++b)
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        const f32x4 u = *(const f32x4*)(out + i * 32 + 8 * a + 4 * half);
+      for (int d = 0; d < DB; ++d) sum[b][d] = *(const f32x4*)(out_of(b) + d * 16);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) sum[i][4 * a + e] = u[e];
-      }
+    for (int b = 0; b < 2; ++b)
 #pragma unroll
-    for (int i = 0; i < DB; ++i) asm volatile("" : "+v"(sum[i]));
+      for (int d = 0; d < DB; ++d) asm volatile("" : "+v"(sum[b][d]));
   }
-  bf16x8 breg[KS];   // B operand of the first product: K rows (role P) or V rows (role S) of my key
-  {
-    const bf16_t* src = (role_p ? k : v) + (int64_t)key_row * kv_stride + (int64_t)kvh * DH + half * 8;
+  bf16x8 breg[2][KS];   // B operand of the first product: K rows (role P) or V rows (role S) of my keys
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) breg[ks] = *(const bf16x8*)(src + ks * 16);
+  for (int b = 0; b < 2; ++b) {
+    const bf16_t* src = (role_p ? k : v) + key_row(b) * kv_stride + (int64_t)kvh * DH + lg * 8;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(breg[ks]));   // (arrived: the compiler must not wait for them in the loop)
-    AT_WAIT_VM(0);
+    for (int kk = 0; kk < KS; ++kk) breg[b][kk] = *(const bf16x8*)(src + kk * 32);
   }
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) asm volatile("" : "+v"(breg[b][kk]));   // (arrived: the compiler must not wait for them in the loop)
+  AT_WAIT_VM(0);
   const float sl = scale * LOG2E;
 
   // query tiles that can see at least one key of this workgroup: query position >= key0
@@ -1058,95 +1037,123 @@ __device__ __forceinline__ void dkv_block(DkvShared<DH>& sh, int key_block, int 
   auto run = [&](auto role_c) __attribute__((always_inline)) {
     constexpr bool RP = decltype(role_c)::value;
     constexpr int NT = KV_TERMS<DH>;
-    f32x16 acc[DB];          // dV^T (role P) or dK^T (role S): rows = head_dim, column = my key
-    f32x16 t[2];             // S or dP of the tile's two 32-query blocks: column = my key, rows = queries b * 32 + acc_row(r, half)
-    bf16x8 w[NT][2][2];      // P or dS: [term][query block][k16 step]
+    f32x4 acc[2][DB];        // dV^T (role P) or dK^T (role S): [16-key block][16 head_dim rows], column = my key
+    f32x4 t[2][4];           // S or dP of the tile: [key block][16-query block], rows = queries 4 lg + r of the block
+    bf16x8 w[NT][2][2];      // P or dS: [term][key block][k32 step]
 #pragma unroll
-    for (int i = 0; i < DB; ++i) acc[i] = zero16();
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int d = 0; d < DB; ++d) acc[b][d] = f32x4{0.f, 0.f, 0.f, 0.f};
     const float f = RP ? 1.0f : scale;
     int present = 0, present_end = IN_TURN ? share(1) : 0;      // IN_TURN: the share that is being summed, and the step after it
     auto close = [&]() __attribute__((always_inline)) {         // total += the share's sum
 #pragma unroll
-      for (int i = 0; i < (IN_TURN ? DB : 0); ++i)
+      for (int i = 0; i < (IN_TURN ? 2 * DB : 0); ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
+        for (int r = 0; r < 4; ++r) {
 #pragma clang fp contract(off)      // product and sum rounded separately, with or without parts
-          sum[i][r] += acc[i][r] * f;
-          acc[i][r] = 0.f;
+          sum[i / DB][i % DB][r] += acc[i / DB][i % DB][r] * f;
+          acc[i / DB][i % DB][r] = 0.f;
         }
     };
-    int qbase = (qt_first + it0 / G) * QT, head = it0 % G;      // of the present step's tile
-    bool held = false;                                          // the previous tile left something to multiply
-    auto second = [&](int stage) __attribute__((always_inline)) {
-      const uint32_t so = (uint32_t)(stage * TILE64<DH>);
-      mfma_chain<4 * DB, CHAIN>(
-          [&](int n) { const uint32_t o = so + (n / DB * 16) * (DH * 2); return lds_tr(g_tr[n % DB * 2] + o, g_tr[n % DB * 2 + 1] + o); },
+    int j = 0, qbase = (qt_first + it0 / G) * QT, head = it0 % G;      // the present step, of its tile
+    // LDS addresses of fragments, one step after the other: of the row-wise operand of the present tile, Q (P) / dO (S), and of the transposed
+    // one, dO (P) / Q (S), of the previous tile
+    uint32_t fr[KS], gt[DB];
+    auto to_next = [&](int step) { return step % KV_STAGES == KV_STAGES - 1 ? (uint32_t)-(int)((KV_STAGES - 1) * TILE64<DH>) : (uint32_t)TILE64<DH>; };      // from its stage
+    constexpr uint32_t ROWS16 = 16 * DH * 2;
+    auto second = [&]() __attribute__((always_inline)) {
+      // n = k32 step * DB + head_dim block
+      mfma_chain<2 * DB, CHAIN>(
+          [&](int n) { const uint32_t o = (uint32_t)(n / DB) * 2 * ROWS16; return lds_tr(gt[n % DB] + o, gt[n % DB] + (o + ROWS16)); },
           [&](int n, const bf16x8& g) {
 #pragma unroll
-            for (int u = 0; u < NT; ++u) acc[n % DB] = MFMA(g, w[u][n / DB >> 1][n / DB & 1], acc[n % DB]);
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+              for (int u = 0; u < NT; ++u) acc[b][n % DB] = MFMA16(g, w[u][b][n / DB], acc[b][n % DB]);
           });
+      const uint32_t move = to_next(j - 1);
+#pragma unroll
+      for (int d = 0; d < DB; ++d) gt[d] = pin(gt[d] + move);
     };
-    auto first = [&](int stage) __attribute__((always_inline)) {
-      const uint32_t so = (uint32_t)(stage * TILE64<DH>);
-      t[0] = zero16();
-      t[1] = zero16();
-      mfma_chain<2 * KS, CHAIN>([&](int n) { return lds_b128(fr.rows[n >> 1] + so + (n & 1) * 32 * (DH * 2)); },
-                                [&](int n, const bf16x8& f) { t[n & 1] = MFMA(f, breg[n >> 1], t[n & 1]); });
+    auto first = [&]() __attribute__((always_inline)) {
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int qb = 0; qb < 4; ++qb) t[b][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
+      // n = k32 step * 4 + query block
+      mfma_chain<4 * KS, CHAIN>([&](int n) { return lds_b128(fr[n >> 2] + (uint32_t)(n & 3) * ROWS16); },
+                                [&](int n, const bf16x8& g) {
+#pragma unroll
+                                  for (int b = 0; b < 2; ++b) t[b][n & 3] = MFMA16(g, breg[b][n >> 2], t[b][n & 3]);
+                                });
+      const uint32_t move = to_next(j);
+#pragma unroll
+      for (int kk = 0; kk < KS; ++kk) fr[kk] = pin(fr[kk] + move);
     };
     auto terms = [&](int b, int ks) __attribute__((always_inline)) {      // P resp. dS as operands of the second product
-      w[0][b][ks] = pack8(t[b], ks);
-      if constexpr (NT == 3) {
-        w[1][b][ks] = rest8(t[b], ks, w[0][b][ks]);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) w[2][b][ks][e] = (bf16_t)((t[b][8 * ks + e] - (float)w[0][b][ks][e]) - (float)w[1][b][ks][e]);
+      for (int e = 0; e < 8; ++e) {
+        const float x = t[b][2 * ks + (e >> 2)][e & 3];
+        w[0][b][ks][e] = (bf16_t)x;
+        if constexpr (NT == 3) {
+          w[1][b][ks][e] = (bf16_t)(x - (float)w[0][b][ks][e]);
+          w[2][b][ks][e] = (bf16_t)((x - (float)w[0][b][ks][e]) - (float)w[1][b][ks][e]);
+        }
       }
     };
-    auto vector = [&](int stage) __attribute__((always_inline)) {
+    auto vector = [&]() __attribute__((always_inline)) {
+      const uint32_t stat = stat_lane + (uint32_t)(j % KV_STAGES) * QT * 4;
       if constexpr (RP) {
         const bool diag = (q_start + qbase < kw0 + 31) || (qbase + QT > c) || kw0 < kv_first ||   // some pair masked, or ragged query tile
                           (window > 0 && q_start + qbase + QT - 1 - window >= kw0);
         if (diag) {
 #pragma unroll
-          for (int b = 0; b < 2; ++b)
+          for (int b = 0; b < 2; ++b) {
+            // query 4 lg + e of the tile sees the key for from <= e < from + n: one unsigned comparison
+            const int key = key_of(b), lo = max(0, key - q_start), hi = window > 0 ? min(c, key + min(window, n_total) - q_start) : c;
+            const uint32_t n = key < kv_first ? 0u : (uint32_t)max(0, hi - lo);
+            const int from = lo - qbase - 4 * lg;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const int qi = qbase + b * 32 + acc_row(r, half);
-              if (qi >= c || my_key > q_start + qi || my_key < kv_first || (window > 0 && my_key <= q_start + qi - window))
-                t[b][r] = -INFINITY;                                          // exp2(-inf) = 0
-              if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);            // (few comparisons at a time: scalar registers)
+            for (int qb = 0; qb < 4; ++qb) {
+#pragma unroll
+              for (int r = 0; r < 4; ++r) t[b][qb][r] = (uint32_t)(qb * 16 + r - from) < n ? t[b][qb][r] : -INFINITY;      // exp2(-inf) = 0
+              __builtin_amdgcn_sched_barrier(0);
             }
+          }
         }
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
+        for (int ks = 0; ks < 2; ++ks) {
 #pragma unroll
-          for (int a = 0; a < 4; ++a) {
-            const float4 l4 = lds_f4(stat_lane + stage * QT * 4 + (b * 32 + 8 * a) * 4);
+          for (int x = 0; x < 2; ++x) {
+            const int qb = 2 * ks + x;
+            const float4 l4 = lds_f4(stat + qb * 64);
             const float lv[4] = {l4.x, l4.y, l4.z, l4.w};
 #pragma unroll
-            for (int e = 0; e < 4; ++e) t[b][4 * a + e] = exp_of<DH>(t[b][4 * a + e], scale, sl, -lv[e]);
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+              for (int r = 0; r < 4; ++r) t[b][qb][r] = exp_of<DH>(t[b][qb][r], scale, sl, -lv[r]);
           }
 #pragma unroll
-          for (int ks = 0; ks < 2; ++ks) {
+          for (int b = 0; b < 2; ++b) {
             terms(b, ks);
             if constexpr (!FP32_STATS<DH>)
               *(bf16x8*)(__attribute__((address_space(3))) char*)(uintptr_t)(sp_lane + (b * 2 + ks) * 1024) = w[0][b][ks];
-          }
-          if constexpr (FP32_STATS<DH>) {
+            else {
 #pragma unroll
-            for (int a = 0; a < 4; ++a)
-              *(f32x4*)(__attribute__((address_space(3))) char*)(uintptr_t)(sp_lane + (b * 4 + a) * 1024) =
-                  f32x4{t[b][4 * a], t[b][4 * a + 1], t[b][4 * a + 2], t[b][4 * a + 3]};
+              for (int x = 0; x < 2; ++x)
+                *(f32x4*)(__attribute__((address_space(3))) char*)(uintptr_t)(sp_lane + (b * 4 + 2 * ks + x) * 1024) = t[b][2 * ks + x];
+            }
           }
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // P is in LDS before the barrier
       } else {
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int ks = 0; ks < 2; ++ks) {
+          const float4 d0 = lds_f4(stat + ks * 128), d1 = lds_f4(stat + ks * 128 + 64);
+          const float dl[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
 #pragma unroll
-          for (int ks = 0; ks < 2; ++ks) {
-            const float4 d0 = lds_f4(stat_lane + stage * QT * 4 + (b * 32 + 16 * ks) * 4);
-            const float4 d1 = lds_f4(stat_lane + stage * QT * 4 + (b * 32 + 16 * ks + 8) * 4);
-            const float dl[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
+          for (int b = 0; b < 2; ++b) {
             float pv[8];
             if constexpr (FP32_STATS<DH>) {
               const float4 p0 = lds_f4(sp_lane + (b * 4 + 2 * ks) * 1024), p1 = lds_f4(sp_lane + (b * 4 + 2 * ks + 1) * 1024);
@@ -1157,9 +1164,13 @@ __device__ __forceinline__ void dkv_block(DkvShared<DH>& sh, int key_block, int 
               for (int e = 0; e < 8; ++e) pv[e] = (float)p8[e];
             }
 #pragma unroll
-            for (int e = 0; e < 8; ++e) t[b][8 * ks + e] = pv[e] * (t[b][8 * ks + e] - dl[e]);     // dS (the softmax scale is applied once at the end)
+            for (int e = 0; e < 8; ++e) {
+              f32x4& x = t[b][2 * ks + (e >> 2)];
+              x[e & 3] = pv[e] * (x[e & 3] - dl[e]);     // dS (the softmax scale is applied once at the end)
+            }
             terms(b, ks);
           }
+        }
       }
     };
     if (n_iter > 0) {
@@ -1168,64 +1179,74 @@ __device__ __forceinline__ void dkv_block(DkvShared<DH>& sh, int key_block, int 
       // behind, at the end of multiply slot j; the one tile issued after it stays in flight.
       constexpr int AHEAD = RP ? 2 : 3;
 #pragma unroll
-      for (int j = 0; j < AHEAD; ++j) issue(j);
+      for (int a = 0; a < AHEAD; ++a) issue(a);
       AT_WAIT_VM(LOADS * (AHEAD - 1));
       AT_SLOT_BARRIER();
       if (!RP) AT_SLOT_BARRIER();
-      auto step = [&](int j, int stage) __attribute__((always_inline)) {      // stage = j % 4, a constant
-        const bool act = j < n_iter && tile_active(qbase);
-        __builtin_amdgcn_s_setprio(1);
-        if (held) second((stage + 3) % KV_STAGES);
+      auto into_vector = [&]() __attribute__((always_inline)) {
+        __builtin_amdgcn_s_setprio(0);
+        if (!RP) AT_WAIT_VM(LOADS);
+        AT_SLOT_BARRIER();
+        issue((j + AHEAD) % KV_STAGES);
+      };
+      auto into_multiply = [&]() __attribute__((always_inline)) {
+        if (++head == G) { head = 0; qbase += QT; }
+        if (RP) AT_WAIT_VM(LOADS);
+        AT_SLOT_BARRIER();
+        ++j;
+      };
+      auto boundary = [&]() __attribute__((always_inline)) {
         if (IN_TURN && j == present_end) {
           close();
           while (present_end == j && present + 1 < slices) present_end = share(++present + 1);      // (shares without steps add nothing)
         }
-        if (act) first(stage);
-        __builtin_amdgcn_s_setprio(0);
-        if (!RP) AT_WAIT_VM(LOADS);
-        AT_SLOT_BARRIER();
-        issue((stage + AHEAD) % KV_STAGES);
-        if (act) vector(stage);
-        held = act;
-        if (++head == G) { head = 0; qbase += QT; }
-        if (RP) AT_WAIT_VM(LOADS);
-        AT_SLOT_BARRIER();
       };
-      int j = 0;
-      for (; j < n_iter; j += 4) {      // (a step past the last tile loads that tile again and passes its barriers)
-        step(j, 0);
-        step(j + 1, 1);
-        step(j + 2, 2);
-        step(j + 3, 3);
+      auto skip = [&]() __attribute__((always_inline)) { into_vector(); into_multiply(); boundary(); };      // a tile that the wave has no pair of
+      boundary();            // (the first shares may be empty)
+      while (j < n_iter && !tile_active(qbase)) skip();
+      if (j < n_iter) {      // the wave's tiles: one run of steps
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) fr[kk] = pin((RP ? lds0 : lds_do) + frag16_rows<DH>(kk) + (uint32_t)(j % KV_STAGES) * TILE64<DH>);
+#pragma unroll
+        for (int d = 0; d < DB; ++d) gt[d] = pin((RP ? lds_do : lds0) + frag16_tr<DH>(col0 / 16 + d) + (uint32_t)(j % KV_STAGES) * TILE64<DH>);
+        __builtin_amdgcn_s_setprio(1);
+        do {
+          first();
+          into_vector();
+          vector();
+          into_multiply();
+          __builtin_amdgcn_s_setprio(1);
+          second();
+          boundary();
+        } while (j < n_iter && tile_active(qbase));
+        __builtin_amdgcn_s_setprio(0);
       }
-      if (held) second(3);
+      while (j < n_iter) skip();
       AT_WAIT_VM(0);
       if (RP) AT_SLOT_BARRIER();        // both roles execute the same number of barriers
     }
-    if (my_key >= n_total) return;
-    if constexpr (IN_TURN) {
-      close();
+    if constexpr (IN_TURN) close();
 #pragma unroll
-      for (int i = 0; i < DB; ++i)
+    for (int b = 0; b < 2; ++b) {
+      if (key_of(b) >= n_total) continue;
+      if constexpr (IN_TURN) {
 #pragma unroll
-        for (int a = 0; a < 4; ++a)
-          *(f32x4*)(out + i * 32 + 8 * a + 4 * half) = f32x4{sum[i][4 * a], sum[i][4 * a + 1], sum[i][4 * a + 2], sum[i][4 * a + 3]};
-    } else {
-      // several workgroups per key block: each leaves its sum in its own slice [workgroup][dk | dv][key][kv head][DH]
-      const int64_t first = (int64_t)key_block0 * KV_TILE;
-      float* to = part ? part + ((int64_t)z * 2 + (RP ? 1 : 0)) * (n_total - first) * kv_stride + (my_key - first) * kv_stride + (int64_t)kvh * DH : out;
+        for (int d = 0; d < DB; ++d) *(f32x4*)(out_of(b) + d * 16) = sum[b][d];
+      } else {
+        // several workgroups per key block: each leaves its sum in its own slice [workgroup][dk | dv][key][kv head][DH]
+        const int64_t first = (int64_t)key_block0 * KV_TILE;
+        float* to = part ? part + ((int64_t)z * 2 + (RP ? 1 : 0)) * (n_total - first) * kv_stride + (key_of(b) - first) * kv_stride + (int64_t)kvh * DH + 4 * lg : out_of(b);
 #pragma unroll
-      for (int i = 0; i < DB; ++i)
+        for (int d = 0; d < DB; ++d) {
+          f32x4 u = part ? f32x4{0.f, 0.f, 0.f, 0.f} : *(f32x4*)(to + d * 16);
 #pragma unroll
-        for (int a = 0; a < 4; ++a) {
-          const int d0 = i * 32 + 8 * a + 4 * half;
-          float4 u = part ? make_float4(0.f, 0.f, 0.f, 0.f) : *(float4*)(to + d0);
-          {
+          for (int r = 0; r < 4; ++r) {
 #pragma clang fp contract(off)
-            u.x += acc[i][4 * a + 0] * f; u.y += acc[i][4 * a + 1] * f; u.z += acc[i][4 * a + 2] * f; u.w += acc[i][4 * a + 3] * f;
+            u[r] += acc[b][d][r] * f;
           }
-          *(float4*)(to + d0) = u;
+          *(f32x4*)(to + d * 16) = u;
         }
+      }
     }
   };
   if (role_p) run(std::true_type{});
