@@ -414,6 +414,10 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
     // us, K = 1024 253 -> 227; 152064 x 3584, K = 1536 2207 -> 2108, K = 16384 14.90 -> 14.74 ms.  (fp32 atomic adds without return cost 1721
     // instead of 1139 us where the pass over C dominates - 152064 x 3584, K = 512 - and the same at K >= 8192; the same form for bf16
     // C, which has half the bytes to wait for: 2 % faster at K = 512, 1-4 % slower from K = 4096 on.)
+    // C is touched once: the accesses are non-temporal, so that its 512 KB per tile do not push the operand panels that the XCD's other tiles share out
+    // of the L2.  Seven gradients of a 7B layer, 0.93 GB, K = 2048 1040 -> 997 us, 2560 1264 -> 1238, 8192 the same; 152064 x 3584, K = 1536 1996
+    // -> 1921 (the loads alone 1001, 1937).  The bf16 form, the plain stores and the elementwise passes gain nothing or lose (SwiGLU adjoint 70 -> 79 us: its
+    // tensors are in the memory-side cache).  A dword of every 128 bytes of C asked for two K steps ahead: 1040 -> 1130.
     const int c4 = threadIdx.x & 63, r0 = threadIdx.x >> 6;
     const char* base = uniform_ptr(Cf + (int64_t)m0 * ldc + n0);
     const uint32_t lane_off = (uint32_t)((r0 * ldc + c4 * 4) * 4);
@@ -425,7 +429,7 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
     auto fetch = [&](int ha) {
 #pragma unroll
       for (int p = 0; p < 16; ++p)
-        if (inside(ha, p)) old[ha][p] = *at(ha, p);
+        if (inside(ha, p)) old[ha][p] = __builtin_nontemporal_load(at(ha, p));
     };
     fetch(0);
 #pragma unroll
@@ -448,7 +452,7 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
       for (int p = 0; p < 16; ++p) {
         const int row_l = p * 8 + r0;
         const f32x4 v = *(const f32x4*)(smem + row_l * 1024 + ((c4 ^ (row_l & 15)) << 4));
-        if (inside(ha, p)) *at(ha, p) = old[ha][p] + v;
+        if (inside(ha, p)) __builtin_nontemporal_store(old[ha][p] + v, at(ha, p));
       }
     }
     return;
@@ -545,7 +549,7 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
         const int row = p * 16 + (threadIdx.x >> 5);
         const i32x4 v = *(const i32x4*)(smem + row * 512 + ((c16 ^ (row & 15)) << 4));
         if (m0 + row < M && col < N) {
-          if (ldc % 8 == 0) *(i32x4*)(Cb + (int64_t)(m0 + row) * ldc + col) = v;
+          if (ldc % 8 == 0) __builtin_nontemporal_store(v, (i32x4*)(Cb + (int64_t)(m0 + row) * ldc + col));      // (as for C += above: 1627 -> 1605 us, 2048 rows)
           else {                               // (rows that start between 16-byte boundaries: half of them at a time)
             typedef int i32x2 __attribute__((ext_vector_type(2)));
             *(i32x2*)(Cb + (int64_t)(m0 + row) * ldc + col) = i32x2{v[0], v[1]};
