@@ -1280,8 +1280,11 @@ __device__ __forceinline__ void bwd_block(const bf16_t* __restrict__ q, const bf
   __shared__ __attribute__((aligned(1024))) union { DkvShared<DH> dkv; DqShared<DH, SPLIT> dq; } sh;
   const int kv_heads = Hkv * seqs.n, heads = Hq * seqs.n, n_dkv = key_blocks * kv_heads * (IN_TURN ? 2 : part ? slices : 1), b = blockIdx.x;
   if (b < n_dkv) {
-    const int r = b / key_blocks;
-    dkv_block<DH, IN_TURN>(sh.dkv, b % key_blocks, r % kv_heads, r / kv_heads, q, k, v, d_o, lse2, delta, dk, dv, Hq, Hkv, q_start, c, scale, window, seqs,
+    // The key blocks that most queries see first, all their workgroups side by side.  Workgroup b runs on XCD b % 8: with the key blocks side by side an
+    // XCD had the same few of them, up to 2.4 times the work of another where a chunk starts at 0 (2048 queries from 0, 28 / 4 heads 182 -> 133 us, from 2048
+    // 344 -> 328; 32 / 8 heads 385 -> 352 from 0, 790 -> 769 from 6144; launches of their own, with many key blocks, gain nothing).
+    const int per = n_dkv / key_blocks, r = b % per;
+    dkv_block<DH, IN_TURN>(sh.dkv, b / per, r % kv_heads, r / kv_heads, q, k, v, d_o, lse2, delta, dk, dv, Hq, Hkv, q_start, c, scale, window, seqs,
                            key_block0, slices, part);
   } else {
     const int i = b - n_dkv;
