@@ -1387,10 +1387,50 @@ bool attn_mfma_aligned(const AttnArgs& a, bool backward) {
 // tokens and 16 / 4 heads of 64 a stack of two layers 2290 -> 2130 us.
 bool attn_sequences_fit(const AttnArgs& a) { return a.batch <= ATTN_MAX_SEQS && a.q_start == 0; }
 
-// Rounds of 256 workgroups (one per CU), a half query tile costing half a round: the half tiles where they leave fewer CUs idle.
-static bool half_tiles_fill_better(const AttnArgs& a) {
-  return 2 * cdiv(cdiv(a.q_len, TQ) * a.Hq * a.batch, 256) > cdiv(cdiv(a.q_len, TQ / 2) * a.Hq * a.batch, 256);
+// Time of a launch in key steps: its query tiles, those with the most keys first, dealt to 256 CUs as they become free.  A tile takes a step for every `keys`
+// keys that it sees and six more for its start and end.  More than eight rounds: their mean.
+static double launch_steps(const AttnArgs& a, int tile, int keys) {
+  const int64_t heads = (int64_t)a.Hq * a.batch, rows = cdiv(a.q_len, tile);
+  auto steps_of = [&](int64_t row) {
+    const int64_t first_q = a.q_start + row * tile, last = std::min<int64_t>(a.q_start + a.q_len, first_q + tile);
+    const int64_t first = std::max<int64_t>(a.kv_first, a.window > 0 ? first_q - a.window + 1 : 0);
+    return cdiv(std::max<int64_t>(last - first, 0), keys) + 6;
+  };
+  if (rows * heads > 8 * 256) {
+    double sum = 0.0;
+    for (int64_t row = 0; row < rows; ++row) sum += (double)steps_of(row) * (double)heads;
+    return sum / 256.0;
+  }
+  struct Free { int64_t at; int n; } cus[258];      // CUs by the time they become free, the earliest first: at most 256 different times and a new one
+  int n_times = 1;
+  int64_t end = 0;
+  cus[0] = {0, 256};
+  for (int64_t row = rows - 1; row >= 0; --row) {
+    const int64_t len = steps_of(row);
+    for (int64_t left = heads; left > 0;) {
+      const int take = (int)std::min<int64_t>(cus[0].n, left);
+      const int64_t at = cus[0].at + len;
+      left -= take;
+      if ((cus[0].n -= take) == 0) std::copy(cus + 1, cus + n_times--, cus);
+      int i = n_times;
+      while (i > 0 && cus[i - 1].at > at) --i;
+      if (i > 0 && cus[i - 1].at == at) cus[i - 1].n += take;
+      else {
+        std::copy_backward(cus + i, cus + n_times, cus + n_times + 1);
+        cus[i] = {at, take};
+        ++n_times;
+      }
+      end = std::max(end, at);
+    }
+  }
+  return (double)end;
 }
+// Query tiles of 128, whose two wave groups take even and odd key tiles, or of 256.  A step of 128 keys costs a half tile `cost` times what one of 64 costs a whole
+// one: forward 2.1 against 1.95 us; dQ, whose half tiles have 32 keys, more.  Whole / half tiles, measured, forward of 2048 queries, 28 heads, from 0 73 / 62
+// us (whole: as long as the longest tile), from 2048 132 / 123, 4096 from 4096 403 / 437; four sequences of 640 tokens 52 / 59, with the backward 81 / 85; 2048
+// queries, 32 heads: backward from 0 352 / 362, from 4096 600 / 580, from 6144 768 / 789.
+constexpr double HALF_STEP_FWD = 1.08, HALF_STEP_DQ = 1.15;
+static bool half_tiles_faster(const AttnArgs& a, double cost) { return cost * launch_steps(a, TQ / 2, 2 * TK) < launch_steps(a, TQ, TK); }
 static AttnSeqs sequences(const AttnArgs& a) {
   AttnSeqs s{};
   s.n = a.batch;
@@ -1405,7 +1445,7 @@ static hipError_t forward_dh(const AttnArgs& a, hipStream_t st) {
     kernel<<<(unsigned)n, AT_THREADS, 0, st>>>((bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v, (bf16_t*)a.o, a.lse, a.Hq, a.Hkv,
                                                a.q_start, a.q_len, a.scale, a.rope_q, a.window, sequences(a));
   };
-  if (half_tiles_fill_better(a)) launch(attn_fwd_mfma_k<DH, true>, halves);
+  if (half_tiles_faster(a, HALF_STEP_FWD)) launch(attn_fwd_mfma_k<DH, true>, halves);
   else launch(attn_fwd_mfma_k<DH, false>, full);
   return hipGetLastError();
 }
@@ -1423,7 +1463,7 @@ static hipError_t backward_dh(const AttnArgs& a, hipStream_t st) {
   const int kb0 = attn_first_key_block(a), kb1 = (int)cdiv(a.q_start + a.q_len, KV_TILE), key_blocks = std::max(0, kb1 - kb0);
   const int slices = std::max(1, a.dkv_slices);
   float* part = slices > 1 ? a.dkv_scratch : nullptr;
-  const bool halves = half_tiles_fill_better(a);
+  const bool halves = half_tiles_faster(a, HALF_STEP_DQ);
   const int64_t blocks = (int64_t)key_blocks * a.Hkv * a.batch, q_blocks = cdiv(a.q_len, halves ? TQ / 2 : TQ), q_tiles = q_blocks * a.Hq * a.batch;
   const bool in_turn = !part && slices > 1 && blocks <= IN_TURN_BLOCKS;      // two workgroups per key block
   const int64_t n_dkv = blocks * (in_turn ? 2 : part ? slices : 1);
