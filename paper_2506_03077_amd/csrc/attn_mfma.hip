@@ -55,9 +55,12 @@ constexpr int TK = ATTN_TILE_K;          // 64 keys per step (fwd, dQ)
 constexpr int KV_TILE = ATTN_KV_TILE;    // keys per workgroup (dK/dV): 4 key blocks x 2 roles = 8 waves
 constexpr int KV_THREADS = 512;
 constexpr int QT = ATTN_KV_QUERIES;      // queries per step (dK/dV)
-// Workgroups of a backward that runs as one launch (four rounds of the chip).  Whole backward in one launch / in two, 256 to 2048 queries, prefixes of 0 to
-// 30720: below the line 0.52-1.01 (mean 0.83), above it 0.88-1.01 (mean 0.96).
+// Workgroups of a backward that runs as one launch (four rounds of the chip; six behind a prefix), unless dK/dV alone is two or more whole rounds and dQ less than
+// one, where neither can fill what the other leaves.  Whole backward in one launch / in two: up to 1024 workgroups 0.52-1.01 (mean 0.83); behind prefixes 1128 + 256
+// 0.97, 1024 + 256 0.985, 692 + 224 and 442 + 448 1.00, the passes of a 32k layer at 7B widths, 640 to 1024 + 448, 0.91 to 0.99 (the layer 67.9 -> 67.2 ms); 1024 +
+// 224 1.004; beyond, 2008 + 256, 1.004.
 constexpr int MERGED_MAX = 1024;
+constexpr int MERGED_MAX_PREFIX = 1536;
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
 
@@ -1468,7 +1471,8 @@ static hipError_t backward_dh(const AttnArgs& a, hipStream_t st) {
   const bool in_turn = !part && slices > 1 && blocks <= IN_TURN_BLOCKS;      // two workgroups per key block
   const int64_t n_dkv = blocks * (in_turn ? 2 : part ? slices : 1);
   const bf16_t *q = (const bf16_t*)a.q, *k = (const bf16_t*)a.k, *v = (const bf16_t*)a.v, *d_o = (const bf16_t*)a.d_o;
-  if (n_dkv > 0 && (in_turn || n_dkv + q_tiles <= MERGED_MAX)) {
+  const bool nothing_to_fill = n_dkv >= 512 && n_dkv % 256 == 0 && q_tiles < 256;
+  if (n_dkv > 0 && (in_turn || (n_dkv + q_tiles <= (a.q_start > 0 ? MERGED_MAX_PREFIX : MERGED_MAX) && !nothing_to_fill))) {
     auto launch = [&](auto kernel) {
       kernel<<<(unsigned)(n_dkv + q_tiles), AT_THREADS, 0, st>>>(q, k, v, d_o, a.lse, lse2, a.delta, (bf16_t*)a.dq, a.dk, a.dv, a.Hq, a.Hkv, a.q_start,
                                                                          a.q_len, a.scale, a.rope_q, a.window, seqs, kb0, key_blocks, slices, part,

@@ -19,3 +19,9 @@ HALF = [(28, 4, 0, 1100, 0, 0),               # causal from 0: the longest whole
 @pytest.mark.parametrize("dh", [128, 64])
 def test_both_sides_of_the_rule(dh, hq, hkv, s, c, window, kv_first):
     masked_attn_case("bf16", hq, hkv, dh, s, c, window, kv_first)
+
+
+# dK/dV and dQ of a chunk behind a prefix: more than 1024 workgroups in one launch, and apart where dK/dV is whole rounds and dQ less than one
+@pytest.mark.parametrize("hq,hkv,s,c", [(64, 32, 4000, 200), (32, 16, 3965, 130), (32, 32, 2000, 500)])
+def test_backward_behind_a_prefix(hq, hkv, s, c):
+    masked_attn_case("bf16", hq, hkv, 64, s, c, 0, 0)
