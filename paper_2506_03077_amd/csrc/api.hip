@@ -501,11 +501,13 @@ int32_t layer_backward_impl(const sbp_layer_cfg* c, const sbp_layer_weights* w, 
       aa.dkc = s.dkc; aa.dvc = s.dvc; aa.rope_k = s.rope + (size_t)p.r0 * half;
       HIPCHK(attn_backward(aa, st));
       if (!aa.rope_q) HIPCHK(rope_apply(dt, s.dq, s.rope + (size_t)p.r0 * half, n, p.n, c->n_q_heads, c->head_dim, true, st));
-      {   // da = dq W_q + dkc W_k + dvc W_v
-        const GemmArgs qkv[3] = {dx_gemm(s.dq, w->wq, s.f0, n, qd, d, dt, DT_F32, false), dx_gemm(s.dkc, w->wk, s.f0, n, kd, d, dt, DT_F32, true),
-                                 dx_gemm(s.dvc, w->wv, s.f0, n, kd, d, dt, DT_F32, true)};
-        HIPCHK(gemm_sum(qkv, 3, st));
-      }
+      // the last pass of a weight-gradient group
+      const bool group_done = !lora && (n_dws + 7 == 7 * plan.sets || (ci == 0 && b0 + seqs == c->batch));
+      // da = dq W_q + dkc W_k + dvc W_v; fp32: with the weight gradients in one launch, where they are launched and it has room
+      const GemmArgs qkv[3] = {dx_gemm(s.dq, w->wq, s.f0, n, qd, d, dt, DT_F32, false), dx_gemm(s.dkc, w->wk, s.f0, n, kd, d, dt, DT_F32, true),
+                               dx_gemm(s.dvc, w->wv, s.f0, n, kd, d, dt, DT_F32, true)};
+      const bool da_with_dw = group_done && dt == DT_F32 && n_dws + 10 <= 7 * MAX_DW_GROUP;
+      if (!da_with_dw) HIPCHK(gemm_sum(qkv, 3, st));
       if (!lora) {
         // ---- the seven weight gradients of the chunk, dW += dY^T X (Eq. 1 summand): queued, and launched together
         //      with those of the other chunks of the group (one pass over every dW for the group's rows)
@@ -514,7 +516,8 @@ int32_t layer_backward_impl(const sbp_layer_cfg* c, const sbp_layer_weights* w, 
                                   dw_gemm(s.dq, s.a, g->wq, n, qd, d, dt, gdt),    dw_gemm(s.dkc, s.a, g->wk, n, kd, d, dt, gdt),
                                   dw_gemm(s.dvc, s.a, g->wv, n, kd, d, dt, gdt)};
         for (int i = 0; i < 7; ++i) dws[n_dws++] = mine[i];
-        if (n_dws == 7 * plan.sets || (ci == 0 && b0 + seqs == c->batch)) {
+        if (group_done) {
+          if (da_with_dw) n_dws = (int)(std::copy_n(qkv, 3, dws + n_dws) - dws);
           HIPCHK(gemm_batch(dws, n_dws, st));
           n_dws = 0;
         }
@@ -893,7 +896,7 @@ int32_t streambp_lmhead_ce_backward(const sbp_head_cfg* c, const void* w, const 
     b.dh = dh; b.dh_bytes = (size_t)rows * d * es;           // ignored rows of dh: exact zeros
     HIPCHK(head_begin(b, st));
   }
-  GemmArgs pending[MAX_DW_GROUP];
+  GemmArgs pending[MAX_DW_GROUP + 1];
   int n_pending = 0;
   // rows [first, first + n) of the list of active rows: at most n, the rest of them on the device
   auto moved = [&](bool scatter, int64_t first, int64_t n, const int32_t* n_dev, void* buf) {
@@ -942,15 +945,21 @@ int32_t streambp_lmhead_ce_backward(const sbp_head_cfg* c, const void* w, const 
     pending[n_pending].rows_dev = n_dev;
     const bool span_done = (ci + 1) % dh_units == 0 || ci + 1 == n_units;
     const int* span_dev = dh_units > 1 ? span_rows + ci / dh_units : n_dev;
+    const bool group_done = n_pending + 1 == per_group || ci + 1 == n_units, dh_with_dw = span_done && group_done && dt == DT_F32;      // dh and dW in one launch
     if (span_done) {
       GemmArgs gh = dx_gemm((char*)dz - (size_t)(first - span_first) * s.ldz * es, w, dhc, (int)(first + n - span_first), V, d, dt, dt, false);
       gh.lda = s.ldz; gh.a_padded = padded;
       gh.rows_dev = span_dev;
-      HIPCHK(gemm(gh, st));
+      if (!dh_with_dw) HIPCHK(gemm(gh, st));
+      else {      // (the longer reduction first)
+        std::copy_backward(pending, pending + n_pending + 1, pending + n_pending + 2);
+        pending[0] = gh;
+      }
     }
     LossSum sum{};
-    if (++n_pending == per_group || ci + 1 == n_units) {
-      HIPCHK(gemm_batch(pending, n_pending, st));
+    ++n_pending;
+    if (group_done) {
+      HIPCHK(gemm_batch(pending, n_pending + dh_with_dw, st));
       // the active rows of the group's chunks are one list: its loss terms are summed together
       sum = LossSum{s.row_loss, (int)(first + n - group_first), c->objective == SBP_OBJ_DPO ? s.ell : loss, unit_rows + n_units,
                     (int)std::min<int64_t>(group_first, INT32_MAX)};

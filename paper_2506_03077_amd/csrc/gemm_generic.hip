@@ -84,19 +84,21 @@ __device__ __forceinline__ f32x4 step_values(typename Held<TI>::type v, bool k_m
   }
   return f;
 }
-// Several problems in one launch, each with its own layout and one or more reduction segments (operand pairs whose products are summed into
-// one output): a launch of the small configuration costs 4.8 us however little it does, its layer and head issued 86 of them.
-// (NP problems, NS segments: the smallest of three sizes, as the arguments' cache lines are fetched one dependent miss after the other.)
+// Several problems in one launch, each with its own layout, adding to its output or storing it, and one or more reduction segments (operand pairs whose products
+// are summed into one output): a launch of the small configuration costs 4.8 us however little it does, its layer and head issued 86 of them.
+// (NP problems, NS segments: the smallest of six sizes, as the arguments' cache lines are fetched one dependent miss after the other.  A 256-token fp32 layer with its
+// head: GEMM launches 14 -> 12 and arguments of 2.6 KB -> 0.3 to 1.1: 108 -> 99 us.)
 constexpr int GENERIC_PROBLEMS = 8, GENERIC_SEGMENTS = 56;
 struct GenericSegment { const void* A; const void* B; const int* rows_dev; int K, lda, ldb; };
-struct GenericProblem { void* C; int64_t ldc; int M, N, ta, tb, seg0, nseg, tile0, tiles_n; };
+enum { GENERIC_TA = 1, GENERIC_TB = 2, GENERIC_ACC = 4 };
+struct GenericProblem { void* C; int64_t ldc; int M, N, flags, seg0, nseg, tile0, tiles_n; };
 template <int NP, int NS> struct GenericArgs { int n; GenericProblem p[NP]; GenericSegment s[NS]; };
 using GenericAll = GenericArgs<GENERIC_PROBLEMS, GENERIC_SEGMENTS>;
 
 // gate (optional; rows of ldc elements, like C, which is then not written): the product is the gradient wrt act = silu(gate) * up; act gets that
 // value, gate and up their gradients, in place.
 struct GenericSwiglu { void *gate, *up, *act; };
-template <typename TI, typename TO, bool ACC, int NP, int NS>
+template <typename TI, typename TO, int NP, int NS>
 __global__ __launch_bounds__(WAVES * 64) void gemm_generic_k(const GenericArgs<NP, NS> ga, const GenericSwiglu sw) {
   int pi = 0;
 #pragma unroll
@@ -106,7 +108,8 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_generic_k(const GenericArgs<N
   const int tile = (int)blockIdx.x - g.tile0, m0 = tile / g.tiles_n * TILE, n0 = tile % g.tiles_n * TILE;
   // run-time row count (M for NT / NN, the reduction K for the dW form)
   auto rows = [&](const GenericSegment& q) { return q.rows_dev ? max(0, *q.rows_dev) : 0x7fffffff; };
-  const int M = g.ta ? g.M : min(g.M, rows(ga.s[g.seg0])), N = g.N;
+  const bool ta = g.flags & GENERIC_TA, tb = g.flags & GENERIC_TB, acc_c = g.flags & GENERIC_ACC;
+  const int M = ta ? g.M : min(g.M, rows(ga.s[g.seg0])), N = g.N;
   __shared__ float part[WAVES][TILE][TILE + 1];
   if (m0 >= M) return;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), li = threadIdx.x & 15, lg = (threadIdx.x & 63) >> 4;
@@ -116,7 +119,6 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_generic_k(const GenericArgs<N
   int seg = -1, k0 = 0, dealt = 0;
   const TI *A = nullptr, *B = nullptr;
   int K = 0, lda = 0, ldb = 0;
-  const bool ta = g.ta != 0, tb = g.tb != 0;
   typename Held<TI>::type a[2], b[2];
   auto enter = [&]() {
     const GenericSegment& q = ga.s[NS == 1 ? 0 : g.seg0 + seg];
@@ -172,7 +174,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_generic_k(const GenericArgs<N
     float v = 0.f;
     for (int w = 0; w < waves; ++w) v += part[w][row][col];
     const int64_t at = (int64_t)(m0 + row) * g.ldc + n0 + col;
-    if (NP == 1 && !ACC && sw.gate) {
+    if (NP == 1 && sw.gate) {
       TO *gate = (TO*)sw.gate + at, *up = (TO*)sw.up + at;
       const float z = ldf(gate), u = ldf(up), s = 1.0f / (1.0f + __expf(-z));
       if (sw.act) stf((TO*)sw.act + at, z * s * u);
@@ -181,12 +183,12 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_generic_k(const GenericArgs<N
       continue;
     }
     TO* p = (TO*)g.C + at;
-    if (ACC) stf(p, ldf(p) + v); else stf(p, v);
+    stf(p, acc_c ? ldf(p) + v : v);
   }
 }
 
-// What one launch takes: problems of the same types that all add to their C or all store it.  Accumulated problems with the same C become
-// segments of one (C is read and written once); sum: all n are segments of one stored output.  False: not in one launch.
+// What one launch takes: problems of the same types.  Accumulated problems with the same C as an earlier one become segments of it (C is written once, and
+// read if the first of them adds); sum: all n are segments of one stored output.  False: not in one launch.
 static bool generic_args(const GemmArgs* gs, int n, bool sum, GenericAll& ga, int64_t& tiles) {
   ga.n = 0;
   tiles = 0;
@@ -195,18 +197,19 @@ static bool generic_args(const GemmArgs* gs, int n, bool sum, GenericAll& ga, in
   for (int i = 0; i < n; ++i) {
     const GemmArgs& g = gs[i];
     if (g.M == 0 || g.N == 0) continue;
-    if (g.in_dt != gs[0].in_dt || g.out_dt != gs[0].out_dt || (!sum && g.acc != gs[0].acc) || g.lda > INT32_MAX || g.ldb > INT32_MAX) return false;
+    if (g.in_dt != gs[0].in_dt || g.out_dt != gs[0].out_dt || g.lda > INT32_MAX || g.ldb > INT32_MAX) return false;
+    const int layout = (g.ta ? GENERIC_TA : 0) | (g.tb ? GENERIC_TB : 0);
     int pi = -1;
     for (int j = 0; j < ga.n && pi < 0; ++j) {
       const GenericProblem& p = ga.p[j];
       if (p.C != g.C) continue;
-      if (!(sum || g.acc) || p.M != g.M || p.N != g.N || p.ldc != g.ldc || p.ta != (g.ta ? 1 : 0) || p.tb != (g.tb ? 1 : 0) || (g.rows_dev && !g.ta)) return false;
+      if (!(sum || g.acc) || p.M != g.M || p.N != g.N || p.ldc != g.ldc || ((p.flags ^ layout) & (GENERIC_TA | GENERIC_TB)) || (g.rows_dev && !g.ta)) return false;
       pi = j;
     }
     if (pi < 0) {
       if (ga.n == GENERIC_PROBLEMS || (sum && ga.n == 1)) return false;
       pi = ga.n++;
-      ga.p[pi] = GenericProblem{g.C, g.ldc, g.M, g.N, g.ta ? 1 : 0, g.tb ? 1 : 0, 0, 0, (int)tiles, (int)cdiv(g.N, TILE)};
+      ga.p[pi] = GenericProblem{g.C, g.ldc, g.M, g.N, layout | (g.acc && !sum ? GENERIC_ACC : 0), 0, 0, (int)tiles, (int)cdiv(g.N, TILE)};
       tiles += cdiv(g.M, TILE) * cdiv(g.N, TILE);
       if (tiles > INT32_MAX) return false;
     }
@@ -242,22 +245,18 @@ hipError_t gemm_generic(const GemmArgs* gs, int n, bool sum, hipStream_t st) {
     std::copy_n(ga.s, std::min<size_t>(std::size(args.s), n_seg), args.s);
     kernel<<<(unsigned)tiles, WAVES * 64, 0, st>>>(args, GenericSwiglu{gs[0].swiglu_gate, gs[0].swiglu_up, gs[0].swiglu_act});
   };
-#define GG(TI, TO, ACC)                                                                                        \
+#define GG(TI, TO)                                                                                             \
   do {                                                                                                         \
-    if (ga.n == 1 && n_seg == 1) go(gemm_generic_k<TI, TO, ACC, 1, 1>, GenericArgs<1, 1>{});                   \
-    else if (ga.n <= 2 && n_seg <= 3) go(gemm_generic_k<TI, TO, ACC, 2, 3>, GenericArgs<2, 3>{});              \
-    else go(gemm_generic_k<TI, TO, ACC, GENERIC_PROBLEMS, GENERIC_SEGMENTS>, GenericAll{});                    \
+    if (ga.n == 1 && n_seg == 1) go(gemm_generic_k<TI, TO, 1, 1>, GenericArgs<1, 1>{});                        \
+    else if (ga.n <= 2 && n_seg <= 3) go(gemm_generic_k<TI, TO, 2, 3>, GenericArgs<2, 3>{});                   \
+    else if (ga.n <= 3 && n_seg <= 3) go(gemm_generic_k<TI, TO, 3, 3>, GenericArgs<3, 3>{});                   \
+    else if (n_seg <= 8) go(gemm_generic_k<TI, TO, GENERIC_PROBLEMS, 8>, GenericArgs<GENERIC_PROBLEMS, 8>{});  \
+    else if (n_seg <= 16) go(gemm_generic_k<TI, TO, GENERIC_PROBLEMS, 16>, GenericArgs<GENERIC_PROBLEMS, 16>{}); \
+    else go(gemm_generic_k<TI, TO, GENERIC_PROBLEMS, GENERIC_SEGMENTS>, GenericAll{});                         \
   } while (0)
-  const bool acc = g.acc && !sum;
-  if (g.in_dt == DT_BF16) {
-    if (g.out_dt == DT_BF16 && acc) GG(bf16_t, bf16_t, true);
-    else if (g.out_dt == DT_BF16) GG(bf16_t, bf16_t, false);
-    else if (acc) GG(bf16_t, float, true);
-    else GG(bf16_t, float, false);
-  } else {
-    if (acc) GG(float, float, true);
-    else GG(float, float, false);
-  }
+  if (g.in_dt != DT_BF16) GG(float, float);
+  else if (g.out_dt == DT_BF16) GG(bf16_t, bf16_t);
+  else GG(bf16_t, float);
 #undef GG
   return hipGetLastError();
 }

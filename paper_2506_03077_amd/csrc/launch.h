@@ -72,7 +72,8 @@ bool gemm_glu_supported(const GemmArgs& g);
 // upper bound of the scratch a GEMM with M <= max_m rows and N <= max_n columns may use
 size_t gemm_scratch_bytes(int max_m, int max_n);
 hipError_t gemm(const GemmArgs& g, hipStream_t st);
-// n independent GEMMs (distinct outputs); one grouped launch when the MFMA kernel can take them all
+// n independent GEMMs (distinct outputs); one grouped launch when the MFMA kernel can take them all, or the shape-agnostic one (of that also several that add to
+// one output, after one that stores it)
 // group_small: take the grouped launch also when the problems together have few output tiles (skinny problems)
 hipError_t gemm_batch(const GemmArgs* gs, int n, hipStream_t st, bool group_small = false);
 struct FewChoice { int tm, tn; double us; };      // output tile of gemm_few_k (0: not for it) and estimated time
