@@ -867,6 +867,7 @@ int32_t streambp_lmhead_ce_backward(const sbp_head_cfg* c, const void* w, const 
   float* target_logit = s.target_logit;
   int chunks = head_span_chunks(s.dw_group, cm);
   const int span = (int)std::min<int64_t>(rows, (int64_t)cm * chunks);
+  size_t z_used = 0;      // bytes of the fp32-logits buffer that other things take
   if (span > cm) {
     auto carve = [&](void* base) {
       if (!numer) { dhc = base; return (size_t)span * d * es; }
@@ -877,22 +878,36 @@ int32_t streambp_lmhead_ce_backward(const sbp_head_cfg* c, const void* w, const 
       if (s.ht) hc = cv.take_bytes((size_t)span * d * es);
       return cv.off;
     };
-    if (carve(nullptr) <= (size_t)cm * s.ldz * sizeof(float)) carve(s.z);
+    if (carve(nullptr) <= (size_t)cm * s.ldz * sizeof(float)) z_used = carve(s.z);
     else { dhc = s.dhc; stats = s.stats; target_logit = s.target_logit; hc = s.hc; chunks = 1; }
   } else chunks = 1;
   const int cu = chunks > 1 && wide ? span : cm;          // rows of a unit: what the logits are formed of at once
   const int dh_units = chunks > 1 && !wide ? chunks : 1, per_group = wide ? s.dw_group / chunks : s.dw_group;      // units of a span of dh, of a weight-gradient group
-  const int64_t ldt = (int64_t)align_up((size_t)cu, 64);
   const bool gather_span = dh_units > 1 && !s.ht;         // all rows of a span fetched at once
   const int n_units = (int)cdiv(rows, (int64_t)cu);
   int32_t* unit_rows = s.chunk_rows;                      // [n_units], then all active rows, then the rows per span
   int32_t* span_rows = unit_rows + n_units + 1;
+  const int n_spans = dh_units > 1 ? (int)cdiv(rows, (int64_t)span) : 0, n_groups = (int)cdiv(n_units, per_group), group_units = std::min(per_group, n_units);
+  int32_t* group_rows = span_rows + n_spans;
+  // All units of the list but the last active one are full, so that the rows of dz and h (the columns of h^T) of a group's units are one matrix of as many rows:
+  // one reduction without a break, whose last round may be split, in place of a segment per unit (about 3 us each and tile, the pipeline emptied and filled
+  // again).  50257 x 1024, 1842 rows in four units 294 -> 240 + 10 us; 152064 x 3584, 16384 rows in eight 13.95 -> 13.85 ms, 151936 x 3584, 8888 in five, the call
+  // 18.02 -> 17.94.  Where h^T is kept a unit has to end with 64 columns, and its rows start 64 columns further apart than they are long where there is room for it:
+  // the fp32-logits buffer, which the numerator form leaves idle (rows 32 KB apart: 13.98 ms).  The list of the groups' rows has to fit behind the others.
+  const bool joined = n_units > 1 && (!s.ht || cu % 64 == 0) && n_units + 1 + n_spans + n_groups <= 2 * (int)cdiv(rows, (int64_t)cm) + 1;
+  int64_t ldt = s.ht && joined ? (int64_t)group_units * cu : (int64_t)align_up((size_t)cu, 64);
+  char* hT_all = (char*)s.hT;
+  if (s.ht && joined && numer && align_up(z_used, 256) + (size_t)d * (ldt + 64) * 2 <= (size_t)cm * s.ldz * sizeof(float)) {
+    hT_all = (char*)s.z + align_up(z_used, 256);
+    ldt += 64;
+  }
   {
     HeadBegin b{};
     b.targets = targets; b.B = c->batch; b.T = c->seq_len; b.V = V;
     b.seq_weight = s.seq_weight; b.n_active = n_active; b.ell = c->objective == SBP_OBJ_DPO ? s.ell : nullptr;
     b.index = s.index; b.unit_rows = unit_rows; b.unit = cu; b.n_units = n_units;
-    b.span_rows = span_rows; b.span = span; b.n_spans = dh_units > 1 ? (int)cdiv(rows, (int64_t)span) : 0;
+    b.span_rows = span_rows; b.span = span; b.n_spans = n_spans;
+    b.group_rows = group_rows; b.group = group_units * cu; b.n_groups = joined ? n_groups : 0;
     b.dh = dh; b.dh_bytes = (size_t)rows * d * es;           // ignored rows of dh: exact zeros
     HIPCHK(head_begin(b, st));
   }
@@ -910,7 +925,7 @@ int32_t streambp_lmhead_ce_backward(const sbp_head_cfg* c, const void* w, const 
     const int n = (int)std::min<int64_t>(cu, rows - first);      // upper bound of the unit's rows
     void* hcu = s.ht ? hc : at(hc, (size_t)n_pending * cu, d, es);
     void* dz = at(s.dz, (size_t)n_pending * cu, s.ldz, es);
-    void* hT = s.ht ? (char*)s.hT + (size_t)n_pending * d * ldt * 2 : nullptr;
+    void* hT = s.ht ? hT_all + (size_t)n_pending * (joined ? (size_t)cu : (size_t)d * ldt) * 2 : nullptr;
     if (ci == 0) HIPCHK(move_rows(dt, RowMove{}, gather_span ? moved(false, 0, span, span_rows, hc) : moved(false, 0, cu, n_dev, hcu), d, st));
     if (s.ht) HIPCHK(transpose_rows(hcu, n_dev, n, d, hT, ldt, st));
     // The logits: fp32 with (max, sum of exp) per row and 256-column block out of the GEMM's epilogue where the MFMA kernel
@@ -959,7 +974,14 @@ int32_t streambp_lmhead_ce_backward(const sbp_head_cfg* c, const void* w, const 
     LossSum sum{};
     ++n_pending;
     if (group_done) {
-      HIPCHK(gemm_batch(pending, n_pending + dh_with_dw, st));
+      int n_products = n_pending;
+      if (joined) {
+        GemmArgs& g = pending[dh_with_dw];      // the group's first unit, and all rows behind it
+        g.K = (int)(first + n - group_first);
+        g.rows_dev = group_rows + group_first / ((int64_t)group_units * cu);
+        n_products = 1;
+      }
+      HIPCHK(gemm_batch(pending, n_products + dh_with_dw, st));
       // the active rows of the group's chunks are one list: its loss terms are summed together
       sum = LossSum{s.row_loss, (int)(first + n - group_first), c->objective == SBP_OBJ_DPO ? s.ell : loss, unit_rows + n_units,
                     (int)std::min<int64_t>(group_first, INT32_MAX)};

@@ -821,6 +821,7 @@ struct TailArgs {
   int n;
   Schedule sched;
   const int* rows_dev;          // run-time row count of p[0] (single problems): the schedule is then made again from it
+  int K;                        // > 0: rows_dev counts the reduction, of at most K rows (weight gradients)
   int k_steps, scratch_tiles;
   const float* scratch;
   int part;                     // floats of a partial tile
@@ -831,9 +832,11 @@ __global__ __launch_bounds__(256) void splitk_tail_k(const TailArgs ta) {
   Schedule sc = ta.sched;
   int M0 = ta.p[0].M, tiles_m0 = ta.p[0].tiles_m;
   if (ta.rows_dev) {
-    M0 = min(M0, max(0, *ta.rows_dev));
+    int k_steps = ta.k_steps;
+    if (ta.K > 0) k_steps = (min(ta.K, max(0, *ta.rows_dev)) + BK - 1) / BK;
+    else M0 = min(M0, max(0, *ta.rows_dev));
     tiles_m0 = (M0 + BM - 1) / BM;
-    sc = make_schedule(tiles_m0 * ta.p[0].tiles_n, ta.k_steps, ta.scratch_tiles);
+    sc = make_schedule(tiles_m0 * ta.p[0].tiles_n, k_steps, ta.scratch_tiles);
   }
   const int t = blockIdx.x / ta.blocks, block = blockIdx.x % ta.blocks;
   if (t >= sc.tail) return;
@@ -975,7 +978,9 @@ hipError_t gemm_mfma(const GemmArgs& g, hipStream_t st) {
   const int mode = g.glu_up ? 8 : g.numer_targets ? 7 : g.row_stats ? 5 : g.swiglu_gate ? 6
                  : g.acc ? (g.out_dt == DT_BF16 ? 4 : 2) : (g.out_dt == DT_BF16 ? 1 : 0);
   const bool dev_rows = g.rows_dev != nullptr;
-  const int scratch_tiles = mode_splits(mode) && !(g.ta && dev_rows) ? scratch_tiles_of(g, g.M) : 0;
+  int scratch_tiles = mode_splits(mode) ? scratch_tiles_of(g, g.M) : 0;
+  // (a run-time reduction: split at most where its largest length is)
+  if (g.ta && dev_rows && make_schedule(tiles_m * tiles_n, k_steps, scratch_tiles).splits == 1) scratch_tiles = 0;
   if (SharedTail sh; shares_tail(g, scratch_tiles, sh)) {
     {
       prof::Scope sc_time(prof::GEMM_SINGLE + (g.tb ? 0 : 4), 2.0 * g.M * g.N * g.K * (g.A2 ? 2 : 1), false, st);
@@ -1031,7 +1036,8 @@ hipError_t gemm_mfma(const GemmArgs& g, hipStream_t st) {
   t.p[0] = TailProblem{g.C, g.M, g.N, g.ldc, 0, tiles_m, tiles_n};
   t.sched = sc; t.rows_dev = g.rows_dev; t.k_steps = k_steps; t.scratch_tiles = scratch_tiles; t.scratch = g.scratch;
   t.part = partial_floats(g.M);
-  return launch_tail(mode, t, dev_rows ? std::min(N_CU / 2, tiles_m * tiles_n) : sc.tail, st);
+  t.K = g.ta ? g.K : 0;
+  return launch_tail(mode, t, dev_rows && !g.ta ? std::min(N_CU / 2, tiles_m * tiles_n) : sc.tail, st);
 }
 
 // Grouped launch.  Requires every problem to be eligible, of the same layout / output type / accumulate mode.

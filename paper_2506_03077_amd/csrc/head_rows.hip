@@ -243,6 +243,7 @@ __device__ __forceinline__ void compact_active(const HeadBegin& a, int (&cnt)[10
   const int total = cnt[1023];
   for (int i = tid; i < a.n_units; i += 1024) a.unit_rows[i] = min(a.unit, max(0, total - i * a.unit));
   for (int i = tid; i < a.n_spans; i += 1024) a.span_rows[i] = min(a.span, max(0, total - i * a.span));
+  for (int i = tid; i < a.n_groups; i += 1024) a.group_rows[i] = min(a.group, max(0, total - i * a.group));
   if (tid == 0) a.unit_rows[a.n_units] = total;
 }
 // What a call starts with, in one launch: the counts (one workgroup), the list of active rows (one), zeros for dh (the others).  Apart, each of the

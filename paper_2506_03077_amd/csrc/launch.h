@@ -260,12 +260,13 @@ struct HeadRowArgs {
 hipError_t head_rows(const HeadRowArgs& a, hipStream_t st);
 // What a head call starts with.  Active rows: 0 <= target < V; seq_weight[j] = 1/(B*T_o,j) of the active rows T_o,j of sequence j (0 if there are none);
 // n_active: their total - or minus the number of targets >= V if there is any; index[0..n_active): the active rows in increasing order;
-// unit_rows[i] = clamp(n_active - i*unit, 0, unit) for i < n_units, unit_rows[n_units] = n_active; span_rows: the same for n_spans spans of `span` rows;
+// unit_rows[i] = clamp(n_active - i*unit, 0, unit) for i < n_units, unit_rows[n_units] = n_active; span_rows, group_rows: the same for n_spans spans of `span` rows and
+// n_groups groups of `group`;
 // ell (or NULL) and dh_bytes of dh become zeros
 struct HeadBegin {
   const int32_t* targets; int B, T, V;
   float* seq_weight; int64_t* n_active; float* ell;
-  int32_t* index; int32_t* unit_rows; int unit, n_units; int32_t* span_rows; int span, n_spans;
+  int32_t* index; int32_t* unit_rows; int unit, n_units; int32_t* span_rows; int span, n_spans; int32_t* group_rows; int group, n_groups;
   void* dh; size_t dh_bytes;
 };
 hipError_t head_begin(const HeadBegin& a, hipStream_t st);
