@@ -99,8 +99,8 @@ __device__ __forceinline__ float exp_of(float x, float scale, float sl, float c)
 // In the tile loops every vector-ALU instruction competes with the softmax arithmetic for the SIMD's VALU issue
 // slots, so nothing there computes an address: the per-lane byte offsets of the fragment reads inside a 64-row
 // tile and of the direct-to-LDS loads are computed once per kernel, every row block is reached with an immediate
-// offset (every stage too in the forward; the backward moves its addresses on, one addition per address and
-// tile), and the global side is an SGPR base plus those per-lane offsets.
+// offset, the addresses move on from stage to stage by one addition each, and the global side is an SGPR base plus
+// those per-lane offsets.
 __device__ __forceinline__ bf16x8 lds_b128(uint32_t addr) {
   return *(const bf16x8*)(__attribute__((address_space(3))) const char*)(uintptr_t)addr;
 }
@@ -238,6 +238,8 @@ __device__ __forceinline__ void query_tile_of(int id, int n_qt, int heads, int& 
 // work a slot takes 1050 cycles, without the MFMAs 1150.  Last 2048-query chunk of 32k, 28 heads: 1110 -> 957 us.
 // The masks and the rows' maxima close the multiply slot, which is the shorter one where few workgroups leave the clock high: 128 queries behind 4096 keys,
 // 28 heads, 69.1 -> 64.9 us, 1024 from the first on 23.8 -> 22.6, 16 heads of 64 23.3 -> 21.5; the same where the chip is full.
+// A wave's tiles are one loop whose LDS stages move with the addresses, as in dQ: 16 registers fewer than four steps unrolled, a quarter of the code, 820 -> 813 us on
+// that chunk, 777 windowed queries 31.9 -> 31.1.  Half of its LDS reads left out 739, its exponentials 789, a quarter of the products 710.
 // Tried with a maximum that lags by up to 2^8, itself 921 us but another rounding of every probability: 32x32x16 MFMAs in the same
 // schedule 965, loads in the multiply slot 954, the next slot's first fragments read early 958.
 template <int DH, bool SPLIT>
@@ -320,11 +322,6 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
   // ---- addresses, computed once: LDS fragments (+ stage, the only part that moves), global loads
   const uint32_t lds0 = lds_addr(sT);
   const uint32_t lds_k = lds0 + (SPLIT ? (uint32_t)grp * STAGES * TILE64<DH> : 0u), lds_v = lds_k + 4 * TILE64<DH>;
-  uint32_t fr[KS], ft[DB];
-#pragma unroll
-  for (int kk = 0; kk < KS; ++kk) fr[kk] = pin(lds_k + frag16_rows<DH>(kk));
-#pragma unroll
-  for (int d = 0; d < DB; ++d) ft[d] = pin(lds_v + frag16_tr<DH>(d));
   const int tid = SPLIT ? (int)threadIdx.x & (LOADERS - 1) : (int)threadIdx.x;
   auto load_offset = [&](int i, int rows_valid) {
     const int id = i * LOADERS + tid, row = id / (DH / 8), chunk = (id % (DH / 8)) ^ swz<DH>(row);
@@ -337,14 +334,14 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
 #pragma unroll
   for (int j = 0; j < LOADS; ++j) { voff[j] = pin(load_offset(j, TK)); voff_last[j] = pin(load_offset(j, min(TK, n_total - t_max * TK))); }
   const uint32_t dst_k = __builtin_amdgcn_readfirstlane(lds_k + (uint32_t)(tid & ~63) * 16u), tile_bytes = (uint32_t)(TK * kv_stride * 2);
-  // load p (of PIECES) of the pair V(i + V_AHEAD), K(i + K_AHEAD); slot = i modulo the stages
+  // load p (of PIECES) of the pair V(i + V_AHEAD), K(i + K_AHEAD)
   constexpr int PIECES = 2 * LOADS;
-  auto issue_piece = [&](int p, int i, int slot) __attribute__((always_inline)) {
+  auto issue_piece = [&](int p, int i) __attribute__((always_inline)) {
     const bool is_k = p >= LOADS;
     const int j = p % LOADS, ahead = is_k ? K_AHEAD : V_AHEAD, t = min(tile_of(i + ahead), t_max);
     const char* src = (const char*)(is_k ? kbase : vbase) + (uint64_t)tile_bytes * (uint32_t)t;
     dma16(src, t == t_max ? voff_last[j] : voff[j],
-          dst_k + (uint32_t)(((is_k ? 0 : 4) + (slot + ahead) % STAGES) * TILE64<DH> + j * LOADERS * 16));
+          dst_k + (uint32_t)(((is_k ? 0 : 4) + (i + ahead) % STAGES) * TILE64<DH> + j * LOADERS * 16));
   };
 
   bf16x8 ones;
@@ -371,23 +368,29 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
   const int step_t = SPLIT ? 2 : 1, first_t = tile_of(0);
   const int act0 = max(0, (wave_lo_min / TK - first_t + step_t - 1) / step_t);
   const int act1 = qw0 < c && wave_last_key >= 0 ? min(n_it, (wave_last_key / TK - first_t + step_t) / step_t) : 0;
-  auto active = [&](int i) { return i >= act0 && i < act1; };
+
+  // LDS addresses of fragments, one step after the other: of K rows of the present tile, of V transposed of the previous one
+  uint32_t fr[KS], ft[DB];
+#pragma unroll
+  for (int kk = 0; kk < KS; ++kk) fr[kk] = pin(lds_k + frag16_rows<DH>(kk) + (uint32_t)(act0 % STAGES) * TILE64<DH>);
+#pragma unroll
+  for (int d = 0; d < DB; ++d) ft[d] = pin(lds_v + frag16_tr<DH>(d) + (uint32_t)(act0 % STAGES) * TILE64<DH>);
+  auto to_next = [&](int i) { return i % STAGES == STAGES - 1 ? (uint32_t)-(int)((STAGES - 1) * TILE64<DH>) : (uint32_t)TILE64<DH>; };      // from the stage of tile i
 
   // fragment reads run RING - 1 fragments (two MFMAs each) ahead of the products
   constexpr int RING = 8;
   constexpr uint32_t ROWS16 = 16 * DH * 2;
   bf16x8 f[RING];
-  auto v_frag = [&](int n, uint32_t st) {      // n = k32 step * DB + head_dim block
-    return lds_tr(ft[n % DB] + (st + (uint32_t)(n / DB) * 2 * ROWS16), ft[n % DB] + (st + (uint32_t)(n / DB) * 2 * ROWS16 + ROWS16));
+  auto v_frag = [&](int n) {      // n = k32 step * DB + head_dim block
+    return lds_tr(ft[n % DB] + (uint32_t)(n / DB) * 2 * ROWS16, ft[n % DB] + ((uint32_t)(n / DB) * 2 * ROWS16 + ROWS16));
   };
-  auto k_frag = [&](int n, uint32_t st) { return lds_b128(fr[n >> 2] + (st + (uint32_t)(n & 3) * ROWS16)); };   // n = k32 step * 4 + key block
-  auto pv = [&](int slot) __attribute__((always_inline)) {
-    const uint32_t st = (uint32_t)((slot % STAGES) * TILE64<DH>);
+  auto k_frag = [&](int n) { return lds_b128(fr[n >> 2] + (uint32_t)(n & 3) * ROWS16); };   // n = k32 step * 4 + key block
+  auto pv = [&](int i) __attribute__((always_inline)) {
 #pragma unroll
-    for (int n = 0; n < RING - 1; ++n) f[n] = v_frag(n, st);
+    for (int n = 0; n < RING - 1; ++n) f[n] = v_frag(n);
 #pragma unroll
     for (int n = 0; n < 2 * DB; ++n) {
-      if (n + RING - 1 < 2 * DB) f[(n + RING - 1) % RING] = v_frag(n + RING - 1, st);
+      if (n + RING - 1 < 2 * DB) f[(n + RING - 1) % RING] = v_frag(n + RING - 1);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int b = 0; b < 2; ++b) {
@@ -399,23 +402,28 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
       }
       __builtin_amdgcn_sched_barrier(0);
     }
+    const uint32_t move = to_next(i);
+#pragma unroll
+    for (int d = 0; d < DB; ++d) ft[d] = pin(ft[d] + move);
   };
-  auto qk = [&](int slot) __attribute__((always_inline)) {
-    const uint32_t st = (uint32_t)((slot % STAGES) * TILE64<DH>);
+  auto qk = [&](int i) __attribute__((always_inline)) {
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
       for (int kb = 0; kb < 4; ++kb) s[b][kb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int n = 0; n < RING - 1; ++n) f[n] = k_frag(n, st);
+    for (int n = 0; n < RING - 1; ++n) f[n] = k_frag(n);
 #pragma unroll
     for (int n = 0; n < 4 * KS; ++n) {
-      if (n + RING - 1 < 4 * KS) f[(n + RING - 1) % RING] = k_frag(n + RING - 1, st);
+      if (n + RING - 1 < 4 * KS) f[(n + RING - 1) % RING] = k_frag(n + RING - 1);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int b = 0; b < 2; ++b) s[b][n & 3] = MFMA16(f[n % RING], bq[b][n >> 2], s[b][n & 3]);
       __builtin_amdgcn_sched_barrier(0);
     }
+    const uint32_t move = to_next(i);
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) fr[kk] = pin(fr[kk] + move);
   };
   auto row_max = [&](int i, float (&mx)[2]) __attribute__((always_inline)) {      // masks, and the maxima of the raw scores (scale > 0 keeps the order)
     const int k0 = tile_of(i) * TK;
@@ -448,7 +456,7 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
 #pragma unroll
     for (int b = 0; b < 2; ++b) mx[b] = max_over_quads(mx[b]);
   };
-  auto softmax = [&](int i, int slot, float (&mx)[2]) __attribute__((always_inline)) {
+  auto softmax = [&](int i, float (&mx)[2]) __attribute__((always_inline)) {
     if constexpr (SPLIT) {
 #pragma unroll
       for (int b = 0; b < 2; ++b) mx[b] = max_raw(mx[b], sM[grp ^ 1][wave & 3][b * 16 + li]);
@@ -480,7 +488,7 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
     for (int x = 0; x < 4; ++x) {        // eight probabilities at a time, the loads spread between them
       const int b = x >> 1, kk = x & 1;
 #pragma unroll
-      for (int p = x * PIECES / 4; p < (x + 1) * PIECES / 4; ++p) issue_piece(p, i, slot);
+      for (int p = x * PIECES / 4; p < (x + 1) * PIECES / 4; ++p) issue_piece(p, i);
       __builtin_amdgcn_sched_barrier(0);
       float pe[8];
 #pragma unroll
@@ -499,42 +507,46 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
 #pragma unroll
     for (int j = 0; j <= V_AHEAD; ++j)
 #pragma unroll
-      for (int p = j == 0 ? LOADS : 0; p < PIECES; ++p) issue_piece(p, j - 1 - V_AHEAD, j - 1 - V_AHEAD + 2 * STAGES);
+      for (int p = j == 0 ? LOADS : 0; p < PIECES; ++p) issue_piece(p, j - 1 - V_AHEAD);
     AT_WAIT_VM(PIECES * V_AHEAD);
     AT_SLOT_BARRIER();
     if (grp == 1) AT_SLOT_BARRIER();        // group 1 falls one slot behind ...
-    auto step = [&](int i, int slot) __attribute__((always_inline)) {      // slot = i % 4, a constant: every stage is an immediate offset
-      __builtin_amdgcn_s_setprio(1);
-      if (active(i - 1)) pv(slot + 3);
-      float mx[2];
-      if (active(i)) {
-        qk(slot);
-        __builtin_amdgcn_s_setprio(0);
-        row_max(i, mx);
-      }
-      __builtin_amdgcn_s_setprio(0);
-      // Before a tile is read every wave has waited for its own share of it and a barrier has passed: V(i), K(i + 1) by group 0 in
-      // its softmax slot, by group 1, one slot behind, at the end of this one (the two later pairs of tiles issued by
-      // then stay in flight, one for group 1 and if SPLIT).
+    // Before a tile is read every wave has waited for its own share of it and a barrier has passed: V(i), K(i + 1) by group 0 in
+    // its softmax slot, by group 1, one slot behind, at the end of its multiply slot (the two later pairs of tiles issued by
+    // then stay in flight, one for group 1 and if SPLIT).
+    int i = 0;
+    auto into_softmax = [&]() __attribute__((always_inline)) {
       if (!SPLIT && grp == 1) AT_WAIT_VM(PIECES * (V_AHEAD - 1));
       AT_SLOT_BARRIER();
-      if (active(i)) softmax(i, slot, mx);
-      else {
-#pragma unroll
-        for (int p = 0; p < PIECES; ++p) issue_piece(p, i, slot);
-      }
+    };
+    auto into_multiply = [&]() __attribute__((always_inline)) {
       if (SPLIT || grp == 0) AT_WAIT_VM(PIECES * V_AHEAD);
       AT_SLOT_BARRIER();
+      ++i;
     };
-    // whole groups of four steps (a step past the last tile loads that tile again, which keeps the wait counts, and passes its barriers)
-    int i = 0;
-    for (; i < n_it; i += 4) {
-      step(i, 0);
-      step(i + 1, 1);
-      step(i + 2, 2);
-      step(i + 3, 3);
+    auto skip = [&]() __attribute__((always_inline)) {      // a tile that no query of the wave sees
+      into_softmax();
+#pragma unroll
+      for (int p = 0; p < PIECES; ++p) issue_piece(p, i);
+      into_multiply();
+    };
+    while (i < min(act0, n_it)) skip();
+    if (i < act1) {      // the wave's tiles: one run of steps, without a branch around the products
+      __builtin_amdgcn_s_setprio(1);
+      do {
+        float mx[2];
+        qk(i);
+        __builtin_amdgcn_s_setprio(0);
+        row_max(i, mx);
+        into_softmax();
+        softmax(i, mx);
+        into_multiply();
+        __builtin_amdgcn_s_setprio(1);
+        pv(i - 1);
+      } while (i < act1);
+      __builtin_amdgcn_s_setprio(0);
     }
-    if (active(i - 1)) pv(3);
+    while (i < n_it) skip();
     AT_WAIT_VM(0);
     if (grp == 0) AT_SLOT_BARRIER();        // ... and group 0 waits for it here: both execute the same number of barriers
   }
