@@ -292,11 +292,12 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
             }
         __syncthreads();
         const int c4 = threadIdx.x & 63;
+        const int past = n0 + c4 * 4 < N ? 0 : 0x40000000;      // columns that C does not have are dropped too (2048 x 32 x 18944, 176 tiles 32.4 -> 29.8 us)
 #pragma unroll
         for (int p = 0; p < 16; ++p) {
           const int row_l = p * 8 + (threadIdx.x >> 6);
           const f32x4 v = *(const f32x4*)(smem + row_l * 1024 + ((c4 ^ (row_l & 15)) << 4));
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), out, ((ha * 128 + row_l) * BN + c4 * 4) * 4, 0, 0);
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), out, past + ((ha * 128 + row_l) * BN + c4 * 4) * 4, 0, 0);
         }
       }
       return;
