@@ -58,7 +58,7 @@ constexpr int QT = ATTN_KV_QUERIES;      // queries per step (dK/dV)
 // Workgroups of a backward that runs as one launch (four rounds of the chip; six behind a prefix), unless dK/dV alone is two or more whole rounds and dQ less than
 // one, where neither can fill what the other leaves.  Whole backward in one launch / in two: up to 1024 workgroups 0.52-1.01 (mean 0.83); behind prefixes 1128 + 256
 // 0.97, 1024 + 256 0.985, 692 + 224 and 442 + 448 1.00, the passes of a 32k layer at 7B widths, 640 to 1024 + 448, 0.91 to 0.99 (the layer 67.9 -> 67.2 ms); 1024 +
-// 224 1.004; beyond, 2008 + 256, 1.004.
+// 224 1.004; beyond, 2008 + 256, 1.004.  (With dQ first, see backward_dh, as many as there are.)
 constexpr int MERGED_MAX = 1024;
 constexpr int MERGED_MAX_PREFIX = 1536;
 constexpr float LOG2E = 1.4426950408889634f;
@@ -1282,7 +1282,7 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
                        seqs, key_block0, slices, part);
 }
 
-// dK/dV and dQ in one launch, the workgroups of dK/dV, the longer ones, first: for chunks that are a few rounds of the chip, where each
+// dK/dV and dQ in one launch, the longer workgroups first: for chunks that are a few rounds of the chip, where each
 // launch on its own leaves CUs idle at its end (777 windowed queries, 32 / 8 heads: 76 + 35 -> 102 us, the whole call 154 -> 141; what
 // a chunk of many rounds gains stands at MERGED_MAX).
 template <int DH, bool SPLIT, bool IN_TURN>
@@ -1290,10 +1290,11 @@ __device__ __forceinline__ void bwd_block(const bf16_t* __restrict__ q, const bf
                                           const bf16_t* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ lse2,
                                           const float* __restrict__ delta, bf16_t* __restrict__ dq, float* __restrict__ dk, float* __restrict__ dv,
                                           int Hq, int Hkv, int q_start, int c, float scale, const float2* __restrict__ rope, int window,
-                                          const AttnSeqs& seqs, int key_block0, int key_blocks, int slices, float* __restrict__ part, int q_blocks) {
+                                          const AttnSeqs& seqs, int key_block0, int key_blocks, int slices, float* __restrict__ part, int q_blocks, bool dq_first) {
   static_assert(AT_THREADS == KV_THREADS, "one workgroup shape");
   __shared__ __attribute__((aligned(1024))) union { DkvShared<DH> dkv; DqShared<DH, SPLIT> dq; } sh;
-  const int kv_heads = Hkv * seqs.n, heads = Hq * seqs.n, n_dkv = key_blocks * kv_heads * (IN_TURN ? 2 : part ? slices : 1), b = blockIdx.x;
+  const int kv_heads = Hkv * seqs.n, heads = Hq * seqs.n, n_dkv = key_blocks * kv_heads * (IN_TURN ? 2 : part ? slices : 1), n_dq = q_blocks * heads;
+  const int b = dq_first ? ((int)blockIdx.x < n_dq ? (int)blockIdx.x + n_dkv : (int)blockIdx.x - n_dq) : (int)blockIdx.x;
   if (b < n_dkv) {
     // The key blocks that most queries see first, all their workgroups side by side.  Workgroup b runs on XCD b % 8: with the key blocks side by side an
     // XCD had the same few of them, up to 2.4 times the work of another where a chunk starts at 0 (2048 queries from 0, 28 / 4 heads 182 -> 133 us, from 2048
@@ -1311,8 +1312,8 @@ __device__ __forceinline__ void bwd_block(const bf16_t* __restrict__ q, const bf
 #define BWD_PARAMS const bf16_t *__restrict__ q, const bf16_t *__restrict__ k, const bf16_t *__restrict__ v, const bf16_t *__restrict__ d_o, \
                    const float *__restrict__ lse, const float *__restrict__ lse2, const float *__restrict__ delta, bf16_t *__restrict__ dq, \
                    float *__restrict__ dk, float *__restrict__ dv, int Hq, int Hkv, int q_start, int c, float scale, \
-                   const float2 *__restrict__ rope, int window, const AttnSeqs seqs, int key_block0, int key_blocks, int slices, float *__restrict__ part, int q_blocks
-#define BWD_ARGS q, k, v, d_o, lse, lse2, delta, dq, dk, dv, Hq, Hkv, q_start, c, scale, rope, window, seqs, key_block0, key_blocks, slices, part, q_blocks
+                   const float2 *__restrict__ rope, int window, const AttnSeqs seqs, int key_block0, int key_blocks, int slices, float *__restrict__ part, int q_blocks, bool dq_first
+#define BWD_ARGS q, k, v, d_o, lse, lse2, delta, dq, dk, dv, Hq, Hkv, q_start, c, scale, rope, window, seqs, key_block0, key_blocks, slices, part, q_blocks, dq_first
 template <int DH, bool SPLIT> __global__ __launch_bounds__(AT_THREADS) void attn_bwd_mfma_k(BWD_PARAMS) { bwd_block<DH, SPLIT, false>(BWD_ARGS); }
 template <int DH, bool SPLIT> __global__ __launch_bounds__(AT_THREADS) void attn_bwd_in_turn_k(BWD_PARAMS) { bwd_block<DH, SPLIT, true>(BWD_ARGS); }
 #undef BWD_PARAMS
@@ -1483,12 +1484,22 @@ static hipError_t backward_dh(const AttnArgs& a, hipStream_t st) {
   const bool in_turn = !part && slices > 1 && blocks <= IN_TURN_BLOCKS;      // two workgroups per key block
   const int64_t n_dkv = blocks * (in_turn ? 2 : part ? slices : 1);
   const bf16_t *q = (const bf16_t*)a.q, *k = (const bf16_t*)a.k, *v = (const bf16_t*)a.v, *d_o = (const bf16_t*)a.d_o;
+  // dQ first in the one launch, which then has no limit, where its workgroups are the longer ones and leave a quarter of the CUs to dK/dV: last, they are a
+  // tail on a chip that is otherwise done.  Backward with forward, dQ last / first, from 16000 keys (512 queries, 32 / 8 heads) 742 / 655 us, 8000 (512, 32 / 32)
+  // 573 / 475 where dQ had been a launch of its own, 3000 (256, 28 / 4) 155 / 131, 30000 (512, 32 / 8) 1428 / 1208; slower at few sizes (640 from 8000, 32 / 8
+  // 429 / 439).  With more dQ workgroups their key tiles are shared in the L2 no better than the queries of dK/dV: 196 (896 from 20000, 28 / 4) 1120 / 1125, 224
+  // (1024 from 30720) 1797 / 1825.  The oldest key blocks of a window are seen by few queries, so dK/dV ends evenly: 36 steps against 32 215 / 224 last / first.
+  const int64_t first_visible = std::max<int64_t>(a.kv_first, a.window > 0 ? (int64_t)a.q_start - a.window + 1 : 0);
+  const int64_t dq_steps = cdiv(std::max<int64_t>((int64_t)a.q_start + a.q_len - first_visible, 0), halves ? 2 * TK : TK);
+  const int64_t seen_by = a.window > 0 ? std::min<int64_t>(a.q_len, (int64_t)a.window + KV_TILE) : a.q_len;
+  const int64_t dkv_steps = cdiv(seen_by, QT) * (a.Hq / a.Hkv) / (part ? slices : 1);
+  const bool dq_first = dq_steps > (a.window > 0 ? 2 : 1) * dkv_steps && q_tiles <= 192;
   const bool nothing_to_fill = n_dkv >= 512 && n_dkv % 256 == 0 && q_tiles < 256;
-  if (n_dkv > 0 && (in_turn || (n_dkv + q_tiles <= (a.q_start > 0 ? MERGED_MAX_PREFIX : MERGED_MAX) && !nothing_to_fill))) {
+  if (n_dkv > 0 && (in_turn || (dq_first && a.q_start > 0) || (n_dkv + q_tiles <= (a.q_start > 0 ? MERGED_MAX_PREFIX : MERGED_MAX) && !nothing_to_fill))) {
     auto launch = [&](auto kernel) {
       kernel<<<(unsigned)(n_dkv + q_tiles), AT_THREADS, 0, st>>>(q, k, v, d_o, a.lse, lse2, a.delta, (bf16_t*)a.dq, a.dk, a.dv, a.Hq, a.Hkv, a.q_start,
                                                                          a.q_len, a.scale, a.rope_q, a.window, seqs, kb0, key_blocks, slices, part,
-                                                                         (int)q_blocks);
+                                                                         (int)q_blocks, dq_first);
     };
     if (in_turn && halves) launch(attn_bwd_in_turn_k<DH, true>);
     else if (in_turn) launch(attn_bwd_in_turn_k<DH, false>);
