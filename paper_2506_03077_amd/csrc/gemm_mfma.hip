@@ -292,7 +292,8 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
             }
         __syncthreads();
         const int c4 = threadIdx.x & 63;
-        const int past = n0 + c4 * 4 < N ? 0 : 0x40000000;      // columns that C does not have are dropped too (2048 x 32 x 18944, 176 tiles 32.4 -> 29.8 us)
+        // an output narrower than a tile: without the columns that it does not have (2048 x 32 x 18944, 176 tiles 32.4 -> 29.8 us); a wider one's are few tiles of many
+        const int past = N < BN && c4 * 4 >= N ? 0x40000000 : 0;
 #pragma unroll
         for (int p = 0; p < 16; ++p) {
           const int row_l = p * 8 + (threadIdx.x >> 6);
