@@ -184,21 +184,23 @@ struct AgShape { int Hq, Hkv, dh, q_start, c; float scale; int window, kv_first;
 __device__ __forceinline__ int first_key(const AgShape& a, int pos) { return max(a.kv_first, a.window > 0 ? pos - a.window + 1 : 0); }
 
 // What a wave is: a slot takes every SLOTS-th block, its waves a share of the head each
-#define AG_WAVE_SETUP(N)                                                                                          \
+#define AG_WAVE_SETUP                                                                                             \
   using Pt = Parts<DB, P, W>;                                                                                    \
   constexpr int SLOTS = Pt::SLOTS;                                                                               \
   constexpr bool FIRST = P == 1;                                                                                 \
-  __shared__ __attribute__((aligned(16))) float part[N * Pt::FLOATS];                                            \
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), slot = wave / P, share = wave % P, d0 = share * DB; \
   const int li = threadIdx.x & 15, lg4 = (threadIdx.x & 63) >> 4 << 2
 // (P == 1: a wave's own number of rounds; else all waves run the same, for the barrier in each)
 #define AG_ROUNDS(n) (P == 1 ? ((n) - slot + SLOTS - 1) / SLOTS : ((n) + SLOTS - 1) / SLOTS)
 
+#define AG_PARTS(N) __shared__ __attribute__((aligned(16))) float part[(N) * Parts<DB, P, W>::FLOATS]
+
 // ---- forward.  rope: q arrives un-rotated, is rotated on load and written back rotated.
 template <typename T, int DB, int P, int W>
 __global__ __launch_bounds__(W * 64) void attn_fwd_generic_k(T* q, const T* __restrict__ k, const T* __restrict__ v, T* __restrict__ o,
                                                                  float* __restrict__ lse, AgShape a, const float2* __restrict__ rope) {
-  AG_WAVE_SETUP(1);
+  AG_PARTS(1);
+  AG_WAVE_SETUP;
   __shared__ f32x4 sX[EXCHANGE<P, 1, W>];
   __shared__ float sM[SLOTS][16], sL[SLOTS][16], sF[SLOTS][16], sT[16];
   const int h = blockIdx.y, t0 = blockIdx.x * 16, kvh = h / (a.Hq / a.Hkv);
@@ -336,14 +338,13 @@ __global__ __launch_bounds__(W * 64) void attn_fwd_generic_k(T* q, const T* __re
 
 // ---- dQ; also delta[h, t] = sum_j d_o[t,h,j] * o[t,h,j], which dK/dV reads.  rope: dq leaves rotated back.
 template <typename T, int DB, int P, int W>
-__global__ __launch_bounds__(W * 64) void attn_dq_generic_k(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
-                                                                const T* __restrict__ o, const T* __restrict__ d_o, const float* __restrict__ lse,
-                                                                float* __restrict__ delta, T* __restrict__ dq, AgShape a,
-                                                                const float2* __restrict__ rope) {
-  AG_WAVE_SETUP(1);
+__device__ __forceinline__ void dq_block(float* part, int tile, int h, const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
+                                         const T* __restrict__ o, const T* __restrict__ d_o, const float* __restrict__ lse, float* __restrict__ delta,
+                                         T* __restrict__ dq, const AgShape& a, const float2* __restrict__ rope) {
+  AG_WAVE_SETUP;
   __shared__ f32x4 sX[EXCHANGE<P, 2, W>];
   __shared__ float sD[P][16];
-  const int h = blockIdx.y, t0 = blockIdx.x * 16, kvh = h / (a.Hq / a.Hkv);
+  const int t0 = tile * 16, kvh = h / (a.Hq / a.Hkv);
   const int kv_stride = a.Hkv * a.dh;
   const T *kb = k + (int64_t)kvh * a.dh, *vb = v + (int64_t)kvh * a.dh;
   const int t = min(t0 + li, a.c - 1), pos = a.q_start + t;
@@ -385,7 +386,7 @@ __global__ __launch_bounds__(W * 64) void attn_dq_generic_k(const T* __restrict_
 #pragma unroll
     for (int i = 1; i < P; ++i) D += sD[i][li];
   }
-  if (wave == 0 && lg4 == 0 && t0 + li < a.c) delta[(int64_t)h * a.c + t] = D;
+  if (delta && wave == 0 && lg4 == 0 && t0 + li < a.c) delta[(int64_t)h * a.c + t] = D;
   f32x4 acc[DB];
 #pragma unroll
   for (int d = 0; d < DB; ++d) acc[d] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -440,16 +441,26 @@ __global__ __launch_bounds__(W * 64) void attn_dq_generic_k(const T* __restrict_
   }
 }
 
-// ---- dK/dV (and dkc, dvc of the chunk's own rows, final with this call): 16 keys of one KV head; the slots walk blocks of 16 queries that see some of them, for every query head of the group
-// (Launch bounds: fp32 heads of 65 to 128 elements need 129 registers otherwise, one more than lets two workgroups share a CU.)
 template <typename T, int DB, int P, int W>
-__global__ __launch_bounds__(W * 64, DB * P == 8 ? 4 : 1) void attn_dkv_generic_k(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
-                                                                                  const T* __restrict__ d_o, const float* __restrict__ lse,
-                                                                                  const float* __restrict__ delta, float* __restrict__ dk, float* __restrict__ dv,
-                                                                                  AgShape a, T* __restrict__ dkc, T* __restrict__ dvc, const float2* __restrict__ rope) {
-  AG_WAVE_SETUP(2);
+__global__ __launch_bounds__(W * 64) void attn_dq_generic_k(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
+                                                                const T* __restrict__ o, const T* __restrict__ d_o, const float* __restrict__ lse,
+                                                                float* __restrict__ delta, T* __restrict__ dq, AgShape a,
+                                                                const float2* __restrict__ rope) {
+  AG_PARTS(1);
+  dq_block<T, DB, P, W>(part, blockIdx.x, blockIdx.y, q, k, v, o, d_o, lse, delta, dq, a, rope);
+}
+
+// ---- dK/dV (and dkc, dvc of the chunk's own rows, final with this call): 16 keys of one KV head; the slots walk blocks of 16 queries that see some of them, for every query head of the group
+// DELTA: D of the queries from d_o and o, as dQ forms it, in place of reading what dQ has left.
+template <typename T, int DB, int P, int W, bool DELTA>
+__device__ __forceinline__ void dkv_block(float* part, int block, int kvh, const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
+                                          const T* __restrict__ o, const T* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ delta,
+                                          float* __restrict__ dk, float* __restrict__ dv, const AgShape& a, T* __restrict__ dkc, T* __restrict__ dvc,
+                                          const float2* __restrict__ rope) {
+  static_assert(!DELTA || P == 1, "a wave has whole rows of d_o and o");
+  AG_WAVE_SETUP;
   __shared__ f32x4 sX[EXCHANGE<P, 2, W>];
-  const int kvh = blockIdx.y, u0 = blockIdx.x * 16, G = a.Hq / a.Hkv;
+  const int u0 = block * 16, G = a.Hq / a.Hkv;
   const int n_total = a.q_start + a.c, u = min(u0 + li, n_total - 1);          // my key
   const int kv_stride = a.Hkv * a.dh, q_stride = a.Hq * a.dh;
   const int t_first = max(0, u0 - a.q_start);                                  // rows before it see none of the keys, nor do rows from t_end on
@@ -457,7 +468,7 @@ __global__ __launch_bounds__(W * 64, DB * P == 8 ? 4 : 1) void attn_dkv_generic_
   if (a.window > 0) t_end = (int)min((int64_t)a.c, max((int64_t)0, (int64_t)u0 + 15 + a.window - a.q_start));
   if (u0 + 15 < a.kv_first) t_end = 0;
   const int b0 = t_first / 16, n_it = max(0, (t_end + 15) / 16 - b0) * G;
-  typename Raw<T>::four qr[DB], dr[DB], raw_k[DB], raw_v[DB];
+  typename Raw<T>::four qr[DB], dr[DB], orow[DELTA ? DB : 1], raw_k[DB], raw_v[DB];
   typename Raw<T>::one dt[DB][4], qt[DB][4];
   float L[4], D[4];
   auto head_of = [&](int it) { return kvh * G + it % G; };
@@ -467,6 +478,7 @@ __global__ __launch_bounds__(W * 64, DB * P == 8 ? 4 : 1) void attn_dkv_generic_
     const int row = min(li, a.c - 1 - query_of(it));
     load_row<T, DB>(qr, q + first_of(it), row, q_stride, FIRST, d0, lg4, a.dh);
     load_row<T, DB>(dr, d_o + first_of(it), row, q_stride, FIRST, d0, lg4, a.dh);
+    if constexpr (DELTA) load_row<T, DB>(orow, o + first_of(it), row, q_stride, FIRST, d0, lg4, a.dh);
   };
   auto load_cols = [&](int it) {
     const int last = a.c - 1 - query_of(it);
@@ -474,7 +486,7 @@ __global__ __launch_bounds__(W * 64, DB * P == 8 ? 4 : 1) void attn_dkv_generic_
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       L[r] = (lse + at)[min(lg4 + r, last)];
-      D[r] = (delta + at)[min(lg4 + r, last)];
+      if constexpr (!DELTA) D[r] = (delta + at)[min(lg4 + r, last)];
     }
     load_across<T, DB>(dt, d_o + first_of(it), lg4, last, q_stride, FIRST, d0, li, a.dh);
     load_across<T, DB>(qt, q + first_of(it), lg4, last, q_stride, FIRST, d0, li, a.dh);
@@ -511,6 +523,7 @@ __global__ __launch_bounds__(W * 64, DB * P == 8 ? 4 : 1) void attn_dkv_generic_
     f32x4 sc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
     f32x4 &s = sc[0], &dp = sc[1];
     if (on) {
+      float dot = 0.f;
 #pragma unroll
       for (int d = 0; d < DB; ++d) {
         const f32x4 qd = row_piece<T, DB>(Raw<T>::value(qr[d]), FIRST, d0, d, lg4, a.dh), dd = row_piece<T, DB>(Raw<T>::value(dr[d]), FIRST, d0, d, lg4, a.dh);
@@ -519,6 +532,16 @@ __global__ __launch_bounds__(W * 64, DB * P == 8 ? 4 : 1) void attn_dkv_generic_
           s = AG_MFMA(qd[j], kf[d][j], s);
           dp = AG_MFMA(dd[j], vf[d][j], dp);
         }
+        if constexpr (DELTA) {
+          const f32x4 of = row_piece<T, DB>(Raw<T>::value(orow[d]), FIRST, d0, d, lg4, a.dh);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) dot += dd[j] * of[j];
+        }
+      }
+      if constexpr (DELTA) {
+        dot = over_groups(dot);                // of query t0 + li
+#pragma unroll
+        for (int r = 0; r < 4; ++r) D[r] = __shfl(dot, lg4 + r, WAVE);
       }
       if (next < n_it) load_rows(next);
     }
@@ -577,6 +600,29 @@ __global__ __launch_bounds__(W * 64, DB * P == 8 ? 4 : 1) void attn_dkv_generic_
   finish(1, dv, dvc);
 }
 
+// (Launch bounds: fp32 heads of 65 to 128 elements need 129 registers otherwise, one more than lets two workgroups share a CU.)
+template <typename T, int DB, int P, int W>
+__global__ __launch_bounds__(W * 64, DB * P == 8 ? 4 : 1) void attn_dkv_generic_k(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
+                                                                                  const T* __restrict__ d_o, const float* __restrict__ lse,
+                                                                                  const float* __restrict__ delta, float* __restrict__ dk, float* __restrict__ dv,
+                                                                                  AgShape a, T* __restrict__ dkc, T* __restrict__ dvc, const float2* __restrict__ rope) {
+  AG_PARTS(2);
+  dkv_block<T, DB, P, W, false>(part, blockIdx.x, blockIdx.y, q, k, v, nullptr, d_o, lse, delta, dk, dv, a, dkc, dvc, rope);
+}
+// dK/dV and dQ side by side, neither waiting for the other: the workgroups of dK/dV form delta themselves, the same sums in the same order.
+template <typename T, int DB>
+__global__ __launch_bounds__(512) void attn_bwd_narrow_k(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, const T* __restrict__ o,
+                                                          const T* __restrict__ d_o, const float* __restrict__ lse, T* __restrict__ dq, float* __restrict__ dk,
+                                                          float* __restrict__ dv, AgShape a, T* __restrict__ dkc, T* __restrict__ dvc,
+                                                          const float2* __restrict__ rope_q, const float2* __restrict__ rope_k, int n_first, bool dq_first) {
+  constexpr int P = 1, W = 8;
+  AG_PARTS(2);
+  const bool first = (int)blockIdx.x < n_first;
+  const int b = (int)blockIdx.x - (first ? 0 : n_first);
+  if (first != dq_first) dkv_block<T, DB, P, W, true>(part, b / a.Hkv, b % a.Hkv, q, k, v, o, d_o, lse, nullptr, dk, dv, a, dkc, dvc, rope_k);
+  else dq_block<T, DB, P, W>(part, b / a.Hq, b % a.Hq, q, k, v, o, d_o, lse, nullptr, dq, a, rope_q);
+}
+
 static AgShape shape_of(const AttnArgs& a) { return AgShape{a.Hq, a.Hkv, a.dh, a.q_start, a.q_len, a.scale, a.window, a.kv_first}; }
 // Instances: pieces per wave, waves per block, waves.  Heads of up to 64 elements: one wave per block.  Wider ones, whose operands would not fit a wave's
 // registers: two, or four - where there are few blocks, where the registers of two would spill (dK/dV, dQ of more than 160 elements), and, on sixteen waves, in
@@ -621,10 +667,25 @@ static hipError_t forward_t(const AttnArgs& a, hipStream_t st) {
   if (a.dh <= 64) narrow_heads(a.dh, go); else if (few_keys(a)) four_per_block(a.dh, go); else forward_long(a.dh, go);
   return hipGetLastError();
 }
+// dQ and dK/dV of heads of up to 64 elements in one launch: without a prefix, up to 1024 workgroups, or with few of dQ behind a long prefix, which come first as
+// the longer ones (so do they wherever a key block has fewer query blocks than the other way round).  Backward apart / in one, fp32, us: 256 queries from 0, 4 heads
+// of 16 10.9 / 6.6, 8 of 64 24.2 / 14.6, 16 of 64, 512 queries, 71.6 / 54.9; 2048 queries, 8 of 64 330 / 268, 16 of 32 297 / 228, bf16 4096, 8 of 16 336 / 262; 64 from
+// 3000, 2 of 16 30.2 / 25.2; 128 from 30000, 16 of 32 741 / 534.  Behind a prefix with more workgroups the loads of o, which dK/dV reads as well, outweigh it: 256 from
+// 8000, 16 of 64 442 / 464, 2048 from 8000 3785 / 3840.
+constexpr int64_t ONE_LAUNCH_MAX = 1024, ONE_LAUNCH_DQ = 192;
 template <typename T>
 static hipError_t backward_t(const AttnArgs& a, hipStream_t st) {
   const AgShape s = shape_of(a);
   const dim3 gq((unsigned)cdiv(a.q_len, 16), (unsigned)a.Hq), gk((unsigned)cdiv((int64_t)a.q_start + a.q_len, 16), (unsigned)a.Hkv);
+  const int64_t n_dkv = (int64_t)gk.x * gk.y, n_dq = (int64_t)gq.x * gq.y, n = n_dkv + n_dq;
+  const bool dq_first = (int64_t)gk.x > (int64_t)gq.x * (a.Hq / a.Hkv);
+  if (a.dh <= 64 && n <= INT32_MAX && (a.q_start == 0 || n <= ONE_LAUNCH_MAX || (dq_first && n_dq <= ONE_LAUNCH_DQ))) {
+    narrow_heads(a.dh, [&](auto db, auto, auto) {
+      attn_bwd_narrow_k<T, decltype(db)::value><<<(unsigned)n, 512, 0, st>>>((const T*)a.q, (const T*)a.k, (const T*)a.v, (const T*)a.o, (const T*)a.d_o, a.lse, (T*)a.dq,
+                                                                            a.dk, a.dv, s, (T*)a.dkc, (T*)a.dvc, a.rope_q, a.rope_k, (int)(dq_first ? n_dq : n_dkv), dq_first);
+    });
+    return hipGetLastError();
+  }
   auto dq = [&](auto db, auto p, auto w) {
     attn_dq_generic_k<T, decltype(db)::value, decltype(p)::value, decltype(w)::value><<<gq, decltype(w)::value * 64, 0, st>>>((const T*)a.q, (const T*)a.k, (const T*)a.v, (const T*)a.o, (const T*)a.d_o,
                                                                                         a.lse, a.delta, (T*)a.dq, s, a.rope_q);
