@@ -312,6 +312,12 @@ GemmArgs mk(const void* A, const void* B, void* C, int M, int N, int K, int64_t 
 GemmArgs fwd_gemm(const void* X, const void* W, void* Y, int M, int N, int K, int dt, int out_dt) {
   return mk(X, W, Y, M, N, K, K, K, N, false, true, dt, out_dt, false);
 }
+// RoPE of K in the store of its product: fp32 products, heads that divide the kernel's tiles.  False: a pass over K is left to do.
+bool rope_in_store(GemmArgs& g, const float2* table, int period, int dh) {
+  if (g.in_dt != DT_F32 || dh % 2 != 0 || GEMM_ROPE_COLS % dh != 0) return false;
+  g.rope = table; g.rope_dim = dh; g.rope_period = period;
+  return true;
+}
 // dX[M,K] (=|+=) dY[M,N] W[N,K]
 GemmArgs dx_gemm(const void* dY, const void* W, void* dX, int M, int N, int K, int dt, int out_dt, bool acc) {
   return mk(dY, W, dX, M, K, N, N, K, K, false, false, dt, out_dt, acc);
@@ -354,10 +360,11 @@ int32_t kv_prepass(const sbp_layer_cfg* c, const sbp_layer_weights* w, const Lay
   for (int r0 = 0; r0 < T; r0 += block) {
     const int n = std::min(block, T - r0);
     HIPCHK(rmsnorm_fwd(dt, at(xb, r0, d, es), nullptr, w->g1, a_rows, nullptr, nullptr, n, d, c->rms_eps, st));
-    const GemmArgs kv[2] = {fwd_gemm(a_rows, w->wk, at(s.K, r0, kd, es), n, kd, d, dt, dt),
-                            fwd_gemm(a_rows, w->wv, at(s.V, r0, kd, es), n, kd, d, dt, dt)};
+    GemmArgs kv[2] = {fwd_gemm(a_rows, w->wk, at(s.K, r0, kd, es), n, kd, d, dt, dt),
+                      fwd_gemm(a_rows, w->wv, at(s.V, r0, kd, es), n, kd, d, dt, dt)};
+    const bool rotated = rope_in_store(kv[0], s.rope + (size_t)r0 * (c->head_dim / 2), n, c->head_dim);
     HIPCHK(gemm_batch(kv, 2, st));
-    HIPCHK(rope_apply(dt, at(s.K, r0, kd, es), s.rope + (size_t)r0 * (c->head_dim / 2), n, n, c->n_kv_heads, c->head_dim, false, st));
+    if (!rotated) HIPCHK(rope_apply(dt, at(s.K, r0, kd, es), s.rope + (size_t)r0 * (c->head_dim / 2), n, n, c->n_kv_heads, c->head_dim, false, st));
   }
   return SBP_OK;
 }
@@ -382,12 +389,13 @@ int32_t chunk_reforward(const sbp_layer_cfg* c, const sbp_layer_weights* w, cons
   const int d = c->hidden, F = c->mlp_width, qd = c->n_q_heads * c->head_dim, kd = c->n_kv_heads * c->head_dim;
   const int n = (int)pass_rows(p);
   HIPCHK(rmsnorm_fwd(dt, xc, nullptr, w->g1, s.a, nullptr, s.rstd1, n, d, c->rms_eps, st));
-  const GemmArgs qkv[3] = {fwd_gemm(s.a, w->wq, s.q, n, qd, d, dt, dt), fwd_gemm(s.a, w->wk, s.K, n, kd, d, dt, dt), fwd_gemm(s.a, w->wv, s.V, n, kd, d, dt, dt)};
+  GemmArgs qkv[3] = {fwd_gemm(s.a, w->wq, s.q, n, qd, d, dt, dt), fwd_gemm(s.a, w->wk, s.K, n, kd, d, dt, dt), fwd_gemm(s.a, w->wv, s.V, n, kd, d, dt, dt)};
   // q with K and V in one launch, as a grouped one or on the kernels for few tiles.  Whole layer, q apart / in one: 64 rows at 7B widths 923 -> 895 us
   // (forward 213 -> 192), 300 rows 1181 -> 1167 (320 -> 303), 640 at 4096 / 14336 1448 -> 1428 (412 -> 385), 1023 at 2048 / 5632 581 -> 574
   // (175 -> 167), 1023 at 1024 / 2816 283 -> 278 (104 -> 100), 2560 at 7B widths 3330 -> 3279; 900 rows at 4096 / 14336 and 7B widths the same.
+  const bool rotated = p.whole && rope_in_store(qkv[1], s.rope, p.n, c->head_dim);
   HIPCHK(gemm_batch(qkv, p.whole ? 3 : 1, st));
-  if (p.whole) {
+  if (p.whole && !rotated) {
     HIPCHK(rope_apply(dt, s.K, s.rope, n, p.n, c->n_kv_heads, c->head_dim, false, st));
   }
   const AttnArgs aa = pass_attn(c, s, p);      // with RoPE(q) inside the kernel, which leaves s.q rotated
@@ -757,7 +765,7 @@ static int32_t check_head_cfg(const sbp_head_cfg* c) {
 }
 
 // The weight gradient of the head is accumulated once per group of chunks (dw_group_for): dz and the gathered h rows of that
-// many chunks stay alive and one GEMM with a segmented reduction adds them into dW, so the 8 bytes per element of
+// many chunks stay alive and one GEMM adds them into dW, so the 8 bytes per element of
 // read-modify-write traffic on dW (the largest tensor of the path) are paid once per group instead of once per
 // chunk.  The fp32 logits - the dominant term - still exist for one chunk only.
 struct HeadWs {

@@ -120,6 +120,7 @@ hipError_t gemm(const GemmArgs& g, hipStream_t st) {
     plain.C0 = nullptr;
     return gemm(plain, st);
   }
+  if (g.rope && g.in_dt != DT_F32) return hipErrorInvalidValue;
   if (g.numer_targets) {
     if (!gemm_numerators_supported(g)) return hipErrorInvalidValue;               // only the MFMA store form has them
   } else if (g.row_stats && !gemm_row_stats_supported(g)) return hipErrorInvalidValue;   // only the MFMA store form emits them

@@ -6,6 +6,7 @@
 
 #include <algorithm>
 #include <iterator>
+#include <type_traits>
 
 namespace sbp {
 
@@ -16,7 +17,7 @@ namespace sbp {
 // through LDS (the earlier form): 64 x 64 x 64 10.7 -> 3.2 us, 64 x 64 x 512 67 -> 6.5, 256 x 1500 x 256 36 -> 7.4; what reads of the
 // operands bound later is no worse: 1024^3 178 -> 35, 2048^3 416 -> 232 us (74 TFLOP/s).
 // Lane l holds, of a 16-row block, row l % 16 at k 4 (l / 16) .. + 3 of the step; MFMA j of the step takes element j of both operands.
-constexpr int TILE = 32, WAVES = 8, KSTEP = 16;
+constexpr int TILE = GEMM_ROPE_COLS, WAVES = 8, KSTEP = 16;
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // An operand's four elements of a row and step, held as they were loaded until the product that takes them (a conversion would wait for them in front of the
@@ -98,8 +99,12 @@ using GenericAll = GenericArgs<GENERIC_PROBLEMS, GENERIC_SEGMENTS>;
 // gate (optional; rows of ldc elements, like C, which is then not written): the product is the gradient wrt act = silu(gate) * up; act gets that
 // value, gate and up their gradients, in place.
 struct GenericSwiglu { void *gate, *up, *act; };
+// tab (optional): the output of problem `problem` is rotated, heads of 2 * half columns, which divide a tile; the angles are fetched before the products.
+// (As a pass over K: one launch more of a chain of 24, 96 us against 89.5 for a 256-token fp32 layer with its head.)
+struct GenericRope { const float2* tab; int half, period, problem; };
 template <typename TI, typename TO, int NP, int NS>
-__global__ __launch_bounds__(WAVES * 64) void gemm_generic_k(const GenericArgs<NP, NS> ga, const GenericSwiglu sw) {
+__global__ __launch_bounds__(WAVES * 64) void gemm_generic_k(const GenericArgs<NP, NS> ga, const GenericSwiglu sw, const GenericRope rope) {
+  constexpr bool ROPE = !std::is_same_v<TI, bf16_t> && NP <= 3;      // (K beside V, or beside q and V)
   int pi = 0;
 #pragma unroll
   for (int i = 1; i < NP; ++i)
@@ -113,6 +118,16 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_generic_k(const GenericArgs<N
   __shared__ float part[WAVES][TILE][TILE + 1];
   if (m0 >= M) return;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), li = threadIdx.x & 15, lg = (threadIdx.x & 63) >> 4;
+  constexpr int OUT = TILE * TILE / (WAVES * 64);      // elements of C per thread
+  const bool rotated = ROPE && rope.tab && pi == rope.problem;
+  float2 cs[OUT];
+  if (rotated) {
+#pragma unroll
+    for (int e = 0; e < OUT; ++e) {
+      const int id = e * WAVES * 64 + (int)threadIdx.x;
+      cs[e] = rope.tab[(int64_t)(min(m0 + id / TILE, M - 1) % rope.period) * rope.half + (id % TILE) % rope.half];
+    }
+  }
   f32x4 acc[2][2] = {};
   // The steps of all segments, one after the other, dealt to the waves: k0 = this wave's next one.  What a step reads by is kept in registers and
   // changes with the segment (NS == 1: never).
@@ -168,11 +183,18 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_generic_k(const GenericArgs<N
   }
   __syncthreads();
 #pragma unroll
-  for (int e = 0; e < TILE * TILE / (WAVES * 64); ++e) {
+  for (int e = 0; e < OUT; ++e) {
     const int id = e * WAVES * 64 + (int)threadIdx.x, row = id / TILE, col = id % TILE;
     if (m0 + row >= M || n0 + col >= N) continue;
     float v = 0.f;
     for (int w = 0; w < waves; ++w) v += part[w][row][col];
+    if (rotated) {
+      const bool up = col % (2 * rope.half) >= rope.half;
+      const int pair = up ? col - rope.half : col + rope.half;
+      float x = 0.f;
+      for (int w = 0; w < waves; ++w) x += part[w][row][pair];
+      v = v * cs[e].x + (up ? x : -x) * cs[e].y;
+    }
     const int64_t at = (int64_t)(m0 + row) * g.ldc + n0 + col;
     if (NP == 1 && sw.gate) {
       TO *gate = (TO*)sw.gate + at, *up = (TO*)sw.up + at;
@@ -237,13 +259,23 @@ hipError_t gemm_generic(const GemmArgs* gs, int n, bool sum, hipStream_t st) {
   if (!generic_args(gs, n, sum, ga, tiles)) return hipErrorInvalidValue;
   if (ga.n == 0) return hipSuccess;
   const GemmArgs& g = gs[0];
+  GenericRope rope{};
+  for (int i = 0; i < n; ++i) {
+    if (!gs[i].rope) continue;
+    // (n problems without a shared or empty output: the i-th of them)
+    if (rope.tab || ga.n != n || gs[i].in_dt == DT_BF16 || gs[i].acc || gs[i].ta || !gs[i].tb || gs[i].rope_dim < 2 || TILE % gs[i].rope_dim || gs[i].rope_dim % 2 ||
+        gs[i].N % gs[i].rope_dim || gs[i].rope_period < 1)
+      return hipErrorInvalidValue;
+    rope = GenericRope{gs[i].rope, gs[i].rope_dim / 2, gs[i].rope_period, i};
+  }
   int n_seg = 0;
   for (int i = 0; i < ga.n; ++i) n_seg += ga.p[i].nseg;
+  if (rope.tab && n_seg > 3) return hipErrorInvalidValue;
   auto go = [&](auto kernel, auto args) {
     args.n = ga.n;
     std::copy_n(ga.p, std::min<size_t>(std::size(args.p), ga.n), args.p);
     std::copy_n(ga.s, std::min<size_t>(std::size(args.s), n_seg), args.s);
-    kernel<<<(unsigned)tiles, WAVES * 64, 0, st>>>(args, GenericSwiglu{gs[0].swiglu_gate, gs[0].swiglu_up, gs[0].swiglu_act});
+    kernel<<<(unsigned)tiles, WAVES * 64, 0, st>>>(args, GenericSwiglu{gs[0].swiglu_gate, gs[0].swiglu_up, gs[0].swiglu_act}, rope);
   };
 #define GG(TI, TO)                                                                                             \
   do {                                                                                                         \

@@ -62,10 +62,15 @@ struct GemmArgs {
   const void* glu_up = nullptr;
   // Accumulated bf16 C: C = C0 + A B instead (C0 laid out like C)
   const void* C0 = nullptr;
+  // Optional rotary embedding of a stored C = A B^T (fp32, one of a launch's problems): heads of rope_dim columns, a divisor of GEMM_ROPE_COLS, row r by row
+  // r % rope_period of the table
+  const float2* rope = nullptr;
+  int rope_dim = 0, rope_period = 0;
   // Outputs of few tiles may go to the kernels of gemm_few.hip (which split no reduction over workgroups and leave `scratch` alone)
   bool few_ok = false;
 };
 constexpr int GEMM_STAT_COLS = 256;
+constexpr int GEMM_ROPE_COLS = 32;      // (of a tile of the shape-agnostic kernel, which all fp32 products run on)
 bool gemm_row_stats_supported(const GemmArgs& g);
 bool gemm_numerators_supported(const GemmArgs& g);
 bool gemm_glu_supported(const GemmArgs& g);
