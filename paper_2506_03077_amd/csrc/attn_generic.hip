@@ -678,8 +678,9 @@ static hipError_t backward_t(const AttnArgs& a, hipStream_t st) {
   const AgShape s = shape_of(a);
   const dim3 gq((unsigned)cdiv(a.q_len, 16), (unsigned)a.Hq), gk((unsigned)cdiv((int64_t)a.q_start + a.q_len, 16), (unsigned)a.Hkv);
   const int64_t n_dkv = (int64_t)gk.x * gk.y, n_dq = (int64_t)gq.x * gq.y, n = n_dkv + n_dq;
+  // (dq may take o's place: dK/dV then has to be a launch that does not read o)
   const bool dq_first = (int64_t)gk.x > (int64_t)gq.x * (a.Hq / a.Hkv);
-  if (a.dh <= 64 && n <= INT32_MAX && (a.q_start == 0 || n <= ONE_LAUNCH_MAX || (dq_first && n_dq <= ONE_LAUNCH_DQ))) {
+  if (a.dh <= 64 && a.dq != a.o && n <= INT32_MAX && (a.q_start == 0 || n <= ONE_LAUNCH_MAX || (dq_first && n_dq <= ONE_LAUNCH_DQ))) {
     narrow_heads(a.dh, [&](auto db, auto, auto) {
       attn_bwd_narrow_k<T, decltype(db)::value><<<(unsigned)n, 512, 0, st>>>((const T*)a.q, (const T*)a.k, (const T*)a.v, (const T*)a.o, (const T*)a.d_o, a.lse, (T*)a.dq,
                                                                             a.dk, a.dv, s, (T*)a.dkc, (T*)a.dvc, a.rope_q, a.rope_k, (int)(dq_first ? n_dq : n_dkv), dq_first);

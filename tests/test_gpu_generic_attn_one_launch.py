@@ -1,7 +1,9 @@
 """Backward of the shape-agnostic attention for heads of up to 64 elements, dQ and dK/dV in one launch with either first and apart, against the fp64 oracle:
 each number of 16-wide pieces, ragged heads, windows, padding, both storage types."""
 import pytest
+import torch
 
+from paper_2506_03077_amd import binding as sb
 from test_gpu_masks import masked_attn_case
 
 pytestmark = pytest.mark.gpu
@@ -17,3 +19,8 @@ pytestmark = pytest.mark.gpu
 ])
 def test_backward(dtype, hq, hkv, dh, s, c, window, kv_first):
     masked_attn_case(dtype, hq, hkv, dh, s, c, window, kv_first)
+
+
+def test_dq_in_the_place_of_o():
+    q, k, v, d_o, ac, o, lse, dq, dk, dv, _ = masked_attn_case("f32", 4, 2, 16, 30, 400, 0, 0)
+    assert all(torch.equal(a, b) for a, b in zip((dq, dk, dv), sb.streambp_attn_chunk_backward(ac, q, k, v, o, lse, d_o, dq=o)))
