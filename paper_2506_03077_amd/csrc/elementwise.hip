@@ -584,7 +584,7 @@ __global__ __launch_bounds__(256) void pad_matrices_k(const PadJobs jobs, int64_
   float v[8];
   if (p.transposed) {      // eight rows of a column: neighbours in src, and the lanes' columns neighbours in dst
     const int r0 = (int)(at / p.C2) * 8, c = (int)(at % p.C2);
-    if (c < p.C && p.R % 8 == 0 && !((uintptr_t)src & 15)) load8(src + (int64_t)c * p.R + r0, v);
+    if (c < p.C && r0 < p.R && p.R % 8 == 0 && !((uintptr_t)src & 15)) load8(src + (int64_t)c * p.R + r0, v);
     else {
 #pragma unroll
       for (int k = 0; k < 8; ++k) v[k] = c < p.C && r0 + k < p.R ? ldf(src + (int64_t)c * p.R + r0 + k) : 0.f;
