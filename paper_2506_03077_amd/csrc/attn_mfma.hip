@@ -88,6 +88,13 @@ template <int DH> constexpr int TERMS = DH == 64 ? 2 : 1;
 template <int DH> constexpr int KV_TERMS = DH == 64 ? 3 : 1;
 template <int DH> constexpr bool FP32_STATS = DH == 64;
 
+// Two values rounded to bf16 by one instruction, and what that leaves of them.  Element by element the conversions were a fifth of the vector work of DH = 64
+// (dQ and dK/dV of 1840 queries behind 5360 keys, 12 / 2 heads, 327 -> 304 us); DH = 128, which has no rests to form, is 0.5 % slower this way.
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef bf16_t bf16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ bf16x2 round2(f32x2 x) { return __builtin_convertvector(x, bf16x2); }
+__device__ __forceinline__ f32x2 rest2(f32x2 x, bf16x2 w) { return f32x2{x[0] - (float)w[0], x[1] - (float)w[1]}; }
+
 // exp(x * scale + c): c in log2 units, or in natural ones where the statistics keep fp32
 template <int DH>
 __device__ __forceinline__ float exp_of(float x, float scale, float sl, float c) {
@@ -627,6 +634,11 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
 // 16x16x32 MFMAs take less of that power than 32x32x16 ones: the kernel itself on that chunk 1123 -> 1050 us.
 // A wave's tiles are one loop without branches around the products, the stages moving with the addresses: with four steps unrolled, each skipping its products by a
 // branch, the accumulators of four registers are moved about and 130 registers spill (1925 us).
+// With few workgroups it is a step's instructions, slot by slot: the groups' slots are as long as the longer of the two, so what need not be in that one is in
+// the other.  DH = 128 multiplies longer, and moves its fragments' addresses on in the vector slot; DH = 64 has the longer vector slot, and SPLIT loads at the start of the
+// multiply slot.  27 queries behind 8877 keys, 12 / 2 heads of 128, backward 130.9 -> 129.9 us with the addresses moved, -> 122.5 with loads that pick their row offsets
+// without a branch (the 32x32x16 kernel, steps unrolled, 126.4); 19 behind 4601, 16 / 4 heads of 64, 73.6 -> 71.2 without the branch, -> 69.5 with the loads moved,
+// -> 65.5 with conversions two at a time (69.0).  More fragments requested ahead (7) or the two halves of the vector work not kept apart: no faster.
 template <int DH, bool SPLIT>
 struct DqShared { char sT[8][TILE64<DH>]; };      // K and V of stage after stage; SPLIT: of group 0, then of group 1
 constexpr int DQ_CHAIN = 5;                       // LDS fragments requested ahead of the products (4: the same within 0.3 %)
@@ -643,6 +655,8 @@ __device__ __forceinline__ void dq_tile(DqShared<DH, SPLIT>& sh, int q_block, in
   constexpr int QW = SPLIT ? TQ / 2 : TQ, NK = SPLIT ? TK / 2 : TK, NB = NK / 16;      // queries of the workgroup; keys of a tile, its 16-key blocks
   constexpr int STAGES = 4, TILE = NK * DH * 2;
   constexpr int LOADERS = SPLIT ? AT_THREADS / 2 : AT_THREADS, LOADS = NK * DH / 8 / LOADERS;      // threads that load a tile, 16-byte loads of each
+  // Which slot a step's addresses and loads lie in (see above)
+  constexpr bool MOVE_LATE = DH == 128, LOAD_LATE = SPLIT && DH == 64;
 
   const int q0 = q_block * QW, kvh = h / (Hq / Hkv);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), grp = wave >> 2, lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
@@ -694,12 +708,26 @@ __device__ __forceinline__ void dq_tile(DqShared<DH, SPLIT>& sh, int q_block, in
   constexpr int ROWS_J = LOADERS / (DH / 8);
   const int t_max = n_tiles - 1, row_last = n_total - 1 - t_max * NK;
   const uint32_t voff = pin(load_offset(tid, tid / (DH / 8)));
+  uint32_t voff_of[SPLIT ? LOADS : 1], voff_last[SPLIT ? LOADS : 1];      // SPLIT has registers for every load's offset, and no branch then
+#pragma unroll
+  for (int j = 0; j < (SPLIT ? LOADS : 0); ++j) {
+    const uint32_t row = tid / (DH / 8) + j * ROWS_J;
+    voff_of[j] = pin(load_offset(tid, row));
+    voff_last[j] = pin(load_offset(tid, min(row, (uint32_t)row_last)));
+  }
   const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_k + (uint32_t)(tid & ~63) * 16u), tile_bytes = (uint32_t)(NK * kv_stride * 2);
   auto issue = [&](int i) __attribute__((always_inline)) {
     const int t = min(tile_of(i), t_max);
     const char *ks = (const char*)kbase + (uint64_t)tile_bytes * (uint32_t)t, *vs = (const char*)vbase + (uint64_t)tile_bytes * (uint32_t)t;
     const uint32_t to = dst + (uint32_t)(i % STAGES) * STAGE;
-    if (t < t_max || row_last >= NK - 1) {
+    if constexpr (SPLIT) {
+#pragma unroll
+      for (int j = 0; j < LOADS; ++j) {
+        const uint32_t off = t == t_max ? voff_last[j] : voff_of[j];
+        dma16(ks, off, to + (uint32_t)(j * LOADERS * 16));
+        dma16(vs, off, to + (uint32_t)(TILE + j * LOADERS * 16));
+      }
+    } else if (t < t_max || row_last >= NK - 1) {
 #pragma unroll
       for (int j = 0; j < LOADS; ++j) {
         const int64_t rows = (int64_t)j * ROWS_J * kv_stride * 2;
@@ -726,8 +754,18 @@ __device__ __forceinline__ void dq_tile(DqShared<DH, SPLIT>& sh, int q_block, in
 #pragma unroll
   for (int kk = 0; kk < KS; ++kk) fr[kk] = pin(lds_k + frag16_rows<DH>(kk) + (uint32_t)(act0 % STAGES) * STAGE);
 #pragma unroll
-  for (int d = 0; d < DB; ++d) ft[d] = pin(lds_k + frag16_tr<DH>(d) + (uint32_t)(act0 % STAGES) * STAGE);
+  for (int d = 0; d < DB; ++d) ft[d] = pin(lds_k + frag16_tr<DH>(d) + (uint32_t)((act0 + (MOVE_LATE ? STAGES - 1 : 0)) % STAGES) * STAGE);
   auto to_next = [&](int i) { return i % STAGES == STAGES - 1 ? (uint32_t)-(int)((STAGES - 1) * STAGE) : STAGE; };      // from the stage of tile i
+  auto move_rows = [&](int i) __attribute__((always_inline)) {
+    const uint32_t move = to_next(i);
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) fr[kk] = pin(fr[kk] + move);
+  };
+  auto move_tr = [&](int i) __attribute__((always_inline)) {
+    const uint32_t move = to_next(i);
+#pragma unroll
+    for (int d = 0; d < DB; ++d) ft[d] = pin(ft[d] + move);
+  };
 
   struct Scores { f32x4 s[2][NB], dp[2][NB]; };        // S^T, dP^T [query block][16 keys]
   struct Operand { bf16x8 w[TERMS<DH>][2][NB / 2]; };  // dS^T: [term][query block][k32 step]
@@ -747,9 +785,7 @@ __device__ __forceinline__ void dq_tile(DqShared<DH, SPLIT>& sh, int q_block, in
 #pragma unroll
             for (int t = 0; t < TERMS<DH>; ++t) acc[b][n % DB] = MFMA16(f, ds.w[t][b][n / DB], acc[b][n % DB]);
         });
-    const uint32_t move = to_next(i);
-#pragma unroll
-    for (int d = 0; d < DB; ++d) ft[d] = pin(ft[d] + move);
+    if (!MOVE_LATE) move_tr(i);
   };
   auto first = [&](Scores& x, int i) __attribute__((always_inline)) {
 #pragma unroll
@@ -765,9 +801,7 @@ __device__ __forceinline__ void dq_tile(DqShared<DH, SPLIT>& sh, int q_block, in
           for (int b = 0; b < 2; ++b)
             if (kb < NB) x.s[b][kb] = MFMA16(f, bq[b][kk], x.s[b][kb]); else x.dp[b][kb - NB] = MFMA16(f, bdo[b][kk], x.dp[b][kb - NB]);
         });
-    const uint32_t move = to_next(i);
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) fr[kk] = pin(fr[kk] + move);
+    if (!MOVE_LATE) move_rows(i);
   };
   auto vector = [&](Scores& x, Operand& ds, int i) __attribute__((always_inline)) {
     const int k0 = tile_of(i) * NK;
@@ -791,13 +825,22 @@ __device__ __forceinline__ void dq_tile(DqShared<DH, SPLIT>& sh, int q_block, in
 #pragma unroll
       for (int ks = 0; ks < NB / 2; ++ks) {
         __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
+        auto grad = [&](int e) __attribute__((always_inline)) {      // dS^T (the factor `scale` is applied at the end)
           const int kb = 2 * ks + (e >> 2), r = e & 3;
           const float p = exp_of<DH>(x.s[b][kb][r], scale, sl, -lse2[b]);
-          const float y = p * (x.dp[b][kb][r] - dlt[b]);                          // dS^T (the factor `scale` is applied at the end)
-          ds.w[0][b][ks][e] = (bf16_t)y;
-          if (TERMS<DH> == 2) ds.w[TERMS<DH> - 1][b][ks][e] = (bf16_t)(y - (float)ds.w[0][b][ks][e]);
+          return p * (x.dp[b][kb][r] - dlt[b]);
+        };
+        if constexpr (TERMS<DH> == 1) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) ds.w[0][b][ks][e] = (bf16_t)grad(e);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; e += 2) {
+            const f32x2 y = {grad(e), grad(e + 1)};
+            const bf16x2 w0 = round2(y), w1 = round2(rest2(y, w0));
+#pragma unroll
+            for (int u = 0; u < 2; ++u) { ds.w[0][b][ks][e + u] = w0[u]; ds.w[1][b][ks][e + u] = w1[u]; }
+          }
         }
       }
     __builtin_amdgcn_sched_barrier(0);
@@ -813,12 +856,12 @@ __device__ __forceinline__ void dq_tile(DqShared<DH, SPLIT>& sh, int q_block, in
     const int ahead = SPLIT || late ? 3 : 2;
     auto wait_late = [&]() __attribute__((always_inline)) { if (late) AT_WAIT_VM(PAIR); };
     auto wait_early = [&]() __attribute__((always_inline)) {
-      if (SPLIT) AT_WAIT_VM(2 * PAIR);
+      if (SPLIT) AT_WAIT_VM((LOAD_LATE ? 1 : 2) * PAIR);
       else if (!late) AT_WAIT_VM(PAIR);
     };
     for (int j = 0; j < ahead; ++j) issue(j);
-    if (late) AT_WAIT_VM(2 * PAIR);
-    wait_early();
+    if (SPLIT || late) AT_WAIT_VM(2 * PAIR);
+    else AT_WAIT_VM(PAIR);
     AT_SLOT_BARRIER();
     if (grp == 1) AT_SLOT_BARRIER();
     int i = 0;
@@ -826,11 +869,12 @@ __device__ __forceinline__ void dq_tile(DqShared<DH, SPLIT>& sh, int q_block, in
       __builtin_amdgcn_s_setprio(0);
       wait_late();
       AT_SLOT_BARRIER();
-      issue(i + ahead);
+      if (!LOAD_LATE) issue(i + ahead);
     };
     auto into_multiply = [&]() __attribute__((always_inline)) {
       wait_early();
       AT_SLOT_BARRIER();
+      if (LOAD_LATE) issue(i + ahead);      // (the stage of tile i - 1, whose K every wave of the group has read by the barrier before)
       ++i;
     };
     auto skip = [&]() __attribute__((always_inline)) { into_vector(); into_multiply(); };      // a tile that no query of the wave sees
@@ -842,6 +886,7 @@ __device__ __forceinline__ void dq_tile(DqShared<DH, SPLIT>& sh, int q_block, in
         Operand ds;
         first(x, i);
         into_vector();
+        if (MOVE_LATE) { move_rows(i); move_tr(i + STAGES - 1); }
         vector(x, ds, i);
         into_multiply();
         __builtin_amdgcn_s_setprio(1);
@@ -1107,13 +1152,19 @@ __device__ __forceinline__ void dkv_block(DkvShared<DH>& sh, int key_block, int 
       for (int kk = 0; kk < KS; ++kk) fr[kk] = pin(fr[kk] + move);
     };
     auto terms = [&](int b, int ks) __attribute__((always_inline)) {      // P resp. dS as operands of the second product
+      auto value = [&](int e) __attribute__((always_inline)) { return t[b][2 * ks + (e >> 2)][e & 3]; };
+      if constexpr (NT == 1) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float x = t[b][2 * ks + (e >> 2)][e & 3];
-        w[0][b][ks][e] = (bf16_t)x;
-        if constexpr (NT == 3) {
-          w[1][b][ks][e] = (bf16_t)(x - (float)w[0][b][ks][e]);
-          w[2][b][ks][e] = (bf16_t)((x - (float)w[0][b][ks][e]) - (float)w[1][b][ks][e]);
+        for (int e = 0; e < 8; ++e) w[0][b][ks][e] = (bf16_t)value(e);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {
+          const f32x2 x = {value(e), value(e + 1)};
+          const bf16x2 w0 = round2(x);
+          const f32x2 r0 = rest2(x, w0);
+          const bf16x2 w1 = round2(r0), w2 = round2(rest2(r0, w1));
+#pragma unroll
+          for (int u = 0; u < 2; ++u) { w[0][b][ks][e + u] = w0[u]; w[1][b][ks][e + u] = w1[u]; w[2][b][ks][e + u] = w2[u]; }
         }
       }
     };
