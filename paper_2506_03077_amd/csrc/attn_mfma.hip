@@ -35,6 +35,7 @@
 //            added to the fp32 prefix accumulators (every element has one owner, or
 //            its parts are summed in a fixed order: no atomics, reproducible).
 #include "launch.h"
+#include "attn_plan.h"
 #include "device.h"
 
 #include <type_traits>
@@ -55,10 +56,9 @@ constexpr int TK = ATTN_TILE_K;          // 64 keys per step (fwd, dQ)
 constexpr int KV_TILE = ATTN_KV_TILE;    // keys per workgroup (dK/dV): 4 key blocks x 2 roles = 8 waves
 constexpr int KV_THREADS = 512;
 constexpr int QT = ATTN_KV_QUERIES;      // queries per step (dK/dV)
-// Workgroups of a backward that runs as one launch (four rounds of the chip; six behind a prefix), unless dK/dV alone is two or more whole rounds and dQ less than
-// one, where neither can fill what the other leaves.  Whole backward in one launch / in two: up to 1024 workgroups 0.52-1.01 (mean 0.83); behind prefixes 1128 + 256
-// 0.97, 1024 + 256 0.985, 692 + 224 and 442 + 448 1.00, the passes of a 32k layer at 7B widths, 640 to 1024 + 448, 0.91 to 0.99 (the layer 67.9 -> 67.2 ms); 1024 +
-// 224 1.004; beyond, 2008 + 256, 1.004.  (With dQ first, see backward_dh, as many as there are.)
+// Workgroups of a backward that runs as one launch (four rounds of the chip; six behind a prefix), which fills what dQ's last workgroups leave.  dQ and dK/dV in
+// one launch / in two: 238 sizes of up to 1024 workgroups 0.59-1.00 (mean 0.75), 19 of up to 1536 0.72-1.01 (0.91), 13 beyond 0.88-1.01 (0.96).  With dQ first, behind a
+// prefix, there is no limit: 164 sizes 0.56-0.99 (0.72).
 constexpr int MERGED_MAX = 1024;
 constexpr int MERGED_MAX_PREFIX = 1536;
 constexpr float LOG2E = 1.4426950408889634f;
@@ -982,7 +982,6 @@ __global__ __launch_bounds__(AT_THREADS) void attn_bwd_dq_mfma_k(const bf16_t* _
 // workgroups share a key block, each with all scores and half of the second product.  Whole backward, without / with a break | one share, dQ
 // apart | with room, 28 / 4 heads: 512 queries from 0 228 / 123 | 143 | 41 us, 2048 from 0 401 / 357 | 459 | 177; 512 from 2560 (96 blocks) 135 /
 // 124 | 184 | 123, from 2816 (104 blocks, whose 208 workgroups leave dQ too few CUs) 136 / 152 | 188 | 127, from 3500 145 / 198 | 205 | 146.
-constexpr int IN_TURN_BLOCKS = 96;       // key blocks times K/V heads up to which shares are taken without a break
 constexpr int KV_STAGES = 4;
 constexpr int CHAIN = 6;                 // LDS fragments requested ahead of the products (dK/dV)
 
@@ -1334,24 +1333,22 @@ __global__ __launch_bounds__(KV_THREADS) void attn_bwd_dkv_mfma_k(const bf16_t* 
 }
 
 // dK/dV and dQ in one launch, the longer workgroups first: for chunks that are a few rounds of the chip, where each
-// launch on its own leaves CUs idle at its end (777 windowed queries, 32 / 8 heads: 76 + 35 -> 102 us, the whole call 154 -> 141; what
-// a chunk of many rounds gains stands at MERGED_MAX).
+// launch on its own leaves CUs idle at its end (AttnBackwardPlan).
 template <int DH, bool SPLIT, bool IN_TURN>
 __device__ __forceinline__ void bwd_block(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
                                           const bf16_t* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ lse2,
                                           const float* __restrict__ delta, bf16_t* __restrict__ dq, float* __restrict__ dk, float* __restrict__ dv,
                                           int Hq, int Hkv, int q_start, int c, float scale, const float2* __restrict__ rope, int window,
-                                          const AttnSeqs& seqs, int key_block0, int key_blocks, int slices, float* __restrict__ part, int q_blocks, bool dq_first) {
+                                          const AttnSeqs& seqs, int key_block0, int key_blocks, int slices, float* __restrict__ part, int q_blocks, bool dq_first, bool side_by_side) {
   static_assert(AT_THREADS == KV_THREADS, "one workgroup shape");
   __shared__ __attribute__((aligned(1024))) union { DkvShared<DH> dkv; DqShared<DH, SPLIT> dq; } sh;
   const int kv_heads = Hkv * seqs.n, heads = Hq * seqs.n, n_dkv = key_blocks * kv_heads * (IN_TURN ? 2 : part ? slices : 1), n_dq = q_blocks * heads;
   const int b = dq_first ? ((int)blockIdx.x < n_dq ? (int)blockIdx.x + n_dkv : (int)blockIdx.x - n_dq) : (int)blockIdx.x;
   if (b < n_dkv) {
-    // The key blocks that most queries see first, all their workgroups side by side.  Workgroup b runs on XCD b % 8: with the key blocks side by side an
-    // XCD had the same few of them, up to 2.4 times the work of another where a chunk starts at 0 (2048 queries from 0, 28 / 4 heads 182 -> 133 us, from 2048
-    // 344 -> 328; 32 / 8 heads 385 -> 352 from 0, 790 -> 769 from 6144; launches of their own, with many key blocks, gain nothing).
-    const int per = n_dkv / key_blocks, r = b % per;
-    dkv_block<DH, IN_TURN>(sh.dkv, b / per, r % kv_heads, r / kv_heads, q, k, v, d_o, lse2, delta, dk, dv, Hq, Hkv, q_start, c, scale, window, seqs,
+    // The key blocks that most queries see first (AttnBackwardPlan: side_by_side)
+    const int of = side_by_side ? key_blocks : n_dkv / key_blocks, slow = __builtin_amdgcn_readfirstlane(b / of), fast = b - slow * of;
+    const int r = side_by_side ? slow : fast;
+    dkv_block<DH, IN_TURN>(sh.dkv, side_by_side ? fast : slow, r % kv_heads, r / kv_heads, q, k, v, d_o, lse2, delta, dk, dv, Hq, Hkv, q_start, c, scale, window, seqs,
                            key_block0, slices, part);
   } else {
     const int i = b - n_dkv;
@@ -1363,8 +1360,8 @@ __device__ __forceinline__ void bwd_block(const bf16_t* __restrict__ q, const bf
 #define BWD_PARAMS const bf16_t *__restrict__ q, const bf16_t *__restrict__ k, const bf16_t *__restrict__ v, const bf16_t *__restrict__ d_o, \
                    const float *__restrict__ lse, const float *__restrict__ lse2, const float *__restrict__ delta, bf16_t *__restrict__ dq, \
                    float *__restrict__ dk, float *__restrict__ dv, int Hq, int Hkv, int q_start, int c, float scale, \
-                   const float2 *__restrict__ rope, int window, const AttnSeqs seqs, int key_block0, int key_blocks, int slices, float *__restrict__ part, int q_blocks, bool dq_first
-#define BWD_ARGS q, k, v, d_o, lse, lse2, delta, dq, dk, dv, Hq, Hkv, q_start, c, scale, rope, window, seqs, key_block0, key_blocks, slices, part, q_blocks, dq_first
+                   const float2 *__restrict__ rope, int window, const AttnSeqs seqs, int key_block0, int key_blocks, int slices, float *__restrict__ part, int q_blocks, bool dq_first, bool side_by_side
+#define BWD_ARGS q, k, v, d_o, lse, lse2, delta, dq, dk, dv, Hq, Hkv, q_start, c, scale, rope, window, seqs, key_block0, key_blocks, slices, part, q_blocks, dq_first, side_by_side
 template <int DH, bool SPLIT> __global__ __launch_bounds__(AT_THREADS) void attn_bwd_mfma_k(BWD_PARAMS) { bwd_block<DH, SPLIT, false>(BWD_ARGS); }
 template <int DH, bool SPLIT> __global__ __launch_bounds__(AT_THREADS) void attn_bwd_in_turn_k(BWD_PARAMS) { bwd_block<DH, SPLIT, true>(BWD_ARGS); }
 #undef BWD_PARAMS
@@ -1454,50 +1451,6 @@ bool attn_mfma_aligned(const AttnArgs& a, bool backward) {
 // tokens and 16 / 4 heads of 64 a stack of two layers 2290 -> 2130 us.
 bool attn_sequences_fit(const AttnArgs& a) { return a.batch <= ATTN_MAX_SEQS && a.q_start == 0; }
 
-// Time of a launch in key steps: its query tiles, those with the most keys first, dealt to 256 CUs as they become free.  A tile takes a step for every `keys`
-// keys that it sees and six more for its start and end.  More than eight rounds: their mean.
-static double launch_steps(const AttnArgs& a, int tile, int keys) {
-  const int64_t heads = (int64_t)a.Hq * a.batch, rows = cdiv(a.q_len, tile);
-  auto steps_of = [&](int64_t row) {
-    const int64_t first_q = a.q_start + row * tile, last = std::min<int64_t>(a.q_start + a.q_len, first_q + tile);
-    const int64_t first = std::max<int64_t>(a.kv_first, a.window > 0 ? first_q - a.window + 1 : 0);
-    return cdiv(std::max<int64_t>(last - first, 0), keys) + 6;
-  };
-  if (rows * heads > 8 * 256) {
-    double sum = 0.0;
-    for (int64_t row = 0; row < rows; ++row) sum += (double)steps_of(row) * (double)heads;
-    return sum / 256.0;
-  }
-  struct Free { int64_t at; int n; } cus[258];      // CUs by the time they become free, the earliest first: at most 256 different times and a new one
-  int n_times = 1;
-  int64_t end = 0;
-  cus[0] = {0, 256};
-  for (int64_t row = rows - 1; row >= 0; --row) {
-    const int64_t len = steps_of(row);
-    for (int64_t left = heads; left > 0;) {
-      const int take = (int)std::min<int64_t>(cus[0].n, left);
-      const int64_t at = cus[0].at + len;
-      left -= take;
-      if ((cus[0].n -= take) == 0) std::copy(cus + 1, cus + n_times--, cus);
-      int i = n_times;
-      while (i > 0 && cus[i - 1].at > at) --i;
-      if (i > 0 && cus[i - 1].at == at) cus[i - 1].n += take;
-      else {
-        std::copy_backward(cus + i, cus + n_times, cus + n_times + 1);
-        cus[i] = {at, take};
-        ++n_times;
-      }
-      end = std::max(end, at);
-    }
-  }
-  return (double)end;
-}
-// Query tiles of 128, whose two wave groups take even and odd key tiles, or of 256.  A step of 128 keys costs a half tile `cost` times what one of 64 costs a whole
-// one: forward 2.1 against 1.95 us; dQ, whose half tiles have 32 keys, more.  Whole / half tiles, measured, forward of 2048 queries, 28 heads, from 0 73 / 62
-// us (whole: as long as the longest tile), from 2048 132 / 123, 4096 from 4096 403 / 437; four sequences of 640 tokens 52 / 59, with the backward 81 / 85; 2048
-// queries, 32 heads: backward from 0 352 / 362, from 4096 600 / 580, from 6144 768 / 789.
-constexpr double HALF_STEP_FWD = 1.08, HALF_STEP_DQ = 1.15;
-static bool half_tiles_faster(const AttnArgs& a, double cost) { return cost * launch_steps(a, TQ / 2, 2 * TK) < launch_steps(a, TQ, TK); }
 static AttnSeqs sequences(const AttnArgs& a) {
   AttnSeqs s{};
   s.n = a.batch;
@@ -1512,7 +1465,7 @@ static hipError_t forward_dh(const AttnArgs& a, hipStream_t st) {
     kernel<<<(unsigned)n, AT_THREADS, 0, st>>>((bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v, (bf16_t*)a.o, a.lse, a.Hq, a.Hkv,
                                                a.q_start, a.q_len, a.scale, a.rope_q, a.window, sequences(a));
   };
-  if (half_tiles_faster(a, HALF_STEP_FWD)) launch(attn_fwd_mfma_k<DH, true>, halves);
+  if (attn_half_tiles_faster(a, ATTN_HALF_STEP_FWD)) launch(attn_fwd_mfma_k<DH, true>, halves);
   else launch(attn_fwd_mfma_k<DH, false>, full);
   return hipGetLastError();
 }
@@ -1525,50 +1478,33 @@ static hipError_t backward_dh(const AttnArgs& a, hipStream_t st) {
   const AttnSeqs seqs = sequences(a);
   attn_delta_mfma_k<DH><<<dim3((unsigned)cdiv(pairs, 256 / (DH / 8)), a.batch), 256, 0, st>>>((const bf16_t*)a.o, (const bf16_t*)a.d_o, a.lse, a.delta, a.Hq,
                                                                                                a.q_len);
-  // key blocks that no query of the chunk can see (before the padding ends, or older than the first query's window)
-  // are not launched: their dK/dV contribution is zero
-  const int kb0 = attn_first_key_block(a), kb1 = (int)cdiv(a.q_start + a.q_len, KV_TILE), key_blocks = std::max(0, kb1 - kb0);
+  const AttnBackwardPlan p = attn_backward_plan(a, MERGED_MAX, MERGED_MAX_PREFIX);
   const int slices = std::max(1, a.dkv_slices);
-  float* part = slices > 1 ? a.dkv_scratch : nullptr;
-  const bool halves = half_tiles_faster(a, HALF_STEP_DQ);
-  const int64_t blocks = (int64_t)key_blocks * a.Hkv * a.batch, q_blocks = cdiv(a.q_len, halves ? TQ / 2 : TQ), q_tiles = q_blocks * a.Hq * a.batch;
-  const bool in_turn = !part && slices > 1 && blocks <= IN_TURN_BLOCKS;      // two workgroups per key block
-  const int64_t n_dkv = blocks * (in_turn ? 2 : part ? slices : 1);
+  float* part = p.parts ? a.dkv_scratch : nullptr;
   const bf16_t *q = (const bf16_t*)a.q, *k = (const bf16_t*)a.k, *v = (const bf16_t*)a.v, *d_o = (const bf16_t*)a.d_o;
-  // dQ first in the one launch, which then has no limit, where its workgroups are the longer ones and leave a quarter of the CUs to dK/dV: last, they are a
-  // tail on a chip that is otherwise done.  Backward with forward, dQ last / first, from 16000 keys (512 queries, 32 / 8 heads) 742 / 655 us, 8000 (512, 32 / 32)
-  // 573 / 475 where dQ had been a launch of its own, 3000 (256, 28 / 4) 155 / 131, 30000 (512, 32 / 8) 1428 / 1208; slower at few sizes (640 from 8000, 32 / 8
-  // 429 / 439).  With more dQ workgroups their key tiles are shared in the L2 no better than the queries of dK/dV: 196 (896 from 20000, 28 / 4) 1120 / 1125, 224
-  // (1024 from 30720) 1797 / 1825.  The oldest key blocks of a window are seen by few queries, so dK/dV ends evenly: 36 steps against 32 215 / 224 last / first.
-  const int64_t first_visible = std::max<int64_t>(a.kv_first, a.window > 0 ? (int64_t)a.q_start - a.window + 1 : 0);
-  const int64_t dq_steps = cdiv(std::max<int64_t>((int64_t)a.q_start + a.q_len - first_visible, 0), halves ? 2 * TK : TK);
-  const int64_t seen_by = a.window > 0 ? std::min<int64_t>(a.q_len, (int64_t)a.window + KV_TILE) : a.q_len;
-  const int64_t dkv_steps = cdiv(seen_by, QT) * (a.Hq / a.Hkv) / (part ? slices : 1);
-  const bool dq_first = dq_steps > (a.window > 0 ? 2 : 1) * dkv_steps && q_tiles <= 192;
-  const bool nothing_to_fill = n_dkv >= 512 && n_dkv % 256 == 0 && q_tiles < 256;
-  if (n_dkv > 0 && (in_turn || (dq_first && a.q_start > 0) || (n_dkv + q_tiles <= (a.q_start > 0 ? MERGED_MAX_PREFIX : MERGED_MAX) && !nothing_to_fill))) {
+  if (p.one_launch) {
     auto launch = [&](auto kernel) {
-      kernel<<<(unsigned)(n_dkv + q_tiles), AT_THREADS, 0, st>>>(q, k, v, d_o, a.lse, lse2, a.delta, (bf16_t*)a.dq, a.dk, a.dv, a.Hq, a.Hkv, a.q_start,
-                                                                         a.q_len, a.scale, a.rope_q, a.window, seqs, kb0, key_blocks, slices, part,
-                                                                         (int)q_blocks, dq_first);
+      kernel<<<(unsigned)(p.n_dkv + p.n_dq), AT_THREADS, 0, st>>>(q, k, v, d_o, a.lse, lse2, a.delta, (bf16_t*)a.dq, a.dk, a.dv, a.Hq, a.Hkv, a.q_start,
+                                                                         a.q_len, a.scale, a.rope_q, a.window, seqs, p.key_block0, p.key_blocks, slices,
+                                                                         part, p.q_blocks, p.dq_first, p.side_by_side);
     };
-    if (in_turn && halves) launch(attn_bwd_in_turn_k<DH, true>);
-    else if (in_turn) launch(attn_bwd_in_turn_k<DH, false>);
-    else if (halves) launch(attn_bwd_mfma_k<DH, true>);
+    if (p.in_turn && p.halves) launch(attn_bwd_in_turn_k<DH, true>);
+    else if (p.in_turn) launch(attn_bwd_in_turn_k<DH, false>);
+    else if (p.halves) launch(attn_bwd_mfma_k<DH, true>);
     else launch(attn_bwd_mfma_k<DH, false>);
   } else {
     auto launch_dq = [&](auto kernel) {
-      kernel<<<(unsigned)q_tiles, AT_THREADS, 0, st>>>(q, k, v, d_o, a.lse, a.delta, (bf16_t*)a.dq, a.Hq, a.Hkv, a.q_start, a.q_len, a.scale,
-                                                                    a.rope_q, a.window, seqs, (int)q_blocks);
+      kernel<<<(unsigned)p.n_dq, AT_THREADS, 0, st>>>(q, k, v, d_o, a.lse, a.delta, (bf16_t*)a.dq, a.Hq, a.Hkv, a.q_start, a.q_len, a.scale,
+                                                                    a.rope_q, a.window, seqs, p.q_blocks);
     };
-    if (halves) launch_dq(attn_bwd_dq_mfma_k<DH, true>);
+    if (p.halves) launch_dq(attn_bwd_dq_mfma_k<DH, true>);
     else launch_dq(attn_bwd_dq_mfma_k<DH, false>);
-    if (n_dkv > 0)
-      attn_bwd_dkv_mfma_k<DH><<<dim3((unsigned)key_blocks, a.Hkv * a.batch, part ? (unsigned)slices : 1u), KV_THREADS, 0, st>>>(
-          q, k, v, d_o, lse2, a.delta, a.dk, a.dv, a.Hq, a.Hkv, a.q_start, a.q_len, a.scale, a.window, seqs, kb0, slices, part);
+    if (p.n_dkv > 0)
+      attn_bwd_dkv_mfma_k<DH><<<dim3((unsigned)p.key_blocks, a.Hkv * a.batch, part ? (unsigned)slices : 1u), KV_THREADS, 0, st>>>(
+          q, k, v, d_o, lse2, a.delta, a.dk, a.dv, a.Hq, a.Hkv, a.q_start, a.q_len, a.scale, a.window, seqs, p.key_block0, slices, part);
   }
   if (part) {
-    const int first = kb0 * KV_TILE;
+    const int first = p.key_block0 * KV_TILE;
     const int64_t pairs = (int64_t)(a.q_start + a.q_len - first) * a.Hkv * (DH / 8);
     attn_dkv_sum_k<DH><<<dim3((unsigned)cdiv(2 * pairs, 256), a.batch), 256, 0, st>>>(part, slices, pairs, first, a.Hkv, a.dk, a.dv, a.q_start, (bf16_t*)a.dkc, (bf16_t*)a.dvc,
                                                                        a.rope_k);
