@@ -1465,7 +1465,7 @@ static hipError_t forward_dh(const AttnArgs& a, hipStream_t st) {
     kernel<<<(unsigned)n, AT_THREADS, 0, st>>>((bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v, (bf16_t*)a.o, a.lse, a.Hq, a.Hkv,
                                                a.q_start, a.q_len, a.scale, a.rope_q, a.window, sequences(a));
   };
-  if (attn_half_tiles_faster(a, ATTN_HALF_STEP_FWD)) launch(attn_fwd_mfma_k<DH, true>, halves);
+  if (attn_half_tiles_faster(a, attn_half_step_forward(DH))) launch(attn_fwd_mfma_k<DH, true>, halves);
   else launch(attn_fwd_mfma_k<DH, false>, full);
   return hipGetLastError();
 }

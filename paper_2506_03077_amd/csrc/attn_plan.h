@@ -46,11 +46,12 @@ inline double attn_launch_steps(const AttnArgs& a, int tile, int keys) {
   return (double)end;
 }
 // Query tiles of 128, whose two wave groups take even and odd key tiles, or of 256.  A step of 128 keys costs a half tile `cost` times what one of 64 costs a whole
-// one: forward 2.1 against 1.95 us; dQ, whose half tiles have 32 keys, more.  Whole / half tiles, measured, forward of 2048 queries, 28 heads, from 0 73 / 62
-// us (whole: as long as the longest tile), from 2048 132 / 123, 4096 from 4096 403 / 437; four sequences of 640 tokens 52 / 59, with the backward 81 / 85; 2048
-// queries, 32 heads: backward from 0 352 / 362, from 4096 600 / 580, from 6144 768 / 789.
+// one.  Forward, heads of 128: 2.1 against 1.95 us; heads of 64, where the vector work of 128 keys is the longer part, 0.94 times (2398 queries from 0, 32 / 8
+// heads, whole / half tiles 75 / 66 us, 3302 under a window of 124, 28 / 4, 36 / 32; 3613 behind 927, 32 / 8, 175 / 187).  dQ, whose half tiles have 32 keys, more.  Whole / half tiles,
+// measured, forward of 2048 queries, 28 heads of 128, from 0 73 / 62 us (whole: as long as the longest tile), from 2048 132 / 123, 4096 from 4096 403 / 437; four
+// sequences of 640 tokens 52 / 59, with the backward 81 / 85; 2048 queries, 32 heads: backward from 0 352 / 362, from 4096 600 / 580, from 6144 768 / 789.
 constexpr double ATTN_HALF_STEP_DQ = 1.15;
-constexpr double ATTN_HALF_STEP_FWD = 1.08;
+inline double attn_half_step_forward(int dh) { return dh == 64 ? 0.94 : 1.08; }
 inline bool attn_half_tiles_faster(const AttnArgs& a, double cost) {
   return cost * attn_launch_steps(a, ATTN_TILE_Q / 2, 2 * ATTN_TILE_K) < attn_launch_steps(a, ATTN_TILE_Q, ATTN_TILE_K);
 }

@@ -18,7 +18,7 @@ int main() {
     const sbp::AttnBackwardPlan p = sbp::attn_backward_plan(a, most, most_prefix);
     std::printf("{\"forward_halves\": %d, \"halves\": %d, \"key_blocks\": %d, \"slices\": %d, \"parts\": %d, \"in_turn\": %d, \"n_dkv\": %lld, \"n_dq\": %lld, \"one_launch\": %d, "
                 "\"dq_first\": %d, \"side_by_side\": %d}\n",
-                sbp::attn_half_tiles_faster(a, sbp::ATTN_HALF_STEP_FWD), p.halves, p.key_blocks, a.dkv_slices, p.parts, p.in_turn, (long long)p.n_dkv, (long long)p.n_dq, p.one_launch,
+                sbp::attn_half_tiles_faster(a, sbp::attn_half_step_forward(a.dh)), p.halves, p.key_blocks, a.dkv_slices, p.parts, p.in_turn, (long long)p.n_dkv, (long long)p.n_dq, p.one_launch,
                 p.dq_first, p.side_by_side);
   }
   return 0;

@@ -60,3 +60,11 @@ def test_key_blocks_lie_side_by_side_where_there_is_nothing_to_even_out(plan):
     assert not plan(28, 4, 28544, 4224)["side_by_side"]                    # ... one more
     assert not plan(28, 4, 0, 2048)["side_by_side"]
     assert not plan(64, 32, 7000, 130)["side_by_side"]                     # dQ first
+
+
+def test_forward_tiles_of_64_wide_heads(plan):
+    """Half tiles cost these heads less than the wider ones: whole tiles only where they leave few CUs idle."""
+    for args in ((32, 8, 0, 2398, 2509), (28, 4, 9300, 3302, 124), (28, 4, 1852, 2767)):
+        assert plan(*args, dh=64)["forward_halves"], args
+    assert plan(32, 8, 0, 2398, 2509)["forward_halves"] == 0
+    assert not plan(32, 8, 927, 3613, dh=64)["forward_halves"]
