@@ -103,7 +103,8 @@ struct GenericSwiglu { void *gate, *up, *act; };
 // (As a pass over K: one launch more of a chain of 24, 96 us against 89.5 for a 256-token fp32 layer with its head.)
 struct GenericRope { const float2* tab; int half, period, problem; };
 // Launch bounds: 80 registers let three workgroups share a CU.  With 82, two: 1024 x 2816 with K = 8, 2816 tiles, 15.0 -> 19.5 us.  One problem is never rotated: the
-// angles' code alone takes those registers.
+// angles' code alone takes those registers.  (Long reductions over columns gain nothing from the third: dh with dW of a fp32 head, 2036 rows, 16000 x 512, two workgroups
+// 1017, three 1147 us, apart 1146; 1000 rows, 2000 x 256, whose 760 tiles are a round of three, the call 91 and 86.)
 template <typename TI, typename TO, int NP, int NS>
 __global__ __launch_bounds__(WAVES * 64, 6) void gemm_generic_k(const GenericArgs<NP, NS> ga, const GenericSwiglu sw, const GenericRope rope) {
   constexpr bool ROPE = !std::is_same_v<TI, bf16_t> && (NP == 2 || NP == 3);      // (K beside V, or beside q and V)

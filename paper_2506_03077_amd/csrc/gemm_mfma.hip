@@ -89,6 +89,7 @@ struct SwigluFuse { bf16_t* gate; bf16_t* up; bf16_t* act; };
 struct NumerFuse { const int32_t* targets; const int32_t* row_index; float* target_value; };
 // The reduction may come in several segments (operand pairs of the same shape and leading dimensions whose products
 // are summed into the same output tile): one accumulator, one epilogue.
+constexpr int64_t NUMERATORS_CACHED = (256 << 20) / 2;      // elements of C (bf16) that the memory-side cache holds
 constexpr int MAX_SEG = 8;
 struct KSegment {
   const bf16_t* A; const bf16_t* B;
@@ -546,12 +547,17 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
     __syncthreads();
     if constexpr (MODE == 7) {
       const int c16 = threadIdx.x & 31, col = n0 + c16 * 8;
+      // Past the caches, as for C += above, where the memory-side cache does not hold all of C for the pass that reads it next: 2048 rows of 152064 1627 -> 1605 us.
+      // Where it does, the pass finds it there, whole call, past / into the caches: 100352 columns, hidden 256, 100 rows (20 MB) 199 / 192 us, 1000 (200 MB) 447 / 425; 50256,
+      // hidden 1024, 1000 rows 500 / 490, 2048 (206 MB) 783 / 790; 151936, hidden 3584, 1000 (304 MB) 3706 / 3720.
+      const bool past_caches = (int64_t)M * ldc > NUMERATORS_CACHED;
 #pragma unroll
       for (int p = 0; p < 16; ++p) {
         const int row = p * 16 + (threadIdx.x >> 5);
         const i32x4 v = *(const i32x4*)(smem + row * 512 + ((c16 ^ (row & 15)) << 4));
         if (m0 + row < M && col < N) {
-          if (ldc % 8 == 0) __builtin_nontemporal_store(v, (i32x4*)(Cb + (int64_t)(m0 + row) * ldc + col));      // (as for C += above: 1627 -> 1605 us, 2048 rows)
+          if (ldc % 8 == 0 && past_caches) __builtin_nontemporal_store(v, (i32x4*)(Cb + (int64_t)(m0 + row) * ldc + col));
+          else if (ldc % 8 == 0) *(i32x4*)(Cb + (int64_t)(m0 + row) * ldc + col) = v;
           else {                               // (rows that start between 16-byte boundaries: half of them at a time)
             typedef int i32x2 __attribute__((ext_vector_type(2)));
             *(i32x2*)(Cb + (int64_t)(m0 + row) * ldc + col) = i32x2{v[0], v[1]};
