@@ -18,6 +18,7 @@
 // of the first product takes element j of both operands' four at head_dim 16 d + 4 (l / 16) .. + 3; MFMA r of the second product takes
 // accumulator register r as its B operand, i.e. row 4 (l / 16) + r of the block as its reduction index.
 #include "launch.h"
+#include "attn_plan.h"
 #include "device.h"
 
 namespace sbp {
@@ -667,23 +668,15 @@ static hipError_t forward_t(const AttnArgs& a, hipStream_t st) {
   if (a.dh <= 64) narrow_heads(a.dh, go); else if (few_keys(a)) four_per_block(a.dh, go); else forward_long(a.dh, go);
   return hipGetLastError();
 }
-// dQ and dK/dV of heads of up to 64 elements in one launch: without a prefix, up to 1024 workgroups, or with few of dQ behind a long prefix, which come first as
-// the longer ones (so do they wherever a key block has fewer query blocks than the other way round).  Backward apart / in one, fp32, us: 256 queries from 0, 4 heads
-// of 16 10.9 / 6.6, 8 of 64 24.2 / 14.6, 16 of 64, 512 queries, 71.6 / 54.9; 2048 queries, 8 of 64 330 / 268, 16 of 32 297 / 228, bf16 4096, 8 of 16 336 / 262; 64 from
-// 3000, 2 of 16 30.2 / 25.2; 128 from 30000, 16 of 32 741 / 534.  Behind a prefix with more workgroups the loads of o, which dK/dV reads as well, outweigh it: 256 from
-// 8000, 16 of 64 442 / 464, 2048 from 8000 3785 / 3840.
-constexpr int64_t ONE_LAUNCH_MAX = 1024, ONE_LAUNCH_DQ = 192;
 template <typename T>
 static hipError_t backward_t(const AttnArgs& a, hipStream_t st) {
   const AgShape s = shape_of(a);
   const dim3 gq((unsigned)cdiv(a.q_len, 16), (unsigned)a.Hq), gk((unsigned)cdiv((int64_t)a.q_start + a.q_len, 16), (unsigned)a.Hkv);
-  const int64_t n_dkv = (int64_t)gk.x * gk.y, n_dq = (int64_t)gq.x * gq.y, n = n_dkv + n_dq;
-  // (dq may take o's place: dK/dV then has to be a launch that does not read o)
-  const bool dq_first = (int64_t)gk.x > (int64_t)gq.x * (a.Hq / a.Hkv);
-  if (a.dh <= 64 && a.dq != a.o && n <= INT32_MAX && (a.q_start == 0 || n <= ONE_LAUNCH_MAX || (dq_first && n_dq <= ONE_LAUNCH_DQ))) {
+  const AttnNarrowPlan p = attn_narrow_plan(a);
+  if (p.one_launch) {
     narrow_heads(a.dh, [&](auto db, auto, auto) {
-      attn_bwd_narrow_k<T, decltype(db)::value><<<(unsigned)n, 512, 0, st>>>((const T*)a.q, (const T*)a.k, (const T*)a.v, (const T*)a.o, (const T*)a.d_o, a.lse, (T*)a.dq,
-                                                                            a.dk, a.dv, s, (T*)a.dkc, (T*)a.dvc, a.rope_q, a.rope_k, (int)(dq_first ? n_dq : n_dkv), dq_first);
+      attn_bwd_narrow_k<T, decltype(db)::value><<<(unsigned)(p.n_dkv + p.n_dq), 512, 0, st>>>((const T*)a.q, (const T*)a.k, (const T*)a.v, (const T*)a.o, (const T*)a.d_o, a.lse, (T*)a.dq,
+                                                                            a.dk, a.dv, s, (T*)a.dkc, (T*)a.dvc, a.rope_q, a.rope_k, (int)(p.dq_first ? p.n_dq : p.n_dkv), p.dq_first);
     });
     return hipGetLastError();
   }

@@ -104,4 +104,24 @@ inline AttnBackwardPlan attn_backward_plan(const AttnArgs& a, int most, int most
   return p;
 }
 
+// The shape-agnostic kernels.
+// dQ and dK/dV of heads of up to 64 elements in one launch: without a prefix, up to 1024 workgroups, or with few of dQ behind a long prefix, which come first as
+// the longer ones (so do they wherever a key block has fewer query blocks than the other way round).  Backward apart / in one, fp32, us: 256 queries from 0, 4 heads
+// of 16 10.9 / 6.6, 8 of 64 24.2 / 14.6, 16 of 64, 512 queries, 71.6 / 54.9; 2048 queries, 8 of 64 330 / 268, 16 of 32 297 / 228, bf16 4096, 8 of 16 336 / 262; 64 from
+// 3000, 2 of 16 30.2 / 25.2; 128 from 30000, 16 of 32 741 / 534.  Behind a prefix with more workgroups the loads of o, which dK/dV reads as well, outweigh it: 256 from
+// 8000, 16 of 64 442 / 464, 2048 from 8000 3785 / 3840.
+constexpr int64_t ATTN_NARROW_MAX = 1024, ATTN_NARROW_DQ = 192;
+struct AttnNarrowPlan { bool one_launch, dq_first; int64_t n_dkv, n_dq; };
+inline AttnNarrowPlan attn_narrow_plan(const AttnArgs& a) {
+  const int64_t q_blocks = cdiv(a.q_len, 16), key_blocks = cdiv((int64_t)a.q_start + a.q_len, 16);
+  AttnNarrowPlan p{};
+  p.n_dkv = key_blocks * a.Hkv;
+  p.n_dq = q_blocks * a.Hq;
+  p.dq_first = key_blocks > q_blocks * (a.Hq / a.Hkv);
+  const int64_t n = p.n_dkv + p.n_dq;
+  // (dq may take o's place: dK/dV then has to be a launch that does not read o)
+  p.one_launch = a.dh <= 64 && a.dq != a.o && n <= INT32_MAX && (a.q_start == 0 || n <= ATTN_NARROW_MAX || (p.dq_first && p.n_dq <= ATTN_NARROW_DQ));
+  return p;
+}
+
 }  // namespace sbp

@@ -7,6 +7,10 @@ import subprocess
 
 import pytest
 
+import test_gpu_attn_order
+import test_gpu_attn_tile_choice as tile_choice
+import test_gpu_generic_attn_one_launch as narrow
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SRC = os.path.join(ROOT, "tests", "host_sanitize")
 CSRC = os.path.join(ROOT, "paper_2506_03077_amd", "csrc")
@@ -68,3 +72,42 @@ def test_forward_tiles_of_64_wide_heads(plan):
         assert plan(*args, dh=64)["forward_halves"], args
     assert plan(32, 8, 0, 2398, 2509)["forward_halves"] == 0
     assert not plan(32, 8, 927, 3613, dh=64)["forward_halves"]
+
+
+def _parameters(test, names):
+    """The values a GPU test is parametrised over."""
+    return next(m.args[1] for m in test.pytestmark if m.name == "parametrize" and m.args[0] == names)
+
+
+def test_calls_of_the_tile_tests(plan):
+    for args in tile_choice.WHOLE:
+        p = plan(*args)
+        assert not p["halves"] and not p["forward_halves"], args
+        assert not plan(*args, dh=64)["halves"], args
+    for args in tile_choice.HALF:
+        assert all(p["halves"] and p["forward_halves"] for p in (plan(*args), plan(*args, dh=64))), args
+    first, last = [plan(*a, dh=64) for a in tile_choice.DQ_FIRST], [plan(*a, dh=64) for a in tile_choice.DKV_FIRST]
+    assert all(p["one_launch"] and p["dq_first"] for p in first)
+    assert first[0]["n_dkv"] > 1024 and first[1]["n_dkv"] % 256 == 0
+    assert not any(p["dq_first"] for p in last)
+    assert last[0]["one_launch"] and last[0]["n_dkv"] > 1024 and not last[1]["one_launch"]
+
+
+def test_calls_of_the_order_tests(plan):
+    calls = _parameters(test_gpu_attn_order.test_a_short_chunk_behind_a_prefix, "hq,hkv,s,c,window,kv_first")
+    got = {c: [plan(*c, dh=dh) for dh in (128, 64)] for c in calls}
+    assert all(p["one_launch"] for ps in got.values() for p in ps)
+    last = {c for c, ps in got.items() if not all(p["dq_first"] for p in ps)}
+    assert last == {(32, 32, 4000, 3, 0, 3990), (24, 3, 2500, 1025, 0, 0)}
+    assert any(p["parts"] and p["dq_first"] for ps in got.values() for p in ps)
+    assert any(p["n_dkv"] + p["n_dq"] > 1536 and p["dq_first"] for ps in got.values() for p in ps)
+    in_turn = [plan(*c, room=0) for c in calls if c[3] < 200]
+    assert any(p["in_turn"] for p in in_turn) and any(p["in_turn"] and p["dq_first"] for p in in_turn)
+
+
+def test_calls_of_the_narrow_tests(plan):
+    calls = _parameters(narrow.test_backward, "dtype,hq,hkv,dh,s,c,window,kv_first")
+    got = [plan(hq, hkv, s, c, window, kv_first, dh=dh) for _, hq, hkv, dh, s, c, window, kv_first in calls]
+    kinds = [(p["narrow_one_launch"], p["narrow_dq_first"]) for p in got]
+    assert kinds == [(1, 0)] * 7 + [(1, 1)] * 4 + [(0, 1)], kinds
+    assert got[10]["narrow_n"] > 1024 and not any(p["narrow_in_place"] for p in got)

@@ -21,7 +21,12 @@ def test_both_sides_of_the_rule(dh, hq, hkv, s, c, window, kv_first):
     masked_attn_case("bf16", hq, hkv, dh, s, c, window, kv_first)
 
 
-# dK/dV and dQ of a chunk behind a prefix: more than 1024 workgroups in one launch, and apart where dK/dV is whole rounds and dQ less than one
-@pytest.mark.parametrize("hq,hkv,s,c", [(64, 32, 4000, 200), (32, 16, 3965, 130), (32, 32, 2000, 500)])
+# A chunk behind a prefix, dQ's workgroups first in one launch: more than 1024 workgroups, whole rounds of dK/dV, neither
+DQ_FIRST = [(64, 32, 4000, 200), (32, 16, 3965, 130), (32, 32, 2000, 500)]
+# ... dK/dV's first, 208 workgroups of dQ behind them: more than 1024 workgroups in one launch, more than 1536 apart
+DKV_FIRST = [(208, 26, 5000, 100), (208, 52, 5000, 100)]
+
+
+@pytest.mark.parametrize("hq,hkv,s,c", DQ_FIRST + DKV_FIRST)
 def test_backward_behind_a_prefix(hq, hkv, s, c):
     masked_attn_case("bf16", hq, hkv, 64, s, c, 0, 0)
