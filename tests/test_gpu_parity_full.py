@@ -6,7 +6,7 @@ The fp64 oracle cannot run a 32k-token layer (it is a plain full-sequence backpr
     oracle finishes in tens of seconds: 4608 tokens for the layer, in two passes of 2304 rows with one grouped launch
     of weight gradients, seven ragged ones and a single one (the benchmark's 32768 tokens take eight passes of 4096 rows, two a
     launch, which a test below holds against passes of other sizes); 8792 rows for the head at the real chunk size: four full
-    chunks and a ragged one, with the split-K factors, operand pairs and multi-segment weight-gradient passes of the benchmark;
+    chunks and a ragged one, with the split-K factors, operand pairs and weight-gradient passes over several chunks of the benchmark;
   * at the full 32k length, chunk attention is compared element by element against the oracle
     for one whole KV group (the oracle's cost there is small), and the layer / head are checked
     through properties that hold at any size (chunk-size invariance, exact zeros of ignored
@@ -67,8 +67,8 @@ _HEAD_REF = {}
 @pytest.mark.parametrize("dw_group_rows", [0, 8192])
 def test_head_full_vocab_vs_oracle(dw_group_rows):
     # V = 152064 at the bench's chunk of 2048 rows with 8792 active rows = four full chunks and a ragged fifth (600 rows).
-    # Default grouping: their weight gradient is ONE five-segment pass over dW; with 8192 rows per pass a four-segment pass
-    # and the ragged chunk as a pass of its own.  Every row of dh and every 256 x 256 tile of dW (8316 of them) is compared
+    # Default grouping: their weight gradient is ONE reduction over the rows of all five, its last round of tiles split; with
+    # 8192 rows per pass one over four chunks and the ragged chunk as a pass of its own.  Every row of dh and every 256 x 256 tile of dW (8316 of them) is compared
     # with the oracle.
     T, chunk = 8792, 2048
     cfg = synth.CONFIGS["lmhead"]
@@ -95,7 +95,7 @@ def test_head_full_vocab_vs_oracle(dw_group_rows):
 
 def test_head_full_vocab_with_prompt_mask_vs_oracle():
     # the same with the first quarter of the rows ignored (the LM-head workload of the shape list): the active rows are
-    # compacted, 2304 of them = one full chunk and a ragged one in ONE two-segment pass over dW
+    # compacted, 2304 of them = one full chunk and a ragged one in ONE pass over dW, a reduction over the rows of both
     T, chunk = 3072, 2048
     cfg = synth.CONFIGS["lmhead"]
     inp = synth.head_inputs(cfg, seed=1, seq_len=T)
