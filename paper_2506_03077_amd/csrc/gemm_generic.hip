@@ -102,12 +102,12 @@ struct GenericSwiglu { void *gate, *up, *act; };
 // tab (optional): the output of problem `problem` is rotated, heads of 2 * half columns, which divide a tile; the angles are fetched before the products.
 // (As a pass over K: one launch more of a chain of 24, 96 us against 89.5 for a 256-token fp32 layer with its head.)
 struct GenericRope { const float2* tab; int half, period, problem; };
-// Launch bounds: 80 registers let three workgroups share a CU.  With 82, two: 1024 x 2816 with K = 8, 2816 tiles, 15.0 -> 19.5 us.  One problem is never rotated: the
-// angles' code alone takes those registers.  (Long reductions over columns gain nothing from the third: dh with dW of a fp32 head, 2036 rows, 16000 x 512, two workgroups
-// 1017, three 1147 us, apart 1146; 1000 rows, 2000 x 256, whose 760 tiles are a round of three, the call 91 and 86.)
+// Launch bounds: 80 registers let three workgroups share a CU, and only the instance that rotates would take more, 82: with them in all fp32 instances of up to three
+// problems two workgroups shared one, and 1024 x 2816 with K = 8, 2816 tiles, took 19.5 us instead of 15.0; with the rotation's code in the smaller instances, but 80 registers,
+// the forward of 2 x 1133 rows at 264 / 2730 371 instead of 367 us, a head of 2036 rows, 16000 x 512, 1709 instead of 1674.
 template <typename TI, typename TO, int NP, int NS>
-__global__ __launch_bounds__(WAVES * 64, 6) void gemm_generic_k(const GenericArgs<NP, NS> ga, const GenericSwiglu sw, const GenericRope rope) {
-  constexpr bool ROPE = !std::is_same_v<TI, bf16_t> && (NP == 2 || NP == 3);      // (K beside V, or beside q and V)
+__global__ __launch_bounds__(WAVES * 64, (!std::is_same_v<TI, bf16_t> && NP == 3 ? 6 : 1)) void gemm_generic_k(const GenericArgs<NP, NS> ga, const GenericSwiglu sw, const GenericRope rope) {
+  constexpr bool ROPE = !std::is_same_v<TI, bf16_t> && NP == 3;      // (K beside V, or beside q and V)
   int pi = 0;
 #pragma unroll
   for (int i = 1; i < NP; ++i)
@@ -283,7 +283,7 @@ hipError_t gemm_generic(const GemmArgs* gs, int n, bool sum, hipStream_t st) {
 #define GG(TI, TO)                                                                                             \
   do {                                                                                                         \
     if (ga.n == 1 && n_seg == 1 && !rope.tab) go(gemm_generic_k<TI, TO, 1, 1>, GenericArgs<1, 1>{});                        \
-    else if (ga.n <= 2 && n_seg <= 3) go(gemm_generic_k<TI, TO, 2, 3>, GenericArgs<2, 3>{});                   \
+    else if (ga.n <= 2 && n_seg <= 3 && !rope.tab) go(gemm_generic_k<TI, TO, 2, 3>, GenericArgs<2, 3>{});                   \
     else if (ga.n <= 3 && n_seg <= 3) go(gemm_generic_k<TI, TO, 3, 3>, GenericArgs<3, 3>{});                   \
     else if (n_seg <= 8) go(gemm_generic_k<TI, TO, GENERIC_PROBLEMS, 8>, GenericArgs<GENERIC_PROBLEMS, 8>{});  \
     else if (n_seg <= 16) go(gemm_generic_k<TI, TO, GENERIC_PROBLEMS, 16>, GenericArgs<GENERIC_PROBLEMS, 16>{}); \
