@@ -81,8 +81,9 @@ __device__ __forceinline__ uint32_t frag_off_mnmaj(int col_base, int hi) {
 //       6 = C is not stored: the tile is the gradient wrt act = silu(gate) * up and the epilogue writes act, d gate, d up
 //       8 = C (bf16) receives silu(A B^T) * (A B2^T): 128 columns of each product per tile, in the halves of B
 //       7 = like 5, but C (bf16) receives exp(c - block max) instead of c, and the value of each row's target column is kept
-constexpr bool mode_accumulates(int mode) { return mode == 2 || mode == 4; }
-constexpr bool mode_splits(int mode) { return mode <= 2; }      // forms whose reduction may be split over workgroups
+//       9 = like 2, through the caches (weight-gradient form of few tiles)
+constexpr bool mode_accumulates(int mode) { return mode == 2 || mode == 4 || mode == 9; }
+constexpr bool mode_splits(int mode) { return mode <= 2 || mode == 9; }      // forms whose reduction may be split over workgroups
 // Floats of a partial tile: an output of fewer than 256 rows has partial tiles of as many (the scratch and its traffic shrink with it)
 __host__ __device__ __forceinline__ int partial_floats(int max_m) { return (max_m < BM ? max_m : BM) * BN; }
 struct SwigluFuse { bf16_t* gate; bf16_t* up; bf16_t* act; };
@@ -90,6 +91,10 @@ struct NumerFuse { const int32_t* targets; const int32_t* row_index; float* targ
 // The reduction may come in several segments (operand pairs of the same shape and leading dimensions whose products
 // are summed into the same output tile): one accumulator, one epilogue.
 constexpr int64_t NUMERATORS_CACHED = (256 << 20) / 2;      // elements of C (bf16) that the memory-side cache holds
+// Up to so many tiles C += goes through the caches: an XCD then has four of them at most, 2 MB of its 4 MB L2, and the next launch that adds to C may find it there.  Past /
+// through them, whole call, heads of 520 x 999, 12 tiles, 132 rows 60.8 / 59.1 us, a layer of 520 / 1378, products of 4 to 18 tiles, 264 / 259; of 5003 x 1024, 80 tiles, 118 / 126,
+// of 16000 x 256, 63 tiles, 98 / 100.
+constexpr int FEW_TILES = 32;
 constexpr int MAX_SEG = 8;
 struct KSegment {
   const bf16_t* A; const bf16_t* B;
@@ -410,7 +415,7 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
     }
     return;
   }
-  if constexpr (MODE == 2) {
+  if constexpr (MODE == 2 || MODE == 9) {
     // fp32 C += acc, half of the tile's rows at a time: a plain read-modify-write, every element has one owner per launch.  What bounds it is
     // the latency of the reads of C, not their rate: those of a half (16 accesses of 16 bytes per lane) all go out before the half is
     // staged, the second half's before the first is added.  Against eight at a time behind the staging: 18944 x 3584, K = 128 134 -> 103
@@ -432,7 +437,7 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
     auto fetch = [&](int ha) {
 #pragma unroll
       for (int p = 0; p < 16; ++p)
-        if (inside(ha, p)) old[ha][p] = __builtin_nontemporal_load(at(ha, p));
+        if (inside(ha, p)) old[ha][p] = MODE == 2 ? __builtin_nontemporal_load(at(ha, p)) : *at(ha, p);
     };
     fetch(0);
 #pragma unroll
@@ -455,7 +460,9 @@ __device__ __forceinline__ void gemm_tile(int n_segments, SegmentF segment, void
       for (int p = 0; p < 16; ++p) {
         const int row_l = p * 8 + r0;
         const f32x4 v = *(const f32x4*)(smem + row_l * 1024 + ((c4 ^ (row_l & 15)) << 4));
-        if (inside(ha, p)) __builtin_nontemporal_store(old[ha][p] + v, at(ha, p));
+        if (!inside(ha, p)) continue;
+        if (MODE == 2) __builtin_nontemporal_store(old[ha][p] + v, at(ha, p));
+        else *at(ha, p) = old[ha][p] + v;
       }
     }
     return;
@@ -1030,6 +1037,7 @@ hipError_t gemm_mfma(const GemmArgs& g, hipStream_t st) {
     else if (mode == 6) LAUNCH(false, false, 6);
     else if (g.ta && g.tb && mode == 4) LAUNCH(true, true, 4);
     else if (g.ta && g.tb) LAUNCH(true, true, 2);
+    else if (g.ta && mode == 2 && tiles_m * tiles_n <= FEW_TILES) LAUNCH(true, false, 9);
     else if (mode == 4) LAUNCH(true, false, 4);
     else if (mode == 1) LAUNCH_LAYOUT(1);
     else if (mode == 2) LAUNCH_LAYOUT(2);
