@@ -631,7 +631,7 @@ __global__ __launch_bounds__(AT_THREADS) void attn_fwd_mfma_k(bf16_t* q, const b
 // What bounds it: the clock that the power limit leaves.  The slots keep the matrix pipe busier than two stages behind one barrier per tile did, and the
 // clock falls by most of what that gives: backward and forward of the last 2048-query chunk of 32k, 28 heads, 3.68 -> 3.64 ms; a 32k layer at 7B widths
 // 69.5 -> 67.9; 777 windowed queries 141.5 -> 139.0 us.  Tiles of 32 keys without SPLIT: 3.66 ms, the layer 70.0 (a slot of 24 MFMAs does not cover its start).
-// 16x16x32 MFMAs take less of that power than 32x32x16 ones: the kernel itself on that chunk 1123 -> 1050 us (1002 to 1013 on other boxes since).
+// 16x16x32 MFMAs take less of that power than 32x32x16 ones: the kernel itself on that chunk 1123 -> 1050 us (1002 to 1013 on other cards since).
 // A wave's tiles are one loop without branches around the products, the stages moving with the addresses: with four steps unrolled, each skipping its products by a
 // branch, the accumulators of four registers are moved about and 130 registers spill (1925 us).
 // With few workgroups it is a step's instructions, slot by slot: the groups' slots are as long as the longer of the two, so what need not be in that one is in
@@ -972,7 +972,7 @@ __global__ __launch_bounds__(AT_THREADS) void attn_bwd_dq_mfma_k(const bf16_t* _
 // What bounds it: as in the forward kernel, vector work and MFMAs of a SIMD's two waves share the issue port, and the power limit leaves 2.0 GHz.  Last
 // 2048-query chunk of 32k, 28 / 4 heads: dQ + dK/dV 3.08 -> 2.95 ms, all of it here (about 1.85 -> 1.72), against one barrier per tile and each wave doing its
 // products and its vector work in any order; 1740 -> 1655 us with 16x16x32 MFMAs in place of 32x32x16, -> 1610 with a loop whose stages move with the
-// addresses in place of four steps unrolled (a quarter of the code); 1494 to 1518 us on other boxes since.  What parts of it cost cannot be told by leaving them out: other values
+// addresses in place of four steps unrolled (a quarter of the code); 1494 to 1518 us on other cards since.  What parts of it cost cannot be told by leaving them out: other values
 // are multiplied then, at another power (without exponentials 1406; the kernel on 32x32x16 MFMAs took 1745, 1630 with half of its LDS reads, 1705 without exponentials).
 // The loop walks the query tiles at or below the diagonal and, for each, the query heads of the group.
 //
